@@ -636,7 +636,7 @@ int run_resident(scd_ctx* c, int64_t n)
     a.w_target = c->hs.k + n;
     a.max_iters = c->hs.max_iters;
     a.max_spin = (int32_t)c->opt[SCD_OPT_MAX_SPIN];
-    a.poll_delay = (int32_t)c->opt[SCD_OPT_POLL_DELAY];
+    resident_poll_delays(c->dims, (int)c->opt[SCD_OPT_POLL_DELAY], &a.poll_delay, &a.poll_delay_v);
     a.seq_u = c->seq_u;
     a.seq_v = c->seq_v;
     a.xbuf = c->xbuf;

@@ -128,6 +128,7 @@ struct ResidentArgs {
     int64_t k_start, w_target;
     int32_t max_iters, max_spin;
     int32_t poll_delay;      // s_sleep units between publishing and the first read of the neighbours' data
+    int32_t poll_delay_v;    // the same for the column exchange
     uint32_t seq_u, seq_v;   // sequence numbers already used by earlier launches
     uint64_t* xbuf;          // [2 kinds][2 parities][256 workgroups][kResSlotWords]
     uint64_t* S;
@@ -141,6 +142,7 @@ struct ResidentArgs {
 
 bool resident_supported(scd_dtype dt, int order, const int64_t* dims);
 int resident_workgroups(const int64_t* dims);  // workgroups of the launch for a supported shape
+void resident_poll_delays(const int64_t* dims, int delay, int32_t* rows, int32_t* cols);  // of the two exchanges
 hipError_t launch_resident(const ResidentArgs& a, hipStream_t st);
 
 // Sparse engine (scd_sparse.hip): cached products updated from the flipped signs only; keeps R and its

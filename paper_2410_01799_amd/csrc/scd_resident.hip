@@ -158,6 +158,13 @@ __device__ __forceinline__ double wave_sum_res(double a)
 // back with loads that bypass the non-coherent caches; no counter, no fence.  Slots alternate by the
 // parity of the sequence number: a workgroup can only be one exchange ahead of the readers of its
 // slot, because finishing exchange e+1 needs data its readers publish after they have read e.
+// An alternation is bound by the latency of the two exchanges and by what lies between them on one workgroup per
+// compute unit (two waves per SIMD, so every vector instruction costs 8 cycles of the chain).  Measured at 4096x4096
+// (us per alternation): 6.33 with barriers that also join a predicate, full-width lane reductions (every lane ends
+// with every sum) and the stop test ahead of the column sums; 5.47 with one plain barrier per exchange, reductions
+// that halve the registers at each step, signs kept as factor bytes, scalar bases for the gathers and the test
+// behind the column sums; 5.40 with the poll delays of resident_poll_delays.  256x256: 3.9 -> 2.9, 1024x1024:
+// 4.4 -> 3.4, 2048x2048: 5.45 -> 4.65.
 // The sum of the 16 column-block shares of c rides on the next row-phase exchange, so the test of
 // Algorithm 4 line 8 is taken one phase late: the row phase already done with the final t is then
 // dropped.  ||R||_F^2 after an update travels the same way (block row sums, then the total).
@@ -171,6 +178,10 @@ __device__ __forceinline__ uint32_t res_slot_off(int kind, uint32_t seq, int wg)
 __device__ __forceinline__ uint64_t* res_slot(const ResidentArgs& a, int kind, uint32_t seq, int wg)
 {
     return a.xbuf + res_slot_off(kind, seq, wg);
+}
+__device__ __forceinline__ const char* res_slot_bytes(const ResidentArgs& a, int kind, uint32_t seq, int wg)
+{
+    return (const char*)(a.xbuf + res_slot_off(kind, seq, wg));
 }
 
 __device__ __forceinline__ double uniform_f64(double v)
@@ -196,29 +207,30 @@ __device__ __forceinline__ void res_publish_f64(uint64_t* p, double v, uint32_t 
 }
 
 // H members' values of one element (one half of a group of 2H) plus NX / 2 piggybacked doubles of one
-// member (NX = 2 or 4 more words; only what the phase at hand uses is published and read: every word is a
-// trip through the fabric), all loads in flight together.  If any word is still from an earlier exchange,
-// all are read again (re-reads are rare once the first read is delayed a little).
+// member (NX = 0, 2 or 4 more words; only what the phase at hand uses is published and read: every word is a
+// trip through the fabric), all loads in flight together.  If any word of the wave is still from an earlier
+// exchange, all are read again (re-reads are rare once the first read is delayed a little).  `base` is the same
+// for the whole workgroup and `off` (bytes) the same in every exchange: the loads take a scalar base and a 32-bit
+// lane offset, so that no 64-bit lane address is worked out between the wait and the first load.
 template <int H, int NX>
-__device__ __forceinline__ bool res_gather_x2(const uint64_t* xbuf, uint32_t off, uint32_t stride, uint32_t xoff,
-                                              uint32_t seq, int max_spin, double& sum, double& x0, double& x1,
-                                              int& spin)
+__device__ __forceinline__ bool res_gather(const char* base, uint32_t off, uint32_t stride, const char* xbase, uint32_t xoff,
+                                           uint32_t seq, int max_spin, double& sum, double& x0, double& x1, int& spin)
 {
-    static_assert(NX == 2 || NX == 4, "one or two piggybacked doubles");
+    static_assert(NX == 0 || NX == 2 || NX == 4, "none, one or two piggybacked doubles");
     uint64_t w[H + 4];
     w[H + 2] = 0;
     w[H + 3] = 0;
     for (;;) {
 #pragma unroll
         for (int q = 0; q < H; ++q)
-            w[q] = __hip_atomic_load(xbuf + (off + q * stride), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            w[q] = __hip_atomic_load((const uint64_t*)(base + (size_t)q * stride + off), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
         for (int q = 0; q < NX; ++q)
-            w[H + q] = __hip_atomic_load(xbuf + (xoff + q), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        bool fresh = true;
+            w[H + q] = __hip_atomic_load((const uint64_t*)(xbase + q * 8 + xoff), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint32_t stale = 0;
 #pragma unroll
-        for (int q = 0; q < H + NX; ++q) fresh = fresh && ((uint32_t)(w[q] >> 32) == seq);
-        if (fresh) break;
+        for (int q = 0; q < H + NX; ++q) stale |= (uint32_t)(w[q] >> 32) ^ seq;
+        if (__ballot(stale != 0) == 0) break;
         if (++spin > max_spin) return false;
         __builtin_amdgcn_s_sleep(1);
     }
@@ -226,32 +238,8 @@ __device__ __forceinline__ bool res_gather_x2(const uint64_t* xbuf, uint32_t off
 #pragma unroll
     for (int q = 0; q < H; ++q) s += (double)__uint_as_float((uint32_t)w[q]);
     sum = s;
-    x0 = __longlong_as_double((long long)((w[H + 1] << 32) | (w[H] & 0xFFFFFFFFull)));
-    x1 = __longlong_as_double((long long)((w[H + 3] << 32) | (w[H + 2] & 0xFFFFFFFFull)));
-    return true;
-}
-
-// H members' values of one element, all loads in flight together.
-template <int H>
-__device__ __forceinline__ bool res_gather(const uint64_t* xbuf, uint32_t off, uint32_t stride, uint32_t seq,
-                                           int max_spin, double& sum, int& spin)
-{
-    uint64_t w[H];
-    for (;;) {
-#pragma unroll
-        for (int q = 0; q < H; ++q)
-            w[q] = __hip_atomic_load(xbuf + (off + q * stride), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        bool fresh = true;
-#pragma unroll
-        for (int q = 0; q < H; ++q) fresh = fresh && ((uint32_t)(w[q] >> 32) == seq);
-        if (fresh) break;
-        if (++spin > max_spin) return false;
-        __builtin_amdgcn_s_sleep(1);
-    }
-    double s = 0.0;
-#pragma unroll
-    for (int q = 0; q < H; ++q) s += (double)__uint_as_float((uint32_t)w[q]);
-    sum = s;
+    if constexpr (NX >= 2) x0 = __longlong_as_double((long long)((w[H + 1] << 32) | (w[H] & 0xFFFFFFFFull)));
+    if constexpr (NX == 4) x1 = __longlong_as_double((long long)((w[H + 3] << 32) | (w[H + 2] & 0xFFFFFFFFull)));
     return true;
 }
 
@@ -270,20 +258,54 @@ __device__ __forceinline__ double dpp_swap1_f64(double v)
     return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
 
-// v[l] + v[l ^ 16] and v[l] + v[l ^ 32] by the row-swap instructions of gfx950 (no LDS traffic):
-// swapping the odd rows of one copy with the even rows of another leaves the two partners of every
-// lane in the two results, in the same order for both partners.
-__device__ __forceinline__ float sum_xor16(float v)
+// Sum over the four 16-lane rows of a wave for two registers at once: the row-swap instructions of gfx950 exchange
+// the odd rows (the upper half of the wave) of one register with the even rows (the lower half) of the other, after
+// which one addition serves both.  half16(a, b): even rows hold a's pair sums, odd rows b's.  half32 of two such:
+// row r of the result holds the full sum of the r-th of the four registers.
+__device__ __forceinline__ float half16(float a, float b)
 {
-    const unsigned b = __float_as_uint(v);
-    const auto r = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
-__device__ __forceinline__ float sum_xor32(float v)
+__device__ __forceinline__ float half32(float a, float b)
 {
-    const unsigned b = __float_as_uint(v);
-    const auto r = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Sum over groups of N = 4, 8 or 16 neighbouring lanes, the same bits in every lane of a group.
+template <int N>
+__device__ __forceinline__ double group_sum_res(double a)
+{
+    a += dpp_f64_res<0xB1, 0>(a);                          // lane ^ 1
+    a += dpp_f64_res<0x4E, 0>(a);                          // lane ^ 2
+    if constexpr (N >= 8) a += dpp_f64_res<0x141, 0x1B>(a);    // lane ^ 4
+    if constexpr (N >= 16) a += dpp_f64_res<0x140, 0x141>(a);  // lane ^ 8
+    return a;
+}
+
+// A sign is kept in LDS as the top byte of the factor +-1.0 it stands for; byte k of a loaded word becomes the
+// factor in one instruction.
+constexpr uint8_t kPosByte = 0x3F, kNegByte = 0xBF;
+template <int K>
+__device__ __forceinline__ float sign_factor(uint32_t bytes)
+{
+    return __uint_as_float(__builtin_amdgcn_perm(bytes, 0x00800000u, 0x00020100u | ((4u + K) << 24)));
+}
+template <int N>
+__device__ __forceinline__ void sign_factors(const uint8_t* p, float (&f)[N])
+{
+    uint32_t w[(N + 3) / 4];
+    if constexpr (N >= 4) {
+#pragma unroll
+        for (int i = 0; i < N / 4; ++i) w[i] = ((const uint32_t*)p)[i];
+    } else {
+        w[0] = *(const uint16_t*)p;
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        f[i] = (i & 3) == 0 ? sign_factor<0>(w[i / 4])
+                            : ((i & 3) == 1 ? sign_factor<1>(w[i / 4]) : ((i & 3) == 2 ? sign_factor<2>(w[i / 4]) : sign_factor<3>(w[i / 4])));
 }
 
 // PAD: the grid overhangs the matrix (a template parameter: the 128 row/column tests of a thread's tile are
@@ -303,11 +325,13 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
     const int pr = blockIdx.x / P, pc = blockIdx.x % P;
     const int wg = blockIdx.x;
 
-    __shared__ float lds_q[kResThreads / 64][BN];
-    __shared__ uint8_t lds_s[2][BM];
-    __shared__ uint8_t lds_t[BN];
-    __shared__ double lds_red[kResThreads / 64];
+    constexpr int NWV = kResThreads / 64;
+    __shared__ float lds_q[NWV][BN];
+    __shared__ __align__(16) uint8_t lds_s[2][BM];  // signs as the top bytes of +-1.0
+    __shared__ __align__(16) uint8_t lds_t[BN];
+    __shared__ double lds_red[NWV];
     __shared__ double lds_x[2][P];
+    __shared__ int lds_fail;  // a wait ran out in some wave; read after the barrier that follows every exchange
 
     // ---- load the block.  The grid may overhang the matrix: rows and columns past its end are zeros in the
     // registers (they add nothing to any sum and stay zero through every update) and are never read or written.
@@ -316,32 +340,46 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
     float x[TR][TC];
     {
         const float* base = a.R + row0 * a.n + col0;
+        if (!padded || (a.n & 3) == 0) {
 #pragma unroll
-        for (int r = 0; r < TR; ++r)
+            for (int r = 0; r < TR; ++r)
 #pragma unroll
-            for (int c4 = 0; c4 < TC / 4; ++c4) {
-                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (!padded || (row0 + r < a.m && col0 + 4 * c4 < a.n)) v = *(const float4*)(base + (int64_t)r * a.n + 4 * c4);
-                x[r][4 * c4 + 0] = v.x;
-                x[r][4 * c4 + 1] = v.y;
-                x[r][4 * c4 + 2] = v.z;
-                x[r][4 * c4 + 3] = v.w;
-            }
+                for (int c4 = 0; c4 < TC / 4; ++c4) {
+                    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (!padded || (row0 + r < a.m && col0 + 4 * c4 < a.n)) v = *(const float4*)(base + (int64_t)r * a.n + 4 * c4);
+                    x[r][4 * c4 + 0] = v.x;
+                    x[r][4 * c4 + 1] = v.y;
+                    x[r][4 * c4 + 2] = v.z;
+                    x[r][4 * c4 + 3] = v.w;
+                }
+        } else {
+            // rows that are no multiple of 16 bytes: one element at a time, once per launch
+#pragma unroll
+            for (int r = 0; r < TR; ++r)
+#pragma unroll
+                for (int c = 0; c < TC; ++c) x[r][c] = (row0 + r < a.m && col0 + c < a.n) ? base[(int64_t)r * a.n + c] : 0.f;
+        }
     }
+    if (tid == 0) lds_fail = 0;
 
     int64_t k = a.k_start;
     int alternations = 0, updates = 0;
     uint32_t seq_u = a.seq_u, seq_v = a.seq_v;
     int j = 0, warn = 0, cur = 0;
     double c_prev = -INFINITY;
-    double cpart = 0.0;      // this column block's sum |v_l| of the last column phase
-    double fsq_block = 0.0;  // sum of squares of this block after the last update
+    double cpart = 0.0;      // wave 0: this column block's sum |v_l| of the last column phase
+    double fsq_block = 0.0;  // wave 0: sum of squares of this block after the last update
     double frow = 0.0;       // ... of this block row
     int norm_stage = 0;      // 1: fsq_block to publish (row exchange); 2: frow to publish (col exchange)
     int64_t norm_k = 0;
     const double total = (double)a.m * (double)a.n;
     bool need_t0 = true;
     int spin = 0, spins = 0;
+    // lane offsets of the two gathers (bytes; the same in every exchange): thread (element, half) reads the
+    // element's words of one half of the partners; threads past the block read a valid element and drop it
+    const int half = tid & 1;
+    const uint32_t off_u = (uint32_t)(half * H * kResSlotWords + ((tid >> 1) < BM ? (tid >> 1) : BM - 1)) * 8u;
+    const uint32_t off_v = (uint32_t)(half * H * P * kResSlotWords + ((tid >> 1) < BN ? (tid >> 1) : BN - 1)) * 8u;
 
     for (;;) {
         if (k >= a.w_target && norm_stage == 0) break;
@@ -349,7 +387,8 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
             // t_0 of term k from the keyed stream (Algorithm 4 line 2)
             if (tid < BN) {
                 const int64_t col = (int64_t)pc * BN + tid;
-                lds_t[tid] = col < a.n ? (uint8_t)((rng_word(a.seed, (uint64_t)k, 1u, (uint64_t)(col >> 6)) >> (col & 63)) & 1ull) : 0;
+                const bool neg = col < a.n && ((rng_word(a.seed, (uint64_t)k, 1u, (uint64_t)(col >> 6)) >> (col & 63)) & 1ull);
+                lds_t[tid] = neg ? kNegByte : kPosByte;
             }
             need_t0 = false;
             __syncthreads();
@@ -358,112 +397,149 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
         // The signs enter as +-1.0 multipliers of a fused multiply-add: x * (+-1) is exact, so each step
         // rounds exactly like the sign-flip-and-add of Section 3.4, in one instruction instead of two
         // (this engine is bound by vector instructions and latency, not by memory).
-        float tf[TC];
+        float prow;  // the row sum this lane publishes: row tc of the thread row's TR rows (lanes tc < TR)
+        {
+            float tf[TC];
+            sign_factors<TC>(lds_t + tc * TC, tf);
+            float p[TR];
 #pragma unroll
-        for (int c = 0; c < TC; ++c) tf[c] = __uint_as_float(0x3F800000u | ((uint32_t)lds_t[tc * TC + c] << 31));
-        float p[TR];
+            for (int r = 0; r < TR; ++r) {
+                float s = 0.f;
 #pragma unroll
-        for (int r = 0; r < TR; ++r) {
-            float s = 0.f;
+                for (int c = 0; c < TC; ++c) s = __builtin_fmaf(x[r][c], tf[c], s);
+                p[r] = s;
+            }
+            // Sum over the 16 lanes that share these rows, lane distances 1, 2, 4, 8.  At distances 1 and 2 a lane
+            // keeps only the rows whose low index bits are its own (it hands the others to its neighbour), which
+            // halves the registers each time: lane tc ends with rows tc mod 4 and 4 + tc mod 4.
+            const bool odd1 = (lane & 1) != 0, odd2 = (lane & 2) != 0;
+            float a1[TR / 2];
 #pragma unroll
-            for (int c = 0; c < TC; ++c) s = __builtin_fmaf(x[r][c], tf[c], s);
-            // sum over the 16 lanes that share these rows (fixed order per lane)
-            s += dpp_f32<0xB1>(s);   // lane ^ 1
-            s += dpp_f32<0x4E>(s);   // lane ^ 2
-            s += dpp_f32<0x124>(s);  // row rotate 4
-            s += dpp_f32<0x128>(s);  // row rotate 8
-            p[r] = s;
+            for (int i = 0; i < TR / 2; ++i) {
+                const float keep = odd1 ? p[2 * i + 1] : p[2 * i], send = odd1 ? p[2 * i] : p[2 * i + 1];
+                a1[i] = keep + dpp_f32<0xB1>(send);  // lane ^ 1
+            }
+            if constexpr (TR == 2) {
+                float s = a1[0];
+                s += dpp_f32<0x4E>(s);   // lane ^ 2
+                s += dpp_f32<0x124>(s);  // row rotate 4
+                s += dpp_f32<0x128>(s);  // row rotate 8
+                prow = s;
+            } else {
+                float a2[TR / 4];
+#pragma unroll
+                for (int i = 0; i < TR / 4; ++i) {
+                    const float keep = odd2 ? a1[2 * i + 1] : a1[2 * i], send = odd2 ? a1[2 * i] : a1[2 * i + 1];
+                    float s = keep + dpp_f32<0x4E>(send);  // lane ^ 2
+                    s += dpp_f32<0x124>(s);                // row rotate 4
+                    s += dpp_f32<0x128>(s);                // row rotate 8
+                    a2[i] = s;
+                }
+                if constexpr (TR == 8) prow = (lane & 4) ? a2[1] : a2[0];
+                else prow = a2[0];
+            }
         }
         ++seq_u;
         ++alternations;
         {
             uint64_t* mine = res_slot(a, 0, seq_u, wg);
-            if (tc < TR) {
-                float v = p[0];
-#pragma unroll
-                for (int r = 1; r < TR; ++r) v = (tc == r) ? p[r] : v;
-                res_publish(mine + tr * TR + tc, v, seq_u);
-            }
+            if (tc < TR) res_publish(mine + tr * TR + tc, prow, seq_u);
             if (tid == 0) {
                 res_publish_f64(mine + BM, cpart, seq_u);
                 if (norm_stage == 1) res_publish_f64(mine + BM + 2, fsq_block, seq_u);  // (only the exchange after an update)
             }
         }
         for (int d = 0; d < a.poll_delay; ++d) __builtin_amdgcn_s_sleep(1);
-        bool ok = true;
         {
             // gather: thread (row, half) adds eight members in order, the two halves are combined low
             // first.  The last wave also fetches the piggybacked scalars (lane mod P = member), in the
-            // same batch of loads; threads past the block's rows read a valid row and drop it.
-            const int row = tid >> 1, h = tid & 1;
-            const int rowc = row < BM ? row : BM - 1;
-            const uint32_t off = res_slot_off(0, seq_u, pr * P + h * H) + (uint32_t)rowc;
-            double half = 0.0;
-            if (wv == kResThreads / 64 - 1) {
-                double x0 = 0.0, x1 = 0.0;
-                const uint32_t xoff = res_slot_off(0, seq_u, pr * P + (lane & (P - 1))) + BM;
-                if (norm_stage == 1) ok = res_gather_x2<H, 4>(a.xbuf, off, kResSlotWords, xoff, seq_u, a.max_spin, half, x0, x1, spin);
-                else ok = res_gather_x2<H, 2>(a.xbuf, off, kResSlotWords, xoff, seq_u, a.max_spin, half, x0, x1, spin);
+            // same batch of loads.
+            const int row = tid >> 1;
+            const char* base = res_slot_bytes(a, 0, seq_u, pr * P);
+            double hs = 0.0, x0 = 0.0, x1 = 0.0;
+            bool ok;
+            if (wv == NWV - 1) {
+                const uint32_t xoff = (uint32_t)((lane & (P - 1)) * kResSlotWords + BM) * 8u;
+                if (norm_stage == 1) ok = res_gather<H, 4>(base, off_u, kResSlotWords * 8, base, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
+                else ok = res_gather<H, 2>(base, off_u, kResSlotWords * 8, base, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
                 if (lane < P) {
                     lds_x[0][lane] = x0;
-                    lds_x[1][lane] = x1;
+                    if (norm_stage == 1) lds_x[1][lane] = x1;
                 }
             } else {
-                ok = res_gather<H>(a.xbuf, off, kResSlotWords, seq_u, a.max_spin, half, spin);
+                ok = res_gather<H, 0>(base, off_u, kResSlotWords * 8, base, 0, seq_u, a.max_spin, hs, x0, x1, spin);
             }
-            const double other = dpp_swap1_f64(half);
-            const double u = h ? other + half : half + other;
-            if (h == 0 && row < BM) lds_s[cur ^ 1][row] = (u < 0.0) ? 1 : 0;
+            const double other = dpp_swap1_f64(hs);
+            const double u = half ? other + hs : hs + other;
+            if (half == 0 && row < BM) lds_s[cur ^ 1][row] = (u < 0.0) ? kNegByte : kPosByte;
+            if (!ok) lds_fail = 1;
         }
-        if (__syncthreads_or(ok ? 0 : 1)) {
+        // One barrier per exchange: the give-up flag is an LDS word that only ever goes from 0 to 1 and is read
+        // with the data behind the barrier (__syncthreads_or takes three barriers and two more LDS round trips).
+        __syncthreads();
+        const int failed = lds_fail;
+        const double cx = lds_x[0][lane & (P - 1)];
+        cur ^= 1;  // s_j = sgn(u)
+
+        // ================= column phase: v = R^T s (Algorithm 4 line 6), c = sum |v| (line 7).  Its sums are formed
+        // before the stop test below is looked at: the test's chain of additions hides behind them, and a term that
+        // ends here has formed one half step too many (once per term).
+        float qv[TC / 4];
+        {
+            float sf[TR];
+            sign_factors<TR>(&lds_s[cur][tr * TR], sf);
+            float q[TC];
+#pragma unroll
+            for (int c = 0; c < TC; ++c) {
+                float s = 0.f;
+#pragma unroll
+                for (int r = 0; r < TR; ++r) s = __builtin_fmaf(x[r][c], sf[r], s);
+                q[c] = s;
+            }
+            // the four thread rows of this wave hold the same columns 16 lanes apart: lane row i ends with the sums
+            // of columns i TC/4 .. (i + 1) TC/4 - 1
+#pragma unroll
+            for (int g = 0; g < TC / 4; ++g)
+                qv[g] = half32(half16(q[g], q[TC / 4 + g]), half16(q[TC / 2 + g], q[3 * (TC / 4) + g]));
+        }
+        const double c_tot = uniform_f64(group_sum_res<P>(cx));
+        if (__builtin_amdgcn_readfirstlane(failed)) {
             if (tid == 0) atomicExch((unsigned*)&a.res->err, 1u);
             return;
         }
         spins += spin;
         spin = 0;
-        // (all loads first, then the adds in order: a dependent chain of LDS reads would cost a latency each)
-        double c_tot = 0.0;
-        {
-            double cq[P];
-#pragma unroll
-            for (int q = 0; q < P; ++q) cq[q] = lds_x[0][q];
-#pragma unroll
-            for (int q = 0; q < P; ++q) c_tot += cq[q];
-        }
-        c_tot = uniform_f64(c_tot);
         if (norm_stage == 1) {
-            double f_tot = 0.0;
-            double fq[P];
-#pragma unroll
-            for (int q = 0; q < P; ++q) fq[q] = lds_x[1][q];
-#pragma unroll
-            for (int q = 0; q < P; ++q) f_tot += fq[q];
-            frow = uniform_f64(f_tot);
+            frow = uniform_f64(group_sum_res<P>(lds_x[1][lane & (P - 1)]));
             norm_stage = 2;
         }
         if (j > 0) {
             const bool conv = (c_tot <= c_prev) || (j >= a.max_iters);
             if (conv) {
-                // ---- the term is (c_tot, s_cur, t): append it (Algorithm 5 lines 7-9) and subtract it (line 10)
+                // ---- the term is (c_tot, s_{j-1}, t): append it (Algorithm 5 lines 7-9) and subtract it (line 10);
+                // the s of the row phase just done (lds_s[cur]) is dropped
+                cur ^= 1;
                 if (!(c_tot <= c_prev)) warn = 1;
                 const double ck = c_tot / total;
                 const float ckf = (float)ck;
                 if (pc == 0 && wv < BM / 64) {
-                    const uint64_t word = __ballot(lds_s[cur][wv * 64 + lane] != 0);
+                    const uint64_t word = __ballot(lds_s[cur][wv * 64 + lane] == kNegByte);
                     if (lane == 0 && pr * (BM / 64) + wv < a.mw) a.S[k * a.mw + pr * (BM / 64) + wv] = word;
                 }
                 if (pr == 0 && wv < BN / 64) {
-                    const uint64_t word = __ballot(lds_t[wv * 64 + lane] != 0);
+                    const uint64_t word = __ballot(lds_t[wv * 64 + lane] == kNegByte);
                     if (lane == 0 && pc * (BN / 64) + wv < a.nw) a.T[k * a.nw + pc * (BN / 64) + wv] = word;
                 }
                 if (wg == 0 && tid == 0) {
                     a.c[k] = ckf;
                     a.iters[k] = j;
                 }
+                float tf[TC];
+                sign_factors<TC>(lds_t + tc * TC, tf);
                 double f = 0.0;
 #pragma unroll
                 for (int r = 0; r < TR; ++r) {
-                    const uint32_t sr = (uint32_t)lds_s[cur][tr * TR + r] << 31;
+                    const uint32_t sr = ((uint32_t)lds_s[cur][tr * TR + r] & 0x80u) << 24;
 #pragma unroll
                     for (int c = 0; c < TC; ++c) {
                         // R_il - ck s_i t_l: the signs choose +ck or -ck
@@ -475,10 +551,12 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
                 f = wave_sum_res(f);
                 if (lane == 0) lds_red[wv] = f;
                 __syncthreads();
-                double fb = 0.0;
-#pragma unroll 2
-                for (int q = 0; q < kResThreads / 64; ++q) fb += lds_red[q];
-                fsq_block = uniform_f64(fb);
+                if (wv == 0) {
+                    double fb = 0.0;
+#pragma unroll
+                    for (int q = 0; q < NWV; ++q) fb += lds_red[q];
+                    fsq_block = uniform_f64(fb);
+                }
                 ++k;
                 ++updates;
                 norm_stage = 1;
@@ -492,90 +570,68 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
             }
             c_prev = c_tot;
         }
-        cur ^= 1;  // s_j = sgn(u)
-
-        // ================= column phase: v = R^T s (Algorithm 4 line 6), c = sum |v| (line 7)
         {
-            float sf[TR];
-#pragma unroll
-            for (int r = 0; r < TR; ++r) sf[r] = __uint_as_float(0x3F800000u | ((uint32_t)lds_s[cur][tr * TR + r] << 31));
-#pragma unroll
-            for (int c4 = 0; c4 < TC / 4; ++c4) {
-                float qv[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    float s = 0.f;
-#pragma unroll
-                    for (int r = 0; r < TR; ++r) s = __builtin_fmaf(x[r][4 * c4 + e], sf[r], s);
-                    // the four thread rows of this wave hold the same columns 16 lanes apart
-                    qv[e] = sum_xor32(sum_xor16(s));
-                }
-                if (lane < 16) *(float4*)&lds_q[wv][tc * TC + 4 * c4] = make_float4(qv[0], qv[1], qv[2], qv[3]);
-            }
+            // lane (i, tc) holds TC/4 neighbouring columns
+            float* dst = &lds_q[wv][tc * TC + (lane >> 4) * (TC / 4)];
+            if constexpr (TC == 16) *(float4*)dst = make_float4(qv[0], qv[1], qv[2], qv[3]);
+            else if constexpr (TC == 8) *(float2*)dst = make_float2(qv[0], qv[1]);
+            else dst[0] = qv[0];
         }
         __syncthreads();
         ++seq_v;
         {
             uint64_t* mine = res_slot(a, 1, seq_v, wg);
             if (tid < BN) {
+                // (all loads in flight together, then the adds in wave order: the empty asm keeps the compiler from
+                // loading two, waiting, adding two)
+                float w[NWV];
+#pragma unroll
+                for (int q = 0; q < NWV; ++q) w[q] = lds_q[q][tid];
+                static_assert(NWV == 8, "operands of the asm");
+                asm volatile("" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(w[4]), "+v"(w[5]), "+v"(w[6]), "+v"(w[7]));
                 float s = 0.f;
 #pragma unroll
-                for (int q = 0; q < kResThreads / 64; ++q) s += lds_q[q][tid];
+                for (int q = 0; q < NWV; ++q) s += w[q];
                 res_publish(mine + tid, s, seq_v);
             }
             if (norm_stage == 2 && tid == kResThreads - 1) res_publish_f64(mine + BN, frow, seq_v);
         }
-        for (int d = 0; d < a.poll_delay; ++d) __builtin_amdgcn_s_sleep(1);
-        ok = true;
+        for (int d = 0; d < a.poll_delay_v; ++d) __builtin_amdgcn_s_sleep(1);
         double absv = 0.0;
         {
-            const int col = tid >> 1, h = tid & 1;
-            const int colc = col < BN ? col : BN - 1;
-            const uint32_t off = res_slot_off(1, seq_v, (h * H) * P + pc) + (uint32_t)colc;
-            double half = 0.0;
-            if (norm_stage == 2 && wv == kResThreads / 64 - 1) {
+            const int col = tid >> 1;
+            const char* base = res_slot_bytes(a, 1, seq_v, pc);
+            double hs = 0.0, x0 = 0.0, x1 = 0.0;
+            bool ok;
+            if (norm_stage == 2 && wv == NWV - 1) {
                 // the block-row sums of squares travel on this exchange once per term
-                double x0 = 0.0, x1 = 0.0;
-                ok = res_gather_x2<H, 2>(a.xbuf, off, P * kResSlotWords, res_slot_off(1, seq_v, (lane & (P - 1)) * P + pc) + BN,
-                                         seq_v, a.max_spin, half, x0, x1, spin);
+                ok = res_gather<H, 2>(base, off_v, P * kResSlotWords * 8, base, (uint32_t)((lane & (P - 1)) * P * kResSlotWords + BN) * 8u,
+                                      seq_v, a.max_spin, hs, x0, x1, spin);
                 if (lane < P) lds_x[1][lane] = x0;
             } else {
-                ok = res_gather<H>(a.xbuf, off, P * kResSlotWords, seq_v, a.max_spin, half, spin);
+                ok = res_gather<H, 0>(base, off_v, P * kResSlotWords * 8, base, 0, seq_v, a.max_spin, hs, x0, x1, spin);
             }
-            const double other = dpp_swap1_f64(half);
-            const double v = h ? other + half : half + other;
-            if (h == 0 && col < BN) {
-                lds_t[col] = (v < 0.0) ? 1 : 0;
+            const double other = dpp_swap1_f64(hs);
+            const double v = half ? other + hs : hs + other;
+            if (half == 0 && col < BN) {
+                lds_t[col] = (v < 0.0) ? kNegByte : kPosByte;
                 absv = fabs(v);
             }
+            if (!ok) lds_fail = 1;
         }
         absv = wave_sum_res(absv);
         if (lane == 0) lds_red[wv] = absv;
-        if (__syncthreads_or(ok ? 0 : 1)) {
+        __syncthreads();
+        if (__builtin_amdgcn_readfirstlane(lds_fail)) {
             if (tid == 0) atomicExch((unsigned*)&a.res->err, 1u);
             return;
         }
-        {
-            double cs = 0.0;
-            {
-                double cq[kResThreads / 64];
-#pragma unroll
-                for (int q = 0; q < kResThreads / 64; ++q) cq[q] = lds_red[q];
-#pragma unroll
-                for (int q = 0; q < kResThreads / 64; ++q) cs += cq[q];
-            }
-            cpart = uniform_f64(cs);
-            if (norm_stage == 2) {
-                double ft = 0.0;
-                double fq[P];
-#pragma unroll
-                for (int q = 0; q < P; ++q) fq[q] = lds_x[1][q];
-#pragma unroll
-                for (int q = 0; q < P; ++q) ft += fq[q];
-                ft = uniform_f64(ft);
-                if (wg == 0 && tid == 0) a.trace[norm_k] = sqrt(ft);
-                norm_stage = 0;
-            }
+        // this column block's share of c travels on the next row exchange (published by thread 0)
+        if (wv == 0) cpart = group_sum_res<8>(lds_red[lane & (NWV - 1)]);
+        if (norm_stage == 2) {
+            const double ft = group_sum_res<P>(lds_x[1][lane & (P - 1)]);
+            if (wg == 0 && tid == 0) a.trace[norm_k] = sqrt(ft);
+            norm_stage = 0;
         }
         ++j;
         spins += spin;
@@ -589,13 +645,21 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
     // ---- write the block back
     {
         float* base = a.R + row0 * a.n + col0;
+        if (!padded || (a.n & 3) == 0) {
 #pragma unroll
-        for (int r = 0; r < TR; ++r)
+            for (int r = 0; r < TR; ++r)
 #pragma unroll
-            for (int c4 = 0; c4 < TC / 4; ++c4)
-                if (!padded || (row0 + r < a.m && col0 + 4 * c4 < a.n))
-                    *(float4*)(base + (int64_t)r * a.n + 4 * c4) =
-                        make_float4(x[r][4 * c4], x[r][4 * c4 + 1], x[r][4 * c4 + 2], x[r][4 * c4 + 3]);
+                for (int c4 = 0; c4 < TC / 4; ++c4)
+                    if (!padded || (row0 + r < a.m && col0 + 4 * c4 < a.n))
+                        *(float4*)(base + (int64_t)r * a.n + 4 * c4) =
+                            make_float4(x[r][4 * c4], x[r][4 * c4 + 1], x[r][4 * c4 + 2], x[r][4 * c4 + 3]);
+        } else {
+#pragma unroll
+            for (int r = 0; r < TR; ++r)
+#pragma unroll
+                for (int c = 0; c < TC; ++c)
+                    if (row0 + r < a.m && col0 + c < a.n) base[(int64_t)r * a.n + c] = x[r][c];
+        }
     }
     if (wg == 0 && tid == 0) {
         a.res->k = k;
@@ -652,6 +716,21 @@ int resident_workgroups(const int64_t* dims)
 {
     int p = 0, tr, tc;
     return resident_shape(dims[0], dims[1], &p, &tr, &tc) ? p * p : 0;
+}
+
+// Sleep units between publishing and the first read, per exchange, from the option's value (default 16).  A read
+// that comes before the last partner's words costs another trip to memory (0.4 us and its traffic), one that comes
+// late costs what it waits, so the optimum is just behind the arrival, which moves with the words of an exchange.
+// Measured in us per alternation: grids of up to 8 x 8 at 10 units 2.87 (256^2) and 3.41 (1024^2), at 16 3.17 and
+// 3.70; 16 x 16 with slots of 256 columns at 18 / 14 units (rows / columns) 5.38 (4096^2), at 16 / 16 5.44, at
+// 12 / 8 5.84; with shorter slots at 16 / 8 4.55 (2048^2) and 4.95 (4096x1024), at 16 / 16 4.69 and 5.14.
+void resident_poll_delays(const int64_t* dims, int delay, int32_t* rows, int32_t* cols)
+{
+    int p = 16, tr = 8, tc = 16;
+    (void)resident_shape(dims[0], dims[1], &p, &tr, &tc);
+    const int u = p <= 8 ? delay - 6 : delay + 2, v = p <= 8 ? delay - 6 : (tc == 16 ? delay - 2 : delay - 8);
+    *rows = delay == 0 || u < 0 ? 0 : u;
+    *cols = delay == 0 || v < 0 ? 0 : v;
 }
 
 template <int TR, int TC, int P, bool PAD>
