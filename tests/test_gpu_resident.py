@@ -13,6 +13,10 @@ SHAPES = [(1024, 4096), (2048, 2048), (4096, 4096), (256, 256), (512, 512), (102
 # shapes the grid overhangs (zero rows and columns in the registers), or with an oblong thread tile
 RAGGED = [(4096, 1024), (2048, 4096), (1000, 4096), (2052, 516), (100, 76), (8, 8), (5, 4096), (300, 260), (1, 4),
           (1030, 520), (4000, 4092), (64, 4096), (3000, 2000)]
+# rows that are no multiple of 16 bytes: first and last lengths, one and two elements past a tile or a word, the
+# largest; and the shapes whose 4 x 4 grid would need a tile it is not built with
+UNALIGNED = [(7, 5), (1, 6), (64, 63), (65, 257), (513, 129), (333, 1025), (1501, 999), (4096, 4093), (4095, 4095)]
+SMALL_OBLONG = [(128, 704), (200, 1024), (600, 256), (1024, 60)]
 
 
 @pytest.fixture(scope="module")
@@ -31,7 +35,7 @@ def gauss(shape, seed):
     return np.random.Generator(np.random.PCG64(seed)).standard_normal(shape).astype(np.float32)
 
 
-@pytest.mark.parametrize("m,n", SHAPES + RAGGED)
+@pytest.mark.parametrize("m,n", SHAPES + RAGGED + UNALIGNED + SMALL_OBLONG)
 def test_resident_matches_oracle_in_lockstep(scd, oracle, m, n):
     w, seed = min(10, m * n), 17
     A = gauss((m, n), m + n)
