@@ -31,13 +31,22 @@ namespace {
 
 constexpr int kSpThreads = 512;
 constexpr int kSpWaves = kSpThreads / kWave;
-constexpr int kSpPayload = 16;                    // payload words per slot (32 sign bits each)
-constexpr int kSpSlotUsed = kSpPayload + 2;       // + one double as two tagged halves
-// Every workgroup reads every slot: slots 4 KB apart land on different memory channels, so that the
-// 256 x 256 reads of one exchange do not queue up at a handful of them.
-constexpr int kSpSlot = 512;
+constexpr int kSpPayload = 16;                    // most payload words of a member (32 sign bits each)
+// Every workgroup reads every word of every member.  Word k of member g lies at (k / 8) * 2048 + 8 g + k mod 8: a
+// member's words share a 64-byte line, the members' lines are neighbours.  Measured alone, 256 members with three words
+// (us per exchange, first read after 16 sleep units / at once): 1.32 / 1.93; words of the same number side by side
+// 1.10 / 3.21 (early reads of the few lines hold up the stores to them, which cost tall matrices 5 %); members 4 KB
+// apart 1.71 / 2.30.
+constexpr int kSpHalfWords = 3 * 8 * kSpGrid;     // words of one parity: up to 18 per member (a double as two halves)
+// Sleep units (in sixteenths) before the first read of an exchange, per wave and kind of exchange: longer by 3/4
+// unit when the first read came too early, shorter by 1/16 when it did not.  The right wait lies just behind the
+// slowest member, and that moves with the shape, the number of workgroups and what else runs; an early read costs
+// everybody, because all members read the same lines.  With a fixed wait of 16 units for all: 4096x4096 f64 on 256
+// workgroups 10.0 us per alternation against 9.6, 4096x4096 f32 on 64 10.3 against 9.75, 200x200 f64 on 32 8.55
+// against 8.27.
+constexpr int kSpWaitShift = 4, kSpWaitUp = 12, kSpWaitDown = 1, kSpWaitMax = 80 << kSpWaitShift;
 constexpr int kSpListCap = 32 * kSpThreads;       // flips handled per compaction round: one 32-bit word per thread
-constexpr size_t kSpMaxLds = 150 * 1024;          // most dynamic LDS a launch may ask for
+constexpr size_t kSpMaxLds = 150 * 1024 + 64;     // most dynamic LDS a launch may ask for
 // Words a thread may have to gather: grid * (ceil(slice / 32) + 2) over the supported pairs, where
 // grid * slice <= 65536 + 8 * grid: at most 67584 / 32 + 256 + 512 = 2880 words for the 512 threads
 // (sparse_supported checks it).
@@ -182,8 +191,14 @@ struct SpShared {
     double* accv;      // v on J_g
     double* red;       // [kSpThreads] partial sums of the sparse accumulation / per-wave scratch
     uint32_t* scal;    // [2][kSpGrid][2] gathered scalars (lo, hi halves)
-    int* scan;         // [kSpWaves + 1]
+    double* cred;      // [kSpWaves] wave sums of |v|
+    int* scan;         // [kSpWaves + 1], then the give-up flag of the exchanges
 };
+// The flag goes from 0 to 1 when a wait runs out in some wave and is read behind the barrier that ends an exchange.
+// (__syncthreads_or takes three barriers and two LDS round trips.  With every wave forming the scalars' sums for
+// itself, the products with the pending terms ahead of the compaction and |v| joined in cells of its own, an
+// alternation has 9 barriers where it had 21.)
+constexpr int kSpFail = kSpWaves + 1;
 
 // Dense pass over `nrows` consecutive rows of Y (row length ld, a multiple of 16 bytes): optionally
 // subtract ck * rowsign * colsign, sum the squares, and form the signed row sums with `sumbits`.
@@ -358,7 +373,7 @@ __device__ void sp_accumulate_flips(const TE* __restrict__ Y, int64_t ld, int64_
     // distance), then the waves in order
     if (slp <= 16) part = sp_sum_xor16(part);
     if (slp <= 32) part = sp_sum_xor32(part);
-    __syncthreads();
+    // (sh.red was last read before the barriers of the compaction)
     if (slp >= kWave) sh.red[tid] = part;
     else if (lane < slp) sh.red[wv * slp + e] = part;
     __syncthreads();
@@ -373,13 +388,20 @@ __device__ void sp_accumulate_flips(const TE* __restrict__ Y, int64_t ld, int64_
         acc[tid] += 2.0 * s;
     }
     // No barrier here: a thread reads back only its own entry of acc, and every path from here passes a barrier
-    // before sh.red is written again (the pending-term products, the exchange, the sum of |v| all start or end
-    // with one).
+    // before sh.red is written again (the one of the coming exchange at the latest; |v| is joined in sh.cred).
 }
 
+// place of word k of member mem (see kSpHalfWords)
+__device__ __forceinline__ int sp_word(int k, int mem) { return ((k >> 3) * kSpGrid + mem) * 8 + (k & 7); }
 __device__ __forceinline__ void sp_store_tagged(uint64_t* p, uint32_t v, uint32_t seq)
 {
     __hip_atomic_store(p, ((uint64_t)seq << 32) | (uint64_t)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ int sp_adapt(int wait, bool late)
+{
+    const int w = late ? wait + kSpWaitUp : wait - kSpWaitDown;
+    return w < 0 ? 0 : (w > kSpWaitMax ? kSpWaitMax : w);
 }
 
 // Publish this workgroup's slice of sign bits (taken from acc < 0) and, if asked, one scalar, then read every
@@ -387,8 +409,9 @@ __device__ __forceinline__ void sp_store_tagged(uint64_t* p, uint32_t v, uint32_
 // `fence`: this exchange also hands over ordinary data (the rows of R or RT this workgroup has just
 // rewritten): the writes are released to the whole device before anything is published, and the
 // caches are invalidated after the gather, because the L2 of one XCD does not see another's writes.
+// `wait`: sleep units (kSpWaitShift) before the first read; `late` tells whether this wave had to read again.
 __device__ bool sp_exchange(const SparseArgs& a, uint32_t seq, const double* acc, int len, int slice, int64_t total_bits,
-                            double sc0, bool has_scalar, uint32_t* dest, SpShared& sh, int& spins, bool fence)
+                            double sc0, bool has_scalar, uint32_t* dest, SpShared& sh, int& spins, bool fence, int wait, bool& late)
 {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     const int g = blockIdx.x;
@@ -396,23 +419,22 @@ __device__ bool sp_exchange(const SparseArgs& a, uint32_t seq, const double* acc
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         __syncthreads();
     }
-    uint64_t* mine = a.xbuf + ((size_t)(seq & 1u) * kSpGrid + g) * kSpSlot;
+    uint64_t* mine = a.xbuf + (size_t)(seq & 1u) * kSpHalfWords;
     const int words = (slice + 31) >> 5;  // payload words every workgroup publishes
     // ---- publish: one ballot per 64 slice entries
     for (int b = wv * kWave; b < slice; b += kSpThreads) {
         const int e = b + lane;
         const uint64_t bal = __ballot(e < len && acc[e] < 0.0);
         if (lane == 0) {
-            sp_store_tagged(mine + (b >> 5), (uint32_t)bal, seq);
-            if (b + 32 < slice) sp_store_tagged(mine + (b >> 5) + 1, (uint32_t)(bal >> 32), seq);
+            sp_store_tagged(mine + sp_word(b >> 5, g), (uint32_t)bal, seq);
+            if (b + 32 < slice) sp_store_tagged(mine + sp_word((b >> 5) + 1, g), (uint32_t)(bal >> 32), seq);
         }
     }
     if (has_scalar && tid == kSpThreads - 1) {
         const uint64_t b0 = (uint64_t)__double_as_longlong(sc0);
-        sp_store_tagged(mine + kSpPayload + 0, (uint32_t)b0, seq);
-        sp_store_tagged(mine + kSpPayload + 1, (uint32_t)(b0 >> 32), seq);
+        sp_store_tagged(mine + sp_word(words, g), (uint32_t)b0, seq);
+        sp_store_tagged(mine + sp_word(words + 1, g), (uint32_t)(b0 >> 32), seq);
     }
-    for (int d = 0; d < a.poll_delay; ++d) __builtin_amdgcn_s_sleep(1);
     // ---- gather: the payload words (+ the two halves of the scalar) of each of the a.grid members, spread
     // over the threads.  Every workgroup polls every slot and every word read or written is a trip through
     // the fabric, so a word that is not needed is not sent: an exchange without a scalar took 5.9 us with the
@@ -420,20 +442,21 @@ __device__ bool sp_exchange(const SparseArgs& a, uint32_t seq, const double* acc
     const int per = words + (has_scalar ? 2 : 0);
     const int items = a.grid * per;
     uint64_t w[kSpMaxItems];
-    // where this thread's words lie (member * kSpSlot + word; -1: none), worked out once.  item / per by a
-    // float product: (item + 0.5) / per is at least 0.5 / 18 away from an integer, items stay below 4608.
+    // where this thread's words lie (-1: none), worked out once.  item / grid by a
+    // float product: (item + 0.5) / grid is at least 0.5 / 256 away from an integer, items stay below 4608.
     int where[kSpMaxItems];
     {
-        const float rper = 1.0f / (float)per;
+        const float rgrid = 1.0f / (float)a.grid;
 #pragma unroll
         for (int it = 0; it < kSpMaxItems; ++it) {
             const int idx = tid + it * kSpThreads;
-            const int mem = (int)(((float)idx + 0.5f) * rper), k = idx - mem * per;
-            const int word = k < words ? k : kSpPayload + (k - words);
-            where[it] = idx < items ? mem * kSpSlot + word : -1;
+            const int k = (int)(((float)idx + 0.5f) * rgrid), mem = idx - k * a.grid;
+            where[it] = idx < items ? sp_word(k, mem) : -1;
         }
     }
-    const uint64_t* xb = a.xbuf + (size_t)(seq & 1u) * kSpGrid * kSpSlot;
+    // (the wait hides the index arithmetic above)
+    for (int d = 0; d < (wait >> kSpWaitShift); ++d) __builtin_amdgcn_s_sleep(1);
+    const uint64_t* xb = a.xbuf + (size_t)(seq & 1u) * kSpHalfWords;
     bool ok = true;
     int spin = 0;
 #pragma unroll
@@ -456,6 +479,7 @@ __device__ bool sp_exchange(const SparseArgs& a, uint32_t seq, const double* acc
         __builtin_amdgcn_s_sleep(1);
     }
     spins += spin;
+    late = __ballot(spin > 0) != 0;
     if (fence) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     if (ok) {
         uint8_t* dbytes = (uint8_t*)dest;
@@ -464,39 +488,61 @@ __device__ bool sp_exchange(const SparseArgs& a, uint32_t seq, const double* acc
 #pragma unroll
         for (int it = 0; it < kSpMaxItems; ++it) {
             if (where[it] >= 0) {
-                const int mem = where[it] / kSpSlot, word = where[it] % kSpSlot;  // (kSpSlot is a power of two)
+                const int word = where[it] / (8 * kSpGrid) * 8 + (where[it] & 7), mem = (where[it] >> 3) & (kSpGrid - 1);
                 const uint32_t v = (uint32_t)w[it];
-                if (word < kSpPayload) {
+                if (word < words) {
                     const int64_t b0 = (int64_t)mem * sbytes + 4 * word;
 #pragma unroll
                     for (int b = 0; b < 4; ++b)
                         if (4 * word + b < sbytes && b0 + b < tbytes) dbytes[b0 + b] = (uint8_t)(v >> (8 * b));
                 } else {
-                    sh.scal[mem * 2 + (word - kSpPayload)] = v;  // low, high half of the scalar
+                    sh.scal[mem * 2 + (word - words)] = v;  // low, high half of the scalar
                 }
             }
         }
     }
-    return !__syncthreads_or(ok ? 0 : 1);
+    if (!ok) sh.scan[kSpFail] = 1;
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(sh.scan[kSpFail]) == 0;
 }
 
-// Sum of one gathered scalar over the members, in a fixed order; every thread gets the same bits.
-__device__ double sp_sum_scalar(const SpShared& sh, double* scratch, int grid)
+// Sum of one gathered scalar over the members, in a fixed order; every thread gets the same bits (every wave forms
+// the sum for itself: no barrier).
+__device__ double sp_sum_scalar(const SpShared& sh, int grid)
 {
-    const int tid = threadIdx.x, lane = tid & (kWave - 1);
-    if (tid < kWave) {
-        double s = 0.0;
-        for (int g = lane; g < grid; g += kWave) {
-            const uint32_t lo = sh.scal[g * 2], hi = sh.scal[g * 2 + 1];
-            s += __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-        }
-        s = sp_wave_sum(s);
-        if (lane == 0) scratch[0] = s;
+    static_assert(kSpGrid == 4 * kWave, "four members per lane");
+    const int lane = threadIdx.x & (kWave - 1);
+    double x[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int g = lane + i * kWave;
+        const uint2 h = g < grid ? *(const uint2*)(sh.scal + 2 * g) : make_uint2(0u, 0u);
+        x[i] = __longlong_as_double((long long)(((uint64_t)h.y << 32) | h.x));
     }
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (lane + i * kWave < grid) s += x[i];
+    return sp_wave_sum(s);
+}
+
+// Joins the wave sums of |v| for the thread that publishes this workgroup's share (the last one; the other waves get
+// nothing of use).  One barrier, which also orders what was read from LDS before it against the coming exchange.
+__device__ __forceinline__ double sp_share_of_c(double cabs, const SpShared& sh)
+{
+    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+    cabs = sp_wave_sum(cabs);
+    if (lane == 0) sh.cred[wv] = cabs;
     __syncthreads();
-    const double r = scratch[0];
-    __syncthreads();
-    return r;
+    double c = 0.0;
+    if (wv == kSpWaves - 1) {
+        double q[kSpWaves];
+#pragma unroll
+        for (int i = 0; i < kSpWaves; ++i) q[i] = sh.cred[i];
+#pragma unroll
+        for (int i = 0; i < kSpWaves; ++i) c += q[i];
+    }
+    return c;
 }
 
 template <typename TE>
@@ -525,7 +571,8 @@ __global__ void __launch_bounds__(kSpThreads) sparse_kernel(SparseArgs a)
         sh.accv = (double*)take((size_t)kSpThreads * 8);
         sh.red = (double*)take((size_t)kSpThreads * 8);
         sh.scal = (uint32_t*)take((size_t)2 * kSpGrid * 2 * 4);
-        sh.scan = (int*)take((size_t)(kSpWaves + 1) * 4);
+        sh.cred = (double*)take((size_t)kSpWaves * 8);
+        sh.scan = (int*)take((size_t)(kSpWaves + 2) * 4);
     }
     for (int64_t i = tid; i < mwords32 + 2; i += kSpThreads) {
         sh.sA[i] = 0;
@@ -535,6 +582,7 @@ __global__ void __launch_bounds__(kSpThreads) sparse_kernel(SparseArgs a)
         sh.tA[i] = 0;
         sh.tB[i] = 0;
     }
+    if (tid == 0) sh.scan[kSpFail] = 0;
     __syncthreads();
     uint32_t *s_cur = sh.sA, *s_oth = sh.sB, *t_cur = sh.tA, *t_oth = sh.tB;
 
@@ -551,6 +599,9 @@ __global__ void __launch_bounds__(kSpThreads) sparse_kernel(SparseArgs a)
     uint32_t seq = a.seq;
     int alternations = 0, updates = 0, warn = 0, spins = 0;
     int64_t flips = 0, flips_rows = 0;
+    bool late = false;
+    const int wait0 = a.poll_delay << kSpWaitShift;  // of the exchanges behind a dense pass
+    int waits = wait0, waitt = wait0;
     bool pending = false;  // a finished term waits to be subtracted
     double ck = 0.0;
     const bool prof = a.profile && g == 0 && tid == 0;
@@ -579,13 +630,13 @@ __global__ void __launch_bounds__(kSpThreads) sparse_kernel(SparseArgs a)
         // rows I_g of R: R <- R - ck s t^T (Algorithm 5 line 10), squares, u = R t_0 (Algorithm 4 line 5)
         if (rlen > 0) sp_dense_rows<TE>(R, n, i0, rlen, pending, s_cur, t_cur, ckt, t_oth, sh.accu, fsq, sh.red);
         const bool was_pending = pending;
-        if (!sp_exchange(a, ++seq, sh.accu, rlen, rs, m, fsq, true, s_oth, sh, spins, was_pending)) {
+        if (!sp_exchange(a, ++seq, sh.accu, rlen, rs, m, fsq, true, s_oth, sh, spins, was_pending, wait0, late)) {
             if (tid == 0) atomicExch((unsigned*)&a.res->err, 1u);
             return;
         }
         ++alternations;
         if (pending) {
-            const double F = sp_sum_scalar(sh, sh.red, a.grid);
+            const double F = sp_sum_scalar(sh, a.grid);
             if (g == 0 && tid == 0) a.trace[k] = sqrt(F);
         }
         // rows J_g of RT (columns of R): same update, v = R^T s_1 (Algorithm 4 line 6)
@@ -606,25 +657,20 @@ __global__ void __launch_bounds__(kSpThreads) sparse_kernel(SparseArgs a)
         bool handover = was_pending;  // RT was rewritten: the next exchange carries the fences
         for (;;) {
             // ---- finish the column half: t = sgn(v), c = sum |v| (Algorithm 4 lines 6-7), all-gather
-            double cabs = (tid < clen) ? fabs(sh.accv[tid]) : 0.0;
-            cabs = sp_wave_sum(cabs);
-            __syncthreads();
-            if (lane == 0) sh.red[wv] = cabs;
-            __syncthreads();
-            double cpart = 0.0;
-            for (int q = 0; q < kSpWaves; ++q) cpart += sh.red[q];
-            __syncthreads();
-            if (!sp_exchange(a, ++seq, sh.accv, clen, cs, n, cpart, true, t_oth, sh, spins, handover)) {
+            const double cabs = (tid < clen) ? fabs(sh.accv[tid]) : 0.0;
+            const double cpart = sp_share_of_c(cabs, sh);
+            if (!sp_exchange(a, ++seq, sh.accv, clen, cs, n, cpart, true, t_oth, sh, spins, handover, waitt, late)) {
                 if (tid == 0) atomicExch((unsigned*)&a.res->err, 1u);
                 return;
             }
+            if (!handover) waitt = sp_adapt(waitt, late);
             handover = false;
             {
                 uint32_t* z = t_cur; t_cur = t_oth; t_oth = z;  // t_cur = t_j, t_oth = t_{j-1}
             }
             ++j;
             SP_TICK(1)
-            const double c = sp_sum_scalar(sh, sh.red, a.grid);
+            const double c = sp_sum_scalar(sh, a.grid);
             // ---- Algorithm 4 line 8
             if (c <= c_prev || j >= a.max_iters) {
                 if (!(c <= c_prev)) warn = 1;
@@ -650,10 +696,11 @@ __global__ void __launch_bounds__(kSpThreads) sparse_kernel(SparseArgs a)
             SP_TICK(2)
             sp_accumulate_flips<TE>(RT, m, i0, rlen, t_cur, t_oth, n, sh.accu, sh, flips);
             SP_TICK(3)
-            if (!sp_exchange(a, ++seq, sh.accu, rlen, rs, m, 0.0, false, s_oth, sh, spins, false)) {
+            if (!sp_exchange(a, ++seq, sh.accu, rlen, rs, m, 0.0, false, s_oth, sh, spins, false, waits, late)) {
                 if (tid == 0) atomicExch((unsigned*)&a.res->err, 1u);
                 return;
             }
+            waits = sp_adapt(waits, late);
             SP_TICK(4)
             {
                 uint32_t* z = s_cur; s_cur = s_oth; s_oth = z;  // s_cur = s_{j+1}
@@ -707,7 +754,8 @@ struct SpPending {
 // reads R anyway, and the dense start of those terms then reads only the transposed copy.
 constexpr int kSpAhead = 8;
 
-// ej[j] = coef[j] * <p_j, cur> for the np pending vectors of one side, 0 for j >= np
+// ej[j] = coef[j] * <p_j, cur> for the np pending vectors of one side, 0 for j >= np (a barrier has to follow before
+// they are read)
 __device__ void sp_pending_dots(const uint32_t* P, int stride, int nwords32, int64_t nbits, const uint32_t* cur, int np,
                                 int width, const double* coef, double* ej)
 {
@@ -722,7 +770,6 @@ __device__ void sp_pending_dots(const uint32_t* P, int stride, int nwords32, int
         cnt = sp_wave_sum_int(cnt);
         if (lane == 0) ej[j] = coef[j] * (double)(nbits - 2 * (int64_t)cnt);
     }
-    __syncthreads();
 }
 
 // eff[tid] = acc[tid] - sum_j ej[j] * (sign of pending vector j at this thread's entry), in the order
@@ -916,7 +963,8 @@ __global__ void __launch_bounds__(kSpThreads) sparse_delay_kernel(SparseArgs a)
         sh.accv = (double*)take((size_t)kSpThreads * 8);
         sh.red = (double*)take((size_t)kSpThreads * 8);
         sh.scal = (uint32_t*)take((size_t)2 * kSpGrid * 2 * 4);
-        sh.scan = (int*)take((size_t)(kSpWaves + 1) * 4);
+        sh.cred = (double*)take((size_t)kSpWaves * 8);
+        sh.scan = (int*)take((size_t)(kSpWaves + 2) * 4);
         pd.ps_stride = (int)mwords32 + 1;
         pd.pt_stride = (int)nwords32 + 1;
         pd.coef = (double*)take(32 * 8);
@@ -937,6 +985,7 @@ __global__ void __launch_bounds__(kSpThreads) sparse_delay_kernel(SparseArgs a)
         sh.tA[i] = 0;
         sh.tB[i] = 0;
     }
+    if (tid == 0) sh.scan[kSpFail] = 0;
     __syncthreads();
     uint32_t *s_cur = sh.sA, *s_oth = sh.sB, *t_cur = sh.tA, *t_oth = sh.tB;
 
@@ -953,6 +1002,9 @@ __global__ void __launch_bounds__(kSpThreads) sparse_delay_kernel(SparseArgs a)
     uint32_t seq = a.seq;
     int alternations = 0, updates = 0, warn = 0, spins = 0;
     int64_t flips = 0, flips_rows = 0;
+    bool late = false;
+    const int wait0 = a.poll_delay << kSpWaitShift;  // of the exchanges behind a dense pass
+    int waits = wait0, waitt = wait0;
     int np = 0;  // pending terms
     int ahead = 0, ahead_made = 0;  // first products R' t_0 formed in advance: still unused / formed by the last pass
     uint32_t own_u = 0u, own_v = 0u;  // their signs at this thread's row of I_g / column of J_g, bit j for term j
@@ -1008,15 +1060,16 @@ __global__ void __launch_bounds__(kSpThreads) sparse_delay_kernel(SparseArgs a)
             if (tid < rlen) pd.effu[tid] = sh.accu[tid];
         } else {
             sp_pending_dots(pd.PT, pd.pt_stride, (int)nwords32, n, t_oth, np, width, pd.coef, pd.ej);
+            __syncthreads();
             sp_effective(sh.accu, rlen, own_u, pd.ej, width, pd.effu);
         }
-        if (!sp_exchange(a, ++seq, pd.effu, rlen, rs, m, fsq, flush, s_oth, sh, spins, flush)) {
+        if (!sp_exchange(a, ++seq, pd.effu, rlen, rs, m, fsq, flush, s_oth, sh, spins, flush, wait0, late)) {
             if (tid == 0) atomicExch((unsigned*)&a.res->err, 1u);
             return;
         }
         ++alternations;
         if (flush) {
-            F = sp_sum_scalar(sh, sh.red, a.grid);  // measured again
+            F = sp_sum_scalar(sh, a.grid);  // measured again
             if (g == 0 && tid == 0) a.trace[k] = sqrt(F);
         }
         // rows J_g of the transposed copy: v = R^T s_1 (Algorithm 4 line 6)
@@ -1034,6 +1087,7 @@ __global__ void __launch_bounds__(kSpThreads) sparse_delay_kernel(SparseArgs a)
             if (clen > 0)
                 sp_dense_rows<TE>(RT, m, j0, clen, false, t_cur, s_cur, (TE)0, s_oth, sh.accv, dummy, sh.red);
             sp_pending_dots(pd.PS, pd.ps_stride, (int)mwords32, m, s_oth, np, width, pd.coef, pd.ej);
+            __syncthreads();
             sp_effective(sh.accv, clen, own_v, pd.ej, width, pd.effv);
         }
         {
@@ -1045,24 +1099,19 @@ __global__ void __launch_bounds__(kSpThreads) sparse_delay_kernel(SparseArgs a)
         bool handover = flush;  // the transposed copy was rewritten: the next exchange carries the fences
         for (;;) {
             // ---- finish the column half: t = sgn(v), c = sum |v| (Algorithm 4 lines 6-7), all-gather
-            double cabs = (tid < clen) ? fabs(pd.effv[tid]) : 0.0;
-            cabs = sp_wave_sum(cabs);
-            __syncthreads();
-            if (lane == 0) sh.red[wv] = cabs;
-            __syncthreads();
-            double cpart = 0.0;
-            for (int q = 0; q < kSpWaves; ++q) cpart += sh.red[q];
-            __syncthreads();
-            if (!sp_exchange(a, ++seq, pd.effv, clen, cs, n, cpart, true, t_oth, sh, spins, handover)) {
+            const double cabs = (tid < clen) ? fabs(pd.effv[tid]) : 0.0;
+            const double cpart = sp_share_of_c(cabs, sh);
+            if (!sp_exchange(a, ++seq, pd.effv, clen, cs, n, cpart, true, t_oth, sh, spins, handover, waitt, late)) {
                 if (tid == 0) atomicExch((unsigned*)&a.res->err, 1u);
                 return;
             }
+            if (!handover) waitt = sp_adapt(waitt, late);
             handover = false;
             {
                 uint32_t* z = t_cur; t_cur = t_oth; t_oth = z;
             }
             ++j;
-            const double c = sp_sum_scalar(sh, sh.red, a.grid);
+            const double c = sp_sum_scalar(sh, a.grid);
             // ---- Algorithm 4 line 8
             if (c <= c_prev || j >= a.max_iters) {
                 if (!(c <= c_prev)) warn = 1;
@@ -1096,20 +1145,22 @@ __global__ void __launch_bounds__(kSpThreads) sparse_delay_kernel(SparseArgs a)
             }
             c_prev = c;
             // ---- row half, sparse: u' += 2 sum over flipped columns (rows of the transposed copy), correction, s
-            sp_accumulate_flips<TE>(RT, m, i0, rlen, t_cur, t_oth, n, sh.accu, sh, flips);
+            // (the products go first: the barriers of the compaction publish them)
             sp_pending_dots(pd.PT, pd.pt_stride, (int)nwords32, n, t_cur, np, width, pd.coef, pd.ej);
+            sp_accumulate_flips<TE>(RT, m, i0, rlen, t_cur, t_oth, n, sh.accu, sh, flips);
             sp_effective(sh.accu, rlen, own_u, pd.ej, width, pd.effu);
-            if (!sp_exchange(a, ++seq, pd.effu, rlen, rs, m, 0.0, false, s_oth, sh, spins, false)) {
+            if (!sp_exchange(a, ++seq, pd.effu, rlen, rs, m, 0.0, false, s_oth, sh, spins, false, waits, late)) {
                 if (tid == 0) atomicExch((unsigned*)&a.res->err, 1u);
                 return;
             }
+            waits = sp_adapt(waits, late);
             {
                 uint32_t* z = s_cur; s_cur = s_oth; s_oth = z;
             }
             ++alternations;
             // ---- column half, sparse: v' += 2 sum over flipped rows, correction
-            sp_accumulate_flips<TE>(R, n, j0, clen, s_cur, s_oth, m, sh.accv, sh, flips_rows);
             sp_pending_dots(pd.PS, pd.ps_stride, (int)mwords32, m, s_cur, np, width, pd.coef, pd.ej);
+            sp_accumulate_flips<TE>(R, n, j0, clen, s_cur, s_oth, m, sh.accv, sh, flips_rows);
             sp_effective(sh.accv, clen, own_v, pd.ej, width, pd.effv);
         }
     }
@@ -1146,7 +1197,7 @@ size_t sparse_lds_bytes(int64_t m, int64_t n, int delay_width)
     auto al = [](size_t b) { return (b + 15) & ~(size_t)15; };
     const size_t mw = (size_t)((m + 31) >> 5), nw = (size_t)((n + 31) >> 5);
     size_t b = 2 * al(mw * 4 + 8) + 2 * al(nw * 4 + 8) + al((size_t)kSpListCap * 2) + 3 * al((size_t)kSpThreads * 8) +
-               al((size_t)2 * kSpGrid * 2 * 4) + al((size_t)(kSpWaves + 1) * 4);
+               al((size_t)2 * kSpGrid * 2 * 4) + al((size_t)kSpWaves * 8) + al((size_t)(kSpWaves + 2) * 4);
     if (delay_width > 0)
         b += 2 * al(32 * 8) + 2 * al((size_t)kSpThreads * 8) + al(16) + al((size_t)delay_width * (mw + 1) * 4) +
              al((size_t)delay_width * (nw + 1) * 4) + al((size_t)kSpAhead * (nw + 1) * 4) +
@@ -1175,7 +1226,7 @@ bool sparse_supported(scd_dtype dt, int order, const int64_t* dims, int grid, in
     return true;
 }
 
-size_t sparse_xbuf_bytes() { return (size_t)2 * kSpGrid * kSpSlot * 8; }
+size_t sparse_xbuf_bytes() { return (size_t)2 * kSpHalfWords * 8; }
 
 hipError_t launch_transpose(const void* in, void* out, scd_dtype dt, int64_t rows, int64_t cols, hipStream_t st)
 {

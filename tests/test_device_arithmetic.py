@@ -6,15 +6,15 @@ They restate what the kernels do in numpy and check it exhaustively, so that a c
 import numpy as np
 
 
-def test_item_to_member_by_float_product_is_exact():
-    # the exchange maps item -> (member, word) with floor((item + 0.5) * (1 / per)) in f32 instead of an
-    # integer division: exact for every slot width the engine can have (1..18 words) and every item a thread
-    # can own (6 items x 512 threads)
-    for per in range(1, 19):
-        r = np.float32(1.0) / np.float32(per)
+def test_item_to_word_by_float_product_is_exact():
+    # the exchange maps item -> (word, member) with floor((item + 0.5) * (1 / grid)) in f32 instead of an
+    # integer division: exact for every number of workgroups (1..256) and every item a thread can own
+    # (6 items x 512 threads)
+    for grid in range(1, 257):
+        r = np.float32(1.0) / np.float32(grid)
         idx = np.arange(0, 6 * 512, dtype=np.int32)
-        mem = ((idx.astype(np.float32) + np.float32(0.5)) * r).astype(np.int32)
-        assert np.array_equal(mem, idx // per), per
+        word = ((idx.astype(np.float32) + np.float32(0.5)) * r).astype(np.int32)
+        assert np.array_equal(word, idx // grid), grid
 
 
 def test_halving_butterfly_leaves_sum_i_in_lane_pair_i():
