@@ -15,6 +15,7 @@
 //               terms, y_i = sum_j +-z_j
 //   reduce      y = sum of the splits, in order, rounded once to the output type
 // Every sum has a fixed order: results are bit-identical from run to run.
+#include "scd_bits.h"
 #include "scd_device.h"
 
 namespace scd {
@@ -47,25 +48,13 @@ __device__ __forceinline__ double ap_dpp_xor_f64(double v)
     const uint32_t lo = ap_dpp_xor<D>((uint32_t)b), hi = ap_dpp_xor<D>((uint32_t)(b >> 32));
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
-// (a, b) = the values of the two partners at distance D = 16 or 32, the same pair in both of them
-template <int D>
-__device__ __forceinline__ void ap_swap_pair(uint32_t v, uint32_t& a, uint32_t& b)
-{
-    if constexpr (D == 16) {
-        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-        a = r[0], b = r[1];
-    } else {
-        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-        a = r[0], b = r[1];
-    }
-}
 template <int D>
 __device__ __forceinline__ void ap_swap_pair_f64(double v, double& a, double& b)
 {
     const unsigned long long w = (unsigned long long)__double_as_longlong(v);
     uint32_t la, lb, ha, hb;
-    ap_swap_pair<D>((uint32_t)w, la, lb);
-    ap_swap_pair<D>((uint32_t)(w >> 32), ha, hb);
+    swap_pair<D>((uint32_t)w, la, lb);
+    swap_pair<D>((uint32_t)(w >> 32), ha, hb);
     a = __longlong_as_double((long long)(((unsigned long long)ha << 32) | la));
     b = __longlong_as_double((long long)(((unsigned long long)hb << 32) | lb));
 }
@@ -101,9 +90,9 @@ __device__ __forceinline__ float ap_wave_max(float a)
     a = fmaxf(a, __uint_as_float(ap_dpp_xor<4>(__float_as_uint(a))));
     a = fmaxf(a, __uint_as_float(ap_dpp_xor<8>(__float_as_uint(a))));
     uint32_t p, q;
-    ap_swap_pair<16>(__float_as_uint(a), p, q);
+    swap_pair<16>(__float_as_uint(a), p, q);
     a = fmaxf(__uint_as_float(p), __uint_as_float(q));
-    ap_swap_pair<32>(__float_as_uint(a), p, q);
+    swap_pair<32>(__float_as_uint(a), p, q);
     return fmaxf(__uint_as_float(p), __uint_as_float(q));
 }
 
@@ -409,64 +398,6 @@ constexpr int kApFxMaxTerms = 2048;  // terms per split: one group of four per t
 // digits of one kind are kApFxPitch words apart: the four that a wave reads together fall into different banks
 constexpr int kApFxPitch = kApFxMaxTerms / 4 + 4;
 
-// 64 x 64 bit transpose across a wave: lane q brings row q (bit i = column i), lane i leaves with column i.
-// Six butterfly stages (distance 32, 16, .., 1): in every 2s x 2s block the two off-diagonal s x s blocks
-// change places, the partner row is s lanes away.  The rows are kept as two 32-bit halves; below distance
-// 32 a stage is, per half, one lane exchange, one rotate (the partner's bits move s columns up in the
-// upper row, s down in the lower) and one bitfield insert.  Distances 1..8 stay within a row of 16 lanes
-// and use the data-parallel lane modes, distances 16 and 32 the row-swap instructions (no LDS traffic).
-template <int S>
-__device__ __forceinline__ uint32_t ap_lane_xor(uint32_t v, int lane)
-{
-    if constexpr (S == 1) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true);  // quad_perm 1,0,3,2
-    else if constexpr (S == 2) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true);  // quad_perm 2,3,0,1
-    else if constexpr (S == 4) {
-        // lane ^ 7 (mirror of half a row), then lane ^ 3 (quad_perm 3,2,1,0)
-        const int h = __builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, true);
-        return (uint32_t)__builtin_amdgcn_mov_dpp(h, 0x1B, 0xF, 0xF, true);
-    } else if constexpr (S == 8) {
-        // lane ^ 15 (mirror of a row), then lane ^ 7
-        const int h = __builtin_amdgcn_mov_dpp((int)v, 0x140, 0xF, 0xF, true);
-        return (uint32_t)__builtin_amdgcn_mov_dpp(h, 0x141, 0xF, 0xF, true);
-    } else {
-        // distance 16 or 32: the row swap leaves (value of the lower partner, value of the upper partner) in
-        // both lanes; each takes the other's
-        uint32_t a, b;
-        ap_swap_pair<S>(v, a, b);
-        return (lane & S) ? a : b;
-    }
-}
-
-template <int S>
-__device__ __forceinline__ uint32_t ap_butterfly(uint32_t h, int lane)
-{
-    constexpr uint32_t m = S == 16 ? 0x0000FFFFu : S == 8 ? 0x00FF00FFu : S == 4 ? 0x0F0F0F0Fu : S == 2 ? 0x33333333u : 0x55555555u;
-    const bool lower = (lane & S) != 0;
-    const uint32_t p = ap_lane_xor<S>(h, lane);
-    const uint32_t rot = __builtin_amdgcn_alignbit(p, p, lower ? S : 32 - S);  // partner >> S (lower row), << S (upper)
-    const uint32_t keep = lower ? ~m : m;
-    return (h & keep) | (rot & ~keep);
-}
-
-__device__ __forceinline__ uint64_t ap_transpose64(uint64_t x, int lane)
-{
-    uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
-    {
-        // distance 32: the upper rows take the partner's low half as their high half, the lower rows the
-        // partner's high half as their low half
-        const bool lower = (lane & 32) != 0;
-        const uint32_t got = ap_lane_xor<32>(lower ? lo : hi, lane);
-        lo = lower ? got : lo;
-        hi = lower ? hi : got;
-    }
-    lo = ap_butterfly<16>(lo, lane), hi = ap_butterfly<16>(hi, lane);
-    lo = ap_butterfly<8>(lo, lane), hi = ap_butterfly<8>(hi, lane);
-    lo = ap_butterfly<4>(lo, lane), hi = ap_butterfly<4>(hi, lane);
-    lo = ap_butterfly<2>(lo, lane), hi = ap_butterfly<2>(hi, lane);
-    lo = ap_butterfly<1>(lo, lane), hi = ap_butterfly<1>(hi, lane);
-    return ((uint64_t)hi << 32) | lo;
-}
-
 __global__ void __launch_bounds__(kApMfmaWaves* kWave)
     apply_outer_mfma_kernel(const uint64_t* __restrict__ bits, int64_t mw, int64_t w, const double* __restrict__ part,
                             int chunks, const float* __restrict__ c, int64_t terms_per_split, double* __restrict__ ypart)
@@ -543,7 +474,7 @@ __global__ void __launch_bounds__(kApMfmaWaves* kWave)
     for (int t = 0; t < ntiles; ++t) {
         const uint64_t mine = next;
         if (t + 1 < ntiles) next = fetch(t + 1);
-        const uint64_t col = ap_transpose64(mine, lane);  // bit q: sign of term (tile + q) at this lane's entry
+        const uint64_t col = transpose64(mine, lane);  // bit q: sign of term (tile + q) at this lane's entry
         const uint32_t half[2] = {(uint32_t)col, (uint32_t)(col >> 32)};
         // this lane's digit of the tile's 16 groups of four terms (four 16-byte reads)
         const ap_int4* zq = (const ap_int4*)(zd + jd * kApFxPitch + t * 16);

@@ -247,6 +247,10 @@ hipError_t launch_scalars_update(void* r, scd_dtype dt, int64_t total, int64_t q
 hipError_t launch_lsq_solve(double* L, int64_t ld, int64_t k, const double* g, double diag, const double* bvec, double* yv,
                             double* c, double* work, double fro0sq, double* trace_out, int* status, hipStream_t st);
 
+// ---- expansion of the packed factors (scd_expand.hip)
+hipError_t launch_expand(const uint64_t* S, const uint64_t* T, const void* c, scd_dtype dt, int64_t m,
+                         int64_t n, int64_t w, void* out, hipStream_t st);
+
 // ---- launchers implemented in scd_kernels.hip ----------------------------------------------------
 hipError_t launch_rowpass(const RowPassArgs& a, scd_dtype dt, int grid, int variant, hipStream_t st);
 hipError_t launch_reduce(const ReduceArgs& a, bool f32_partials, hipStream_t st);
@@ -256,8 +260,6 @@ hipError_t launch_unpack(const uint64_t* bits, int64_t n, scd_dtype dt, void* va
 hipError_t launch_rng(uint64_t seed, uint64_t term, uint32_t mode, int64_t n, uint64_t* bits, hipStream_t st);
 hipError_t launch_kron_terms(int order, const int64_t* dims, const uint64_t* const* signs, int64_t w,
                              uint64_t* out, int64_t cols, hipStream_t st);
-hipError_t launch_expand(const uint64_t* S, const uint64_t* T, const void* c, scd_dtype dt, int64_t m,
-                         int64_t n, int64_t w, void* out, hipStream_t st);
 hipError_t launch_halfstep(const void* R, scd_dtype dt, int64_t m, int64_t n, int rows_per_wg, int grid, int do_rows,
                            const uint64_t* sumbits, const uint64_t* rowbits, void* partials, double* u, hipStream_t st);
 hipError_t launch_reduce_plain(const void* partials, scd_dtype dt, int nparts, int64_t cols, double* W, uint64_t* bits,

@@ -765,45 +765,6 @@ __global__ void __launch_bounds__(kBlock) kron_terms_kernel(KronTermsArgs a)
 }
 
 // ------------------------------------------------------------------------------------------------
-// expand: out[i][l] = sum_j c_j s_j[i] t_j[l], terms added in order into an f64 accumulator.
-// A wave owns 64 columns (one word of t_j) and 32 rows (half a word of s_j).
-
-constexpr int kExpRows = 32;
-
-template <typename TE>
-__global__ void __launch_bounds__(kBlock)
-    expand_kernel(const uint64_t* __restrict__ S, const uint64_t* __restrict__ T, const TE* __restrict__ c, int64_t m,
-                  int64_t n, int64_t w, TE* __restrict__ out)
-{
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int64_t cw = blockIdx.x;                                             // column word
-    const int64_t rt = (int64_t)blockIdx.y * kWavesPerBlock + wv;              // row tile of 32
-    const int64_t row0 = rt * kExpRows;
-    if (row0 >= m) return;
-    const int64_t mw = (m + 63) / 64, nw = (n + 63) / 64;
-    const int64_t sw = row0 >> 6;
-    const int sh = (int)(row0 & 63);
-    double acc[kExpRows];
-#pragma unroll
-    for (int r = 0; r < kExpRows; ++r) acc[r] = 0.0;
-    for (int64_t j = 0; j < w; ++j) {
-        const uint64_t tw = T[j * nw + cw];
-        const uint32_t sbits = (uint32_t)(S[j * mw + sw] >> sh);
-        const double cj = (double)c[j];
-        const double cl = flip(cj, (uint32_t)((tw >> lane) & 1ull));
-#pragma unroll
-        for (int r = 0; r < kExpRows; ++r) acc[r] += flip(cl, (sbits >> r) & 1u);
-    }
-    const int64_t col = cw * 64 + lane;
-    if (col < n) {
-#pragma unroll
-        for (int r = 0; r < kExpRows; ++r)
-            if (row0 + r < m) out[(row0 + r) * n + col] = (TE)acc[r];
-    }
-}
-
-// ------------------------------------------------------------------------------------------------
 // bitset utilities (Section 3.1)
 
 template <typename TE>
@@ -1010,18 +971,6 @@ hipError_t launch_kron_terms(int order, const int64_t* dims, const uint64_t* con
     a.out = out;
     const int grid = grid_for(w * ((cols + 63) / 64), kWavesPerBlock, 8192);
     hipLaunchKernelGGL(kron_terms_kernel, dim3(grid), dim3(kBlock), 0, st, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_expand(const uint64_t* S, const uint64_t* T, const void* c, scd_dtype dt, int64_t m, int64_t n,
-                         int64_t w, void* out, hipStream_t st)
-{
-    const int64_t tiles = (m + kExpRows - 1) / kExpRows;
-    dim3 grid((unsigned)((n + 63) / 64), (unsigned)((tiles + kWavesPerBlock - 1) / kWavesPerBlock));
-    if (dt == SCD_F32)
-        hipLaunchKernelGGL((expand_kernel<float>), grid, dim3(kBlock), 0, st, S, T, (const float*)c, m, n, w, (float*)out);
-    else
-        hipLaunchKernelGGL((expand_kernel<double>), grid, dim3(kBlock), 0, st, S, T, (const double*)c, m, n, w, (double*)out);
     return hipGetLastError();
 }
 

@@ -79,6 +79,38 @@ def test_expand_bit_exact(scd, oracle, shape, w, dtype):
     assert got.dtype == dtype and np.array_equal(got, ref)
 
 
+@pytest.mark.parametrize("shape,w", [((1, 1), 1), ((127, 63), 63), ((128, 64), 64), ((129, 65), 65), ((200, 300), 129),
+                                     ((64, 129), 700), ((40, 9, 7), 66)])
+@pytest.mark.parametrize("bits", [24, 30, 31, 38, 39, 60])
+def test_expand_bit_exact_over_the_span_of_the_coefficients(scd, oracle, shape, w, bits):
+    # f32 coefficients that span `bits` bits from the highest to the lowest one set: 30 is the last span of four int8
+    # digits, 38 of five, above that the sums are f64; a span of 53 - log2(w) bits is the last with exact sums
+    rs = np.random.Generator(np.random.PCG64(w + bits))
+    signs = [np.stack([oracle.pack(rs.standard_normal(d)) for _ in range(w)]) for d in shape]
+    mant = rs.integers(1 << 23, 1 << 24, w) | 1                    # 24 significant bits
+    ex = rs.integers(0, bits - 23, w)
+    ex[0], ex[-1] = 0, bits - 24
+    c = (np.ldexp(mant.astype(np.float64), ex - 30) * rs.choice([-1.0, 1.0], w)).astype(np.float32)
+    if w > 10:
+        c[w // 2] = 0.0
+        c[3] = 2.0 ** -20                                           # (a power of two: trailing zeros only)
+    got = scd.scd_expand([to_dev_bits(s) for s in signs], dev(c), shape).cpu().numpy()
+    ref = oracle.expand(signs, c.astype(np.float64), shape).astype(np.float32)
+    assert np.array_equal(got, ref)
+
+
+def test_expand_bit_exact_at_the_ends_of_the_exponents(scd, oracle):
+    rs = np.random.Generator(np.random.PCG64(3))
+    signs = [np.stack([oracle.pack(rs.standard_normal(d)) for _ in range(70)]) for d in (66, 70)]
+    db = [to_dev_bits(s) for s in signs]
+    for c in (rs.integers(1, 1 << 20, 70).astype(np.float32) * np.float32(2.0 ** -149), np.float32(3e38) * rs.random(70).astype(np.float32),
+              np.zeros(70, np.float32), rs.standard_normal(70) * 1e-309, rs.standard_normal(70) * 1e300):
+        ref = oracle.expand(signs, c.astype(np.float64), (66, 70))
+        with np.errstate(over="ignore"):
+            ref = ref.astype(c.dtype)
+        assert np.array_equal(scd.scd_expand(db, dev(c), (66, 70)).cpu().numpy(), ref)
+
+
 def test_expand_zero_terms(scd):
     out = scd.scd_expand([torch.zeros((0, 1), dtype=torch.int64, device="cuda")] * 2,
                          torch.zeros(0, dtype=torch.float32, device="cuda"), (40, 50))
