@@ -1401,6 +1401,117 @@ int check_tensor_args(const void* A, scd_dtype dt, int order, const int64_t* dim
 
 }  // namespace
 
+// ---------------------------------------------------------------------------------------------- Algorithm 6, device loop
+
+namespace {
+
+// The sweeps are enqueued blindly, about as many as the terms so far took; launches past the end return at once.
+int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uint64_t seed, int32_t max_iters, hipStream_t st, uint64_t* S,
+               uint64_t* T, void* cvec, double* fro_trace, int32_t* iters)
+{
+    const int64_t mw = words_for(m), nw = words_for(n);
+    const int nsq = 256;
+    struct Pinned {
+        LsqState state;
+        double scal[2];
+    };
+    // one block: every array of doubles or words, then the iteration counts and the state
+    const size_t words = (size_t)(mw + nw + 2 * nw + w * w + 3 * w + nsq + 2);
+    const size_t bytes = words * 8 + (((size_t)w * 4 + 15) & ~(size_t)15) + sizeof(LsqState);
+    void* dev = nullptr;
+    Pinned* pin = nullptr;
+    hipError_t e = hipMalloc(&dev, bytes);
+    if (e == hipSuccess) e = hipHostMalloc((void**)&pin, sizeof(Pinned), hipHostMallocDefault);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        if (dev) (void)hipFree(dev);
+        return SCD_ENOMEM;
+    }
+    auto cleanup = [&](int code) {
+        (void)hipStreamSynchronize(st);
+        (void)hipFree(dev);
+        (void)hipHostFree(pin);
+        (void)hipGetLastError();
+        return code;
+    };
+#define LM(expr)                              \
+    do {                                      \
+        hipError_t _e = (expr);               \
+        if (_e != hipSuccess) {               \
+            g_last_hip = (int)_e;             \
+            (void)hipGetLastError();          \
+            return cleanup(SCD_EHIP);         \
+        }                                     \
+    } while (0)
+    uint64_t* p = (uint64_t*)dev;
+    auto take = [&](int64_t n_words) {
+        uint64_t* q = p;
+        p += n_words;
+        return q;
+    };
+    LsqMatArgs a;
+    memset(&a, 0, sizeof(a));
+    a.A = A;
+    a.m = m;
+    a.n = n;
+    a.w = w;
+    a.seed = seed;
+    a.max_iters = max_iters;
+    a.S = S;
+    a.T = T;
+    a.s = take(mw);
+    a.t = take(nw);
+    a.abs_parts = (double*)take(nw);
+    a.dot_parts = (double*)take(nw);
+    a.L = (double*)take(w * w);
+    a.yv = (double*)take(w);
+    a.c = (double*)take(w);
+    a.bvec = (double*)take(w);
+    double* sq = (double*)take(nsq);
+    double* scal = (double*)take(2);
+    a.trace = fro_trace;
+    a.iters = (int32_t*)p;
+    a.st = (LsqState*)((char*)p + (((size_t)w * 4 + 15) & ~(size_t)15));
+
+    LM(launch_lsq_sumsq(A, dt, m * n, sq, nsq, st));
+    LM(launch_lsq_sum2(sq, nullptr, nsq, scal, st));
+    LM(hipMemcpyAsync(pin->scal, scal, 16, hipMemcpyDeviceToHost, st));
+    LM(hipStreamSynchronize(st));
+    a.fro0sq = pin->scal[0];
+    if (!isfinite(a.fro0sq)) return cleanup(SCD_ENONFINITE);
+    pin->scal[0] = sqrt(a.fro0sq);
+    memset(&pin->state, 0, sizeof(LsqState));
+    pin->state.c_prev = -INFINITY;
+    LM(hipMemcpyAsync(fro_trace, pin->scal, 8, hipMemcpyHostToDevice, st));
+    LM(hipMemcpyAsync(a.st, &pin->state, sizeof(LsqState), hipMemcpyHostToDevice, st));
+    LM(launch_rng(seed, 0, 1u, n, a.t, st));
+    LM(hipStreamSynchronize(st));  // (the pinned block receives the state from here on)
+    double per_term = 12.0;
+    int64_t swept = 0;
+    const double bound = ((double)w + 1.0) * ((double)max_iters + 1.0);
+    for (;;) {
+        const double want = per_term * (double)(w - pin->state.k);
+        const int batch = want < 4.0 ? 4 : (want > 96.0 ? 96 : (int)want);
+        for (int b = 0; b < batch; ++b) LM(launch_lsq_sweep(a, dt, st));
+        swept += batch;
+        LM(hipMemcpyAsync(&pin->state, a.st, sizeof(LsqState), hipMemcpyDeviceToHost, st));
+        LM(hipStreamSynchronize(st));
+        if (pin->state.done) break;
+        if ((double)swept > bound + batch) return cleanup(SCD_EINVAL);  // cannot happen: the device loop is bounded
+        if (pin->state.k > 0) per_term = (double)swept / (double)pin->state.k;
+    }
+    const LsqState fin = pin->state;
+    if (fin.status == 2) return cleanup(SCD_ENONFINITE);
+    if (fin.status == 1) return cleanup(SCD_ESINGULAR);
+    LM(launch_lsq_cast(a.c, w, dt, cvec, st));
+    if (iters) LM(hipMemcpyAsync(iters, a.iters, (size_t)w * 4, hipMemcpyDeviceToDevice, st));
+    LM(hipStreamSynchronize(st));
+#undef LM
+    return cleanup(fin.warn ? SCD_WMAXITER : SCD_OK);
+}
+
+}  // namespace
+
 // ---------------------------------------------------------------------------------------------- Algorithms 6 and 14
 
 int scd_lsq_decompose_tensor(const void* A, scd_dtype dt, int order, const int64_t* dims, int64_t w, uint64_t seed,
@@ -1412,6 +1523,8 @@ int scd_lsq_decompose_tensor(const void* A, scd_dtype dt, int order, const int64
     if (w > SCD_LSQ_MAX_WIDTH || (w > 0 && (!signs || !cvec))) return SCD_EINVAL;
     for (int i = 0; i < order; ++i)
         if (w > 0 && !signs[i]) return SCD_EINVAL;
+    if (order == 2 && w > 0 && lsq_matrix_supported(dt, dims[0], dims[1]))
+        return lsq_matrix(A, dt, dims[0], dims[1], w, seed, max_iters, (hipStream_t)stream, signs[0], signs[1], cvec, fro_trace, iters);
     hipStream_t st = (hipStream_t)stream;
     const int64_t wl = w > 0 ? w : 1;
     const int nsq = 256;
@@ -1419,7 +1532,7 @@ int scd_lsq_decompose_tensor(const void* A, scd_dtype dt, int order, const int64
     double* host = nullptr;  // pinned: [0] cut value, [1] b of the current term, [2] upload slot, [3] status
     int rc = SCD_OK;
     double *e = nullptr, *D = nullptr, *g = nullptr, *absp = nullptr, *dotp = nullptr;
-    double *scal = nullptr, *L = nullptr, *yv = nullptr, *c = nullptr, *work = nullptr, *bvec = nullptr, *sq = nullptr;
+    double *scal = nullptr, *L = nullptr, *yv = nullptr, *c = nullptr, *bvec = nullptr, *sq = nullptr;
     int* status = nullptr;
     std::vector<int32_t> it_host((size_t)wl, 0);
     bool ok = ms.init(order, dims);
@@ -1427,7 +1540,7 @@ int scd_lsq_decompose_tensor(const void* A, scd_dtype dt, int order, const int64
          ms.alloc((void**)&g, (size_t)wl * 8) && ms.alloc((void**)&absp, (size_t)ms.max_words * 8) &&
          ms.alloc((void**)&dotp, (size_t)ms.max_words * 8) && ms.alloc((void**)&scal, 16) &&
          ms.alloc((void**)&L, (size_t)wl * wl * 8) && ms.alloc((void**)&yv, (size_t)wl * 8) && ms.alloc((void**)&c, (size_t)wl * 8) &&
-         ms.alloc((void**)&work, (size_t)wl * 8) && ms.alloc((void**)&bvec, (size_t)wl * 8) &&
+         ms.alloc((void**)&bvec, (size_t)wl * 8) &&
          ms.alloc((void**)&sq, (size_t)nsq * 8) && ms.alloc((void**)&status, 4);
     if (ok && hipHostMalloc((void**)&host, 4 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
@@ -1503,7 +1616,7 @@ int scd_lsq_decompose_tensor(const void* A, scd_dtype dt, int order, const int64
         host[2] = bnew;
         LQ(hipMemcpyAsync(bvec + k, host + 2, 8, hipMemcpyHostToDevice, st));
         LQ(launch_lsq_prod(D, wl, order, -1, k, nullptr, g, st));  // Gram row: product of the per-mode inner products
-        LQ(launch_lsq_solve(L, wl, k, g, (double)total, bvec, yv, c, work, fro0sq, fro_trace + k + 1, status, st));
+        LQ(launch_lsq_solve(L, wl, k, g, (double)total, bvec, yv, c, fro0sq, fro_trace + k + 1, status, st));
         LQ(hipMemcpyAsync(host + 3, status, 4, hipMemcpyDeviceToHost, st));
         LQ(hipStreamSynchronize(st));  // host[2] is reused by the next term
         if (*(const int*)(host + 3) != 0) return cleanup(SCD_ESINGULAR);

@@ -245,7 +245,39 @@ hipError_t launch_scalars_coef(const double* u, int64_t q, double P, scd_dtype d
 hipError_t launch_scalars_update(void* r, scd_dtype dt, int64_t total, int64_t q, const uint64_t* lead, const void* c,
                                  double* parts, int nparts, hipStream_t st);
 hipError_t launch_lsq_solve(double* L, int64_t ld, int64_t k, const double* g, double diag, const double* bvec, double* yv,
-                            double* c, double* work, double fro0sq, double* trace_out, int* status, hipStream_t st);
+                            double* c, double fro0sq, double* trace_out, int* status, hipStream_t st);
+
+// Matrices: position of the loop on the device and the arguments of a sweep's three launches.
+struct LsqState {
+    int64_t k;       // terms complete
+    double c_prev;   // cut value of the previous sweep of the current term (-inf before the first)
+    int32_t j;       // sweeps of the current term
+    int32_t done;    // all terms complete, or status set
+    int32_t status;  // 1: normal equations singular, 2: a cut value is not finite
+    int32_t warn;    // some term ended on max_iters
+};
+struct LsqMatArgs {
+    const void* A;
+    int64_t m, n, w;
+    uint64_t seed;
+    int32_t max_iters;
+    double fro0sq;
+    uint64_t* S;     // term-major outputs
+    uint64_t* T;
+    uint64_t* s;     // current sign vectors
+    uint64_t* t;
+    double* abs_parts;
+    double* dot_parts;
+    double* L;       // [w][w]
+    double* yv;
+    double* c;
+    double* bvec;
+    double* trace;
+    int32_t* iters;  // [w]
+    LsqState* st;
+};
+bool lsq_matrix_supported(scd_dtype dt, int64_t m, int64_t n);
+hipError_t launch_lsq_sweep(const LsqMatArgs& a, scd_dtype dt, hipStream_t st);
 
 // ---- expansion of the packed factors (scd_expand.hip)
 hipError_t launch_expand(const uint64_t* S, const uint64_t* T, const void* c, scd_dtype dt, int64_t m,

@@ -10,6 +10,7 @@
 // factor that grows by one row per term; b_j = <s_j, A t_j> falls out of the last half step of term j.
 // Everything here is f64; the kernels are small and latency-bound (one term = a few hundred launches).
 #include "scd_device.h"
+#include "scd_rng.h"
 
 namespace scd {
 
@@ -220,62 +221,378 @@ __device__ double lq_block_sum(double v, double* red)
 
 // The new term has index k.  Appends row k to the Cholesky factor L (lower triangular, row-major, leading
 // dimension ld) of the Gram matrix, whose new row is g[j] (j < k) with `diag` on the diagonal;
-// extends the forward solution y of L y = b by one entry; solves L^T c = y for all k + 1 coefficients;
-// and records ||A - S diag(c) T^T||_F = sqrt(||A||^2 - <c, b>) (the remainder is orthogonal to the fit).
-// One workgroup.  status: 1 if the new term is (numerically) in the span of the old ones.
-__global__ void __launch_bounds__(kLqThreads)
-    lsq_solve_kernel(double* __restrict__ L, int64_t ld, int64_t k, const double* __restrict__ g, double diag, const double* __restrict__ bvec, double* __restrict__ yv, double* __restrict__ c,
-                     double* __restrict__ work, double fro0sq, double* __restrict__ trace_out, int* __restrict__ status)
+// extends the forward solution y of L y = b by one entry; solves L^T c = y for all k + 1 coefficients.
+// Returns <c, b>, the same in every thread, or -1 if the new term is (numerically) in the span of the old ones.
+// One workgroup.  Both substitutions are in axpy form: a thread keeps up to four unknowns in registers, the owner of
+// the next one divides and hands it on through LDS, one barrier per unknown, and the column (row) of L that the next
+// step needs is loaded ahead of the barrier.  (With a sum over the workgroup per unknown, forward substitution alone
+// took 0.7 us per unknown.)
+__device__ double lq_refit(double* __restrict__ L, int64_t ld, int64_t k, const double* g, double diag, const double* __restrict__ bvec,
+                           double* __restrict__ yv, double* __restrict__ c, double* red, double* hand)
 {
-    __shared__ double red[kLqThreads / kWave];
+    constexpr int NQ = SCD_LSQ_MAX_WIDTH / kLqThreads;
     const int tid = threadIdx.x;
     double* row = L + k * ld;
-    // ---- forward substitution: row_r = (g_r - sum_{q<r} L[r][q] row_q) / L[r][r]
+    double x[NQ], col[NQ];
+    // ---- forward substitution L row = g
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+        const int64_t q = tid + (int64_t)i * kLqThreads;
+        x[i] = q < k ? g[q] : 0.0;
+        col[i] = q < k ? L[q * ld] : 0.0;
+    }
     for (int64_t r = 0; r < k; ++r) {
-        double s = 0.0;
-        for (int64_t q = tid; q < r; q += kLqThreads) s += L[r * ld + q] * row[q];
-        s = lq_block_sum(s, red);
-        if (tid == 0) row[r] = (g[r] - s) / L[r * ld + r];
-        __threadfence_block();
+        double cur[NQ];
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) {
+            const int64_t q = tid + (int64_t)i * kLqThreads;
+            cur[i] = col[i];
+            if (q == r) hand[r & 1] = x[i] = x[i] / cur[i];
+            col[i] = q < k && q > r ? L[q * ld + r + 1] : 0.0;  // (q > r: column r + 1 of the rows from r + 1 on)
+        }
         __syncthreads();
+        const double xr = hand[r & 1];
+#pragma unroll
+        for (int i = 0; i < NQ; ++i)
+            if (tid + (int64_t)i * kLqThreads > r) x[i] -= cur[i] * xr;
     }
     double s2 = 0.0, sy = 0.0;
-    for (int64_t q = tid; q < k; q += kLqThreads) {
-        s2 += row[q] * row[q];
-        sy += row[q] * yv[q];
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+        const int64_t q = tid + (int64_t)i * kLqThreads;
+        if (q < k) {
+            row[q] = x[i];
+            s2 += x[i] * x[i];
+            sy += x[i] * yv[q];
+        }
     }
     s2 = lq_block_sum(s2, red);
     sy = lq_block_sum(sy, red);
     const double d2 = diag - s2;
-    if (!(d2 > 1e-9 * diag)) {
-        if (tid == 0) *status = 1;
-        return;
-    }
-    const double lkk = sqrt(d2);
+    if (!(d2 > 1e-9 * diag)) return -1.0;
+    const double lkk = sqrt(d2), yk = (bvec[k] - sy) / lkk;
     if (tid == 0) {
         row[k] = lkk;
-        yv[k] = (bvec[k] - sy) / lkk;
+        yv[k] = yk;
     }
-    __threadfence_block();
-    __syncthreads();
-    // ---- back substitution L^T c = y, in axpy form: rows of L are contiguous
-    for (int64_t q = tid; q <= k; q += kLqThreads) work[q] = yv[q];
-    __threadfence_block();
-    __syncthreads();
-    for (int64_t r = k; r >= 0; --r) {
-        const double cr = work[r] / L[r * ld + r];
-        if (tid == 0) c[r] = cr;
-        for (int64_t q = tid; q < r; q += kLqThreads) work[q] -= L[r * ld + q] * cr;
-        __threadfence_block();
-        __syncthreads();
-    }
+    // ---- back substitution L^T c = y: rows of L are contiguous.  Row k is this launch's own: from the registers.
     double cb = 0.0;
-    for (int64_t q = tid; q <= k; q += kLqThreads) cb += c[q] * bvec[q];
-    cb = lq_block_sum(cb, red);
-    if (tid == 0) {
-        const double f2 = fro0sq - cb;
-        trace_out[0] = sqrt(f2 > 0.0 ? f2 : 0.0);
+    const double ck = yk / lkk;
+    double nxt[NQ];
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+        const int64_t q = tid + (int64_t)i * kLqThreads;
+        const double lkq = x[i];
+        x[i] = q < k ? yv[q] - lkq * ck : (q == k ? ck : 0.0);
+        nxt[i] = q < k ? L[(k - 1) * ld + q] : 0.0;
+        if (q == k) {
+            c[q] = ck;
+            cb += ck * bvec[q];
+        }
     }
+    __syncthreads();  // hand is free again
+    for (int64_t r = k - 1; r >= 0; --r) {
+        double cur[NQ];
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) {
+            const int64_t q = tid + (int64_t)i * kLqThreads;
+            cur[i] = nxt[i];
+            if (q == r) {
+                hand[r & 1] = x[i] = x[i] / cur[i];
+                c[q] = x[i];
+                cb += x[i] * bvec[q];
+            }
+            nxt[i] = q < r ? L[(r - 1) * ld + q] : 0.0;
+        }
+        __syncthreads();
+        const double cr = hand[r & 1];
+#pragma unroll
+        for (int i = 0; i < NQ; ++i)
+            if (tid + (int64_t)i * kLqThreads < r) x[i] -= cur[i] * cr;
+    }
+    return lq_block_sum(cb, red);
+}
+
+// One workgroup: refit after the new term k and record ||A - S diag(c) T^T||_F = sqrt(||A||^2 - <c, b>) (the remainder
+// is orthogonal to the fit).  status: 1 if the new term is (numerically) in the span of the old ones.
+__global__ void __launch_bounds__(kLqThreads)
+    lsq_solve_kernel(double* __restrict__ L, int64_t ld, int64_t k, const double* __restrict__ g, double diag, const double* __restrict__ bvec, double* __restrict__ yv, double* __restrict__ c,
+                     double fro0sq, double* __restrict__ trace_out, int* __restrict__ status)
+{
+    __shared__ double red[kLqThreads / kWave];
+    __shared__ double hand[2];
+    const double cb = lq_refit(L, ld, k, g, diag, bvec, yv, c, red, hand);
+    if (threadIdx.x == 0) {
+        const double f2 = fro0sq - cb;
+        if (cb < 0.0) *status = 1;
+        else trace_out[0] = sqrt(f2 > 0.0 ? f2 : 0.0);
+    }
+}
+
+// =================================================================================================
+// Matrices of up to kLqMaxWords words a side: a sweep (both half steps of Algorithm 4 on the implicit remainder, the
+// stop test and, at the end of a term, the refit) is three launches that the host enqueues blindly, many sweeps
+// ahead; the position of the loop lives on the device.  A half step is one launch because a workgroup owns one word (64 rows
+// or columns) from the entries of A to the sign bits: it forms the inner products with the earlier terms, the f64 sums
+// over its strip of A, the correction and the signs.  Bound by the chain of memory trips, barriers and launches, not by
+// bytes.  Us per sweep with ten launches and a read-back, and now: 1024x1024 f32 57 / 17.5, 64x64 57 / 15.5, 4096x4096
+// 71 / 41, 2048x2048 f64 60 / 35.  (The sweep's end in the workgroup of the column step that comes last needs fences
+// that write back and invalidate the caches: 20 instead of 17.5.)
+constexpr int kLqMaxWords = 64;
+constexpr int kLqWaves = kLqThreads / kWave;
+
+template <typename TE>
+struct LqVec;
+template <>
+struct LqVec<float> {
+    typedef float4 type;
+    static constexpr int N = 4;
+};
+template <>
+struct LqVec<double> {
+    typedef double2 type;
+    static constexpr int N = 2;
+};
+__device__ __forceinline__ double lq_sign(uint32_t bit) { return __hiloint2double((int)(0x3FF00000u | (bit << 31)), 0); }
+
+// The entries of one 16-byte chunk (or one entry) as doubles.
+template <typename TE, bool VEC>
+__device__ __forceinline__ void lq_load(const TE* __restrict__ p, double (&x)[VEC ? LqVec<TE>::N : 1])
+{
+    if constexpr (!VEC) {
+        x[0] = (double)p[0];
+    } else {
+        const typename LqVec<TE>::type v = *(const typename LqVec<TE>::type*)p;
+        x[0] = (double)v.x;
+        x[1] = (double)v.y;
+        if constexpr (LqVec<TE>::N == 4) x[2] = (double)v.z, x[3] = (double)v.w;
+    }
+}
+
+struct LqShared {
+    uint64_t vec[kLqMaxWords];       // the other side's sign vector
+    double e[SCD_LSQ_MAX_WIDTH];     // coefficient times inner product, per earlier term
+    double part[kLqWaves][kWave];
+    double sums[kWave];              // the strip's entries of A t or A^T s
+    double red[kLqWaves];
+    int flag;
+};
+
+// out[j] = coef[j] * <x_j, vec> (coef null: 1) for j < k: a group of 2^g >= nw lanes per term.  No barrier at the end.
+__device__ void lq_dots(const uint64_t* __restrict__ bits, int64_t k, int nw, int64_t len, const uint64_t* vec,
+                        const double* __restrict__ coef, double* out)
+{
+    int g = 1;
+    while (g < nw) g <<= 1;  // at most 64
+    const int p = threadIdx.x & (g - 1), per = kLqThreads / g;
+    const uint64_t mine = p < nw ? vec[p] : 0;
+    for (int64_t j0 = 0; j0 < k; j0 += per) {  // (whole waves stay together for the lane exchanges)
+        const int64_t j = j0 + threadIdx.x / g;
+        int cnt = (j < k && p < nw) ? __popcll(bits[j * nw + p] ^ mine) : 0;
+        for (int off = g >> 1; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off, kWave);
+        if (j < k && p == 0) {
+            const double d = (double)(len - 2 * (int64_t)cnt);
+            out[j] = coef ? coef[j] * d : d;
+        }
+    }
+}
+
+// The correction, the signs and (COLS) the sums of |y| and sgn(y) base for word p of `bits` (kw words per term), the
+// strip's sums in sh.sums and the weights in sh.e.
+template <bool COLS>
+__device__ void lq_finish(const uint64_t* __restrict__ bits, int64_t k, int64_t kw, int64_t p, int64_t len, LqShared& sh,
+                          uint64_t* __restrict__ out_bits, double* __restrict__ abs_parts, double* __restrict__ dot_parts)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    double acc = 0.0;
+    for (int64_t j0 = wv; j0 < k; j0 += 4 * kLqWaves) {
+        uint64_t word[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) word[i] = bits[(j0 + i * kLqWaves < k ? j0 + i * kLqWaves : j0) * kw + p];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (j0 + i * kLqWaves < k) acc = __builtin_fma(sh.e[j0 + i * kLqWaves], lq_sign((uint32_t)(word[i] >> lane) & 1u), acc);
+    }
+    sh.part[wv][lane] = acc;
+    __syncthreads();
+    if (wv != 0) return;
+    double q[kLqWaves], tot = 0.0;
+#pragma unroll
+    for (int i = 0; i < kLqWaves; ++i) q[i] = sh.part[i][lane];
+#pragma unroll
+    for (int i = 0; i < kLqWaves; ++i) tot += q[i];
+    const bool valid = p * 64 + lane < len;
+    const double b = valid ? sh.sums[lane] : 0.0;
+    const double y = valid ? b - tot : 0.0;
+    const bool neg = y < 0.0;
+    const uint64_t bal = __ballot(valid && neg);
+    if (lane == 0) out_bits[p] = bal;
+    if constexpr (COLS) {
+        const double a = lq_wave_sum(fabs(y));
+        const double d = lq_wave_sum(neg ? -b : b);
+        if (lane == 0) {
+            abs_parts[p] = a;
+            dot_parts[p] = d;
+        }
+    }
+}
+
+// s = sgn(A t - S (c o T^T t)), 64 rows per workgroup, four per wave
+template <typename TE, bool VEC>
+__global__ void __launch_bounds__(kLqThreads) lsq_rows_kernel(LsqMatArgs a)
+{
+    __shared__ LqShared sh;
+    constexpr int VE = VEC ? LqVec<TE>::N : 1;
+    if (a.st->done) return;
+    const int64_t k = a.st->k;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    const int mw = (int)((a.m + 63) / 64), nw = (int)((a.n + 63) / 64);
+    if (tid < nw) sh.vec[tid] = a.t[tid];
+    __syncthreads();
+    lq_dots(a.T, k, nw, a.n, sh.vec, a.c, sh.e);
+    const TE* A = (const TE*)a.A;
+    const TE* rowp[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int64_t row = (int64_t)blockIdx.x * 64 + wv * 4 + r;
+        rowp[r] = A + (row < a.m ? row : a.m - 1) * a.n;
+    }
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    const int nch = (int)(a.n / VE);
+#pragma unroll 2
+    for (int ch = lane; ch < nch; ch += kWave) {
+        double x[4][VE];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) lq_load<TE, VEC>(rowp[r] + (int64_t)ch * VE, x[r]);
+        const uint32_t b = (uint32_t)(sh.vec[(ch * VE) >> 6] >> ((ch * VE) & 63));
+#pragma unroll
+        for (int e = 0; e < VE; ++e) {
+            const double sg = lq_sign((b >> e) & 1u);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[r] = __builtin_fma(x[r][e], sg, acc[r]);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const double u = lq_wave_sum(acc[r]);
+        if (lane == 0) sh.sums[wv * 4 + r] = u;
+    }
+    __syncthreads();
+    lq_finish<false>(a.S, k, mw, blockIdx.x, a.m, sh, a.s, nullptr, nullptr);
+}
+
+// t = sgn(A^T s - T (c o S^T s)), 64 columns per workgroup: 64 / VE lanes share a row, the waves take rows in turn
+template <typename TE, bool VEC>
+__global__ void __launch_bounds__(kLqThreads) lsq_cols_kernel(LsqMatArgs a)
+{
+    __shared__ LqShared sh;
+    constexpr int VE = VEC ? LqVec<TE>::N : 1;
+    constexpr int RG = VE;  // rows per load of a wave
+    if (a.st->done) return;
+    const int64_t k = a.st->k;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    const int mw = (int)((a.m + 63) / 64), nw = (int)((a.n + 63) / 64);
+    if (tid < mw) sh.vec[tid] = a.s[tid];
+    __syncthreads();
+    lq_dots(a.S, k, mw, a.m, sh.vec, a.c, sh.e);
+    const int cl = lane % (kWave / VE), rg = lane / (kWave / VE);
+    const int64_t col = (int64_t)blockIdx.x * 64 + cl * VE;
+    const TE* colp = (const TE*)a.A + (col < a.n ? col : 0);  // (columns past the end are dropped below)
+    double acc[VE];
+#pragma unroll
+    for (int e = 0; e < VE; ++e) acc[e] = 0.0;
+    const int m = (int)a.m;
+#pragma unroll 4
+    for (int row = wv * RG + rg; row < m; row += kLqWaves * RG) {
+        double x[VE];
+        lq_load<TE, VEC>(colp + (int64_t)row * a.n, x);
+        const double sg = lq_sign((uint32_t)(sh.vec[row >> 6] >> (row & 63)) & 1u);
+#pragma unroll
+        for (int e = 0; e < VE; ++e) acc[e] = __builtin_fma(x[e], sg, acc[e]);
+    }
+#pragma unroll
+    for (int e = 0; e < VE; ++e) {
+        if constexpr (RG >= 4) acc[e] += __shfl_xor(acc[e], 16, kWave);
+        if constexpr (RG >= 2) acc[e] += __shfl_xor(acc[e], 32, kWave);
+        if (rg == 0) sh.part[wv][cl * VE + e] = acc[e];
+    }
+    __syncthreads();
+    if (wv == 0) {
+        double q[kLqWaves], v = 0.0;
+#pragma unroll
+        for (int i = 0; i < kLqWaves; ++i) q[i] = sh.part[i][lane];
+#pragma unroll
+        for (int i = 0; i < kLqWaves; ++i) v += q[i];
+        sh.sums[lane] = v;
+    }
+    __syncthreads();
+    lq_finish<true>(a.T, k, nw, blockIdx.x, a.n, sh, a.t, a.abs_parts, a.dot_parts);
+}
+
+// End of a sweep: Algorithm 4 line 8; when the term is complete, append it, refit all coefficients (Section 3.3) and draw
+// the next start.  One workgroup.
+__global__ void __launch_bounds__(kLqThreads) lsq_next_kernel(LsqMatArgs a)
+{
+    __shared__ LqShared sh;
+    LsqState* st = a.st;
+    if (st->done) return;
+    const int64_t k = st->k;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    const int mw = (int)((a.m + 63) / 64), nw = (int)((a.n + 63) / 64);
+    if (wv == 0) {
+        const double cut = lq_wave_sum(lane < nw ? a.abs_parts[lane] : 0.0);
+        const double b = lq_wave_sum(lane < nw ? a.dot_parts[lane] : 0.0);
+        if (lane == 0) {
+            const int j = st->j + 1;
+            int conv = 0;
+            if (!(fabs(cut) < INFINITY)) {
+                st->status = 2;
+                st->done = 1;
+            } else if (cut <= st->c_prev || j >= a.max_iters) {
+                if (!(cut <= st->c_prev)) st->warn = 1;
+                conv = 1;
+                a.bvec[k] = b;
+                a.iters[k] = j;
+            } else {
+                st->c_prev = cut;
+                st->j = j;
+            }
+            sh.flag = conv;
+        }
+    }
+    if (tid < nw) sh.vec[tid] = a.t[tid];
+    __syncthreads();
+    if (!sh.flag) return;
+    // the Gram row of the new term: products of the two sides' inner products
+    lq_dots(a.T, k, nw, a.n, sh.vec, nullptr, sh.e);
+    __syncthreads();
+    if (tid < nw) a.T[k * nw + tid] = sh.vec[tid];
+    __syncthreads();
+    if (tid < mw) {
+        sh.vec[tid] = a.s[tid];
+        a.S[k * mw + tid] = sh.vec[tid];
+    }
+    __syncthreads();
+    lq_dots(a.S, k, mw, a.m, sh.vec, sh.e, sh.e);  // (each element is read and written by the same lane)
+    __syncthreads();
+    const double fro2 = lq_refit(a.L, a.w, k, sh.e, (double)a.m * (double)a.n, a.bvec, a.yv, a.c, sh.red, &sh.part[0][0]);
+    if (fro2 < 0.0) {
+        if (tid == 0) {
+            st->status = 1;
+            st->done = 1;
+        }
+        return;
+    }
+    if (tid == 0) {
+        const double f2 = a.fro0sq - fro2;
+        a.trace[k + 1] = sqrt(f2 > 0.0 ? f2 : 0.0);
+        st->k = k + 1;
+        st->j = 0;
+        st->c_prev = -INFINITY;
+        if (k + 1 >= a.w) st->done = 1;
+    }
+    if (tid < nw) a.t[tid] = rng_word_masked(a.seed, (uint64_t)k + 1, 1u, tid, a.n);
 }
 
 }  // namespace
@@ -370,11 +687,35 @@ hipError_t launch_lsq_cast(const double* c, int64_t k, scd_dtype dt, void* out, 
 }
 
 hipError_t launch_lsq_solve(double* L, int64_t ld, int64_t k, const double* g, double diag, const double* bvec, double* yv,
-                            double* c, double* work, double fro0sq, double* trace_out, int* status, hipStream_t st)
+                            double* c, double fro0sq, double* trace_out, int* status, hipStream_t st)
 {
-    hipLaunchKernelGGL(lsq_solve_kernel, dim3(1), dim3(kLqThreads), 0, st, L, ld, k, g, diag, bvec, yv, c, work, fro0sq,
+    hipLaunchKernelGGL(lsq_solve_kernel, dim3(1), dim3(kLqThreads), 0, st, L, ld, k, g, diag, bvec, yv, c, fro0sq,
                        trace_out, status);
     return hipGetLastError();
+}
+
+// A workgroup per word of rows or columns: up to 64 of them, each reading a strip of at most 1 MiB.
+bool lsq_matrix_supported(scd_dtype dt, int64_t m, int64_t n)
+{
+    const int64_t es = dt == SCD_F32 ? 4 : 8;
+    return m <= kLqMaxWords * 64 && n <= kLqMaxWords * 64 && 64 * m * es <= (1 << 20) && 64 * n * es <= (1 << 20);
+}
+
+template <typename TE, bool VEC>
+static hipError_t lsq_sweep_t(const LsqMatArgs& a, hipStream_t st)
+{
+    hipLaunchKernelGGL((lsq_rows_kernel<TE, VEC>), dim3((unsigned)((a.m + 63) / 64)), dim3(kLqThreads), 0, st, a);
+    hipLaunchKernelGGL((lsq_cols_kernel<TE, VEC>), dim3((unsigned)((a.n + 63) / 64)), dim3(kLqThreads), 0, st, a);
+    hipLaunchKernelGGL(lsq_next_kernel, dim3(1), dim3(kLqThreads), 0, st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_lsq_sweep(const LsqMatArgs& a, scd_dtype dt, hipStream_t st)
+{
+    const int ve = dt == SCD_F32 ? 4 : 2;
+    const bool vec = a.n % ve == 0 && ((uintptr_t)a.A & 15u) == 0;  // every row starts on a 16-byte boundary
+    if (dt == SCD_F32) return vec ? lsq_sweep_t<float, true>(a, st) : lsq_sweep_t<float, false>(a, st);
+    return vec ? lsq_sweep_t<double, true>(a, st) : lsq_sweep_t<double, false>(a, st);
 }
 
 }  // namespace scd

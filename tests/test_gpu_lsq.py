@@ -68,6 +68,37 @@ def test_lsq_matches_oracle_in_lockstep(scd, oracle, m, n, w, dtype):
     run_and_check(scd, oracle, gauss((m, n), 7 * m + n, dtype), w, 3)
 
 
+# the device loop at the ends of its range (64 words a side, strips of 1 MiB; f64: 2048 entries), one word past them on
+# the other driver, single words, rows that are no multiple of 16 bytes
+@pytest.mark.parametrize("m,n,w,dtype", [(3, 5, 2, np.float32), (63, 65, 8, np.float32), (64, 64, 8, np.float64),
+                                         (129, 4096, 5, np.float32), (4096, 67, 5, np.float32), (130, 4097, 4, np.float32),
+                                         (2048, 66, 5, np.float64), (70, 2050, 4, np.float64), (257, 515, 6, np.float32)])
+def test_lsq_device_loop_range(scd, oracle, m, n, w, dtype):
+    run_and_check(scd, oracle, gauss((m, n), 3 * m + n, dtype), w, 5)
+
+
+def test_lsq_unaligned_input(scd):
+    flat = torch.from_numpy(gauss((1, 96 * 128 + 1), 8)).cuda().reshape(-1)
+    off = flat[1:].reshape(96, 128)                       # contiguous, rows 4 bytes past a 16-byte boundary
+    assert off.data_ptr() % 16 == 4
+    a, b = scd.scd_lsq_decompose(off, 12, 4), scd.scd_lsq_decompose(off.clone(), 12, 4)
+    assert torch.equal(a["signs"][0], b["signs"][0]) and torch.equal(a["signs"][1], b["signs"][1])
+    torch.testing.assert_close(a["c"], b["c"], rtol=1e-6, atol=0)
+    torch.testing.assert_close(a["trace"], b["trace"], rtol=1e-12, atol=0)
+
+
+def test_lsq_refit_with_more_terms_than_threads(scd):
+    # 1100 terms: a thread of the refit holds two unknowns
+    A = torch.from_numpy(gauss((150, 170), 6, np.float64)).cuda()
+    r = scd.scd_lsq_decompose(A, 1100, 2)
+    R = A - scd.scd_expand(r["signs"], r["c"], (150, 170))
+    assert float(R.norm()) == pytest.approx(float(r["trace"][-1]), rel=1e-7)
+    S = torch.stack([scd.scd_unpack(x, 150, torch.float64) for x in r["signs"][0]])
+    T = torch.stack([scd.scd_unpack(x, 170, torch.float64) for x in r["signs"][1]])
+    # the remainder is orthogonal to every term; bound: f64 sums of 1100 terms of the normal equations
+    assert float(((S @ R) * T).sum(1).abs().max()) <= 1e-9 * float(A.abs().sum())
+
+
 def test_lsq_free_run_and_first_term(scd, oracle):
     A = gauss((96, 160), 5, np.float64)
     res, adopted = run_and_check(scd, oracle, A, 16, 9)
