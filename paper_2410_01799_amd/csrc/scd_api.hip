@@ -1797,13 +1797,8 @@ int scd_apply(const uint64_t* S, const uint64_t* T, const void* c, scd_dtype dt,
     ApplyPlan pl;
     apply_plan(nin, nout, w, &pl);
     if (workspace_bytes < pl.bytes) return SCD_EINVAL;
-    const size_t es = dt == SCD_F32 ? 4 : 8;
     hipStream_t st = (hipStream_t)stream;
-    for (int64_t v = 0; v < nvec; ++v) {
-        HIP_TRY(launch_apply(transpose ? S : T, transpose ? T : S, c, dt, nin, nout, w,
-                             x ? (const char*)x + (size_t)v * (size_t)nin * es : nullptr,
-                             (char*)y + (size_t)v * (size_t)nout * es, workspace, st));
-    }
+    HIP_TRY(launch_apply(transpose ? S : T, transpose ? T : S, c, dt, nin, nout, w, x, nvec, y, workspace, workspace_bytes, st));
     HIP_TRY(hipStreamSynchronize(st));
     return SCD_OK;
 }

@@ -1,8 +1,7 @@
 // Product of a signed cut decomposition with a vector, straight from the packed factors
 // (Section 6.1 of arXiv 2410.01799, Question A):
 //     y = (sum_j c_j s_j t_j^T) x = sum_j z_j s_j,    z_j = c_j <t_j, x>.
-// The matrix is never expanded: the kernels read the w (m + n) / 8 bytes of sign bits once and do one
-// select and one add per bit.
+// The matrix is never expanded: the kernels read the w (m + n) / 8 bytes of sign bits, once per group of vectors.
 //
 // f32: both passes are contractions of a +-1 matrix with a vector and run on the matrix cores in block
 // fixed point (see the two MFMA kernels).  f64: vector units; a wave owns 64 consecutive entries (one per
@@ -167,157 +166,185 @@ __global__ void __launch_bounds__(kApInnerWaves* kWave)
 // Inner pass on the matrix cores (f32 x).  <t_j, x> for many terms j is a dense contraction of a +-1
 // matrix with x, so it belongs on MFMA; what keeps it exact is fixed point.  Per chunk of 4096 entries
 // x is scaled by a power of two so that |x| 2^s < 2^30, rounded to integers and cut into four balanced
-// base-256 digits (int8).  v_mfma_i32_4x4x4_16B_i8 multiplies, in each of its 16 blocks, 4 terms x 4
-// entries of signs (int8 +-1, expanded from a nibble of the bitset by a 16-entry table) with 4 entries x
-// 4 digits: the four digit columns use the whole instruction, the products and the int32 sums are exact,
-// and the digits are recombined in f64.  The only rounding is the fixed point itself: at most
-// max|x| 2^-30 per entry of the chunk, below the resolution of the f32 input for all but entries more
-// than 64 times smaller than the largest.
-// Operand layout of the instruction (lane l, block l / 4): A = row (l % 4) of the block's 4 x 4 sign
-// matrix (4 bytes along the contraction), B = column (l % 4) of its 4 x 4 digit matrix (4 bytes along the
-// contraction), D register r = element (row r, column l % 4).  Lane = term, so A comes from the lane's
-// own row of sign bits; the digit matrix is the same for every block.
+// base-256 digits (int8).  The only rounding is the fixed point itself: at most max|x| 2^-30 per entry of the
+// chunk, below the resolution of the f32 input for all but entries more than 64 times smaller than the largest.
+// v_mfma_i32_16x16x64_i8 takes 16 terms x 64 entries of sign bits (as bytes 0 / 1) against the digits of up to four
+// vectors (16 columns); <t, x> = sum x - 2 sum over the -1 signs, exact in integers, the digits recombined in f64.
+// The order of the contraction index is free as long as both operands share it, and is chosen for the bits: lane
+// (term, kq) reads words 2 kq and 2 kq + 1 of eight neighbouring words of its term (64 bytes per term and load), and
+// byte b of operand dword q of its instruction t = 0..7 is bit (t & 1) * 4 + q + 8 b of the half word t / 2 of the two:
+// one shift and one mask per four signs.  (With v_mfma_i32_4x4x4_16B_i8 and a table look-up per nibble the pass used a
+// quarter of the instruction's columns for one vector and took them one after the other: 14336x4096 transposed, four
+// vectors, 4 x 30 us; now 42 us for three and 25 for
+// one more.)
 typedef int ap_int4 __attribute__((ext_vector_type(4)));
 
-constexpr int kApMfmaWaves = 8;                      // waves per workgroup: each takes 8 of the chunk's 64 words
-constexpr int kApTileWords = kApChunkWords / kApMfmaWaves;  // words of a row per wave (64 bytes per term)
-constexpr int kApTilePitch = kApTileWords + 1;       // LDS pitch in words: rows 72 bytes apart
-static_assert(kApTileWords == 8, "staging below assumes 8 words per wave");
+constexpr int kApMfmaWaves = 8;                      // waves per workgroup of the outer pass: one word of outputs each
+constexpr int kApFxWaves = 4;                        // waves per workgroup of the inner pass: 16 terms each
+constexpr int kApFxThreads = kApFxWaves * kWave;
+constexpr int kApFxTile = 16 * kApFxWaves;           // terms per workgroup and turn
+constexpr int kApFxSets = 1024 / kApFxThreads;       // dwords of the fixed point per thread and digit
 
-// part[chunk * w + j] = <t_j, x> restricted to the chunk: each wave forms the sum over its 512 entries, the
-// eight are joined in wave order through LDS
-__global__ void __launch_bounds__(kApMfmaWaves* kWave)
-    apply_inner_mfma_kernel(const uint64_t* __restrict__ bits, int64_t nw, int64_t w, const float* __restrict__ x, int64_t n,
-                            double* __restrict__ part, int tiles_per_wg)
+// |v| as an integer below 2^30 in the chunk's scale -> digit jd of four of them as one dword per digit
+__device__ __forceinline__ void ap_digits(const int (&q4)[4], uint32_t (&dig)[4])
 {
-    __shared__ int xd[kApChunkWords * 16 * 4];                    // [group of 4 entries][digit]: 4 packed int8
-    __shared__ int lut[16];                                       // nibble -> 4 packed int8 signs
-    __shared__ uint64_t tile[kApMfmaWaves][kWave * kApTilePitch];  // per wave: 64 terms x 8 words
-    __shared__ float redmax[kApMfmaWaves];
-    __shared__ double wsum[kApMfmaWaves][kWave];
+#pragma unroll
+    for (int jd = 0; jd < 4; ++jd) dig[jd] = 0u;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        int q = q4[k];
+#pragma unroll
+        for (int jd = 0; jd < 3; ++jd) {
+            const int d = (int)(int8_t)(q & 0xFF);
+            dig[jd] |= (uint32_t)(d & 0xFF) << (8 * k);
+            q = (q - d) >> 8;
+        }
+        dig[3] |= (uint32_t)(q & 0xFF) << (8 * k);
+    }
+}
+
+// part[v * pstride + chunk * w + j] = <t_j, x_v> restricted to the chunk, for nv <= NV vectors
+template <int NV>
+__global__ void __launch_bounds__(kApFxThreads)
+    apply_inner_fx_kernel(const uint64_t* __restrict__ bits, int64_t nw, int64_t w, const float* __restrict__ x, int nv, int64_t n,
+                          double* __restrict__ part, int64_t pstride, int tiles_per_wg)
+{
+    constexpr int NC = 4 * NV;  // columns in use
+    __shared__ __align__(16) uint32_t xd[kApChunkWords * 4 * NC * 4];  // [8 words][t][kq][column][dword]
+    __shared__ float redmax[NV][kApFxWaves];
+    __shared__ double redsum[NV][kApFxWaves];
+    __shared__ int bad[NV];
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int64_t chunk = blockIdx.y;
     const int64_t p0 = chunk * kApChunkWords;
     const int nwc = (int)(nw - p0 < kApChunkWords ? nw - p0 : kApChunkWords);
+    const int ngrp = (nwc + 7) / 8;
+    const int row = lane & 15, kq = lane >> 4;
 
-    // the first tile of sign bits is requested before anything else: its latency hides behind the fixed point
-    const int pw = wv * kApTileWords;  // first word of this wave within the chunk
-    uint64_t stage[8];
+    // the sign bits of the first 16 terms are requested before anything else: their latency hides behind the fixed point
+    uint64_t wbuf[8][2];
     auto fetch = [&](int64_t jbase) {
-        // lane l fetches word (l % 8) of terms (l / 8) + 8 r: every load reads 8 rows x 64 bytes
+        int64_t j = jbase + wv * 16 + row;
+        j = j < w ? j : w - 1;
+        const uint64_t* r = bits + j * nw + p0;
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            int64_t j = jbase + (lane >> 3) + 8 * r;
-            j = j < w ? j : w - 1;
-            int p = pw + (lane & 7);
-            p = p < nwc ? p : nwc - 1;
-            stage[r] = bits[j * nw + p0 + p];
+        for (int g = 0; g < 8; ++g) {
+            const int q = (g < ngrp ? g : 0) * 8 + 2 * kq;  // (words past the end meet digits that are zero)
+            wbuf[g][0] = r[q < nwc ? q : nwc - 1];
+            wbuf[g][1] = r[q + 1 < nwc ? q + 1 : nwc - 1];
         }
     };
-    fetch((int64_t)blockIdx.x * tiles_per_wg * kWave);
+    fetch((int64_t)blockIdx.x * tiles_per_wg * kApFxTile);
 
-    // ---- fixed point of this chunk of x: thread t owns the groups of four entries t and t + 512
-    float xv[2][4];
-    float amax = 0.f;
-    bool finite = true;
+    // ---- fixed point of this chunk: thread t owns dwords t + kApFxThreads i (word, half, d): entries d + 8 b of the half word
+    if (tid < NV) bad[tid] = 0;
+    __syncthreads();
+    float xv[NV][kApFxSets][4];
 #pragma unroll
-    for (int r = 0; r < 2; ++r)
+    for (int v = 0; v < NV; ++v) {
+        if (v >= nv) continue;  // (the columns of vectors past nv hold what they hold and are not stored)
+        float amax = 0.f;
+        bool finite = true;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int64_t l = p0 * 64 + 4 * (tid + 512 * r) + k;
-            const float v = x[l < n ? l : n - 1];
-            xv[r][k] = l < n ? v : 0.f;
-            finite = finite && (fabsf(xv[r][k]) <= 3.0e38f);
-            amax = fmaxf(amax, fabsf(xv[r][k]));
-        }
-    amax = ap_wave_max(amax);
-    if (tid < 16) {
-        uint32_t v = 0;
+        for (int i = 0; i < kApFxSets; ++i)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) v |= (((tid >> k) & 1) ? 0xFFu : 0x01u) << (8 * k);
-        lut[tid] = (int)v;
-    }
-    if (lane == 0) redmax[wv] = amax;
-    const bool all_finite = !__syncthreads_or(finite ? 0 : 1);
-    amax = 0.f;
-#pragma unroll
-    for (int q = 0; q < kApMfmaWaves; ++q) amax = fmaxf(amax, redmax[q]);
-    int ex = 0;
-    if (amax > 0.f) (void)frexpf(amax, &ex);  // amax < 2^ex
-    const int sh = 30 - ex;
-    const double scale = ldexp(1.0, sh), inv_scale = ldexp(1.0, -sh);
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-        uint32_t dig[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            int q = all_finite ? (int)rint((double)xv[r][k] * scale) : 0;
-#pragma unroll
-            for (int jd = 0; jd < 3; ++jd) {
-                const int d = (int)(int8_t)(q & 0xFF);
-                dig[jd] |= (uint32_t)(d & 0xFF) << (8 * k);
-                q = (q - d) >> 8;
+            for (int b = 0; b < 4; ++b) {
+                const int sidx = tid + kApFxThreads * i;
+                const int64_t l = p0 * 64 + (sidx >> 4) * 64 + ((sidx >> 3) & 1) * 32 + (sidx & 7) + 8 * b;
+                const float val = x[(int64_t)v * n + (l < n ? l : n - 1)];
+                xv[v][i][b] = l < n ? val : 0.f;
+                finite = finite && (fabsf(xv[v][i][b]) <= 3.0e38f);
+                amax = fmaxf(amax, fabsf(xv[v][i][b]));
             }
-            dig[3] |= (uint32_t)(q & 0xFF) << (8 * k);
-        }
-        const int g = tid + 512 * r;
-#pragma unroll
-        for (int jd = 0; jd < 4; ++jd) xd[g * 4 + jd] = (int)dig[jd];
+        amax = ap_wave_max(amax);
+        if (lane == 0) redmax[v][wv] = amax;
+        if (!finite) bad[v] = 1;
     }
     __syncthreads();
-
-    uint64_t* mytile = tile[wv];
-    const int jd = lane & 3;
+    double inv_scale[NV];
+    bool all_finite[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        inv_scale[v] = 1.0;
+        all_finite[v] = true;
+        if (v >= nv) continue;
+        float amax = 0.f;
+#pragma unroll
+        for (int q = 0; q < kApFxWaves; ++q) amax = fmaxf(amax, redmax[v][q]);
+        all_finite[v] = bad[v] == 0;
+        int ex = 0;
+        if (amax > 0.f) (void)frexpf(amax, &ex);  // amax < 2^ex
+        const int sh = 30 - ex;
+        const double scale = ldexp(1.0, sh);
+        inv_scale[v] = ldexp(1.0, -sh);
+        double sum = 0.0;  // of integers below 2^30: exact
+#pragma unroll
+        for (int i = 0; i < kApFxSets; ++i) {
+            int q4[4];
+            uint32_t dig[4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                q4[b] = all_finite[v] ? (int)rint((double)xv[v][i][b] * scale) : 0;
+                sum += (double)q4[b];
+            }
+            ap_digits(q4, dig);
+            const int sidx = tid + kApFxThreads * i, wd = sidx >> 4, h = (sidx >> 3) & 1, d = sidx & 7;
+            const int t = (wd & 1) * 4 + h * 2 + (d >> 2);
+            uint32_t* dst = xd + ((((wd >> 3) * 8 + t) * 4 + ((wd & 7) >> 1)) * NC + 4 * v) * 4 + (d & 3);
+#pragma unroll
+            for (int jd = 0; jd < 4; ++jd) dst[jd * 4] = dig[jd];
+        }
+        sum = ap_wave_sum(sum);
+        if (lane == 0) redsum[v][wv] = sum;
+    }
+    __syncthreads();
+    // this lane's column: digit jd of vector vc
+    const int jd = lane & 3, vc = (row & (NC - 1)) >> 2;
+    double total = 0.0, inv = 0.0;
+    bool fin = true;
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+        if (v == vc) {
+#pragma unroll
+            for (int q = 0; q < kApFxWaves; ++q) total += redsum[v][q];
+            inv = inv_scale[v];
+            fin = all_finite[v];
+        }
     const double digit_weight = (double)(1u << (8 * jd));
-    double* mypart = part + chunk * w;
-    for (int t = 0; t < tiles_per_wg; ++t) {
-        const int64_t jbase = ((int64_t)blockIdx.x * tiles_per_wg + t) * kWave;
+    const ap_int4* xb = (const ap_int4*)xd + kq * NC + (row & (NC - 1));
+    double* mypart = part + (int64_t)vc * pstride + chunk * w;
+    for (int t0 = 0; t0 < tiles_per_wg; ++t0) {
+        const int64_t jbase = ((int64_t)blockIdx.x * tiles_per_wg + t0) * kApFxTile;
         if (jbase >= w) break;
         ap_int4 acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};
-        if (pw < nwc) {
 #pragma unroll
-            for (int r = 0; r < 8; ++r) mytile[((lane >> 3) + 8 * r) * kApTilePitch + (lane & 7)] = stage[r];
-            if (t + 1 < tiles_per_wg && jbase + kWave < w) fetch(jbase + kWave);  // the next 64 terms, during the products
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        for (int g = 0; g < 8; ++g) {
+            if (g < ngrp) {
 #pragma unroll
-            for (int pp = 0; pp < kApTileWords; ++pp) {
-                if (pw + pp < nwc) {
-                    const uint64_t word = mytile[lane * kApTilePitch + pp];
-                    const uint32_t half[2] = {(uint32_t)word, (uint32_t)(word >> 32)};
-                    const int* xg = xd + ((pw + pp) * 16) * 4 + jd;
+                for (int t = 0; t < 8; ++t) {
+                    const uint64_t word = wbuf[g][t >> 2];
+                    const uint32_t half = (t >> 1) & 1 ? (uint32_t)(word >> 32) : (uint32_t)word;
+                    ap_int4 A;
 #pragma unroll
-                    for (int q = 0; q < 16; ++q) {
-                        const uint32_t hw = half[q >> 3];
-                        const int s4 = 4 * (q & 7);
-                        const uint32_t off = s4 >= 2 ? ((hw >> (s4 - 2)) & 0x3Cu) : ((hw << 2) & 0x3Cu);
-                        const int a = *(const int*)((const char*)lut + off);
-                        if (q & 1) acc1 = __builtin_amdgcn_mfma_i32_4x4x4i8(a, xg[q * 4], acc1, 0, 0, 0);
-                        else acc0 = __builtin_amdgcn_mfma_i32_4x4x4i8(a, xg[q * 4], acc0, 0, 0, 0);
-                    }
+                    for (int q = 0; q < 4; ++q) A[q] = (int)((half >> ((t & 1) * 4 + q)) & 0x01010101u);
+                    const ap_int4 B = xb[(g * 8 + t) * 4 * NC];
+                    if (t & 1) acc1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, B, acc1, 0, 0, 0);
+                    else acc0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, B, acc0, 0, 0, 0);
                 }
             }
-            __builtin_amdgcn_wave_barrier();  // the tile is rewritten for the next 64 terms
         }
-        // D register i = term jbase + 4 (lane / 4) + i, digit (lane % 4): recombine the digits (exact in f64)
+        if (t0 + 1 < tiles_per_wg && jbase + kApFxTile < w) fetch(jbase + kApFxTile);
+        // register i = term jbase + 16 wave + 4 (lane / 16) + i, column lane mod 16: recombine the digits (exact in f64)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             double v = (double)(acc0[i] + acc1[i]) * digit_weight;
             v += ap_dpp_xor_f64<1>(v);
             v += ap_dpp_xor_f64<2>(v);
-            if (jd == 0) wsum[wv][4 * (lane >> 2) + i] = v;
+            const int64_t j = jbase + wv * 16 + 4 * kq + i;
+            if (jd == 0 && row < NC && vc < nv && j < w)
+                mypart[j] = fin ? (total - 2.0 * v) * inv : __longlong_as_double(0x7FF8000000000000ll);
         }
-        __syncthreads();  // (every wave of the workgroup runs the same tiles)
-        if (wv == 0) {
-            double tot = 0.0;
-#pragma unroll
-            for (int q = 0; q < kApMfmaWaves; ++q) tot += wsum[q][lane];
-            const int64_t j = jbase + lane;
-            if (j < w) mypart[j] = all_finite ? tot * inv_scale : __longlong_as_double(0x7FF8000000000000ll);
-        }
-        __syncthreads();  // wsum is rewritten for the next tile
     }
 }
 
@@ -389,22 +416,23 @@ __global__ void __launch_bounds__(kApOuterWaves* kWave)
 // Outer pass on the matrix cores (f32).  y_i = sum_j z_j s_j[i] is the same kind of contraction as the
 // inner pass with the roles swapped: the terms are the contraction index and z plays the part of x (block
 // fixed point per split of the terms: |z| 2^s < 2^30, four balanced base-256 digits, at most
-// max|z| 2^-30 per term, exact sums afterwards).  The bitset is term-major, so the four signs an
-// instruction wants per lane (one output entry, four consecutive terms) sit in four different words:
-// a wave loads word p of 64 consecutive terms (one per lane) and transposes the 64 x 64 bits across
-// its lanes (six butterfly stages); lane i then holds the signs of output entry 64 p + i for the 64 terms,
-// packed along the contraction exactly as the inner pass has them.
-constexpr int kApFxMaxTerms = 2048;  // terms per split: one group of four per thread of the workgroup
-// digits of one kind are kApFxPitch words apart: the four that a wave reads together fall into different banks
-constexpr int kApFxPitch = kApFxMaxTerms / 4 + 4;
+// max|z| 2^-30 per term, exact sums afterwards; up to four vectors in the 16 columns).  The bitset is term-major, so
+// the signs an instruction wants per lane (one output entry, 16 terms) sit in 16 different words: a wave loads word p of
+// 64 consecutive terms (one per lane) and transposes every 16 x 16 block of bits in place (the four lower stages of the
+// butterfly).  Field b (16 bits) of lane (a, i) then holds terms 16 a .. 16 a + 15 at entry 16 b + i, which is what lane
+// (row i, quarter a) of the instruction for entries 16 b .. 16 b + 15 takes; byte q' of its operand dword q is term
+// 16 a + 4 q' + q, a shift and a mask once the field's nibbles are spread over the bytes.
+constexpr int kApFxMaxTerms = 2048;  // terms per split: one dword set (four terms) per thread of the workgroup
 
+template <int NV>
 __global__ void __launch_bounds__(kApMfmaWaves* kWave)
-    apply_outer_mfma_kernel(const uint64_t* __restrict__ bits, int64_t mw, int64_t w, const double* __restrict__ part,
-                            int chunks, const float* __restrict__ c, int64_t terms_per_split, double* __restrict__ ypart)
+    apply_outer_fx_kernel(const uint64_t* __restrict__ bits, int64_t mw, int64_t w, const double* __restrict__ part, int64_t pstride,
+                          int chunks, const float* __restrict__ c, int nv, int64_t terms_per_split, double* __restrict__ ypart)
 {
-    __shared__ __align__(16) int zd[4 * kApFxPitch];  // [digit][group of 4 terms]: 4 packed int8
-    __shared__ int lut[16];            // nibble -> 4 packed int8 signs
-    __shared__ double redmax[kApMfmaWaves];
+    constexpr int NC = 4 * NV;
+    __shared__ __align__(16) uint32_t zd[kApFxMaxTerms / 4 * NC];  // [tile of 64 terms][quarter][column][dword]
+    __shared__ double redmax[NV][kApMfmaWaves], redsum[NV][kApMfmaWaves];
+    __shared__ int bad[NV];
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int64_t p = (int64_t)blockIdx.x * kApMfmaWaves + wv;  // word of the output this wave owns
@@ -419,95 +447,121 @@ __global__ void __launch_bounds__(kApMfmaWaves* kWave)
     };
     uint64_t next = fetch(0);
 
-    // ---- z of this split in fixed point: thread t owns the group of four terms t
-    double zv[4];
-    double amax = 0.0;
-    bool finite = true;
+    // ---- z of this split in fixed point: thread t owns terms 16 (t / 4) + t mod 4 + 4 b
+    if (tid < NV) bad[tid] = 0;
+    __syncthreads();
+    double zv[NV][4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int64_t j = j0 + 4 * tid + k;
-        const int64_t jc = j < j1 ? j : j1 - 1;
-        const double s = ap_sum_parts(part, w, jc, chunks);
-        zv[k] = j < j1 ? (double)c[jc] * s : 0.0;
-        finite = finite && (fabs(zv[k]) <= 1.7e308);
-        amax = fmax(amax, fabs(zv[k]));
-    }
-    amax = ap_wave_max(amax);
-    if (tid < 16) {
-        uint32_t v = 0;
+    for (int v = 0; v < NV; ++v) {
+        if (v >= nv) continue;  // (as above)
+        double amax = 0.0;
+        bool finite = true;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) v |= (((tid >> k) & 1) ? 0xFFu : 0x01u) << (8 * k);
-        lut[tid] = (int)v;
-    }
-    if (lane == 0) redmax[wv] = amax;
-    const bool all_finite = !__syncthreads_or(finite ? 0 : 1);
-    amax = 0.0;
-#pragma unroll
-    for (int q = 0; q < kApMfmaWaves; ++q) amax = fmax(amax, redmax[q]);
-    int ex = 0;
-    if (amax > 0.0) (void)frexp(amax, &ex);  // amax < 2^ex
-    int sh = 30 - ex;
-    sh = sh > 1000 ? 1000 : sh;              // (2^sh stays a normal number; smaller z round to zero)
-    const double scale = ldexp(1.0, sh), inv_scale = ldexp(1.0, -sh);
-    {
-        uint32_t dig[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            int q = all_finite ? (int)rint(zv[k] * scale) : 0;
-#pragma unroll
-            for (int jd = 0; jd < 3; ++jd) {
-                const int d = (int)(int8_t)(q & 0xFF);
-                dig[jd] |= (uint32_t)(d & 0xFF) << (8 * k);
-                q = (q - d) >> 8;
-            }
-            dig[3] |= (uint32_t)(q & 0xFF) << (8 * k);
+        for (int b = 0; b < 4; ++b) {
+            const int64_t j = j0 + 16 * (tid >> 2) + (tid & 3) + 4 * b;
+            const int64_t jc = j < j1 ? j : j1 - 1;
+            const double sp = ap_sum_parts(part + (int64_t)v * pstride, w, jc, chunks);
+            zv[v][b] = j < j1 ? (double)c[jc] * sp : 0.0;
+            finite = finite && (fabs(zv[v][b]) <= 1.7e308);
+            amax = fmax(amax, fabs(zv[v][b]));
         }
+        amax = ap_wave_max(amax);
+        if (lane == 0) redmax[v][wv] = amax;
+        if (!finite) bad[v] = 1;
+    }
+    __syncthreads();
+    double inv_scale[NV];
+    bool all_finite[NV];
 #pragma unroll
-        for (int jd = 0; jd < 4; ++jd) zd[jd * kApFxPitch + tid] = (int)dig[jd];
+    for (int v = 0; v < NV; ++v) {
+        inv_scale[v] = 1.0;
+        all_finite[v] = true;
+        if (v >= nv) continue;
+        double amax = 0.0;
+#pragma unroll
+        for (int q = 0; q < kApMfmaWaves; ++q) amax = fmax(amax, redmax[v][q]);
+        all_finite[v] = bad[v] == 0;
+        int ex = 0;
+        if (amax > 0.0) (void)frexp(amax, &ex);  // amax < 2^ex
+        int sh = 30 - ex;
+        sh = sh > 1000 ? 1000 : sh;              // (2^sh stays a normal number; smaller z round to zero)
+        const double scale = ldexp(1.0, sh);
+        inv_scale[v] = ldexp(1.0, -sh);
+        int q4[4];
+        uint32_t dig[4];
+        double sum = 0.0;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            q4[b] = all_finite[v] ? (int)rint(zv[v][b] * scale) : 0;
+            sum += (double)q4[b];
+        }
+        ap_digits(q4, dig);
+        uint32_t* dst = zd + ((tid >> 2) * NC + 4 * v) * 4 + (tid & 3);  // (tile * 4 + quarter = tid / 4)
+#pragma unroll
+        for (int jd = 0; jd < 4; ++jd) dst[jd * 4] = dig[jd];
+        sum = ap_wave_sum(sum);
+        if (lane == 0) redsum[v][wv] = sum;
     }
     __syncthreads();
     if (p >= mw) return;  // (no workgroup-wide barrier below)
 
-    const int jd = lane & 3;
+    const int col = lane & 15, a = lane >> 4;
+    const int jd = lane & 3, vc = (col & (NC - 1)) >> 2;
+    double total = 0.0, inv = 0.0;
+    bool fin = true;
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+        if (v == vc) {
+#pragma unroll
+            for (int q = 0; q < kApMfmaWaves; ++q) total += redsum[v][q];
+            inv = inv_scale[v];
+            fin = all_finite[v];
+        }
     const int ntiles = (int)((j1 - j0 + kWave - 1) / kWave);
-    ap_int4 acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};
+    const ap_int4* zb = (const ap_int4*)zd + a * NC + (col & (NC - 1));
+    ap_int4 acc[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) acc[b] = ap_int4{0, 0, 0, 0};
     for (int t = 0; t < ntiles; ++t) {
         const uint64_t mine = next;
         if (t + 1 < ntiles) next = fetch(t + 1);
-        const uint64_t col = transpose64(mine, lane);  // bit q: sign of term (tile + q) at this lane's entry
-        const uint32_t half[2] = {(uint32_t)col, (uint32_t)(col >> 32)};
-        // this lane's digit of the tile's 16 groups of four terms (four 16-byte reads)
-        const ap_int4* zq = (const ap_int4*)(zd + jd * kApFxPitch + t * 16);
-        int zg[16];
+        uint32_t half[2] = {(uint32_t)mine, (uint32_t)(mine >> 32)};
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const ap_int4 v = zq[q];
-            zg[4 * q] = v[0], zg[4 * q + 1] = v[1], zg[4 * q + 2] = v[2], zg[4 * q + 3] = v[3];
+        for (int h = 0; h < 2; ++h) {
+            half[h] = bit_butterfly<8>(half[h], lane);
+            half[h] = bit_butterfly<4>(half[h], lane);
+            half[h] = bit_butterfly<2>(half[h], lane);
+            half[h] = bit_butterfly<1>(half[h], lane);
         }
+        const ap_int4 B = zb[t * 4 * NC];
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const uint32_t hw = half[q >> 3];
-            const int s4 = 4 * (q & 7);
-            const uint32_t off = s4 >= 2 ? ((hw >> (s4 - 2)) & 0x3Cu) : ((hw << 2) & 0x3Cu);
-            const int a = *(const int*)((const char*)lut + off);
-            if (q & 1) acc1 = __builtin_amdgcn_mfma_i32_4x4x4i8(a, zg[q], acc1, 0, 0, 0);
-            else acc0 = __builtin_amdgcn_mfma_i32_4x4x4i8(a, zg[q], acc0, 0, 0, 0);
+        for (int b = 0; b < 4; ++b) {
+            // nibbles 0..3 of the field into bytes 0..3
+            const uint32_t two = __builtin_amdgcn_perm(0u, half[b >> 1], (b & 1) ? 0x0C030C02u : 0x0C010C00u);
+            const uint32_t nib = (two | (two << 4)) & 0x0F0F0F0Fu;
+            ap_int4 A;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) A[q] = (int)((nib >> q) & 0x01010101u);
+            acc[b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, B, acc[b], 0, 0, 0);
         }
     }
-    // D register i = output entry 64 p + 4 (lane / 4) + i, digit (lane % 4): recombine the digits (exact in f64)
+    // register i of acc[b] = output entry 64 p + 16 b + 4 (lane / 16) + i, column lane mod 16
     const double digit_weight = (double)(1u << (8 * jd));
-    double* out = ypart + split * (mw * 64) + p * 64 + 4 * (lane >> 2);
+    double* out = ypart + (split * nv + vc) * (mw * 64) + p * 64 + 4 * a;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        double v = (double)(acc0[i] + acc1[i]) * digit_weight;
-        v += ap_dpp_xor_f64<1>(v);
-        v += ap_dpp_xor_f64<2>(v);
-        if (jd == 0) out[i] = all_finite ? v * inv_scale : __longlong_as_double(0x7FF8000000000000ll);
-    }
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            double v = (double)acc[b][i] * digit_weight;
+            v += ap_dpp_xor_f64<1>(v);
+            v += ap_dpp_xor_f64<2>(v);
+            if (jd == 0 && col < NC && vc < nv) out[16 * b + i] = fin ? (total - 2.0 * v) * inv : __longlong_as_double(0x7FF8000000000000ll);
+        }
 }
 
-// y = sum of the splits in order, rounded once.  64 entries per workgroup; the splits are cut into four
-// runs that are added side by side (their loads in flight together) and joined in order.
+// y = sum of the splits in order, rounded once, for vector blockIdx.y of the launch (ypart: [split][vector][mpad]).  64
+// entries per workgroup; the splits are cut into four runs that are added side by side (their loads in flight together)
+// and joined in order.
 template <typename TE>
 __global__ void __launch_bounds__(256)
     apply_reduce_kernel(const double* __restrict__ ypart, int splits, int64_t mpad, int64_t m, TE* __restrict__ y)
@@ -515,10 +569,14 @@ __global__ void __launch_bounds__(256)
     __shared__ double run[4][64];
     const int r = threadIdx.x & 63, g = threadIdx.x >> 6;
     const int64_t i = (int64_t)blockIdx.x * 64 + r;
+    const int64_t len = mpad;
+    ypart += (int64_t)blockIdx.y * mpad;
+    y += (int64_t)blockIdx.y * m;
+    mpad *= gridDim.y;  // from one split to the next
     const int per = (splits + 3) / 4;
     const int q0 = g * per, q1 = q0 + per < splits ? q0 + per : splits;
     double s = 0.0;
-    if (i < mpad) {
+    if (i < len) {
         int q = q0;
         for (; q + 4 <= q1; q += 4) {
             const double a0 = ypart[(int64_t)q * mpad + i], a1 = ypart[(int64_t)(q + 1) * mpad + i];
@@ -577,8 +635,40 @@ void apply_plan(int64_t nin, int64_t nout, int64_t w, ApplyPlan* pl)
     if (pl->bytes < 8) pl->bytes = 8;
 }
 
+namespace {
+
+template <int NV>
+hipError_t launch_fx(const uint64_t* in_bits, const uint64_t* out_bits, const float* c, int64_t nin, int64_t nout, int64_t w,
+                     const float* x, int nv, float* y, const ApplyPlan& pl, int64_t tps, int splits, void* workspace, hipStream_t st)
+{
+    const int64_t win = (nin + 63) / 64, wout = (nout + 63) / 64;
+    const int64_t pstride = (int64_t)pl.parts * w;
+    double* part = (double*)workspace;
+    double* ypart = part + nv * pstride;
+    // a workgroup per tile of 64 terms; several tiles per workgroup once there are more than two per compute unit, to pay
+    // for the fixed point less often (14336x4096 transposed, four vectors: 113 us, with up to 1024 workgroups 123)
+    const int64_t tiles = (w + kApFxTile - 1) / kApFxTile;
+    int tpw = (int)((tiles * pl.chunks + 511) / 512);
+    if (tpw < 1) tpw = 1;
+    const int64_t wgs = (tiles + tpw - 1) / tpw;
+    hipLaunchKernelGGL((apply_inner_fx_kernel<NV>), dim3((unsigned)wgs, (unsigned)pl.chunks), dim3(kApFxThreads), 0, st, in_bits, win, w, x,
+                       nv, nin, part, pstride, tpw);
+    dim3 go((unsigned)((wout + kApMfmaWaves - 1) / kApMfmaWaves), (unsigned)splits);
+    hipLaunchKernelGGL((apply_outer_fx_kernel<NV>), go, dim3(kApMfmaWaves * kWave), 0, st, out_bits, wout, w, part, pstride, pl.parts, c, nv,
+                       tps, ypart);
+    hipLaunchKernelGGL((apply_reduce_kernel<float>), dim3((unsigned)((nout + 63) / 64), (unsigned)nv), dim3(256), 0, st, ypart, splits,
+                       wout * 64, nout, y);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+// nvec vectors (rows of x and y).  f32: up to four share a pass over the bits.  The workspace is sized for one vector
+// whatever their number: several take it with fewer splits of the terms (at most kApFxMaxTerms each), and where even
+// those do not fit, in smaller groups (as many at once as fit: a pass costs 30 us for one vector and 45 for four, so
+// 3 + 1 is faster than 2 + 2).
 hipError_t launch_apply(const uint64_t* in_bits, const uint64_t* out_bits, const void* c, scd_dtype dt, int64_t nin,
-                        int64_t nout, int64_t w, const void* x, void* y, void* workspace, hipStream_t st)
+                        int64_t nout, int64_t w, const void* x, int64_t nvec, void* y, void* workspace, size_t workspace_bytes, hipStream_t st)
 {
     ApplyPlan pl;
     apply_plan(nin, nout, w, &pl);
@@ -586,42 +676,56 @@ hipError_t launch_apply(const uint64_t* in_bits, const uint64_t* out_bits, const
     double* part = (double*)((char*)workspace + pl.off_part);
     double* ypart = (double*)((char*)workspace + pl.off_ypart);
     if (nout == 0) return hipSuccess;
+    const unsigned gr = (unsigned)((nout + 63) / 64);
     if (w == 0 || nin == 0) {
         // the empty sum: a reduce over no splits writes zeros
-        const unsigned g0 = (unsigned)((nout + 63) / 64);
-        if (dt == SCD_F32)
-            hipLaunchKernelGGL((apply_reduce_kernel<float>), dim3(g0), dim3(256), 0, st, ypart, 0, wout * 64, nout, (float*)y);
-        else
-            hipLaunchKernelGGL((apply_reduce_kernel<double>), dim3(g0), dim3(256), 0, st, ypart, 0, wout * 64, nout, (double*)y);
+        for (int64_t v = 0; v < nvec; ++v) {
+            if (dt == SCD_F32)
+                hipLaunchKernelGGL((apply_reduce_kernel<float>), dim3(gr), dim3(256), 0, st, ypart, 0, wout * 64, nout, (float*)y + v * nout);
+            else
+                hipLaunchKernelGGL((apply_reduce_kernel<double>), dim3(gr), dim3(256), 0, st, ypart, 0, wout * 64, nout, (double*)y + v * nout);
+        }
         return hipGetLastError();
     }
-    const int64_t waves = (w + pl.terms_per_wave - 1) / pl.terms_per_wave;
-    dim3 gi((unsigned)((waves + kApInnerWaves - 1) / kApInnerWaves), (unsigned)pl.chunks);
     if (dt == SCD_F32) {
-        // one workgroup per tile of 64 terms (eight waves split the chunk's words); several tiles per
-        // workgroup once there are enough of them, to pay for the fixed point less often
-        const int64_t tiles = (w + kWave - 1) / kWave;
-        int tpw = (int)((tiles * pl.chunks + 1023) / 1024);
-        if (tpw < 1) tpw = 1;
-        const int64_t wgs = (tiles + tpw - 1) / tpw;
-        hipLaunchKernelGGL(apply_inner_mfma_kernel, dim3((unsigned)wgs, (unsigned)pl.chunks), dim3(kApMfmaWaves * kWave), 0, st,
-                           in_bits, win, w, (const float*)x, nin, part, tpw);
-    } else
+        for (int64_t v = 0; v < nvec;) {
+            const float* xv = (const float*)x + v * nin;
+            float* yv = (float*)y + v * nout;
+            int64_t tps = pl.terms_per_split_fx, splits = pl.splits_fx;
+            auto fits = [&](int64_t nv) {  // sets tps and splits
+                if (nv == 1) {
+                    tps = pl.terms_per_split_fx, splits = pl.splits_fx;
+                    return true;
+                }
+                const int64_t room = (int64_t)(workspace_bytes / 8) - nv * pl.parts * w;
+                int64_t most = room > 0 ? room / (nv * wout * 64) : 0;
+                if (most > pl.splits_fx) most = pl.splits_fx;
+                if (most < 1) return false;
+                tps = ((w + most - 1) / most + kWave - 1) / kWave * kWave;
+                splits = (w + tps - 1) / tps;
+                return tps <= kApFxMaxTerms;
+            };
+            int64_t nv = nvec - v < 4 ? nvec - v : 4;
+            while (!fits(nv)) --nv;
+            hipError_t e;
+            if (nv > 2) e = launch_fx<4>(in_bits, out_bits, (const float*)c, nin, nout, w, xv, (int)nv, yv, pl, tps, (int)splits, workspace, st);
+            else if (nv == 2) e = launch_fx<2>(in_bits, out_bits, (const float*)c, nin, nout, w, xv, 2, yv, pl, tps, (int)splits, workspace, st);
+            else e = launch_fx<1>(in_bits, out_bits, (const float*)c, nin, nout, w, xv, 1, yv, pl, tps, (int)splits, workspace, st);
+            if (e != hipSuccess) return e;
+            v += nv;
+        }
+        return hipSuccess;
+    }
+    for (int64_t v = 0; v < nvec; ++v) {
+        const int64_t waves = (w + pl.terms_per_wave - 1) / pl.terms_per_wave;
+        dim3 gi((unsigned)((waves + kApInnerWaves - 1) / kApInnerWaves), (unsigned)pl.chunks);
         hipLaunchKernelGGL((apply_inner_kernel<double>), gi, dim3(kApInnerWaves * kWave), 0, st, in_bits, win, w,
-                           (const double*)x, nin, part, pl.terms_per_wave);
-    dim3 go((unsigned)((wout + kApOuterWaves - 1) / kApOuterWaves), (unsigned)pl.splits);
-    if (dt == SCD_F32) {
-        dim3 gf((unsigned)((wout + kApMfmaWaves - 1) / kApMfmaWaves), (unsigned)pl.splits_fx);
-        hipLaunchKernelGGL(apply_outer_mfma_kernel, gf, dim3(kApMfmaWaves * kWave), 0, st, out_bits, wout, w, part, pl.parts,
-                           (const float*)c, pl.terms_per_split_fx, ypart);
-    } else
+                           (const double*)x + v * nin, nin, part, pl.terms_per_wave);
+        dim3 go((unsigned)((wout + kApOuterWaves - 1) / kApOuterWaves), (unsigned)pl.splits);
         hipLaunchKernelGGL((apply_outer_kernel<double>), go, dim3(kApOuterWaves * kWave), 0, st, out_bits, wout, w, part,
                            pl.parts, (const double*)c, pl.terms_per_split, ypart);
-    const unsigned gr = (unsigned)((nout + 63) / 64);
-    if (dt == SCD_F32)
-        hipLaunchKernelGGL((apply_reduce_kernel<float>), dim3(gr), dim3(256), 0, st, ypart, pl.splits_fx, wout * 64, nout, (float*)y);
-    else
-        hipLaunchKernelGGL((apply_reduce_kernel<double>), dim3(gr), dim3(256), 0, st, ypart, pl.splits, wout * 64, nout, (double*)y);
+        hipLaunchKernelGGL((apply_reduce_kernel<double>), dim3(gr), dim3(256), 0, st, ypart, pl.splits, wout * 64, nout, (double*)y + v * nout);
+    }
     return hipGetLastError();
 }
 

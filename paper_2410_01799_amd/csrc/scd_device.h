@@ -227,7 +227,8 @@ struct ApplyPlan {
 };
 void apply_plan(int64_t nin, int64_t nout, int64_t w, ApplyPlan* pl);
 hipError_t launch_apply(const uint64_t* in_bits, const uint64_t* out_bits, const void* c, scd_dtype dt, int64_t nin,
-                        int64_t nout, int64_t w, const void* x, void* y, void* workspace, hipStream_t st);
+                        int64_t nout, int64_t w, const void* x, int64_t nvec, void* y, void* workspace, size_t workspace_bytes,
+                        hipStream_t st);
 
 // ---- least squares decomposition, Algorithm 6 (scd_lsq.hip) -----------------------------------------
 hipError_t launch_lsq_dots(const uint64_t* bits, int64_t k, int64_t nw, int64_t len, const uint64_t* vec, const double* coef,

@@ -102,6 +102,25 @@ def test_apply_several_vectors_and_empty_sum(scd, oracle):
     check(scd, oracle, 130, 70, 0, 8, np.float64, True)
 
 
+@pytest.mark.parametrize("m,n,w", [(64, 64, 1), (65, 127, 17), (130, 4100, 65), (700, 512, 2049), (513, 600, 300)])
+@pytest.mark.parametrize("nvec", [1, 2, 3, 4, 5, 7])
+def test_apply_groups_of_vectors(scd, oracle, m, n, w, nvec):
+    # every size of a group of vectors (4, 3, 2, 1 and what is left of them), at the ends of words, tiles of 16 and 64
+    # terms, chunks of 4096 entries and splits of 2048 terms
+    check(scd, oracle, m, n, w, 11 + nvec, np.float32, nvec % 2 == 0, nvec=nvec)
+
+
+def test_apply_a_bad_vector_leaves_its_neighbours_alone(scd):
+    S, T, c = random_factors(200, 300, 90, 4, np.float32)
+    x = torch.from_numpy(np.random.Generator(np.random.PCG64(4)).standard_normal((4, 300)).astype(np.float32)).cuda()
+    good = scd.scd_apply(dev_bits(S), dev_bits(T), torch.from_numpy(c).cuda(), 200, 300, x)
+    x[2, 17] = float("inf")
+    bad = scd.scd_apply(dev_bits(S), dev_bits(T), torch.from_numpy(c).cuda(), 200, 300, x)
+    assert torch.isnan(bad[2]).all()
+    for v in (0, 1, 3):
+        assert torch.equal(bad[v], good[v])
+
+
 def test_apply_full_size_layer_width(scd, oracle):
     # 4096 x 4096 at the 50 % width of Table 2 (16320 terms): several chunks of terms per wave, 64 splits
     check(scd, oracle, 4096, 4096, 16320, 11, np.float32, False)
