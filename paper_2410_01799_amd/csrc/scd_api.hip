@@ -1122,29 +1122,9 @@ int scd_row_signed_sum(const void* R, scd_dtype dt, int64_t m, int64_t n, const 
 {
     if (!R || !tbits || !dtype_ok(dt) || m < 1 || n < 1) return SCD_EINVAL;
     hipStream_t st = (hipStream_t)stream;
-    double* utmp = nullptr;
-    if (!u) {
-        hipError_t e = hipMalloc((void**)&utmp, (size_t)m * 8);
-        if (e != hipSuccess) {
-            g_last_hip = (int)e;
-            (void)hipGetLastError();
-            return SCD_ENOMEM;
-        }
-        u = utmp;
-    }
-    int rpw, grid;
-    halfstep_geometry(m, &rpw, &grid);
-    int rc = SCD_OK;
-    hipError_t e = launch_halfstep(R, dt, m, n, rpw, grid, 1, tbits, nullptr, nullptr, u, st);
-    if (e == hipSuccess && sbits) e = launch_pack(u, SCD_F64, m, sbits, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e != hipSuccess) {
-        g_last_hip = (int)e;
-        (void)hipGetLastError();
-        rc = SCD_EHIP;
-    }
-    if (utmp) (void)hipFree(utmp);
-    return rc;
+    HIP_TRY(launch_row_sums(R, dt, m, n, tbits, u, sbits, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    return SCD_OK;
 }
 
 // The three launches of a column half step on caller data: per-workgroup partial column sums, their
@@ -1154,7 +1134,7 @@ static hipError_t enqueue_col_signed_sum(const void* R, scd_dtype dt, int64_t m,
                                          const uint64_t* sbits, void* partials, double* cparts, double* v, uint64_t* tbits,
                                          double* cout, hipStream_t st)
 {
-    hipError_t e = launch_halfstep(R, dt, m, n, rpw, grid, 0, nullptr, sbits, partials, nullptr, st);
+    hipError_t e = launch_col_partials(R, dt, m, n, rpw, grid, sbits, partials, st);
     if (e == hipSuccess) e = launch_reduce_plain(partials, dt, grid, n, v, tbits, cparts, st);
     if (e == hipSuccess) e = launch_sum_parts(cparts, (int)words_for(n), cout, st);
     return e;
@@ -1367,7 +1347,7 @@ struct ModeSums {
             double* to = trailing ? W[i & 1] : uA;
             int rpw, grid;
             halfstep_geometry(rows, &rpw, &grid);
-            err = launch_halfstep(from, fdt, rows, wcols, rpw, grid, 0, nullptr, cur[i - 1], partials, nullptr, st);
+            err = launch_col_partials(from, fdt, rows, wcols, rpw, grid, cur[i - 1], partials, st);
             if (err != hipSuccess) return err;
             err = launch_reduce_plain(partials, fdt, grid, wcols, to, nullptr, cparts, st);
             if (err != hipSuccess) return err;
@@ -1381,9 +1361,7 @@ struct ModeSums {
                 if (err != hipSuccess) return err;
                 tau = kr_in;
             }
-            int rpw, grid;
-            halfstep_geometry(dims[i], &rpw, &grid);
-            err = launch_halfstep(src, sdt, dims[i], inner[i], rpw, grid, 1, tau, nullptr, nullptr, uA, st);
+            err = launch_row_sums(src, sdt, dims[i], inner[i], tau, uA, nullptr, st);
         }
         return err;
     }

@@ -293,8 +293,10 @@ hipError_t launch_unpack(const uint64_t* bits, int64_t n, scd_dtype dt, void* va
 hipError_t launch_rng(uint64_t seed, uint64_t term, uint32_t mode, int64_t n, uint64_t* bits, hipStream_t st);
 hipError_t launch_kron_terms(int order, const int64_t* dims, const uint64_t* const* signs, int64_t w,
                              uint64_t* out, int64_t cols, hipStream_t st);
-hipError_t launch_halfstep(const void* R, scd_dtype dt, int64_t m, int64_t n, int rows_per_wg, int grid, int do_rows,
-                           const uint64_t* sumbits, const uint64_t* rowbits, void* partials, double* u, hipStream_t st);
+hipError_t launch_row_sums(const void* R, scd_dtype dt, int64_t m, int64_t n, const uint64_t* tbits, double* u, uint64_t* sbits,
+                           hipStream_t st);  // u, sbits: optional
+hipError_t launch_col_partials(const void* R, scd_dtype dt, int64_t m, int64_t n, int rows_per_wg, int grid, const uint64_t* rowbits,
+                               void* partials, hipStream_t st);
 hipError_t launch_reduce_plain(const void* partials, scd_dtype dt, int nparts, int64_t cols, double* W, uint64_t* bits,
                                double* cparts, hipStream_t st);
 hipError_t launch_sum_parts(const double* parts, int n, double* out, hipStream_t st);

@@ -58,6 +58,19 @@ __device__ __forceinline__ double sum_fixed(const double* x, int n)
     return wave_sum(a);
 }
 
+template <typename TE>
+struct Vec16;
+template <>
+struct Vec16<float> {
+    typedef float4 type;
+    static constexpr int N = 4;
+};
+template <>
+struct Vec16<double> {
+    typedef double2 type;
+    static constexpr int N = 2;
+};
+
 // ------------------------------------------------------------------------------------------------
 // row pass, generic form: any rows, cols; two phases inside a workgroup.
 //   phase A  one wave per row: optional update, squares, signed row sum, sign of the row
@@ -252,16 +265,127 @@ __global__ void __launch_bounds__(kBlock) rowpass_generic_kernel(RowPassArgs a)
     }
 }
 
-// Half steps on caller data (no state): rows only, or columns only with s given in `rowbits`.
-template <typename TE>
+// Half steps on caller data (no state).  Row step: u = R t and s = sgn(u) in one pass; a workgroup takes 8 rows (one
+// byte of sign bits), a wave two, the sums are f64 from the first addition on.  A read of the matrix bounds it:
+// 4096x4096 f32 20.1 us a launch with 4-byte loads and a launch of its own for the signs (3.8), now 12.  Bytes past
+// the last row are written as zeros, so that the words of `sbits` are complete.
+template <typename TE, bool VEC>
 __global__ void __launch_bounds__(kBlock)
-    halfstep_kernel(TE* X, int64_t rows, int64_t cols, int rows_per_wg, int do_rows, const uint64_t* sumbits,
-                    const uint64_t* rowbits, TE* partials, double* u)
+    row_sums_kernel(const TE* __restrict__ X, int64_t rows, int64_t cols, const uint64_t* __restrict__ tbits, double* __restrict__ u,
+                    uint8_t* __restrict__ sbytes)
 {
-    __shared__ uint8_t sh_s[kMaxRowsPerWg];
-    __shared__ double sh_red[kWavesPerBlock];
-    rowpass_generic_body<TE>(X, rows, cols, rows_per_wg, false, false, do_rows != 0, do_rows == 0, sumbits, nullptr,
-                             rowbits, (TE)0, partials, u, nullptr, sh_s, sh_red);
+    constexpr int VE = VEC ? Vec16<TE>::N : 1;
+    constexpr int RW = 2, U = sizeof(TE) == 8 ? 6 : 4;
+    __shared__ double us[kWavesPerBlock * RW];
+    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
+    const int64_t r0 = (int64_t)blockIdx.x * (kWavesPerBlock * RW) + wv * RW;
+    const TE* rowp[RW];
+    double acc[RW];
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+        rowp[r] = X + (r0 + r < rows ? r0 + r : rows - 1) * cols;
+        acc[r] = 0.0;
+    }
+    const int64_t nch = cols / VE;
+    auto add = [&](const TE (&x)[RW][VE], int64_t ch) {
+        const int64_t col = ch * VE;
+        const uint32_t b = (uint32_t)(tbits[col >> 6] >> (col & 63));
+#pragma unroll
+        for (int e = 0; e < VE; ++e) {
+            const double sg = __hiloint2double((int)(0x3FF00000u | (((b >> e) & 1u) << 31)), 0);
+#pragma unroll
+            for (int r = 0; r < RW; ++r) acc[r] = __builtin_fma((double)x[r][e], sg, acc[r]);
+        }
+    };
+    auto load = [&](TE (&x)[RW][VE], int64_t ch) {
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            if constexpr (VEC) {
+                typedef typename Vec16<TE>::type V;
+                const V v = ((const V*)rowp[r])[ch];
+                x[r][0] = v.x;
+                x[r][1] = v.y;
+                if constexpr (VE == 4) x[r][2] = v.z, x[r][3] = v.w;
+            } else {
+                x[r][0] = rowp[r][ch];
+            }
+        }
+    };
+    int64_t ch = lane;
+    for (; ch + (U - 1) * kWave < nch; ch += U * kWave) {
+        TE x[U][RW][VE];
+#pragma unroll
+        for (int i = 0; i < U; ++i) load(x[i], ch + i * kWave);
+#pragma unroll
+        for (int i = 0; i < U; ++i) add(x[i], ch + i * kWave);
+    }
+    for (; ch < nch; ch += kWave) {
+        TE x[RW][VE];
+        load(x, ch);
+        add(x, ch);
+    }
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+        const double v = wave_sum(acc[r]);
+        if (lane == 0) {
+            us[wv * RW + r] = r0 + r < rows ? v : 0.0;
+            if (u && r0 + r < rows) u[r0 + r] = v;
+        }
+    }
+    if (!sbytes) return;
+    __syncthreads();
+    if (wv == 0) {
+        const uint64_t neg = __ballot(lane < kWavesPerBlock * RW && us[lane & (kWavesPerBlock * RW - 1)] < 0.0);
+        if (lane == 0) sbytes[blockIdx.x] = (uint8_t)neg;
+    }
+}
+
+// Column step: partials[g][l] = sum over the rows of group g (rows_per_wg of them, in order) of the entries with the
+// signs `rowbits`.  A thread takes 16-byte chunks of the columns, four rows in flight.
+template <typename TE, bool VEC>
+__global__ void __launch_bounds__(kBlock)
+    col_partials_kernel(const TE* __restrict__ X, int64_t rows, int64_t cols, int rows_per_wg, const uint64_t* __restrict__ rowbits,
+                        TE* __restrict__ partials)
+{
+    constexpr int VE = VEC ? Vec16<TE>::N : 1;
+    typedef typename Vec16<TE>::type V;
+    const int64_t r0 = (int64_t)blockIdx.x * rows_per_wg;
+    const int nr = (int)(r0 + rows_per_wg < rows ? rows_per_wg : rows - r0);
+    const int64_t nch = cols / VE;
+    for (int64_t ch = threadIdx.x; ch < nch; ch += kBlock) {
+        TE acc[VE];
+#pragma unroll
+        for (int e = 0; e < VE; ++e) acc[e] = 0;
+        for (int rb = 0; rb < nr; rb += 4) {
+            TE x[4][VE];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const TE* p = X + (r0 + (rb + i < nr ? rb + i : rb)) * cols + ch * VE;
+                if constexpr (VEC) {
+                    const V v = *(const V*)p;
+                    x[i][0] = v.x;
+                    x[i][1] = v.y;
+                    if constexpr (VE == 4) x[i][2] = v.z, x[i][3] = v.w;
+                } else {
+                    x[i][0] = p[0];
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (rb + i >= nr) break;
+                const uint32_t neg = bit_at(rowbits, r0 + rb + i);
+#pragma unroll
+                for (int e = 0; e < VE; ++e) acc[e] += flip(x[i][e], neg);
+            }
+        }
+        TE* dst = partials + (int64_t)blockIdx.x * cols + ch * VE;
+        if constexpr (VEC) {
+            if constexpr (VE == 4) *(V*)dst = V{acc[0], acc[1], acc[2], acc[3]};
+            else *(V*)dst = V{acc[0], acc[1]};
+        } else {
+            dst[0] = acc[0];
+        }
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -276,19 +400,6 @@ __global__ void __launch_bounds__(kBlock)
 // Loads are never predicated: a row or chunk index past the end is clamped to the last valid one
 // (the address stays in bounds) and the value is zeroed afterwards, only in the code path that
 // handles a ragged batch.  Full batches run without any select.
-
-template <typename TE>
-struct Vec16;
-template <>
-struct Vec16<float> {
-    typedef float4 type;
-    static constexpr int N = 4;
-};
-template <>
-struct Vec16<double> {
-    typedef double2 type;
-    static constexpr int N = 2;
-};
 
 template <typename TE, int CPT, int RB>
 struct Tile {
@@ -974,15 +1085,47 @@ hipError_t launch_kron_terms(int order, const int64_t* dims, const uint64_t* con
     return hipGetLastError();
 }
 
-hipError_t launch_halfstep(const void* R, scd_dtype dt, int64_t m, int64_t n, int rows_per_wg, int grid, int do_rows,
-                           const uint64_t* sumbits, const uint64_t* rowbits, void* partials, double* u, hipStream_t st)
+// every row starts on a 16-byte boundary
+static bool rows_aligned(const void* p, scd_dtype dt, int64_t cols)
 {
-    if (dt == SCD_F32)
-        hipLaunchKernelGGL((halfstep_kernel<float>), dim3(grid), dim3(kBlock), 0, st, (float*)R, m, n, rows_per_wg, do_rows,
-                           sumbits, rowbits, (float*)partials, u);
-    else
-        hipLaunchKernelGGL((halfstep_kernel<double>), dim3(grid), dim3(kBlock), 0, st, (double*)R, m, n, rows_per_wg,
-                           do_rows, sumbits, rowbits, (double*)partials, u);
+    return cols % (dt == SCD_F32 ? 4 : 2) == 0 && ((uintptr_t)p & 15u) == 0;
+}
+
+hipError_t launch_row_sums(const void* R, scd_dtype dt, int64_t m, int64_t n, const uint64_t* tbits, double* u, uint64_t* sbits,
+                           hipStream_t st)
+{
+    const dim3 grid((unsigned)((m + 63) / 64 * 8));  // a workgroup per byte of sign bits
+    uint8_t* sb = (uint8_t*)sbits;
+    const bool vec = rows_aligned(R, dt, n);
+    if (dt == SCD_F32) {
+        if (vec) hipLaunchKernelGGL((row_sums_kernel<float, true>), grid, dim3(kBlock), 0, st, (const float*)R, m, n, tbits, u, sb);
+        else hipLaunchKernelGGL((row_sums_kernel<float, false>), grid, dim3(kBlock), 0, st, (const float*)R, m, n, tbits, u, sb);
+    } else {
+        if (vec) hipLaunchKernelGGL((row_sums_kernel<double, true>), grid, dim3(kBlock), 0, st, (const double*)R, m, n, tbits, u, sb);
+        else hipLaunchKernelGGL((row_sums_kernel<double, false>), grid, dim3(kBlock), 0, st, (const double*)R, m, n, tbits, u, sb);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_col_partials(const void* R, scd_dtype dt, int64_t m, int64_t n, int rows_per_wg, int grid, const uint64_t* rowbits,
+                               void* partials, hipStream_t st)
+{
+    const bool vec = rows_aligned(R, dt, n) && ((uintptr_t)partials & 15u) == 0;
+    if (dt == SCD_F32) {
+        if (vec)
+            hipLaunchKernelGGL((col_partials_kernel<float, true>), dim3(grid), dim3(kBlock), 0, st, (const float*)R, m, n, rows_per_wg,
+                               rowbits, (float*)partials);
+        else
+            hipLaunchKernelGGL((col_partials_kernel<float, false>), dim3(grid), dim3(kBlock), 0, st, (const float*)R, m, n, rows_per_wg,
+                               rowbits, (float*)partials);
+    } else {
+        if (vec)
+            hipLaunchKernelGGL((col_partials_kernel<double, true>), dim3(grid), dim3(kBlock), 0, st, (const double*)R, m, n, rows_per_wg,
+                               rowbits, (double*)partials);
+        else
+            hipLaunchKernelGGL((col_partials_kernel<double, false>), dim3(grid), dim3(kBlock), 0, st, (const double*)R, m, n, rows_per_wg,
+                               rowbits, (double*)partials);
+    }
     return hipGetLastError();
 }
 
