@@ -11,6 +11,8 @@
 #include <string.h>
 
 #include <condition_variable>
+#include <iterator>
+#include <list>
 #include <map>
 #include <mutex>
 #include <new>
@@ -133,14 +135,28 @@ std::mutex g_slots_mutex;
 std::condition_variable g_slots_cv;
 int g_slots_in_use = 0;
 
-// hipFree and hipHostFree wait for every stream of the device.  While other contexts keep the device busy
-// from other threads that wait lasts until their launches end, so a context destroyed then parks its
-// blocks here, and contexts created later take blocks of the same size back out (the matrices of a model
-// come in a handful of shapes).  With the device idle the blocks are freed.
+// Device and pinned blocks of contexts and calls come from here and go back here.  Allocating and freeing costs more than
+// a small decomposition's other host work (some twenty blocks; us a call without and with blocks kept: 256x256 to width
+// 64 2594 and 2435, the column half step on 4096x4096 f32 76 and 49, 14336x4096 f32 with 24 terms 14.94 and 14.6 ms), and
+// hipFree and hipHostFree wait for every stream of the device: while other contexts run, that wait lasts until their
+// launches end.  A returned block serves the next request of the same size on its device; its owner has waited for its
+// own work before it returns it.  Kept are at most kPoolKeepBytes (while
+// others run, when freeing would wait: kPoolMaxBytes) and what has been used within the last kPoolAge returns; the rest,
+// and everything when an allocation fails, is given back to the device.
 std::mutex g_pool_mutex;
-std::multimap<size_t, void*> g_pool_dev, g_pool_host;
+struct PoolBlock {
+    void* p;
+    size_t bytes;
+    int dev;
+    bool host;
+    uint64_t stamp;
+};
+std::list<PoolBlock> g_pool;            // oldest first
+std::map<void*, int> g_pool_device;     // device of every block handed out
 size_t g_pool_dev_bytes = 0;
-constexpr size_t kPoolMaxBytes = (size_t)48 << 30;
+uint64_t g_pool_clock = 0;
+constexpr size_t kPoolKeepBytes = (size_t)1 << 30, kPoolMaxBytes = (size_t)48 << 30;
+constexpr uint64_t kPoolAge = 1024;
 
 bool others_running()
 {
@@ -148,48 +164,89 @@ bool others_running()
     return g_slots_in_use > 0;
 }
 
-hipError_t pool_malloc(void** p, size_t bytes, bool host)
+// Frees the oldest blocks until at most `keep` bytes are left, and those that are too old.
+void pool_trim(size_t keep)
 {
+    std::vector<PoolBlock> out;
     {
         std::lock_guard<std::mutex> lk(g_pool_mutex);
-        auto& pool = host ? g_pool_host : g_pool_dev;
-        auto it = pool.find(bytes);
-        if (it != pool.end()) {
-            *p = it->second;
-            pool.erase(it);
+        while (!g_pool.empty() &&
+               (g_pool_dev_bytes > keep || keep == 0 || g_pool.front().stamp + kPoolAge < g_pool_clock)) {
+            out.push_back(g_pool.front());
+            if (!g_pool.front().host) g_pool_dev_bytes -= g_pool.front().bytes;
+            g_pool.pop_front();
+        }
+    }
+    for (PoolBlock& b : out) (void)(b.host ? hipHostFree(b.p) : hipFree(b.p));
+}
+
+hipError_t pool_malloc(void** p, size_t bytes, bool host)
+{
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    {
+        std::lock_guard<std::mutex> lk(g_pool_mutex);
+        for (auto it = g_pool.rbegin(); it != g_pool.rend(); ++it) {  // the latest one first
+            if (it->bytes != bytes || it->host != host || it->dev != dev) continue;
+            *p = it->p;
             if (!host) g_pool_dev_bytes -= bytes;
+            g_pool_device[*p] = dev;
+            g_pool.erase(std::next(it).base());
             return hipSuccess;
         }
     }
-    return host ? hipHostMalloc(p, bytes, hipHostMallocDefault) : hipMalloc(p, bytes);
+    e = host ? hipHostMalloc(p, bytes, hipHostMallocDefault) : hipMalloc(p, bytes);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        pool_trim(0);
+        e = host ? hipHostMalloc(p, bytes, hipHostMallocDefault) : hipMalloc(p, bytes);
+    }
+    if (e == hipSuccess) {
+        std::lock_guard<std::mutex> lk(g_pool_mutex);
+        g_pool_device[*p] = dev;
+    }
+    return e;
 }
 
+// The caller has waited for all work on the block.
 void pool_free(void* p, size_t bytes, bool host)
 {
     if (!p) return;
-    if (others_running()) {
-        std::lock_guard<std::mutex> lk(g_pool_mutex);
-        if (host || g_pool_dev_bytes + bytes <= kPoolMaxBytes) {
-            (host ? g_pool_host : g_pool_dev).emplace(bytes, p);
-            if (!host) g_pool_dev_bytes += bytes;
-            return;
-        }
-    }
-    if (host) (void)hipHostFree(p);
-    else (void)hipFree(p);
-}
-
-void pool_drain()
-{
-    std::multimap<size_t, void*> dev, host;
+    const bool busy = others_running();
+    bool keep;
     {
         std::lock_guard<std::mutex> lk(g_pool_mutex);
-        dev.swap(g_pool_dev);
-        host.swap(g_pool_host);
-        g_pool_dev_bytes = 0;
+        auto it = g_pool_device.find(p);
+        const int dev = it == g_pool_device.end() ? 0 : it->second;
+        if (it != g_pool_device.end()) g_pool_device.erase(it);
+        keep = host || (busy ? g_pool_dev_bytes + bytes <= kPoolMaxBytes : bytes <= kPoolKeepBytes);
+        if (keep) {
+            g_pool.push_back({p, bytes, dev, host, ++g_pool_clock});
+            if (!host) g_pool_dev_bytes += bytes;
+        }
     }
-    for (auto& kv : dev) (void)hipFree(kv.second);
-    for (auto& kv : host) (void)hipHostFree(kv.second);
+    if (!keep) (void)(host ? hipHostFree(p) : hipFree(p));
+    if (!busy) pool_trim(kPoolKeepBytes);
+}
+
+// Waits for the work of a stream on blocks that are about to be returned; for the whole device where the stream cannot
+// be waited for.
+void settle(hipStream_t st)
+{
+    if (hipStreamSynchronize(st) != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipDeviceSynchronize();
+        (void)hipGetLastError();
+    }
+}
+
+int device_cus()
+{
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;
+    (void)hipGetLastError();
+    return cus > 0 ? cus : 256;
 }
 
 int dev_alloc(scd_ctx* c, void** p, size_t bytes)
@@ -715,15 +772,7 @@ int scd_create(scd_ctx** out, const void* A, scd_dtype dt, int order, const int6
     c->stream = (hipStream_t)stream;
     for (int i = 0; i < order; ++i) c->dims[i] = dims[i];
     // one workgroup per compute unit: every partial row costs a write and a read per alternation
-    int cus = 256;
-    {
-        int devid = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&devid) == hipSuccess && hipGetDeviceProperties(&prop, devid) == hipSuccess &&
-            prop.multiProcessorCount > 0)
-            cus = prop.multiProcessorCount;
-        (void)hipGetLastError();
-    }
+    const int cus = device_cus();
     const int wg_target = cus;
 
     int st = SCD_OK;
@@ -813,11 +862,10 @@ int scd_create(scd_ctx** out, const void* A, scd_dtype dt, int order, const int6
 void scd_destroy(scd_ctx* c)
 {
     if (!c) return;
-    (void)hipStreamSynchronize(c->stream);
+    settle(c->stream);
     for (auto& b : c->allocs) pool_free(b.first, b.second, false);
     pool_free(c->pinned, sizeof(State), true);
     pool_free(c->res_pin, sizeof(ResidentResult), true);
-    if (!others_running()) pool_drain();
     if (c->ev0) (void)hipEventDestroy(c->ev0);
     if (c->ev1) (void)hipEventDestroy(c->ev1);
     (void)hipGetLastError();
@@ -1149,30 +1197,27 @@ int scd_col_signed_sum(const void* R, scd_dtype dt, int64_t m, int64_t n, const 
     halfstep_geometry(m, &rpw, &grid);
     const size_t es = dt == SCD_F32 ? 4 : 8;
     const int ncp = (int)words_for(n);
-    void* partials = nullptr;
-    double* cparts = nullptr;
-    double* ctmp = nullptr;
-    int rc = SCD_OK;
-    hipError_t e = hipMalloc(&partials, (size_t)grid * (size_t)n * es);
-    if (e == hipSuccess) e = hipMalloc((void**)&cparts, (size_t)ncp * 8);
-    if (e == hipSuccess && !cout) e = hipMalloc((void**)&ctmp, 8);
+    // one block: the cut value when the caller does not want it, the partial sums of |v|, the partial column sums
+    const size_t cparts_bytes = (((size_t)ncp * 8 + 255) / 256) * 256, bytes = 256 + cparts_bytes + (size_t)grid * (size_t)n * es;
+    unsigned char* base = nullptr;
+    hipError_t e = pool_malloc((void**)&base, bytes, false);
     if (e != hipSuccess) {
         g_last_hip = (int)e;
         (void)hipGetLastError();
-        rc = SCD_ENOMEM;
-    } else {
-        e = enqueue_col_signed_sum(R, dt, m, n, rpw, grid, sbits, partials, cparts, v, tbits, cout ? cout : ctmp, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-        if (e != hipSuccess) {
-            g_last_hip = (int)e;
-            (void)hipGetLastError();
-            rc = SCD_EHIP;
-        }
+        return SCD_ENOMEM;
     }
-    if (partials) (void)hipFree(partials);
-    if (cparts) (void)hipFree(cparts);
-    if (ctmp) (void)hipFree(ctmp);
-    return rc;
+    e = enqueue_col_signed_sum(R, dt, m, n, rpw, grid, sbits, base + 256 + cparts_bytes, (double*)(base + 256), v, tbits,
+                               cout ? cout : (double*)base, st);
+    hipError_t es2 = hipStreamSynchronize(st);
+    if (e == hipSuccess) e = es2;
+    if (es2 != hipSuccess) settle(st);
+    pool_free(base, bytes, false);
+    if (e != hipSuccess) {
+        g_last_hip = (int)e;
+        (void)hipGetLastError();
+        return SCD_EHIP;
+    }
+    return SCD_OK;
 }
 
 // ---------------------------------------------------------------------------------------------- no allocation
@@ -1242,9 +1287,10 @@ int scd_expand(const uint64_t* const* signs, const void* cvec, scd_dtype dt, int
     hipStream_t st = (hipStream_t)stream;
     const int64_t m = dims[0], cols = total / dims[0];
     uint64_t* kr = nullptr;
+    const size_t kr_bytes = (size_t)w * (size_t)words_for(cols) * 8;
     const uint64_t* T = signs[1];
     if (order >= 3 && w > 0) {
-        hipError_t e = hipMalloc((void**)&kr, (size_t)w * (size_t)words_for(cols) * 8);
+        hipError_t e = pool_malloc((void**)&kr, kr_bytes, false);
         if (e != hipSuccess) {
             g_last_hip = (int)e;
             (void)hipGetLastError();
@@ -1254,14 +1300,18 @@ int scd_expand(const uint64_t* const* signs, const void* cvec, scd_dtype dt, int
         if (e != hipSuccess) {
             g_last_hip = (int)e;
             (void)hipGetLastError();
-            (void)hipFree(kr);
+            settle(st);
+            pool_free(kr, kr_bytes, false);
             return SCD_EHIP;
         }
         T = kr;
     }
     hipError_t e = launch_expand(signs[0], T, cvec, dt, m, cols, w, out, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (kr) (void)hipFree(kr);
+    if (kr) {
+        if (e != hipSuccess) settle(st);
+        pool_free(kr, kr_bytes, false);
+    }
     if (e != hipSuccess) {
         g_last_hip = (int)e;
         (void)hipGetLastError();
@@ -1289,16 +1339,17 @@ struct ModeSums {
     void* partials = nullptr;
     uint64_t* kr_in = nullptr;
     uint64_t* cur[SCD_MAX_ORDER] = {nullptr};  // current sign vector of every mode
-    std::vector<void*> bufs;
+    std::vector<std::pair<void*, size_t>> bufs;
 
     bool alloc(void** p, size_t bytes)
     {
-        if (hipMalloc(p, bytes ? bytes : 8) != hipSuccess) {
+        if (bytes == 0) bytes = 8;
+        if (pool_malloc(p, bytes, false) != hipSuccess) {
             (void)hipGetLastError();
             *p = nullptr;
             return false;
         }
-        bufs.push_back(*p);
+        bufs.emplace_back(*p, bytes);
         return true;
     }
     bool init(int ord, const int64_t* d)
@@ -1329,7 +1380,7 @@ struct ModeSums {
     }
     void release()
     {
-        for (void* p : bufs) (void)hipFree(p);
+        for (auto& b : bufs) pool_free(b.first, b.second, false);  // (the caller has waited for the stream)
         bufs.clear();
     }
     // uA <- x x_i (others), x of dtype dt
@@ -1398,17 +1449,17 @@ int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uin
     const size_t bytes = words * 8 + (((size_t)w * 4 + 15) & ~(size_t)15) + sizeof(LsqState);
     void* dev = nullptr;
     Pinned* pin = nullptr;
-    hipError_t e = hipMalloc(&dev, bytes);
-    if (e == hipSuccess) e = hipHostMalloc((void**)&pin, sizeof(Pinned), hipHostMallocDefault);
+    hipError_t e = pool_malloc(&dev, bytes, false);
+    if (e == hipSuccess) e = pool_malloc((void**)&pin, sizeof(Pinned), true);
     if (e != hipSuccess) {
         (void)hipGetLastError();
-        if (dev) (void)hipFree(dev);
+        if (dev) pool_free(dev, bytes, false);
         return SCD_ENOMEM;
     }
     auto cleanup = [&](int code) {
-        (void)hipStreamSynchronize(st);
-        (void)hipFree(dev);
-        (void)hipHostFree(pin);
+        settle(st);
+        pool_free(dev, bytes, false);
+        pool_free(pin, sizeof(Pinned), true);
         (void)hipGetLastError();
         return code;
     };
@@ -1520,15 +1571,15 @@ int scd_lsq_decompose_tensor(const void* A, scd_dtype dt, int order, const int64
          ms.alloc((void**)&L, (size_t)wl * wl * 8) && ms.alloc((void**)&yv, (size_t)wl * 8) && ms.alloc((void**)&c, (size_t)wl * 8) &&
          ms.alloc((void**)&bvec, (size_t)wl * 8) &&
          ms.alloc((void**)&sq, (size_t)nsq * 8) && ms.alloc((void**)&status, 4);
-    if (ok && hipHostMalloc((void**)&host, 4 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+    if (ok && pool_malloc((void**)&host, 4 * sizeof(double), true) != hipSuccess) {
         (void)hipGetLastError();
         host = nullptr;
         ok = false;
     }
     auto cleanup = [&](int code) {
-        (void)hipStreamSynchronize(st);
+        settle(st);
         ms.release();
-        if (host) (void)hipHostFree(host);
+        if (host) pool_free(host, 4 * sizeof(double), true);
         (void)hipGetLastError();
         return code;
     };
@@ -1628,7 +1679,7 @@ int scd_decompose_scalars(const void* A, scd_dtype dt, int order, const int64_t*
         if (rc < 0) return rc;
         rc = scd_set_max_iters(c, max_iters);
         if (rc >= 0 && c->pstream) {
-            hipError_t e = hipMalloc(&c->c_scal, (size_t)w * (size_t)q * es);
+            hipError_t e = pool_malloc(&c->c_scal, (size_t)w * (size_t)q * es, false);
             if (e != hipSuccess) {
                 g_last_hip = (int)e;
                 (void)hipGetLastError();
@@ -1651,8 +1702,8 @@ int scd_decompose_scalars(const void* A, scd_dtype dt, int order, const int64_t*
                     run = SCD_EHIP;
                 }
             }
-            (void)hipStreamSynchronize(st);
-            if (c->c_scal) (void)hipFree(c->c_scal);
+            settle(st);
+            if (c->c_scal) pool_free(c->c_scal, (size_t)w * (size_t)q * es, false);
             c->c_scal = nullptr;
             scd_destroy(c);
             return run;
@@ -1672,15 +1723,15 @@ int scd_decompose_scalars(const void* A, scd_dtype dt, int order, const int64_t*
     ok = ok && ms.alloc(&R, (size_t)total * es) && ms.alloc((void**)&absp, (size_t)ms.max_words * 8) &&
          ms.alloc((void**)&dotp, (size_t)ms.max_words * 8) && ms.alloc((void**)&scal, 16) &&
          ms.alloc((void**)&sq, (size_t)nsq * 8) && ms.alloc((void**)&lead, (size_t)words_for(P) * 8);
-    if (ok && hipHostMalloc((void**)&host, 4 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+    if (ok && pool_malloc((void**)&host, 4 * sizeof(double), true) != hipSuccess) {
         (void)hipGetLastError();
         host = nullptr;
         ok = false;
     }
     auto cleanup = [&](int code) {
-        (void)hipStreamSynchronize(st);
+        settle(st);
         ms.release();
-        if (host) (void)hipHostFree(host);
+        if (host) pool_free(host, 4 * sizeof(double), true);
         (void)hipGetLastError();
         return code;
     };

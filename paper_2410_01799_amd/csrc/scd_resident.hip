@@ -740,14 +740,13 @@ static hipError_t launch_resident_k(const ResidentArgs& a, hipStream_t st)
     // All P x P workgroups must be resident at once.  One workgroup of 512 threads fits every compute
     // unit (checked here against the occupancy the runtime reports); an ordinary launch on an idle
     // device then places them all, and every wait in the kernel is bounded in case it does not.
-    int dev = 0, per_cu = 0;
-    hipDeviceProp_t prop;
+    int dev = 0, per_cu = 0, cus = 0;
     hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipGetDeviceProperties(&prop, dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess)
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, resident_kernel<TR, TC, P, PAD>, kResThreads, 0);
     if (e != hipSuccess) return e;
-    if ((int64_t)per_cu * prop.multiProcessorCount < P * P) return hipErrorCooperativeLaunchTooLarge;
+    if ((int64_t)per_cu * cus < P * P) return hipErrorCooperativeLaunchTooLarge;
     hipLaunchKernelGGL((resident_kernel<TR, TC, P, PAD>), dim3(P * P), dim3(kResThreads), 0, st, a);
     return hipGetLastError();
 }

@@ -1255,10 +1255,9 @@ static hipError_t launch_sparse_t(const SparseArgs& a, hipStream_t st)
     // always the same ceiling, whatever this launch needs: launches from several host threads set it too
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSpMaxLds);
     if (e != hipSuccess) return e;
-    int dev = 0, per_cu = 0;
-    hipDeviceProp_t prop;
+    int dev = 0, per_cu = 0, cus = 0;
     e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipGetDeviceProperties(&prop, dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess) {
         if (a.delay_width > 0) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sparse_delay_kernel<TE>, kSpThreads, lds);
         else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sparse_kernel<TE>, kSpThreads, lds);
@@ -1266,7 +1265,7 @@ static hipError_t launch_sparse_t(const SparseArgs& a, hipStream_t st)
     if (e != hipSuccess) return e;
     // all workgroups must be resident at once (every wait in the kernel is bounded in case they are not)
     if (a.grid < 1 || a.grid > kSpGrid) return hipErrorInvalidValue;
-    if ((int64_t)per_cu * prop.multiProcessorCount < a.grid) return hipErrorCooperativeLaunchTooLarge;
+    if ((int64_t)per_cu * cus < a.grid) return hipErrorCooperativeLaunchTooLarge;
     if (a.delay_width > 0) hipLaunchKernelGGL((sparse_delay_kernel<TE>), dim3(a.grid), dim3(kSpThreads), lds, st, a);
     else hipLaunchKernelGGL((sparse_kernel<TE>), dim3(a.grid), dim3(kSpThreads), lds, st, a);
     return hipGetLastError();

@@ -914,13 +914,12 @@ hipError_t ps_launch_k(const PStreamArgs& a, size_t lds_bytes, hipStream_t st)
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
     if (e != hipSuccess) return e;
     // every workgroup of the grid must be resident at once: one per compute unit is enough
-    int dev = 0, per_cu = 0;
-    hipDeviceProp_t prop;
+    int dev = 0, per_cu = 0, cus = 0;
     e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipGetDeviceProperties(&prop, dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kPsThreads, lds_bytes);
     if (e != hipSuccess) return e;
-    if ((int64_t)per_cu * prop.multiProcessorCount < a.grid) return hipErrorCooperativeLaunchTooLarge;
+    if ((int64_t)per_cu * cus < a.grid) return hipErrorCooperativeLaunchTooLarge;
     hipLaunchKernelGGL(kern, dim3(a.grid), dim3(kPsThreads), lds_bytes, st, a);
     return hipGetLastError();
 }
