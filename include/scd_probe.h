@@ -24,7 +24,7 @@ int scd_traffic(const scd_ctx* ctx, double* bytes, int64_t* passes, int64_t* swe
 
 /* Which engine scd_run uses for this context: 0 = a stream of launches that re-read the remainder from
  * memory every alternation (any shape, dtype, order); 1 = one persistent launch that keeps the whole
- * remainder in the register files of a grid of workgroups (f32 matrices that fit, see SCD_OPT_RESIDENT);
+ * remainder in the register files of a grid of workgroups (matrices that fit, see SCD_OPT_RESIDENT);
  * 2 = one persistent launch that caches R t and R^T s and updates them from the flipped signs only
  * (Section 3.1; f32/f64 matrices with 8 <= m, n <= 65536 whose rows and columns are multiples of 16 bytes and
  * whose remainder takes at least SCD_OPT_SPARSE_MIN_MIB, or any size once the context has a share of the

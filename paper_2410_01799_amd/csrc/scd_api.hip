@@ -460,7 +460,7 @@ int setup_engines(scd_ctx* c)
 {
     const int limit = c->share > 0 ? c->share : c->cus;
     c->resident = c->opt[SCD_OPT_RESIDENT] != 0 && resident_supported(c->dt, c->order, c->dims) &&
-                  resident_workgroups(c->dims) <= limit;
+                  resident_workgroups(c->dt, c->dims) <= limit;
     c->sparse = false;
     if (!c->resident && c->opt[SCD_OPT_SPARSE] != 0) {
         // The sparse engine pays about 15 us per alternation whatever the size, the launch-stream engine
@@ -689,7 +689,7 @@ int run_resident(scd_ctx* c, int64_t n)
 {
     ResidentArgs a;
     memset(&a, 0, sizeof(a));
-    a.R = (float*)c->R;
+    a.R = c->R;
     a.m = c->dims[0];
     a.n = c->dims[1];
     a.seed = c->seed;
@@ -697,23 +697,23 @@ int run_resident(scd_ctx* c, int64_t n)
     a.w_target = c->hs.k + n;
     a.max_iters = c->hs.max_iters;
     a.max_spin = (int32_t)c->opt[SCD_OPT_MAX_SPIN];
-    resident_poll_delays(c->dims, (int)c->opt[SCD_OPT_POLL_DELAY], &a.poll_delay, &a.poll_delay_v);
+    resident_poll_delays(c->dt, c->dims, (int)c->opt[SCD_OPT_POLL_DELAY], &a.poll_delay, &a.poll_delay_v);
     a.seq_u = c->seq_u;
     a.seq_v = c->seq_v;
     a.xbuf = c->xbuf;
     a.S = c->out_signs[0];
     a.T = c->out_signs[1];
-    a.c = (float*)c->c_out;
+    a.c = c->c_out;
     a.iters = c->iters;
     a.trace = c->trace;
     a.mw = (int32_t)words_for(c->dims[0]);
     a.nw = (int32_t)words_for(c->dims[1]);
     a.res = c->res_dev;
     SlotLease lease;
-    lease.acquire(resident_workgroups(c->dims), c->cus);
+    lease.acquire(resident_workgroups(c->dt, c->dims), c->cus);
     HIP_TRY(hipMemsetAsync(c->res_dev, 0, sizeof(ResidentResult), c->stream));
     HIP_TRY(hipEventRecord(c->ev0, c->stream));
-    HIP_TRY(launch_resident(a, c->stream));
+    HIP_TRY(launch_resident(a, c->dt, c->stream));
     HIP_TRY(hipEventRecord(c->ev1, c->stream));
     HIP_TRY(hipMemcpyAsync(c->res_pin, c->res_dev, sizeof(ResidentResult), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));

@@ -122,7 +122,7 @@ struct ResidentResult {
 };
 
 struct ResidentArgs {
-    float* R;
+    void* R;
     int64_t m, n;
     uint64_t seed;
     int64_t k_start, w_target;
@@ -133,7 +133,7 @@ struct ResidentArgs {
     uint64_t* xbuf;          // [2 kinds][2 parities][256 workgroups][kResSlotWords]
     uint64_t* S;
     uint64_t* T;
-    float* c;
+    void* c;
     int32_t* iters;
     double* trace;
     int32_t mw, nw;
@@ -141,9 +141,9 @@ struct ResidentArgs {
 };
 
 bool resident_supported(scd_dtype dt, int order, const int64_t* dims);
-int resident_workgroups(const int64_t* dims);  // workgroups of the launch for a supported shape
-void resident_poll_delays(const int64_t* dims, int delay, int32_t* rows, int32_t* cols);  // of the two exchanges
-hipError_t launch_resident(const ResidentArgs& a, hipStream_t st);
+int resident_workgroups(scd_dtype dt, const int64_t* dims);  // workgroups of the launch for a supported shape
+void resident_poll_delays(scd_dtype dt, const int64_t* dims, int delay, int32_t* rows, int32_t* cols);  // of the two exchanges
+hipError_t launch_resident(const ResidentArgs& a, scd_dtype dt, hipStream_t st);
 
 // Sparse engine (scd_sparse.hip): cached products updated from the flipped signs only; keeps R and its
 // transpose in HBM.

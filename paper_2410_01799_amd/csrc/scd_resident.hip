@@ -165,6 +165,14 @@ __device__ __forceinline__ double wave_sum_res(double a)
 // that halve the registers at each step, signs kept as factor bytes, scalar bases for the gathers and the test
 // behind the column sums; 5.40 with the poll delays of resident_poll_delays.  256x256: 3.9 -> 2.9, 1024x1024:
 // 4.4 -> 3.4, 2048x2048: 5.45 -> 4.65.
+//
+// f64 (TE = double): everything the exchanges carry and the tiles hold stays 64 bits wide, so a thread holds at most 64
+// values (matrices up to 4096x2048 or 2048x4096) and a published value is two tagged words, all lower halves of a slot
+// before all upper ones, so that a wave's loads stay contiguous.  The same chain with twice the words; measured in us per
+// alternation against the best of the other engines on the same matrix: 256x256 3.4 (9.4 persistent stream), 1024x1024
+// 4.8 (11.2), 1501x999 6.8 (19.4, launch stream), 1024x4096 7.5 (15.2), 2048x2048 6.9 (13.6), 4096x2048 8.0 (9.7,
+// sparse), 2048x4096 7.7 (9.9, sparse), 2000x3999 7.7 (65.9, launch stream).  The 64-value tiles on 16 x 16 workgroups
+// spill 28 to 56 bytes a thread.
 // The sum of the 16 column-block shares of c rides on the next row-phase exchange, so the test of
 // Algorithm 4 line 8 is taken one phase late: the row phase already done with the final t is then
 // dropped.  ||R||_F^2 after an update travels the same way (block row sums, then the total).
@@ -193,10 +201,21 @@ __device__ __forceinline__ double uniform_f64(double v)
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-__device__ __forceinline__ void res_publish(uint64_t* p, float v, uint32_t seq)
+// Tagged words per published value: the value itself (f32), or its two halves, `apart` words from each other (f64).
+template <typename TE>
+constexpr int kResWords = (int)(sizeof(TE) / 4);
+
+__device__ __forceinline__ void res_publish(uint64_t* p, int apart, float v, uint32_t seq)
 {
+    (void)apart;
     __hip_atomic_store(p, ((uint64_t)seq << 32) | (uint64_t)__float_as_uint(v), __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void res_publish(uint64_t* p, int apart, double v, uint32_t seq)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    __hip_atomic_store(p, ((uint64_t)seq << 32) | (b & 0xFFFFFFFFull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p + apart, ((uint64_t)seq << 32) | (b >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __device__ __forceinline__ void res_publish_f64(uint64_t* p, double v, uint32_t seq)
@@ -212,34 +231,41 @@ __device__ __forceinline__ void res_publish_f64(uint64_t* p, double v, uint32_t 
 // exchange, all are read again (re-reads are rare once the first read is delayed a little).  `base` is the same
 // for the whole workgroup and `off` (bytes) the same in every exchange: the loads take a scalar base and a 32-bit
 // lane offset, so that no 64-bit lane address is worked out between the wait and the first load.
-template <int H, int NX>
-__device__ __forceinline__ bool res_gather(const char* base, uint32_t off, uint32_t stride, const char* xbase, uint32_t xoff,
+template <typename TE, int H, int NX>
+__device__ __forceinline__ bool res_gather(const char* base, uint32_t off, uint32_t stride, uint32_t apart, const char* xbase, uint32_t xoff,
                                            uint32_t seq, int max_spin, double& sum, double& x0, double& x1, int& spin)
 {
     static_assert(NX == 0 || NX == 2 || NX == 4, "none, one or two piggybacked doubles");
-    uint64_t w[H + 4];
-    w[H + 2] = 0;
-    w[H + 3] = 0;
+    constexpr int W = kResWords<TE>, N = W * H;
+    uint64_t w[N + 4];
+    w[N + 2] = 0;
+    w[N + 3] = 0;
     for (;;) {
 #pragma unroll
         for (int q = 0; q < H; ++q)
-            w[q] = __hip_atomic_load((const uint64_t*)(base + (size_t)q * stride + off), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int h = 0; h < W; ++h)
+                w[W * q + h] = __hip_atomic_load((const uint64_t*)(base + (size_t)q * stride + (size_t)h * apart + off), __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
         for (int q = 0; q < NX; ++q)
-            w[H + q] = __hip_atomic_load((const uint64_t*)(xbase + q * 8 + xoff), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            w[N + q] = __hip_atomic_load((const uint64_t*)(xbase + q * 8 + xoff), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         uint32_t stale = 0;
 #pragma unroll
-        for (int q = 0; q < H + NX; ++q) stale |= (uint32_t)(w[q] >> 32) ^ seq;
+        for (int q = 0; q < N + NX; ++q) stale |= (uint32_t)(w[q] >> 32) ^ seq;
         if (__ballot(stale != 0) == 0) break;
         if (++spin > max_spin) return false;
         __builtin_amdgcn_s_sleep(1);
     }
     double s = 0.0;
 #pragma unroll
-    for (int q = 0; q < H; ++q) s += (double)__uint_as_float((uint32_t)w[q]);
+    for (int q = 0; q < H; ++q) {
+        if constexpr (W == 1) s += (double)__uint_as_float((uint32_t)w[q]);
+        else s += __longlong_as_double((long long)((w[2 * q + 1] << 32) | (w[2 * q] & 0xFFFFFFFFull)));
+    }
     sum = s;
-    if constexpr (NX >= 2) x0 = __longlong_as_double((long long)((w[H + 1] << 32) | (w[H] & 0xFFFFFFFFull)));
-    if constexpr (NX == 4) x1 = __longlong_as_double((long long)((w[H + 3] << 32) | (w[H + 2] & 0xFFFFFFFFull)));
+    if constexpr (NX >= 2) x0 = __longlong_as_double((long long)((w[N + 1] << 32) | (w[N] & 0xFFFFFFFFull)));
+    if constexpr (NX == 4) x1 = __longlong_as_double((long long)((w[N + 3] << 32) | (w[N + 2] & 0xFFFFFFFFull)));
     return true;
 }
 
@@ -248,6 +274,53 @@ __device__ __forceinline__ float dpp_f32(float v)
 {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
 }
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_val(float v)
+{
+    return dpp_f32<CTRL>(v);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_val(double v)
+{
+    return dpp_f64_res<CTRL, 0>(v);
+}
+__device__ __forceinline__ float res_fma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double res_fma(double a, double b, double c) { return __builtin_fma(a, b, c); }
+// the sign bit of a factor +-1.0, at the top of a word; ck with that word's top bit flipped in
+__device__ __forceinline__ uint32_t sign_of(float f) { return __float_as_uint(f) & 0x80000000u; }
+__device__ __forceinline__ uint32_t sign_of(double f) { return (uint32_t)__double2hiint(f) & 0x80000000u; }
+__device__ __forceinline__ float flip_by(float ck, uint32_t top) { return __uint_as_float(__float_as_uint(ck) ^ top); }
+__device__ __forceinline__ double flip_by(double ck, uint32_t top)
+{
+    return __hiloint2double((int)((uint32_t)__double2hiint(ck) ^ top), __double2loint(ck));
+}
+
+// 16 bytes of the matrix
+template <typename TE>
+struct ResVec;
+template <>
+struct ResVec<float> {
+    typedef float4 type;
+    static constexpr int N = 4;
+    static __device__ __forceinline__ void get(const float* p, float* x)
+    {
+        const float4 v = *(const float4*)p;
+        x[0] = v.x, x[1] = v.y, x[2] = v.z, x[3] = v.w;
+    }
+    static __device__ __forceinline__ void put(float* p, const float* x) { *(float4*)p = make_float4(x[0], x[1], x[2], x[3]); }
+};
+template <>
+struct ResVec<double> {
+    typedef double2 type;
+    static constexpr int N = 2;
+    static __device__ __forceinline__ void get(const double* p, double* x)
+    {
+        const double2 v = *(const double2*)p;
+        x[0] = v.x, x[1] = v.y;
+    }
+    static __device__ __forceinline__ void put(double* p, const double* x) { *(double2*)p = make_double2(x[0], x[1]); }
+};
 
 // the value of the neighbouring lane (lane ^ 1), for doubles
 __device__ __forceinline__ double dpp_swap1_f64(double v)
@@ -272,6 +345,18 @@ __device__ __forceinline__ float half32(float a, float b)
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
+__device__ __forceinline__ double half16(double a, double b)
+{
+    const auto l = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+__device__ __forceinline__ double half32(double a, double b)
+{
+    const auto l = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
 
 // Sum over groups of N = 4, 8 or 16 neighbouring lanes, the same bits in every lane of a group.
 template <int N>
@@ -284,16 +369,21 @@ __device__ __forceinline__ double group_sum_res(double a)
     return a;
 }
 
-// A sign is kept in LDS as the top byte of the factor +-1.0 it stands for; byte k of a loaded word becomes the
-// factor in one instruction.
+// A sign is kept in LDS as the top byte of the factor +-1.0 it stands for (the same byte in f32 and f64); byte k of a
+// loaded word becomes the factor's (upper) word in one instruction.
 constexpr uint8_t kPosByte = 0x3F, kNegByte = 0xBF;
 template <int K>
-__device__ __forceinline__ float sign_factor(uint32_t bytes)
+__device__ __forceinline__ void sign_factor(uint32_t bytes, float& f)
 {
-    return __uint_as_float(__builtin_amdgcn_perm(bytes, 0x00800000u, 0x00020100u | ((4u + K) << 24)));
+    f = __uint_as_float(__builtin_amdgcn_perm(bytes, 0x00800000u, 0x00020100u | ((4u + K) << 24)));
 }
-template <int N>
-__device__ __forceinline__ void sign_factors(const uint8_t* p, float (&f)[N])
+template <int K>
+__device__ __forceinline__ void sign_factor(uint32_t bytes, double& f)
+{
+    f = __hiloint2double((int)__builtin_amdgcn_perm(bytes, 0x00F00000u, 0x00020100u | ((4u + K) << 24)), 0);
+}
+template <typename TE, int N>
+__device__ __forceinline__ void sign_factors(const uint8_t* p, TE (&f)[N])
 {
     uint32_t w[(N + 3) / 4];
     if constexpr (N >= 4) {
@@ -303,30 +393,35 @@ __device__ __forceinline__ void sign_factors(const uint8_t* p, float (&f)[N])
         w[0] = *(const uint16_t*)p;
     }
 #pragma unroll
-    for (int i = 0; i < N; ++i)
-        f[i] = (i & 3) == 0 ? sign_factor<0>(w[i / 4])
-                            : ((i & 3) == 1 ? sign_factor<1>(w[i / 4]) : ((i & 3) == 2 ? sign_factor<2>(w[i / 4]) : sign_factor<3>(w[i / 4])));
+    for (int i = 0; i < N; ++i) {
+        if ((i & 3) == 0) sign_factor<0>(w[i / 4], f[i]);
+        else if ((i & 3) == 1) sign_factor<1>(w[i / 4], f[i]);
+        else if ((i & 3) == 2) sign_factor<2>(w[i / 4], f[i]);
+        else sign_factor<3>(w[i / 4], f[i]);
+    }
 }
 
 // PAD: the grid overhangs the matrix (a template parameter: the 128 row/column tests of a thread's tile are
 // invariants of the whole launch, and a kernel that has to keep them takes twice the instructions and runs out of
 // scalar registers even when no test ever fails).
-template <int TR, int TC, int P, bool PAD>
+template <typename TE, int TR, int TC, int P, bool PAD>
 __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
 {
+    constexpr int W = kResWords<TE>, VE = ResVec<TE>::N;
+    TE* const Rm = (TE*)a.R;
     constexpr int H = P / 2;  // members per half of an exchange group
     static_assert(P == 4 || P == 8 || P == 16, "grid side");
     constexpr int BM = 32 * TR, BN = 16 * TC;  // block of this workgroup
     static_assert(TR >= 2 && TR <= 16 && (TR % 2) == 0, "rows per thread");
     static_assert(TC >= 4 && TC <= 32 && (TC % 4) == 0, "columns per thread");
-    static_assert(BM + 4 <= kResSlotWords && BN + 4 <= kResSlotWords, "slot size");
+    static_assert(W * BM + 4 <= kResSlotWords && W * BN + 4 <= kResSlotWords, "slot size");
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int tr = tid >> 4, tc = tid & 15;  // 32 x 16 threads, each TR x TC elements
     const int pr = blockIdx.x / P, pc = blockIdx.x % P;
     const int wg = blockIdx.x;
 
     constexpr int NWV = kResThreads / 64;
-    __shared__ float lds_q[NWV][BN];
+    __shared__ __align__(16) TE lds_q[NWV][BN];
     __shared__ __align__(16) uint8_t lds_s[2][BM];  // signs as the top bytes of +-1.0
     __shared__ __align__(16) uint8_t lds_t[BN];
     __shared__ double lds_red[NWV];
@@ -337,27 +432,24 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
     // registers (they add nothing to any sum and stay zero through every update) and are never read or written.
     const int64_t row0 = (int64_t)pr * BM + tr * TR, col0 = (int64_t)pc * BN + tc * TC;
     constexpr bool padded = PAD;
-    float x[TR][TC];
+    TE x[TR][TC];
     {
-        const float* base = a.R + row0 * a.n + col0;
-        if (!padded || (a.n & 3) == 0) {
+        const TE* base = Rm + row0 * a.n + col0;
+        if (!padded || a.n % VE == 0) {
 #pragma unroll
             for (int r = 0; r < TR; ++r)
 #pragma unroll
-                for (int c4 = 0; c4 < TC / 4; ++c4) {
-                    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (!padded || (row0 + r < a.m && col0 + 4 * c4 < a.n)) v = *(const float4*)(base + (int64_t)r * a.n + 4 * c4);
-                    x[r][4 * c4 + 0] = v.x;
-                    x[r][4 * c4 + 1] = v.y;
-                    x[r][4 * c4 + 2] = v.z;
-                    x[r][4 * c4 + 3] = v.w;
+                for (int c = 0; c < TC; c += VE) {
+#pragma unroll
+                    for (int e = 0; e < VE; ++e) x[r][c + e] = 0;
+                    if (!padded || (row0 + r < a.m && col0 + c < a.n)) ResVec<TE>::get(base + (int64_t)r * a.n + c, &x[r][c]);
                 }
         } else {
             // rows that are no multiple of 16 bytes: one element at a time, once per launch
 #pragma unroll
             for (int r = 0; r < TR; ++r)
 #pragma unroll
-                for (int c = 0; c < TC; ++c) x[r][c] = (row0 + r < a.m && col0 + c < a.n) ? base[(int64_t)r * a.n + c] : 0.f;
+                for (int c = 0; c < TC; ++c) x[r][c] = (row0 + r < a.m && col0 + c < a.n) ? base[(int64_t)r * a.n + c] : (TE)0;
         }
     }
     if (tid == 0) lds_fail = 0;
@@ -397,42 +489,42 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
         // The signs enter as +-1.0 multipliers of a fused multiply-add: x * (+-1) is exact, so each step
         // rounds exactly like the sign-flip-and-add of Section 3.4, in one instruction instead of two
         // (this engine is bound by vector instructions and latency, not by memory).
-        float prow;  // the row sum this lane publishes: row tc of the thread row's TR rows (lanes tc < TR)
+        TE prow;  // the row sum this lane publishes: row tc of the thread row's TR rows (lanes tc < TR)
         {
-            float tf[TC];
-            sign_factors<TC>(lds_t + tc * TC, tf);
-            float p[TR];
+            TE tf[TC];
+            sign_factors(lds_t + tc * TC, tf);
+            TE p[TR];
 #pragma unroll
             for (int r = 0; r < TR; ++r) {
-                float s = 0.f;
+                TE s = 0;
 #pragma unroll
-                for (int c = 0; c < TC; ++c) s = __builtin_fmaf(x[r][c], tf[c], s);
+                for (int c = 0; c < TC; ++c) s = res_fma(x[r][c], tf[c], s);
                 p[r] = s;
             }
             // Sum over the 16 lanes that share these rows, lane distances 1, 2, 4, 8.  At distances 1 and 2 a lane
             // keeps only the rows whose low index bits are its own (it hands the others to its neighbour), which
             // halves the registers each time: lane tc ends with rows tc mod 4 and 4 + tc mod 4.
             const bool odd1 = (lane & 1) != 0, odd2 = (lane & 2) != 0;
-            float a1[TR / 2];
+            TE a1[TR / 2];
 #pragma unroll
             for (int i = 0; i < TR / 2; ++i) {
-                const float keep = odd1 ? p[2 * i + 1] : p[2 * i], send = odd1 ? p[2 * i] : p[2 * i + 1];
-                a1[i] = keep + dpp_f32<0xB1>(send);  // lane ^ 1
+                const TE keep = odd1 ? p[2 * i + 1] : p[2 * i], send = odd1 ? p[2 * i] : p[2 * i + 1];
+                a1[i] = keep + dpp_val<0xB1>(send);  // lane ^ 1
             }
             if constexpr (TR == 2) {
-                float s = a1[0];
-                s += dpp_f32<0x4E>(s);   // lane ^ 2
-                s += dpp_f32<0x124>(s);  // row rotate 4
-                s += dpp_f32<0x128>(s);  // row rotate 8
+                TE s = a1[0];
+                s += dpp_val<0x4E>(s);   // lane ^ 2
+                s += dpp_val<0x124>(s);  // row rotate 4
+                s += dpp_val<0x128>(s);  // row rotate 8
                 prow = s;
             } else {
-                float a2[TR / 4];
+                TE a2[TR / 4];
 #pragma unroll
                 for (int i = 0; i < TR / 4; ++i) {
-                    const float keep = odd2 ? a1[2 * i + 1] : a1[2 * i], send = odd2 ? a1[2 * i] : a1[2 * i + 1];
-                    float s = keep + dpp_f32<0x4E>(send);  // lane ^ 2
-                    s += dpp_f32<0x124>(s);                // row rotate 4
-                    s += dpp_f32<0x128>(s);                // row rotate 8
+                    const TE keep = odd2 ? a1[2 * i + 1] : a1[2 * i], send = odd2 ? a1[2 * i] : a1[2 * i + 1];
+                    TE s = keep + dpp_val<0x4E>(send);  // lane ^ 2
+                    s += dpp_val<0x124>(s);             // row rotate 4
+                    s += dpp_val<0x128>(s);             // row rotate 8
                     a2[i] = s;
                 }
                 if constexpr (TR == 8) prow = (lane & 4) ? a2[1] : a2[0];
@@ -443,10 +535,10 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
         ++alternations;
         {
             uint64_t* mine = res_slot(a, 0, seq_u, wg);
-            if (tc < TR) res_publish(mine + tr * TR + tc, prow, seq_u);
+            if (tc < TR) res_publish(mine + tr * TR + tc, BM, prow, seq_u);
             if (tid == 0) {
-                res_publish_f64(mine + BM, cpart, seq_u);
-                if (norm_stage == 1) res_publish_f64(mine + BM + 2, fsq_block, seq_u);  // (only the exchange after an update)
+                res_publish_f64(mine + W * BM, cpart, seq_u);
+                if (norm_stage == 1) res_publish_f64(mine + W * BM + 2, fsq_block, seq_u);  // (only the exchange after an update)
             }
         }
         for (int d = 0; d < a.poll_delay; ++d) __builtin_amdgcn_s_sleep(1);
@@ -459,15 +551,15 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
             double hs = 0.0, x0 = 0.0, x1 = 0.0;
             bool ok;
             if (wv == NWV - 1) {
-                const uint32_t xoff = (uint32_t)((lane & (P - 1)) * kResSlotWords + BM) * 8u;
-                if (norm_stage == 1) ok = res_gather<H, 4>(base, off_u, kResSlotWords * 8, base, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
-                else ok = res_gather<H, 2>(base, off_u, kResSlotWords * 8, base, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
+                const uint32_t xoff = (uint32_t)((lane & (P - 1)) * kResSlotWords + W * BM) * 8u;
+                if (norm_stage == 1) ok = res_gather<TE, H, 4>(base, off_u, kResSlotWords * 8, BM * 8, base, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
+                else ok = res_gather<TE, H, 2>(base, off_u, kResSlotWords * 8, BM * 8, base, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
                 if (lane < P) {
                     lds_x[0][lane] = x0;
                     if (norm_stage == 1) lds_x[1][lane] = x1;
                 }
             } else {
-                ok = res_gather<H, 0>(base, off_u, kResSlotWords * 8, base, 0, seq_u, a.max_spin, hs, x0, x1, spin);
+                ok = res_gather<TE, H, 0>(base, off_u, kResSlotWords * 8, BM * 8, base, 0, seq_u, a.max_spin, hs, x0, x1, spin);
             }
             const double other = dpp_swap1_f64(hs);
             const double u = half ? other + hs : hs + other;
@@ -484,16 +576,16 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
         // ================= column phase: v = R^T s (Algorithm 4 line 6), c = sum |v| (line 7).  Its sums are formed
         // before the stop test below is looked at: the test's chain of additions hides behind them, and a term that
         // ends here has formed one half step too many (once per term).
-        float qv[TC / 4];
+        TE qv[TC / 4];
         {
-            float sf[TR];
-            sign_factors<TR>(&lds_s[cur][tr * TR], sf);
-            float q[TC];
+            TE sf[TR];
+            sign_factors(&lds_s[cur][tr * TR], sf);
+            TE q[TC];
 #pragma unroll
             for (int c = 0; c < TC; ++c) {
-                float s = 0.f;
+                TE s = 0;
 #pragma unroll
-                for (int r = 0; r < TR; ++r) s = __builtin_fmaf(x[r][c], sf[r], s);
+                for (int r = 0; r < TR; ++r) s = res_fma(x[r][c], sf[r], s);
                 q[c] = s;
             }
             // the four thread rows of this wave hold the same columns 16 lanes apart: lane row i ends with the sums
@@ -521,7 +613,7 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
                 cur ^= 1;
                 if (!(c_tot <= c_prev)) warn = 1;
                 const double ck = c_tot / total;
-                const float ckf = (float)ck;
+                const TE ckf = (TE)ck;
                 if (pc == 0 && wv < BM / 64) {
                     const uint64_t word = __ballot(lds_s[cur][wv * 64 + lane] == kNegByte);
                     if (lane == 0 && pr * (BM / 64) + wv < a.mw) a.S[k * a.mw + pr * (BM / 64) + wv] = word;
@@ -531,11 +623,11 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
                     if (lane == 0 && pc * (BN / 64) + wv < a.nw) a.T[k * a.nw + pc * (BN / 64) + wv] = word;
                 }
                 if (wg == 0 && tid == 0) {
-                    a.c[k] = ckf;
+                    ((TE*)a.c)[k] = ckf;
                     a.iters[k] = j;
                 }
-                float tf[TC];
-                sign_factors<TC>(lds_t + tc * TC, tf);
+                TE tf[TC];
+                sign_factors(lds_t + tc * TC, tf);
                 double f = 0.0;
 #pragma unroll
                 for (int r = 0; r < TR; ++r) {
@@ -543,8 +635,8 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
 #pragma unroll
                     for (int c = 0; c < TC; ++c) {
                         // R_il - ck s_i t_l: the signs choose +ck or -ck
-                        const float d = __uint_as_float(__float_as_uint(ckf) ^ sr ^ (__float_as_uint(tf[c]) & 0x80000000u));
-                        x[r][c] = (!padded || (row0 + r < a.m && col0 + c < a.n)) ? x[r][c] - d : 0.f;  // padding stays zero
+                        const TE d = flip_by(ckf, sr ^ sign_of(tf[c]));
+                        x[r][c] = (!padded || (row0 + r < a.m && col0 + c < a.n)) ? x[r][c] - d : (TE)0;  // padding stays zero
                         f += (double)x[r][c] * (double)x[r][c];
                     }
                 }
@@ -572,10 +664,14 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
         }
         {
             // lane (i, tc) holds TC/4 neighbouring columns
-            float* dst = &lds_q[wv][tc * TC + (lane >> 4) * (TC / 4)];
-            if constexpr (TC == 16) *(float4*)dst = make_float4(qv[0], qv[1], qv[2], qv[3]);
-            else if constexpr (TC == 8) *(float2*)dst = make_float2(qv[0], qv[1]);
-            else dst[0] = qv[0];
+            TE* dst = &lds_q[wv][tc * TC + (lane >> 4) * (TC / 4)];
+            if constexpr (TC / 4 >= VE) {
+#pragma unroll
+                for (int g = 0; g < TC / 4; g += VE) ResVec<TE>::put(dst + g, qv + g);
+            } else {
+#pragma unroll
+                for (int g = 0; g < TC / 4; ++g) dst[g] = qv[g];
+            }
         }
         __syncthreads();
         ++seq_v;
@@ -584,17 +680,17 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
             if (tid < BN) {
                 // (all loads in flight together, then the adds in wave order: the empty asm keeps the compiler from
                 // loading two, waiting, adding two)
-                float w[NWV];
+                TE w[NWV];
 #pragma unroll
                 for (int q = 0; q < NWV; ++q) w[q] = lds_q[q][tid];
                 static_assert(NWV == 8, "operands of the asm");
                 asm volatile("" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(w[4]), "+v"(w[5]), "+v"(w[6]), "+v"(w[7]));
-                float s = 0.f;
+                TE s = 0;
 #pragma unroll
                 for (int q = 0; q < NWV; ++q) s += w[q];
-                res_publish(mine + tid, s, seq_v);
+                res_publish(mine + tid, BN, s, seq_v);
             }
-            if (norm_stage == 2 && tid == kResThreads - 1) res_publish_f64(mine + BN, frow, seq_v);
+            if (norm_stage == 2 && tid == kResThreads - 1) res_publish_f64(mine + W * BN, frow, seq_v);
         }
         for (int d = 0; d < a.poll_delay_v; ++d) __builtin_amdgcn_s_sleep(1);
         double absv = 0.0;
@@ -605,11 +701,11 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
             bool ok;
             if (norm_stage == 2 && wv == NWV - 1) {
                 // the block-row sums of squares travel on this exchange once per term
-                ok = res_gather<H, 2>(base, off_v, P * kResSlotWords * 8, base, (uint32_t)((lane & (P - 1)) * P * kResSlotWords + BN) * 8u,
-                                      seq_v, a.max_spin, hs, x0, x1, spin);
+                ok = res_gather<TE, H, 2>(base, off_v, P * kResSlotWords * 8, BN * 8, base,
+                                          (uint32_t)((lane & (P - 1)) * P * kResSlotWords + W * BN) * 8u, seq_v, a.max_spin, hs, x0, x1, spin);
                 if (lane < P) lds_x[1][lane] = x0;
             } else {
-                ok = res_gather<H, 0>(base, off_v, P * kResSlotWords * 8, base, 0, seq_v, a.max_spin, hs, x0, x1, spin);
+                ok = res_gather<TE, H, 0>(base, off_v, P * kResSlotWords * 8, BN * 8, base, 0, seq_v, a.max_spin, hs, x0, x1, spin);
             }
             const double other = dpp_swap1_f64(hs);
             const double v = half ? other + hs : hs + other;
@@ -644,15 +740,13 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
 
     // ---- write the block back
     {
-        float* base = a.R + row0 * a.n + col0;
-        if (!padded || (a.n & 3) == 0) {
+        TE* base = Rm + row0 * a.n + col0;
+        if (!padded || a.n % VE == 0) {
 #pragma unroll
             for (int r = 0; r < TR; ++r)
 #pragma unroll
-                for (int c4 = 0; c4 < TC / 4; ++c4)
-                    if (!padded || (row0 + r < a.m && col0 + 4 * c4 < a.n))
-                        *(float4*)(base + (int64_t)r * a.n + 4 * c4) =
-                            make_float4(x[r][4 * c4], x[r][4 * c4 + 1], x[r][4 * c4 + 2], x[r][4 * c4 + 3]);
+                for (int c = 0; c < TC; c += VE)
+                    if (!padded || (row0 + r < a.m && col0 + c < a.n)) ResVec<TE>::put(base + (int64_t)r * a.n + c, &x[r][c]);
         } else {
 #pragma unroll
             for (int r = 0; r < TR; ++r)
@@ -680,9 +774,10 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
 // 8 x 8 with at most 8 values per thread, else the smallest grid with at most 32, else the grid that fits with
 // the smallest tile.  Rows that are no multiple of 16 bytes are loaded and written back element by element, once per
 // launch (1501x999, 16 terms: 2.4 ms a call; two launches per alternation on the unaligned rows took 8.7 ms).
-static bool resident_shape(int64_t m, int64_t n, int* p, int* tr, int* tc)
+static bool resident_shape(scd_dtype dt, int64_t m, int64_t n, int* p, int* tr, int* tc)
 {
     if (m < 1 || n < 4) return false;
+    const int most = dt == SCD_F32 ? 128 : 64;  // values a thread can hold
     static const int grids[3] = {4, 8, 16};
     static const int trs[3] = {2, 4, 8}, tcs[3] = {4, 8, 16};
     int best = -1, bp = 0, btr = 0, btc = 0;
@@ -693,7 +788,7 @@ static bool resident_shape(int64_t m, int64_t n, int* p, int* tr, int* tc)
                 if (!r && (int64_t)P * 32 * t >= m) r = t;
             for (int t : tcs)
                 if (!c && (int64_t)P * 16 * t >= n) c = t;
-            if (!r || !c) continue;
+            if (!r || !c || r * c > most) continue;
             if (P == 4 && (r > 4 || c > 8)) continue;  // (the 4 x 4 grid is built with the small tiles only)
             if (pass == 0 ? (P <= 8 && r * c <= 8) : (r * c <= 32)) {
                 *p = P, *tr = r, *tc = c;
@@ -710,13 +805,13 @@ static bool resident_shape(int64_t m, int64_t n, int* p, int* tr, int* tc)
 bool resident_supported(scd_dtype dt, int order, const int64_t* dims)
 {
     int p, tr, tc;
-    return dt == SCD_F32 && order == 2 && resident_shape(dims[0], dims[1], &p, &tr, &tc);
+    return order == 2 && resident_shape(dt, dims[0], dims[1], &p, &tr, &tc);
 }
 
-int resident_workgroups(const int64_t* dims)
+int resident_workgroups(scd_dtype dt, const int64_t* dims)
 {
     int p = 0, tr, tc;
-    return resident_shape(dims[0], dims[1], &p, &tr, &tc) ? p * p : 0;
+    return resident_shape(dt, dims[0], dims[1], &p, &tr, &tc) ? p * p : 0;
 }
 
 // Sleep units between publishing and the first read, per exchange, from the option's value (default 16).  A read
@@ -725,16 +820,21 @@ int resident_workgroups(const int64_t* dims)
 // Measured in us per alternation: grids of up to 8 x 8 at 10 units 2.87 (256^2) and 3.41 (1024^2), at 16 3.17 and
 // 3.70; 16 x 16 with slots of 256 columns at 18 / 14 units (rows / columns) 5.38 (4096^2), at 16 / 16 5.44, at
 // 12 / 8 5.84; with shorter slots at 16 / 8 4.55 (2048^2) and 4.95 (4096x1024), at 16 / 16 4.69 and 5.14.
-void resident_poll_delays(const int64_t* dims, int delay, int32_t* rows, int32_t* cols)
+// f64 has twice the words: up to 8 x 8 at 10 / 10 3.40 (256^2), 4.55 (600x400) and 4.78 (1024^2), at 18 / 14 3.66, 4.71
+// and 4.81; 16 x 16 at 22 / 18 6.78 (1501x999) and 6.93 (2048^2), at 18 / 14 7.03 and 7.24, at 26 / 22 6.95 and 7.09; with
+// column slots of 256 values at 26 / 22 7.68 (2048x4096), at 22 / 18 8.56.
+void resident_poll_delays(scd_dtype dt, const int64_t* dims, int delay, int32_t* rows, int32_t* cols)
 {
     int p = 16, tr = 8, tc = 16;
-    (void)resident_shape(dims[0], dims[1], &p, &tr, &tc);
-    const int u = p <= 8 ? delay - 6 : delay + 2, v = p <= 8 ? delay - 6 : (tc == 16 ? delay - 2 : delay - 8);
+    (void)resident_shape(dt, dims[0], dims[1], &p, &tr, &tc);
+    int u = delay - 6, v = delay - 6;
+    if (p > 8 && dt == SCD_F32) u = delay + 2, v = tc == 16 ? delay - 2 : delay - 8;
+    if (p > 8 && dt != SCD_F32) u = tc == 16 ? delay + 10 : delay + 6, v = tc == 16 ? delay + 6 : delay + 2;
     *rows = delay == 0 || u < 0 ? 0 : u;
     *cols = delay == 0 || v < 0 ? 0 : v;
 }
 
-template <int TR, int TC, int P, bool PAD>
+template <typename TE, int TR, int TC, int P, bool PAD>
 static hipError_t launch_resident_k(const ResidentArgs& a, hipStream_t st)
 {
     // All P x P workgroups must be resident at once.  One workgroup of 512 threads fits every compute
@@ -744,52 +844,60 @@ static hipError_t launch_resident_k(const ResidentArgs& a, hipStream_t st)
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, resident_kernel<TR, TC, P, PAD>, kResThreads, 0);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, resident_kernel<TE, TR, TC, P, PAD>, kResThreads, 0);
     if (e != hipSuccess) return e;
     if ((int64_t)per_cu * cus < P * P) return hipErrorCooperativeLaunchTooLarge;
-    hipLaunchKernelGGL((resident_kernel<TR, TC, P, PAD>), dim3(P * P), dim3(kResThreads), 0, st, a);
+    hipLaunchKernelGGL((resident_kernel<TE, TR, TC, P, PAD>), dim3(P * P), dim3(kResThreads), 0, st, a);
     return hipGetLastError();
 }
 
-template <int TR, int TC, int P>
+template <typename TE, int TR, int TC, int P>
 static hipError_t launch_resident_t(const ResidentArgs& a, hipStream_t st)
 {
     // does the grid of P x P blocks of 32 TR x 16 TC overhang the matrix?
     const bool padded = (int64_t)P * 32 * TR != a.m || (int64_t)P * 16 * TC != a.n;
-    return padded ? launch_resident_k<TR, TC, P, true>(a, st) : launch_resident_k<TR, TC, P, false>(a, st);
+    return padded ? launch_resident_k<TE, TR, TC, P, true>(a, st) : launch_resident_k<TE, TR, TC, P, false>(a, st);
 }
 
-template <int P>
+template <typename TE, int P>
 static hipError_t launch_resident_p(const ResidentArgs& a, int tr, int tc, hipStream_t st)
 {
     const int key = tr * 100 + tc;
     switch (key) {
-        case 204: return launch_resident_t<2, 4, P>(a, st);
-        case 208: return launch_resident_t<2, 8, P>(a, st);
-        case 404: return launch_resident_t<4, 4, P>(a, st);
-        case 408: return launch_resident_t<4, 8, P>(a, st);
+        case 204: return launch_resident_t<TE, 2, 4, P>(a, st);
+        case 208: return launch_resident_t<TE, 2, 8, P>(a, st);
+        case 404: return launch_resident_t<TE, 4, 4, P>(a, st);
+        case 408: return launch_resident_t<TE, 4, 8, P>(a, st);
         default: break;
     }
     if constexpr (P >= 8) {
         switch (key) {
-            case 216: return launch_resident_t<2, 16, P>(a, st);
-            case 416: return launch_resident_t<4, 16, P>(a, st);
-            case 804: return launch_resident_t<8, 4, P>(a, st);
-            case 808: return launch_resident_t<8, 8, P>(a, st);
-            case 816: return launch_resident_t<8, 16, P>(a, st);
+            case 216: return launch_resident_t<TE, 2, 16, P>(a, st);
+            case 416: return launch_resident_t<TE, 4, 16, P>(a, st);
+            case 804: return launch_resident_t<TE, 8, 4, P>(a, st);
+            case 808: return launch_resident_t<TE, 8, 8, P>(a, st);
             default: break;
+        }
+        if constexpr (sizeof(TE) == 4) {
+            if (key == 816) return launch_resident_t<TE, 8, 16, P>(a, st);
         }
     }
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_resident(const ResidentArgs& a, hipStream_t st)
+template <typename TE>
+static hipError_t launch_resident_e(const ResidentArgs& a, int p, int tr, int tc, hipStream_t st)
+{
+    if (p == 16) return launch_resident_p<TE, 16>(a, tr, tc, st);
+    if (p == 8) return launch_resident_p<TE, 8>(a, tr, tc, st);
+    return launch_resident_p<TE, 4>(a, tr, tc, st);
+}
+
+hipError_t launch_resident(const ResidentArgs& a, scd_dtype dt, hipStream_t st)
 {
     int p = 0, tr = 0, tc = 0;
-    if (!resident_shape(a.m, a.n, &p, &tr, &tc)) return hipErrorInvalidValue;
-    if (p == 16) return launch_resident_p<16>(a, tr, tc, st);
-    if (p == 8) return launch_resident_p<8>(a, tr, tc, st);
-    return launch_resident_p<4>(a, tr, tc, st);
+    if (!resident_shape(dt, a.m, a.n, &p, &tr, &tc)) return hipErrorInvalidValue;
+    return dt == SCD_F32 ? launch_resident_e<float>(a, p, tr, tc, st) : launch_resident_e<double>(a, p, tr, tc, st);
 }
 
 }  // namespace scd

@@ -64,6 +64,41 @@ def test_resident_matches_oracle_in_lockstep(scd, oracle, m, n):
     assert float((torch.from_numpy(A).cuda() - E.float() - R).abs().max()) <= 2e-6 * float(np.abs(A).max())
 
 
+# f64: half the values a thread holds and two words a value, so its own tiles (each of them once, the largest on every
+# grid) and its own limit, 4096x2048 or 2048x4096 values; odd row lengths end 16-byte reads of two values
+F64_SHAPES = [(1, 4), (7, 5), (64, 63), (128, 64), (256, 512), (600, 400), (1024, 1024), (1501, 999), (100, 2048), (1024, 2048),
+              (2048, 1024), (4096, 513), (1024, 4096), (2048, 2048), (4096, 2048), (4095, 2047), (2048, 4096), (1030, 4093)]
+
+
+@pytest.mark.parametrize("m,n", F64_SHAPES)
+def test_resident_f64_matches_oracle_in_lockstep(scd, oracle, m, n):
+    w, seed = min(6, m * n // 2), 23  # (a 1 x 4 matrix is exhausted after three terms)
+    A = gauss((m, n), m + n).astype(np.float64) * 1.5
+    with scd.ScdContext(torch.from_numpy(A).cuda(), w, seed, options=RESIDENT) as ctx:
+        assert ctx.engine()["engine"] == 1
+        ctx.run(w)
+        res = ctx.results()
+        R = ctx.remainder()
+    S, T = to_np_bits(res["signs"][0]), to_np_bits(res["signs"][1])
+    c, trace = res["c"].cpu().numpy(), res["trace"].cpu().numpy()
+    curve, _ = lockstep_check(oracle, A, seed, S, T, c, trace, res["iters"].cpu().numpy(), False)
+    # sums of up to 2^23 values in another order: 2^23 * 2^-53 relative at the very worst, about its root in practice
+    np.testing.assert_allclose(trace, curve, rtol=1e-9)
+    if m % 64:
+        assert np.all(S[:, -1] >> np.uint64(m % 64) == 0)
+    if n % 64:
+        assert np.all(T[:, -1] >> np.uint64(n % 64) == 0)
+    E = scd.scd_expand(res["signs"], res["c"], (m, n))
+    assert float((torch.from_numpy(A).cuda() - E - R).abs().max()) <= 2e-15 * w * float(np.abs(A).max())
+
+
+def test_resident_f64_limit(scd):
+    """One row or column past the registers: the next engine, as for every larger matrix."""
+    for m, n in [(4097, 2048), (2049, 2049), (2048, 4097)]:
+        with scd.ScdContext(torch.ones((m, n), dtype=torch.float64, device="cuda"), 1, 1) as ctx:
+            assert ctx.engine()["engine"] != 1
+
+
 @pytest.mark.parametrize("m,n", SHAPES[:2] + SHAPES[3:])
 def test_resident_and_stream_paths_agree(scd, m, n):
     A = torch.from_numpy(gauss((m, n), 5)).cuda()
