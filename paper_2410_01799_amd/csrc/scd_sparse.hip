@@ -43,8 +43,11 @@ constexpr int kSpHalfWords = 3 * 8 * kSpGrid;     // words of one parity: up to 
 // slowest member, and that moves with the shape, the number of workgroups and what else runs; an early read costs
 // everybody, because all members read the same lines.  With a fixed wait of 16 units for all: 4096x4096 f64 on 256
 // workgroups 10.0 us per alternation against 9.6, 4096x4096 f32 on 64 10.3 against 9.75, 200x200 f64 on 32 8.55
-// against 8.27.
-constexpr int kSpWaitShift = 4, kSpWaitUp = 12, kSpWaitDown = 1, kSpWaitMax = 80 << kSpWaitShift;
+// against 8.27.  The bound of 32 units is for many contexts at once: their traffic spreads the arrivals, and every wave
+// waiting for nine in ten of them makes all of them later.  Seven matrices of a decoder layer in flight: 22.65 s with 32,
+// 22.9 with a fixed wait, 23.1 with 16, 26.9 with 80; one context alone 9.53 us with 32, 9.51 with 16 (f64 4096x4096),
+// 14.55 and 14.99 (14336x4096 f32).
+constexpr int kSpWaitShift = 4, kSpWaitUp = 12, kSpWaitDown = 1, kSpWaitMax = 32 << kSpWaitShift;
 constexpr int kSpListCap = 32 * kSpThreads;       // flips handled per compaction round: one 32-bit word per thread
 constexpr size_t kSpMaxLds = 150 * 1024 + 64;     // most dynamic LDS a launch may ask for
 // Words a thread may have to gather: grid * (ceil(slice / 32) + 2) over the supported pairs, where
