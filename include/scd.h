@@ -148,7 +148,8 @@ int scd_set_remainder(scd_ctx* ctx, const void* R_in);
 /* ---- half steps of Algorithm 4 on caller data (lines 5 and 6-7) --------------------------------
  * Row signed sum: u = R t (m doubles, optional) and s = sgn(u) packed (ceil(m/64) words, optional).
  * Column signed sum: v = R^T s (n doubles, optional), t = sgn(v) packed (optional) and
- * c = sum_l |v_l| = <s, R t> (one double, optional; not normalised).  R is m x n of `dt`. */
+ * c = sum_l |v_l| = <s, R t> (one double, optional; not normalised).  R is m x n of `dt`.  The bitset read and the
+ * bitset written may share memory, so that one buffer serves the alternation on a square matrix. */
 int scd_row_signed_sum(const void* R, scd_dtype dt, int64_t m, int64_t n, const uint64_t* tbits,
                        void* stream, double* u, uint64_t* sbits);
 int scd_col_signed_sum(const void* R, scd_dtype dt, int64_t m, int64_t n, const uint64_t* sbits,

@@ -1170,8 +1170,32 @@ int scd_row_signed_sum(const void* R, scd_dtype dt, int64_t m, int64_t n, const 
 {
     if (!R || !tbits || !dtype_ok(dt) || m < 1 || n < 1) return SCD_EINVAL;
     hipStream_t st = (hipStream_t)stream;
-    HIP_TRY(launch_row_sums(R, dt, m, n, tbits, u, sbits, st));
-    HIP_TRY(hipStreamSynchronize(st));
+    // The pass writes the signs of its first rows while workgroups that come later still read tbits: where the two
+    // share memory (a caller that alternates in one buffer) the signs go to a block of their own and are copied last.
+    const size_t sbytes = (size_t)words_for(m) * 8, tbytes = (size_t)words_for(n) * 8;
+    const uintptr_t s0 = (uintptr_t)sbits, t0 = (uintptr_t)tbits;
+    const bool shared = sbits && s0 < t0 + tbytes && t0 < s0 + sbytes;
+    uint64_t* own = nullptr;
+    if (shared) {
+        hipError_t e = pool_malloc((void**)&own, sbytes, false);
+        if (e != hipSuccess) {
+            g_last_hip = (int)e;
+            (void)hipGetLastError();
+            return SCD_ENOMEM;
+        }
+    }
+    hipError_t e = launch_row_sums(R, dt, m, n, tbits, u, shared ? own : sbits, st);
+    if (e == hipSuccess && shared) e = hipMemcpyAsync(sbits, own, sbytes, hipMemcpyDeviceToDevice, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (shared) {
+        if (e != hipSuccess) settle(st);
+        pool_free(own, sbytes, false);
+    }
+    if (e != hipSuccess) {
+        g_last_hip = (int)e;
+        (void)hipGetLastError();
+        return SCD_EHIP;
+    }
     return SCD_OK;
 }
 

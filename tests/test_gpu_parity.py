@@ -6,6 +6,7 @@ Tolerances (north-star): bit-exact for bitsets, random streams and expansion; si
 where the reference value is within 1e-6 of a tie; c within 1e-5; Frobenius identity within 1e-6;
 error curve within 1e-3.
 """
+import ctypes as C
 import math
 
 import numpy as np
@@ -141,6 +142,32 @@ def test_half_steps(scd, oracle, m, n, dtype):
     assert_signs_match(to_np_bits(sb), oracle.pack(u_ref), u_ref, m, "s = sgn(R t)")
     assert_signs_match(to_np_bits(tb), oracle.pack(v_ref), v_ref, n, "t = sgn(R^T s)")
     assert float(c) == pytest.approx(np.abs(v_ref).sum(), rel=C_RTOL)
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("n,m", [(64, 64), (1024, 1024), (2500, 2500), (4096, 1000), (1000, 4096)])
+def test_half_steps_in_one_sign_buffer(scd, oracle, m, n, dtype):
+    # a caller that alternates in one buffer: the bitset written is the one that is read (or a part of it)
+    Rd = dev(gauss((m, n), m + n, dtype))
+    t = to_dev_bits(oracle.rng_signs(5, 0, 1, n))
+    L, st = scd.lib(), C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    dt = scd.F32 if dtype == np.float32 else scd.F64
+    u, s = scd.scd_row_signed_sum(Rd, t)
+    v, t2, _ = scd.scd_col_signed_sum(Rd, s)
+    mw, nw = (m + 63) // 64, (n + 63) // 64
+    for shift in (0, min(mw, nw) - 1):      # the same words, or one word in common
+        for want_u in (True, False):
+            buf = torch.zeros(mw + nw + shift, dtype=torch.int64, device="cuda")
+            buf[:nw] = t
+            uu = torch.zeros(m, dtype=torch.float64, device="cuda")
+            rc = L.scd_row_signed_sum(C.c_void_p(Rd.data_ptr()), dt, m, n, C.c_void_p(buf.data_ptr()), st,
+                                      C.c_void_p(uu.data_ptr()) if want_u else None, C.c_void_p(buf.data_ptr() + 8 * shift))
+            assert rc == 0 and torch.equal(buf[shift:shift + mw], s) and torch.equal(buf[:shift], t[:shift])
+            assert not want_u or torch.equal(uu, u)
+            buf[:mw] = s
+            rc = L.scd_col_signed_sum(C.c_void_p(Rd.data_ptr()), dt, m, n, C.c_void_p(buf.data_ptr()), st, None,
+                                      C.c_void_p(buf.data_ptr() + 8 * shift), None)
+            assert rc == 0 and torch.equal(buf[shift:shift + nw], t2)
 
 
 # ------------------------------------------------------------------ one term from the same remainder and start
