@@ -1091,20 +1091,31 @@ static bool rows_aligned(const void* p, scd_dtype dt, int64_t cols)
     return cols % (dt == SCD_F32 ? 4 : 2) == 0 && ((uintptr_t)p & 15u) == 0;
 }
 
+template <typename TE>
+static void row_sums_launch(const TE* R, int64_t m, int64_t n, const uint64_t* tbits, double* u, uint64_t* sbits, hipStream_t st)
+{
+    const dim3 grid((unsigned)((m + 63) / 64 * 8));  // a workgroup per byte of sign bits
+    if (rows_aligned(R, sizeof(TE) == 4 ? SCD_F32 : SCD_F64, n))
+        hipLaunchKernelGGL((row_sums_kernel<TE, true>), grid, dim3(kBlock), 0, st, R, m, n, tbits, u, (uint8_t*)sbits);
+    else
+        hipLaunchKernelGGL((row_sums_kernel<TE, false>), grid, dim3(kBlock), 0, st, R, m, n, tbits, u, (uint8_t*)sbits);
+}
+
 hipError_t launch_row_sums(const void* R, scd_dtype dt, int64_t m, int64_t n, const uint64_t* tbits, double* u, uint64_t* sbits,
                            hipStream_t st)
 {
-    const dim3 grid((unsigned)((m + 63) / 64 * 8));  // a workgroup per byte of sign bits
-    uint8_t* sb = (uint8_t*)sbits;
-    const bool vec = rows_aligned(R, dt, n);
-    if (dt == SCD_F32) {
-        if (vec) hipLaunchKernelGGL((row_sums_kernel<float, true>), grid, dim3(kBlock), 0, st, (const float*)R, m, n, tbits, u, sb);
-        else hipLaunchKernelGGL((row_sums_kernel<float, false>), grid, dim3(kBlock), 0, st, (const float*)R, m, n, tbits, u, sb);
-    } else {
-        if (vec) hipLaunchKernelGGL((row_sums_kernel<double, true>), grid, dim3(kBlock), 0, st, (const double*)R, m, n, tbits, u, sb);
-        else hipLaunchKernelGGL((row_sums_kernel<double, false>), grid, dim3(kBlock), 0, st, (const double*)R, m, n, tbits, u, sb);
+    // 2^23 rows per launch: with a workgroup per eight rows, 2^27 of them would pass the 2^32 threads a launch can have
+    constexpr int64_t slab = 1 << 23;
+    for (int64_t r = 0; r < m; r += slab) {
+        const int64_t rows = m - r < slab ? m - r : slab;
+        double* ur = u ? u + r : nullptr;
+        uint64_t* sr = sbits ? sbits + r / 64 : nullptr;
+        if (dt == SCD_F32) row_sums_launch((const float*)R + r * n, rows, n, tbits, ur, sr, st);
+        else row_sums_launch((const double*)R + r * n, rows, n, tbits, ur, sr, st);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 hipError_t launch_col_partials(const void* R, scd_dtype dt, int64_t m, int64_t n, int rows_per_wg, int grid, const uint64_t* rowbits,

@@ -144,6 +144,20 @@ def test_half_steps(scd, oracle, m, n, dtype):
     assert float(c) == pytest.approx(np.abs(v_ref).sum(), rel=C_RTOL)
 
 
+@pytest.mark.parametrize("m", [(1 << 23) - 3, (1 << 23) + 5, (1 << 27) + 70])
+def test_row_half_step_of_very_many_rows(scd, m):
+    # 2^23 rows go into one launch; at 2^27 rows a single one would pass the limit on threads
+    i = torch.arange(m, device="cuda", dtype=torch.int32)
+    R = ((i * 7919) % 1009 - 504).to(torch.float32).reshape(m, 1)
+    t = torch.ones(1, dtype=torch.int64, device="cuda")        # the one column counts negative
+    u, s = scd.scd_row_signed_sum(R, t)
+    assert bool((u == -R[:, 0].double()).all())
+    neg = torch.zeros((m + 63) // 64 * 64, dtype=torch.bool, device="cuda")
+    neg[:m] = R[:, 0] > 0
+    got = ((s.view(torch.uint8).unsqueeze(1) >> torch.arange(8, device="cuda", dtype=torch.uint8)) & 1).reshape(-1).bool()
+    assert torch.equal(got, neg)
+
+
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
 @pytest.mark.parametrize("n,m", [(64, 64), (1024, 1024), (2500, 2500), (4096, 1000), (1000, 4096)])
 def test_half_steps_in_one_sign_buffer(scd, oracle, m, n, dtype):
