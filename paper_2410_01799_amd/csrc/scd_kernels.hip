@@ -341,8 +341,12 @@ __global__ void __launch_bounds__(kBlock)
 }
 
 // Column step: partials[g][l] = sum over the rows of group g (rows_per_wg of them, in order) of the entries with the
-// signs `rowbits`.  A thread takes 16-byte chunks of the columns, four rows in flight.
-template <typename TE, bool VEC>
+// signs `rowbits`.  A thread takes 16-byte chunks of the columns (VEC) or single ones, RB rows in flight.  Tall matrices
+// with few columns leave most of a workgroup's threads idle and are bound by the trips of the others: eight rows a trip
+// below 1024 columns from eight rows a group on (14336x4096 73 with four, 75 with eight), and no chunks below 128 columns.  Us a call with four rows and chunks throughout, and now:
+// 1000000x4 f32 158 and 94, 200000x100 104 and 60, 100000x200 75 and 55, 1000000x2 f64 139 and 97; 16 rows in flight
+// lose from 512 columns on (50000x512 95, eight rows 57, four 61).
+template <typename TE, bool VEC, int RB>
 __global__ void __launch_bounds__(kBlock)
     col_partials_kernel(const TE* __restrict__ X, int64_t rows, int64_t cols, int rows_per_wg, const uint64_t* __restrict__ rowbits,
                         TE* __restrict__ partials)
@@ -356,11 +360,13 @@ __global__ void __launch_bounds__(kBlock)
         TE acc[VE];
 #pragma unroll
         for (int e = 0; e < VE; ++e) acc[e] = 0;
-        for (int rb = 0; rb < nr; rb += 4) {
-            TE x[4][VE];
+        for (int rb = 0; rb < nr; rb += RB) {
+            const int64_t g = r0 + rb;
+            const int left = nr - rb;
+            TE x[RB][VE];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const TE* p = X + (r0 + (rb + i < nr ? rb + i : rb)) * cols + ch * VE;
+            for (int i = 0; i < RB; ++i) {
+                const TE* p = X + (g + (i < left ? i : 0)) * cols + ch * VE;
                 if constexpr (VEC) {
                     const V v = *(const V*)p;
                     x[i][0] = v.x;
@@ -370,10 +376,17 @@ __global__ void __launch_bounds__(kBlock)
                     x[i][0] = p[0];
                 }
             }
+            // the signs of a long batch: bits of one word, or of two
+            uint64_t word = 0;
+            if constexpr (RB > 4) {
+                const int sh = (int)(g & 63);
+                word = rowbits[g >> 6] >> sh;
+                if (sh + RB > 64) word |= rowbits[(g + (left < RB ? left : RB) - 1) >> 6] << (64 - sh);
+            }
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if (rb + i >= nr) break;
-                const uint32_t neg = bit_at(rowbits, r0 + rb + i);
+            for (int i = 0; i < RB; ++i) {
+                if (i >= left) break;
+                const uint32_t neg = RB > 4 ? (uint32_t)(word >> i) & 1u : bit_at(rowbits, g + i);
 #pragma unroll
                 for (int e = 0; e < VE; ++e) acc[e] += flip(x[i][e], neg);
             }
@@ -1118,24 +1131,26 @@ hipError_t launch_row_sums(const void* R, scd_dtype dt, int64_t m, int64_t n, co
     return hipSuccess;
 }
 
+template <typename TE, bool VEC>
+static void col_partials_launch(const TE* R, int64_t m, int64_t n, int rows_per_wg, int grid, const uint64_t* rowbits, TE* partials,
+                                hipStream_t st)
+{
+    if (rows_per_wg >= 8 && n < 1024)
+        hipLaunchKernelGGL((col_partials_kernel<TE, VEC, 8>), dim3(grid), dim3(kBlock), 0, st, R, m, n, rows_per_wg, rowbits, partials);
+    else
+        hipLaunchKernelGGL((col_partials_kernel<TE, VEC, 4>), dim3(grid), dim3(kBlock), 0, st, R, m, n, rows_per_wg, rowbits, partials);
+}
+
 hipError_t launch_col_partials(const void* R, scd_dtype dt, int64_t m, int64_t n, int rows_per_wg, int grid, const uint64_t* rowbits,
                                void* partials, hipStream_t st)
 {
-    const bool vec = rows_aligned(R, dt, n) && ((uintptr_t)partials & 15u) == 0;
+    const bool vec = n >= 128 && rows_aligned(R, dt, n) && ((uintptr_t)partials & 15u) == 0;
     if (dt == SCD_F32) {
-        if (vec)
-            hipLaunchKernelGGL((col_partials_kernel<float, true>), dim3(grid), dim3(kBlock), 0, st, (const float*)R, m, n, rows_per_wg,
-                               rowbits, (float*)partials);
-        else
-            hipLaunchKernelGGL((col_partials_kernel<float, false>), dim3(grid), dim3(kBlock), 0, st, (const float*)R, m, n, rows_per_wg,
-                               rowbits, (float*)partials);
+        if (vec) col_partials_launch<float, true>((const float*)R, m, n, rows_per_wg, grid, rowbits, (float*)partials, st);
+        else col_partials_launch<float, false>((const float*)R, m, n, rows_per_wg, grid, rowbits, (float*)partials, st);
     } else {
-        if (vec)
-            hipLaunchKernelGGL((col_partials_kernel<double, true>), dim3(grid), dim3(kBlock), 0, st, (const double*)R, m, n, rows_per_wg,
-                               rowbits, (double*)partials);
-        else
-            hipLaunchKernelGGL((col_partials_kernel<double, false>), dim3(grid), dim3(kBlock), 0, st, (const double*)R, m, n, rows_per_wg,
-                               rowbits, (double*)partials);
+        if (vec) col_partials_launch<double, true>((const double*)R, m, n, rows_per_wg, grid, rowbits, (double*)partials, st);
+        else col_partials_launch<double, false>((const double*)R, m, n, rows_per_wg, grid, rowbits, (double*)partials, st);
     }
     return hipGetLastError();
 }

@@ -144,6 +144,21 @@ def test_half_steps(scd, oracle, m, n, dtype):
     assert float(c) == pytest.approx(np.abs(v_ref).sum(), rel=C_RTOL)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("m", [7168, 7169, 9001, 66001])
+@pytest.mark.parametrize("n", [1, 3, 4, 124, 128, 131, 1020, 1023, 1024])
+def test_column_half_step_of_tall_matrices(scd, m, n, dtype):
+    # seven and eight rows a group, groups whose signs straddle two words, a last group that is cut short, with and
+    # without 16-byte chunks.  Small integers: every sum is exact, whatever its order.
+    g = torch.Generator(device="cuda").manual_seed(m + n)
+    R = torch.randint(-50, 51, (m, n), generator=g, device="cuda").to(dtype)
+    s = scd.scd_rng_signs(9, 1, 0, m)
+    sd = scd.scd_unpack(s, m, torch.float64)
+    ref = (R.double() * sd[:, None]).sum(0)
+    v, t, c = scd.scd_col_signed_sum(R, s)
+    assert torch.equal(v, ref) and torch.equal(t, scd.scd_pack(ref)) and float(c) == float(ref.abs().sum())
+
+
 @pytest.mark.parametrize("m", [(1 << 23) - 3, (1 << 23) + 5, (1 << 27) + 70])
 def test_row_half_step_of_very_many_rows(scd, m):
     # 2^23 rows go into one launch; at 2^27 rows a single one would pass the limit on threads
