@@ -201,9 +201,9 @@ __device__ __forceinline__ double uniform_f64(double v)
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// Tagged words per published value: the value itself (f32), or its two halves, `apart` words from each other (f64).
-template <typename TE>
-constexpr int kResWords = (int)(sizeof(TE) / 4);
+// Tagged words per published sum: the value itself (f32), or its two halves, `apart` words from each other (f64).
+template <typename TX>
+constexpr int kResWords = (int)(sizeof(TX) / 4);
 
 __device__ __forceinline__ void res_publish(uint64_t* p, int apart, float v, uint32_t seq)
 {
@@ -231,12 +231,12 @@ __device__ __forceinline__ void res_publish_f64(uint64_t* p, double v, uint32_t 
 // exchange, all are read again (re-reads are rare once the first read is delayed a little).  `base` is the same
 // for the whole workgroup and `off` (bytes) the same in every exchange: the loads take a scalar base and a 32-bit
 // lane offset, so that no 64-bit lane address is worked out between the wait and the first load.
-template <typename TE, int H, int NX>
+template <typename TX, int H, int NX>
 __device__ __forceinline__ bool res_gather(const char* base, uint32_t off, uint32_t stride, uint32_t apart, const char* xbase, uint32_t xoff,
                                            uint32_t seq, int max_spin, double& sum, double& x0, double& x1, int& spin)
 {
     static_assert(NX == 0 || NX == 2 || NX == 4, "none, one or two piggybacked doubles");
-    constexpr int W = kResWords<TE>, N = W * H;
+    constexpr int W = kResWords<TX>, N = W * H;
     uint64_t w[N + 4];
     w[N + 2] = 0;
     w[N + 3] = 0;
@@ -404,10 +404,11 @@ __device__ __forceinline__ void sign_factors(const uint8_t* p, TE (&f)[N])
 // PAD: the grid overhangs the matrix (a template parameter: the 128 row/column tests of a thread's tile are
 // invariants of the whole launch, and a kernel that has to keep them takes twice the instructions and runs out of
 // scalar registers even when no test ever fails).
-template <typename TE, int TR, int TC, int P, bool PAD>
+// TA: type of the sums inside a workgroup, TX: of the sums that it publishes (see resident_sums).
+template <typename TE, typename TA, typename TX, int TR, int TC, int P, bool PAD>
 __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
 {
-    constexpr int W = kResWords<TE>, VE = ResVec<TE>::N;
+    constexpr int W = kResWords<TX>, VE = ResVec<TE>::N;
     TE* const Rm = (TE*)a.R;
     constexpr int H = P / 2;  // members per half of an exchange group
     static_assert(P == 4 || P == 8 || P == 16, "grid side");
@@ -421,7 +422,7 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
     const int wg = blockIdx.x;
 
     constexpr int NWV = kResThreads / 64;
-    __shared__ __align__(16) TE lds_q[NWV][BN];
+    __shared__ __align__(16) TA lds_q[NWV][BN];
     __shared__ __align__(16) uint8_t lds_s[2][BM];  // signs as the top bytes of +-1.0
     __shared__ __align__(16) uint8_t lds_t[BN];
     __shared__ double lds_red[NWV];
@@ -453,6 +454,16 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
         }
     }
     if (tid == 0) lds_fail = 0;
+    // Values that are widened for the sums are widened anew in each phase: kept from one to the next they would take twice
+    // the registers again and go through scratch (4095x4093 f32, 8 terms: 23.3 ms instead of 5.9).
+    auto keep_narrow = [&]() {
+        if constexpr (sizeof(TA) != sizeof(TE)) {
+#pragma unroll
+            for (int r = 0; r < TR; ++r)
+#pragma unroll
+                for (int c = 0; c < TC; ++c) asm volatile("" : "+v"(x[r][c]));
+        }
+    };
 
     int64_t k = a.k_start;
     int alternations = 0, updates = 0;
@@ -489,40 +500,41 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
         // The signs enter as +-1.0 multipliers of a fused multiply-add: x * (+-1) is exact, so each step
         // rounds exactly like the sign-flip-and-add of Section 3.4, in one instruction instead of two
         // (this engine is bound by vector instructions and latency, not by memory).
-        TE prow;  // the row sum this lane publishes: row tc of the thread row's TR rows (lanes tc < TR)
+        keep_narrow();
+        TA prow;  // the row sum this lane publishes: row tc of the thread row's TR rows (lanes tc < TR)
         {
-            TE tf[TC];
+            TA tf[TC];
             sign_factors(lds_t + tc * TC, tf);
-            TE p[TR];
+            TA p[TR];
 #pragma unroll
             for (int r = 0; r < TR; ++r) {
-                TE s = 0;
+                TA s = 0;
 #pragma unroll
-                for (int c = 0; c < TC; ++c) s = res_fma(x[r][c], tf[c], s);
+                for (int c = 0; c < TC; ++c) s = res_fma((TA)x[r][c], tf[c], s);
                 p[r] = s;
             }
             // Sum over the 16 lanes that share these rows, lane distances 1, 2, 4, 8.  At distances 1 and 2 a lane
             // keeps only the rows whose low index bits are its own (it hands the others to its neighbour), which
             // halves the registers each time: lane tc ends with rows tc mod 4 and 4 + tc mod 4.
             const bool odd1 = (lane & 1) != 0, odd2 = (lane & 2) != 0;
-            TE a1[TR / 2];
+            TA a1[TR / 2];
 #pragma unroll
             for (int i = 0; i < TR / 2; ++i) {
-                const TE keep = odd1 ? p[2 * i + 1] : p[2 * i], send = odd1 ? p[2 * i] : p[2 * i + 1];
+                const TA keep = odd1 ? p[2 * i + 1] : p[2 * i], send = odd1 ? p[2 * i] : p[2 * i + 1];
                 a1[i] = keep + dpp_val<0xB1>(send);  // lane ^ 1
             }
             if constexpr (TR == 2) {
-                TE s = a1[0];
+                TA s = a1[0];
                 s += dpp_val<0x4E>(s);   // lane ^ 2
                 s += dpp_val<0x124>(s);  // row rotate 4
                 s += dpp_val<0x128>(s);  // row rotate 8
                 prow = s;
             } else {
-                TE a2[TR / 4];
+                TA a2[TR / 4];
 #pragma unroll
                 for (int i = 0; i < TR / 4; ++i) {
-                    const TE keep = odd2 ? a1[2 * i + 1] : a1[2 * i], send = odd2 ? a1[2 * i] : a1[2 * i + 1];
-                    TE s = keep + dpp_val<0x4E>(send);  // lane ^ 2
+                    const TA keep = odd2 ? a1[2 * i + 1] : a1[2 * i], send = odd2 ? a1[2 * i] : a1[2 * i + 1];
+                    TA s = keep + dpp_val<0x4E>(send);  // lane ^ 2
                     s += dpp_val<0x124>(s);             // row rotate 4
                     s += dpp_val<0x128>(s);             // row rotate 8
                     a2[i] = s;
@@ -535,7 +547,7 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
         ++alternations;
         {
             uint64_t* mine = res_slot(a, 0, seq_u, wg);
-            if (tc < TR) res_publish(mine + tr * TR + tc, BM, prow, seq_u);
+            if (tc < TR) res_publish(mine + tr * TR + tc, BM, (TX)prow, seq_u);
             if (tid == 0) {
                 res_publish_f64(mine + W * BM, cpart, seq_u);
                 if (norm_stage == 1) res_publish_f64(mine + W * BM + 2, fsq_block, seq_u);  // (only the exchange after an update)
@@ -552,14 +564,14 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
             bool ok;
             if (wv == NWV - 1) {
                 const uint32_t xoff = (uint32_t)((lane & (P - 1)) * kResSlotWords + W * BM) * 8u;
-                if (norm_stage == 1) ok = res_gather<TE, H, 4>(base, off_u, kResSlotWords * 8, BM * 8, base, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
-                else ok = res_gather<TE, H, 2>(base, off_u, kResSlotWords * 8, BM * 8, base, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
+                if (norm_stage == 1) ok = res_gather<TX, H, 4>(base, off_u, kResSlotWords * 8, BM * 8, base, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
+                else ok = res_gather<TX, H, 2>(base, off_u, kResSlotWords * 8, BM * 8, base, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
                 if (lane < P) {
                     lds_x[0][lane] = x0;
                     if (norm_stage == 1) lds_x[1][lane] = x1;
                 }
             } else {
-                ok = res_gather<TE, H, 0>(base, off_u, kResSlotWords * 8, BM * 8, base, 0, seq_u, a.max_spin, hs, x0, x1, spin);
+                ok = res_gather<TX, H, 0>(base, off_u, kResSlotWords * 8, BM * 8, base, 0, seq_u, a.max_spin, hs, x0, x1, spin);
             }
             const double other = dpp_swap1_f64(hs);
             const double u = half ? other + hs : hs + other;
@@ -576,16 +588,17 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
         // ================= column phase: v = R^T s (Algorithm 4 line 6), c = sum |v| (line 7).  Its sums are formed
         // before the stop test below is looked at: the test's chain of additions hides behind them, and a term that
         // ends here has formed one half step too many (once per term).
-        TE qv[TC / 4];
+        keep_narrow();
+        TA qv[TC / 4];
         {
-            TE sf[TR];
+            TA sf[TR];
             sign_factors(&lds_s[cur][tr * TR], sf);
-            TE q[TC];
+            TA q[TC];
 #pragma unroll
             for (int c = 0; c < TC; ++c) {
-                TE s = 0;
+                TA s = 0;
 #pragma unroll
-                for (int r = 0; r < TR; ++r) s = res_fma(x[r][c], sf[r], s);
+                for (int r = 0; r < TR; ++r) s = res_fma((TA)x[r][c], sf[r], s);
                 q[c] = s;
             }
             // the four thread rows of this wave hold the same columns 16 lanes apart: lane row i ends with the sums
@@ -664,10 +677,11 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
         }
         {
             // lane (i, tc) holds TC/4 neighbouring columns
-            TE* dst = &lds_q[wv][tc * TC + (lane >> 4) * (TC / 4)];
-            if constexpr (TC / 4 >= VE) {
+            constexpr int VA = ResVec<TA>::N;
+            TA* dst = &lds_q[wv][tc * TC + (lane >> 4) * (TC / 4)];
+            if constexpr (TC / 4 >= VA) {
 #pragma unroll
-                for (int g = 0; g < TC / 4; g += VE) ResVec<TE>::put(dst + g, qv + g);
+                for (int g = 0; g < TC / 4; g += VA) ResVec<TA>::put(dst + g, qv + g);
             } else {
 #pragma unroll
                 for (int g = 0; g < TC / 4; ++g) dst[g] = qv[g];
@@ -680,15 +694,15 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
             if (tid < BN) {
                 // (all loads in flight together, then the adds in wave order: the empty asm keeps the compiler from
                 // loading two, waiting, adding two)
-                TE w[NWV];
+                TA w[NWV];
 #pragma unroll
                 for (int q = 0; q < NWV; ++q) w[q] = lds_q[q][tid];
                 static_assert(NWV == 8, "operands of the asm");
                 asm volatile("" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(w[4]), "+v"(w[5]), "+v"(w[6]), "+v"(w[7]));
-                TE s = 0;
+                TA s = 0;
 #pragma unroll
                 for (int q = 0; q < NWV; ++q) s += w[q];
-                res_publish(mine + tid, BN, s, seq_v);
+                res_publish(mine + tid, BN, (TX)s, seq_v);
             }
             if (norm_stage == 2 && tid == kResThreads - 1) res_publish_f64(mine + W * BN, frow, seq_v);
         }
@@ -701,11 +715,11 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
             bool ok;
             if (norm_stage == 2 && wv == NWV - 1) {
                 // the block-row sums of squares travel on this exchange once per term
-                ok = res_gather<TE, H, 2>(base, off_v, P * kResSlotWords * 8, BN * 8, base,
+                ok = res_gather<TX, H, 2>(base, off_v, P * kResSlotWords * 8, BN * 8, base,
                                           (uint32_t)((lane & (P - 1)) * P * kResSlotWords + W * BN) * 8u, seq_v, a.max_spin, hs, x0, x1, spin);
                 if (lane < P) lds_x[1][lane] = x0;
             } else {
-                ok = res_gather<TE, H, 0>(base, off_v, P * kResSlotWords * 8, BN * 8, base, 0, seq_v, a.max_spin, hs, x0, x1, spin);
+                ok = res_gather<TX, H, 0>(base, off_v, P * kResSlotWords * 8, BN * 8, base, 0, seq_v, a.max_spin, hs, x0, x1, spin);
             }
             const double other = dpp_swap1_f64(hs);
             const double v = half ? other + hs : hs + other;
@@ -814,6 +828,20 @@ int resident_workgroups(scd_dtype dt, const int64_t* dims)
     return resident_shape(dt, dims[0], dims[1], &p, &tr, &tc) ? p * p : 0;
 }
 
+// Types of the sums.  f64 matrices: f64 throughout.  f32 matrices whose rows are 16-byte steps: f32 inside a workgroup.
+// The other f32 matrices come here from the launch stream, which adds across lanes, waves and workgroups in f64 after f32
+// sums of ceil(n / 64) entries a lane (rows) and ceil(m / 256) rows a workgroup (columns): here f64 inside a workgroup, and
+// f32 words where one rounding a workgroup is no more than those f32 sums cost, that is from two of them on each side
+// (emulated, rms error of the row and column sums against f64, launch stream / here: 257x255 4.5e-8, 3.0e-8 / 2.6e-8,
+// 2.7e-8; 1501x999 7.3e-8, 5.1e-8 / 2.4e-8, 2.5e-8; 4095x4093 1.5e-7, 7.8e-8 / 2.6e-8, 2.5e-8; with f32 sums inside the
+// workgroup too the column sums of 1501x999 are off by 7.9e-8).  Smaller ones exchange f64.
+enum class ResSums { plain, wide_inside, wide };
+static ResSums resident_sums(scd_dtype dt, int64_t m, int64_t n)
+{
+    if (dt == SCD_F32 && n % ResVec<float>::N == 0) return ResSums::plain;
+    return dt == SCD_F32 && m > 256 && n > 128 ? ResSums::wide_inside : ResSums::wide;
+}
+
 // Sleep units between publishing and the first read, per exchange, from the option's value (default 16).  A read
 // that comes before the last partner's words costs another trip to memory (0.4 us and its traffic), one that comes
 // late costs what it waits, so the optimum is just behind the arrival, which moves with the words of an exchange.
@@ -822,19 +850,23 @@ int resident_workgroups(scd_dtype dt, const int64_t* dims)
 // 12 / 8 5.84; with shorter slots at 16 / 8 4.55 (2048^2) and 4.95 (4096x1024), at 16 / 16 4.69 and 5.14.
 // f64 has twice the words: up to 8 x 8 at 10 / 10 3.40 (256^2), 4.55 (600x400) and 4.78 (1024^2), at 18 / 14 3.66, 4.71
 // and 4.81; 16 x 16 at 22 / 18 6.78 (1501x999) and 6.93 (2048^2), at 18 / 14 7.03 and 7.24, at 26 / 22 6.95 and 7.09; with
-// column slots of 256 values at 26 / 22 7.68 (2048x4096), at 22 / 18 8.56.
+// column slots of 256 values at 26 / 22 7.68 (2048x4096), at 22 / 18 8.56.  f64 sums inside a workgroup make the slots of
+// tall blocks later: three units more, 5.50 instead of 5.99 (3000x1999) and 6.77 instead of 7.40 (4095x4093).
 void resident_poll_delays(scd_dtype dt, const int64_t* dims, int delay, int32_t* rows, int32_t* cols)
 {
     int p = 16, tr = 8, tc = 16;
     (void)resident_shape(dt, dims[0], dims[1], &p, &tr, &tc);
     int u = delay - 6, v = delay - 6;
-    if (p > 8 && dt == SCD_F32) u = delay + 2, v = tc == 16 ? delay - 2 : delay - 8;
-    if (p > 8 && dt != SCD_F32) u = tc == 16 ? delay + 10 : delay + 6, v = tc == 16 ? delay + 6 : delay + 2;
+    const ResSums sums = resident_sums(dt, dims[0], dims[1]);
+    const bool wide = sums == ResSums::wide;  // twice the words
+    if (sums == ResSums::wide_inside && p > 8 && tr > 2) delay = delay ? delay + 3 : 0;
+    if (p > 8 && !wide) u = delay + 2, v = tc == 16 ? delay - 2 : delay - 8;
+    if (p > 8 && wide) u = tc == 16 ? delay + 10 : delay + 6, v = tc == 16 ? delay + 6 : delay + 2;
     *rows = delay == 0 || u < 0 ? 0 : u;
     *cols = delay == 0 || v < 0 ? 0 : v;
 }
 
-template <typename TE, int TR, int TC, int P, bool PAD>
+template <typename TE, typename TA, typename TX, int TR, int TC, int P, bool PAD>
 static hipError_t launch_resident_k(const ResidentArgs& a, hipStream_t st)
 {
     // All P x P workgroups must be resident at once.  One workgroup of 512 threads fits every compute
@@ -844,10 +876,10 @@ static hipError_t launch_resident_k(const ResidentArgs& a, hipStream_t st)
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, resident_kernel<TE, TR, TC, P, PAD>, kResThreads, 0);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, resident_kernel<TE, TA, TX, TR, TC, P, PAD>, kResThreads, 0);
     if (e != hipSuccess) return e;
     if ((int64_t)per_cu * cus < P * P) return hipErrorCooperativeLaunchTooLarge;
-    hipLaunchKernelGGL((resident_kernel<TE, TR, TC, P, PAD>), dim3(P * P), dim3(kResThreads), 0, st, a);
+    hipLaunchKernelGGL((resident_kernel<TE, TA, TX, TR, TC, P, PAD>), dim3(P * P), dim3(kResThreads), 0, st, a);
     return hipGetLastError();
 }
 
@@ -856,7 +888,13 @@ static hipError_t launch_resident_t(const ResidentArgs& a, hipStream_t st)
 {
     // does the grid of P x P blocks of 32 TR x 16 TC overhang the matrix?
     const bool padded = (int64_t)P * 32 * TR != a.m || (int64_t)P * 16 * TC != a.n;
-    return padded ? launch_resident_k<TE, TR, TC, P, true>(a, st) : launch_resident_k<TE, TR, TC, P, false>(a, st);
+    if constexpr (sizeof(TE) == 4) {
+        // (rows that are no 16-byte steps never fit the grid exactly)
+        const ResSums sums = resident_sums(SCD_F32, a.m, a.n);
+        if (sums == ResSums::wide_inside) return launch_resident_k<TE, double, TE, TR, TC, P, true>(a, st);
+        if (sums == ResSums::wide) return launch_resident_k<TE, double, double, TR, TC, P, true>(a, st);
+    }
+    return padded ? launch_resident_k<TE, TE, TE, TR, TC, P, true>(a, st) : launch_resident_k<TE, TE, TE, TR, TC, P, false>(a, st);
 }
 
 template <typename TE, int P>

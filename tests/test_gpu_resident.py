@@ -64,6 +64,43 @@ def test_resident_matches_oracle_in_lockstep(scd, oracle, m, n):
     assert float((torch.from_numpy(A).cuda() - E.float() - R).abs().max()) <= 2e-6 * float(np.abs(A).max())
 
 
+def cancelling(m, n, seed):
+    """Small integers, and in rows four by four two entries of 2^27 that cancel when summed with signs +1: a sum that rounds
+    to 24 bits before they meet loses the small ones, which decide the sign.  The two lie in one block of 64 columns (the
+    smallest a workgroup owns) and 16 or more apart, in different threads; no other rows have large entries in these
+    columns."""
+    rs = np.random.Generator(np.random.PCG64(seed))
+    A = rs.integers(-3, 4, (m, n)).astype(np.float32)
+    first = [c for c in range(n) if c % 64 < 16 and c + 16 < n]
+    for g in range(min((m + 3) // 4, len(first))):
+        r = slice(4 * g, min(4 * g + 4, m))
+        A[r, first[g]] = 2.0 ** 27
+        A[r, first[g] + 16] = -(2.0 ** 27)
+    return A
+
+
+@pytest.mark.parametrize("m,n", [(130, 21), (64, 63), (65, 257), (256, 129), (257, 127), (257, 129), (513, 129), (333, 1025), (1501, 999),
+                                 (3000, 1999), (4095, 4093)])
+def test_resident_sums_of_rows_without_16_byte_steps(scd, oracle, m, n):
+    # f64 inside a workgroup; the words exchanged are f64 up to 256 rows or 128 columns, beyond f32, which rounds a sum of
+    # large entries that do not cancel (in the columns; c then holds to one such rounding, its signs are exact)
+    t0 = oracle.rng_signs(3, 0, 1, n)
+    td = 1.0 - 2.0 * np.unpackbits(t0.view(np.uint8), bitorder="little")[:n].astype(np.float32)
+    A = np.ascontiguousarray(cancelling(m, n, m + n) * td)     # (cancels under the start of the run's first term)
+    ref = oracle.greedy_signed_cut(A.astype(np.float64), t0)
+    with scd.ScdContext(torch.from_numpy(A).cuda(), 1, 3, options=RESIDENT) as ctx:
+        assert ctx.engine()["engine"] == 1
+        ctx.run(1)
+        res = ctx.results()
+    assert np.array_equal(to_np_bits(res["signs"][0])[0], ref["s"])
+    assert np.array_equal(to_np_bits(res["signs"][1])[0], ref["t"])
+    assert int(res["iters"][0]) == ref["iters"]
+    if m <= 256 or n <= 128:
+        assert float(res["c"][0]) == np.float32(ref["c"] / (m * n))
+    else:
+        assert float(res["c"][0]) == pytest.approx(ref["c"] / (m * n), rel=2.0 ** -23)
+
+
 # f64: half the values a thread holds and two words a value, so its own tiles (each of them once, the largest on every
 # grid) and its own limit, 4096x2048 or 2048x4096 values; odd row lengths end 16-byte reads of two values
 F64_SHAPES = [(1, 4), (7, 5), (64, 63), (128, 64), (256, 512), (600, 400), (1024, 1024), (1501, 999), (100, 2048), (1024, 2048),
