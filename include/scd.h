@@ -228,8 +228,9 @@ int scd_decompose_scalars(const void* A, scd_dtype dt, int order, const int64_t*
  * integers below 2^30: at most max|x| 2^-30 per entry and max|z| 2^-30 per term, exact integer sums
  * afterwards), the rest in f64.  Non-finite entries of x give NaN.  S, T: device, term-major bitsets as scd_decompose writes them (w * ceil(m/64) and
  * w * ceil(n/64) words, padding bits 0); c, x, y: device, dtype dt; x and y must not overlap.
- * nvec >= 1 vectors are taken one after the other: x is nvec rows of the input length, y nvec rows of the
- * output length.  workspace: device, at least scd_apply_workspace_bytes(m, n, w) bytes, 8-byte aligned,
+ * nvec >= 1 vectors: x is nvec rows of the input length, y nvec rows of the output length.  SCD_F32: up to four
+ * vectors share a pass over the bits; each gets the bits of y that it gets alone, whatever the number of vectors
+ * and the size of the workspace (a larger one, up to four times, only saves time).  workspace: device, at least scd_apply_workspace_bytes(m, n, w) bytes, 8-byte aligned,
  * owned by the caller and free again on return; the call allocates nothing and is synchronous on stream.
  * w == 0 gives y = 0.  SCD_EINVAL on null pointers, negative sizes, m or n above 2^31, a workspace that
  * is too small. */

@@ -423,6 +423,31 @@ __global__ void __launch_bounds__(kApOuterWaves* kWave)
 // (row i, quarter a) of the instruction for entries 16 b .. 16 b + 15 takes; byte q' of its operand dword q is term
 // 16 a + 4 q' + q, a shift and a mask once the field's nibbles are spread over the bytes.
 constexpr int kApFxMaxTerms = 2048;  // terms per split: one dword set (four terms) per thread of the workgroup
+constexpr int kApFxMaxTiles = kApFxMaxTerms / kWave;
+constexpr int kApFxOctet = 8;        // splits that are added as a tree (see apply_reduce_kernel)
+
+// acc[b] += the 64 terms whose word of the output `mine` holds (one per lane) times their digits B
+__device__ __forceinline__ void ap_outer_tile(uint64_t mine, ap_int4 B, int lane, ap_int4 (&acc)[4])
+{
+    uint32_t half[2] = {(uint32_t)mine, (uint32_t)(mine >> 32)};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        half[h] = bit_butterfly<8>(half[h], lane);
+        half[h] = bit_butterfly<4>(half[h], lane);
+        half[h] = bit_butterfly<2>(half[h], lane);
+        half[h] = bit_butterfly<1>(half[h], lane);
+    }
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        // nibbles 0..3 of the field into bytes 0..3
+        const uint32_t two = __builtin_amdgcn_perm(0u, half[b >> 1], (b & 1) ? 0x0C030C02u : 0x0C010C00u);
+        const uint32_t nib = (two | (two << 4)) & 0x0F0F0F0Fu;
+        ap_int4 A;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) A[q] = (int)((nib >> q) & 0x01010101u);
+        acc[b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, B, acc[b], 0, 0, 0);
+    }
+}
 
 template <int NV>
 __global__ void __launch_bounds__(kApMfmaWaves* kWave)
@@ -525,25 +550,7 @@ __global__ void __launch_bounds__(kApMfmaWaves* kWave)
     for (int t = 0; t < ntiles; ++t) {
         const uint64_t mine = next;
         if (t + 1 < ntiles) next = fetch(t + 1);
-        uint32_t half[2] = {(uint32_t)mine, (uint32_t)(mine >> 32)};
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            half[h] = bit_butterfly<8>(half[h], lane);
-            half[h] = bit_butterfly<4>(half[h], lane);
-            half[h] = bit_butterfly<2>(half[h], lane);
-            half[h] = bit_butterfly<1>(half[h], lane);
-        }
-        const ap_int4 B = zb[t * 4 * NC];
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            // nibbles 0..3 of the field into bytes 0..3
-            const uint32_t two = __builtin_amdgcn_perm(0u, half[b >> 1], (b & 1) ? 0x0C030C02u : 0x0C010C00u);
-            const uint32_t nib = (two | (two << 4)) & 0x0F0F0F0Fu;
-            ap_int4 A;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) A[q] = (int)((nib >> q) & 0x01010101u);
-            acc[b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, B, acc[b], 0, 0, 0);
-        }
+        ap_outer_tile(mine, zb[t * 4 * NC], lane, acc);
     }
     // register i of acc[b] = output entry 64 p + 16 b + 4 (lane / 16) + i, column lane mod 16
     const double digit_weight = (double)(1u << (8 * jd));
@@ -559,12 +566,188 @@ __global__ void __launch_bounds__(kApMfmaWaves* kWave)
         }
 }
 
-// y = sum of the splits in order, rounded once, for vector blockIdx.y of the launch (ypart: [split][vector][mpad]).  64
-// entries per workgroup; the splits are cut into four runs that are added side by side (their loads in flight together)
-// and joined in order.
-template <typename TE>
+// The same for `group` = 2, 4 or 8 splits in a row per workgroup, added as the tree of apply_reduce_kernel: with several
+// vectors the workspace, which is sized for one, has no room for the results of every split.  A split stays what it is
+// with one vector, the block of the fixed point, so that a vector keeps its bits in company; as many splits as there are
+// threads for (four terms each) are put into fixed point at a time.  With few workgroups, as here, the end of a split
+// weighs most: joining the digits in f64 in all four lanes and not one entry a lane took 70 instead of 63 us a call at
+// 4096x4096, four vectors (one block of the fixed point for all terms of a workgroup, with fewer bits: 57), and workgroups
+// of four or two waves, which form z more often, 75 and 92.
+template <int NV>
+__global__ void __launch_bounds__(kApMfmaWaves* kWave)
+    apply_outer_group_kernel(const uint64_t* __restrict__ bits, int64_t mw, int64_t w, const double* __restrict__ part, int64_t pstride,
+                             int chunks, const float* __restrict__ c, int nv, int64_t terms_per_split, int group,
+                             double* __restrict__ ypart)
+{
+    constexpr int NC = 4 * NV;
+    __shared__ __align__(16) uint32_t zd[kApFxMaxTerms / 4 * NC];  // [tile of 64 terms][quarter][column][dword]
+    __shared__ double redmax[NV][kApFxMaxTiles], redsum[NV][kApFxMaxTiles], unit[NV][kApFxOctet];
+    __shared__ int bad[NV];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int64_t p = (int64_t)blockIdx.x * kApMfmaWaves + wv;  // word of the output this wave owns
+    const int64_t pc = p < mw ? p : mw - 1;
+    const int64_t j0 = blockIdx.y * terms_per_split * group;
+    const int64_t j1 = j0 + terms_per_split * group < w ? j0 + terms_per_split * group : w;  // (the plan leaves no split empty)
+    const int tps = (int)(terms_per_split / kWave);                        // tiles per split, at most kApFxMaxTiles
+    const int ntiles = (int)((j1 - j0 + kWave - 1) / kWave);
+    const int fit = kApFxMaxTiles / tps, spr = fit < group ? fit : group;  // splits per round
+    // lane q fetches word p of term (tile + q); terms past the end re-read the last one (their z is zero)
+    auto fetch = [&](int64_t tile) {
+        const int64_t j = j0 + tile * kWave + lane;
+        return bits[(j < j1 ? j : j1 - 1) * mw + pc];
+    };
+    uint64_t next = fetch(0);
+    const int col = lane & 15, a = lane >> 4;
+    const int jd = lane & 3, vc = (col & (NC - 1)) >> 2;
+    const ap_int4* zb = (const ap_int4*)zd + a * NC + (col & (NC - 1));
+    // sums of 1, 2 and 4 splits that wait for their partners, and the last result
+    double y1[4], y2[4], y4[4], r[4];
+    int g = 0;
+    if (tid < NV) bad[tid] = 0;
+    for (int base = 0; base < ntiles; base += spr * tps) {
+        // ---- z in fixed point: thread t owns terms 16 (t / 4) + t mod 4 + 4 b of the round, all of them of tile t / 16
+        const int mytile = tid >> 4, mysplit = mytile / tps;
+        const int64_t jr = j0 + (int64_t)base * kWave;
+        const int64_t je = jr + spr * terms_per_split < j1 ? jr + spr * terms_per_split : j1;
+        __syncthreads();  // (what the last round left is read)
+        // sums over the chunks in order, a chunk of all vectors and terms at a time (their loads in flight together)
+        double zv[NV][4];
+        int64_t jc[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int64_t j = jr + 16 * (tid >> 2) + (tid & 3) + 4 * b;
+            jc[b] = j < je ? j : je - 1;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) zv[v][b] = 0.0;
+        }
+        for (int q = 0; q < chunks; ++q) {
+            double x[NV][4];
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) x[v][b] = part[(v < nv ? v : 0) * pstride + q * w + jc[b]];
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) zv[v][b] += x[v][b];
+        }
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            if (v >= nv) continue;  // (as above)
+            double amax = 0.0;
+            bool finite = true;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                zv[v][b] = jr + 16 * (tid >> 2) + (tid & 3) + 4 * b < je ? (double)c[jc[b]] * zv[v][b] : 0.0;
+                finite = finite && (fabs(zv[v][b]) <= 1.7e308);
+                amax = fmax(amax, fabs(zv[v][b]));
+            }
+            amax = fmax(amax, ap_dpp_xor_f64<1>(amax));
+            amax = fmax(amax, ap_dpp_xor_f64<2>(amax));
+            amax = fmax(amax, ap_dpp_xor_f64<4>(amax));
+            amax = fmax(amax, ap_dpp_xor_f64<8>(amax));
+            if ((lane & 15) == 0) redmax[v][mytile] = amax;
+            if (!finite) bad[v] = 1;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            if (v >= nv) continue;
+            double amax = 0.0;
+            for (int q = 0; q < tps; ++q) {
+                const int t = mysplit * tps + q;
+                amax = fmax(amax, redmax[v][t < kApFxMaxTiles ? t : mytile]);  // (past the round's splits all z are zero)
+            }
+            const bool all_finite = bad[v] == 0;
+            int ex = 0;
+            if (amax > 0.0) (void)frexp(amax, &ex);  // amax < 2^ex
+            int sh = 30 - ex;
+            sh = sh > 1000 ? 1000 : sh;              // (2^sh stays a normal number; smaller z round to zero)
+            const double scale = ldexp(1.0, sh);
+            if (mysplit < spr && tid == mysplit * tps * 16) unit[v][mysplit] = ldexp(1.0, -sh);
+            int q4[4];
+            uint32_t dig[4];
+            double sum = 0.0;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                q4[b] = all_finite ? (int)rint(zv[v][b] * scale) : 0;
+                sum += (double)q4[b];
+            }
+            ap_digits(q4, dig);
+            uint32_t* dst = zd + ((tid >> 2) * NC + 4 * v) * 4 + (tid & 3);  // (tile * 4 + quarter = tid / 4)
+#pragma unroll
+            for (int d = 0; d < 4; ++d) dst[d * 4] = dig[d];
+            sum += ap_dpp_xor_f64<1>(sum);  // (integers below 2^36: exact)
+            sum += ap_dpp_xor_f64<2>(sum);
+            sum += ap_dpp_xor_f64<4>(sum);
+            sum += ap_dpp_xor_f64<8>(sum);
+            if ((lane & 15) == 0) redsum[v][mytile] = sum;
+        }
+        __syncthreads();
+        if (p >= mw) continue;
+        for (int s = 0; s < spr && base + s * tps < ntiles; ++s, ++g) {
+            ap_int4 acc[4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) acc[b] = ap_int4{0, 0, 0, 0};
+            double total = 0.0;
+            const int t1 = (s + 1) * tps < ntiles - base ? (s + 1) * tps : ntiles - base;
+            for (int t = s * tps; t < t1; ++t) {
+                const uint64_t mine = next;
+                if (base + t + 1 < ntiles) next = fetch(base + t + 1);
+                total += redsum[vc][t];
+                ap_outer_tile(mine, zb[t * 4 * NC], lane, acc);
+            }
+            const double inv = unit[vc][s];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                // register i = entry 16 b + 4 a + i of the word, digit jd of it in lane jd of four: lane jd gathers the
+                // digits of entry i = jd.  Two of them make an integer below 2^29 (digits up to 128, 2048 terms).
+                int x[4], even, odd;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) x[i] = acc[b][i] << (8 * (jd & 1));
+                even = (jd & 1 ? x[1] : x[0]) + (int)ap_dpp_xor<1>((uint32_t)(jd & 1 ? x[0] : x[1]));
+                odd = (jd & 1 ? x[3] : x[2]) + (int)ap_dpp_xor<1>((uint32_t)(jd & 1 ? x[2] : x[3]));
+                const int keep = jd & 2 ? odd : even, got = (int)ap_dpp_xor<2>((uint32_t)(jd & 2 ? even : odd));
+                const double v = __builtin_fma((double)(jd & 2 ? keep : got), 65536.0, (double)(jd & 2 ? got : keep));
+                r[b] = (total - 2.0 * v) * inv;
+                if (!(g & 1)) {
+                    y1[b] = r[b];
+                } else {
+                    r[b] = y1[b] + r[b];
+                    if (!(g & 2)) {
+                        y2[b] = r[b];
+                    } else {
+                        r[b] = y2[b] + r[b];
+                        if (!(g & 4)) y4[b] = r[b];
+                        else r[b] = y4[b] + r[b];
+                    }
+                }
+            }
+        }
+    }
+    if (p >= mw || col >= NC || vc >= nv) return;
+    const bool fin = bad[vc] == 0;  // (last written ahead of two barriers)
+    double* out = ypart + ((int64_t)blockIdx.y * nv + vc) * (mw * 64) + p * 64 + 4 * a + jd;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        // a group that is cut short: the sums that wait, the shortest first
+        double s = 0.0;
+        if (g & 1) s = y1[b];
+        if (g & 2) s = y2[b] + s;
+        if (g & 4) s = y4[b] + s;
+        if (g == 8) s = r[b];
+        out[16 * b] = fin ? s : __longlong_as_double(0x7FF8000000000000ll);
+    }
+}
+
+// y = sum of the splits, rounded once, for vector blockIdx.y of the launch (ypart: [split][vector][mpad]).  64 entries per
+// workgroup.  The splits are cut into four runs that are added side by side (their loads in flight together) and joined in
+// order.  f32 (TREE): eight splits at a time are added as a tree, ((0 + 1) + (2 + 3)) + ((4 + 5) + (6 + 7)), so that sums
+// of 2, 4 or 8 neighbours that the outer pass has formed (then per_octet is 4, 2 or 1) lead to the same bits.
+template <typename TE, bool TREE>
 __global__ void __launch_bounds__(256)
-    apply_reduce_kernel(const double* __restrict__ ypart, int splits, int64_t mpad, int64_t m, TE* __restrict__ y)
+    apply_reduce_kernel(const double* __restrict__ ypart, int splits, int per_octet, int64_t mpad, int64_t m, TE* __restrict__ y)
 {
     __shared__ double run[4][64];
     const int r = threadIdx.x & 63, g = threadIdx.x >> 6;
@@ -573,17 +756,30 @@ __global__ void __launch_bounds__(256)
     ypart += (int64_t)blockIdx.y * mpad;
     y += (int64_t)blockIdx.y * m;
     mpad *= gridDim.y;  // from one split to the next
-    const int per = (splits + 3) / 4;
-    const int q0 = g * per, q1 = q0 + per < splits ? q0 + per : splits;
+    const int units = TREE ? (splits + per_octet - 1) / per_octet : splits;
+    const int per = (units + 3) / 4;
+    const int q0 = g * per, q1 = q0 + per < units ? q0 + per : units;
     double s = 0.0;
     if (i < len) {
         int q = q0;
-        for (; q + 4 <= q1; q += 4) {
-            const double a0 = ypart[(int64_t)q * mpad + i], a1 = ypart[(int64_t)(q + 1) * mpad + i];
-            const double a2 = ypart[(int64_t)(q + 2) * mpad + i], a3 = ypart[(int64_t)(q + 3) * mpad + i];
-            s = (((s + a0) + a1) + a2) + a3;
+        if constexpr (TREE) {
+            for (; q < q1; ++q) {
+                double x[kApFxOctet];
+#pragma unroll
+                for (int e = 0; e < kApFxOctet; ++e) {
+                    const int sp = q * per_octet + e;
+                    x[e] = e < per_octet && sp < splits ? ypart[(int64_t)sp * mpad + i] : 0.0;
+                }
+                s += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+            }
+        } else {
+            for (; q + 4 <= q1; q += 4) {
+                const double a0 = ypart[(int64_t)q * mpad + i], a1 = ypart[(int64_t)(q + 1) * mpad + i];
+                const double a2 = ypart[(int64_t)(q + 2) * mpad + i], a3 = ypart[(int64_t)(q + 3) * mpad + i];
+                s = (((s + a0) + a1) + a2) + a3;
+            }
+            for (; q < q1; ++q) s += ypart[(int64_t)q * mpad + i];
         }
-        for (; q < q1; ++q) s += ypart[(int64_t)q * mpad + i];
     }
     run[g][r] = s;
     __syncthreads();
@@ -639,7 +835,7 @@ namespace {
 
 template <int NV>
 hipError_t launch_fx(const uint64_t* in_bits, const uint64_t* out_bits, const float* c, int64_t nin, int64_t nout, int64_t w,
-                     const float* x, int nv, float* y, const ApplyPlan& pl, int64_t tps, int splits, void* workspace, hipStream_t st)
+                     const float* x, int nv, float* y, const ApplyPlan& pl, int group, void* workspace, hipStream_t st)
 {
     const int64_t win = (nin + 63) / 64, wout = (nout + 63) / 64;
     const int64_t pstride = (int64_t)pl.parts * w;
@@ -653,20 +849,30 @@ hipError_t launch_fx(const uint64_t* in_bits, const uint64_t* out_bits, const fl
     const int64_t wgs = (tiles + tpw - 1) / tpw;
     hipLaunchKernelGGL((apply_inner_fx_kernel<NV>), dim3((unsigned)wgs, (unsigned)pl.chunks), dim3(kApFxThreads), 0, st, in_bits, win, w, x,
                        nv, nin, part, pstride, tpw);
+    const int splits = (pl.splits_fx + group - 1) / group;
     dim3 go((unsigned)((wout + kApMfmaWaves - 1) / kApMfmaWaves), (unsigned)splits);
-    hipLaunchKernelGGL((apply_outer_fx_kernel<NV>), go, dim3(kApMfmaWaves * kWave), 0, st, out_bits, wout, w, part, pstride, pl.parts, c, nv,
-                       tps, ypart);
-    hipLaunchKernelGGL((apply_reduce_kernel<float>), dim3((unsigned)((nout + 63) / 64), (unsigned)nv), dim3(256), 0, st, ypart, splits,
-                       wout * 64, nout, y);
+    bool one_each = true;
+    if constexpr (NV > 1) {
+        if (group > 1) {
+            hipLaunchKernelGGL((apply_outer_group_kernel<NV>), go, dim3(kApMfmaWaves * kWave), 0, st, out_bits, wout, w, part, pstride,
+                               pl.parts, c, nv, pl.terms_per_split_fx, group, ypart);
+            one_each = false;
+        }
+    }
+    if (one_each)
+        hipLaunchKernelGGL((apply_outer_fx_kernel<NV>), go, dim3(kApMfmaWaves * kWave), 0, st, out_bits, wout, w, part, pstride, pl.parts, c,
+                           nv, pl.terms_per_split_fx, ypart);
+    hipLaunchKernelGGL((apply_reduce_kernel<float, true>), dim3((unsigned)((nout + 63) / 64), (unsigned)nv), dim3(256), 0, st, ypart, splits,
+                       kApFxOctet / group, wout * 64, nout, y);
     return hipGetLastError();
 }
 
 }  // namespace
 
-// nvec vectors (rows of x and y).  f32: up to four share a pass over the bits.  The workspace is sized for one vector
-// whatever their number: several take it with fewer splits of the terms (at most kApFxMaxTerms each), and where even
-// those do not fit, in smaller groups (as many at once as fit: a pass costs 30 us for one vector and 45 for four, so
-// 3 + 1 is faster than 2 + 2).
+// nvec vectors (rows of x and y).  f32: up to four share a pass over the bits, with the bits of y that each has alone: the
+// splits of the terms (the blocks of the fixed point) and the order of their sums do not depend on the number of vectors
+// or on the workspace.  The workspace is sized for one vector whatever their number: several take it with the sums of
+// groups of splits, and where even those do not fit, in smaller sets, as many at once as fit.
 hipError_t launch_apply(const uint64_t* in_bits, const uint64_t* out_bits, const void* c, scd_dtype dt, int64_t nin,
                         int64_t nout, int64_t w, const void* x, int64_t nvec, void* y, void* workspace, size_t workspace_bytes, hipStream_t st)
 {
@@ -681,9 +887,9 @@ hipError_t launch_apply(const uint64_t* in_bits, const uint64_t* out_bits, const
         // the empty sum: a reduce over no splits writes zeros
         for (int64_t v = 0; v < nvec; ++v) {
             if (dt == SCD_F32)
-                hipLaunchKernelGGL((apply_reduce_kernel<float>), dim3(gr), dim3(256), 0, st, ypart, 0, wout * 64, nout, (float*)y + v * nout);
+                hipLaunchKernelGGL((apply_reduce_kernel<float, true>), dim3(gr), dim3(256), 0, st, ypart, 0, kApFxOctet, wout * 64, nout, (float*)y + v * nout);
             else
-                hipLaunchKernelGGL((apply_reduce_kernel<double>), dim3(gr), dim3(256), 0, st, ypart, 0, wout * 64, nout, (double*)y + v * nout);
+                hipLaunchKernelGGL((apply_reduce_kernel<double, false>), dim3(gr), dim3(256), 0, st, ypart, 0, 1, wout * 64, nout, (double*)y + v * nout);
         }
         return hipGetLastError();
     }
@@ -691,26 +897,21 @@ hipError_t launch_apply(const uint64_t* in_bits, const uint64_t* out_bits, const
         for (int64_t v = 0; v < nvec;) {
             const float* xv = (const float*)x + v * nin;
             float* yv = (float*)y + v * nout;
-            int64_t tps = pl.terms_per_split_fx, splits = pl.splits_fx;
-            auto fits = [&](int64_t nv) {  // sets tps and splits
-                if (nv == 1) {
-                    tps = pl.terms_per_split_fx, splits = pl.splits_fx;
-                    return true;
-                }
+            int group = 1;
+            auto fits = [&](int64_t nv) {  // sets group to the smallest that fits
+                if (nv == 1) return group = 1, true;
                 const int64_t room = (int64_t)(workspace_bytes / 8) - nv * pl.parts * w;
-                int64_t most = room > 0 ? room / (nv * wout * 64) : 0;
-                if (most > pl.splits_fx) most = pl.splits_fx;
-                if (most < 1) return false;
-                tps = ((w + most - 1) / most + kWave - 1) / kWave * kWave;
-                splits = (w + tps - 1) / tps;
-                return tps <= kApFxMaxTerms;
+                const int64_t most = room > 0 ? room / (nv * wout * 64) : 0;
+                for (group = 1; group <= kApFxOctet; group *= 2)
+                    if ((pl.splits_fx + group - 1) / group <= most) return true;
+                return false;
             };
             int64_t nv = nvec - v < 4 ? nvec - v : 4;
             while (!fits(nv)) --nv;
             hipError_t e;
-            if (nv > 2) e = launch_fx<4>(in_bits, out_bits, (const float*)c, nin, nout, w, xv, (int)nv, yv, pl, tps, (int)splits, workspace, st);
-            else if (nv == 2) e = launch_fx<2>(in_bits, out_bits, (const float*)c, nin, nout, w, xv, 2, yv, pl, tps, (int)splits, workspace, st);
-            else e = launch_fx<1>(in_bits, out_bits, (const float*)c, nin, nout, w, xv, 1, yv, pl, tps, (int)splits, workspace, st);
+            if (nv > 2) e = launch_fx<4>(in_bits, out_bits, (const float*)c, nin, nout, w, xv, (int)nv, yv, pl, group, workspace, st);
+            else if (nv == 2) e = launch_fx<2>(in_bits, out_bits, (const float*)c, nin, nout, w, xv, 2, yv, pl, group, workspace, st);
+            else e = launch_fx<1>(in_bits, out_bits, (const float*)c, nin, nout, w, xv, 1, yv, pl, group, workspace, st);
             if (e != hipSuccess) return e;
             v += nv;
         }
@@ -724,7 +925,7 @@ hipError_t launch_apply(const uint64_t* in_bits, const uint64_t* out_bits, const
         dim3 go((unsigned)((wout + kApOuterWaves - 1) / kApOuterWaves), (unsigned)pl.splits);
         hipLaunchKernelGGL((apply_outer_kernel<double>), go, dim3(kApOuterWaves * kWave), 0, st, out_bits, wout, w, part,
                            pl.parts, (const double*)c, pl.terms_per_split, ypart);
-        hipLaunchKernelGGL((apply_reduce_kernel<double>), dim3(gr), dim3(256), 0, st, ypart, pl.splits, wout * 64, nout, (double*)y + v * nout);
+        hipLaunchKernelGGL((apply_reduce_kernel<double, false>), dim3(gr), dim3(256), 0, st, ypart, pl.splits, 1, wout * 64, nout, (double*)y + v * nout);
     }
     return hipGetLastError();
 }

@@ -110,6 +110,26 @@ def test_apply_groups_of_vectors(scd, oracle, m, n, w, nvec):
     check(scd, oracle, m, n, w, 11 + nvec, np.float32, nvec % 2 == 0, nvec=nvec)
 
 
+@pytest.mark.parametrize("m,n,w", [(64, 64, 1), (65, 127, 17), (130, 4100, 65), (300, 500, 300), (700, 512, 2049), (513, 600, 4500),
+                                   (4096, 130, 6000), (4096, 4096, 16320), (14336, 4096, 9000)])
+@pytest.mark.parametrize("transpose", [False, True])
+def test_apply_bits_depend_on_neither_neighbours_nor_workspace(scd, m, n, w, transpose):
+    # each vector of a batch gets the bits it gets alone, with the smallest workspace and with larger ones.  The terms'
+    # coefficients fall off so fast that a fixed point over more terms than a split would keep fewer bits of the later ones.
+    S, T, c = random_factors(m, n, w, m + w, np.float32)
+    c = (np.abs(c) * 10.0 ** (-6.0 * np.arange(w) / w)).astype(np.float32)
+    x = torch.from_numpy(np.random.Generator(np.random.PCG64(w)).standard_normal((5, m if transpose else n)).astype(np.float32)).cuda()
+    Sd, Td, cd = dev_bits(S), dev_bits(T), torch.from_numpy(c).cuda()
+    alone = [scd.scd_apply(Sd, Td, cd, m, n, x[v].contiguous(), transpose=transpose) for v in range(5)]
+    need = scd.lib().scd_apply_workspace_bytes(m, n, w)
+    for nvec in (2, 3, 4, 5):
+        for words in ((need + 7) // 8, need // 8 * 3 // 2 + 8, need, 2 * need):
+            ws = torch.full((words,), float("nan"), dtype=torch.float64, device="cuda")
+            y = scd.scd_apply(Sd, Td, cd, m, n, x[:nvec].contiguous(), transpose=transpose, workspace=ws)
+            for v in range(nvec):
+                assert torch.equal(y[v], alone[v]), (nvec, words, v)
+
+
 def test_apply_a_bad_vector_leaves_its_neighbours_alone(scd):
     S, T, c = random_factors(200, 300, 90, 4, np.float32)
     x = torch.from_numpy(np.random.Generator(np.random.PCG64(4)).standard_normal((4, 300)).astype(np.float32)).cuda()
