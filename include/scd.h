@@ -13,7 +13,8 @@
  * Conventions shared by every entry point
  *  - Every data pointer is a DEVICE pointer (HIP global memory on the current device) unless the
  *    argument is documented "host".  The caller owns every buffer it passes; the library neither
- *    frees nor keeps them after the call returns.  The library owns only scd_ctx internals.
+ *    frees nor keeps them after the call returns.  The library owns only scd_ctx internals and the work
+ *    space it keeps for later contexts and calls (scd_release_memory).
  *  - Arrays are dense row-major, last mode fastest.  A matrix is order 2, dims = {m, n}.
  *  - dtype: SCD_F32 (float) or SCD_F64 (double) for the input, the remainder and the coefficients.
  *  - Sign vectors are bitsets of uint64 words (Section 3.1: a 1 bit stands for -1).  Element
@@ -36,6 +37,7 @@
 #ifndef SCD_H
 #define SCD_H
 
+#include <stddef.h>
 #include <stdint.h>
 
 #ifdef __cplusplus
@@ -84,6 +86,12 @@ int scd_decompose(const void* A, scd_dtype dt, int order, const int64_t* dims, i
 int scd_create(scd_ctx** out, const void* A, scd_dtype dt, int order, const int64_t* dims,
                int64_t w_capacity, uint64_t seed, void* stream);
 void scd_destroy(scd_ctx* ctx);
+
+/* Work space of contexts and calls is kept for the next ones when a context is destroyed or a call returns: at most
+ * 1 GiB (device and pinned host memory together) once no launch of another context is running, up to 48 GiB while one
+ * is (giving memory back would wait for it).  scd_release_memory gives back all of it that is not in use and returns its
+ * size in bytes; it waits for the work of every stream of the device, as hipFree does. */
+size_t scd_release_memory(void);
 
 /* Iteration cap of Algorithm 4's loop (the paper's loop is unbounded); default SCD_DEFAULT_MAX_ITERS. */
 int scd_set_max_iters(scd_ctx* ctx, int32_t max_iters);
@@ -188,7 +196,7 @@ int scd_expand(const uint64_t* const* signs, const void* c, scd_dtype dt, int or
  * w values of dt: the FINAL coefficients c_w of all terms (they are direct coefficients of s_j t_j^T, like the
  * normalised c of scd_decompose).  fro_trace: device out, w + 1 doubles, ||A - S_k diag(c_k) T_k^T||_F for
  * k = 0..w.  iters: device out, optional.  w <= SCD_LSQ_MAX_WIDTH (the factor takes 8 w^2 bytes).
- * Allocates its work space on the device and frees it before returning; synchronous on stream.
+ * Takes its work space from the library's (see scd_release_memory) and returns it; synchronous on stream.
  * Returns SCD_OK, SCD_WMAXITER, or SCD_EINVAL / SCD_ENOMEM / SCD_EHIP / SCD_ENONFINITE / SCD_ESINGULAR. */
 int scd_lsq_decompose(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uint64_t seed, int32_t max_iters,
                       void* stream, uint64_t* S, uint64_t* T, void* c, double* fro_trace, int32_t* iters);
@@ -212,7 +220,7 @@ int scd_lsq_decompose_tensor(const void* A, scd_dtype dt, int order, const int64
  * A: device, order >= 2, row-major, last mode fastest, not modified.  signs: host array of order - 1 device
  * pointers (modes 1..k-1), term-major bitsets as in scd_decompose.  c: device out, w * dims[order-1] values of
  * dt, term-major.  fro_trace: device out, w + 1 doubles.  iters: device out, optional (sweeps per term).
- * The remainder is kept in dt; allocates its work space and frees it before returning; synchronous on stream.
+ * The remainder is kept in dt; the work space is the library's (see scd_release_memory); synchronous on stream.
  * Returns SCD_OK, SCD_WMAXITER, or SCD_EINVAL / SCD_ENOMEM / SCD_EHIP / SCD_ENONFINITE. */
 int scd_decompose_scalars(const void* A, scd_dtype dt, int order, const int64_t* dims, int64_t w, uint64_t seed,
                           int32_t max_iters, void* stream, uint64_t* const* signs, void* c, double* fro_trace,

@@ -123,7 +123,7 @@ struct scd_ctx {
     hipEvent_t ev0 = nullptr, ev1 = nullptr;  // around the engine's launch
     double last_launch_seconds = 0.0;
     double last_launch_bytes = 0.0;
-    std::vector<std::pair<void*, size_t>> allocs;  // device blocks of the context and their sizes
+    std::vector<void*> allocs;  // device blocks of the context
 };
 
 namespace {
@@ -140,20 +140,20 @@ int g_slots_in_use = 0;
 // 64 2594 and 2435, the column half step on 4096x4096 f32 76 and 49, 14336x4096 f32 with 24 terms 14.94 and 14.6 ms), and
 // hipFree and hipHostFree wait for every stream of the device: while other contexts run, that wait lasts until their
 // launches end.  A returned block serves the next request of the same size on its device; its owner has waited for its
-// own work before it returns it.  Kept are at most kPoolKeepBytes (while
-// others run, when freeing would wait: kPoolMaxBytes) and what has been used within the last kPoolAge returns; the rest,
-// and everything when an allocation fails, is given back to the device.
-std::mutex g_pool_mutex;
+// own work before it returns it.  Kept are at most kPoolKeepBytes (device and pinned together; while others run, when
+// freeing would wait: kPoolMaxBytes) and what has been used within the last kPoolAge returns; the rest, and everything
+// when an allocation fails or the program asks for it (scd_release_memory), is given back.
 struct PoolBlock {
     void* p;
     size_t bytes;
     int dev;
     bool host;
-    uint64_t stamp;
+    uint64_t stamp;  // clock of its return
 };
-std::list<PoolBlock> g_pool;            // oldest first
-std::map<void*, int> g_pool_device;     // device of every block handed out
-size_t g_pool_dev_bytes = 0;
+std::mutex g_pool_mutex;
+std::list<PoolBlock> g_pool;       // kept, oldest first
+std::list<PoolBlock> g_pool_out;   // handed out (nodes only move between lists: returning a block allocates nothing)
+size_t g_pool_bytes = 0;           // of g_pool
 uint64_t g_pool_clock = 0;
 constexpr size_t kPoolKeepBytes = (size_t)1 << 30, kPoolMaxBytes = (size_t)48 << 30;
 constexpr uint64_t kPoolAge = 1024;
@@ -164,20 +164,29 @@ bool others_running()
     return g_slots_in_use > 0;
 }
 
-// Frees the oldest blocks until at most `keep` bytes are left, and those that are too old.
-void pool_trim(size_t keep)
+void pool_give_back(const PoolBlock& b)
 {
-    std::vector<PoolBlock> out;
+    (void)(b.host ? hipHostFree(b.p) : hipFree(b.p));
+    (void)hipGetLastError();
+}
+
+// Frees the oldest blocks until at most `keep` bytes are left, and those that are too old; the bytes freed.
+size_t pool_trim(size_t keep)
+{
+    std::list<PoolBlock> out;
     {
         std::lock_guard<std::mutex> lk(g_pool_mutex);
-        while (!g_pool.empty() &&
-               (g_pool_dev_bytes > keep || keep == 0 || g_pool.front().stamp + kPoolAge < g_pool_clock)) {
-            out.push_back(g_pool.front());
-            if (!g_pool.front().host) g_pool_dev_bytes -= g_pool.front().bytes;
-            g_pool.pop_front();
+        while (!g_pool.empty() && (g_pool_bytes > keep || keep == 0 || g_pool.front().stamp + kPoolAge < g_pool_clock)) {
+            g_pool_bytes -= g_pool.front().bytes;
+            out.splice(out.end(), g_pool, g_pool.begin());
         }
     }
-    for (PoolBlock& b : out) (void)(b.host ? hipHostFree(b.p) : hipFree(b.p));
+    size_t freed = 0;
+    for (const PoolBlock& b : out) {
+        pool_give_back(b);
+        freed += b.bytes;
+    }
+    return freed;
 }
 
 hipError_t pool_malloc(void** p, size_t bytes, bool host)
@@ -190,44 +199,53 @@ hipError_t pool_malloc(void** p, size_t bytes, bool host)
         for (auto it = g_pool.rbegin(); it != g_pool.rend(); ++it) {  // the latest one first
             if (it->bytes != bytes || it->host != host || it->dev != dev) continue;
             *p = it->p;
-            if (!host) g_pool_dev_bytes -= bytes;
-            g_pool_device[*p] = dev;
-            g_pool.erase(std::next(it).base());
+            g_pool_bytes -= bytes;
+            g_pool_out.splice(g_pool_out.end(), g_pool, std::next(it).base());
             return hipSuccess;
         }
+    }
+    std::list<PoolBlock> node;
+    try {
+        node.push_back({nullptr, bytes, dev, host, 0});
+    } catch (...) {
+        return hipErrorOutOfMemory;
     }
     e = host ? hipHostMalloc(p, bytes, hipHostMallocDefault) : hipMalloc(p, bytes);
     if (e != hipSuccess) {
         (void)hipGetLastError();
-        pool_trim(0);
+        (void)pool_trim(0);
         e = host ? hipHostMalloc(p, bytes, hipHostMallocDefault) : hipMalloc(p, bytes);
     }
     if (e == hipSuccess) {
+        node.front().p = *p;
         std::lock_guard<std::mutex> lk(g_pool_mutex);
-        g_pool_device[*p] = dev;
+        g_pool_out.splice(g_pool_out.end(), node);
     }
     return e;
 }
 
 // The caller has waited for all work on the block.
-void pool_free(void* p, size_t bytes, bool host)
+void pool_free(void* p)
 {
     if (!p) return;
     const bool busy = others_running();
-    bool keep;
+    std::list<PoolBlock> gone;
     {
         std::lock_guard<std::mutex> lk(g_pool_mutex);
-        auto it = g_pool_device.find(p);
-        const int dev = it == g_pool_device.end() ? 0 : it->second;
-        if (it != g_pool_device.end()) g_pool_device.erase(it);
-        keep = host || (busy ? g_pool_dev_bytes + bytes <= kPoolMaxBytes : bytes <= kPoolKeepBytes);
-        if (keep) {
-            g_pool.push_back({p, bytes, dev, host, ++g_pool_clock});
-            if (!host) g_pool_dev_bytes += bytes;
+        auto it = g_pool_out.end();
+        while (it != g_pool_out.begin() && std::prev(it)->p != p) --it;  // (the latest ones are returned first)
+        if (it == g_pool_out.begin()) return;
+        --it;
+        if (busy ? g_pool_bytes + it->bytes <= kPoolMaxBytes : it->bytes <= kPoolKeepBytes) {
+            it->stamp = ++g_pool_clock;
+            g_pool_bytes += it->bytes;
+            g_pool.splice(g_pool.end(), g_pool_out, it);
+        } else {
+            gone.splice(gone.end(), g_pool_out, it);
         }
     }
-    if (!keep) (void)(host ? hipHostFree(p) : hipFree(p));
-    if (!busy) pool_trim(kPoolKeepBytes);
+    for (const PoolBlock& b : gone) pool_give_back(b);
+    if (!busy) (void)pool_trim(kPoolKeepBytes);
 }
 
 // Waits for the work of a stream on blocks that are about to be returned; for the whole device where the stream cannot
@@ -258,7 +276,7 @@ int dev_alloc(scd_ctx* c, void** p, size_t bytes)
         (void)hipGetLastError();
         return SCD_ENOMEM;
     }
-    c->allocs.emplace_back(*p, bytes);
+    c->allocs.push_back(*p);
     return SCD_OK;
 }
 
@@ -492,7 +510,7 @@ int setup_engines(scd_ctx* c)
             c->RT = nullptr;
             c->sparse = false;
         } else {
-            c->allocs.emplace_back(c->RT, (size_t)c->total * c->esize);
+            c->allocs.push_back(c->RT);
             c->rt_stale = true;
             SCD_TRY(dev_alloc(c, (void**)&c->xbuf_sp, sparse_xbuf_bytes()));
             if (!hip_ok(hipMemsetAsync(c->xbuf_sp, 0, sparse_xbuf_bytes(), c->stream))) return SCD_EHIP;
@@ -859,13 +877,15 @@ int scd_create(scd_ctx** out, const void* A, scd_dtype dt, int order, const int6
 #undef CHIP
 }
 
+size_t scd_release_memory(void) { return pool_trim(0); }
+
 void scd_destroy(scd_ctx* c)
 {
     if (!c) return;
     settle(c->stream);
-    for (auto& b : c->allocs) pool_free(b.first, b.second, false);
-    pool_free(c->pinned, sizeof(State), true);
-    pool_free(c->res_pin, sizeof(ResidentResult), true);
+    for (void* b : c->allocs) pool_free(b);
+    pool_free(c->pinned);
+    pool_free(c->res_pin);
     if (c->ev0) (void)hipEventDestroy(c->ev0);
     if (c->ev1) (void)hipEventDestroy(c->ev1);
     (void)hipGetLastError();
@@ -1189,7 +1209,7 @@ int scd_row_signed_sum(const void* R, scd_dtype dt, int64_t m, int64_t n, const 
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (shared) {
         if (e != hipSuccess) settle(st);
-        pool_free(own, sbytes, false);
+        pool_free(own);
     }
     if (e != hipSuccess) {
         g_last_hip = (int)e;
@@ -1235,7 +1255,7 @@ int scd_col_signed_sum(const void* R, scd_dtype dt, int64_t m, int64_t n, const 
     hipError_t es2 = hipStreamSynchronize(st);
     if (e == hipSuccess) e = es2;
     if (es2 != hipSuccess) settle(st);
-    pool_free(base, bytes, false);
+    pool_free(base);
     if (e != hipSuccess) {
         g_last_hip = (int)e;
         (void)hipGetLastError();
@@ -1325,7 +1345,7 @@ int scd_expand(const uint64_t* const* signs, const void* cvec, scd_dtype dt, int
             g_last_hip = (int)e;
             (void)hipGetLastError();
             settle(st);
-            pool_free(kr, kr_bytes, false);
+            pool_free(kr);
             return SCD_EHIP;
         }
         T = kr;
@@ -1334,7 +1354,7 @@ int scd_expand(const uint64_t* const* signs, const void* cvec, scd_dtype dt, int
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (kr) {
         if (e != hipSuccess) settle(st);
-        pool_free(kr, kr_bytes, false);
+        pool_free(kr);
     }
     if (e != hipSuccess) {
         g_last_hip = (int)e;
@@ -1363,7 +1383,7 @@ struct ModeSums {
     void* partials = nullptr;
     uint64_t* kr_in = nullptr;
     uint64_t* cur[SCD_MAX_ORDER] = {nullptr};  // current sign vector of every mode
-    std::vector<std::pair<void*, size_t>> bufs;
+    std::vector<void*> bufs;
 
     bool alloc(void** p, size_t bytes)
     {
@@ -1373,7 +1393,7 @@ struct ModeSums {
             *p = nullptr;
             return false;
         }
-        bufs.emplace_back(*p, bytes);
+        bufs.push_back(*p);
         return true;
     }
     bool init(int ord, const int64_t* d)
@@ -1404,7 +1424,7 @@ struct ModeSums {
     }
     void release()
     {
-        for (auto& b : bufs) pool_free(b.first, b.second, false);  // (the caller has waited for the stream)
+        for (void* b : bufs) pool_free(b);  // (the caller has waited for the stream)
         bufs.clear();
     }
     // uA <- x x_i (others), x of dtype dt
@@ -1477,13 +1497,13 @@ int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uin
     if (e == hipSuccess) e = pool_malloc((void**)&pin, sizeof(Pinned), true);
     if (e != hipSuccess) {
         (void)hipGetLastError();
-        if (dev) pool_free(dev, bytes, false);
+        if (dev) pool_free(dev);
         return SCD_ENOMEM;
     }
     auto cleanup = [&](int code) {
         settle(st);
-        pool_free(dev, bytes, false);
-        pool_free(pin, sizeof(Pinned), true);
+        pool_free(dev);
+        pool_free(pin);
         (void)hipGetLastError();
         return code;
     };
@@ -1603,7 +1623,7 @@ int scd_lsq_decompose_tensor(const void* A, scd_dtype dt, int order, const int64
     auto cleanup = [&](int code) {
         settle(st);
         ms.release();
-        if (host) pool_free(host, 4 * sizeof(double), true);
+        if (host) pool_free(host);
         (void)hipGetLastError();
         return code;
     };
@@ -1727,7 +1747,7 @@ int scd_decompose_scalars(const void* A, scd_dtype dt, int order, const int64_t*
                 }
             }
             settle(st);
-            if (c->c_scal) pool_free(c->c_scal, (size_t)w * (size_t)q * es, false);
+            if (c->c_scal) pool_free(c->c_scal);
             c->c_scal = nullptr;
             scd_destroy(c);
             return run;
@@ -1755,7 +1775,7 @@ int scd_decompose_scalars(const void* A, scd_dtype dt, int order, const int64_t*
     auto cleanup = [&](int code) {
         settle(st);
         ms.release();
-        if (host) pool_free(host, 4 * sizeof(double), true);
+        if (host) pool_free(host);
         (void)hipGetLastError();
         return code;
     };

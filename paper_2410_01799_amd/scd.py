@@ -27,7 +27,7 @@ EXPORTS = [
     "scd_expand", "scd_pack", "scd_unpack", "scd_rng_signs", "scd_strerror", "scd_last_hip_error", "scd_traffic",
     "scd_probe_stream", "scd_profile_sweeps", "scd_probe_exchange", "scd_engine", "scd_set_workgroups",
     "scd_apply", "scd_apply_workspace_bytes", "scd_lsq_decompose", "scd_lsq_decompose_tensor", "scd_decompose_scalars", "scd_sparse_flips",
-    "scd_col_signed_sum_noalloc", "scd_set_option", "scd_get_option", "scd_stream_geometry",
+    "scd_col_signed_sum_noalloc", "scd_set_option", "scd_get_option", "scd_stream_geometry", "scd_release_memory",
 ]
 
 # scd_option of include/scd.h
@@ -58,6 +58,8 @@ def lib() -> C.CDLL:
         L.scd_decompose.argtypes = [vp, C.c_int, C.c_int, pi64, i64, u64, vp, pvp, vp, vp, vp]
         L.scd_create.argtypes = [pvp, vp, C.c_int, C.c_int, pi64, i64, u64, vp]
         L.scd_destroy.argtypes = [vp]
+        L.scd_release_memory.argtypes = []
+        L.scd_release_memory.restype = C.c_size_t
         L.scd_destroy.restype = None
         L.scd_set_max_iters.argtypes = [vp, i32]
         L.scd_set_workgroups.argtypes = [vp, C.c_int]
@@ -331,6 +333,11 @@ def scd_probe_exchange(which: int, grid: int = 256, group: int = 16, rounds: int
     _check(lib().scd_probe_exchange(int(which), int(grid), int(group), int(rounds), _stream(), C.byref(sec)),
            "scd_probe_exchange")
     return sec.value
+
+
+def scd_release_memory() -> int:
+    """Give back the work space the library keeps for the next contexts and calls; the bytes given back."""
+    return int(lib().scd_release_memory())
 
 
 # --------------------------------------------------------------------------- stateful context

@@ -39,15 +39,32 @@ def test_reused_blocks_do_not_show(scd):
             assert torch.equal(f(scd, k), ref[k - 1])
 
 
-def test_kept_memory_is_bounded(scd):
-    A = gauss((4096, 4096), 3)
-    scd.scd_decompose(A, 1, 1, options={"resident": 0, "sparse_min_mib": 0})
+def device_free():
     torch.cuda.synchronize()
-    free0 = torch.cuda.mem_get_info()[0]
-    for i in range(12):                # a new shape each time: 100 MB and more a context
-        scd.scd_decompose(gauss((3000 + 64 * i, 4096), i), 1, 1, options={"resident": 0, "sparse_min_mib": 0})
-    torch.cuda.empty_cache()
-    assert free0 - torch.cuda.mem_get_info()[0] <= (1 << 30) + (64 << 20)
+    torch.cuda.empty_cache()           # (what torch keeps would hide what the library keeps)
+    return torch.cuda.mem_get_info()[0]
+
+
+def test_kept_memory_is_bounded_and_given_back(scd):
+    opts = {"resident": 0, "sparse_min_mib": 0}
+    scd.scd_decompose(gauss((512, 512), 3), 1, 1, options=opts)
+    scd.scd_release_memory()
+    free0 = device_free()
+    for i in range(40):                # a new shape each time, 100 MB and more a context: 5 GB in all
+        scd.scd_decompose(torch.full((3000 + 64 * i, 4096), 1.0 + i, device="cuda"), 1, 1, options=opts)
+    kept = free0 - device_free()
+    assert 0 < kept <= (1 << 30) + (64 << 20)
+    released = scd.scd_release_memory()
+    assert kept - (64 << 20) <= released <= 1 << 30
+    assert free0 - device_free() <= 16 << 20
+    assert scd.scd_release_memory() == 0
+    # blocks in use are not touched
+    with scd.ScdContext(gauss((301, 257), 4), 6, 4) as ctx:
+        ctx.run(2)
+        scd.scd_release_memory()
+        ctx.run(4)
+        c = ctx.results()["c"]
+    assert torch.equal(c, scd.scd_decompose(gauss((301, 257), 4), 6, 4)["c"])
 
 
 def test_threads_with_streams_of_their_own(scd):
@@ -57,6 +74,8 @@ def test_threads_with_streams_of_their_own(scd):
     def work(i):
         with torch.cuda.stream(torch.cuda.Stream()):
             for r in range(3):
+                if i == 5:
+                    scd.scd_release_memory()   # (waits for the others and takes what they have returned)
                 j = (i + r) % len(CALLS)
                 k = 1 + (i + r) % 2
                 if not torch.equal(CALLS[j](scd, k), ref[j][k - 1]):
