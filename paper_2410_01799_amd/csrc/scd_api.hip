@@ -149,6 +149,7 @@ struct PoolBlock {
     int dev;
     bool host;
     uint64_t stamp;  // clock of its return
+    uint64_t id;     // of the allocation, unique in the process
 };
 std::mutex g_pool_mutex;
 std::list<PoolBlock> g_pool;       // kept, oldest first
@@ -164,10 +165,25 @@ bool others_running()
     return g_slots_in_use > 0;
 }
 
-void pool_give_back(const PoolBlock& b)
+// The runtime's number of the allocation at p; 0 if there is none.
+uint64_t allocation_id(void* p)
 {
+    uint64_t id = 0;
+    if (hipPointerGetAttribute(&id, HIP_POINTER_ATTRIBUTE_BUFFER_ID, (hipDeviceptr_t)p) != hipSuccess) id = 0;
+    (void)hipGetLastError();
+    return id;
+}
+
+// A device reset frees all blocks; their addresses may then be another owner's (0.1 us a look).
+bool pool_valid(const PoolBlock& b) { return b.id != 0 && allocation_id(b.p) == b.id; }
+
+// The bytes given back.
+size_t pool_give_back(const PoolBlock& b)
+{
+    if (!pool_valid(b)) return 0;
     (void)(b.host ? hipHostFree(b.p) : hipFree(b.p));
     (void)hipGetLastError();
+    return b.bytes;
 }
 
 // Frees the oldest blocks until at most `keep` bytes are left, and those that are too old; the bytes freed.
@@ -182,10 +198,7 @@ size_t pool_trim(size_t keep)
         }
     }
     size_t freed = 0;
-    for (const PoolBlock& b : out) {
-        pool_give_back(b);
-        freed += b.bytes;
-    }
+    for (const PoolBlock& b : out) freed += pool_give_back(b);
     return freed;
 }
 
@@ -196,17 +209,22 @@ hipError_t pool_malloc(void** p, size_t bytes, bool host)
     if (e != hipSuccess) return e;
     {
         std::lock_guard<std::mutex> lk(g_pool_mutex);
-        for (auto it = g_pool.rbegin(); it != g_pool.rend(); ++it) {  // the latest one first
+        for (auto it = g_pool.end(); it != g_pool.begin();) {  // the latest one first
+            --it;
             if (it->bytes != bytes || it->host != host || it->dev != dev) continue;
-            *p = it->p;
             g_pool_bytes -= bytes;
-            g_pool_out.splice(g_pool_out.end(), g_pool, std::next(it).base());
+            if (!pool_valid(*it)) {
+                it = g_pool.erase(it);
+                continue;
+            }
+            *p = it->p;
+            g_pool_out.splice(g_pool_out.end(), g_pool, it);
             return hipSuccess;
         }
     }
     std::list<PoolBlock> node;
     try {
-        node.push_back({nullptr, bytes, dev, host, 0});
+        node.push_back({nullptr, bytes, dev, host, 0, 0});
     } catch (...) {
         return hipErrorOutOfMemory;
     }
@@ -218,6 +236,7 @@ hipError_t pool_malloc(void** p, size_t bytes, bool host)
     }
     if (e == hipSuccess) {
         node.front().p = *p;
+        node.front().id = allocation_id(*p);
         std::lock_guard<std::mutex> lk(g_pool_mutex);
         g_pool_out.splice(g_pool_out.end(), node);
     }
@@ -244,7 +263,7 @@ void pool_free(void* p)
             gone.splice(gone.end(), g_pool_out, it);
         }
     }
-    for (const PoolBlock& b : gone) pool_give_back(b);
+    for (const PoolBlock& b : gone) (void)pool_give_back(b);
     if (!busy) (void)pool_trim(kPoolKeepBytes);
 }
 

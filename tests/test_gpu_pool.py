@@ -88,3 +88,40 @@ def test_threads_with_streams_of_their_own(scd):
     for t in threads:
         t.join()
     assert not bad
+
+
+AFTER_RESET = """
+import ctypes as C, sys
+hip, scd = C.CDLL("libamdhip64.so"), C.CDLL(sys.argv[1])
+def malloc(n):
+    p = C.c_void_p()
+    assert hip.hipMalloc(C.byref(p), C.c_size_t(n)) == 0
+    return p
+def known(p):
+    v = C.c_uint64()
+    return hip.hipPointerGetAttribute(C.byref(v), 7, p) == 0     # HIP_POINTER_ATTRIBUTE_BUFFER_ID
+m, n = 640, 512
+A, S, T, c, tr = malloc(4 * m * n), malloc(8 * 10), malloc(8 * 8), malloc(4), malloc(16)
+assert hip.hipMemset(A, 0, C.c_size_t(4 * m * n)) == 0
+scd.scd_release_memory.restype = C.c_size_t
+scd.scd_decompose.argtypes = [C.c_void_p, C.c_int, C.c_int, C.c_void_p, C.c_int64, C.c_uint64, C.c_void_p, C.c_void_p] + 3 * [C.c_void_p]
+dims, signs = (C.c_int64 * 2)(m, n), (C.c_void_p * 2)(S.value, T.value)
+assert scd.scd_decompose(A, 0, 2, dims, 1, 3, None, signs, c, tr, None) == 0
+assert hip.hipDeviceSynchronize() == 0 and known(A)
+assert hip.hipDeviceReset() == 0 and not known(A)
+mine = [malloc(k) for k in (4 * m * n, 4 * m * n, 1 << 20, 4096, 4096, 80, 64, 16, 8, 8, 4)]
+assert scd.scd_release_memory() == 0
+assert all(known(p) for p in mine)
+print("whole")
+"""
+
+
+def test_blocks_of_before_a_device_reset_are_forgotten(scd, tmp_path):
+    # the addresses belong to the program's own allocations now; no kernel runs after the reset
+    import subprocess
+    import sys
+
+    prog = tmp_path / "after_reset.py"
+    prog.write_text(AFTER_RESET)
+    run = subprocess.run([sys.executable, str(prog), str(scd.LIB_PATH)], capture_output=True, text=True, timeout=100)
+    assert run.returncode == 0 and run.stdout.strip() == "whole", run.stderr[-2000:]
