@@ -222,13 +222,13 @@ __device__ double lq_block_sum(double v, double* red)
 // The new term has index k.  Appends row k to the Cholesky factor L (lower triangular, row-major, leading
 // dimension ld) of the Gram matrix, whose new row is g[j] (j < k) with `diag` on the diagonal;
 // extends the forward solution y of L y = b by one entry; solves L^T c = y for all k + 1 coefficients.
-// Returns <c, b>, the same in every thread, or -1 if the new term is (numerically) in the span of the old ones.
+// False if the new term is (numerically) in the span of the old ones; else *cb = <c, b>; the same in every thread.
 // One workgroup.  Both substitutions are in axpy form: a thread keeps up to four unknowns in registers, the owner of
 // the next one divides and hands it on through LDS, one barrier per unknown, and the column (row) of L that the next
 // step needs is loaded ahead of the barrier.  (With a sum over the workgroup per unknown, forward substitution alone
 // took 0.7 us per unknown.)
-__device__ double lq_refit(double* __restrict__ L, int64_t ld, int64_t k, const double* g, double diag, const double* __restrict__ bvec,
-                           double* __restrict__ yv, double* __restrict__ c, double* red, double* hand)
+__device__ bool lq_refit(double* __restrict__ L, int64_t ld, int64_t k, const double* g, double diag, const double* __restrict__ bvec,
+                           double* __restrict__ yv, double* __restrict__ c, double* red, double* hand, double* cb_out)
 {
     constexpr int NQ = SCD_LSQ_MAX_WIDTH / kLqThreads;
     const int tid = threadIdx.x;
@@ -269,7 +269,7 @@ __device__ double lq_refit(double* __restrict__ L, int64_t ld, int64_t k, const 
     s2 = lq_block_sum(s2, red);
     sy = lq_block_sum(sy, red);
     const double d2 = diag - s2;
-    if (!(d2 > 1e-9 * diag)) return -1.0;
+    if (!(d2 > 1e-9 * diag)) return false;
     const double lkk = sqrt(d2), yk = (bvec[k] - sy) / lkk;
     if (tid == 0) {
         row[k] = lkk;
@@ -310,7 +310,8 @@ __device__ double lq_refit(double* __restrict__ L, int64_t ld, int64_t k, const 
         for (int i = 0; i < NQ; ++i)
             if (tid + (int64_t)i * kLqThreads < r) x[i] -= cur[i] * cr;
     }
-    return lq_block_sum(cb, red);
+    *cb_out = lq_block_sum(cb, red);
+    return true;
 }
 
 // One workgroup: refit after the new term k and record ||A - S diag(c) T^T||_F = sqrt(||A||^2 - <c, b>) (the remainder
@@ -321,10 +322,11 @@ __global__ void __launch_bounds__(kLqThreads)
 {
     __shared__ double red[kLqThreads / kWave];
     __shared__ double hand[2];
-    const double cb = lq_refit(L, ld, k, g, diag, bvec, yv, c, red, hand);
+    double cb = 0.0;
+    const bool ok = lq_refit(L, ld, k, g, diag, bvec, yv, c, red, hand, &cb);
     if (threadIdx.x == 0) {
         const double f2 = fro0sq - cb;
-        if (cb < 0.0) *status = 1;
+        if (!ok) *status = 1;
         else trace_out[0] = sqrt(f2 > 0.0 ? f2 : 0.0);
     }
 }
@@ -576,8 +578,8 @@ __global__ void __launch_bounds__(kLqThreads) lsq_next_kernel(LsqMatArgs a)
     __syncthreads();
     lq_dots(a.S, k, mw, a.m, sh.vec, sh.e, sh.e);  // (each element is read and written by the same lane)
     __syncthreads();
-    const double fro2 = lq_refit(a.L, a.w, k, sh.e, (double)a.m * (double)a.n, a.bvec, a.yv, a.c, sh.red, &sh.part[0][0]);
-    if (fro2 < 0.0) {
+    double cb = 0.0;
+    if (!lq_refit(a.L, a.w, k, sh.e, (double)a.m * (double)a.n, a.bvec, a.yv, a.c, sh.red, &sh.part[0][0], &cb)) {
         if (tid == 0) {
             st->status = 1;
             st->done = 1;
@@ -585,7 +587,7 @@ __global__ void __launch_bounds__(kLqThreads) lsq_next_kernel(LsqMatArgs a)
         return;
     }
     if (tid == 0) {
-        const double f2 = a.fro0sq - fro2;
+        const double f2 = a.fro0sq - cb;
         a.trace[k + 1] = sqrt(f2 > 0.0 ? f2 : 0.0);
         st->k = k + 1;
         st->j = 0;
