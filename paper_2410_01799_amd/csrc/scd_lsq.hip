@@ -8,7 +8,8 @@
 // comes from the bitsets, and the correction is a signed sum of k scalars per entry.  The normal equations
 // (Section 3.3) use the Gram matrix G_ij = <s_i,s_j><t_i,t_j>, again from popcounts, kept as a Cholesky
 // factor that grows by one row per term; b_j = <s_j, A t_j> falls out of the last half step of term j.
-// Everything here is f64; the kernels are small and latency-bound (one term = a few hundred launches).
+// Everything here is f64; the kernels are small and latency-bound (matrices of up to 64 words a side: three launches per
+// sweep and no host in the loop; others, and tensors: about ten and a read-back).
 #include "scd_device.h"
 #include "scd_rng.h"
 
@@ -380,9 +381,10 @@ struct LqShared {
     int flag;
 };
 
-// out[j] = coef[j] * <x_j, vec> (coef null: 1) for j < k: a group of 2^g >= nw lanes per term.  No barrier at the end.
-__device__ void lq_dots(const uint64_t* __restrict__ bits, int64_t k, int nw, int64_t len, const uint64_t* vec,
-                        const double* __restrict__ coef, double* out)
+// out[j] = coef[j] * <x_j, vec> (coef null: 1; it may be out) for j < k: a group of 2^g >= nw lanes per term.  No barrier
+// at the end.
+__device__ void lq_dots(const uint64_t* __restrict__ bits, int64_t k, int nw, int64_t len, const uint64_t* vec, const double* coef,
+                        double* out)
 {
     int g = 1;
     while (g < nw) g <<= 1;  // at most 64
