@@ -1,5 +1,7 @@
-// HIP kernels of libscd for gfx950 (wave64).  Everything here is memory-bound sign-flip-and-add
-// work (Section 3.4 of arXiv 2410.01799: no multiplies are needed), so there is no MFMA code.
+// HIP kernels of the launch-stream engine, of the half steps on caller data and of the bitsets, for gfx950 (wave64).
+// Everything here is memory-bound sign-flip-and-add work (Section 3.4 of arXiv 2410.01799: no multiplies are needed), so
+// there is no MFMA code (products from the packed factors and their expansion, which are contractions, have files of
+// their own).
 //
 //  rowpass  : one pass over a rows x cols array X with a sign vector t over the columns:
 //             u = X t, s = sgn(u) and, in the same pass, the per-workgroup partial sums of
@@ -9,7 +11,7 @@
 //  reduce   : fixed-order sum of the partials -> R^T s, t = sgn(.), c = sum |.| (Algorithm 4 line 7
 //             via Section 3.1: <s, R t> = ||R^T s||_1), packs s from u with 64-lane ballots.
 //  kron     : Kronecker products of sign bitsets for the tensor sweep (Algorithm 12 lines 5-7).
-//  expand   : the definition sum_j c_j s_j t_j^T with one f64 accumulator per entry.
+//  row_sums, col_partials : the half steps on caller data.
 #include <stddef.h>
 
 #include "scd_device.h"
@@ -77,8 +79,7 @@ struct Vec16<double> {
 //   phase B  one thread per column: signed sum of the workgroup's rows (re-read from cache)
 
 template <typename TE>
-__device__ void rowpass_generic_body(TE* __restrict__ X, int64_t rows, int64_t cols, int rows_per_wg,
-                                     bool do_update, bool do_norm, bool do_rows, bool do_cols,
+__device__ void rowpass_generic_body(TE* __restrict__ X, int64_t rows, int64_t cols, int rows_per_wg, bool do_update, bool do_norm,
                                      const uint64_t* __restrict__ sumbits, const uint64_t* __restrict__ updbits,
                                      const uint64_t* __restrict__ rowbits, TE ck, TE* __restrict__ partials,
                                      double* __restrict__ u, double* __restrict__ fparts, uint8_t* sh_s,
@@ -92,31 +93,25 @@ __device__ void rowpass_generic_body(TE* __restrict__ X, int64_t rows, int64_t c
 
     for (int64_t r = r0 + wv; r < r1; r += kWavesPerBlock) {
         TE* row = X + r * cols;
-        uint32_t sold = (do_update || !do_rows) ? bit_at(rowbits, r) : 0u;
+        const uint32_t sold = do_update ? bit_at(rowbits, r) : 0u;
         TE p = 0;
         double f = 0.0;
-        if (do_update || do_norm || do_rows) {
-            for (int64_t l = lane; l < cols; l += kWave) {
-                TE x = row[l];
-                if (do_update) {
-                    // x - ck * s_r * t_l : the product of the signs picks +ck or -ck
-                    uint32_t neg = sold ^ bit_at(updbits, l);
-                    x = x - flip(ck, neg);
-                    row[l] = x;
-                }
-                if (do_norm) f += (double)x * (double)x;
-                if (do_rows) p += flip(x, bit_at(sumbits, l));
+        for (int64_t l = lane; l < cols; l += kWave) {
+            TE x = row[l];
+            if (do_update) {
+                // x - ck * s_r * t_l : the product of the signs picks +ck or -ck
+                uint32_t neg = sold ^ bit_at(updbits, l);
+                x = x - flip(ck, neg);
+                row[l] = x;
             }
+            if (do_norm) f += (double)x * (double)x;
+            p += flip(x, bit_at(sumbits, l));
         }
         fsq += f;
-        if (do_rows) {
-            double ur = wave_sum((double)p);
-            if (lane == 0) {
-                u[r] = ur;
-                sh_s[r - r0] = (ur < 0.0) ? 1 : 0;
-            }
-        } else if (lane == 0) {
-            sh_s[r - r0] = (uint8_t)sold;
+        const double ur = wave_sum((double)p);
+        if (lane == 0) {
+            u[r] = ur;
+            sh_s[r - r0] = (ur < 0.0) ? 1 : 0;
         }
     }
     if (do_norm) {
@@ -129,14 +124,12 @@ __device__ void rowpass_generic_body(TE* __restrict__ X, int64_t rows, int64_t c
         for (int i = 0; i < kWavesPerBlock; ++i) t += sh_red[i];
         fparts[blockIdx.x] = t;
     }
-    if (do_cols) {
-        const int nr = (int)(r1 - r0);
-        for (int64_t l = threadIdx.x; l < cols; l += kBlock) {
-            TE acc = 0;
-            const TE* colp = X + r0 * cols + l;
-            for (int r = 0; r < nr; ++r) acc += flip(colp[(int64_t)r * cols], (uint32_t)sh_s[r]);
-            partials[(int64_t)blockIdx.x * cols + l] = acc;
-        }
+    const int nr = (int)(r1 - r0);
+    for (int64_t l = threadIdx.x; l < cols; l += kBlock) {
+        TE acc = 0;
+        const TE* colp = X + r0 * cols + l;
+        for (int r = 0; r < nr; ++r) acc += flip(colp[(int64_t)r * cols], (uint32_t)sh_s[r]);
+        partials[(int64_t)blockIdx.x * cols + l] = acc;
     }
 }
 
@@ -253,21 +246,21 @@ __global__ void __launch_bounds__(kBlock) rowpass_generic_kernel(RowPassArgs a)
         const bool upd = d.mode == PASS_UPDATE;
         const bool start = d.mode == PASS_START;
         const uint64_t* sumbits = (upd || (start && !st.t0_given)) ? a.sign_rng : a.sign_cur;
-        rowpass_generic_body<TE>((TE*)a.X, a.rows, a.cols, a.rows_per_wg, upd, upd || start, true, true, sumbits,
+        rowpass_generic_body<TE>((TE*)a.X, a.rows, a.cols, a.rows_per_wg, upd, upd || start, sumbits,
                                  a.sign_cur, a.row_bits, (TE)d.ck, (TE*)a.partials, a.u, a.fparts, sh_s, sh_red);
         level0_bookkeeping<TE>(a, st, d);
     } else {
         const StateView st = view_state(a.next);
         if (!st.active) return;
         const uint64_t* sumbits = st.sweep_rng ? a.sign_rng : a.sign_cur;
-        rowpass_generic_body<TE>((TE*)a.X, a.rows, a.cols, a.rows_per_wg, false, false, true, true, sumbits,
+        rowpass_generic_body<TE>((TE*)a.X, a.rows, a.cols, a.rows_per_wg, false, false, sumbits,
                                  a.sign_cur, a.row_bits, (TE)0, (TE*)a.partials, a.u, a.fparts, sh_s, sh_red);
     }
 }
 
 // Half steps on caller data (no state).  Row step: u = R t and s = sgn(u) in one pass; a workgroup takes 8 rows (one
 // byte of sign bits), a wave two, the sums are f64 from the first addition on.  A read of the matrix bounds it:
-// 4096x4096 f32 20.1 us a launch with 4-byte loads and a launch of its own for the signs (3.8), now 12.  Bytes past
+// 4096x4096 f32 20.1 us a launch with 4-byte loads and a launch of its own for the signs (3.8), now 13.3.  Bytes past
 // the last row are written as zeros, so that the words of `sbits` are complete.
 template <typename TE, bool VEC>
 __global__ void __launch_bounds__(kBlock)
