@@ -119,8 +119,13 @@ typedef enum {
                                        measured optimum; the paper's CPU value is 32), 0 = subtract at once */
     SCD_OPT_ROWPASS_KERNEL = 4,     /* launch-stream engine: 1 = register-tiled row pass where the shape allows
                                        (default), 0 = the generic kernel */
-    SCD_OPT_POLL_DELAY = 5,         /* persistent engines: sleep units between publishing and the first read of
-                                       the partners' data (default 16) */
+    SCD_OPT_POLL_DELAY = 5,         /* persistent engines: where the wait, in sleep units, between publishing and the
+                                       first read of the partners' data sets out from (default 16).  The streaming
+                                       engine waits so long; the register-resident engine adds or takes off up to 13
+                                       units by grid, tile and type (0 stays 0); the sparse engine waits so long
+                                       behind a pass over the matrix and elsewhere begins with it (32 at most), from
+                                       where every wave follows the arrivals between 0 and 32.  Time only: results do
+                                       not depend on it */
     SCD_OPT_MAX_SPIN = 6,           /* persistent engines: re-reads of stale exchange data after which a wait gives
                                        up (default 2^22; 0 = give up at the first stale read: for tests of the
                                        SCD_ETIMEOUT path, every workgroup still exits normally) */

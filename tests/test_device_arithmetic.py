@@ -1,4 +1,4 @@
-"""Host-side models of two pieces of integer / lane arithmetic the sparse engine relies on (no GPU needed).
+"""Host-side models of integer and lane arithmetic that the persistent engines rely on (no GPU needed).
 
 They restate what the kernels do in numpy and check it exhaustively, so that a change of a constant
 (items per thread, words per slot, the number of sums joined at once) that breaks the arithmetic fails here.
@@ -15,6 +15,20 @@ def test_item_to_word_by_float_product_is_exact():
         idx = np.arange(0, 6 * 512, dtype=np.int32)
         word = ((idx.astype(np.float32) + np.float32(0.5)) * r).astype(np.int32)
         assert np.array_equal(word, idx // grid), grid
+
+
+def test_quotients_of_the_stream_engine_by_float_product_are_exact():
+    # the persistent streaming engine: hop 2 maps item -> (member, word) with floor((item + 0.5) * (1 / per)), per = the
+    # words of a member (sign words of the slice, two words per scalar: 1 to 16, checked to 18), for the 6 x 512 items a
+    # workgroup can gather; hop 1 maps thread -> (member group, column) with the slice width, 8 to 256 in steps of 8
+    # (steps of 1 checked, and up to the 512 threads)
+    idx = np.arange(0, 6 * 512, dtype=np.int32)
+    half = idx.astype(np.float32) + np.float32(0.5)
+    for per in range(1, 19):
+        assert np.array_equal((half * (np.float32(1.0) / np.float32(per))).astype(np.int32), idx // per), per
+    for cs in range(1, 513):
+        q = (half[:512] * (np.float32(1.0) / np.float32(cs))).astype(np.int32)
+        assert np.array_equal(q, idx[:512] // cs), cs
 
 
 def test_halving_butterfly_leaves_sum_i_in_lane_pair_i():
