@@ -101,6 +101,7 @@ struct scd_ctx {
     ResidentResult* res_dev = nullptr;
     ResidentResult* res_pin = nullptr;
     uint32_t seq_u = 0, seq_v = 0;
+    double fro = 0.0;               // ||R||_F when the remainder was last given (terms only lower it)
     // sparse engine
     bool sparse = false;
     bool rt_stale = true;           // RT does not mirror R (R was changed by the launch-stream kernels)
@@ -734,7 +735,8 @@ int run_resident(scd_ctx* c, int64_t n)
     a.w_target = c->hs.k + n;
     a.max_iters = c->hs.max_iters;
     a.max_spin = (int32_t)c->opt[SCD_OPT_MAX_SPIN];
-    resident_poll_delays(c->dt, c->dims, (int)c->opt[SCD_OPT_POLL_DELAY], &a.poll_delay, &a.poll_delay_v);
+    a.fro = c->fro;
+    resident_poll_delays(c->dt, c->dims, c->fro, (int)c->opt[SCD_OPT_POLL_DELAY], &a.poll_delay, &a.poll_delay_v);
     a.seq_u = c->seq_u;
     a.seq_v = c->seq_v;
     a.xbuf = c->xbuf;
@@ -890,6 +892,7 @@ int scd_create(scd_ctx** out, const void* A, scd_dtype dt, int order, const int6
     double f0 = 0.0;
     CHIP(hipMemcpy(&f0, c->trace, sizeof(double), hipMemcpyDeviceToHost));
     if (!isfinite(f0)) return fail(SCD_ENONFINITE);
+    c->fro = f0;
     *out = c;
     return SCD_OK;
 #undef CTRY
@@ -1079,6 +1082,7 @@ int scd_set_remainder(scd_ctx* c, const void* R_in)
     double f = 0.0;
     HIP_TRY(hipMemcpy(&f, c->trace + c->hs.k, sizeof(double), hipMemcpyDeviceToHost));
     if (!isfinite(f)) return SCD_ENONFINITE;
+    c->fro = f;
     return SCD_OK;
 }
 

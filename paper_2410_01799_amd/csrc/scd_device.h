@@ -137,12 +137,13 @@ struct ResidentArgs {
     int32_t* iters;
     double* trace;
     int32_t mw, nw;
+    double fro;              // a bound on ||R||_F (host side only: chooses the type of the sums)
     ResidentResult* res;
 };
 
 bool resident_supported(scd_dtype dt, int order, const int64_t* dims);
 int resident_workgroups(scd_dtype dt, const int64_t* dims);  // workgroups of the launch for a supported shape
-void resident_poll_delays(scd_dtype dt, const int64_t* dims, int delay, int32_t* rows, int32_t* cols);  // of the two exchanges
+void resident_poll_delays(scd_dtype dt, const int64_t* dims, double fro, int delay, int32_t* rows, int32_t* cols);  // of the two exchanges
 hipError_t launch_resident(const ResidentArgs& a, scd_dtype dt, hipStream_t st);
 
 // Sparse engine (scd_sparse.hip): cached products updated from the flipped signs only; keeps R and its

@@ -834,12 +834,13 @@ int resident_workgroups(scd_dtype dt, const int64_t* dims)
 // f32 words where one rounding a workgroup is no more than those f32 sums cost, that is from two of them on each side
 // (emulated, rms error of the row and column sums against f64, launch stream / here: 257x255 4.5e-8, 3.0e-8 / 2.6e-8,
 // 2.7e-8; 1501x999 7.3e-8, 5.1e-8 / 2.4e-8, 2.5e-8; 4095x4093 1.5e-7, 7.8e-8 / 2.6e-8, 2.5e-8; with f32 sums inside the
-// workgroup too the column sums of 1501x999 are off by 7.9e-8).  Smaller ones exchange f64.
+// workgroup too the column sums of 1501x999 are off by 7.9e-8).  Smaller ones exchange f64, and those whose sums of up
+// to 256 entries a workgroup could pass the largest f32: they are at most 16 ||R||_F.
 enum class ResSums { plain, wide_inside, wide };
-static ResSums resident_sums(scd_dtype dt, int64_t m, int64_t n)
+static ResSums resident_sums(scd_dtype dt, int64_t m, int64_t n, double fro)
 {
     if (dt == SCD_F32 && n % ResVec<float>::N == 0) return ResSums::plain;
-    return dt == SCD_F32 && m > 256 && n > 128 ? ResSums::wide_inside : ResSums::wide;
+    return dt == SCD_F32 && m > 256 && n > 128 && fro < 1e36 ? ResSums::wide_inside : ResSums::wide;
 }
 
 // Sleep units between publishing and the first read, per exchange, from the option's value (default 16).  A read
@@ -852,12 +853,12 @@ static ResSums resident_sums(scd_dtype dt, int64_t m, int64_t n)
 // and 4.81; 16 x 16 at 22 / 18 6.78 (1501x999) and 6.93 (2048^2), at 18 / 14 7.03 and 7.24, at 26 / 22 6.95 and 7.09; with
 // column slots of 256 values at 26 / 22 7.68 (2048x4096), at 22 / 18 8.56.  f64 sums inside a workgroup make the slots of
 // tall blocks later: three units more, 5.50 instead of 5.99 (3000x1999) and 6.77 instead of 7.40 (4095x4093).
-void resident_poll_delays(scd_dtype dt, const int64_t* dims, int delay, int32_t* rows, int32_t* cols)
+void resident_poll_delays(scd_dtype dt, const int64_t* dims, double fro, int delay, int32_t* rows, int32_t* cols)
 {
     int p = 16, tr = 8, tc = 16;
     (void)resident_shape(dt, dims[0], dims[1], &p, &tr, &tc);
     int u = delay - 6, v = delay - 6;
-    const ResSums sums = resident_sums(dt, dims[0], dims[1]);
+    const ResSums sums = resident_sums(dt, dims[0], dims[1], fro);
     const bool wide = sums == ResSums::wide;  // twice the words
     if (sums == ResSums::wide_inside && p > 8 && tr > 2) delay = delay ? delay + 3 : 0;
     if (p > 8 && !wide) u = delay + 2, v = tc == 16 ? delay - 2 : delay - 8;
@@ -890,7 +891,7 @@ static hipError_t launch_resident_t(const ResidentArgs& a, hipStream_t st)
     const bool padded = (int64_t)P * 32 * TR != a.m || (int64_t)P * 16 * TC != a.n;
     if constexpr (sizeof(TE) == 4) {
         // (rows that are no 16-byte steps never fit the grid exactly)
-        const ResSums sums = resident_sums(SCD_F32, a.m, a.n);
+        const ResSums sums = resident_sums(SCD_F32, a.m, a.n, a.fro);
         if (sums == ResSums::wide_inside) return launch_resident_k<TE, double, TE, TR, TC, P, true>(a, st);
         if (sums == ResSums::wide) return launch_resident_k<TE, double, double, TR, TC, P, true>(a, st);
     }

@@ -101,6 +101,22 @@ def test_resident_sums_of_rows_without_16_byte_steps(scd, oracle, m, n):
         assert float(res["c"][0]) == pytest.approx(ref["c"] / (m * n), rel=2.0 ** -23)
 
 
+def test_resident_sums_near_the_largest_f32(scd, oracle):
+    # all entries about 1e37: the sum of a workgroup's 64 columns is beyond f32, the c of a term is not
+    A = (1e37 * (1.0 + 0.01 * gauss((300, 261), 7))).astype(np.float32)
+    t0 = oracle.rng_signs(3, 0, 1, 261)
+    ref = oracle.greedy_signed_cut(A.astype(np.float64), t0)
+    for first in (A, A / np.float32(1e20)):    # given at the start, and later
+        with scd.ScdContext(torch.from_numpy(first).cuda(), 1, 3, options=RESIDENT) as ctx:
+            if first is not A:
+                ctx.set_remainder(torch.from_numpy(A).cuda())
+            ctx.run(1)
+            assert ctx.engine()["engine"] == 1
+            res = ctx.results()
+        assert np.array_equal(to_np_bits(res["signs"][0])[0], ref["s"]) and np.array_equal(to_np_bits(res["signs"][1])[0], ref["t"])
+        assert float(res["c"][0]) == pytest.approx(ref["c"] / A.size, rel=2.0 ** -23)
+
+
 # f64: half the values a thread holds and two words a value, so its own tiles (each of them once, the largest on every
 # grid) and its own limit, 4096x2048 or 2048x4096 values; odd row lengths end 16-byte reads of two values
 F64_SHAPES = [(1, 4), (7, 5), (64, 63), (128, 64), (256, 512), (600, 400), (1024, 1024), (1501, 999), (100, 2048), (1024, 2048),
