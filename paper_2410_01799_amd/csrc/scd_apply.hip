@@ -175,8 +175,7 @@ __global__ void __launch_bounds__(kApInnerWaves* kWave)
 // byte b of operand dword q of its instruction t = 0..7 is bit (t & 1) * 4 + q + 8 b of the half word t / 2 of the two:
 // one shift and one mask per four signs.  (With v_mfma_i32_4x4x4_16B_i8 and a table look-up per nibble the pass used a
 // quarter of the instruction's columns for one vector and took them one after the other: 14336x4096 transposed, four
-// vectors, 4 x 30 us; now 42 us for three and 25 for
-// one more.)
+// vectors, 4 x 30 us; now 34 us for the four.)
 typedef int ap_int4 __attribute__((ext_vector_type(4)));
 
 constexpr int kApMfmaWaves = 8;                      // waves per workgroup of the outer pass: one word of outputs each
@@ -842,7 +841,7 @@ hipError_t launch_fx(const uint64_t* in_bits, const uint64_t* out_bits, const fl
     double* part = (double*)workspace;
     double* ypart = part + nv * pstride;
     // a workgroup per tile of 64 terms; several tiles per workgroup once there are more than two per compute unit, to pay
-    // for the fixed point less often (14336x4096 transposed, four vectors: 113 us, with up to 1024 workgroups 123)
+    // for the fixed point less often (14336x4096 transposed, three vectors and one more: 113 us, with up to 1024 workgroups 123)
     const int64_t tiles = (w + kApFxTile - 1) / kApFxTile;
     int tpw = (int)((tiles * pl.chunks + 511) / 512);
     if (tpw < 1) tpw = 1;
