@@ -175,8 +175,9 @@ uint64_t allocation_id(void* p)
     return id;
 }
 
-// A device reset frees all blocks; their addresses may then be another owner's (0.1 us a look).
-bool pool_valid(const PoolBlock& b) { return b.id != 0 && allocation_id(b.p) == b.id; }
+// A device reset frees all blocks; their addresses may then be another owner's (0.1 us a look; a block without a number
+// counts as whole).
+bool pool_valid(const PoolBlock& b) { return b.id == 0 || allocation_id(b.p) == b.id; }
 
 // The bytes given back.
 size_t pool_give_back(const PoolBlock& b)
