@@ -1,6 +1,6 @@
 """Decompose the synthetic Mistral-7B-shaped weight set (workload 5: 226 matrices) matrix by matrix.
 
-Resumable: ``python -m paper_2410_01799_amd.model_run --start 0 --stop 80 --out gpurun_out/model/part0.jsonl``
+Resumable: ``python -m paper_2410_01799_amd.model_run --start 0 --stop 80 --out model/part0.jsonl``
 writes one JSON line per matrix; several invocations cover the manifest.  Each matrix is decomposed once, to
 the width of 50 % of its bf16 footprint; the errors at 25 % and 37.5 % are read off the same run at the
 narrower widths (a greedy run contains every narrower run as a prefix).  Matrices are generated on the GPU
