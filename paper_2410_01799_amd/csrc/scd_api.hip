@@ -1502,9 +1502,11 @@ int check_tensor_args(const void* A, scd_dtype dt, int order, const int64_t* dim
 
 namespace {
 
-// The sweeps are enqueued blindly, about as many as the terms so far took; launches past the end return at once.
+// Everything is enqueued blindly; launches past the end return at once.  `resident`: two launches per term, its cut on the
+// register-resident engine and the refit (SCD_ETIMEOUT where the workgroups did not all get a compute unit); else three per
+// sweep, about as many sweeps as the terms so far took.
 int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uint64_t seed, int32_t max_iters, hipStream_t st, uint64_t* S,
-               uint64_t* T, void* cvec, double* fro_trace, int32_t* iters)
+               uint64_t* T, void* cvec, double* fro_trace, int32_t* iters, bool resident)
 {
     const int64_t mw = words_for(m), nw = words_for(n);
     const int nsq = 256;
@@ -1513,7 +1515,8 @@ int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uin
         double scal[2];
     };
     // one block: every array of doubles or words, then the iteration counts and the state
-    const size_t words = (size_t)(mw + nw + 2 * nw + w * w + 3 * w + nsq + 2);
+    const size_t xbuf_words = resident ? (size_t)4 * kResGrid * kResGrid * kResSlotWords : 0;
+    const size_t words = (size_t)(mw + nw + 2 * nw + w * w + 3 * w + nsq + 2) + xbuf_words + (sizeof(ResidentResult) + 7) / 8;
     const size_t bytes = words * 8 + (((size_t)w * 4 + 15) & ~(size_t)15) + sizeof(LsqState);
     void* dev = nullptr;
     Pinned* pin = nullptr;
@@ -1566,6 +1569,8 @@ int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uin
     a.bvec = (double*)take(w);
     double* sq = (double*)take(nsq);
     double* scal = (double*)take(2);
+    ResidentResult* res = (ResidentResult*)take((sizeof(ResidentResult) + 7) / 8);
+    uint64_t* xbuf = take((int64_t)xbuf_words);
     a.trace = fro_trace;
     a.iters = (int32_t*)p;
     a.st = (LsqState*)((char*)p + (((size_t)w * 4 + 15) & ~(size_t)15));
@@ -1581,12 +1586,50 @@ int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uin
     pin->state.c_prev = -INFINITY;
     LM(hipMemcpyAsync(fro_trace, pin->scal, 8, hipMemcpyHostToDevice, st));
     LM(hipMemcpyAsync(a.st, &pin->state, sizeof(LsqState), hipMemcpyHostToDevice, st));
-    LM(launch_rng(seed, 0, 1u, n, a.t, st));
+    if (resident) {
+        LM(hipMemsetAsync(res, 0, sizeof(ResidentResult) + xbuf_words * 8, st));
+    } else {
+        LM(launch_rng(seed, 0, 1u, n, a.t, st));
+    }
     LM(hipStreamSynchronize(st));  // (the pinned block receives the state from here on)
+    if (resident) {
+        const int64_t dims[2] = {m, n};
+        ResidentArgs r;
+        memset(&r, 0, sizeof(r));
+        r.m = m;
+        r.n = n;
+        r.seed = seed;
+        r.max_iters = max_iters;
+        r.max_spin = 1 << 22;
+        resident_poll_delays(SCD_F64, dims, 0.0, 16, &r.poll_delay, &r.poll_delay_v);
+        r.xbuf = xbuf;
+        r.S = S;
+        r.T = T;
+        r.iters = a.iters;
+        r.mw = (int32_t)mw;
+        r.nw = (int32_t)nw;
+        r.res = res;
+        r.A = A;
+        r.a_f32 = dt == SCD_F32 ? 1 : 0;
+        r.coef = a.c;
+        r.lsq = a.st;
+        SlotLease lease;
+        lease.acquire(resident_workgroups(SCD_F64, dims), device_cus());
+        for (int64_t k = 0; k < w && !pin->state.done;) {
+            const int64_t batch = w - k < 64 ? w - k : 64;  // (a look at the state now and then: a singular system ends the call)
+            for (int64_t b = 0; b < batch; ++b) {
+                LM(launch_resident_lsq(r, st));
+                LM(launch_lsq_term(a, res, st));
+            }
+            k += batch;
+            LM(hipMemcpyAsync(&pin->state, a.st, sizeof(LsqState), hipMemcpyDeviceToHost, st));
+            LM(hipStreamSynchronize(st));
+        }
+    }
     double per_term = 12.0;
     int64_t swept = 0;
     const double bound = ((double)w + 1.0) * ((double)max_iters + 1.0);
-    for (;;) {
+    while (!resident) {
         const double want = per_term * (double)(w - pin->state.k);
         const int batch = want < 4.0 ? 4 : (want > 96.0 ? 96 : (int)want);
         for (int b = 0; b < batch; ++b) LM(launch_lsq_sweep(a, dt, st));
@@ -1598,6 +1641,7 @@ int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uin
         if (pin->state.k > 0) per_term = (double)swept / (double)pin->state.k;
     }
     const LsqState fin = pin->state;
+    if (fin.status == 3) return cleanup(SCD_ETIMEOUT);
     if (fin.status == 2) return cleanup(SCD_ENONFINITE);
     if (fin.status == 1) return cleanup(SCD_ESINGULAR);
     LM(launch_lsq_cast(a.c, w, dt, cvec, st));
@@ -1620,8 +1664,19 @@ int scd_lsq_decompose_tensor(const void* A, scd_dtype dt, int order, const int64
     if (w > SCD_LSQ_MAX_WIDTH || (w > 0 && (!signs || !cvec))) return SCD_EINVAL;
     for (int i = 0; i < order; ++i)
         if (w > 0 && !signs[i]) return SCD_EINVAL;
-    if (order == 2 && w > 0 && lsq_matrix_supported(dt, dims[0], dims[1]))
-        return lsq_matrix(A, dt, dims[0], dims[1], w, seed, max_iters, (hipStream_t)stream, signs[0], signs[1], cvec, fro_trace, iters);
+    if (order == 2 && w > 0) {
+        // The register-resident engine takes every matrix whose f64 remainder fits the register files; should its
+        // workgroups not find room beside others' work, the launches that need no such thing start again.  Us a call, three
+        // launches per sweep / here: 64x64 f32 to 16 terms 1680 / 720, 100x900 f32 to 32 2170 / 1280, 1024x1024 f32 to 32
+        // 15100 / 5000, 2048x2048 f64 to 16 26000 / 5570, 4096x2048 f32 to 8 9380 / 2360, 1024x1024 f32 to 512 474000 /
+        // 244000; slower on none that was tried.
+        if (resident_supported(SCD_F64, 2, dims) && resident_workgroups(SCD_F64, dims) <= device_cus()) {
+            const int rc = lsq_matrix(A, dt, dims[0], dims[1], w, seed, max_iters, (hipStream_t)stream, signs[0], signs[1], cvec, fro_trace, iters, true);
+            if (rc != SCD_ETIMEOUT) return rc;
+        }
+        if (lsq_matrix_supported(dt, dims[0], dims[1]))
+            return lsq_matrix(A, dt, dims[0], dims[1], w, seed, max_iters, (hipStream_t)stream, signs[0], signs[1], cvec, fro_trace, iters, false);
+    }
     hipStream_t st = (hipStream_t)stream;
     const int64_t wl = w > 0 ? w : 1;
     const int nsq = 256;

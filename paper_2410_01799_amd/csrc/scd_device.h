@@ -121,6 +121,17 @@ struct ResidentResult {
     int64_t ticks[6];      // sparse engine, profile mode: 100 MHz ticks of workgroup 0 per phase
 };
 
+// Least squares decomposition of a matrix: position of the loop on the device.
+struct LsqState {
+    int64_t k;       // terms complete
+    double c_prev;   // cut value of the previous sweep of the current term (-inf before the first); of the term just cut
+    int32_t j;       // sweeps of the current term
+    int32_t done;    // all terms complete, or status set
+    int32_t status;  // 1: normal equations singular, 2: a cut value is not finite, 3: a bounded wait ran out
+    int32_t warn;    // some term ended on max_iters
+    uint32_t seq_u, seq_v;  // exchange sequence numbers used so far (register-resident cuts)
+};
+
 struct ResidentArgs {
     void* R;
     int64_t m, n;
@@ -139,12 +150,18 @@ struct ResidentArgs {
     int32_t mw, nw;
     double fro;              // a bound on ||R||_F (host side only: chooses the type of the sums)
     ResidentResult* res;
+    // least squares form: R, k_start, w_target, seq_u, seq_v, c and trace are not used
+    const void* A;
+    int32_t a_f32;           // A is f32
+    const double* coef;      // coefficients of the terms so far
+    LsqState* lsq;
 };
 
 bool resident_supported(scd_dtype dt, int order, const int64_t* dims);
 int resident_workgroups(scd_dtype dt, const int64_t* dims);  // workgroups of the launch for a supported shape
 void resident_poll_delays(scd_dtype dt, const int64_t* dims, double fro, int delay, int32_t* rows, int32_t* cols);  // of the two exchanges
 hipError_t launch_resident(const ResidentArgs& a, scd_dtype dt, hipStream_t st);
+hipError_t launch_resident_lsq(const ResidentArgs& a, hipStream_t st);  // shapes that resident_supported takes in f64
 
 // Sparse engine (scd_sparse.hip): cached products updated from the flipped signs only; keeps R and its
 // transpose in HBM.
@@ -249,15 +266,7 @@ hipError_t launch_scalars_update(void* r, scd_dtype dt, int64_t total, int64_t q
 hipError_t launch_lsq_solve(double* L, int64_t ld, int64_t k, const double* g, double diag, const double* bvec, double* yv,
                             double* c, double fro0sq, double* trace_out, int* status, hipStream_t st);
 
-// Matrices: position of the loop on the device and the arguments of a sweep's three launches.
-struct LsqState {
-    int64_t k;       // terms complete
-    double c_prev;   // cut value of the previous sweep of the current term (-inf before the first)
-    int32_t j;       // sweeps of the current term
-    int32_t done;    // all terms complete, or status set
-    int32_t status;  // 1: normal equations singular, 2: a cut value is not finite
-    int32_t warn;    // some term ended on max_iters
-};
+// Matrices: the arguments of a sweep's three launches, or of the launch that ends a term.
 struct LsqMatArgs {
     const void* A;
     int64_t m, n, w;
@@ -280,6 +289,7 @@ struct LsqMatArgs {
 };
 bool lsq_matrix_supported(scd_dtype dt, int64_t m, int64_t n);
 hipError_t launch_lsq_sweep(const LsqMatArgs& a, scd_dtype dt, hipStream_t st);
+hipError_t launch_lsq_term(const LsqMatArgs& a, const ResidentResult* res, hipStream_t st);
 
 // ---- expansion of the packed factors (scd_expand.hip)
 hipError_t launch_expand(const uint64_t* S, const uint64_t* T, const void* c, scd_dtype dt, int64_t m,

@@ -8,8 +8,10 @@
 // comes from the bitsets, and the correction is a signed sum of k scalars per entry.  The normal equations
 // (Section 3.3) use the Gram matrix G_ij = <s_i,s_j><t_i,t_j>, again from popcounts, kept as a Cholesky
 // factor that grows by one row per term; b_j = <s_j, A t_j> falls out of the last half step of term j.
-// Everything here is f64; the kernels are small and latency-bound (matrices of up to 64 words a side: three launches per
-// sweep and no host in the loop; others, and tensors: about ten and a read-back).
+// Everything here is f64; the kernels are small and latency-bound.  Matrices whose f64 remainder fits the register files
+// (up to 4096x2048 or 2048x4096): two launches per term, the cut on the register-resident engine (scd_resident_lsq.hip)
+// and lsq_term_kernel.  Others of up to 64 words a side: three launches per sweep and no host in the loop; larger ones, and
+// tensors: about ten and a read-back.
 #include "scd_device.h"
 #include "scd_rng.h"
 
@@ -333,7 +335,7 @@ __global__ void __launch_bounds__(kLqThreads)
 }
 
 // =================================================================================================
-// Matrices of up to kLqMaxWords words a side: a sweep (both half steps of Algorithm 4 on the implicit remainder, the
+// Matrices of up to kLqMaxWords words a side that the register-resident engine does not take: a sweep (both half steps of Algorithm 4 on the implicit remainder, the
 // stop test and, at the end of a term, the refit) is three launches that the host enqueues blindly, many sweeps
 // ahead; the position of the loop lives on the device.  A half step is one launch because a workgroup owns one word (64 rows
 // or columns) from the entries of A to the sign bits: it forms the inner products with the earlier terms, the f64 sums
@@ -599,6 +601,196 @@ __global__ void __launch_bounds__(kLqThreads) lsq_next_kernel(LsqMatArgs a)
     if (tid < nw) a.t[tid] = rng_word_masked(a.seed, (uint64_t)k + 1, 1u, tid, a.n);
 }
 
+// Few terms: the refit of lq_refit by one wave that holds two unknowns a lane, step for step (the same additions in the
+// same order), with the factor in LDS: no barrier and no trip to memory per unknown.
+constexpr int kLqSmall = 88;  // most terms before the new one; their factor's triangle takes 31 KB
+static_assert(kLqSmall <= 2 * kWave && kLqSmall <= 6 * kLqWaves, "unknowns of a lane, terms of a wave");
+struct LqSmallShared {
+    double e[kLqSmall];                           // Gram row of the new term
+    double L[kLqSmall * (kLqSmall + 1) / 2];      // rows of the factor, packed
+};
+__device__ __forceinline__ double lq_lane(double v, int l)
+{
+    const int lo = __builtin_amdgcn_readlane(__double2loint(v), l), hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
+    return __hiloint2double(hi, lo);
+}
+// Wave 0.  yv, bvec: the lane's entries; b: of the new term.
+__device__ bool lq_refit_small(const LqSmallShared& sm, double* __restrict__ L, int64_t ld, int k, double diag, double b, const double (&yl)[2],
+                               const double (&bl)[2], double* __restrict__ yv, double* __restrict__ c, double* cb_out)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    double x[2], d[2], col[2];
+    int at[2];  // of the lane's rows
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int q = lane + i * kWave;
+        at[i] = q * (q + 1) / 2;
+        x[i] = q < k ? sm.e[q] : 0.0;
+        d[i] = q < k ? sm.L[at[i] + q] : 1.0;
+        col[i] = q < k ? sm.L[at[i]] : 0.0;
+    }
+    // ---- forward substitution L row = g
+    for (int r = 0; r < k; ++r) {
+        const int i0 = r >> 6;
+        const double xr = lq_lane(i0 ? x[1] / d[1] : x[0] / d[0], r & 63);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int q = lane + i * kWave;
+            const double cur = col[i];
+            col[i] = q < k && q > r ? sm.L[at[i] + r + 1] : 0.0;
+            x[i] = q > r ? __builtin_fma(-cur, xr, x[i]) : (q == r ? xr : x[i]);
+        }
+    }
+    double s2 = 0.0, sy = 0.0;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int q = lane + i * kWave;
+        if (q < k) L[k * ld + q] = x[i];
+        s2 += lq_wave_sum(q < k ? x[i] * x[i] : 0.0);
+        sy += lq_wave_sum(q < k ? x[i] * yl[i] : 0.0);
+    }
+    const double d2 = diag - s2;
+    if (!(d2 > 1e-9 * diag)) return false;
+    const double lkk = sqrt(d2), yk = (b - sy) / lkk;
+    // ---- back substitution L^T c = y
+    const double ck = yk / lkk;
+    double cb = 0.0;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int q = lane + i * kWave;
+        x[i] = q < k ? __builtin_fma(-x[i], ck, yl[i]) : 0.0;
+        col[i] = q < k ? sm.L[(k - 1) * k / 2 + q] : 0.0;
+    }
+    for (int r = k - 1; r >= 0; --r) {
+        const int i0 = r >> 6;
+        const double xr = lq_lane(i0 ? x[1] / d[1] : x[0] / d[0], r & 63);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int q = lane + i * kWave;
+            const double cur = col[i];
+            col[i] = q < r ? sm.L[(r - 1) * r / 2 + q] : 0.0;
+            x[i] = q < r ? __builtin_fma(-cur, xr, x[i]) : (q == r ? xr : x[i]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int q = lane + i * kWave;
+        if (q < k) c[q] = x[i];
+        cb += lq_wave_sum(q < k ? x[i] * bl[i] : 0.0);
+    }
+    if (lane == 0) {
+        L[k * ld + k] = lkk;
+        yv[k] = yk;
+        c[k] = ck;
+    }
+    *cb_out = cb + ck * b;
+    return true;
+}
+
+// End of a term whose cut the register-resident engine has found (its sign vectors are rows k of S and T, its cut value
+// <s, R t> in the state): refit of all coefficients.  With the remainder R = A - sum c_j s_j t_j^T,
+// <s_k, A t_k> = <s_k, R t_k> + sum_j c_j <s_j, s_k> <t_j, t_k>.  One workgroup, bound by its trips to memory and the chain
+// of the two substitutions: with few terms everything is requested at once and one wave substitutes
+// (1024x1024, mean over the first 32 terms: 12.6 us, with lq_dots and lq_refit 22.3).
+__global__ void __launch_bounds__(kLqThreads) lsq_term_kernel(LsqMatArgs a, const ResidentResult* __restrict__ res)
+{
+    __shared__ union {
+        LqShared sh;
+        LqSmallShared sm;
+    } u;
+    LqShared& sh = u.sh;
+    LsqState* st = a.st;
+    if (st->done) return;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    const int64_t k = st->k;
+    const double cut = st->c_prev;
+    const bool gave_up = res->err != 0;
+    if (gave_up || !(fabs(cut) < INFINITY)) {
+        __syncthreads();  // (all waves have read the state)
+        if (tid == 0) {
+            st->status = gave_up ? 3 : 2;
+            st->done = 1;
+        }
+        return;
+    }
+    const int mw = (int)((a.m + 63) / 64), nw = (int)((a.n + 63) / 64);
+    double cb = 0.0;
+    bool ok;
+    if (k <= kLqSmall) {
+        // a wave takes terms wv, wv + 16, .. : their inner products with the new one and their rows of the factor
+        constexpr int NT = (kLqSmall + kLqWaves - 1) / kLqWaves;
+        const int kk = (int)k;
+        const int pt = lane < nw ? lane : 0, ps = lane < mw ? lane : 0;
+        const uint64_t vt = a.T[k * nw + pt], vs = a.S[k * mw + ps];
+        uint64_t tw[NT], sw[NT];
+        double row[NT][2], yl[2], bl[2], cl[2];
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            const int j = wv + i * kLqWaves, jc = j < kk ? j : kk;  // (the new term's words stand for what is past the end)
+            tw[i] = a.T[(int64_t)jc * nw + pt];
+            sw[i] = a.S[(int64_t)jc * mw + ps];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) row[i][h] = j < kk && lane + h * kWave <= j ? a.L[j * a.w + lane + h * kWave] : 0.0;
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int q = lane + h * kWave;
+            yl[h] = wv == 0 && q < kk ? a.yv[q] : 0.0;
+            bl[h] = wv == 0 && q < kk ? a.bvec[q] : 0.0;
+            cl[h] = wv == 0 && q < kk ? a.c[q] : 0.0;
+        }
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            const int j = wv + i * kLqWaves;
+            int ct = lane < nw ? __popcll(tw[i] ^ vt) : 0, cs = lane < mw ? __popcll(sw[i] ^ vs) : 0;
+            for (int off = 32; off > 0; off >>= 1) {
+                ct += __shfl_xor(ct, off, kWave);
+                cs += __shfl_xor(cs, off, kWave);
+            }
+            if (j < kk) {
+                if (lane == 0) u.sm.e[j] = (double)(a.n - 2 * (int64_t)ct) * (double)(a.m - 2 * (int64_t)cs);
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    if (lane + h * kWave <= j) u.sm.L[j * (j + 1) / 2 + lane + h * kWave] = row[i][h];
+            }
+        }
+        __syncthreads();
+        if (wv != 0) return;
+        double b = 0.0;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) b += lq_wave_sum(lane + h * kWave < kk ? cl[h] * u.sm.e[lane + h * kWave] : 0.0);
+        b += cut;
+        if (lane == 0) a.bvec[k] = b;
+        ok = lq_refit_small(u.sm, a.L, a.w, kk, (double)a.m * (double)a.n, b, yl, bl, a.yv, a.c, &cb);
+    } else {
+        if (tid < nw) sh.vec[tid] = a.T[k * nw + tid];
+        __syncthreads();
+        lq_dots(a.T, k, nw, a.n, sh.vec, nullptr, sh.e);
+        __syncthreads();
+        if (tid < mw) sh.vec[tid] = a.S[k * mw + tid];
+        __syncthreads();
+        lq_dots(a.S, k, mw, a.m, sh.vec, sh.e, sh.e);  // (each element is read and written by the same lane)
+        __syncthreads();
+        double b = 0.0;
+        for (int64_t j = tid; j < k; j += kLqThreads) b = __builtin_fma(a.c[j], sh.e[j], b);
+        b = cut + lq_block_sum(b, sh.red);
+        if (tid == 0) a.bvec[k] = b;
+        __syncthreads();
+        ok = lq_refit(a.L, a.w, k, sh.e, (double)a.m * (double)a.n, a.bvec, a.yv, a.c, sh.red, &sh.part[0][0], &cb);
+    }
+    if (tid == 0) {
+        if (!ok) {
+            st->status = 1;
+            st->done = 1;
+        } else {
+            const double f2 = a.fro0sq - cb;
+            a.trace[k + 1] = sqrt(f2 > 0.0 ? f2 : 0.0);
+            st->k = k + 1;
+            if (k + 1 >= a.w) st->done = 1;
+        }
+    }
+}
+
 }  // namespace
 
 hipError_t launch_lsq_dots(const uint64_t* bits, int64_t k, int64_t nw, int64_t len, const uint64_t* vec, const double* coef,
@@ -720,6 +912,12 @@ hipError_t launch_lsq_sweep(const LsqMatArgs& a, scd_dtype dt, hipStream_t st)
     const bool vec = a.n % ve == 0 && ((uintptr_t)a.A & 15u) == 0;  // every row starts on a 16-byte boundary
     if (dt == SCD_F32) return vec ? lsq_sweep_t<float, true>(a, st) : lsq_sweep_t<float, false>(a, st);
     return vec ? lsq_sweep_t<double, true>(a, st) : lsq_sweep_t<double, false>(a, st);
+}
+
+hipError_t launch_lsq_term(const LsqMatArgs& a, const ResidentResult* res, hipStream_t st)
+{
+    hipLaunchKernelGGL(lsq_term_kernel, dim3(1), dim3(kLqThreads), 0, st, a, res);
+    return hipGetLastError();
 }
 
 }  // namespace scd

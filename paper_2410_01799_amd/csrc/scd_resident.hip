@@ -1,6 +1,5 @@
 // Probes of workgroup-to-workgroup exchange latency inside one persistent launch (measurement only).
-#include "scd_device.h"
-#include "scd_rng.h"
+#include "scd_resident_kernel.h"
 
 namespace scd {
 
@@ -90,730 +89,6 @@ hipError_t launch_exchange_probe(int which, int grid, uint64_t* buf, unsigned* c
     else
         hipLaunchKernelGGL(barrier_probe_kernel, dim3(grid), dim3(256), 0, st, counter, rounds, max_spin, err, out);
     return hipGetLastError();
-}
-
-// ---- helpers of the engine
-
-// Sum over the 64 lanes, the same bits in every lane, without LDS traffic (a chain of ds_bpermute would cost
-// an LDS round trip per step): distances 1, 2, 4, 8 by the data-parallel lane modes (4 = mirror of half a row
-// then reversed quads, 8 = mirror of a row then of half a row), 16 and 32 by the row-swap instructions of
-// gfx950 (swapping the odd rows of one copy with the even rows of another leaves the two partners of every
-// lane in the two results, in the same order for both partners).
-template <int C0, int C1>
-__device__ __forceinline__ double dpp_f64_res(double v)
-{
-    const long long b = __double_as_longlong(v);
-    int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xFFFFFFFFll), C0, 0xF, 0xF, true);
-    int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), C0, 0xF, 0xF, true);
-    if constexpr (C1 != 0) {
-        lo = __builtin_amdgcn_update_dpp(0, lo, C1, 0xF, 0xF, true);
-        hi = __builtin_amdgcn_update_dpp(0, hi, C1, 0xF, 0xF, true);
-    }
-    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
-template <int D>
-__device__ __forceinline__ double swap_sum_f64_res(double a)
-{
-    const unsigned long long b = (unsigned long long)__double_as_longlong(a);
-    const unsigned lo = (unsigned)b, hi = (unsigned)(b >> 32);
-    unsigned l0, l1, h0, h1;
-    if constexpr (D == 16) {
-        const auto rl = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-        const auto rh = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-        l0 = rl[0], l1 = rl[1], h0 = rh[0], h1 = rh[1];
-    } else {
-        const auto rl = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-        const auto rh = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-        l0 = rl[0], l1 = rl[1], h0 = rh[0], h1 = rh[1];
-    }
-    return __longlong_as_double((long long)(((unsigned long long)h0 << 32) | l0)) +
-           __longlong_as_double((long long)(((unsigned long long)h1 << 32) | l1));
-}
-__device__ __forceinline__ double wave_sum_res(double a)
-{
-    a += dpp_f64_res<0xB1, 0>(a);       // lane ^ 1
-    a += dpp_f64_res<0x4E, 0>(a);       // lane ^ 2
-    a += dpp_f64_res<0x141, 0x1B>(a);   // lane ^ 4
-    a += dpp_f64_res<0x140, 0x141>(a);  // lane ^ 8
-    a = swap_sum_f64_res<16>(a);
-    a = swap_sum_f64_res<32>(a);
-    return a;
-}
-
-
-// =================================================================================================
-// Register-resident engine.
-//
-// A 4096 x 4096 f32 remainder is 64 MiB; the 256 compute units of the chip hold 128 MiB of vector
-// registers.  Workgroup (pr, pc) of a 16 x 16 grid keeps block (pr, pc) of R in its registers for the
-// whole run, so an alternation of Algorithm 4 moves no matrix data at all: only 256 partial sums per
-// workgroup and phase travel through memory.
-//
-//   row phase   p_i = sum over the block's columns of +-R_il (signs t), published to the 16
-//               workgroups of the same block row; each adds the 16 partials in order -> u_i, s_i
-//   col phase   q_l = sum over the block's rows of +-R_il (signs s), published to the 16 workgroups
-//               of the same block column -> v_l, t_l, and this column block's share of c = sum |v_l|
-//
-// Exchange: value and sequence number travel in one 8-byte store (the datum is its own flag), read
-// back with loads that bypass the non-coherent caches; no counter, no fence.  Slots alternate by the
-// parity of the sequence number: a workgroup can only be one exchange ahead of the readers of its
-// slot, because finishing exchange e+1 needs data its readers publish after they have read e.
-// An alternation is bound by the latency of the two exchanges and by what lies between them on one workgroup per
-// compute unit (two waves per SIMD, so every vector instruction costs 8 cycles of the chain).  Measured at 4096x4096
-// (us per alternation): 6.33 with barriers that also join a predicate, full-width lane reductions (every lane ends
-// with every sum) and the stop test ahead of the column sums; 5.47 with one plain barrier per exchange, reductions
-// that halve the registers at each step, signs kept as factor bytes, scalar bases for the gathers and the test
-// behind the column sums; 5.40 with the poll delays of resident_poll_delays.  256x256: 3.9 -> 2.9, 1024x1024:
-// 4.4 -> 3.4, 2048x2048: 5.45 -> 4.65.
-//
-// f64 (TE = double): everything the exchanges carry and the tiles hold stays 64 bits wide, so a thread holds at most 64
-// values (matrices up to 4096x2048 or 2048x4096) and a published value is two tagged words, all lower halves of a slot
-// before all upper ones, so that a wave's loads stay contiguous.  The same chain with twice the words; measured in us per
-// alternation against the best of the other engines on the same matrix: 256x256 3.4 (9.4 persistent stream), 1024x1024
-// 4.8 (11.2), 1501x999 6.8 (19.4, launch stream), 1024x4096 7.5 (15.2), 2048x2048 6.9 (13.6), 4096x2048 8.0 (9.7,
-// sparse), 2048x4096 7.7 (9.9, sparse), 2000x3999 7.7 (65.9, launch stream).  The 64-value tiles on 16 x 16 workgroups
-// spill 28 to 56 bytes a thread.
-// The sum of the 16 column-block shares of c rides on the next row-phase exchange, so the test of
-// Algorithm 4 line 8 is taken one phase late: the row phase already done with the final t is then
-// dropped.  ||R||_F^2 after an update travels the same way (block row sums, then the total).
-// Every wait is bounded; on expiry all workgroups leave and the host reports an error.
-
-// word offset of the slot of workgroup `wg` for exchange `seq` of kind 0 (rows) or 1 (columns)
-__device__ __forceinline__ uint32_t res_slot_off(int kind, uint32_t seq, int wg)
-{
-    return (uint32_t)(((kind * 2 + (int)(seq & 1u)) * (kResGrid * kResGrid) + wg) * kResSlotWords);
-}
-__device__ __forceinline__ uint64_t* res_slot(const ResidentArgs& a, int kind, uint32_t seq, int wg)
-{
-    return a.xbuf + res_slot_off(kind, seq, wg);
-}
-__device__ __forceinline__ const char* res_slot_bytes(const ResidentArgs& a, int kind, uint32_t seq, int wg)
-{
-    return (const char*)(a.xbuf + res_slot_off(kind, seq, wg));
-}
-
-__device__ __forceinline__ double uniform_f64(double v)
-{
-    // the value is the same in every lane: keep it in scalar registers
-    const long long b = __double_as_longlong(v);
-    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)(b & 0xFFFFFFFFll));
-    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)((unsigned long long)b >> 32));
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
-// Tagged words per published sum: the value itself (f32), or its two halves, `apart` words from each other (f64).
-template <typename TX>
-constexpr int kResWords = (int)(sizeof(TX) / 4);
-
-__device__ __forceinline__ void res_publish(uint64_t* p, int apart, float v, uint32_t seq)
-{
-    (void)apart;
-    __hip_atomic_store(p, ((uint64_t)seq << 32) | (uint64_t)__float_as_uint(v), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void res_publish(uint64_t* p, int apart, double v, uint32_t seq)
-{
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    __hip_atomic_store(p, ((uint64_t)seq << 32) | (b & 0xFFFFFFFFull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(p + apart, ((uint64_t)seq << 32) | (b >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ __forceinline__ void res_publish_f64(uint64_t* p, double v, uint32_t seq)
-{
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    __hip_atomic_store(p, ((uint64_t)seq << 32) | (b & 0xFFFFFFFFull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(p + 1, ((uint64_t)seq << 32) | (b >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// H members' values of one element (one half of a group of 2H) plus NX / 2 piggybacked doubles of one
-// member (NX = 0, 2 or 4 more words; only what the phase at hand uses is published and read: every word is a
-// trip through the fabric), all loads in flight together.  If any word of the wave is still from an earlier
-// exchange, all are read again (re-reads are rare once the first read is delayed a little).  `base` is the same
-// for the whole workgroup and `off` (bytes) the same in every exchange: the loads take a scalar base and a 32-bit
-// lane offset, so that no 64-bit lane address is worked out between the wait and the first load.
-template <typename TX, int H, int NX>
-__device__ __forceinline__ bool res_gather(const char* base, uint32_t off, uint32_t stride, uint32_t apart, const char* xbase, uint32_t xoff,
-                                           uint32_t seq, int max_spin, double& sum, double& x0, double& x1, int& spin)
-{
-    static_assert(NX == 0 || NX == 2 || NX == 4, "none, one or two piggybacked doubles");
-    constexpr int W = kResWords<TX>, N = W * H;
-    uint64_t w[N + 4];
-    w[N + 2] = 0;
-    w[N + 3] = 0;
-    for (;;) {
-#pragma unroll
-        for (int q = 0; q < H; ++q)
-#pragma unroll
-            for (int h = 0; h < W; ++h)
-                w[W * q + h] = __hip_atomic_load((const uint64_t*)(base + (size_t)q * stride + (size_t)h * apart + off), __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-        for (int q = 0; q < NX; ++q)
-            w[N + q] = __hip_atomic_load((const uint64_t*)(xbase + q * 8 + xoff), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        uint32_t stale = 0;
-#pragma unroll
-        for (int q = 0; q < N + NX; ++q) stale |= (uint32_t)(w[q] >> 32) ^ seq;
-        if (__ballot(stale != 0) == 0) break;
-        if (++spin > max_spin) return false;
-        __builtin_amdgcn_s_sleep(1);
-    }
-    double s = 0.0;
-#pragma unroll
-    for (int q = 0; q < H; ++q) {
-        if constexpr (W == 1) s += (double)__uint_as_float((uint32_t)w[q]);
-        else s += __longlong_as_double((long long)((w[2 * q + 1] << 32) | (w[2 * q] & 0xFFFFFFFFull)));
-    }
-    sum = s;
-    if constexpr (NX >= 2) x0 = __longlong_as_double((long long)((w[N + 1] << 32) | (w[N] & 0xFFFFFFFFull)));
-    if constexpr (NX == 4) x1 = __longlong_as_double((long long)((w[N + 3] << 32) | (w[N + 2] & 0xFFFFFFFFull)));
-    return true;
-}
-
-template <int CTRL>
-__device__ __forceinline__ float dpp_f32(float v)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
-}
-
-template <int CTRL>
-__device__ __forceinline__ float dpp_val(float v)
-{
-    return dpp_f32<CTRL>(v);
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp_val(double v)
-{
-    return dpp_f64_res<CTRL, 0>(v);
-}
-__device__ __forceinline__ float res_fma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double res_fma(double a, double b, double c) { return __builtin_fma(a, b, c); }
-// the sign bit of a factor +-1.0, at the top of a word; ck with that word's top bit flipped in
-__device__ __forceinline__ uint32_t sign_of(float f) { return __float_as_uint(f) & 0x80000000u; }
-__device__ __forceinline__ uint32_t sign_of(double f) { return (uint32_t)__double2hiint(f) & 0x80000000u; }
-__device__ __forceinline__ float flip_by(float ck, uint32_t top) { return __uint_as_float(__float_as_uint(ck) ^ top); }
-__device__ __forceinline__ double flip_by(double ck, uint32_t top)
-{
-    return __hiloint2double((int)((uint32_t)__double2hiint(ck) ^ top), __double2loint(ck));
-}
-
-// 16 bytes of the matrix
-template <typename TE>
-struct ResVec;
-template <>
-struct ResVec<float> {
-    typedef float4 type;
-    static constexpr int N = 4;
-    static __device__ __forceinline__ void get(const float* p, float* x)
-    {
-        const float4 v = *(const float4*)p;
-        x[0] = v.x, x[1] = v.y, x[2] = v.z, x[3] = v.w;
-    }
-    static __device__ __forceinline__ void put(float* p, const float* x) { *(float4*)p = make_float4(x[0], x[1], x[2], x[3]); }
-};
-template <>
-struct ResVec<double> {
-    typedef double2 type;
-    static constexpr int N = 2;
-    static __device__ __forceinline__ void get(const double* p, double* x)
-    {
-        const double2 v = *(const double2*)p;
-        x[0] = v.x, x[1] = v.y;
-    }
-    static __device__ __forceinline__ void put(double* p, const double* x) { *(double2*)p = make_double2(x[0], x[1]); }
-};
-
-// the value of the neighbouring lane (lane ^ 1), for doubles
-__device__ __forceinline__ double dpp_swap1_f64(double v)
-{
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xFFFFFFFFll), 0xB1, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0xB1, 0xF, 0xF, true);
-    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
-
-// Sum over the four 16-lane rows of a wave for two registers at once: the row-swap instructions of gfx950 exchange
-// the odd rows (the upper half of the wave) of one register with the even rows (the lower half) of the other, after
-// which one addition serves both.  half16(a, b): even rows hold a's pair sums, odd rows b's.  half32 of two such:
-// row r of the result holds the full sum of the r-th of the four registers.
-__device__ __forceinline__ float half16(float a, float b)
-{
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ float half32(float a, float b)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ double half16(double a, double b)
-{
-    const auto l = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
-    const auto h = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
-    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-}
-__device__ __forceinline__ double half32(double a, double b)
-{
-    const auto l = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
-    const auto h = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
-    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-}
-
-// Sum over groups of N = 4, 8 or 16 neighbouring lanes, the same bits in every lane of a group.
-template <int N>
-__device__ __forceinline__ double group_sum_res(double a)
-{
-    a += dpp_f64_res<0xB1, 0>(a);                          // lane ^ 1
-    a += dpp_f64_res<0x4E, 0>(a);                          // lane ^ 2
-    if constexpr (N >= 8) a += dpp_f64_res<0x141, 0x1B>(a);    // lane ^ 4
-    if constexpr (N >= 16) a += dpp_f64_res<0x140, 0x141>(a);  // lane ^ 8
-    return a;
-}
-
-// A sign is kept in LDS as the top byte of the factor +-1.0 it stands for (the same byte in f32 and f64); byte k of a
-// loaded word becomes the factor's (upper) word in one instruction.
-constexpr uint8_t kPosByte = 0x3F, kNegByte = 0xBF;
-template <int K>
-__device__ __forceinline__ void sign_factor(uint32_t bytes, float& f)
-{
-    f = __uint_as_float(__builtin_amdgcn_perm(bytes, 0x00800000u, 0x00020100u | ((4u + K) << 24)));
-}
-template <int K>
-__device__ __forceinline__ void sign_factor(uint32_t bytes, double& f)
-{
-    f = __hiloint2double((int)__builtin_amdgcn_perm(bytes, 0x00F00000u, 0x00020100u | ((4u + K) << 24)), 0);
-}
-template <typename TE, int N>
-__device__ __forceinline__ void sign_factors(const uint8_t* p, TE (&f)[N])
-{
-    uint32_t w[(N + 3) / 4];
-    if constexpr (N >= 4) {
-#pragma unroll
-        for (int i = 0; i < N / 4; ++i) w[i] = ((const uint32_t*)p)[i];
-    } else {
-        w[0] = *(const uint16_t*)p;
-    }
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        if ((i & 3) == 0) sign_factor<0>(w[i / 4], f[i]);
-        else if ((i & 3) == 1) sign_factor<1>(w[i / 4], f[i]);
-        else if ((i & 3) == 2) sign_factor<2>(w[i / 4], f[i]);
-        else sign_factor<3>(w[i / 4], f[i]);
-    }
-}
-
-// PAD: the grid overhangs the matrix (a template parameter: the 128 row/column tests of a thread's tile are
-// invariants of the whole launch, and a kernel that has to keep them takes twice the instructions and runs out of
-// scalar registers even when no test ever fails).
-// TA: type of the sums inside a workgroup, TX: of the sums that it publishes (see resident_sums).
-template <typename TE, typename TA, typename TX, int TR, int TC, int P, bool PAD>
-__global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
-{
-    constexpr int W = kResWords<TX>, VE = ResVec<TE>::N;
-    TE* const Rm = (TE*)a.R;
-    constexpr int H = P / 2;  // members per half of an exchange group
-    static_assert(P == 4 || P == 8 || P == 16, "grid side");
-    constexpr int BM = 32 * TR, BN = 16 * TC;  // block of this workgroup
-    static_assert(TR >= 2 && TR <= 16 && (TR % 2) == 0, "rows per thread");
-    static_assert(TC >= 4 && TC <= 32 && (TC % 4) == 0, "columns per thread");
-    static_assert(W * BM + 4 <= kResSlotWords && W * BN + 4 <= kResSlotWords, "slot size");
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int tr = tid >> 4, tc = tid & 15;  // 32 x 16 threads, each TR x TC elements
-    const int pr = blockIdx.x / P, pc = blockIdx.x % P;
-    const int wg = blockIdx.x;
-
-    constexpr int NWV = kResThreads / 64;
-    __shared__ __align__(16) TA lds_q[NWV][BN];
-    __shared__ __align__(16) uint8_t lds_s[2][BM];  // signs as the top bytes of +-1.0
-    __shared__ __align__(16) uint8_t lds_t[BN];
-    __shared__ double lds_red[NWV];
-    __shared__ double lds_x[2][P];
-    __shared__ int lds_fail;  // a wait ran out in some wave; read after the barrier that follows every exchange
-
-    // ---- load the block.  The grid may overhang the matrix: rows and columns past its end are zeros in the
-    // registers (they add nothing to any sum and stay zero through every update) and are never read or written.
-    const int64_t row0 = (int64_t)pr * BM + tr * TR, col0 = (int64_t)pc * BN + tc * TC;
-    constexpr bool padded = PAD;
-    TE x[TR][TC];
-    {
-        const TE* base = Rm + row0 * a.n + col0;
-        if (!padded || a.n % VE == 0) {
-#pragma unroll
-            for (int r = 0; r < TR; ++r)
-#pragma unroll
-                for (int c = 0; c < TC; c += VE) {
-#pragma unroll
-                    for (int e = 0; e < VE; ++e) x[r][c + e] = 0;
-                    if (!padded || (row0 + r < a.m && col0 + c < a.n)) ResVec<TE>::get(base + (int64_t)r * a.n + c, &x[r][c]);
-                }
-        } else {
-            // rows that are no multiple of 16 bytes: one element at a time, once per launch
-#pragma unroll
-            for (int r = 0; r < TR; ++r)
-#pragma unroll
-                for (int c = 0; c < TC; ++c) x[r][c] = (row0 + r < a.m && col0 + c < a.n) ? base[(int64_t)r * a.n + c] : (TE)0;
-        }
-    }
-    if (tid == 0) lds_fail = 0;
-    // Values that are widened for the sums are widened anew in each phase: kept from one to the next they would take twice
-    // the registers again and go through scratch (4095x4093 f32, 8 terms: 23.3 ms instead of 5.9).
-    auto keep_narrow = [&]() {
-        if constexpr (sizeof(TA) != sizeof(TE)) {
-#pragma unroll
-            for (int r = 0; r < TR; ++r)
-#pragma unroll
-                for (int c = 0; c < TC; ++c) asm volatile("" : "+v"(x[r][c]));
-        }
-    };
-
-    int64_t k = a.k_start;
-    int alternations = 0, updates = 0;
-    uint32_t seq_u = a.seq_u, seq_v = a.seq_v;
-    int j = 0, warn = 0, cur = 0;
-    double c_prev = -INFINITY;
-    double cpart = 0.0;      // wave 0: this column block's sum |v_l| of the last column phase
-    double fsq_block = 0.0;  // wave 0: sum of squares of this block after the last update
-    double frow = 0.0;       // ... of this block row
-    int norm_stage = 0;      // 1: fsq_block to publish (row exchange); 2: frow to publish (col exchange)
-    int64_t norm_k = 0;
-    const double total = (double)a.m * (double)a.n;
-    bool need_t0 = true;
-    int spin = 0, spins = 0;
-    // lane offsets of the two gathers (bytes; the same in every exchange): thread (element, half) reads the
-    // element's words of one half of the partners; threads past the block read a valid element and drop it
-    const int half = tid & 1;
-    const uint32_t off_u = (uint32_t)(half * H * kResSlotWords + ((tid >> 1) < BM ? (tid >> 1) : BM - 1)) * 8u;
-    const uint32_t off_v = (uint32_t)(half * H * P * kResSlotWords + ((tid >> 1) < BN ? (tid >> 1) : BN - 1)) * 8u;
-
-    for (;;) {
-        if (k >= a.w_target && norm_stage == 0) break;
-        if (need_t0) {
-            // t_0 of term k from the keyed stream (Algorithm 4 line 2)
-            if (tid < BN) {
-                const int64_t col = (int64_t)pc * BN + tid;
-                const bool neg = col < a.n && ((rng_word(a.seed, (uint64_t)k, 1u, (uint64_t)(col >> 6)) >> (col & 63)) & 1ull);
-                lds_t[tid] = neg ? kNegByte : kPosByte;
-            }
-            need_t0 = false;
-            __syncthreads();
-        }
-        // ================= row phase: u = R t (Algorithm 4 line 5)
-        // The signs enter as +-1.0 multipliers of a fused multiply-add: x * (+-1) is exact, so each step
-        // rounds exactly like the sign-flip-and-add of Section 3.4, in one instruction instead of two
-        // (this engine is bound by vector instructions and latency, not by memory).
-        keep_narrow();
-        TA prow;  // the row sum this lane publishes: row tc of the thread row's TR rows (lanes tc < TR)
-        {
-            TA tf[TC];
-            sign_factors(lds_t + tc * TC, tf);
-            TA p[TR];
-#pragma unroll
-            for (int r = 0; r < TR; ++r) {
-                TA s = 0;
-#pragma unroll
-                for (int c = 0; c < TC; ++c) s = res_fma((TA)x[r][c], tf[c], s);
-                p[r] = s;
-            }
-            // Sum over the 16 lanes that share these rows, lane distances 1, 2, 4, 8.  At distances 1 and 2 a lane
-            // keeps only the rows whose low index bits are its own (it hands the others to its neighbour), which
-            // halves the registers each time: lane tc ends with rows tc mod 4 and 4 + tc mod 4.
-            const bool odd1 = (lane & 1) != 0, odd2 = (lane & 2) != 0;
-            TA a1[TR / 2];
-#pragma unroll
-            for (int i = 0; i < TR / 2; ++i) {
-                const TA keep = odd1 ? p[2 * i + 1] : p[2 * i], send = odd1 ? p[2 * i] : p[2 * i + 1];
-                a1[i] = keep + dpp_val<0xB1>(send);  // lane ^ 1
-            }
-            if constexpr (TR == 2) {
-                TA s = a1[0];
-                s += dpp_val<0x4E>(s);   // lane ^ 2
-                s += dpp_val<0x124>(s);  // row rotate 4
-                s += dpp_val<0x128>(s);  // row rotate 8
-                prow = s;
-            } else {
-                TA a2[TR / 4];
-#pragma unroll
-                for (int i = 0; i < TR / 4; ++i) {
-                    const TA keep = odd2 ? a1[2 * i + 1] : a1[2 * i], send = odd2 ? a1[2 * i] : a1[2 * i + 1];
-                    TA s = keep + dpp_val<0x4E>(send);  // lane ^ 2
-                    s += dpp_val<0x124>(s);             // row rotate 4
-                    s += dpp_val<0x128>(s);             // row rotate 8
-                    a2[i] = s;
-                }
-                if constexpr (TR == 8) prow = (lane & 4) ? a2[1] : a2[0];
-                else prow = a2[0];
-            }
-        }
-        ++seq_u;
-        ++alternations;
-        {
-            uint64_t* mine = res_slot(a, 0, seq_u, wg);
-            if (tc < TR) res_publish(mine + tr * TR + tc, BM, (TX)prow, seq_u);
-            if (tid == 0) {
-                res_publish_f64(mine + W * BM, cpart, seq_u);
-                if (norm_stage == 1) res_publish_f64(mine + W * BM + 2, fsq_block, seq_u);  // (only the exchange after an update)
-            }
-        }
-        for (int d = 0; d < a.poll_delay; ++d) __builtin_amdgcn_s_sleep(1);
-        {
-            // gather: thread (row, half) adds eight members in order, the two halves are combined low
-            // first.  The last wave also fetches the piggybacked scalars (lane mod P = member), in the
-            // same batch of loads.
-            const int row = tid >> 1;
-            const char* base = res_slot_bytes(a, 0, seq_u, pr * P);
-            double hs = 0.0, x0 = 0.0, x1 = 0.0;
-            bool ok;
-            if (wv == NWV - 1) {
-                const uint32_t xoff = (uint32_t)((lane & (P - 1)) * kResSlotWords + W * BM) * 8u;
-                if (norm_stage == 1) ok = res_gather<TX, H, 4>(base, off_u, kResSlotWords * 8, BM * 8, base, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
-                else ok = res_gather<TX, H, 2>(base, off_u, kResSlotWords * 8, BM * 8, base, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
-                if (lane < P) {
-                    lds_x[0][lane] = x0;
-                    if (norm_stage == 1) lds_x[1][lane] = x1;
-                }
-            } else {
-                ok = res_gather<TX, H, 0>(base, off_u, kResSlotWords * 8, BM * 8, base, 0, seq_u, a.max_spin, hs, x0, x1, spin);
-            }
-            const double other = dpp_swap1_f64(hs);
-            const double u = half ? other + hs : hs + other;
-            if (half == 0 && row < BM) lds_s[cur ^ 1][row] = (u < 0.0) ? kNegByte : kPosByte;
-            if (!ok) lds_fail = 1;
-        }
-        // One barrier per exchange: the give-up flag is an LDS word that only ever goes from 0 to 1 and is read
-        // with the data behind the barrier (__syncthreads_or takes three barriers and two more LDS round trips).
-        __syncthreads();
-        const int failed = lds_fail;
-        const double cx = lds_x[0][lane & (P - 1)];
-        cur ^= 1;  // s_j = sgn(u)
-
-        // ================= column phase: v = R^T s (Algorithm 4 line 6), c = sum |v| (line 7).  Its sums are formed
-        // before the stop test below is looked at: the test's chain of additions hides behind them, and a term that
-        // ends here has formed one half step too many (once per term).
-        keep_narrow();
-        TA qv[TC / 4];
-        {
-            TA sf[TR];
-            sign_factors(&lds_s[cur][tr * TR], sf);
-            TA q[TC];
-#pragma unroll
-            for (int c = 0; c < TC; ++c) {
-                TA s = 0;
-#pragma unroll
-                for (int r = 0; r < TR; ++r) s = res_fma((TA)x[r][c], sf[r], s);
-                q[c] = s;
-            }
-            // the four thread rows of this wave hold the same columns 16 lanes apart: lane row i ends with the sums
-            // of columns i TC/4 .. (i + 1) TC/4 - 1
-#pragma unroll
-            for (int g = 0; g < TC / 4; ++g)
-                qv[g] = half32(half16(q[g], q[TC / 4 + g]), half16(q[TC / 2 + g], q[3 * (TC / 4) + g]));
-        }
-        const double c_tot = uniform_f64(group_sum_res<P>(cx));
-        if (__builtin_amdgcn_readfirstlane(failed)) {
-            if (tid == 0) atomicExch((unsigned*)&a.res->err, 1u);
-            return;
-        }
-        spins += spin;
-        spin = 0;
-        if (norm_stage == 1) {
-            frow = uniform_f64(group_sum_res<P>(lds_x[1][lane & (P - 1)]));
-            norm_stage = 2;
-        }
-        if (j > 0) {
-            const bool conv = (c_tot <= c_prev) || (j >= a.max_iters);
-            if (conv) {
-                // ---- the term is (c_tot, s_{j-1}, t): append it (Algorithm 5 lines 7-9) and subtract it (line 10);
-                // the s of the row phase just done (lds_s[cur]) is dropped
-                cur ^= 1;
-                if (!(c_tot <= c_prev)) warn = 1;
-                const double ck = c_tot / total;
-                const TE ckf = (TE)ck;
-                if (pc == 0 && wv < BM / 64) {
-                    const uint64_t word = __ballot(lds_s[cur][wv * 64 + lane] == kNegByte);
-                    if (lane == 0 && pr * (BM / 64) + wv < a.mw) a.S[k * a.mw + pr * (BM / 64) + wv] = word;
-                }
-                if (pr == 0 && wv < BN / 64) {
-                    const uint64_t word = __ballot(lds_t[wv * 64 + lane] == kNegByte);
-                    if (lane == 0 && pc * (BN / 64) + wv < a.nw) a.T[k * a.nw + pc * (BN / 64) + wv] = word;
-                }
-                if (wg == 0 && tid == 0) {
-                    ((TE*)a.c)[k] = ckf;
-                    a.iters[k] = j;
-                }
-                TE tf[TC];
-                sign_factors(lds_t + tc * TC, tf);
-                double f = 0.0;
-#pragma unroll
-                for (int r = 0; r < TR; ++r) {
-                    const uint32_t sr = ((uint32_t)lds_s[cur][tr * TR + r] & 0x80u) << 24;
-#pragma unroll
-                    for (int c = 0; c < TC; ++c) {
-                        // R_il - ck s_i t_l: the signs choose +ck or -ck
-                        const TE d = flip_by(ckf, sr ^ sign_of(tf[c]));
-                        x[r][c] = (!padded || (row0 + r < a.m && col0 + c < a.n)) ? x[r][c] - d : (TE)0;  // padding stays zero
-                        f += (double)x[r][c] * (double)x[r][c];
-                    }
-                }
-                f = wave_sum_res(f);
-                if (lane == 0) lds_red[wv] = f;
-                __syncthreads();
-                if (wv == 0) {
-                    double fb = 0.0;
-#pragma unroll
-                    for (int q = 0; q < NWV; ++q) fb += lds_red[q];
-                    fsq_block = uniform_f64(fb);
-                }
-                ++k;
-                ++updates;
-                norm_stage = 1;
-                norm_k = k;
-                j = 0;
-                c_prev = -INFINITY;
-                cpart = 0.0;
-                need_t0 = true;
-                __syncthreads();  // lds_t and lds_red are rewritten next
-                continue;
-            }
-            c_prev = c_tot;
-        }
-        {
-            // lane (i, tc) holds TC/4 neighbouring columns
-            constexpr int VA = ResVec<TA>::N;
-            TA* dst = &lds_q[wv][tc * TC + (lane >> 4) * (TC / 4)];
-            if constexpr (TC / 4 >= VA) {
-#pragma unroll
-                for (int g = 0; g < TC / 4; g += VA) ResVec<TA>::put(dst + g, qv + g);
-            } else {
-#pragma unroll
-                for (int g = 0; g < TC / 4; ++g) dst[g] = qv[g];
-            }
-        }
-        __syncthreads();
-        ++seq_v;
-        {
-            uint64_t* mine = res_slot(a, 1, seq_v, wg);
-            if (tid < BN) {
-                // (all loads in flight together, then the adds in wave order: the empty asm keeps the compiler from
-                // loading two, waiting, adding two)
-                TA w[NWV];
-#pragma unroll
-                for (int q = 0; q < NWV; ++q) w[q] = lds_q[q][tid];
-                static_assert(NWV == 8, "operands of the asm");
-                asm volatile("" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(w[4]), "+v"(w[5]), "+v"(w[6]), "+v"(w[7]));
-                TA s = 0;
-#pragma unroll
-                for (int q = 0; q < NWV; ++q) s += w[q];
-                res_publish(mine + tid, BN, (TX)s, seq_v);
-            }
-            if (norm_stage == 2 && tid == kResThreads - 1) res_publish_f64(mine + W * BN, frow, seq_v);
-        }
-        for (int d = 0; d < a.poll_delay_v; ++d) __builtin_amdgcn_s_sleep(1);
-        double absv = 0.0;
-        {
-            const int col = tid >> 1;
-            const char* base = res_slot_bytes(a, 1, seq_v, pc);
-            double hs = 0.0, x0 = 0.0, x1 = 0.0;
-            bool ok;
-            if (norm_stage == 2 && wv == NWV - 1) {
-                // the block-row sums of squares travel on this exchange once per term
-                ok = res_gather<TX, H, 2>(base, off_v, P * kResSlotWords * 8, BN * 8, base,
-                                          (uint32_t)((lane & (P - 1)) * P * kResSlotWords + W * BN) * 8u, seq_v, a.max_spin, hs, x0, x1, spin);
-                if (lane < P) lds_x[1][lane] = x0;
-            } else {
-                ok = res_gather<TX, H, 0>(base, off_v, P * kResSlotWords * 8, BN * 8, base, 0, seq_v, a.max_spin, hs, x0, x1, spin);
-            }
-            const double other = dpp_swap1_f64(hs);
-            const double v = half ? other + hs : hs + other;
-            if (half == 0 && col < BN) {
-                lds_t[col] = (v < 0.0) ? kNegByte : kPosByte;
-                absv = fabs(v);
-            }
-            if (!ok) lds_fail = 1;
-        }
-        absv = wave_sum_res(absv);
-        if (lane == 0) lds_red[wv] = absv;
-        __syncthreads();
-        if (__builtin_amdgcn_readfirstlane(lds_fail)) {
-            if (tid == 0) atomicExch((unsigned*)&a.res->err, 1u);
-            return;
-        }
-        // this column block's share of c travels on the next row exchange (published by thread 0)
-        if (wv == 0) cpart = group_sum_res<8>(lds_red[lane & (NWV - 1)]);
-        if (norm_stage == 2) {
-            const double ft = group_sum_res<P>(lds_x[1][lane & (P - 1)]);
-            if (wg == 0 && tid == 0) a.trace[norm_k] = sqrt(ft);
-            norm_stage = 0;
-        }
-        ++j;
-        spins += spin;
-        spin = 0;
-        // No barrier here: what was read above (lds_red, lds_x[1]) is next written after the two barriers of the
-        // coming row and column phases (lds_x[1] in a row phase only right after an update, never right after
-        // the column phase that read it), and what the coming row phase writes first (lds_s of the other
-        // parity, lds_x[0]) was last read before this phase's barriers.
-    }
-
-    // ---- write the block back
-    {
-        TE* base = Rm + row0 * a.n + col0;
-        if (!padded || a.n % VE == 0) {
-#pragma unroll
-            for (int r = 0; r < TR; ++r)
-#pragma unroll
-                for (int c = 0; c < TC; c += VE)
-                    if (!padded || (row0 + r < a.m && col0 + c < a.n)) ResVec<TE>::put(base + (int64_t)r * a.n + c, &x[r][c]);
-        } else {
-#pragma unroll
-            for (int r = 0; r < TR; ++r)
-#pragma unroll
-                for (int c = 0; c < TC; ++c)
-                    if (row0 + r < a.m && col0 + c < a.n) base[(int64_t)r * a.n + c] = x[r][c];
-        }
-    }
-    if (wg == 0 && tid == 0) {
-        a.res->k = k;
-        a.res->alternations = alternations;
-        a.res->updates = updates;
-        a.res->seq_u = seq_u;
-        a.res->seq_v = seq_v;
-        a.res->warn = warn;
-        a.res->spins = spins;
-    }
-}
-
-// Grid side P and thread tile TR x TC for an m x n matrix: the P x P workgroups of 32 x 16 threads cover
-// P * 32 * TR rows and P * 16 * TC columns, at least the matrix (the overhang is kept as zeros).  Fewer
-// workgroups mean fewer partners per exchange, more workgroups less arithmetic each; measured on the square
-// sizes (256 and 512 fastest with 8 values per thread on 4 x 4 and 8 x 8 workgroups, 1024 with 32 values on
-// 8 x 8, 2048 with 32 values on 16 x 16), which gives the order of preference: the smallest grid of at most
-// 8 x 8 with at most 8 values per thread, else the smallest grid with at most 32, else the grid that fits with
-// the smallest tile.  Rows that are no multiple of 16 bytes are loaded and written back element by element, once per
-// launch (1501x999, 16 terms: 2.4 ms a call; two launches per alternation on the unaligned rows took 8.7 ms).
-static bool resident_shape(scd_dtype dt, int64_t m, int64_t n, int* p, int* tr, int* tc)
-{
-    if (m < 1 || n < 4) return false;
-    const int most = dt == SCD_F32 ? 128 : 64;  // values a thread can hold
-    static const int grids[3] = {4, 8, 16};
-    static const int trs[3] = {2, 4, 8}, tcs[3] = {4, 8, 16};
-    int best = -1, bp = 0, btr = 0, btc = 0;
-    for (int pass = 0; pass < 2; ++pass) {
-        for (int P : grids) {
-            int r = 0, c = 0;
-            for (int t : trs)
-                if (!r && (int64_t)P * 32 * t >= m) r = t;
-            for (int t : tcs)
-                if (!c && (int64_t)P * 16 * t >= n) c = t;
-            if (!r || !c || r * c > most) continue;
-            if (P == 4 && (r > 4 || c > 8)) continue;  // (the 4 x 4 grid is built with the small tiles only)
-            if (pass == 0 ? (P <= 8 && r * c <= 8) : (r * c <= 32)) {
-                *p = P, *tr = r, *tc = c;
-                return true;
-            }
-            if (best < 0 || r * c < best) best = r * c, bp = P, btr = r, btc = c;
-        }
-    }
-    if (best < 0) return false;
-    *p = bp, *tr = btr, *tc = btc;
-    return true;
 }
 
 bool resident_supported(scd_dtype dt, int order, const int64_t* dims)

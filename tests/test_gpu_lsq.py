@@ -77,6 +77,20 @@ def test_lsq_device_loop_range(scd, oracle, m, n, w, dtype):
     run_and_check(scd, oracle, gauss((m, n), 3 * m + n, dtype), w, 5)
 
 
+# cuts on the register-resident engine in f64: exact fits of its grids and one row or column past them, the smallest and
+# largest matrices it takes, both types, rows that are no 16-byte steps; 3 columns go to the sweeps
+@pytest.mark.parametrize("m,n,w,dtype", [(256, 128, 6, np.float32), (257, 129, 6, np.float64), (2, 4, 1, np.float32), (40, 3, 2, np.float32),
+                                         (1024, 1024, 5, np.float32), (1025, 1023, 4, np.float64), (4096, 2048, 2, np.float32),
+                                         (2047, 4095, 2, np.float32), (511, 2050, 4, np.float32)])
+def test_lsq_resident_cuts(scd, oracle, m, n, w, dtype):
+    run_and_check(scd, oracle, gauss((m, n), 5 * m + n, dtype), w, 6)
+
+
+def test_lsq_refit_past_one_wave(scd, oracle):
+    # 88 terms is what one wave refits; the next ones go to the workgroup's form
+    run_and_check(scd, oracle, gauss((96, 84), 11, np.float64), 94, 7)
+
+
 def test_lsq_unaligned_input(scd):
     flat = torch.from_numpy(gauss((1, 96 * 128 + 1), 8)).cuda().reshape(-1)
     off = flat[1:].reshape(96, 128)                       # contiguous, rows 4 bytes past a 16-byte boundary
