@@ -1354,31 +1354,34 @@ int scd_expand(const uint64_t* const* signs, const void* cvec, scd_dtype dt, int
         if (w > 0 && !signs[i]) return SCD_EINVAL;
     hipStream_t st = (hipStream_t)stream;
     const int64_t m = dims[0], cols = total / dims[0];
+    // one block: the digits of the coefficients, then (tensors) the Kronecker products of the trailing modes' signs
     uint64_t* kr = nullptr;
-    const size_t kr_bytes = (size_t)w * (size_t)words_for(cols) * 8;
+    const size_t dig_bytes = (expand_scratch_bytes(dt, w) + 255) & ~(size_t)255;
+    const size_t kr_bytes = order >= 3 ? (size_t)w * (size_t)words_for(cols) * 8 : 0;
+    char* block = nullptr;
     const uint64_t* T = signs[1];
+    if (dig_bytes + kr_bytes > 0) {
+        hipError_t e = pool_malloc((void**)&block, dig_bytes + kr_bytes, false);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            block = nullptr;
+            if (kr_bytes > 0) {
+                g_last_hip = (int)e;
+                return SCD_ENOMEM;
+            }
+        }
+    }
+    hipError_t e = hipSuccess;
     if (order >= 3 && w > 0) {
-        hipError_t e = pool_malloc((void**)&kr, kr_bytes, false);
-        if (e != hipSuccess) {
-            g_last_hip = (int)e;
-            (void)hipGetLastError();
-            return SCD_ENOMEM;
-        }
+        kr = (uint64_t*)(block + dig_bytes);
         e = launch_kron_terms(order, dims, signs, w, kr, cols, st);
-        if (e != hipSuccess) {
-            g_last_hip = (int)e;
-            (void)hipGetLastError();
-            settle(st);
-            pool_free(kr);
-            return SCD_EHIP;
-        }
         T = kr;
     }
-    hipError_t e = launch_expand(signs[0], T, cvec, dt, m, cols, w, out, st);
+    if (e == hipSuccess) e = launch_expand(signs[0], T, cvec, dt, m, cols, w, out, block, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (kr) {
+    if (block) {
         if (e != hipSuccess) settle(st);
-        pool_free(kr);
+        pool_free(block);
     }
     if (e != hipSuccess) {
         g_last_hip = (int)e;

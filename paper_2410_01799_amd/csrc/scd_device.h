@@ -292,8 +292,9 @@ hipError_t launch_lsq_sweep(const LsqMatArgs& a, scd_dtype dt, hipStream_t st);
 hipError_t launch_lsq_term(const LsqMatArgs& a, const ResidentResult* res, hipStream_t st);
 
 // ---- expansion of the packed factors (scd_expand.hip)
+size_t expand_scratch_bytes(scd_dtype dt, int64_t w);
 hipError_t launch_expand(const uint64_t* S, const uint64_t* T, const void* c, scd_dtype dt, int64_t m,
-                         int64_t n, int64_t w, void* out, hipStream_t st);
+                         int64_t n, int64_t w, void* out, void* scratch, hipStream_t st);
 
 // ---- launchers implemented in scd_kernels.hip ----------------------------------------------------
 hipError_t launch_rowpass(const RowPassArgs& a, scd_dtype dt, int grid, int variant, hipStream_t st);

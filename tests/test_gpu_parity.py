@@ -100,6 +100,14 @@ def test_expand_bit_exact_over_the_span_of_the_coefficients(scd, oracle, shape, 
     assert np.array_equal(got, ref)
 
 
+# more than 128 tiles of 128 x 128 (the last ones ragged) in all three forms, whole and cut chunks of terms, more tiles than
+# workgroups; 32 terms are the last that go to the f64 form at once
+@pytest.mark.parametrize("shape,w,bits", [((1470, 1500), 33, 30), ((1470, 1500), 129, 38), ((1409, 1537), 128, 60), ((1500, 1400), 32, 24),
+                                          ((130, 127 * 127), 65, 30), ((2100, 2200), 191, 30), ((512, 17, 250), 70, 31)])
+def test_expand_bit_exact_on_large_tiles(scd, oracle, shape, w, bits):
+    test_expand_bit_exact_over_the_span_of_the_coefficients(scd, oracle, shape, w, bits)
+
+
 def test_expand_bit_exact_at_the_ends_of_the_exponents(scd, oracle):
     rs = np.random.Generator(np.random.PCG64(3))
     signs = [np.stack([oracle.pack(rs.standard_normal(d)) for _ in range(70)]) for d in (66, 70)]
