@@ -555,7 +555,7 @@ int setup_engines(scd_ctx* c)
         if (!hip_ok(hipMemsetAsync(c->xbuf_p2, 0, c->xbuf_p2_bytes, c->stream))) return SCD_EHIP;
         c->seq_ps = 0;
     }
-    if (c->resident && !c->xbuf) {
+    if (c->resident && !c->xbuf && resident_workgroups(c->dt, c->dims) > 1) {  // (one workgroup exchanges nothing)
         const size_t xb = (size_t)4 * kResGrid * kResGrid * kResSlotWords * 8;
         SCD_TRY(dev_alloc(c, (void**)&c->xbuf, xb));
         if (!hip_ok(hipMemsetAsync(c->xbuf, 0, xb, c->stream))) return SCD_EHIP;
@@ -1518,7 +1518,8 @@ int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uin
         double scal[2];
     };
     // one block: every array of doubles or words, then the iteration counts and the state
-    const size_t xbuf_words = resident ? (size_t)4 * kResGrid * kResGrid * kResSlotWords : 0;
+    const int64_t dims[2] = {m, n};
+    const size_t xbuf_words = resident && resident_workgroups(SCD_F64, dims) > 1 ? (size_t)4 * kResGrid * kResGrid * kResSlotWords : 0;
     const size_t words = (size_t)(mw + nw + 2 * nw + w * w + 3 * w + nsq + 2) + xbuf_words + (sizeof(ResidentResult) + 7) / 8;
     const size_t bytes = words * 8 + (((size_t)w * 4 + 15) & ~(size_t)15) + sizeof(LsqState);
     void* dev = nullptr;
@@ -1596,7 +1597,6 @@ int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uin
     }
     LM(hipStreamSynchronize(st));  // (the pinned block receives the state from here on)
     if (resident) {
-        const int64_t dims[2] = {m, n};
         ResidentArgs r;
         memset(&r, 0, sizeof(r));
         r.m = m;

@@ -164,13 +164,19 @@ static hipError_t launch_resident_t(const ResidentArgs& a, hipStream_t st)
 {
     // does the grid of P x P blocks of 32 TR x 16 TC overhang the matrix?
     const bool padded = (int64_t)P * 32 * TR != a.m || (int64_t)P * 16 * TC != a.n;
-    if constexpr (sizeof(TE) == 4) {
-        // (rows that are no 16-byte steps never fit the grid exactly)
-        const ResSums sums = resident_sums(SCD_F32, a.m, a.n, a.fro);
-        if (sums == ResSums::wide_inside) return launch_resident_k<TE, double, TE, TR, TC, P, true>(a, st);
-        if (sums == ResSums::wide) return launch_resident_k<TE, double, double, TR, TC, P, true>(a, st);
+    if constexpr (P == 1 && sizeof(TE) == 4) {
+        // f32 sums inside a thread, f64 across threads; rows that are no 16-byte steps: f64 from the first addition
+        if (a.n % ResVec<float>::N != 0) return launch_resident_k<TE, double, double, TR, TC, P, true>(a, st);
+        return padded ? launch_resident_k<TE, double, float, TR, TC, P, true>(a, st) : launch_resident_k<TE, double, float, TR, TC, P, false>(a, st);
+    } else {
+        if constexpr (sizeof(TE) == 4) {
+            // (rows that are no 16-byte steps never fit the grid exactly)
+            const ResSums sums = resident_sums(SCD_F32, a.m, a.n, a.fro);
+            if (sums == ResSums::wide_inside) return launch_resident_k<TE, double, TE, TR, TC, P, true>(a, st);
+            if (sums == ResSums::wide) return launch_resident_k<TE, double, double, TR, TC, P, true>(a, st);
+        }
+        return padded ? launch_resident_k<TE, TE, TE, TR, TC, P, true>(a, st) : launch_resident_k<TE, TE, TE, TR, TC, P, false>(a, st);
     }
-    return padded ? launch_resident_k<TE, TE, TE, TR, TC, P, true>(a, st) : launch_resident_k<TE, TE, TE, TR, TC, P, false>(a, st);
 }
 
 template <typename TE, int P>
@@ -184,7 +190,7 @@ static hipError_t launch_resident_p(const ResidentArgs& a, int tr, int tc, hipSt
         case 408: return launch_resident_t<TE, 4, 8, P>(a, st);
         default: break;
     }
-    if constexpr (P >= 8) {
+    if constexpr (P >= 8 || P == 1) {
         switch (key) {
             case 216: return launch_resident_t<TE, 2, 16, P>(a, st);
             case 416: return launch_resident_t<TE, 4, 16, P>(a, st);
@@ -204,6 +210,7 @@ static hipError_t launch_resident_e(const ResidentArgs& a, int p, int tr, int tc
 {
     if (p == 16) return launch_resident_p<TE, 16>(a, tr, tc, st);
     if (p == 8) return launch_resident_p<TE, 8>(a, tr, tc, st);
+    if (p == 1) return launch_resident_p<TE, 1>(a, tr, tc, st);
     return launch_resident_p<TE, 4>(a, tr, tc, st);
 }
 

@@ -1,6 +1,8 @@
 // The kernel of the register-resident engine and the rule that picks its shape (shared by the decomposition and the least
 // squares decomposition, each of which instantiates its own forms).
 #pragma once
+#include <type_traits>
+
 #include "scd_device.h"
 #include "scd_rng.h"
 
@@ -383,7 +385,10 @@ __device__ __forceinline__ void res_subtract_terms(const ResidentArgs& a, int64_
 // PAD: the grid overhangs the matrix (a template parameter: the 128 row/column tests of a thread's tile are
 // invariants of the whole launch, and a kernel that has to keep them takes twice the instructions and runs out of
 // scalar registers even when no test ever fails).
-// TA: type of the sums inside a workgroup, TX: of the sums that it publishes (see resident_sums).
+// SOLO (P = 1): a matrix that one workgroup holds.  Its f32 sums end inside a thread, with at most eight entries added one
+// after the other; across threads they are f64 (rms error of the row and column sums against f64, 4 x 4 workgroups / one:
+// 256x256 6.9e-8, 7.4e-8 / 6.1e-8, 5.7e-8; 64x64 7.1e-8, 7.6e-8 / 4.3e-8, 3.0e-8).  Nothing is published or waited for.
+// TA: type of the sums inside a workgroup, TX: of the sums that it publishes (see resident_sums; SOLO: of a thread's sums).
 // LSQ: one greedy cut of A - sum c_j s_j t_j^T for the coefficients that the refit of the last term left; the position of
 // the loop is the device's (a.lsq), and the refit follows as a launch of its own.
 template <typename TE, typename TA, typename TX, int TR, int TC, int P, bool PAD, bool LSQ = false>
@@ -391,8 +396,10 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
 {
     constexpr int W = kResWords<TX>, VE = ResVec<TE>::N;
     TE* const Rm = (TE*)a.R;
-    constexpr int H = P / 2;  // members per half of an exchange group
-    static_assert(P == 4 || P == 8 || P == 16, "grid side");
+    constexpr bool SOLO = P == 1;         // one workgroup holds the matrix: its sums are the sums, nothing is exchanged
+    constexpr int H = SOLO ? 1 : P / 2;   // members per half of an exchange group
+    static_assert(SOLO || P == 4 || P == 8 || P == 16, "grid side");
+    using TI = std::conditional_t<SOLO && sizeof(TX) == 4, float, TA>;  // of a thread's own sums
     constexpr int BM = 32 * TR, BN = 16 * TC;  // block of this workgroup
     static_assert(TR >= 2 && TR <= 16 && (TR % 2) == 0, "rows per thread");
     static_assert(TC >= 4 && TC <= 32 && (TC % 4) == 0, "columns per thread");
@@ -448,7 +455,7 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
     // Values that are widened for the sums are widened anew in each phase: kept from one to the next they would take twice
     // the registers again and go through scratch (4095x4093 f32, 8 terms: 23.3 ms instead of 5.9).
     auto keep_narrow = [&]() {
-        if constexpr (sizeof(TA) != sizeof(TE)) {
+        if constexpr (sizeof(TI) != sizeof(TE)) {
 #pragma unroll
             for (int r = 0; r < TR; ++r)
 #pragma unroll
@@ -492,15 +499,22 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
         keep_narrow();
         TA prow;  // the row sum this lane publishes: row tc of the thread row's TR rows (lanes tc < TR)
         {
-            TA tf[TC];
+            TI tf[TC];
             sign_factors(lds_t + tc * TC, tf);
             TA p[TR];
 #pragma unroll
             for (int r = 0; r < TR; ++r) {
-                TA s = 0;
+                // (SOLO: two runs of at most eight, so that no f32 sum is longer than it is on a 4 x 4 grid)
+                constexpr int RUN = SOLO && TC > 4 ? TC / 2 : TC;
+                TI s[TC / RUN];
 #pragma unroll
-                for (int c = 0; c < TC; ++c) s = res_fma((TA)x[r][c], tf[c], s);
-                p[r] = s;
+                for (int h = 0; h < TC / RUN; ++h) {
+                    s[h] = 0;
+#pragma unroll
+                    for (int c = h * RUN; c < (h + 1) * RUN; ++c) s[h] = res_fma((TI)x[r][c], tf[c], s[h]);
+                }
+                if constexpr (TC / RUN == 2) p[r] = (TA)(s[0] + s[1]);
+                else p[r] = (TA)s[0];
             }
             // Sum over the 16 lanes that share these rows, lane distances 1, 2, 4, 8.  At distances 1 and 2 a lane
             // keeps only the rows whose low index bits are its own (it hands the others to its neighbour), which
@@ -532,8 +546,11 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
                 else prow = a2[0];
             }
         }
-        ++seq_u;
         ++alternations;
+        if constexpr (SOLO) {
+            if (tc < TR) lds_s[cur ^ 1][tr * TR + tc] = (prow < 0) ? kNegByte : kPosByte;
+        } else {
+        ++seq_u;
         {
             uint64_t* mine = res_slot(a, 0, seq_u, wg);
             if (tc < TR) res_publish(mine + tr * TR + tc, BM, (TX)prow, seq_u);
@@ -567,6 +584,7 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
             if (half == 0 && row < BM) lds_s[cur ^ 1][row] = (u < 0.0) ? kNegByte : kPosByte;
             if (!ok) lds_fail = 1;
         }
+        }
         // One barrier per exchange: the give-up flag is an LDS word that only ever goes from 0 to 1 and is read
         // with the data behind the barrier (__syncthreads_or takes three barriers and two more LDS round trips).
         __syncthreads();
@@ -580,15 +598,15 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
         keep_narrow();
         TA qv[TC / 4];
         {
-            TA sf[TR];
+            TI sf[TR];
             sign_factors(&lds_s[cur][tr * TR], sf);
             TA q[TC];
 #pragma unroll
             for (int c = 0; c < TC; ++c) {
-                TA s = 0;
+                TI s = 0;
 #pragma unroll
-                for (int r = 0; r < TR; ++r) s = res_fma((TA)x[r][c], sf[r], s);
-                q[c] = s;
+                for (int r = 0; r < TR; ++r) s = res_fma((TI)x[r][c], sf[r], s);
+                q[c] = (TA)s;
             }
             // the four thread rows of this wave hold the same columns 16 lanes apart: lane row i ends with the sums
             // of columns i TC/4 .. (i + 1) TC/4 - 1
@@ -596,16 +614,20 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
             for (int g = 0; g < TC / 4; ++g)
                 qv[g] = half32(half16(q[g], q[TC / 4 + g]), half16(q[TC / 2 + g], q[3 * (TC / 4) + g]));
         }
-        const double c_tot = uniform_f64(group_sum_res<P>(cx));
+        double c_tot;
+        if constexpr (SOLO) c_tot = uniform_f64(cpart);
+        else c_tot = uniform_f64(group_sum_res<P>(cx));
         if (__builtin_amdgcn_readfirstlane(failed)) {
             if (tid == 0) atomicExch((unsigned*)&a.res->err, 1u);
             return;
         }
         spins += spin;
         spin = 0;
-        if (norm_stage == 1) {
-            frow = uniform_f64(group_sum_res<P>(lds_x[1][lane & (P - 1)]));
-            norm_stage = 2;
+        if constexpr (!SOLO) {
+            if (norm_stage == 1) {
+                frow = uniform_f64(group_sum_res<P>(lds_x[1][lane & (P - 1)]));
+                norm_stage = 2;
+            }
         }
         if (j > 0) {
             const bool conv = (c_tot <= c_prev) || (j >= a.max_iters) || (LSQ && !(fabs(c_tot) < INFINITY));
@@ -662,10 +684,11 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
 #pragma unroll
                     for (int q = 0; q < NWV; ++q) fb += lds_red[q];
                     fsq_block = uniform_f64(fb);
+                    if (SOLO && tid == 0) a.trace[k + 1] = sqrt(fsq_block);
                 }
                 ++k;
                 ++updates;
-                norm_stage = 1;
+                norm_stage = SOLO ? 0 : 1;
                 norm_k = k;
                 j = 0;
                 c_prev = -INFINITY;
@@ -689,6 +712,18 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
             }
         }
         __syncthreads();
+        double absv = 0.0;
+        if constexpr (SOLO) {
+            if (tid < BN) {
+                TA w[NWV];
+#pragma unroll
+                for (int q = 0; q < NWV; ++q) w[q] = lds_q[q][tid];
+                asm volatile("" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(w[4]), "+v"(w[5]), "+v"(w[6]), "+v"(w[7]));
+                const TA v = ((w[0] + w[1]) + (w[2] + w[3])) + ((w[4] + w[5]) + (w[6] + w[7]));
+                lds_t[tid] = (v < 0) ? kNegByte : kPosByte;
+                absv = fabs((double)v);
+            }
+        } else {
         ++seq_v;
         {
             uint64_t* mine = res_slot(a, 1, seq_v, wg);
@@ -708,7 +743,6 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
             if (norm_stage == 2 && tid == kResThreads - 1) res_publish_f64(mine + W * BN, frow, seq_v);
         }
         for (int d = 0; d < a.poll_delay_v; ++d) __builtin_amdgcn_s_sleep(1);
-        double absv = 0.0;
         {
             const int col = tid >> 1;
             const char* base = res_slot_bytes(a, 1, seq_v, pc);
@@ -730,6 +764,7 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
             }
             if (!ok) lds_fail = 1;
         }
+        }
         absv = wave_sum_res(absv);
         if (lane == 0) lds_red[wv] = absv;
         __syncthreads();
@@ -738,11 +773,13 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
             return;
         }
         // this column block's share of c travels on the next row exchange (published by thread 0)
-        if (wv == 0) cpart = group_sum_res<8>(lds_red[lane & (NWV - 1)]);
-        if (norm_stage == 2) {
-            const double ft = group_sum_res<P>(lds_x[1][lane & (P - 1)]);
-            if (wg == 0 && tid == 0) a.trace[norm_k] = sqrt(ft);
-            norm_stage = 0;
+        if (SOLO || wv == 0) cpart = group_sum_res<8>(lds_red[lane & (NWV - 1)]);
+        if constexpr (!SOLO) {
+            if (norm_stage == 2) {
+                const double ft = group_sum_res<P>(lds_x[1][lane & (P - 1)]);
+                if (wg == 0 && tid == 0) a.trace[norm_k] = sqrt(ft);
+                norm_stage = 0;
+            }
         }
         ++j;
         spins += spin;
@@ -795,6 +832,21 @@ inline bool resident_shape(scd_dtype dt, int64_t m, int64_t n, int* p, int* tr, 
     const int most = dt == SCD_F32 ? 128 : 64;  // values a thread can hold
     static const int grids[3] = {4, 8, 16};
     static const int trs[3] = {2, 4, 8}, tcs[3] = {4, 8, 16};
+    // One workgroup, whatever a thread can hold (odd f32 rows: 64 values, which are widened in every phase): three barriers
+    // an alternation instead of two exchanges.  Us per alternation, 4 x 4 workgroups / one: f32 64x64 3.15 / 1.11, 128x128
+    // 3.01 / 1.38, 256x128 3.02 / 1.76, 192x192 2.97 / 2.53, 256x256 2.91 / 2.32; 61x67 3.69 / 1.44, 130x101 3.62 / 2.49,
+    // 127x255 3.64 / 2.74; f64 128x128 3.56 / 1.47, 256x128 3.55 / 1.84, 127x255 3.59 / 2.28.
+    {
+        int r = 0, c = 0;
+        for (int t : trs)
+            if (!r && 32 * t >= m) r = t;
+        for (int t : tcs)
+            if (!c && 16 * t >= n) c = t;
+        if (r && c && r * c <= (dt == SCD_F32 && n % ResVec<float>::N == 0 ? 128 : 64)) {
+            *p = 1, *tr = r, *tc = c;
+            return true;
+        }
+    }
     int best = -1, bp = 0, btr = 0, btc = 0;
     for (int pass = 0; pass < 2; ++pass) {
         for (int P : grids) {

@@ -34,7 +34,7 @@ static hipError_t launch_lsq_p(const ResidentArgs& a, int tr, int tc, hipStream_
         case 408: return launch_lsq_k<4, 8, P>(a, st);
         default: break;
     }
-    if constexpr (P >= 8) {
+    if constexpr (P >= 8 || P == 1) {
         switch (key) {
             case 216: return launch_lsq_k<2, 16, P>(a, st);
             case 416: return launch_lsq_k<4, 16, P>(a, st);
@@ -52,6 +52,7 @@ hipError_t launch_resident_lsq(const ResidentArgs& a, hipStream_t st)
     if (!resident_shape(SCD_F64, a.m, a.n, &p, &tr, &tc)) return hipErrorInvalidValue;
     if (p == 16) return launch_lsq_p<16>(a, tr, tc, st);
     if (p == 8) return launch_lsq_p<8>(a, tr, tc, st);
+    if (p == 1) return launch_lsq_p<1>(a, tr, tc, st);
     return launch_lsq_p<4>(a, tr, tc, st);
 }
 

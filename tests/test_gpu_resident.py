@@ -145,6 +145,34 @@ def test_resident_f64_matches_oracle_in_lockstep(scd, oracle, m, n):
     assert float((torch.from_numpy(A).cuda() - E - R).abs().max()) <= 2e-15 * w * float(np.abs(A).max())
 
 
+# matrices that one workgroup holds: every tile, exact and with overhang, their ends and one row or column past them; odd f32
+# rows end at 64 values a thread
+SOLO = [(64, 64), (65, 68), (64, 128), (33, 132), (128, 64), (66, 61), (128, 128), (100, 126), (64, 256), (40, 255), (256, 64), (255, 62),
+        (128, 256), (127, 253), (256, 128), (129, 127), (129, 132), (129, 129), (255, 252), (256, 260), (257, 256), (255, 255)]
+
+
+@pytest.mark.parametrize("m,n", SOLO)
+def test_one_workgroup_matches_oracle_in_lockstep(scd, oracle, m, n):
+    test_resident_matches_oracle_in_lockstep(scd, oracle, m, n)
+    test_resident_f64_matches_oracle_in_lockstep(scd, oracle, m, n)
+
+
+def test_one_workgroup_takes_up_where_it_left(scd):
+    # launches of one term, a remainder given back and a share of the device: the same bits as one launch
+    A = torch.from_numpy(gauss((200, 240), 9)).cuda()
+    whole = scd.scd_decompose(A, 8, 5)
+    with scd.ScdContext(A, 8, 5) as ctx:
+        ctx.set_workgroups(16)
+        for k in range(8):
+            if k == 4:
+                ctx.set_remainder(ctx.remainder())
+            ctx.step()
+        parts = ctx.results()
+    for x, y in zip(whole["signs"] + [whole["c"], whole["iters"]], parts["signs"] + [parts["c"], parts["iters"]]):
+        assert torch.equal(x, y)
+    np.testing.assert_allclose(whole["trace"].cpu().numpy(), parts["trace"].cpu().numpy(), rtol=1e-8)
+
+
 def test_resident_f64_limit(scd):
     """One row or column past the registers: the next engine, as for every larger matrix."""
     for m, n in [(4097, 2048), (2049, 2049), (2048, 4097)]:
