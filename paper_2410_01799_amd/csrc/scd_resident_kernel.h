@@ -399,6 +399,7 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
     constexpr bool SOLO = P == 1;         // one workgroup holds the matrix: its sums are the sums, nothing is exchanged
     constexpr int H = SOLO ? 1 : P / 2;   // members per half of an exchange group
     static_assert(SOLO || P == 4 || P == 8 || P == 16, "grid side");
+    constexpr bool kEarly = SOLO && TR * TC >= 32;  // (with less to save, the branch costs more: 61x67 1.44 us per alternation, with it 1.53)
     using TI = std::conditional_t<SOLO && sizeof(TX) == 4, float, TA>;  // of a thread's own sums
     constexpr int BM = 32 * TR, BN = 16 * TC;  // block of this workgroup
     static_assert(TR >= 2 && TR <= 16 && (TR % 2) == 0, "rows per thread");
@@ -492,127 +493,136 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
             need_t0 = false;
             __syncthreads();
         }
-        // ================= row phase: u = R t (Algorithm 4 line 5)
-        // The signs enter as +-1.0 multipliers of a fused multiply-add: x * (+-1) is exact, so each step
-        // rounds exactly like the sign-flip-and-add of Section 3.4, in one instruction instead of two
-        // (this engine is bound by vector instructions and latency, not by memory).
-        keep_narrow();
-        TA prow;  // the row sum this lane publishes: row tc of the thread row's TR rows (lanes tc < TR)
-        {
-            TI tf[TC];
-            sign_factors(lds_t + tc * TC, tf);
-            TA p[TR];
-#pragma unroll
-            for (int r = 0; r < TR; ++r) {
-                // (SOLO: two runs of at most eight, so that no f32 sum is longer than it is on a 4 x 4 grid)
-                constexpr int RUN = SOLO && TC > 4 ? TC / 2 : TC;
-                TI s[TC / RUN];
-#pragma unroll
-                for (int h = 0; h < TC / RUN; ++h) {
-                    s[h] = 0;
-#pragma unroll
-                    for (int c = h * RUN; c < (h + 1) * RUN; ++c) s[h] = res_fma((TI)x[r][c], tf[c], s[h]);
-                }
-                if constexpr (TC / RUN == 2) p[r] = (TA)(s[0] + s[1]);
-                else p[r] = (TA)s[0];
-            }
-            // Sum over the 16 lanes that share these rows, lane distances 1, 2, 4, 8.  At distances 1 and 2 a lane
-            // keeps only the rows whose low index bits are its own (it hands the others to its neighbour), which
-            // halves the registers each time: lane tc ends with rows tc mod 4 and 4 + tc mod 4.
-            const bool odd1 = (lane & 1) != 0, odd2 = (lane & 2) != 0;
-            TA a1[TR / 2];
-#pragma unroll
-            for (int i = 0; i < TR / 2; ++i) {
-                const TA keep = odd1 ? p[2 * i + 1] : p[2 * i], send = odd1 ? p[2 * i] : p[2 * i + 1];
-                a1[i] = keep + dpp_val<0xB1>(send);  // lane ^ 1
-            }
-            if constexpr (TR == 2) {
-                TA s = a1[0];
-                s += dpp_val<0x4E>(s);   // lane ^ 2
-                s += dpp_val<0x124>(s);  // row rotate 4
-                s += dpp_val<0x128>(s);  // row rotate 8
-                prow = s;
-            } else {
-                TA a2[TR / 4];
-#pragma unroll
-                for (int i = 0; i < TR / 4; ++i) {
-                    const TA keep = odd2 ? a1[2 * i + 1] : a1[2 * i], send = odd2 ? a1[2 * i] : a1[2 * i + 1];
-                    TA s = keep + dpp_val<0x4E>(send);  // lane ^ 2
-                    s += dpp_val<0x124>(s);             // row rotate 4
-                    s += dpp_val<0x128>(s);             // row rotate 8
-                    a2[i] = s;
-                }
-                if constexpr (TR == 8) prow = (lane & 4) ? a2[1] : a2[0];
-                else prow = a2[0];
-            }
-        }
-        ++alternations;
-        if constexpr (SOLO) {
-            if (tc < TR) lds_s[cur ^ 1][tr * TR + tc] = (prow < 0) ? kNegByte : kPosByte;
-        } else {
-        ++seq_u;
-        {
-            uint64_t* mine = res_slot(a, 0, seq_u, wg);
-            if (tc < TR) res_publish(mine + tr * TR + tc, BM, (TX)prow, seq_u);
-            if (tid == 0) {
-                res_publish_f64(mine + W * BM, cpart, seq_u);
-                if (norm_stage == 1) res_publish_f64(mine + W * BM + 2, fsq_block, seq_u);  // (only the exchange after an update)
-            }
-        }
-        for (int d = 0; d < a.poll_delay; ++d) __builtin_amdgcn_s_sleep(1);
-        {
-            // gather: thread (row, half) adds eight members in order, the two halves are combined low
-            // first.  The last wave also fetches the piggybacked scalars (lane mod P = member), in the
-            // same batch of loads.
-            const int row = tid >> 1;
-            const char* base = res_slot_bytes(a, 0, seq_u, pr * P);
-            double hs = 0.0, x0 = 0.0, x1 = 0.0;
-            bool ok;
-            if (wv == NWV - 1) {
-                const uint32_t xoff = (uint32_t)((lane & (P - 1)) * kResSlotWords + W * BM) * 8u;
-                if (norm_stage == 1) ok = res_gather<TX, H, 4>(base, off_u, kResSlotWords * 8, BM * 8, base, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
-                else ok = res_gather<TX, H, 2>(base, off_u, kResSlotWords * 8, BM * 8, base, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
-                if (lane < P) {
-                    lds_x[0][lane] = x0;
-                    if (norm_stage == 1) lds_x[1][lane] = x1;
-                }
-            } else {
-                ok = res_gather<TX, H, 0>(base, off_u, kResSlotWords * 8, BM * 8, base, 0, seq_u, a.max_spin, hs, x0, x1, spin);
-            }
-            const double other = dpp_swap1_f64(hs);
-            const double u = half ? other + hs : hs + other;
-            if (half == 0 && row < BM) lds_s[cur ^ 1][row] = (u < 0.0) ? kNegByte : kPosByte;
-            if (!ok) lds_fail = 1;
-        }
-        }
-        // One barrier per exchange: the give-up flag is an LDS word that only ever goes from 0 to 1 and is read
-        // with the data behind the barrier (__syncthreads_or takes three barriers and two more LDS round trips).
-        __syncthreads();
-        const int failed = lds_fail;
-        const double cx = lds_x[0][lane & (P - 1)];
-        cur ^= 1;  // s_j = sgn(u)
-
-        // ================= column phase: v = R^T s (Algorithm 4 line 6), c = sum |v| (line 7).  Its sums are formed
-        // before the stop test below is looked at: the test's chain of additions hides behind them, and a term that
-        // ends here has formed one half step too many (once per term).
-        keep_narrow();
+        // One workgroup knows c at once: a term that is complete forms no further sums (the block below flips cur back).
+        const bool over = kEarly && j > 0 && (uniform_f64(cpart) <= c_prev || j >= a.max_iters || (LSQ && !(fabs(uniform_f64(cpart)) < INFINITY)));
+        int failed = 0;
+        double cx = 0.0;
         TA qv[TC / 4];
-        {
-            TI sf[TR];
-            sign_factors(&lds_s[cur][tr * TR], sf);
-            TA q[TC];
+        if (!over) {
+            // ================= row phase: u = R t (Algorithm 4 line 5)
+            // The signs enter as +-1.0 multipliers of a fused multiply-add: x * (+-1) is exact, so each step
+            // rounds exactly like the sign-flip-and-add of Section 3.4, in one instruction instead of two
+            // (this engine is bound by vector instructions and latency, not by memory).
+            keep_narrow();
+            TA prow;  // the row sum this lane publishes: row tc of the thread row's TR rows (lanes tc < TR)
+            {
+                TI tf[TC];
+                sign_factors(lds_t + tc * TC, tf);
+                TA p[TR];
 #pragma unroll
-            for (int c = 0; c < TC; ++c) {
-                TI s = 0;
+                for (int r = 0; r < TR; ++r) {
+                    // (SOLO: two runs of at most eight, so that no f32 sum is longer than it is on a 4 x 4 grid)
+                    constexpr int RUN = SOLO && TC > 4 ? TC / 2 : TC;
+                    TI s[TC / RUN];
 #pragma unroll
-                for (int r = 0; r < TR; ++r) s = res_fma((TI)x[r][c], sf[r], s);
-                q[c] = (TA)s;
+                    for (int h = 0; h < TC / RUN; ++h) {
+                        s[h] = 0;
+#pragma unroll
+                        for (int c = h * RUN; c < (h + 1) * RUN; ++c) s[h] = res_fma((TI)x[r][c], tf[c], s[h]);
+                    }
+                    if constexpr (TC / RUN == 2) p[r] = (TA)(s[0] + s[1]);
+                    else p[r] = (TA)s[0];
+                }
+                // Sum over the 16 lanes that share these rows, lane distances 1, 2, 4, 8.  At distances 1 and 2 a lane
+                // keeps only the rows whose low index bits are its own (it hands the others to its neighbour), which
+                // halves the registers each time: lane tc ends with rows tc mod 4 and 4 + tc mod 4.
+                const bool odd1 = (lane & 1) != 0, odd2 = (lane & 2) != 0;
+                TA a1[TR / 2];
+#pragma unroll
+                for (int i = 0; i < TR / 2; ++i) {
+                    const TA keep = odd1 ? p[2 * i + 1] : p[2 * i], send = odd1 ? p[2 * i] : p[2 * i + 1];
+                    a1[i] = keep + dpp_val<0xB1>(send);  // lane ^ 1
+                }
+                if constexpr (TR == 2) {
+                    TA s = a1[0];
+                    s += dpp_val<0x4E>(s);   // lane ^ 2
+                    s += dpp_val<0x124>(s);  // row rotate 4
+                    s += dpp_val<0x128>(s);  // row rotate 8
+                    prow = s;
+                } else {
+                    TA a2[TR / 4];
+#pragma unroll
+                    for (int i = 0; i < TR / 4; ++i) {
+                        const TA keep = odd2 ? a1[2 * i + 1] : a1[2 * i], send = odd2 ? a1[2 * i] : a1[2 * i + 1];
+                        TA s = keep + dpp_val<0x4E>(send);  // lane ^ 2
+                        s += dpp_val<0x124>(s);             // row rotate 4
+                        s += dpp_val<0x128>(s);             // row rotate 8
+                        a2[i] = s;
+                    }
+                    if constexpr (TR == 8) prow = (lane & 4) ? a2[1] : a2[0];
+                    else prow = a2[0];
+                }
             }
-            // the four thread rows of this wave hold the same columns 16 lanes apart: lane row i ends with the sums
-            // of columns i TC/4 .. (i + 1) TC/4 - 1
+            ++alternations;
+            if constexpr (SOLO) {
+                if (tc < TR) lds_s[cur ^ 1][tr * TR + tc] = (prow < 0) ? kNegByte : kPosByte;
+            } else {
+                ++seq_u;
+                {
+                    uint64_t* mine = res_slot(a, 0, seq_u, wg);
+                    if (tc < TR) res_publish(mine + tr * TR + tc, BM, (TX)prow, seq_u);
+                    if (tid == 0) {
+                        res_publish_f64(mine + W * BM, cpart, seq_u);
+                        if (norm_stage == 1) res_publish_f64(mine + W * BM + 2, fsq_block, seq_u);  // (only the exchange after an update)
+                    }
+                }
+                for (int d = 0; d < a.poll_delay; ++d) __builtin_amdgcn_s_sleep(1);
+                {
+                    // gather: thread (row, half) adds eight members in order, the two halves are combined low
+                    // first.  The last wave also fetches the piggybacked scalars (lane mod P = member), in the
+                    // same batch of loads.
+                    const int row = tid >> 1;
+                    const char* base = res_slot_bytes(a, 0, seq_u, pr * P);
+                    double hs = 0.0, x0 = 0.0, x1 = 0.0;
+                    bool ok;
+                    if (wv == NWV - 1) {
+                        const uint32_t xoff = (uint32_t)((lane & (P - 1)) * kResSlotWords + W * BM) * 8u;
+                        if (norm_stage == 1) ok = res_gather<TX, H, 4>(base, off_u, kResSlotWords * 8, BM * 8, base, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
+                        else ok = res_gather<TX, H, 2>(base, off_u, kResSlotWords * 8, BM * 8, base, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
+                        if (lane < P) {
+                            lds_x[0][lane] = x0;
+                            if (norm_stage == 1) lds_x[1][lane] = x1;
+                        }
+                    } else {
+                        ok = res_gather<TX, H, 0>(base, off_u, kResSlotWords * 8, BM * 8, base, 0, seq_u, a.max_spin, hs, x0, x1, spin);
+                    }
+                    const double other = dpp_swap1_f64(hs);
+                    const double u = half ? other + hs : hs + other;
+                    if (half == 0 && row < BM) lds_s[cur ^ 1][row] = (u < 0.0) ? kNegByte : kPosByte;
+                    if (!ok) lds_fail = 1;
+                }
+            }
+            // One barrier per exchange: the give-up flag is an LDS word that only ever goes from 0 to 1 and is read
+            // with the data behind the barrier (__syncthreads_or takes three barriers and two more LDS round trips).
+            __syncthreads();
+            failed = lds_fail;
+            cx = lds_x[0][lane & (P - 1)];
+            cur ^= 1;  // s_j = sgn(u)
+
+            // ================= column phase: v = R^T s (Algorithm 4 line 6), c = sum |v| (line 7).  Its sums are formed
+            // before the stop test below is looked at: the test's chain of additions hides behind them, and a term that
+            // ends here has formed one half step too many (once per term).
+            keep_narrow();
+            {
+                TI sf[TR];
+                sign_factors(&lds_s[cur][tr * TR], sf);
+                TA q[TC];
 #pragma unroll
-            for (int g = 0; g < TC / 4; ++g)
-                qv[g] = half32(half16(q[g], q[TC / 4 + g]), half16(q[TC / 2 + g], q[3 * (TC / 4) + g]));
+                for (int c = 0; c < TC; ++c) {
+                    TI s = 0;
+#pragma unroll
+                    for (int r = 0; r < TR; ++r) s = res_fma((TI)x[r][c], sf[r], s);
+                    q[c] = (TA)s;
+                }
+                // the four thread rows of this wave hold the same columns 16 lanes apart: lane row i ends with the sums
+                // of columns i TC/4 .. (i + 1) TC/4 - 1
+#pragma unroll
+                for (int g = 0; g < TC / 4; ++g)
+                    qv[g] = half32(half16(q[g], q[TC / 4 + g]), half16(q[TC / 2 + g], q[3 * (TC / 4) + g]));
+            }
+        } else {
+            cur ^= 1;
+            __syncthreads();  // (every wave has read lds_red, which the update writes)
         }
         double c_tot;
         if constexpr (SOLO) c_tot = uniform_f64(cpart);
@@ -724,46 +734,46 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
                 absv = fabs((double)v);
             }
         } else {
-        ++seq_v;
-        {
-            uint64_t* mine = res_slot(a, 1, seq_v, wg);
-            if (tid < BN) {
-                // (all loads in flight together, then the adds in wave order: the empty asm keeps the compiler from
-                // loading two, waiting, adding two)
-                TA w[NWV];
+            ++seq_v;
+            {
+                uint64_t* mine = res_slot(a, 1, seq_v, wg);
+                if (tid < BN) {
+                    // (all loads in flight together, then the adds in wave order: the empty asm keeps the compiler from
+                    // loading two, waiting, adding two)
+                    TA w[NWV];
 #pragma unroll
-                for (int q = 0; q < NWV; ++q) w[q] = lds_q[q][tid];
-                static_assert(NWV == 8, "operands of the asm");
-                asm volatile("" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(w[4]), "+v"(w[5]), "+v"(w[6]), "+v"(w[7]));
-                TA s = 0;
+                    for (int q = 0; q < NWV; ++q) w[q] = lds_q[q][tid];
+                    static_assert(NWV == 8, "operands of the asm");
+                    asm volatile("" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(w[4]), "+v"(w[5]), "+v"(w[6]), "+v"(w[7]));
+                    TA s = 0;
 #pragma unroll
-                for (int q = 0; q < NWV; ++q) s += w[q];
-                res_publish(mine + tid, BN, (TX)s, seq_v);
+                    for (int q = 0; q < NWV; ++q) s += w[q];
+                    res_publish(mine + tid, BN, (TX)s, seq_v);
+                }
+                if (norm_stage == 2 && tid == kResThreads - 1) res_publish_f64(mine + W * BN, frow, seq_v);
             }
-            if (norm_stage == 2 && tid == kResThreads - 1) res_publish_f64(mine + W * BN, frow, seq_v);
-        }
-        for (int d = 0; d < a.poll_delay_v; ++d) __builtin_amdgcn_s_sleep(1);
-        {
-            const int col = tid >> 1;
-            const char* base = res_slot_bytes(a, 1, seq_v, pc);
-            double hs = 0.0, x0 = 0.0, x1 = 0.0;
-            bool ok;
-            if (norm_stage == 2 && wv == NWV - 1) {
-                // the block-row sums of squares travel on this exchange once per term
-                ok = res_gather<TX, H, 2>(base, off_v, P * kResSlotWords * 8, BN * 8, base,
-                                          (uint32_t)((lane & (P - 1)) * P * kResSlotWords + W * BN) * 8u, seq_v, a.max_spin, hs, x0, x1, spin);
-                if (lane < P) lds_x[1][lane] = x0;
-            } else {
-                ok = res_gather<TX, H, 0>(base, off_v, P * kResSlotWords * 8, BN * 8, base, 0, seq_v, a.max_spin, hs, x0, x1, spin);
+            for (int d = 0; d < a.poll_delay_v; ++d) __builtin_amdgcn_s_sleep(1);
+            {
+                const int col = tid >> 1;
+                const char* base = res_slot_bytes(a, 1, seq_v, pc);
+                double hs = 0.0, x0 = 0.0, x1 = 0.0;
+                bool ok;
+                if (norm_stage == 2 && wv == NWV - 1) {
+                    // the block-row sums of squares travel on this exchange once per term
+                    ok = res_gather<TX, H, 2>(base, off_v, P * kResSlotWords * 8, BN * 8, base,
+                                              (uint32_t)((lane & (P - 1)) * P * kResSlotWords + W * BN) * 8u, seq_v, a.max_spin, hs, x0, x1, spin);
+                    if (lane < P) lds_x[1][lane] = x0;
+                } else {
+                    ok = res_gather<TX, H, 0>(base, off_v, P * kResSlotWords * 8, BN * 8, base, 0, seq_v, a.max_spin, hs, x0, x1, spin);
+                }
+                const double other = dpp_swap1_f64(hs);
+                const double v = half ? other + hs : hs + other;
+                if (half == 0 && col < BN) {
+                    lds_t[col] = (v < 0.0) ? kNegByte : kPosByte;
+                    absv = fabs(v);
+                }
+                if (!ok) lds_fail = 1;
             }
-            const double other = dpp_swap1_f64(hs);
-            const double v = half ? other + hs : hs + other;
-            if (half == 0 && col < BN) {
-                lds_t[col] = (v < 0.0) ? kNegByte : kPosByte;
-                absv = fabs(v);
-            }
-            if (!ok) lds_fail = 1;
-        }
         }
         absv = wave_sum_res(absv);
         if (lane == 0) lds_red[wv] = absv;
@@ -834,7 +844,7 @@ inline bool resident_shape(scd_dtype dt, int64_t m, int64_t n, int* p, int* tr, 
     static const int trs[3] = {2, 4, 8}, tcs[3] = {4, 8, 16};
     // One workgroup, whatever a thread can hold (odd f32 rows: 64 values, which are widened in every phase): three barriers
     // an alternation instead of two exchanges.  Us per alternation, 4 x 4 workgroups / one: f32 64x64 3.15 / 1.11, 128x128
-    // 3.01 / 1.38, 256x128 3.02 / 1.76, 192x192 2.97 / 2.53, 256x256 2.91 / 2.32; 61x67 3.69 / 1.44, 130x101 3.62 / 2.49,
+    // 3.01 / 1.38, 256x128 3.02 / 1.76, 192x192 2.97 / 2.53, 256x256 2.91 / 2.23; 61x67 3.69 / 1.44, 130x101 3.62 / 2.49,
     // 127x255 3.64 / 2.74; f64 128x128 3.56 / 1.47, 256x128 3.55 / 1.84, 127x255 3.59 / 2.28.
     {
         int r = 0, c = 0;
