@@ -454,7 +454,7 @@ hipError_t launch_expand(const uint64_t* S, const uint64_t* T, const void* c, sc
     if (dt == SCD_F64) {
         hipLaunchKernelGGL((expand_f64_kernel<double>), dim3(gridf), dim3(kExThreads), 0, st, S, T, (const double*)c, m, n, w,
                            (double*)out);
-    } else if (w <= kExFewTerms || !scratch) {
+    } else if (w <= kExFewTerms || !scratch || mw >= 1 << 29 || nw >= 1 << 29) {  // (rows of bits of 4 GiB and more: 32-bit strides)
         hipLaunchKernelGGL((expand_f64_kernel<float>), dim3(gridf), dim3(kExThreads), 0, st, S, T, (const float*)c, m, n, w,
                            (float*)out);
     } else {
