@@ -165,7 +165,7 @@ static hipError_t launch_resident_t(const ResidentArgs& a, hipStream_t st)
     // does the grid of P x P blocks of 32 TR x 16 TC overhang the matrix?
     const bool padded = (int64_t)P * 32 * TR != a.m || (int64_t)P * 16 * TC != a.n;
     if constexpr (P == 1 && sizeof(TE) == 4) {
-        // f32 sums inside a thread, f64 across threads; rows that are no 16-byte steps: f64 from the first addition
+        // f32 sums inside a thread (columns: a wave), f64 beyond; rows that are no 16-byte steps: f64 from the first addition
         if (a.n % ResVec<float>::N != 0) return launch_resident_k<TE, double, double, TR, TC, P, true>(a, st);
         return padded ? launch_resident_k<TE, double, float, TR, TC, P, true>(a, st) : launch_resident_k<TE, double, float, TR, TC, P, false>(a, st);
     } else {

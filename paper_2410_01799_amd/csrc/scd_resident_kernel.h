@@ -385,9 +385,10 @@ __device__ __forceinline__ void res_subtract_terms(const ResidentArgs& a, int64_
 // PAD: the grid overhangs the matrix (a template parameter: the 128 row/column tests of a thread's tile are
 // invariants of the whole launch, and a kernel that has to keep them takes twice the instructions and runs out of
 // scalar registers even when no test ever fails).
-// SOLO (P = 1): a matrix that one workgroup holds.  Its f32 sums end inside a thread, with at most eight entries added one
-// after the other; across threads they are f64 (rms error of the row and column sums against f64, 4 x 4 workgroups / one:
-// 256x256 6.9e-8, 7.4e-8 / 6.1e-8, 5.7e-8; 64x64 7.1e-8, 7.6e-8 / 4.3e-8, 3.0e-8).  Nothing is published or waited for.
+// SOLO (P = 1): a matrix that one workgroup holds.  A thread adds at most eight entries one after the other; its row sums
+// are f64 across threads, its column sums f32 across the four thread rows of a wave (f64 there too: 2.24 instead of 2.17 us
+// per alternation at 256x256) and f64 across waves (emulated, rms error of the row and column sums against f64, 4 x 4 workgroups / one: 256x256
+// 6.9e-8, 7.4e-8 / 6.1e-8, 7.0e-8; 64x64 7.1e-8, 7.6e-8 / 4.3e-8, 5.2e-8).  Nothing is published or waited for.
 // TA: type of the sums inside a workgroup, TX: of the sums that it publishes (see resident_sums; SOLO: of a thread's sums).
 // LSQ: one greedy cut of A - sum c_j s_j t_j^T for the coefficients that the refit of the last term left; the position of
 // the loop is the device's (a.lsq), and the refit follows as a launch of its own.
@@ -606,19 +607,19 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
             {
                 TI sf[TR];
                 sign_factors(&lds_s[cur][tr * TR], sf);
-                TA q[TC];
+                TI q[TC];
 #pragma unroll
                 for (int c = 0; c < TC; ++c) {
                     TI s = 0;
 #pragma unroll
                     for (int r = 0; r < TR; ++r) s = res_fma((TI)x[r][c], sf[r], s);
-                    q[c] = (TA)s;
+                    q[c] = s;
                 }
                 // the four thread rows of this wave hold the same columns 16 lanes apart: lane row i ends with the sums
                 // of columns i TC/4 .. (i + 1) TC/4 - 1
 #pragma unroll
                 for (int g = 0; g < TC / 4; ++g)
-                    qv[g] = half32(half16(q[g], q[TC / 4 + g]), half16(q[TC / 2 + g], q[3 * (TC / 4) + g]));
+                    qv[g] = (TA)half32(half16(q[g], q[TC / 4 + g]), half16(q[TC / 2 + g], q[3 * (TC / 4) + g]));
             }
         } else {
             cur ^= 1;
@@ -843,8 +844,8 @@ inline bool resident_shape(scd_dtype dt, int64_t m, int64_t n, int* p, int* tr, 
     static const int grids[3] = {4, 8, 16};
     static const int trs[3] = {2, 4, 8}, tcs[3] = {4, 8, 16};
     // One workgroup, whatever a thread can hold (odd f32 rows: 64 values, which are widened in every phase): three barriers
-    // an alternation instead of two exchanges.  Us per alternation, 4 x 4 workgroups / one: f32 64x64 3.15 / 1.11, 128x128
-    // 3.01 / 1.38, 256x128 3.02 / 1.76, 192x192 2.97 / 2.53, 256x256 2.91 / 2.23; 61x67 3.69 / 1.44, 130x101 3.62 / 2.49,
+    // an alternation instead of two exchanges.  Us per alternation, 4 x 4 workgroups / one: f32 64x64 3.15 / 1.07, 128x128
+    // 3.01 / 1.31, 256x128 3.02 / 1.60, 192x192 2.97 / 2.40, 256x256 2.91 / 2.17; 61x67 3.69 / 1.43, 130x101 3.62 / 2.37,
     // 127x255 3.64 / 2.74; f64 128x128 3.56 / 1.47, 256x128 3.55 / 1.84, 127x255 3.59 / 2.28.
     {
         int r = 0, c = 0;
