@@ -196,7 +196,7 @@ int scd_expand(const uint64_t* const* signs, const void* c, scd_dtype dt, int or
  * For k = 0..w-1: greedy signed cut (Algorithm 4) of R_k = A - S_k diag(c_k) T_k^T from the keyed random start
  * of term k, append its (s, t), then refit ALL coefficients: c_{k+1} = argmin ||A - S_{k+1} diag(c) T_{k+1}^T||_F
  * by the normal equations of Section 3.3 (Gram matrix from popcounts of the bitsets, Cholesky factor grown by a
- * row per term, f64).  The remainder is kept implicit, A is not modified.  Matrices only.
+ * row per term, f64).  A is not modified.  Matrices only.
  * A: device, m x n row-major of dt.  S, T: device out, term-major bitsets as in scd_decompose.  c: device out,
  * w values of dt: the FINAL coefficients c_w of all terms (they are direct coefficients of s_j t_j^T, like the
  * normalised c of scd_decompose).  fro_trace: device out, w + 1 doubles, ||A - S_k diag(c_k) T_k^T||_F for
