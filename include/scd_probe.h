@@ -46,6 +46,13 @@ int scd_engine(const scd_ctx* ctx, int* engine, double* last_launch_seconds, dou
  * buffers.  For tests of the host arithmetic against the bounds the kernel assumes. */
 int scd_stream_geometry(scd_dtype dt, int order, const int64_t* dims, int limit, int64_t out[8]);
 
+/* scd_lsq_decompose with a say in how the cuts are found, for tests and measurement.  cuts = 0: as scd_lsq_decompose
+ * does; 1: by the three launches per sweep that serve what the register-resident engine does not take (SCD_EINVAL where
+ * they do not take the matrix).  terms: host, 3 values, may be NULL: terms whose cuts came from the register-resident
+ * engine, from the sweeps, and from the loop on the host. */
+int scd_lsq_decompose_form(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uint64_t seed, int32_t max_iters, void* stream,
+                           uint64_t* S, uint64_t* T, void* c, double* fro_trace, int32_t* iters, int cuts, int64_t* terms);
+
 /* Measurement: run n (<= 4096) further sweeps of the greedy loop with a HIP event before and after
  * each kernel of the pass over the remainder; returns the average duration of the row-pass launch
  * and of the reduce launch that follows it (host pointers, seconds).  The terms found meanwhile are

@@ -1505,11 +1505,17 @@ int check_tensor_args(const void* A, scd_dtype dt, int order, const int64_t* dim
 
 namespace {
 
+// How a call finds its cuts (see scd_lsq_decompose_form) and how many terms came from where.
+struct LsqForm {
+    int cuts = 0;
+    int64_t terms[3] = {0, 0, 0};  // register-resident, sweeps, host loop
+};
+
 // Everything is enqueued blindly; launches past the end return at once.  `resident`: two launches per term, its cut on the
 // register-resident engine and the refit (SCD_ETIMEOUT where the workgroups did not all get a compute unit); else three per
 // sweep, about as many sweeps as the terms so far took.
 int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uint64_t seed, int32_t max_iters, hipStream_t st, uint64_t* S,
-               uint64_t* T, void* cvec, double* fro_trace, int32_t* iters, bool resident)
+               uint64_t* T, void* cvec, double* fro_trace, int32_t* iters, bool resident, LsqForm& form)
 {
     const int64_t mw = words_for(m), nw = words_for(n);
     const int nsq = 256;
@@ -1644,6 +1650,7 @@ int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uin
         if (pin->state.k > 0) per_term = (double)swept / (double)pin->state.k;
     }
     const LsqState fin = pin->state;
+    form.terms[resident ? 0 : 1] = fin.k;
     if (fin.status == 3) return cleanup(SCD_ETIMEOUT);
     if (fin.status == 2) return cleanup(SCD_ENONFINITE);
     if (fin.status == 1) return cleanup(SCD_ESINGULAR);
@@ -1654,13 +1661,10 @@ int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uin
     return cleanup(fin.warn ? SCD_WMAXITER : SCD_OK);
 }
 
-}  // namespace
-
 // ---------------------------------------------------------------------------------------------- Algorithms 6 and 14
 
-int scd_lsq_decompose_tensor(const void* A, scd_dtype dt, int order, const int64_t* dims, int64_t w, uint64_t seed,
-                             int32_t max_iters, void* stream, uint64_t* const* signs, void* cvec, double* fro_trace,
-                             int32_t* iters)
+int lsq_decompose(const void* A, scd_dtype dt, int order, const int64_t* dims, int64_t w, uint64_t seed, int32_t max_iters, void* stream,
+                  uint64_t* const* signs, void* cvec, double* fro_trace, int32_t* iters, LsqForm& form)
 {
     int64_t total = 0;
     SCD_TRY(check_tensor_args(A, dt, order, dims, w, max_iters, fro_trace, &total));
@@ -1673,12 +1677,14 @@ int scd_lsq_decompose_tensor(const void* A, scd_dtype dt, int order, const int64
         // launches per sweep / here: 64x64 f32 to 16 terms 1680 / 720, 100x900 f32 to 32 2170 / 1280, 1024x1024 f32 to 32
         // 15100 / 5000, 2048x2048 f64 to 16 26000 / 5570, 4096x2048 f32 to 8 9380 / 2360, 1024x1024 f32 to 512 474000 /
         // 244000; slower on none that was tried.
-        if (resident_supported(SCD_F64, 2, dims) && resident_workgroups(SCD_F64, dims) <= device_cus()) {
-            const int rc = lsq_matrix(A, dt, dims[0], dims[1], w, seed, max_iters, (hipStream_t)stream, signs[0], signs[1], cvec, fro_trace, iters, true);
+        const bool sweeps = lsq_matrix_supported(dt, dims[0], dims[1]);
+        if (form.cuts == 1 && !sweeps) return SCD_EINVAL;
+        if (form.cuts != 1 && resident_supported(SCD_F64, 2, dims) && resident_workgroups(SCD_F64, dims) <= device_cus()) {
+            const int rc = lsq_matrix(A, dt, dims[0], dims[1], w, seed, max_iters, (hipStream_t)stream, signs[0], signs[1], cvec, fro_trace, iters, true, form);
             if (rc != SCD_ETIMEOUT) return rc;
         }
-        if (lsq_matrix_supported(dt, dims[0], dims[1]))
-            return lsq_matrix(A, dt, dims[0], dims[1], w, seed, max_iters, (hipStream_t)stream, signs[0], signs[1], cvec, fro_trace, iters, false);
+        if (sweeps)
+            return lsq_matrix(A, dt, dims[0], dims[1], w, seed, max_iters, (hipStream_t)stream, signs[0], signs[1], cvec, fro_trace, iters, false, form);
     }
     hipStream_t st = (hipStream_t)stream;
     const int64_t wl = w > 0 ? w : 1;
@@ -1775,11 +1781,35 @@ int scd_lsq_decompose_tensor(const void* A, scd_dtype dt, int order, const int64
         LQ(hipMemcpyAsync(host + 3, status, 4, hipMemcpyDeviceToHost, st));
         LQ(hipStreamSynchronize(st));  // host[2] is reused by the next term
         if (*(const int*)(host + 3) != 0) return cleanup(SCD_ESINGULAR);
+        form.terms[2] = k + 1;
     }
     LQ(launch_lsq_cast(c, w, dt, cvec, st));
     if (iters && w > 0) LQ(hipMemcpyAsync(iters, it_host.data(), (size_t)w * 4, hipMemcpyHostToDevice, st));
     LQ(hipStreamSynchronize(st));
     return cleanup(rc);
+}
+
+}  // namespace
+
+int scd_lsq_decompose_tensor(const void* A, scd_dtype dt, int order, const int64_t* dims, int64_t w, uint64_t seed,
+                             int32_t max_iters, void* stream, uint64_t* const* signs, void* cvec, double* fro_trace,
+                             int32_t* iters)
+{
+    LsqForm form;
+    return lsq_decompose(A, dt, order, dims, w, seed, max_iters, stream, signs, cvec, fro_trace, iters, form);
+}
+
+int scd_lsq_decompose_form(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uint64_t seed, int32_t max_iters, void* stream,
+                           uint64_t* S, uint64_t* T, void* cvec, double* fro_trace, int32_t* iters, int cuts, int64_t* terms)
+{
+    if (cuts < 0 || cuts > 1) return SCD_EINVAL;
+    const int64_t dims[2] = {m, n};
+    uint64_t* const signs[2] = {S, T};
+    LsqForm form;
+    form.cuts = cuts;
+    const int rc = lsq_decompose(A, dt, 2, dims, w, seed, max_iters, stream, signs, cvec, fro_trace, iters, form);
+    for (int i = 0; terms && i < 3; ++i) terms[i] = form.terms[i];
+    return rc;
 }
 
 // ---------------------------------------------------------------------------------------------- real last mode

@@ -26,7 +26,7 @@ EXPORTS = [
     "scd_width", "scd_results", "scd_remainder", "scd_set_remainder", "scd_row_signed_sum", "scd_col_signed_sum",
     "scd_expand", "scd_pack", "scd_unpack", "scd_rng_signs", "scd_strerror", "scd_last_hip_error", "scd_traffic",
     "scd_probe_stream", "scd_profile_sweeps", "scd_probe_exchange", "scd_engine", "scd_set_workgroups",
-    "scd_apply", "scd_apply_workspace_bytes", "scd_lsq_decompose", "scd_lsq_decompose_tensor", "scd_decompose_scalars", "scd_sparse_flips",
+    "scd_apply", "scd_apply_workspace_bytes", "scd_lsq_decompose", "scd_lsq_decompose_tensor", "scd_lsq_decompose_form", "scd_decompose_scalars", "scd_sparse_flips",
     "scd_col_signed_sum_noalloc", "scd_set_option", "scd_get_option", "scd_stream_geometry", "scd_release_memory",
 ]
 
@@ -68,6 +68,7 @@ def lib() -> C.CDLL:
         L.scd_get_option.argtypes = [vp, C.c_int, pi64]
         L.scd_sparse_flips.argtypes = [vp, pi64, pi64]
         L.scd_lsq_decompose.argtypes = [vp, C.c_int, i64, i64, i64, C.c_uint64, i32, vp, vp, vp, vp, vp, vp]
+        L.scd_lsq_decompose_form.argtypes = [vp, C.c_int, i64, i64, i64, C.c_uint64, i32, vp, vp, vp, vp, vp, vp, C.c_int, pi64]
         L.scd_lsq_decompose_tensor.argtypes = [vp, C.c_int, C.c_int, pi64, i64, C.c_uint64, i32, vp, pvp, vp, vp, vp]
         L.scd_decompose_scalars.argtypes = [vp, C.c_int, C.c_int, pi64, i64, C.c_uint64, i32, vp, pvp, vp, vp, vp]
         L.scd_apply_workspace_bytes.argtypes = [i64, i64, i64]
@@ -216,6 +217,23 @@ def scd_lsq_decompose(A: torch.Tensor, w: int, seed: int, max_iters: int = 4096)
                                             _stream(), _ptr_array(signs), _ptr(c), _ptr(trace), _ptr(iters))
     st = _check(st, "scd_lsq_decompose")
     return dict(signs=signs, c=c, trace=trace, iters=iters, status=st)
+
+
+def scd_lsq_decompose_form(A: torch.Tensor, w: int, seed: int, max_iters: int = 4096, cuts: int = 0) -> dict:
+    """scd_lsq_decompose of a matrix with a say in how its cuts are found (see scd_probe.h): also returns
+    terms=(register-resident, sweeps, host loop)."""
+    A = _dev(A, "A")
+    m, n = A.shape
+    w = int(w)
+    signs = [_bits(words(d), A.device, rows=w) for d in A.shape]
+    c = torch.empty(w, dtype=A.dtype, device=A.device)
+    trace = torch.empty(w + 1, dtype=torch.float64, device=A.device)
+    iters = torch.empty(w, dtype=torch.int32, device=A.device)
+    terms = (C.c_int64 * 3)()
+    st = lib().scd_lsq_decompose_form(_ptr(A), _dt(A), m, n, w, int(seed), int(max_iters), _stream(), _ptr(signs[0]), _ptr(signs[1]),
+                                      _ptr(c), _ptr(trace), _ptr(iters), int(cuts), terms)
+    st = _check(st, "scd_lsq_decompose_form")
+    return dict(signs=signs, c=c, trace=trace, iters=iters, status=st, terms=tuple(terms))
 
 
 def scd_decompose_scalars(A: torch.Tensor, w: int, seed: int, max_iters: int = 4096) -> dict:

@@ -24,11 +24,12 @@ def gauss(shape, seed, dtype=np.float32):
     return np.random.Generator(np.random.PCG64(seed)).standard_normal(shape).astype(dtype)
 
 
-def run_and_check(scd, oracle, A, w, seed):
+def run_and_check(scd, oracle, A, w, seed, **form):
     m, n = A.shape
     f32 = A.dtype == np.float32
     A64 = A.astype(np.float64)
-    res = scd.scd_lsq_decompose(torch.from_numpy(A).cuda(), w, seed)
+    x = torch.from_numpy(A).cuda()
+    res = scd.scd_lsq_decompose_form(x, w, seed, **form) if form else scd.scd_lsq_decompose(x, w, seed)
     assert res["status"] == 0
     S, T = to_np_bits(res["signs"][0]), to_np_bits(res["signs"][1])
     c = res["c"].cpu().numpy().astype(np.float64)
@@ -68,13 +69,48 @@ def test_lsq_matches_oracle_in_lockstep(scd, oracle, m, n, w, dtype):
     run_and_check(scd, oracle, gauss((m, n), 7 * m + n, dtype), w, 3)
 
 
-# the device loop at the ends of its range (64 words a side, strips of 1 MiB; f64: 2048 entries), one word past them on
-# the other driver, single words, rows that are no multiple of 16 bytes
+# long and thin matrices and small ones of single words, rows that are no multiple of 16 bytes: on the register-resident
+# engine, but for 130x4097, whose rows are one word longer than it takes (the host loop)
 @pytest.mark.parametrize("m,n,w,dtype", [(3, 5, 2, np.float32), (63, 65, 8, np.float32), (64, 64, 8, np.float64),
                                          (129, 4096, 5, np.float32), (4096, 67, 5, np.float32), (130, 4097, 4, np.float32),
                                          (2048, 66, 5, np.float64), (70, 2050, 4, np.float64), (257, 515, 6, np.float32)])
 def test_lsq_device_loop_range(scd, oracle, m, n, w, dtype):
     run_and_check(scd, oracle, gauss((m, n), 3 * m + n, dtype), w, 5)
+
+
+# the sweeps at the ends of their range (64 words a side, strips of 1 MiB; f64: 2048 entries): both types, 16-byte and single
+# loads, one word or workgroup and many.  Of these only the last two get there by rule: f32 beyond the register files, and
+# rows of three entries
+@pytest.mark.parametrize("m,n,w,dtype,cuts", [(3, 5, 2, np.float32, 1), (63, 65, 8, np.float32, 1), (64, 64, 8, np.float64, 1), (256, 256, 12, np.float64, 1),
+                                              (129, 4096, 5, np.float32, 1), (4096, 67, 5, np.float32, 1), (2048, 66, 5, np.float64, 1),
+                                              (70, 2048, 4, np.float64, 1), (65, 131, 8, np.float64, 1), (1030, 520, 8, np.float32, 1),
+                                              (257, 515, 6, np.float32, 1), (2052, 2056, 2, np.float32, 0), (2050, 2051, 2, np.float32, 0),
+                                              (40, 3, 2, np.float64, 0)])
+def test_lsq_sweeps_range(scd, oracle, m, n, w, dtype, cuts):
+    res, _ = run_and_check(scd, oracle, gauss((m, n), 3 * m + n, dtype), w, 5, cuts=cuts)
+    assert res["terms"] == (0, w, 0)
+
+
+def test_lsq_sweeps_edges(scd):
+    # the zero matrix repeats its first term; an iteration cap is a warning; reruns are the same bits
+    with pytest.raises(scd.ScdError) as e:
+        scd.scd_lsq_decompose_form(torch.zeros(40, 72, device="cuda"), 3, 1, cuts=1)
+    assert e.value.code == scd.ESINGULAR
+    A = torch.from_numpy(gauss((70, 50), 1)).cuda()
+    capped = scd.scd_lsq_decompose_form(A, 3, 1, max_iters=1, cuts=1)
+    assert capped["status"] == scd.WMAXITER and torch.all(capped["iters"] == 1)
+    one, two = (scd.scd_lsq_decompose_form(A, 12, 1, cuts=1) for _ in range(2))
+    assert torch.equal(one["c"], two["c"]) and torch.equal(one["trace"], two["trace"]) and one["terms"] == (0, 12, 0)
+
+
+def test_lsq_form_is_checked(scd):
+    A = torch.from_numpy(gauss((130, 4097), 1)).cuda()
+    for cuts in (-1, 1, 2):                               # the sweeps do not take 65 words
+        with pytest.raises(scd.ScdError) as e:
+            scd.scd_lsq_decompose_form(A, 2, 1, cuts=cuts)
+        assert e.value.code == scd.EINVAL
+    assert scd.scd_lsq_decompose_form(A, 2, 1)["terms"] == (0, 0, 2)
+    assert scd.scd_lsq_decompose_form(A[:, :4096].contiguous(), 2, 1)["terms"] == (2, 0, 0)
 
 
 # cuts on the register-resident engine in f64: exact fits of its grids and one row or column past them, the smallest and
@@ -91,11 +127,12 @@ def test_lsq_refit_past_one_wave(scd, oracle):
     run_and_check(scd, oracle, gauss((96, 84), 11, np.float64), 94, 7)
 
 
-def test_lsq_unaligned_input(scd):
+@pytest.mark.parametrize("cuts", [0, 1])
+def test_lsq_unaligned_input(scd, cuts):
     flat = torch.from_numpy(gauss((1, 96 * 128 + 1), 8)).cuda().reshape(-1)
     off = flat[1:].reshape(96, 128)                       # contiguous, rows 4 bytes past a 16-byte boundary
     assert off.data_ptr() % 16 == 4
-    a, b = scd.scd_lsq_decompose(off, 12, 4), scd.scd_lsq_decompose(off.clone(), 12, 4)
+    a, b = (scd.scd_lsq_decompose_form(x, 12, 4, cuts=cuts) for x in (off, off.clone()))
     assert torch.equal(a["signs"][0], b["signs"][0]) and torch.equal(a["signs"][1], b["signs"][1])
     torch.testing.assert_close(a["c"], b["c"], rtol=1e-6, atol=0)
     torch.testing.assert_close(a["trace"], b["trace"], rtol=1e-12, atol=0)
