@@ -1508,6 +1508,7 @@ namespace {
 // How a call finds its cuts (see scd_lsq_decompose_form) and how many terms came from where.
 struct LsqForm {
     int cuts = 0;
+    int64_t max_spin = 1 << 22;    // re-reads after which a wait of the register-resident cuts gives up
     int64_t terms[3] = {0, 0, 0};  // register-resident, sweeps, host loop
 };
 
@@ -1609,8 +1610,8 @@ int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uin
         r.n = n;
         r.seed = seed;
         r.max_iters = max_iters;
-        r.max_spin = 1 << 22;
-        resident_poll_delays(SCD_F64, dims, 0.0, 16, &r.poll_delay, &r.poll_delay_v);
+        r.max_spin = (int32_t)form.max_spin;
+        resident_poll_delays(SCD_F64, dims, 0.0, form.max_spin ? 16 : 0, &r.poll_delay, &r.poll_delay_v);
         r.xbuf = xbuf;
         r.S = S;
         r.T = T;
@@ -1650,7 +1651,7 @@ int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uin
         if (pin->state.k > 0) per_term = (double)swept / (double)pin->state.k;
     }
     const LsqState fin = pin->state;
-    form.terms[resident ? 0 : 1] = fin.k;
+    form.terms[resident ? 0 : 1] = fin.status == 3 ? 0 : fin.k;
     if (fin.status == 3) return cleanup(SCD_ETIMEOUT);
     if (fin.status == 2) return cleanup(SCD_ENONFINITE);
     if (fin.status == 1) return cleanup(SCD_ESINGULAR);
@@ -1679,7 +1680,7 @@ int lsq_decompose(const void* A, scd_dtype dt, int order, const int64_t* dims, i
         // 244000; slower on none that was tried.
         const bool sweeps = lsq_matrix_supported(dt, dims[0], dims[1]);
         if (form.cuts == 1 && !sweeps) return SCD_EINVAL;
-        if (form.cuts != 1 && resident_supported(SCD_F64, 2, dims) && resident_workgroups(SCD_F64, dims) <= device_cus()) {
+        if (form.cuts != 1 && resident_supported(SCD_F64, 2, dims) && resident_workgroups(SCD_F64, dims) <= resident_lsq_room(dims)) {
             const int rc = lsq_matrix(A, dt, dims[0], dims[1], w, seed, max_iters, (hipStream_t)stream, signs[0], signs[1], cvec, fro_trace, iters, true, form);
             if (rc != SCD_ETIMEOUT) return rc;
         }
@@ -1800,13 +1801,14 @@ int scd_lsq_decompose_tensor(const void* A, scd_dtype dt, int order, const int64
 }
 
 int scd_lsq_decompose_form(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uint64_t seed, int32_t max_iters, void* stream,
-                           uint64_t* S, uint64_t* T, void* cvec, double* fro_trace, int32_t* iters, int cuts, int64_t* terms)
+                           uint64_t* S, uint64_t* T, void* cvec, double* fro_trace, int32_t* iters, int cuts, int64_t max_spin, int64_t* terms)
 {
-    if (cuts < 0 || cuts > 1) return SCD_EINVAL;
+    if (cuts < 0 || cuts > 1 || max_spin < 0 || max_spin > INT32_MAX - 1) return SCD_EINVAL;
     const int64_t dims[2] = {m, n};
     uint64_t* const signs[2] = {S, T};
     LsqForm form;
     form.cuts = cuts;
+    form.max_spin = max_spin;
     const int rc = lsq_decompose(A, dt, 2, dims, w, seed, max_iters, stream, signs, cvec, fro_trace, iters, form);
     for (int i = 0; terms && i < 3; ++i) terms[i] = form.terms[i];
     return rc;

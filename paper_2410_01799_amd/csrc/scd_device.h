@@ -161,6 +161,7 @@ bool resident_supported(scd_dtype dt, int order, const int64_t* dims);
 int resident_workgroups(scd_dtype dt, const int64_t* dims);  // workgroups of the launch for a supported shape
 void resident_poll_delays(scd_dtype dt, const int64_t* dims, double fro, int delay, int32_t* rows, int32_t* cols);  // of the two exchanges
 hipError_t launch_resident(const ResidentArgs& a, scd_dtype dt, hipStream_t st);
+int resident_lsq_room(const int64_t* dims);  // workgroups of that launch the device holds at once (0: none, or no such launch)
 hipError_t launch_resident_lsq(const ResidentArgs& a, hipStream_t st);  // shapes that resident_supported takes in f64
 
 // Sparse engine (scd_sparse.hip): cached products updated from the flipped signs only; keeps R and its

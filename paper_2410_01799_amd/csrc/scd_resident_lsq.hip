@@ -7,53 +7,78 @@
 
 namespace scd {
 
+// What the dispatch does with the kernel of a shape: launch it (st), or ask how many of its workgroups the device holds.
+// All P x P must be resident at once (see launch_resident_k): the caller asks once, ahead of a call's launches.
+struct LsqDo {
+    const ResidentArgs* a;
+    hipStream_t st;
+    int room;
+};
+
 template <int TR, int TC, int P>
-static hipError_t launch_lsq_k(const ResidentArgs& a, hipStream_t st)
+static hipError_t lsq_k(LsqDo& d)
 {
-    // all P x P workgroups at once, as in launch_resident_k
+    if (d.a) {
+        hipLaunchKernelGGL((resident_kernel<double, double, double, TR, TC, P, true, true>), dim3(P * P), dim3(kResThreads), 0, d.st, *d.a);
+        return hipGetLastError();
+    }
     int dev = 0, per_cu = 0, cus = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess)
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, resident_kernel<double, double, double, TR, TC, P, true, true>,
                                                          kResThreads, 0);
-    if (e != hipSuccess) return e;
-    if ((int64_t)per_cu * cus < P * P) return hipErrorCooperativeLaunchTooLarge;
-    hipLaunchKernelGGL((resident_kernel<double, double, double, TR, TC, P, true, true>), dim3(P * P), dim3(kResThreads), 0, st, a);
-    return hipGetLastError();
+    if (e == hipSuccess) d.room = per_cu > 0 ? cus : 0;  // (leases count one workgroup per compute unit)
+    return e;
 }
 
 template <int P>
-static hipError_t launch_lsq_p(const ResidentArgs& a, int tr, int tc, hipStream_t st)
+static hipError_t lsq_p(LsqDo& d, int tr, int tc)
 {
     const int key = tr * 100 + tc;
     switch (key) {
-        case 204: return launch_lsq_k<2, 4, P>(a, st);
-        case 208: return launch_lsq_k<2, 8, P>(a, st);
-        case 404: return launch_lsq_k<4, 4, P>(a, st);
-        case 408: return launch_lsq_k<4, 8, P>(a, st);
+        case 204: return lsq_k<2, 4, P>(d);
+        case 208: return lsq_k<2, 8, P>(d);
+        case 404: return lsq_k<4, 4, P>(d);
+        case 408: return lsq_k<4, 8, P>(d);
         default: break;
     }
     if constexpr (P >= 8 || P == 1) {
         switch (key) {
-            case 216: return launch_lsq_k<2, 16, P>(a, st);
-            case 416: return launch_lsq_k<4, 16, P>(a, st);
-            case 804: return launch_lsq_k<8, 4, P>(a, st);
-            case 808: return launch_lsq_k<8, 8, P>(a, st);
+            case 216: return lsq_k<2, 16, P>(d);
+            case 416: return lsq_k<4, 16, P>(d);
+            case 804: return lsq_k<8, 4, P>(d);
+            case 808: return lsq_k<8, 8, P>(d);
             default: break;
         }
     }
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_resident_lsq(const ResidentArgs& a, hipStream_t st)
+static hipError_t lsq_do(LsqDo& d, int64_t m, int64_t n)
 {
     int p = 0, tr = 0, tc = 0;
-    if (!resident_shape(SCD_F64, a.m, a.n, &p, &tr, &tc)) return hipErrorInvalidValue;
-    if (p == 16) return launch_lsq_p<16>(a, tr, tc, st);
-    if (p == 8) return launch_lsq_p<8>(a, tr, tc, st);
-    if (p == 1) return launch_lsq_p<1>(a, tr, tc, st);
-    return launch_lsq_p<4>(a, tr, tc, st);
+    if (!resident_shape(SCD_F64, m, n, &p, &tr, &tc)) return hipErrorInvalidValue;
+    if (p == 16) return lsq_p<16>(d, tr, tc);
+    if (p == 8) return lsq_p<8>(d, tr, tc);
+    if (p == 1) return lsq_p<1>(d, tr, tc);
+    return lsq_p<4>(d, tr, tc);
+}
+
+int resident_lsq_room(const int64_t* dims)
+{
+    LsqDo d = {nullptr, nullptr, 0};
+    if (lsq_do(d, dims[0], dims[1]) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    return d.room;
+}
+
+hipError_t launch_resident_lsq(const ResidentArgs& a, hipStream_t st)
+{
+    LsqDo d = {&a, st, 0};
+    return lsq_do(d, a.m, a.n);
 }
 
 }  // namespace scd

@@ -103,12 +103,24 @@ def test_lsq_sweeps_edges(scd):
     assert torch.equal(one["c"], two["c"]) and torch.equal(one["trace"], two["trace"]) and one["terms"] == (0, 12, 0)
 
 
+# a wait of the register-resident cuts that gives up (forced from the host: no re-reads): the sweeps, or for f64 above 2048
+# entries a side the host loop, take the call; one workgroup waits for nothing
+@pytest.mark.parametrize("m,n,w,dtype,terms", [(300, 520, 6, np.float32, (0, 6, 0)), (1024, 1024, 4, np.float64, (0, 4, 0)),
+                                               (2100, 70, 4, np.float64, (0, 0, 4)), (200, 100, 4, np.float64, (4, 0, 0))])
+def test_lsq_wait_that_gives_up(scd, oracle, m, n, w, dtype, terms):
+    res, _ = run_and_check(scd, oracle, gauss((m, n), 9 * m + n, dtype), w, 4, max_spin=0)
+    assert res["terms"] == terms
+
+
 def test_lsq_form_is_checked(scd):
     A = torch.from_numpy(gauss((130, 4097), 1)).cuda()
     for cuts in (-1, 1, 2):                               # the sweeps do not take 65 words
         with pytest.raises(scd.ScdError) as e:
             scd.scd_lsq_decompose_form(A, 2, 1, cuts=cuts)
         assert e.value.code == scd.EINVAL
+    with pytest.raises(scd.ScdError) as e:
+        scd.scd_lsq_decompose_form(A, 2, 1, max_spin=-1)
+    assert e.value.code == scd.EINVAL
     assert scd.scd_lsq_decompose_form(A, 2, 1)["terms"] == (0, 0, 2)
     assert scd.scd_lsq_decompose_form(A[:, :4096].contiguous(), 2, 1)["terms"] == (2, 0, 0)
 
