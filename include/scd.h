@@ -202,6 +202,10 @@ int scd_expand(const uint64_t* const* signs, const void* c, scd_dtype dt, int or
  * normalised c of scd_decompose).  fro_trace: device out, w + 1 doubles, ||A - S_k diag(c_k) T_k^T||_F for
  * k = 0..w.  iters: device out, optional.  w <= SCD_LSQ_MAX_WIDTH (the factor takes 8 w^2 bytes).
  * Takes its work space from the library's (see scd_release_memory) and returns it; synchronous on stream.
+ * Waits for no other persistent launch of the process: matrices whose f64 remainder fits the register files take their
+ * workgroups' compute units for at most 64 terms at a time (other persistent launches that need them wait so long) and only
+ * where they are free; else the cuts come from kernels that run beside anything.  Those add in another order: beside
+ * other persistent launches near-tie signs and the last bits of c and fro_trace may differ from those of the call alone.
  * Returns SCD_OK, SCD_WMAXITER, or SCD_EINVAL / SCD_ENOMEM / SCD_EHIP / SCD_ENONFINITE / SCD_ESINGULAR. */
 int scd_lsq_decompose(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uint64_t seed, int32_t max_iters,
                       void* stream, uint64_t* S, uint64_t* T, void* c, double* fro_trace, int32_t* iters);

@@ -47,13 +47,16 @@ int scd_engine(const scd_ctx* ctx, int* engine, double* last_launch_seconds, dou
 int scd_stream_geometry(scd_dtype dt, int order, const int64_t* dims, int limit, int64_t out[8]);
 
 /* scd_lsq_decompose with a say in how the cuts are found, for tests and measurement.  cuts = 0: as scd_lsq_decompose
- * does; 1: by the three launches per sweep that serve what the register-resident engine does not take (SCD_EINVAL where
- * they do not take the matrix).  max_spin: as SCD_OPT_MAX_SPIN (default there: 2^22), for the register-resident cuts; when
- * one gives up, the call starts again without that engine.  terms: host, 3 values, may be NULL: terms whose cuts came from the register-resident
- * engine, from the sweeps, and from the loop on the host. */
+ * does; 1: by the three launches per sweep that serve what the register-resident engine does not take or has no
+ * compute units for (SCD_EINVAL where they do not take the matrix); 2, 3: batches of that engine and of sweeps in turn,
+ * beginning with the engine (2) or the sweeps (3), as if its compute units were taken every other time (SCD_EINVAL where
+ * the engine does not take the matrix).  batch: most terms of a batch of the engine, and what a batch of sweeps aims
+ * at (64 in scd_lsq_decompose).  max_spin: as SCD_OPT_MAX_SPIN (default there: 2^22), for the engine's cuts; when one
+ * gives up, the call goes on without the engine.  terms: host, 3 values, may be NULL: terms whose cuts came from the
+ * register-resident engine, from the sweeps, and from the loop on the host. */
 int scd_lsq_decompose_form(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uint64_t seed, int32_t max_iters, void* stream,
-                           uint64_t* S, uint64_t* T, void* c, double* fro_trace, int32_t* iters, int cuts, int64_t max_spin,
-                           int64_t* terms);
+                           uint64_t* S, uint64_t* T, void* c, double* fro_trace, int32_t* iters, int cuts, int64_t batch,
+                           int64_t max_spin, int64_t* terms);
 
 /* Measurement: run n (<= 4096) further sweeps of the greedy loop with a HIP event before and after
  * each kernel of the pass over the remainder; returns the average duration of the row-pass launch

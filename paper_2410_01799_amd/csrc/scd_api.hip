@@ -135,6 +135,7 @@ namespace {
 std::mutex g_slots_mutex;
 std::condition_variable g_slots_cv;
 int g_slots_in_use = 0;
+int g_slots_waiting = 0;  // callers that wait for some
 
 // Device and pinned blocks of contexts and calls come from here and go back here.  Allocating and freeing costs more than
 // a small decomposition's other host work (some twenty blocks; us a call without and with blocks kept: 256x256 to width
@@ -479,9 +480,20 @@ struct SlotLease {
     {
         if (want > capacity) want = capacity;  // the occupancy check of the launcher has the last word
         std::unique_lock<std::mutex> lk(g_slots_mutex);
+        ++g_slots_waiting;
         g_slots_cv.wait(lk, [&] { return g_slots_in_use + want <= capacity; });
+        --g_slots_waiting;
         g_slots_in_use += want;
         n = want;
+    }
+    // Takes them only if they are free and nobody waits (who waits comes first, also where he wants more than are free).
+    bool try_acquire(int want, int capacity)
+    {
+        std::lock_guard<std::mutex> lk(g_slots_mutex);
+        if (g_slots_waiting > 0 || g_slots_in_use + want > capacity) return false;
+        g_slots_in_use += want;
+        n = want;
+        return true;
     }
     ~SlotLease()
     {
@@ -1508,15 +1520,21 @@ namespace {
 // How a call finds its cuts (see scd_lsq_decompose_form) and how many terms came from where.
 struct LsqForm {
     int cuts = 0;
-    int64_t max_spin = 1 << 22;    // re-reads after which a wait of the register-resident cuts gives up
+    int64_t batch = 64;            // terms of the register-resident engine between two looks at the state
+    int64_t max_spin = 1 << 22;    // re-reads after which a wait of its cuts gives up
     int64_t terms[3] = {0, 0, 0};  // register-resident, sweeps, host loop
 };
+constexpr int kLsqHostLoop = 100;  // of lsq_matrix: nothing done, the loop on the host is to take the call
 
-// Everything is enqueued blindly; launches past the end return at once.  `resident`: two launches per term, its cut on the
-// register-resident engine and the refit (SCD_ETIMEOUT where the workgroups did not all get a compute unit); else three per
-// sweep, about as many sweeps as the terms so far took.
+// Everything is enqueued blindly, batch by batch; launches past the end return at once.  A batch is either terms of the
+// register-resident engine, two launches each (its cut and the refit), or sweeps, three launches each.  `resident`: the
+// engine may take the matrix.  A batch of it needs its workgroups' compute units free of other persistent launches; it
+// takes them without waiting and gives them back after at most form.batch terms, so that nobody waits for a whole
+// call.  Where they are taken, or a wait in a kernel gave up, the call goes on with sweeps, which run beside anything; a
+// term that they have begun when the compute units are free again is begun anew.  `sweeps`: the sweeps are no slower than the
+// host loop; if not, they only go on with calls that the engine has begun.
 int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uint64_t seed, int32_t max_iters, hipStream_t st, uint64_t* S,
-               uint64_t* T, void* cvec, double* fro_trace, int32_t* iters, bool resident, LsqForm& form)
+               uint64_t* T, void* cvec, double* fro_trace, int32_t* iters, bool resident, bool sweeps, LsqForm& form)
 {
     const int64_t mw = words_for(m), nw = words_for(n);
     const int nsq = 256;
@@ -1597,62 +1615,71 @@ int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uin
     pin->state.c_prev = -INFINITY;
     LM(hipMemcpyAsync(fro_trace, pin->scal, 8, hipMemcpyHostToDevice, st));
     LM(hipMemcpyAsync(a.st, &pin->state, sizeof(LsqState), hipMemcpyHostToDevice, st));
-    if (resident) {
-        LM(hipMemsetAsync(res, 0, sizeof(ResidentResult) + xbuf_words * 8, st));
-    } else {
-        LM(launch_rng(seed, 0, 1u, n, a.t, st));
-    }
+    if (resident) LM(hipMemsetAsync(res, 0, sizeof(ResidentResult) + xbuf_words * 8, st));
     LM(hipStreamSynchronize(st));  // (the pinned block receives the state from here on)
-    if (resident) {
-        ResidentArgs r;
-        memset(&r, 0, sizeof(r));
-        r.m = m;
-        r.n = n;
-        r.seed = seed;
-        r.max_iters = max_iters;
-        r.max_spin = (int32_t)form.max_spin;
-        resident_poll_delays(SCD_F64, dims, 0.0, form.max_spin ? 16 : 0, &r.poll_delay, &r.poll_delay_v);
-        r.xbuf = xbuf;
-        r.S = S;
-        r.T = T;
-        r.iters = a.iters;
-        r.mw = (int32_t)mw;
-        r.nw = (int32_t)nw;
-        r.res = res;
-        r.A = A;
-        r.a_f32 = dt == SCD_F32 ? 1 : 0;
-        r.coef = a.c;
-        r.lsq = a.st;
+    ResidentArgs r;
+    memset(&r, 0, sizeof(r));
+    r.m = m;
+    r.n = n;
+    r.seed = seed;
+    r.max_iters = max_iters;
+    r.max_spin = (int32_t)form.max_spin;
+    if (resident) resident_poll_delays(SCD_F64, dims, 0.0, form.max_spin ? 16 : 0, &r.poll_delay, &r.poll_delay_v);
+    r.xbuf = xbuf;
+    r.S = S;
+    r.T = T;
+    r.iters = a.iters;
+    r.mw = (int32_t)mw;
+    r.nw = (int32_t)nw;
+    r.res = res;
+    r.A = A;
+    r.a_f32 = dt == SCD_F32 ? 1 : 0;
+    r.coef = a.c;
+    r.lsq = a.st;
+    const int workgroups = resident ? resident_workgroups(SCD_F64, dims) : 0, capacity = device_cus();
+    bool begun = false;  // the sweeps are inside term k
+    double per_term = 12.0, swept = 0.0;
+    int64_t swept_terms = 0;
+    for (int64_t turn = 0; !pin->state.done; ++turn) {
+        const int64_t k = pin->state.k;
         SlotLease lease;
-        lease.acquire(resident_workgroups(SCD_F64, dims), device_cus());
-        for (int64_t k = 0; k < w && !pin->state.done;) {
-            const int64_t batch = w - k < 64 ? w - k : 64;  // (a look at the state now and then: a singular system ends the call)
-            for (int64_t b = 0; b < batch; ++b) {
+        const bool mine = resident && (form.cuts < 2 || ((turn ^ form.cuts) & 1) == 0) && lease.try_acquire(workgroups, capacity);
+        if (mine) {
+            begun = false;
+            for (int64_t b = 0; b < form.batch && k + b < w; ++b) {
                 LM(launch_resident_lsq(r, st));
                 LM(launch_lsq_term(a, res, st));
             }
-            k += batch;
-            LM(hipMemcpyAsync(&pin->state, a.st, sizeof(LsqState), hipMemcpyDeviceToHost, st));
-            LM(hipStreamSynchronize(st));
+        } else {
+            if (!sweeps && k == 0) return cleanup(kLsqHostLoop);
+            if (!begun) {
+                pin->state.j = 0;
+                pin->state.c_prev = -INFINITY;
+                LM(hipMemcpyAsync(a.st, &pin->state, sizeof(LsqState), hipMemcpyHostToDevice, st));
+                LM(launch_rng(seed, (uint64_t)k, 1u, n, a.t, st));
+                begun = true;
+            }
+            // about as many as the rest takes, but another look at the compute units before long
+            const double rest = (double)(form.batch < w - k ? form.batch : w - k);
+            const double want = per_term * rest;
+            const int batch = want < 4.0 ? 4 : (want > 96.0 ? 96 : (int)want);
+            for (int b = 0; b < batch; ++b) LM(launch_lsq_sweep(a, dt, st));
+            swept += batch;
         }
-    }
-    double per_term = 12.0;
-    int64_t swept = 0;
-    const double bound = ((double)w + 1.0) * ((double)max_iters + 1.0);
-    while (!resident) {
-        const double want = per_term * (double)(w - pin->state.k);
-        const int batch = want < 4.0 ? 4 : (want > 96.0 ? 96 : (int)want);
-        for (int b = 0; b < batch; ++b) LM(launch_lsq_sweep(a, dt, st));
-        swept += batch;
         LM(hipMemcpyAsync(&pin->state, a.st, sizeof(LsqState), hipMemcpyDeviceToHost, st));
         LM(hipStreamSynchronize(st));
-        if (pin->state.done) break;
-        if ((double)swept > bound + batch) return cleanup(SCD_EINVAL);  // cannot happen: the device loop is bounded
-        if (pin->state.k > 0) per_term = (double)swept / (double)pin->state.k;
+        form.terms[mine ? 0 : 1] += pin->state.k - k;
+        if (!mine) {
+            swept_terms += pin->state.k - k;
+            if (swept_terms > 0) per_term = swept / (double)swept_terms;
+        }
+        if (pin->state.status == 3) {
+            resident = false;
+            pin->state.status = 0;
+            pin->state.done = 0;
+        }
     }
     const LsqState fin = pin->state;
-    form.terms[resident ? 0 : 1] = fin.status == 3 ? 0 : fin.k;
-    if (fin.status == 3) return cleanup(SCD_ETIMEOUT);
     if (fin.status == 2) return cleanup(SCD_ENONFINITE);
     if (fin.status == 1) return cleanup(SCD_ESINGULAR);
     LM(launch_lsq_cast(a.c, w, dt, cvec, st));
@@ -1673,19 +1700,18 @@ int lsq_decompose(const void* A, scd_dtype dt, int order, const int64_t* dims, i
     for (int i = 0; i < order; ++i)
         if (w > 0 && !signs[i]) return SCD_EINVAL;
     if (order == 2 && w > 0) {
-        // The register-resident engine takes every matrix whose f64 remainder fits the register files; should its
-        // workgroups not find room beside others' work, the launches that need no such thing start again.  Us a call, three
+        // The register-resident engine takes every matrix whose f64 remainder fits the register files.  Us a call, three
         // launches per sweep / here: 64x64 f32 to 16 terms 1680 / 720, 100x900 f32 to 32 2170 / 1280, 1024x1024 f32 to 32
         // 15100 / 5000, 2048x2048 f64 to 16 26000 / 5570, 4096x2048 f32 to 8 9380 / 2360, 1024x1024 f32 to 512 474000 /
         // 244000; slower on none that was tried.
         const bool sweeps = lsq_matrix_supported(dt, dims[0], dims[1]);
-        if (form.cuts == 1 && !sweeps) return SCD_EINVAL;
-        if (form.cuts != 1 && resident_supported(SCD_F64, 2, dims) && resident_workgroups(SCD_F64, dims) <= resident_lsq_room(dims)) {
-            const int rc = lsq_matrix(A, dt, dims[0], dims[1], w, seed, max_iters, (hipStream_t)stream, signs[0], signs[1], cvec, fro_trace, iters, true, form);
-            if (rc != SCD_ETIMEOUT) return rc;
+        const bool resident = form.cuts != 1 && resident_supported(SCD_F64, 2, dims) && resident_workgroups(SCD_F64, dims) <= resident_lsq_room(dims);
+        if ((form.cuts == 1 && !sweeps) || (form.cuts > 1 && !resident)) return SCD_EINVAL;
+        if (resident || sweeps) {
+            const int rc = lsq_matrix(A, dt, dims[0], dims[1], w, seed, max_iters, (hipStream_t)stream, signs[0], signs[1], cvec, fro_trace, iters,
+                                      resident, sweeps, form);
+            if (rc != kLsqHostLoop) return rc;
         }
-        if (sweeps)
-            return lsq_matrix(A, dt, dims[0], dims[1], w, seed, max_iters, (hipStream_t)stream, signs[0], signs[1], cvec, fro_trace, iters, false, form);
     }
     hipStream_t st = (hipStream_t)stream;
     const int64_t wl = w > 0 ? w : 1;
@@ -1801,13 +1827,15 @@ int scd_lsq_decompose_tensor(const void* A, scd_dtype dt, int order, const int64
 }
 
 int scd_lsq_decompose_form(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uint64_t seed, int32_t max_iters, void* stream,
-                           uint64_t* S, uint64_t* T, void* cvec, double* fro_trace, int32_t* iters, int cuts, int64_t max_spin, int64_t* terms)
+                           uint64_t* S, uint64_t* T, void* cvec, double* fro_trace, int32_t* iters, int cuts, int64_t batch, int64_t max_spin,
+                           int64_t* terms)
 {
-    if (cuts < 0 || cuts > 1 || max_spin < 0 || max_spin > INT32_MAX - 1) return SCD_EINVAL;
+    if (cuts < 0 || cuts > 3 || batch < 1 || max_spin < 0 || max_spin > INT32_MAX - 1) return SCD_EINVAL;
     const int64_t dims[2] = {m, n};
     uint64_t* const signs[2] = {S, T};
     LsqForm form;
     form.cuts = cuts;
+    form.batch = batch;
     form.max_spin = max_spin;
     const int rc = lsq_decompose(A, dt, 2, dims, w, seed, max_iters, stream, signs, cvec, fro_trace, iters, form);
     for (int i = 0; terms && i < 3; ++i) terms[i] = form.terms[i];

@@ -68,7 +68,7 @@ def lib() -> C.CDLL:
         L.scd_get_option.argtypes = [vp, C.c_int, pi64]
         L.scd_sparse_flips.argtypes = [vp, pi64, pi64]
         L.scd_lsq_decompose.argtypes = [vp, C.c_int, i64, i64, i64, C.c_uint64, i32, vp, vp, vp, vp, vp, vp]
-        L.scd_lsq_decompose_form.argtypes = [vp, C.c_int, i64, i64, i64, C.c_uint64, i32, vp, vp, vp, vp, vp, vp, C.c_int, i64, pi64]
+        L.scd_lsq_decompose_form.argtypes = [vp, C.c_int, i64, i64, i64, C.c_uint64, i32, vp, vp, vp, vp, vp, vp, C.c_int, i64, i64, pi64]
         L.scd_lsq_decompose_tensor.argtypes = [vp, C.c_int, C.c_int, pi64, i64, C.c_uint64, i32, vp, pvp, vp, vp, vp]
         L.scd_decompose_scalars.argtypes = [vp, C.c_int, C.c_int, pi64, i64, C.c_uint64, i32, vp, pvp, vp, vp, vp]
         L.scd_apply_workspace_bytes.argtypes = [i64, i64, i64]
@@ -219,7 +219,8 @@ def scd_lsq_decompose(A: torch.Tensor, w: int, seed: int, max_iters: int = 4096)
     return dict(signs=signs, c=c, trace=trace, iters=iters, status=st)
 
 
-def scd_lsq_decompose_form(A: torch.Tensor, w: int, seed: int, max_iters: int = 4096, cuts: int = 0, max_spin: int = 1 << 22) -> dict:
+def scd_lsq_decompose_form(A: torch.Tensor, w: int, seed: int, max_iters: int = 4096, cuts: int = 0, batch: int = 64,
+                           max_spin: int = 1 << 22) -> dict:
     """scd_lsq_decompose of a matrix with a say in how its cuts are found (see scd_probe.h): also returns
     terms=(register-resident, sweeps, host loop)."""
     A = _dev(A, "A")
@@ -231,7 +232,7 @@ def scd_lsq_decompose_form(A: torch.Tensor, w: int, seed: int, max_iters: int = 
     iters = torch.empty(w, dtype=torch.int32, device=A.device)
     terms = (C.c_int64 * 3)()
     st = lib().scd_lsq_decompose_form(_ptr(A), _dt(A), m, n, w, int(seed), int(max_iters), _stream(), _ptr(signs[0]), _ptr(signs[1]),
-                                      _ptr(c), _ptr(trace), _ptr(iters), int(cuts), int(max_spin), terms)
+                                      _ptr(c), _ptr(trace), _ptr(iters), int(cuts), int(batch), int(max_spin), terms)
     st = _check(st, "scd_lsq_decompose_form")
     return dict(signs=signs, c=c, trace=trace, iters=iters, status=st, terms=tuple(terms))
 

@@ -2,6 +2,8 @@
 coefficients of Algorithm 6 are a function of (A, S_k, T_k) alone, so for every term the oracle refits them
 for the GPU's own sign vectors, forms the remainder in f64 and repeats the greedy cut from the keyed start."""
 import math
+import threading
+import time
 
 import numpy as np
 import pytest
@@ -103,8 +105,8 @@ def test_lsq_sweeps_edges(scd):
     assert torch.equal(one["c"], two["c"]) and torch.equal(one["trace"], two["trace"]) and one["terms"] == (0, 12, 0)
 
 
-# a wait of the register-resident cuts that gives up (forced from the host: no re-reads): the sweeps, or for f64 above 2048
-# entries a side the host loop, take the call; one workgroup waits for nothing
+# a wait of the register-resident cuts that gives up (forced from the host: no re-reads) in the first term: the sweeps, or for
+# f64 above 2048 entries a side the host loop, take the call; one workgroup waits for nothing
 @pytest.mark.parametrize("m,n,w,dtype,terms", [(300, 520, 6, np.float32, (0, 6, 0)), (1024, 1024, 4, np.float64, (0, 4, 0)),
                                                (2100, 70, 4, np.float64, (0, 0, 4)), (200, 100, 4, np.float64, (4, 0, 0))])
 def test_lsq_wait_that_gives_up(scd, oracle, m, n, w, dtype, terms):
@@ -112,14 +114,75 @@ def test_lsq_wait_that_gives_up(scd, oracle, m, n, w, dtype, terms):
     assert res["terms"] == terms
 
 
+# batches of the engine and of sweeps in turn, from either side: every handover is at a term; with no re-reads the engine
+# gives up in its first batch, behind terms of the sweeps.  2100x70 in f64 is more than the sweeps take by rule
+@pytest.mark.parametrize("m,n,w,dtype,form", [(300, 520, 14, np.float32, dict(cuts=2, batch=3)), (65, 130, 14, np.float64, dict(cuts=3, batch=2)),
+                                              (40, 72, 95, np.float64, dict(cuts=2, batch=5)), (2100, 70, 9, np.float64, dict(cuts=2, batch=2)),
+                                              (300, 520, 14, np.float32, dict(cuts=3, batch=2, max_spin=0))])
+def test_lsq_handover_between_engine_and_sweeps(scd, oracle, m, n, w, dtype, form):
+    res, _ = run_and_check(scd, oracle, gauss((m, n), 2 * m + n, dtype), w, 8, **form)
+    resident, sweeps, loop = res["terms"]
+    assert resident + sweeps == w and loop == 0 and sweeps > 0 and (resident > 0) == ("max_spin" not in form)
+
+
+def in_thread(f):
+    """f on a stream and a host thread of its own, given a moment to get under way."""
+    out = []
+
+    def work():
+        with torch.cuda.stream(torch.cuda.Stream()):
+            out.append(f())
+            torch.cuda.current_stream().synchronize()
+
+    th = threading.Thread(target=work)
+    th.start()
+    time.sleep(0.1)
+    return th, out
+
+
+def test_lsq_beside_a_context_waits_for_nothing(scd, oracle):
+    B = torch.from_numpy(gauss((2048, 1024), 12)).cuda()
+    ctx = scd.ScdContext(B, 12000, 1)
+    ctx.set_workgroups(128)                               # 1040x1040 wants all compute units
+    torch.cuda.synchronize()
+    th, out = in_thread(lambda: ctx.run(12000))
+    with torch.cuda.stream(torch.cuda.Stream()):
+        res = scd.scd_lsq_decompose_form(torch.from_numpy(gauss((1040, 1040), 13)).cuda(), 4, 2)
+    beside = th.is_alive()
+    th.join()
+    ctx.close()
+    assert out == [scd.OK] and beside and res["terms"] == (0, 4, 0)
+    run_and_check(scd, oracle, gauss((1040, 1040), 13), 4, 2)   # (what the sweeps find is checked above)
+
+
+def test_lsq_lets_a_context_in(scd):
+    A = torch.from_numpy(gauss((1024, 1024), 14)).cuda()
+    B = torch.from_numpy(gauss((1500, 4096), 15)).cuda()
+    alone = scd.scd_decompose(B, 4, 3)
+    torch.cuda.synchronize()
+    th, out = in_thread(lambda: scd.scd_lsq_decompose_form(A, 1024, 2))
+    with torch.cuda.stream(torch.cuda.Stream()):
+        got = scd.scd_decompose(B, 4, 3)                  # wants the whole device
+        torch.cuda.current_stream().synchronize()
+    beside = th.is_alive()
+    th.join()
+    assert beside and torch.equal(alone["c"], got["c"]) and torch.equal(alone["trace"], got["trace"])
+    assert out[0]["status"] == scd.OK and sum(out[0]["terms"]) == 1024 and out[0]["terms"][0] > 0
+    R = A.double() - scd.scd_expand(out[0]["signs"], out[0]["c"].double(), (1024, 1024))
+    assert float(R.norm()) == pytest.approx(float(out[0]["trace"][-1]), rel=1e-6)
+
+
 def test_lsq_form_is_checked(scd):
     A = torch.from_numpy(gauss((130, 4097), 1)).cuda()
-    for cuts in (-1, 1, 2):                               # the sweeps do not take 65 words
+    for cuts in (-1, 1, 2, 3, 4):                             # the sweeps do not take 65 words
         with pytest.raises(scd.ScdError) as e:
             scd.scd_lsq_decompose_form(A, 2, 1, cuts=cuts)
         assert e.value.code == scd.EINVAL
     with pytest.raises(scd.ScdError) as e:
         scd.scd_lsq_decompose_form(A, 2, 1, max_spin=-1)
+    assert e.value.code == scd.EINVAL
+    with pytest.raises(scd.ScdError) as e:
+        scd.scd_lsq_decompose_form(A, 2, 1, batch=0)
     assert e.value.code == scd.EINVAL
     assert scd.scd_lsq_decompose_form(A, 2, 1)["terms"] == (0, 0, 2)
     assert scd.scd_lsq_decompose_form(A[:, :4096].contiguous(), 2, 1)["terms"] == (2, 0, 0)
