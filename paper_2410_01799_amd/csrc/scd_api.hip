@@ -1543,9 +1543,7 @@ int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uin
         double scal[2];
     };
     // one block: every array of doubles or words, then the iteration counts and the state
-    const int64_t dims[2] = {m, n};
-    const size_t xbuf_words = resident && resident_workgroups(SCD_F64, dims) > 1 ? (size_t)4 * kResGrid * kResGrid * kResSlotWords : 0;
-    const size_t words = (size_t)(mw + nw + 2 * nw + w * w + 3 * w + nsq + 2) + xbuf_words + (sizeof(ResidentResult) + 7) / 8;
+    const size_t words = (size_t)(mw + nw + 2 * nw + w * w + 3 * w + nsq + 2);
     const size_t bytes = words * 8 + (((size_t)w * 4 + 15) & ~(size_t)15) + sizeof(LsqState);
     void* dev = nullptr;
     Pinned* pin = nullptr;
@@ -1556,8 +1554,19 @@ int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uin
         if (dev) pool_free(dev);
         return SCD_ENOMEM;
     }
+    // a second one, which only the engine needs: its result and the slots of its exchanges
+    const int64_t dims[2] = {m, n};
+    const size_t xbuf_bytes = resident && resident_workgroups(SCD_F64, dims) > 1 ? (size_t)4 * kResGrid * kResGrid * kResSlotWords * 8 : 0;
+    const size_t res_bytes = (sizeof(ResidentResult) + 7) & ~(size_t)7;
+    void* eng = nullptr;
+    if (resident && pool_malloc(&eng, res_bytes + xbuf_bytes, false) != hipSuccess) {
+        (void)hipGetLastError();
+        eng = nullptr;
+        resident = false;
+    }
     auto cleanup = [&](int code) {
         settle(st);
+        pool_free(eng);
         pool_free(dev);
         pool_free(pin);
         (void)hipGetLastError();
@@ -1598,8 +1607,8 @@ int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uin
     a.bvec = (double*)take(w);
     double* sq = (double*)take(nsq);
     double* scal = (double*)take(2);
-    ResidentResult* res = (ResidentResult*)take((sizeof(ResidentResult) + 7) / 8);
-    uint64_t* xbuf = take((int64_t)xbuf_words);
+    ResidentResult* res = (ResidentResult*)eng;
+    uint64_t* xbuf = eng ? (uint64_t*)((char*)eng + res_bytes) : nullptr;
     a.trace = fro_trace;
     a.iters = (int32_t*)p;
     a.st = (LsqState*)((char*)p + (((size_t)w * 4 + 15) & ~(size_t)15));
@@ -1615,7 +1624,7 @@ int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uin
     pin->state.c_prev = -INFINITY;
     LM(hipMemcpyAsync(fro_trace, pin->scal, 8, hipMemcpyHostToDevice, st));
     LM(hipMemcpyAsync(a.st, &pin->state, sizeof(LsqState), hipMemcpyHostToDevice, st));
-    if (resident) LM(hipMemsetAsync(res, 0, sizeof(ResidentResult) + xbuf_words * 8, st));
+    if (resident) LM(hipMemsetAsync(eng, 0, res_bytes + xbuf_bytes, st));
     LM(hipStreamSynchronize(st));  // (the pinned block receives the state from here on)
     ResidentArgs r;
     memset(&r, 0, sizeof(r));
