@@ -1366,14 +1366,20 @@ int scd_expand(const uint64_t* const* signs, const void* cvec, scd_dtype dt, int
         if (w > 0 && !signs[i]) return SCD_EINVAL;
     hipStream_t st = (hipStream_t)stream;
     const int64_t m = dims[0], cols = total / dims[0];
-    // one block: the digits of the coefficients, then (tensors) the Kronecker products of the trailing modes' signs
+    // one block: the digits of the coefficients, then (tensors) the Kronecker products of the trailing modes' signs.  The
+    // digits can be done without (the f64 form needs none).
     uint64_t* kr = nullptr;
-    const size_t dig_bytes = (expand_scratch_bytes(dt, w) + 255) & ~(size_t)255;
+    size_t dig_bytes = (expand_scratch_bytes(dt, w) + 255) & ~(size_t)255;
     const size_t kr_bytes = order >= 3 ? (size_t)w * (size_t)words_for(cols) * 8 : 0;
     char* block = nullptr;
     const uint64_t* T = signs[1];
     if (dig_bytes + kr_bytes > 0) {
         hipError_t e = pool_malloc((void**)&block, dig_bytes + kr_bytes, false);
+        if (e != hipSuccess && dig_bytes > 0) {
+            dig_bytes = 0;
+            block = nullptr;
+            if (kr_bytes > 0) e = pool_malloc((void**)&block, kr_bytes, false);
+        }
         if (e != hipSuccess) {
             (void)hipGetLastError();
             block = nullptr;
@@ -1389,7 +1395,7 @@ int scd_expand(const uint64_t* const* signs, const void* cvec, scd_dtype dt, int
         e = launch_kron_terms(order, dims, signs, w, kr, cols, st);
         T = kr;
     }
-    if (e == hipSuccess) e = launch_expand(signs[0], T, cvec, dt, m, cols, w, out, block, st);
+    if (e == hipSuccess) e = launch_expand(signs[0], T, cvec, dt, m, cols, w, out, dig_bytes > 0 ? block : nullptr, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (block) {
         if (e != hipSuccess) settle(st);
