@@ -11,8 +11,8 @@
 //   a multiple of 2^q below w 2^(q + B): if B + log2 w <= 53 each of its f64 additions is exact, so any exact
 //   evaluation gives the same bits.  k_j is written in four or five balanced base-255 digits of -127 .. 127 (B <= 30
 //   or 38); signs times digits are int8, products and 32-bit sums are exact, the digits' sums are put together in
-//   f64 integers below 2^53.  A launch ahead works out q, B and the digits; the one that follows takes the form that
-//   applies.
+//   f64 integers below 2^53.  With few terms every workgroup works out q, B and the digits for itself; with many a launch
+//   ahead does; the form that applies is taken on the device.
 //
 // The bitsets are term-major and the terms are the contraction index: a wave loads one word (64 rows or columns) of 64
 // terms, one per lane, and transposes the 64 x 64 bits across its lanes.
@@ -38,15 +38,16 @@ struct ExScale {
     bool ok;
 };
 
-// All threads of a workgroup of kExScanThreads call it; every thread gets the same answer.
-constexpr int kExScanThreads = 1024;
+// All threads of a workgroup call it; every thread gets the same answer.
+constexpr int kExScanThreads = 1024;  // of the launch that works out the digits
+template <int THREADS>
 __device__ ExScale ex_scan(const float* __restrict__ c, int64_t w, int (*red)[3])
 {
     int lo = 1 << 20, hi = -(1 << 20), bad = 0;
-    for (int64_t i0 = threadIdx.x; i0 < w; i0 += 8 * kExScanThreads) {
+    for (int64_t i0 = threadIdx.x; i0 < w; i0 += 8 * THREADS) {
         uint32_t u[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) u[e] = __float_as_uint(c[i0 + e * kExScanThreads < w ? i0 + e * kExScanThreads : i0]);
+        for (int e = 0; e < 8; ++e) u[e] = __float_as_uint(c[i0 + e * THREADS < w ? i0 + e * THREADS : i0]);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const int ex = (int)((u[e] >> 23) & 255u);
@@ -71,7 +72,7 @@ __device__ ExScale ex_scan(const float* __restrict__ c, int64_t w, int (*red)[3]
     if ((threadIdx.x & (kWave - 1)) == 0) red[wv][0] = lo, red[wv][1] = hi, red[wv][2] = bad;
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kExScanThreads / kWave; ++i) {
+    for (int i = 0; i < THREADS / kWave; ++i) {
         lo = red[i][0] < lo ? red[i][0] : lo;
         hi = red[i][1] > hi ? red[i][1] : hi;
         bad |= red[i][2];
@@ -84,6 +85,25 @@ __device__ ExScale ex_scan(const float* __restrict__ c, int64_t w, int (*red)[3]
     s.ok = !bad && s.bits <= 38 && s.bits + lw <= 53 && lw <= 24;  // (32-bit sums of w digits)
     __syncthreads();  // red may be reused
     return s;
+}
+
+// A coefficient (its bits) as k 2^q, k in ND balanced base-255 digits.
+template <int ND>
+__device__ __forceinline__ void ex_digits(uint32_t u, int q, int (&r)[ND])
+{
+    const int ex = (int)((u >> 23) & 255u);
+    const uint32_t mant = (u & 0x7FFFFFu) | (ex ? 0x800000u : 0u);
+    uint64_t k = mant;
+    const int shift = (ex ? ex : 1) - 150 - q;  // negative only by trailing zeros of the mantissa
+    k = mant == 0 ? 0 : (shift >= 0 ? k << shift : k >> -shift);
+    const bool neg = (u >> 31) != 0;
+#pragma unroll
+    for (int g = 0; g < ND; ++g) {
+        const uint64_t k127 = k + 127, quot = k127 / 255;  // k = 255 quot + r, r in -127 .. 127
+        const int d = (int)(k127 - quot * 255) - 127;
+        k = quot;
+        r[g] = neg ? -d : d;
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -182,6 +202,132 @@ __global__ void __launch_bounds__(kExThreads, 2)
 }
 
 // ------------------------------------------------------------------------------------------------
+// int8 form in one launch, for few terms.  Every workgroup scans the coefficients and forms their digits itself; tiles of
+// 128 rows x 64 columns on four waves, 64 x 32 each (two 32 x 32 accumulators per digit), two workgroups per compute unit, so
+// that the store of one tile overlaps with the products of another.  Per chunk of 64 terms three waves transpose the
+// tile's three words of bits and the fourth splits the coefficients, double-buffered in LDS; operand bytes as below, a column's
+// byte the digit or its negative.  Bound by the store of the output and the ends of the tiles (4096x4096 to 33 terms 34 us
+// a call, staged operands 47; see launch_expand).
+constexpr int kExDirectM = 128, kExDirectN = 64;
+
+struct ExDirectLds {
+    uint64_t abits[2][kExDirectM];   // transposed: bit t = sign of term t of the chunk at this row
+    uint64_t bbits[2][kExDirectN];
+    uint32_t dig[2][2][2][5][2][4];  // [buffer][half of the chunk][lane half][digit][sign][dword]
+};
+
+template <int ND>
+__device__ __forceinline__ void ex_direct_tiles(const uint64_t* __restrict__ S, const uint64_t* __restrict__ T, const float* __restrict__ c,
+                                                int64_t m, int64_t n, int64_t w, float* __restrict__ out, int q, ExDirectLds& sh)
+{
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int wr = wv >> 1, wc = wv & 1;
+    const int li = lane & 31, kh = lane >> 5;
+    const int64_t mw = (m + 63) / 64, nw = (n + 63) / 64;
+    const int64_t tm = (m + kExDirectM - 1) / kExDirectM, tiles = tm * nw;
+    const int64_t chunks = (w + 63) / 64;
+    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const int64_t ti = tile % tm, tj = tile / tm;
+        v16i acc[2][ND];
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int d = 0; d < ND; ++d) acc[a][d] = (v16i)0;
+        // waves 0, 1: words 2 ti, 2 ti + 1 of S; wave 2: word tj of T; wave 3: the coefficients.  Lane = term.
+        auto fetch = [&](int64_t ch) -> uint64_t {
+            const int64_t j = ch * 64 + lane;
+            if (j >= w) return 0;
+            if (wv < 2) return 2 * ti + wv < mw ? S[j * mw + 2 * ti + wv] : 0;
+            if (wv == 2) return T[j * nw + tj];
+            return (uint64_t)__float_as_uint(c[j]);
+        };
+        auto stage = [&](int buf, uint64_t v) {
+            if (wv < 2) {
+                sh.abits[buf][wv * 64 + lane] = transpose64(v, lane);
+            } else if (wv == 2) {
+                sh.bbits[buf][lane] = transpose64(v, lane);
+            } else {
+                int r[ND];
+                ex_digits<ND>((uint32_t)v, q, r);
+                const int t = lane & 31, d = t & 7;
+                uint8_t* p = (uint8_t*)&sh.dig[buf][lane >> 5][d >> 2][0][0][d & 3] + (t >> 3);
+#pragma unroll
+                for (int g = 0; g < ND; ++g) {
+                    p[g * 32] = (uint8_t)r[g];
+                    p[g * 32 + 16] = (uint8_t)-r[g];
+                }
+            }
+        };
+        stage(0, fetch(0));
+        uint64_t next = fetch(1);
+        __syncthreads();
+        for (int64_t ch = 0; ch < chunks; ++ch) {
+            const int buf = (int)(ch & 1);
+            if (ch + 1 < chunks) stage(buf ^ 1, next);
+            next = fetch(ch + 2);
+            const uint64_t ab0 = sh.abits[buf][wr * 64 + li], ab1 = sh.abits[buf][wr * 64 + 32 + li];
+            const uint64_t bb = sh.bbits[buf][wc * 32 + li];
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf) {
+                const uint32_t x0 = (uint32_t)(ab0 >> (32 * hf)) >> (4 * kh), x1 = (uint32_t)(ab1 >> (32 * hf)) >> (4 * kh);
+                const uint32_t xb = (uint32_t)(bb >> (32 * hf)) >> (4 * kh);
+                v4i A0, A1;
+                uint32_t selb[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    A0[e] = (int)__builtin_amdgcn_perm(0xFFFFFFFFu, 0x01010101u, (e < 2 ? x0 << (2 - e) : x0 >> (e - 2)) & 0x04040404u);
+                    A1[e] = (int)__builtin_amdgcn_perm(0xFFFFFFFFu, 0x01010101u, (e < 2 ? x1 << (2 - e) : x1 >> (e - 2)) & 0x04040404u);
+                    selb[e] = ((e < 2 ? xb << (2 - e) : xb >> (e - 2)) & 0x04040404u) | 0x03020100u;
+                }
+#pragma unroll
+                for (int g = 0; g < ND; ++g) {
+                    const uint4 pos = *(const uint4*)sh.dig[buf][hf][kh][g][0], neg = *(const uint4*)sh.dig[buf][hf][kh][g][1];
+                    v4i B;
+                    B[0] = (int)__builtin_amdgcn_perm(neg.x, pos.x, selb[0]);
+                    B[1] = (int)__builtin_amdgcn_perm(neg.y, pos.y, selb[1]);
+                    B[2] = (int)__builtin_amdgcn_perm(neg.z, pos.z, selb[2]);
+                    B[3] = (int)__builtin_amdgcn_perm(neg.w, pos.w, selb[3]);
+                    acc[0][g] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A0, B, acc[0][g], 0, 0, 0);
+                    acc[1][g] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A1, B, acc[1][g], 0, 0, 0);
+                }
+            }
+            __syncthreads();
+        }
+        // register r of a 32 x 32 accumulator: row 8 (r / 4) + 4 (lane / 32) + r mod 4, column lane mod 32
+        const int64_t col = tj * 64 + wc * 32 + li;
+        const double unit = ldexp(1.0, q);
+        if (col < n) {
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int64_t row = ti * kExDirectM + wr * 64 + a * 32 + 8 * (r >> 2) + 4 * kh + (r & 3);
+                    double v = (double)acc[a][ND - 1][r];
+#pragma unroll
+                    for (int g = ND - 2; g >= 0; --g) v = v * 255.0 + (double)acc[a][g][r];
+                    if (row < m) out[row * n + col] = (float)(v * unit);
+                }
+        }
+    }
+}
+
+__global__ void __launch_bounds__(kExThreads, 2)
+    expand_direct_kernel(const uint64_t* __restrict__ S, const uint64_t* __restrict__ T, const float* __restrict__ c, int64_t m, int64_t n,
+                         int64_t w, float* __restrict__ out)
+{
+    __shared__ __align__(16) union {
+        ExDirectLds d;
+        ExF64Lds f;
+        int red[kExThreads / kWave][3];
+    } sh;
+    const ExScale sc = ex_scan<kExThreads>(c, w, sh.red);
+    if (!sc.ok) ex_f64_tiles<float, 1>(S, T, c, m, n, w, out, &sh.f);
+    else if (sc.bits <= 30) ex_direct_tiles<4>(S, T, c, m, n, w, out, sc.q, sh.d);
+    else ex_direct_tiles<5>(S, T, c, m, n, w, out, sc.q, sh.d);
+}
+
+// ------------------------------------------------------------------------------------------------
 // int8 form.  expand_digits_kernel writes the scale and the digits once per call; the tile kernel then runs on three
 // stages per chunk of 64 terms, one barrier apart:
 //   chunk ch + 2  the tile's words of bits are transposed across a wave (lane = term -> lane = row or column), each wave
@@ -209,7 +355,7 @@ __global__ void __launch_bounds__(kExScanThreads)
     expand_digits_kernel(const float* __restrict__ c, int64_t w, ExPlan* __restrict__ plan, uint32_t* __restrict__ dig)
 {
     __shared__ int red[kExScanThreads / kWave][3];
-    const ExScale sc = ex_scan(c, w, red);
+    const ExScale sc = ex_scan<kExScanThreads>(c, w, red);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         plan->ok = sc.ok ? 1 : 0;
         plan->digits = sc.bits <= 30 ? 4 : 5;
@@ -219,24 +365,14 @@ __global__ void __launch_bounds__(kExScanThreads)
     const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
     const int64_t chunks = (w + 127) / 128 * 2;
     for (int64_t ch = (int64_t)blockIdx.x * (kExScanThreads / kWave) + wv; ch <= chunks; ch += (int64_t)gridDim.x * (kExScanThreads / kWave)) {
-        // c = k 2^q, |k| in balanced base-255 digits; terms past the end are zero
+        // terms past the end are zero
         const int64_t j = ch * 64 + lane;
-        const uint32_t u = j < w ? __float_as_uint(c[j]) : 0u;
-        const int ex = (int)((u >> 23) & 255u);
-        const uint32_t mant = (u & 0x7FFFFFu) | (ex ? 0x800000u : 0u);
-        uint64_t k = mant;
-        const int shift = (ex ? ex : 1) - 150 - sc.q;  // negative only by trailing zeros of the mantissa
-        k = mant == 0 ? 0 : (shift >= 0 ? k << shift : k >> -shift);
-        const bool neg = (u >> 31) != 0;
+        int r[kExDigits];
+        ex_digits<kExDigits>(j < w ? __float_as_uint(c[j]) : 0u, sc.q, r);
         const int t = lane & 31, d = t & 7;
         uint8_t* p = (uint8_t*)(dig + ch * kExChunkDwords + (((lane >> 5) * 2 + (d >> 2)) * kExDigits) * 4 + (d & 3)) + (t >> 3);
 #pragma unroll
-        for (int g = 0; g < kExDigits; ++g) {
-            const uint64_t k127 = k + 127, quot = k127 / 255;  // k = 255 quot + r, r in -127 .. 127
-            int r = (int)(k127 - quot * 255) - 127;
-            k = quot;
-            p[g * 16] = (uint8_t)(neg ? -r : r);
-        }
+        for (int g = 0; g < kExDigits; ++g) p[g * 16] = (uint8_t)r[g];
     }
 }
 
@@ -414,7 +550,19 @@ __global__ void __launch_bounds__((ExTile<RW, CW>::kThreads), 2)
     else ex_int_tiles<RW, CW, 5>(S, T, dig, m, n, w, out, plan->q, sh);
 }
 
-constexpr int64_t kExFewTerms = 32;  // up to here the f64 form takes f32 coefficients at once
+// f32 coefficients: most terms that go to the f64 form at once, by the number of entries, and to the int8 form in one launch.
+// Us a call, f64 form / one launch: 64x64 to 48 terms 16.9 / 17.0, to 64 17.9 / 16.9; 1024x1024 to 48 18.1 / 18.2, to 64
+// 19.1 / 18.2; 2048x2048 to 24 19.8 / 20.8, to 32 20.8 / 20.8, to 40 21.8 / 20.8; 4096x4096 to 20 34.0 / 34.2, to 24 34.5 / 34.1;
+// 14336x4096 to 17 73.4 / 77.0, to 20 77.3 / 77.0.
+// One launch / staged operands: 64x64 to 384 terms 21.2 / 21.8; 1024x1024 to 384 22.9 / 24.0, to 700 28.7 / 28.7; 2048x2048 to 33
+// 20.2 / 25.4, to 384 26.9 / 29.5; 4096x4096 to 33 33.0 / 46.7, to 384 57.9 / 61.2, to 450 71.5 / 68.0; 14336x4096 to 33
+// 74 / 114, to 384 164 / 164, to 450 208 / 186 (one launch takes another step at each 64 terms, the staged form at each 128).
+int64_t ex_few_terms(int64_t m, int64_t n)
+{
+    const double entries = (double)m * (double)n;
+    return entries <= (double)(1 << 20) ? 48 : (entries <= (double)(1 << 22) ? 32 : 20);
+}
+constexpr int64_t kExDirectTerms = 448;
 
 unsigned ex_grid(int64_t tiles, int64_t cap) { return (unsigned)(tiles < 1 ? 1 : (tiles < cap ? tiles : cap)); }
 
@@ -422,7 +570,7 @@ unsigned ex_grid(int64_t tiles, int64_t cap) { return (unsigned)(tiles < 1 ? 1 :
 
 size_t expand_scratch_bytes(scd_dtype dt, int64_t w)
 {
-    if (dt != SCD_F32 || w <= kExFewTerms) return 0;
+    if (dt != SCD_F32 || w <= kExDirectTerms) return 0;
     return sizeof(ExPlan) + ((size_t)((w + 127) / 128) * 2 + 1) * kExChunkDwords * 4;
 }
 
@@ -445,16 +593,19 @@ hipError_t launch_expand(const uint64_t* S, const uint64_t* T, const void* c, sc
                          void* scratch, hipStream_t st)
 {
     const int64_t mw = (m + 63) / 64, nw = (n + 63) / 64;
-    // Measured, us a call, before the digits had a kernel of their own and the operands a stage (every workgroup scanned the
-    // coefficients, one wave of four formed a chunk's digits) / now: 1024x4096 to 6512 terms 167 / 123, 2048x2048 to 5900
-    // 180 / 136, 4096x4096 to 1500 200 / 165, 1024x1024 to 3000 80 / 63, 300x500 to 1400 51 / 43, 64x64 to 170 29 / 29;
-    // 4096x4096 to 80 57 / 60 (the ends of the four tiles of a workgroup are not overlapped; even from 450 terms on).  Up to
-    // 32 terms the f64 form alone is faster than the two launches: 1024x1024 to 20 24 / 29, to 40 26 / 29 (4096x4096 55 / 52).
+    // Measured, us a call, one launch in which every workgroup works out the digits / staged operands: 1024x4096 to 6512 terms
+    // 167 / 123, 2048x2048 to 5900 180 / 136, 4096x4096 to 1500 200 / 165, 1024x1024 to 3000 80 / 63, 300x500 to 1400
+    // 51 / 43, 64x64 to 700 27 / 26; with fewer terms the ends of the tiles, which a workgroup that fills its compute unit does not
+    // overlap, and the second launch weigh more (see ex_few_terms).
     const unsigned gridf = ex_grid(mw * ((nw + 1) / 2), 1024);
     if (dt == SCD_F64) {
         hipLaunchKernelGGL((expand_f64_kernel<double>), dim3(gridf), dim3(kExThreads), 0, st, S, T, (const double*)c, m, n, w,
                            (double*)out);
-    } else if (w <= kExFewTerms || !scratch || mw >= 1 << 29 || nw >= 1 << 29) {  // (rows of bits of 4 GiB and more: 32-bit strides)
+    } else if (w > ex_few_terms(m, n) && w <= kExDirectTerms) {
+        const int64_t tiles = (m + kExDirectM - 1) / kExDirectM * nw;
+        hipLaunchKernelGGL(expand_direct_kernel, dim3(ex_grid(tiles, 512)), dim3(kExThreads), 0, st, S, T, (const float*)c, m, n, w,
+                           (float*)out);
+    } else if (w <= kExDirectTerms || !scratch || mw >= 1 << 29 || nw >= 1 << 29) {  // (rows of bits of 4 GiB and more: 32-bit strides)
         hipLaunchKernelGGL((expand_f64_kernel<float>), dim3(gridf), dim3(kExThreads), 0, st, S, T, (const float*)c, m, n, w,
                            (float*)out);
     } else {

@@ -100,20 +100,42 @@ def test_expand_bit_exact_over_the_span_of_the_coefficients(scd, oracle, shape, 
     assert np.array_equal(got, ref)
 
 
-# more than 128 tiles of 128 x 128 (the last ones ragged) in all three forms, whole and cut chunks of terms, more tiles than
-# workgroups; 32 terms are the last that go to the f64 form at once
+# large matrices and tensors (the last tiles ragged) in all three forms, whole and cut chunks of terms, more tiles than
+# workgroups
 @pytest.mark.parametrize("shape,w,bits", [((1470, 1500), 33, 30), ((1470, 1500), 129, 38), ((1409, 1537), 128, 60), ((1500, 1400), 32, 24),
                                           ((130, 127 * 127), 65, 30), ((2100, 2200), 191, 30), ((512, 17, 250), 70, 31)])
 def test_expand_bit_exact_on_large_tiles(scd, oracle, shape, w, bits):
     test_expand_bit_exact_over_the_span_of_the_coefficients(scd, oracle, shape, w, bits)
 
 
-def test_expand_bit_exact_at_the_ends_of_the_exponents(scd, oracle):
+# operands staged behind a launch for the digits: from 449 terms on, with 64 x 64 tiles and, for more than 128 of 128 x 128,
+# with those; whole and cut chunks, cut pairs of chunks, the spans' ends
+@pytest.mark.parametrize("shape,w", [((1, 1), 449), ((129, 63), 512), ((64, 129), 513), ((70, 200), 500), ((40, 9, 7), 577)])
+@pytest.mark.parametrize("bits", [24, 30, 31, 38, 39, 60])
+def test_expand_bit_exact_with_many_terms(scd, oracle, shape, w, bits):
+    test_expand_bit_exact_over_the_span_of_the_coefficients(scd, oracle, shape, w, bits)
+
+
+@pytest.mark.parametrize("shape,w,bits", [((1470, 1500), 449, 30), ((1409, 1537), 513, 38), ((1500, 1400), 512, 60), ((130, 127 * 127), 500, 31),
+                                          ((512, 17, 250), 460, 30), ((2100, 2200), 513, 30)])
+def test_expand_bit_exact_with_many_terms_on_large_tiles(scd, oracle, shape, w, bits):
+    test_expand_bit_exact_over_the_span_of_the_coefficients(scd, oracle, shape, w, bits)
+
+
+# the last term that the f64 form takes at once and the next, by the size of the matrix; the last of one launch
+@pytest.mark.parametrize("shape,w", [((1024, 1024), 48), ((1024, 1024), 49), ((1025, 1024), 32), ((1025, 1024), 33), ((2049, 2048), 20),
+                                     ((2049, 2048), 21), ((300, 200), 448)])
+def test_expand_bit_exact_where_the_form_changes(scd, oracle, shape, w):
+    test_expand_bit_exact_over_the_span_of_the_coefficients(scd, oracle, shape, w, 30)
+
+
+@pytest.mark.parametrize("w", [70, 460])
+def test_expand_bit_exact_at_the_ends_of_the_exponents(scd, oracle, w):
     rs = np.random.Generator(np.random.PCG64(3))
-    signs = [np.stack([oracle.pack(rs.standard_normal(d)) for _ in range(70)]) for d in (66, 70)]
+    signs = [np.stack([oracle.pack(rs.standard_normal(d)) for _ in range(w)]) for d in (66, 70)]
     db = [to_dev_bits(s) for s in signs]
-    for c in (rs.integers(1, 1 << 20, 70).astype(np.float32) * np.float32(2.0 ** -149), np.float32(3e38) * rs.random(70).astype(np.float32),
-              np.zeros(70, np.float32), rs.standard_normal(70) * 1e-309, rs.standard_normal(70) * 1e300):
+    for c in (rs.integers(1, 1 << 20, w).astype(np.float32) * np.float32(2.0 ** -149), np.float32(3e38) * rs.random(w).astype(np.float32),
+              np.zeros(w, np.float32), rs.standard_normal(w) * 1e-309, rs.standard_normal(w) * 1e300):
         ref = oracle.expand(signs, c.astype(np.float64), (66, 70))
         with np.errstate(over="ignore"):
             ref = ref.astype(c.dtype)
