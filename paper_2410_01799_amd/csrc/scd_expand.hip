@@ -525,9 +525,10 @@ __device__ __forceinline__ void ex_int_tiles(const uint64_t* __restrict__ S, con
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int off = a * 32 + 8 * (r >> 2) + (r & 3);
-                    double v = (double)(rows[off][ND - 1] - 2 * acc[a][ND - 1][r]);
+                    // (one at a time: twice the sum passes 32 bits from 2^23 terms on, both differences never do)
+                    double v = (double)(rows[off][ND - 1] - acc[a][ND - 1][r] - acc[a][ND - 1][r]);
 #pragma unroll
-                    for (int g = ND - 2; g >= 0; --g) v = v * 255.0 + (double)(rows[off][g] - 2 * acc[a][g][r]);
+                    for (int g = ND - 2; g >= 0; --g) v = v * 255.0 + (double)(rows[off][g] - acc[a][g][r] - acc[a][g][r]);
                     if (row_i + off < m) *po = (float)(v * unit);
                     po += (r & 3) == 3 ? 5 * n : n;
                     if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);  // (no room for more entries at a time)

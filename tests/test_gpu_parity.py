@@ -86,6 +86,13 @@ def test_expand_bit_exact(scd, oracle, shape, w, dtype):
 def test_expand_bit_exact_over_the_span_of_the_coefficients(scd, oracle, shape, w, bits):
     # f32 coefficients that span `bits` bits from the highest to the lowest one set: 30 is the last span of four int8
     # digits, 38 of five, above that the sums are f64; a span of 53 - log2(w) bits is the last with exact sums
+    signs, c = spanning(oracle, shape, w, bits)
+    got = scd.scd_expand([to_dev_bits(s) for s in signs], dev(c), shape).cpu().numpy()
+    ref = oracle.expand(signs, c.astype(np.float64), shape).astype(np.float32)
+    assert np.array_equal(got, ref)
+
+
+def spanning(oracle, shape, w, bits):
     rs = np.random.Generator(np.random.PCG64(w + bits))
     signs = [np.stack([oracle.pack(rs.standard_normal(d)) for _ in range(w)]) for d in shape]
     mant = rs.integers(1 << 23, 1 << 24, w) | 1                    # 24 significant bits
@@ -95,9 +102,7 @@ def test_expand_bit_exact_over_the_span_of_the_coefficients(scd, oracle, shape, 
     if w > 10:
         c[w // 2] = 0.0
         c[3] = 2.0 ** -20                                           # (a power of two: trailing zeros only)
-    got = scd.scd_expand([to_dev_bits(s) for s in signs], dev(c), shape).cpu().numpy()
-    ref = oracle.expand(signs, c.astype(np.float64), shape).astype(np.float32)
-    assert np.array_equal(got, ref)
+    return signs, c
 
 
 # large matrices and tensors (the last tiles ragged) in all three forms, whole and cut chunks of terms, more tiles than
@@ -116,10 +121,19 @@ def test_expand_bit_exact_with_many_terms(scd, oracle, shape, w, bits):
     test_expand_bit_exact_over_the_span_of_the_coefficients(scd, oracle, shape, w, bits)
 
 
-@pytest.mark.parametrize("shape,w,bits", [((1470, 1500), 449, 30), ((1409, 1537), 513, 38), ((1500, 1400), 512, 60), ((130, 127 * 127), 500, 31),
-                                          ((512, 17, 250), 460, 30), ((2100, 2200), 513, 30)])
+# (every f64 sum of these is exact, so a matrix product of any order has the bits of the definition)
+@pytest.mark.parametrize("shape,w,bits", [((1470, 1500), 449, 30), ((1409, 1537), 513, 38), ((1500, 1400), 512, 24), ((130, 127 * 127), 500, 31),
+                                          ((2100, 2200), 513, 30), ((2100, 2200), 640, 38)])
 def test_expand_bit_exact_with_many_terms_on_large_tiles(scd, oracle, shape, w, bits):
-    test_expand_bit_exact_over_the_span_of_the_coefficients(scd, oracle, shape, w, bits)
+    signs, c = spanning(oracle, shape, w, bits)
+    assert bits + np.ceil(np.log2(w)) <= 53
+    S, T = (np.stack([oracle.unpack(x, d) for x in s]) for s, d in zip(signs, shape))
+    got = scd.scd_expand([to_dev_bits(s) for s in signs], dev(c), shape).cpu().numpy()
+    assert np.array_equal(got, ((S * c.astype(np.float64)[:, None]).T @ T).astype(np.float32))
+
+
+def test_expand_bit_exact_with_many_terms_on_large_tiles_of_the_f64_form(scd, oracle):
+    test_expand_bit_exact_over_the_span_of_the_coefficients(scd, oracle, (1409, 1537), 450, 60)
 
 
 # the last term that the f64 form takes at once and the next, by the size of the matrix; the last of one launch
@@ -140,6 +154,15 @@ def test_expand_bit_exact_at_the_ends_of_the_exponents(scd, oracle, w):
         with np.errstate(over="ignore"):
             ref = ref.astype(c.dtype)
         assert np.array_equal(scd.scd_expand(db, dev(c), (66, 70)).cpu().numpy(), ref)
+
+
+def test_expand_past_two_to_the_23_terms(scd):
+    # the same term 9 000 000 times with the largest digit: twice a column's sum of digits passes 2^31, its entries do not
+    w, word = 9_000_000, 0x5A0F33C9_71E2846B
+    bits = torch.full((w, 1), word, dtype=torch.int64, device="cuda")
+    got = scd.scd_expand([bits, bits], torch.full((w,), 127.0, device="cuda"), (64, 64)).cpu().numpy()
+    s = np.where((np.uint64(word) >> np.arange(64, dtype=np.uint64)) & np.uint64(1), -1.0, 1.0)
+    assert np.array_equal(got, (127.0 * w * np.outer(s, s)).astype(np.float32))
 
 
 def test_expand_zero_terms(scd):
