@@ -103,21 +103,6 @@ int resident_workgroups(scd_dtype dt, const int64_t* dims)
     return resident_shape(dt, dims[0], dims[1], &p, &tr, &tc) ? p * p : 0;
 }
 
-// Types of the sums.  f64 matrices: f64 throughout.  f32 matrices whose rows are 16-byte steps: f32 inside a workgroup.
-// The other f32 matrices come here from the launch stream, which adds across lanes, waves and workgroups in f64 after f32
-// sums of ceil(n / 64) entries a lane (rows) and ceil(m / 256) rows a workgroup (columns): here f64 inside a workgroup, and
-// f32 words where one rounding a workgroup is no more than those f32 sums cost, that is from two of them on each side
-// (emulated, rms error of the row and column sums against f64, launch stream / here: 257x255 4.5e-8, 3.0e-8 / 2.6e-8,
-// 2.7e-8; 1501x999 7.3e-8, 5.1e-8 / 2.4e-8, 2.5e-8; 4095x4093 1.5e-7, 7.8e-8 / 2.6e-8, 2.5e-8; with f32 sums inside the
-// workgroup too the column sums of 1501x999 are off by 7.9e-8).  Smaller ones exchange f64, and those whose sums of up
-// to 256 entries a workgroup could pass the largest f32: they are at most 16 ||R||_F.
-enum class ResSums { plain, wide_inside, wide };
-static ResSums resident_sums(scd_dtype dt, int64_t m, int64_t n, double fro)
-{
-    if (dt == SCD_F32 && n % ResVec<float>::N == 0) return ResSums::plain;
-    return dt == SCD_F32 && m > 256 && n > 128 && fro < 1e36 ? ResSums::wide_inside : ResSums::wide;
-}
-
 // Sleep units between publishing and the first read, per exchange, from the option's value (default 16).  A read
 // that comes before the last partner's words costs another trip to memory (0.4 us and its traffic), one that comes
 // late costs what it waits, so the optimum is just behind the arrival, which moves with the words of an exchange.
@@ -159,66 +144,37 @@ static hipError_t launch_resident_k(const ResidentArgs& a, hipStream_t st)
     return hipGetLastError();
 }
 
-template <typename TE, int TR, int TC, int P>
+template <typename TE, typename Tile>
 static hipError_t launch_resident_t(const ResidentArgs& a, hipStream_t st)
 {
-    // does the grid of P x P blocks of 32 TR x 16 TC overhang the matrix?
-    const bool padded = (int64_t)P * 32 * TR != a.m || (int64_t)P * 16 * TC != a.n;
-    if constexpr (P == 1 && sizeof(TE) == 4) {
-        // f32 sums inside a thread (columns: a wave), f64 beyond; rows that are no 16-byte steps: f64 from the first addition
-        if (a.n % ResVec<float>::N != 0) return launch_resident_k<TE, double, double, TR, TC, P, true>(a, st);
-        return padded ? launch_resident_k<TE, double, float, TR, TC, P, true>(a, st) : launch_resident_k<TE, double, float, TR, TC, P, false>(a, st);
-    } else {
-        if constexpr (sizeof(TE) == 4) {
-            // (rows that are no 16-byte steps never fit the grid exactly)
-            const ResSums sums = resident_sums(SCD_F32, a.m, a.n, a.fro);
-            if (sums == ResSums::wide_inside) return launch_resident_k<TE, double, TE, TR, TC, P, true>(a, st);
-            if (sums == ResSums::wide) return launch_resident_k<TE, double, double, TR, TC, P, true>(a, st);
-        }
-        return padded ? launch_resident_k<TE, TE, TE, TR, TC, P, true>(a, st) : launch_resident_k<TE, TE, TE, TR, TC, P, false>(a, st);
+    constexpr scd_dtype dt = sizeof(TE) == 4 ? SCD_F32 : SCD_F64;
+    constexpr int P = Tile::P, TR = Tile::TR, TC = Tile::TC;
+    // one workgroup: f32 sums inside a thread (columns: a wave), f64 beyond; in f32 rows that are no 16-byte steps f64 from
+    // the first addition
+    using TA = std::conditional_t<P == 1, double, TE>;
+    const int form = resident_form(dt, a.m, a.n, a.fro, P, TR, TC);
+    if constexpr (Tile::taken(dt, kResExact)) {
+        if (form == kResExact) return launch_resident_k<TE, TA, TE, TR, TC, P, false>(a, st);
     }
-}
-
-template <typename TE, int P>
-static hipError_t launch_resident_p(const ResidentArgs& a, int tr, int tc, hipStream_t st)
-{
-    const int key = tr * 100 + tc;
-    switch (key) {
-        case 204: return launch_resident_t<TE, 2, 4, P>(a, st);
-        case 208: return launch_resident_t<TE, 2, 8, P>(a, st);
-        case 404: return launch_resident_t<TE, 4, 4, P>(a, st);
-        case 408: return launch_resident_t<TE, 4, 8, P>(a, st);
-        default: break;
+    if constexpr (Tile::taken(dt, (int)ResSums::plain)) {
+        if (form == (int)ResSums::plain) return launch_resident_k<TE, TA, TE, TR, TC, P, true>(a, st);
     }
-    if constexpr (P >= 8 || P == 1) {
-        switch (key) {
-            case 216: return launch_resident_t<TE, 2, 16, P>(a, st);
-            case 416: return launch_resident_t<TE, 4, 16, P>(a, st);
-            case 804: return launch_resident_t<TE, 8, 4, P>(a, st);
-            case 808: return launch_resident_t<TE, 8, 8, P>(a, st);
-            default: break;
-        }
-        if constexpr (sizeof(TE) == 4) {
-            if (key == 816) return launch_resident_t<TE, 8, 16, P>(a, st);
-        }
+    if constexpr (Tile::taken(dt, (int)ResSums::wide_inside)) {
+        if (form == (int)ResSums::wide_inside) return launch_resident_k<TE, double, TE, TR, TC, P, true>(a, st);
+    }
+    if constexpr (Tile::taken(dt, (int)ResSums::wide)) {
+        if (form == (int)ResSums::wide) return launch_resident_k<TE, double, double, TR, TC, P, true>(a, st);
     }
     return hipErrorInvalidValue;
-}
-
-template <typename TE>
-static hipError_t launch_resident_e(const ResidentArgs& a, int p, int tr, int tc, hipStream_t st)
-{
-    if (p == 16) return launch_resident_p<TE, 16>(a, tr, tc, st);
-    if (p == 8) return launch_resident_p<TE, 8>(a, tr, tc, st);
-    if (p == 1) return launch_resident_p<TE, 1>(a, tr, tc, st);
-    return launch_resident_p<TE, 4>(a, tr, tc, st);
 }
 
 hipError_t launch_resident(const ResidentArgs& a, scd_dtype dt, hipStream_t st)
 {
     int p = 0, tr = 0, tc = 0;
     if (!resident_shape(dt, a.m, a.n, &p, &tr, &tc)) return hipErrorInvalidValue;
-    return dt == SCD_F32 ? launch_resident_e<float>(a, p, tr, tc, st) : launch_resident_e<double>(a, p, tr, tc, st);
+    return res_with_tile(p, tr, tc, [&](auto tile) {
+        return dt == SCD_F32 ? launch_resident_t<float, decltype(tile)>(a, st) : launch_resident_t<double, decltype(tile)>(a, st);
+    });
 }
 
 }  // namespace scd

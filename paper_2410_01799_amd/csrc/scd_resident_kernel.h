@@ -1,9 +1,10 @@
-// The kernel of the register-resident engine and the rule that picks its shape (shared by the decomposition and the least
-// squares decomposition, each of which instantiates its own forms).
+// The kernel of the register-resident engine (shared by the decomposition and the least squares decomposition, each of
+// which instantiates its own forms; the rule that picks the form is in scd_resident_shape.h).
 #pragma once
 #include <type_traits>
 
 #include "scd_device.h"
+#include "scd_resident_shape.h"
 #include "scd_rng.h"
 
 namespace scd {
@@ -829,56 +830,30 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
     }
 }
 
-// Grid side P and thread tile TR x TC for an m x n matrix: the P x P workgroups of 32 x 16 threads cover
-// P * 32 * TR rows and P * 16 * TC columns, at least the matrix (the overhang is kept as zeros).  Fewer
-// workgroups mean fewer partners per exchange, more workgroups less arithmetic each; measured on the square
-// sizes (256 and 512 fastest with 8 values per thread on 4 x 4 and 8 x 8 workgroups, 1024 with 32 values on
-// 8 x 8, 2048 with 32 values on 16 x 16), which gives the order of preference: the smallest grid of at most
-// 8 x 8 with at most 8 values per thread, else the smallest grid with at most 32, else the grid that fits with
-// the smallest tile.  Rows that are no multiple of 16 bytes are loaded and written back element by element, once per
-// launch (1501x999, 16 terms: 2.4 ms a call; two launches per alternation on the unaligned rows took 8.7 ms).
-inline bool resident_shape(scd_dtype dt, int64_t m, int64_t n, int* p, int* tr, int* tc)
+template <int P_, int TR_, int TC_>
+struct ResTile {
+    static constexpr int P = P_, TR = TR_, TC = TC_;
+    static constexpr bool taken(scd_dtype dt, int form) { return kResForms.taken(dt, form, P, TR, TC); }
+};
+// f(ResTile) for the numbers that resident_shape gives
+template <int P, int TR, typename F>
+hipError_t res_with_columns(int tc, F& f)
 {
-    if (m < 1 || n < 4) return false;
-    const int most = dt == SCD_F32 ? 128 : 64;  // values a thread can hold
-    static const int grids[3] = {4, 8, 16};
-    static const int trs[3] = {2, 4, 8}, tcs[3] = {4, 8, 16};
-    // One workgroup, whatever a thread can hold (odd f32 rows: 64 values, which are widened in every phase): three barriers
-    // an alternation instead of two exchanges.  Us per alternation, 4 x 4 workgroups / one: f32 64x64 3.15 / 1.07, 128x128
-    // 3.01 / 1.31, 256x128 3.02 / 1.60, 192x192 2.97 / 2.40, 256x256 2.91 / 2.17; 61x67 3.69 / 1.43, 130x101 3.62 / 2.37,
-    // 127x255 3.64 / 2.74; f64 128x128 3.56 / 1.47, 256x128 3.55 / 1.84, 127x255 3.59 / 2.28.
-    {
-        int r = 0, c = 0;
-        for (int t : trs)
-            if (!r && 32 * t >= m) r = t;
-        for (int t : tcs)
-            if (!c && 16 * t >= n) c = t;
-        if (r && c && r * c <= (dt == SCD_F32 && n % ResVec<float>::N == 0 ? 128 : 64)) {
-            *p = 1, *tr = r, *tc = c;
-            return true;
-        }
-    }
-    int best = -1, bp = 0, btr = 0, btc = 0;
-    for (int pass = 0; pass < 2; ++pass) {
-        for (int P : grids) {
-            int r = 0, c = 0;
-            for (int t : trs)
-                if (!r && (int64_t)P * 32 * t >= m) r = t;
-            for (int t : tcs)
-                if (!c && (int64_t)P * 16 * t >= n) c = t;
-            if (!r || !c || r * c > most) continue;
-            if (P == 4 && (r > 4 || c > 8)) continue;  // (the 4 x 4 grid is built with the small tiles only)
-            if (pass == 0 ? (P <= 8 && r * c <= 8) : (r * c <= 32)) {
-                *p = P, *tr = r, *tc = c;
-                return true;
-            }
-            if (best < 0 || r * c < best) best = r * c, bp = P, btr = r, btc = c;
-        }
-    }
-    if (best < 0) return false;
-    *p = bp, *tr = btr, *tc = btc;
-    return true;
+    if (tc == 4) return f(ResTile<P, TR, 4>());
+    return tc == 8 ? f(ResTile<P, TR, 8>()) : f(ResTile<P, TR, 16>());
 }
-
+template <int P, typename F>
+hipError_t res_with_rows(int tr, int tc, F& f)
+{
+    if (tr == 2) return res_with_columns<P, 2>(tc, f);
+    return tr == 4 ? res_with_columns<P, 4>(tc, f) : res_with_columns<P, 8>(tc, f);
+}
+template <typename F>
+hipError_t res_with_tile(int p, int tr, int tc, F f)
+{
+    if (p == 1) return res_with_rows<1>(tr, tc, f);
+    if (p == 4) return res_with_rows<4>(tr, tc, f);
+    return p == 8 ? res_with_rows<8>(tr, tc, f) : res_with_rows<16>(tr, tc, f);
+}
 
 }  // namespace scd

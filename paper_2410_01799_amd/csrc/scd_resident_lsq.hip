@@ -32,37 +32,15 @@ static hipError_t lsq_k(LsqDo& d)
     return e;
 }
 
-template <int P>
-static hipError_t lsq_p(LsqDo& d, int tr, int tc)
-{
-    const int key = tr * 100 + tc;
-    switch (key) {
-        case 204: return lsq_k<2, 4, P>(d);
-        case 208: return lsq_k<2, 8, P>(d);
-        case 404: return lsq_k<4, 4, P>(d);
-        case 408: return lsq_k<4, 8, P>(d);
-        default: break;
-    }
-    if constexpr (P >= 8 || P == 1) {
-        switch (key) {
-            case 216: return lsq_k<2, 16, P>(d);
-            case 416: return lsq_k<4, 16, P>(d);
-            case 804: return lsq_k<8, 4, P>(d);
-            case 808: return lsq_k<8, 8, P>(d);
-            default: break;
-        }
-    }
-    return hipErrorInvalidValue;
-}
-
 static hipError_t lsq_do(LsqDo& d, int64_t m, int64_t n)
 {
     int p = 0, tr = 0, tc = 0;
     if (!resident_shape(SCD_F64, m, n, &p, &tr, &tc)) return hipErrorInvalidValue;
-    if (p == 16) return lsq_p<16>(d, tr, tc);
-    if (p == 8) return lsq_p<8>(d, tr, tc);
-    if (p == 1) return lsq_p<1>(d, tr, tc);
-    return lsq_p<4>(d, tr, tc);
+    return res_with_tile(p, tr, tc, [&](auto tile) {
+        using Tile = decltype(tile);
+        if constexpr (Tile::taken(SCD_F64, kResExact) || Tile::taken(SCD_F64, (int)ResSums::plain)) return lsq_k<Tile::TR, Tile::TC, Tile::P>(d);
+        else return hipErrorInvalidValue;
+    });
 }
 
 int resident_lsq_room(const int64_t* dims)
