@@ -38,7 +38,7 @@ static hipError_t lsq_do(LsqDo& d, int64_t m, int64_t n)
     if (!resident_shape(SCD_F64, m, n, &p, &tr, &tc)) return hipErrorInvalidValue;
     return res_with_tile(p, tr, tc, [&](auto tile) {
         using Tile = decltype(tile);
-        if constexpr (Tile::taken(SCD_F64, kResExact) || Tile::taken(SCD_F64, (int)ResSums::plain)) return lsq_k<Tile::TR, Tile::TC, Tile::P>(d);
+        if constexpr (Tile::taken(SCD_F64, kResExact) || Tile::taken(SCD_F64, (int)ResSums::wide)) return lsq_k<Tile::TR, Tile::TC, Tile::P>(d);
         else return hipErrorInvalidValue;
     });
 }

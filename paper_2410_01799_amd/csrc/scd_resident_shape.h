@@ -66,17 +66,18 @@ constexpr bool resident_shape(scd_dtype dt, int64_t m, int64_t n, int* p, int* t
 // 2.7e-8; 1501x999 7.3e-8, 5.1e-8 / 2.4e-8, 2.5e-8; 4095x4093 1.5e-7, 7.8e-8 / 2.6e-8, 2.5e-8; with f32 sums inside the
 // workgroup too the column sums of 1501x999 are off by 7.9e-8).  Smaller ones exchange f64, and those whose sums of up
 // to 256 entries a workgroup could pass the largest f32: they are at most 16 ||R||_F.
+// plain: the input's type (one workgroup: see the kernel), wide: f64 throughout.
 enum class ResSums { plain, wide_inside, wide };
 constexpr ResSums resident_sums(scd_dtype dt, int64_t m, int64_t n, double fro)
 {
-    if (dt != SCD_F32 || n % 4 == 0) return ResSums::plain;
-    return m > 256 && n > 128 && fro < 1e36 ? ResSums::wide_inside : ResSums::wide;
+    if (dt == SCD_F32 && n % 4 == 0) return ResSums::plain;
+    return dt == SCD_F32 && m > 256 && n > 128 && fro < 1e36 ? ResSums::wide_inside : ResSums::wide;
 }
 
 // The forms of the kernel that some matrix takes; no others are built.  The rules above change only where a side passes what a
 // grid and tile cover and with the remainder of a row by 4 (256 rows and 128 columns are such sides), so the smallest sizes and
 // those at and one or four past such a side stand for all.
-constexpr int kResExact = 3;  // plain sums and a matrix that the grid covers without overhang (0 .. 2: ResSums, overhang)
+constexpr int kResExact = 3;  // rows of 16-byte steps and a matrix that the grid covers without overhang (0 .. 2: ResSums, overhang)
 constexpr int res_log2(int v) { return v <= 1 ? 0 : 1 + res_log2(v / 2); }
 struct ResForms {
     bool at[2][4][5][4][5];  // [type][form][log2 P][log2 TR][log2 TC]

@@ -16,6 +16,10 @@ int main()
                 int p = 0, tr = 0, tc = 0;
                 if (!resident_shape((scd_dtype)dt, m, n, &p, &tr, &tc)) continue;
                 ++taken;
+                if (dt == SCD_F64 && resident_sums(SCD_F64, m, n, 0.0) != ResSums::wide) {
+                    std::printf("f64 %ld x %ld: two words a value\n", (long)m, (long)n);
+                    return 1;
+                }
                 const bool grid = (p == 1 || p == 4 || p == 8 || p == 16) && (tr == 2 || tr == 4 || tr == 8) && (tc == 4 || tc == 8 || tc == 16);
                 if (!grid || (int64_t)p * 32 * tr < m || (int64_t)p * 16 * tc < n || tr * tc > (dt == SCD_F32 ? 128 : 64)) {
                     std::printf("type %d %ld x %ld: grid %d tile %d x %d\n", dt, (long)m, (long)n, p, tr, tc);
