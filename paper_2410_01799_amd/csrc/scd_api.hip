@@ -1560,7 +1560,8 @@ int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uin
         if (dev) pool_free(dev);
         return SCD_ENOMEM;
     }
-    // a second one, which only the engine needs: its result and the slots of its exchanges
+    // a second one, which only the engine needs: the slots of its exchanges (at the block's start: they are lines of memory
+    // that one workgroup writes and others poll) and its result
     const int64_t dims[2] = {m, n};
     const size_t xbuf_bytes = resident && resident_workgroups(SCD_F64, dims) > 1 ? (size_t)4 * kResGrid * kResGrid * kResSlotWords * 8 : 0;
     const size_t res_bytes = (sizeof(ResidentResult) + 7) & ~(size_t)7;
@@ -1613,8 +1614,8 @@ int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uin
     a.bvec = (double*)take(w);
     double* sq = (double*)take(nsq);
     double* scal = (double*)take(2);
-    ResidentResult* res = (ResidentResult*)eng;
-    uint64_t* xbuf = eng ? (uint64_t*)((char*)eng + res_bytes) : nullptr;
+    uint64_t* xbuf = (uint64_t*)eng;
+    ResidentResult* res = eng ? (ResidentResult*)((char*)eng + xbuf_bytes) : nullptr;
     a.trace = fro_trace;
     a.iters = (int32_t*)p;
     a.st = (LsqState*)((char*)p + (((size_t)w * 4 + 15) & ~(size_t)15));
