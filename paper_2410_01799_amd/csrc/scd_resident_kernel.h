@@ -345,38 +345,59 @@ __device__ __forceinline__ void res_load_block(const TS* __restrict__ A, int64_t
     }
 }
 
-// x <- x - sum_j c_j s_j t_j^T for the k terms so far, in their order.  A thread's rows lie in one word of s, its columns in
-// one of t; the words of four terms are in flight together.
+// x <- x - sum_j c_j s_j t_j^T for the k terms so far, in their order: one fused multiply-add per entry and term (the product
+// of -c_j s_j with t_j = +-1 is exact).  The block's words of 64 terms at a time go through LDS, the next ones on their way from
+// memory meanwhile: with the words of four terms in a thread's registers the chain of trips to memory was the bound
+// (ms a call, before / here: 1024x1024 to 512 terms 242 / 224, 256x128 to 512 211 / 181, to 1500 1918 / 1666, 100x900 to 1500 1540 / 1431).
 template <int TR, int TC>
-__device__ __forceinline__ void res_subtract_terms(const ResidentArgs& a, int64_t k, int64_t row0, int64_t col0, double (&x)[TR][TC])
+__device__ __forceinline__ void res_subtract_terms(const ResidentArgs& a, int64_t k, int pr, int pc, uint32_t* lds, double (&x)[TR][TC])
 {
-    const int64_t ws = row0 < a.m ? row0 >> 6 : 0, wt = col0 < a.n ? col0 >> 6 : 0;  // (the overhang is set to zero below)
-    const int bs = (int)(row0 & 63), bt = (int)(col0 & 63);
-    for (int64_t j0 = 0; j0 < k; j0 += 4) {
-        uint64_t sw[4], tw[4];
-        double cj[4];
+    constexpr int RW = TR / 2, CW = TC / 4, REC = 1 + RW + CW, NT = 64;  // a term: coefficient, words of rows and of columns
+    constexpr int PER = (NT * REC + kResThreads - 1) / kResThreads;
+    const int tid = threadIdx.x, tr = tid >> 4, tc = tid & 15;
+    uint64_t w[PER];
+    auto fetch = [&](int64_t j0) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int64_t j = j0 + i < k ? j0 + i : k - 1;
-            sw[i] = a.S[j * a.mw + ws];
-            tw[i] = a.T[j * a.nw + wt];
-            cj[i] = j0 + i < k ? a.coef[j] : 0.0;
+        for (int i = 0; i < PER; ++i) {
+            const int at = tid + i * kResThreads, f = at % REC;
+            const int64_t j = j0 + at / REC;
+            const int64_t row = (int64_t)pr * RW + f - 1, col = (int64_t)pc * CW + f - 1 - RW;
+            w[i] = 0;  // (past the last term: +0.0)
+            if (at < NT * REC && j < k) {
+                if (f == 0) w[i] = (uint64_t)__double_as_longlong(a.coef[j]);
+                else if (f <= RW) w[i] = row < a.mw ? a.S[j * a.mw + row] : 0;
+                else w[i] = col < a.nw ? a.T[j * a.nw + col] : 0;
+            }
         }
+    };
+    // a thread's rows lie in one half of a word, its columns in another
+    const int hr = 2 + (tr * TR >> 5), br = tr * TR & 31, hc = 2 + 2 * RW + (tc * TC >> 5), bc = tc * TC & 31;
+    if (k > 0) fetch(0);
+    for (int64_t j0 = 0; j0 < k; j0 += NT) {
+        __syncthreads();
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t sb = (uint32_t)(sw[i] >> bs), tb = (uint32_t)(tw[i] >> bt);
-            const uint32_t lo = (uint32_t)__double2loint(cj[i]);
-            uint32_t hi[TC];
+        for (int i = 0; i < PER; ++i)
+            if (const int at = tid + i * kResThreads; at < NT * REC) lds[2 * at] = (uint32_t)w[i], lds[2 * at + 1] = (uint32_t)(w[i] >> 32);
+        __syncthreads();
+        if (j0 + NT < k) fetch(j0 + NT);
+        const int n = k - j0 < NT ? (int)(k - j0) : NT;
+#pragma unroll 2
+        for (int j = 0; j < n; ++j) {
+            const uint32_t* rec = lds + 2 * j * REC;
+            const double c = __hiloint2double((int)rec[1], (int)rec[0]);
+            const uint32_t sb = ~(rec[hr] >> br), tb = rec[hc] >> bc;
+            double t[TC];
 #pragma unroll
-            for (int c = 0; c < TC; ++c) hi[c] = (uint32_t)__double2hiint(cj[i]) ^ (tb << (31 - c) & 0x80000000u);
+            for (int e = 0; e < TC; ++e) t[e] = __hiloint2double((int)(0x3FF00000u | (tb << (31 - e) & 0x80000000u)), 0);
 #pragma unroll
             for (int r = 0; r < TR; ++r) {
-                const uint32_t top = sb << (31 - r) & 0x80000000u;
+                const double cs = flip_by(c, sb << (31 - r) & 0x80000000u);  // -c_j s_j
 #pragma unroll
-                for (int c = 0; c < TC; ++c) x[r][c] -= __hiloint2double((int)(hi[c] ^ top), (int)lo);
+                for (int e = 0; e < TC; ++e) x[r][e] = __builtin_fma(cs, t[e], x[r][e]);
             }
         }
     }
+    const int64_t row0 = (int64_t)pr * 32 * TR + tr * TR, col0 = (int64_t)pc * 16 * TC + tc * TC;
 #pragma unroll
     for (int r = 0; r < TR; ++r)
 #pragma unroll
@@ -434,7 +455,8 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
         seq_v = a.lsq->seq_v;
         if (a.a_f32) res_load_block<float, TR, TC>((const float*)a.A, a.m, a.n, row0, col0, x);
         else res_load_block<double, TR, TC>((const double*)a.A, a.m, a.n, row0, col0, x);
-        res_subtract_terms<TR, TC>(a, k, row0, col0, x);
+        static_assert(sizeof(lds_q) >= 64 * (1 + TR / 2 + TC / 4) * 8, "records of 64 terms");
+        res_subtract_terms<TR, TC>(a, k, pr, pc, (uint32_t*)&lds_q[0][0], x);
     } else {
         const TE* base = Rm + row0 * a.n + col0;
         if (!padded || a.n % VE == 0) {

@@ -1,7 +1,7 @@
 // The register-resident engine for least squares decompositions (Algorithm 6, Section 3.3 of arXiv 2410.01799): one launch
 // finds one greedy cut of the remainder R = A - sum_j c_j s_j t_j^T.  The refit changes every coefficient with every
 // term, so the remainder is formed anew at the start of a launch, in f64 and in the registers: a thread loads its tile of A
-// and subtracts the terms from their sign bits (one add and one xor per entry and term), after which an alternation costs
+// and subtracts the terms from their sign bits (one multiply-add per entry and term), after which an alternation costs
 // what it does for a greedy decomposition in f64, two exchanges, whatever the number of terms.
 #include "scd_resident_kernel.h"
 

@@ -197,6 +197,13 @@ def test_lsq_resident_cuts(scd, oracle, m, n, w, dtype):
     run_and_check(scd, oracle, gauss((m, n), 5 * m + n, dtype), w, 6)
 
 
+# more terms than are staged at once when the remainder is formed (64), on grids of 8 x 8 and 16 x 16 and on one workgroup
+@pytest.mark.parametrize("m,n,w,dtype", [(270, 140, 67, np.float32), (20, 2100, 66, np.float32), (200, 100, 66, np.float64)])
+def test_lsq_remainder_of_many_terms(scd, oracle, m, n, w, dtype):
+    res, _ = run_and_check(scd, oracle, gauss((m, n), 4 * m + n, dtype), w, 7, cuts=0)
+    assert res["terms"] == (w, 0, 0)
+
+
 def test_lsq_refit_past_one_wave(scd, oracle):
     # 88 terms is what one wave refits; the next ones go to the workgroup's form
     run_and_check(scd, oracle, gauss((96, 84), 11, np.float64), 94, 7)
