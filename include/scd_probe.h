@@ -47,8 +47,8 @@ int scd_engine(const scd_ctx* ctx, int* engine, double* last_launch_seconds, dou
 int scd_stream_geometry(scd_dtype dt, int order, const int64_t* dims, int limit, int64_t out[8]);
 
 /* scd_lsq_decompose with a say in how the cuts are found, for tests and measurement.  cuts = 0: as scd_lsq_decompose
- * does; 1: by the three launches per sweep that serve what the register-resident engine does not take or has no
- * compute units for (SCD_EINVAL where they do not take the matrix); 2, 3: batches of that engine and of sweeps in turn,
+ * does; 1: by the three launches per sweep that serve what the register-resident engine does not take, is slower
+ * at (many terms of few sweeps) or has no compute units for (SCD_EINVAL where they do not take the matrix); 2, 3: batches of that engine and of sweeps in turn,
  * beginning with the engine (2) or the sweeps (3), as if its compute units were taken every other time (SCD_EINVAL where
  * the engine does not take the matrix).  batch: most terms of a batch of the engine, and what a batch of sweeps aims
  * at (64 in scd_lsq_decompose).  max_spin: as SCD_OPT_MAX_SPIN (default there: 2^22), for the engine's cuts; when one

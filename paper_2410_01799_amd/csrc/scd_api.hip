@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "scd_device.h"
+#include "scd_resident_shape.h"
 
 using namespace scd;
 
@@ -1532,11 +1533,25 @@ struct LsqForm {
 };
 constexpr int kLsqHostLoop = 100;  // of lsq_matrix: nothing done, the loop on the host is to take the call
 
+// Does the register-resident engine find the cut of term k faster than sweeps, given the sweeps of the terms so far?  It forms
+// the remainder first, some (0.17 + 0.0045 values of a thread) us per earlier term, and saves some 12 us per sweep; a
+// sweep grows by some 1 / 40 us per earlier term.  Fitted to calls of up to 1024 terms; from there on the sweeps are
+// faster (measured / by this rule): 16x2000 (2.2 sweeps a term) 100 / 103, 60x2000 (3.2) 153 / 167, 40x4000 (2.7) 174 /
+// 134, 64x256 (5.0) 222 / 318, 256x128 (8.6) 378 / 427, 100x900 (4.6) 641 / 447, 128x128 (8.8) 766 / 1134, 64x64 (6.3) 1258 /
+// 1571; never with 256x256 (12.4), 300x1000 (10.3), 512x512 and above.  Ms a call, engine alone / this: 256x128 to 1500
+// terms 1666 / 1514, 128x128 to 1500 1490 / 1470, 100x900 to 1500 1431 / 1418.
+bool lsq_resident_pays(int64_t k, int64_t sweeps, int values)
+{
+    if (k == 0) return true;
+    const double mean = (double)sweeps / (double)k;
+    return (double)k * (0.17 + 0.0045 * values - mean / 40.0) <= 12.0 * mean;
+}
+
 // Everything is enqueued blindly, batch by batch; launches past the end return at once.  A batch is either terms of the
 // register-resident engine, two launches each (its cut and the refit), or sweeps, three launches each.  `resident`: the
-// engine may take the matrix.  A batch of it needs its workgroups' compute units free of other persistent launches; it
+// engine may take the matrix; it does where it is faster (lsq_resident_pays).  A batch of it needs its workgroups' compute units free of other persistent launches; it
 // takes them without waiting and gives them back after at most form.batch terms, so that nobody waits for a whole
-// call.  Where they are taken, or a wait in a kernel gave up, the call goes on with sweeps, which run beside anything; a
+// call.  Where they are taken, it is slower, or a wait in a kernel gave up, the call goes on with sweeps, which run beside anything; a
 // term that they have begun when the compute units are free again is begun anew.  `sweeps`: the sweeps are no slower than the
 // host loop; if not, they only go on with calls that the engine has begun.
 int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uint64_t seed, int32_t max_iters, hipStream_t st, uint64_t* S,
@@ -1653,13 +1668,17 @@ int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uin
     r.coef = a.c;
     r.lsq = a.st;
     const int workgroups = resident ? resident_workgroups(SCD_F64, dims) : 0, capacity = device_cus();
+    int p_side = 0, tr = 1, tc = 1;
+    if (resident) (void)resident_shape(SCD_F64, m, n, &p_side, &tr, &tc);
+    const int values = tr * tc;
     bool begun = false;  // the sweeps are inside term k
     double per_term = 12.0, swept = 0.0;
     int64_t swept_terms = 0;
     for (int64_t turn = 0; !pin->state.done; ++turn) {
         const int64_t k = pin->state.k;
         SlotLease lease;
-        const bool mine = resident && (form.cuts < 2 || ((turn ^ form.cuts) & 1) == 0) && lease.try_acquire(workgroups, capacity);
+        const bool pays = !sweeps || form.cuts >= 2 || lsq_resident_pays(k, pin->state.total, values);
+        const bool mine = resident && pays && (form.cuts < 2 || ((turn ^ form.cuts) & 1) == 0) && lease.try_acquire(workgroups, capacity);
         if (mine) {
             begun = false;
             for (int64_t b = 0; b < form.batch && k + b < w; ++b) {

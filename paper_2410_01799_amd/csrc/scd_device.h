@@ -130,6 +130,7 @@ struct LsqState {
     int32_t status;  // 1: normal equations singular, 2: a cut value is not finite, 3: a bounded wait ran out
     int32_t warn;    // some term ended on max_iters
     uint32_t seq_u, seq_v;  // exchange sequence numbers used so far (register-resident cuts)
+    int64_t total;   // sweeps of the complete terms
 };
 
 struct ResidentArgs {

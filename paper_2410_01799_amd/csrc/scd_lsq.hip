@@ -594,6 +594,7 @@ __global__ void __launch_bounds__(kLqThreads) lsq_next_kernel(LsqMatArgs a)
         const double f2 = a.fro0sq - cb;
         a.trace[k + 1] = sqrt(f2 > 0.0 ? f2 : 0.0);
         st->k = k + 1;
+        st->total += a.iters[k];
         st->j = 0;
         st->c_prev = -INFINITY;
         if (k + 1 >= a.w) st->done = 1;
@@ -786,6 +787,7 @@ __global__ void __launch_bounds__(kLqThreads) lsq_term_kernel(LsqMatArgs a, cons
             const double f2 = a.fro0sq - cb;
             a.trace[k + 1] = sqrt(f2 > 0.0 ? f2 : 0.0);
             st->k = k + 1;
+            st->total += a.iters[k];
             if (k + 1 >= a.w) st->done = 1;
         }
     }

@@ -204,6 +204,13 @@ def test_lsq_remainder_of_many_terms(scd, oracle, m, n, w, dtype):
     assert res["terms"] == (w, 0, 0)
 
 
+def test_lsq_many_terms_of_few_sweeps(scd, oracle):
+    # two sweeps a term: behind some hundred terms the engine spends more on the remainder than it saves on them
+    res, _ = run_and_check(scd, oracle, gauss((8, 250), 4), 150, 7, cuts=0)
+    resident, sweeps, loop = res["terms"]
+    assert resident >= 64 and resident % 64 == 0 and sweeps > 0 and resident + sweeps == 150
+
+
 def test_lsq_refit_past_one_wave(scd, oracle):
     # 88 terms is what one wave refits; the next ones go to the workgroup's form
     run_and_check(scd, oracle, gauss((96, 84), 11, np.float64), 94, 7)
