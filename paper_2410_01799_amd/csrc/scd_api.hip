@@ -1736,9 +1736,9 @@ int lsq_decompose(const void* A, scd_dtype dt, int order, const int64_t* dims, i
         if (w > 0 && !signs[i]) return SCD_EINVAL;
     if (order == 2 && w > 0) {
         // The register-resident engine takes every matrix whose f64 remainder fits the register files.  Us a call, three
-        // launches per sweep / here: 64x64 f32 to 16 terms 1680 / 720, 100x900 f32 to 32 2170 / 1280, 1024x1024 f32 to 32
-        // 15100 / 5000, 2048x2048 f64 to 16 26000 / 5570, 4096x2048 f32 to 8 9380 / 2360, 1024x1024 f32 to 512 474000 /
-        // 244000; slower on none that was tried.
+        // launches per sweep / here: 64x64 f32 to 16 terms 1860 / 400, 100x900 f32 to 32 2150 / 1210, 1024x1024 f32 to 32
+        // 16300 / 4900, 1501x999 f32 to 24 14900 / 4820, 2048x2048 f64 to 16 22900 / 4930, 4096x2048 f32 to 8 9310 / 2330,
+        // 1024x1024 f32 to 512 468000 / 224000.  For many terms see lsq_resident_pays.
         const bool sweeps = lsq_matrix_supported(dt, dims[0], dims[1]);
         const bool resident = form.cuts != 1 && resident_supported(SCD_F64, 2, dims) && resident_workgroups(SCD_F64, dims) <= resident_lsq_room(dims);
         if ((form.cuts == 1 && !sweeps) || (form.cuts > 1 && !resident)) return SCD_EINVAL;

@@ -1,17 +1,19 @@
 // Least squares decomposition (Algorithm 6, Section 3.3 of arXiv 2410.01799): after every greedy signed
 // cut the coefficients of ALL terms are refitted, c = argmin ||A - S diag(c) T^T||_F.
 //
-// The remainder R_k = A - S_k diag(c_k) T_k^T is never formed: every coefficient changes with every term,
-// so keeping R up to date would cost a rank-k update per term.  Instead each half step of the cut works on
+// The remainder R_k = A - S_k diag(c_k) T_k^T is never kept: every coefficient changes with every term.  The
+// register-resident engine forms it anew for each cut (scd_resident_lsq.hip).  The sweeps and the host loop below leave it
+// implicit; each half step of their cut works on
 //     R t   = A t   - S (c o (T^T t)),        R^T s = A^T s - T (c o (S^T s)),
 // where A t and A^T s are the ordinary signed-sum passes over A, <t_j, t> = n - 2 popcount(t_j xor t)
 // comes from the bitsets, and the correction is a signed sum of k scalars per entry.  The normal equations
 // (Section 3.3) use the Gram matrix G_ij = <s_i,s_j><t_i,t_j>, again from popcounts, kept as a Cholesky
-// factor that grows by one row per term; b_j = <s_j, A t_j> falls out of the last half step of term j.
+// factor that grows by one row per term; b_j = <s_j, A t_j> falls out of the last half step of term j, or comes from the
+// cut value and the Gram row where the remainder was formed.
 // Everything here is f64; the kernels are small and latency-bound.  Matrices whose f64 remainder fits the register files
 // (up to 4096x2048 or 2048x4096): two launches per term, the cut on the register-resident engine (scd_resident_lsq.hip)
-// and lsq_term_kernel.  Others of up to 64 words a side: three launches per sweep and no host in the loop; larger ones, and
-// tensors: about ten and a read-back.
+// and lsq_term_kernel.  Others of up to 64 words a side, and those for which the engine has no compute units or is slower: three
+// launches per sweep and no host in the loop; larger ones, and tensors: about ten and a read-back.
 #include "scd_device.h"
 #include "scd_rng.h"
 
@@ -335,8 +337,8 @@ __global__ void __launch_bounds__(kLqThreads)
 }
 
 // =================================================================================================
-// Matrices of up to kLqMaxWords words a side that the register-resident engine does not take: a sweep (both half steps of Algorithm 4 on the implicit remainder, the
-// stop test and, at the end of a term, the refit) is three launches that the host enqueues blindly, many sweeps
+// Matrices of up to kLqMaxWords words a side, where the register-resident engine does not take the cut: a sweep (both half
+// steps of Algorithm 4 on the implicit remainder, the stop test and, at the end of a term, the refit) is three launches that the host enqueues blindly, many sweeps
 // ahead; the position of the loop lives on the device.  A half step is one launch because a workgroup owns one word (64 rows
 // or columns) from the entries of A to the sign bits: it forms the inner products with the earlier terms, the f64 sums
 // over its strip of A, the correction and the signs.  Bound by the chain of memory trips, barriers and launches, not by
@@ -602,8 +604,9 @@ __global__ void __launch_bounds__(kLqThreads) lsq_next_kernel(LsqMatArgs a)
     if (tid < nw) a.t[tid] = rng_word_masked(a.seed, (uint64_t)k + 1, 1u, tid, a.n);
 }
 
-// Few terms: the refit of lq_refit by one wave that holds two unknowns a lane, step for step (the same additions in the
-// same order), with the factor in LDS: no barrier and no trip to memory per unknown.
+// Few terms: the refit of lq_refit by one wave that holds two unknowns a lane, with the factor in LDS: no barrier and no trip
+// to memory per unknown.  Both substitutions are those of lq_refit step for step; the sums over the unknowns (the
+// squares, <row, y>, <c, b>) are added in another order.
 constexpr int kLqSmall = 88;  // most terms before the new one; their factor's triangle takes 31 KB
 static_assert(kLqSmall <= 2 * kWave && kLqSmall <= 6 * kLqWaves, "unknowns of a lane, terms of a wave");
 struct LqSmallShared {

@@ -14,7 +14,7 @@ SHAPES = [(1024, 4096), (2048, 2048), (4096, 4096), (256, 256), (512, 512), (102
 RAGGED = [(4096, 1024), (2048, 4096), (1000, 4096), (2052, 516), (100, 76), (8, 8), (5, 4096), (300, 260), (1, 4),
           (1030, 520), (4000, 4092), (64, 4096), (3000, 2000)]
 # rows that are no multiple of 16 bytes: first and last lengths, one and two elements past a tile or a word, the
-# largest; and the shapes whose 4 x 4 grid would need a tile it is not built with
+# largest; and the shapes whose 4 x 4 grid would need a tile that it does not take
 UNALIGNED = [(7, 5), (1, 6), (64, 63), (65, 257), (513, 129), (333, 1025), (1501, 999), (4096, 4093), (4095, 4095)]
 SMALL_OBLONG = [(128, 704), (200, 1024), (600, 256), (1024, 60)]
 

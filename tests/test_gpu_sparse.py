@@ -206,7 +206,7 @@ def test_share_limits_and_engine_choice(scd):
     B = torch.from_numpy(gauss((256, 256), 2)).cuda()
     with scd.ScdContext(B, 4, 1) as ctx:
         ctx.set_workgroups(64)
-        assert ctx.engine()["engine"] == 1            # 4 x 4 workgroups fit
+        assert ctx.engine()["engine"] == 1            # one workgroup holds it
     # a tensor has no persistent engine: the share is accepted and changes nothing
     Tn = torch.from_numpy(gauss((20, 30, 3), 3)).cuda()
     with scd.ScdContext(Tn, 4, 1) as ctx:
