@@ -146,8 +146,11 @@ def test_lsq_beside_a_context_waits_for_nothing(scd, oracle):
     ctx.set_workgroups(128)                               # 1040x1040 wants all compute units
     torch.cuda.synchronize()
     th, out = in_thread(lambda: ctx.run(12000))
+    A = torch.from_numpy(gauss((1040, 1040), 13)).cuda()
     with torch.cuda.stream(torch.cuda.Stream()):
-        res = scd.scd_lsq_decompose_form(torch.from_numpy(gauss((1040, 1040), 13)).cuda(), 4, 2)
+        res = scd.scd_lsq_decompose_form(A, 4, 2)
+        while th.is_alive() and res["terms"][0]:          # (the other thread's launch is not under way yet)
+            res = scd.scd_lsq_decompose_form(A, 4, 2)
     beside = th.is_alive()
     th.join()
     ctx.close()
