@@ -144,9 +144,9 @@ def test_lsq_beside_a_context_waits_for_nothing(scd, oracle):
     B = torch.from_numpy(gauss((2048, 1024), 12)).cuda()
     ctx = scd.ScdContext(B, 12000, 1)
     ctx.set_workgroups(128)                               # 1040x1040 wants all compute units
+    A = torch.from_numpy(gauss((1040, 1040), 13)).cuda()  # (on the stream that the context's launch will occupy)
     torch.cuda.synchronize()
     th, out = in_thread(lambda: ctx.run(12000))
-    A = torch.from_numpy(gauss((1040, 1040), 13)).cuda()
     with torch.cuda.stream(torch.cuda.Stream()):
         res = scd.scd_lsq_decompose_form(A, 4, 2)
         while th.is_alive() and res["terms"][0]:          # (the other thread's launch is not under way yet)
