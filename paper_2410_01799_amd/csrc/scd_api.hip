@@ -102,6 +102,7 @@ struct scd_ctx {
     ResidentResult* res_dev = nullptr;
     ResidentResult* res_pin = nullptr;
     uint32_t seq_u = 0, seq_v = 0;
+    int xbuf_sum = 0;               // bytes of a sum in the exchange slots as they were last written (0: cleared)
     double fro = 0.0;               // ||R||_F when the remainder was last given (terms only lower it)
     // sparse engine
     bool sparse = false;
@@ -569,9 +570,8 @@ int setup_engines(scd_ctx* c)
         c->seq_ps = 0;
     }
     if (c->resident && !c->xbuf && resident_workgroups(c->dt, c->dims) > 1) {  // (one workgroup exchanges nothing)
-        const size_t xb = (size_t)4 * kResGrid * kResGrid * kResSlotWords * 8;
-        SCD_TRY(dev_alloc(c, (void**)&c->xbuf, xb));
-        if (!hip_ok(hipMemsetAsync(c->xbuf, 0, xb, c->stream))) return SCD_EHIP;
+        SCD_TRY(dev_alloc(c, (void**)&c->xbuf, kResXbufBytes));
+        if (!hip_ok(hipMemsetAsync(c->xbuf, 0, kResXbufBytes, c->stream))) return SCD_EHIP;
     }
     if ((c->resident || c->sparse || c->pstream) && !c->res_dev) {
         SCD_TRY(dev_alloc(c, (void**)&c->res_dev, sizeof(ResidentResult)));
@@ -751,6 +751,15 @@ int run_resident(scd_ctx* c, int64_t n)
     a.max_spin = (int32_t)c->opt[SCD_OPT_MAX_SPIN];
     a.fro = c->fro;
     resident_poll_delays(c->dt, c->dims, c->fro, (int)c->opt[SCD_OPT_POLL_DELAY], &a.poll_delay, &a.poll_delay_v);
+    a.xexp = resident_exponent(c->fro, 0);
+    // a remainder of another size may have changed the type of the sums, and with it the words of a slot: the numbering starts
+    // again on cleared slots
+    const int sum = resident_sum_bytes(c->dt, c->dims, c->fro);
+    if (c->xbuf && c->xbuf_sum && c->xbuf_sum != sum) {
+        HIP_TRY(hipMemsetAsync(c->xbuf, 0, kResXbufBytes, c->stream));
+        c->seq_u = c->seq_v = 0;
+    }
+    c->xbuf_sum = sum;
     a.seq_u = c->seq_u;
     a.seq_v = c->seq_v;
     a.xbuf = c->xbuf;
@@ -1076,7 +1085,7 @@ int scd_set_remainder(scd_ctx* c, const void* R_in)
         // A launch that gave up left tagged words of exchanges it never finished in the slots, and its
         // sequence numbers were not handed back: start the numbering again on cleared buffers, so that no
         // stale word can pass for a fresh one.
-        if (c->xbuf) HIP_TRY(hipMemsetAsync(c->xbuf, 0, (size_t)4 * kResGrid * kResGrid * kResSlotWords * 8, c->stream));
+        if (c->xbuf) HIP_TRY(hipMemsetAsync(c->xbuf, 0, kResXbufBytes, c->stream));
         if (c->xbuf_sp) HIP_TRY(hipMemsetAsync(c->xbuf_sp, 0, sparse_xbuf_bytes(), c->stream));
         if (c->xbuf_p1) HIP_TRY(hipMemsetAsync(c->xbuf_p1, 0, c->xbuf_p1_bytes, c->stream));
         if (c->xbuf_p2) HIP_TRY(hipMemsetAsync(c->xbuf_p2, 0, c->xbuf_p2_bytes, c->stream));
@@ -1578,7 +1587,7 @@ int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uin
     // a second one, which only the engine needs: the slots of its exchanges (at the block's start: they are lines of memory
     // that one workgroup writes and others poll) and its result
     const int64_t dims[2] = {m, n};
-    const size_t xbuf_bytes = resident && resident_workgroups(SCD_F64, dims) > 1 ? (size_t)4 * kResGrid * kResGrid * kResSlotWords * 8 : 0;
+    const size_t xbuf_bytes = resident && resident_workgroups(SCD_F64, dims) > 1 ? kResXbufBytes : 0;
     const size_t res_bytes = (sizeof(ResidentResult) + 7) & ~(size_t)7;
     void* eng = nullptr;
     if (resident && pool_malloc(&eng, res_bytes + xbuf_bytes, false) != hipSuccess) {
@@ -1657,6 +1666,7 @@ int lsq_matrix(const void* A, scd_dtype dt, int64_t m, int64_t n, int64_t w, uin
     r.max_spin = (int32_t)form.max_spin;
     if (resident) resident_poll_delays(SCD_F64, dims, 0.0, form.max_spin ? 16 : 0, &r.poll_delay, &r.poll_delay_v);
     r.xbuf = xbuf;
+    r.xexp = resident_exponent(sqrt(a.fro0sq), 128);  // (a remainder that follows from coefficients: room for their errors)
     r.S = S;
     r.T = T;
     r.iters = a.iters;
@@ -2125,7 +2135,7 @@ int scd_probe_exchange(int which, int grid, int group, int rounds, void* stream,
     unsigned* flags = nullptr;  // [0] counter, [1] error
     float* out = nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr;
-    const size_t bufbytes = (size_t)2 * grid * 256 * 8;
+    const size_t bufbytes = (size_t)2 * grid * kResSlotWords * 8;
     hipError_t e = hipMalloc((void**)&buf, bufbytes);
     if (e == hipSuccess) e = hipMalloc((void**)&flags, 8);
     if (e == hipSuccess) e = hipMalloc((void**)&out, (size_t)grid * 4);

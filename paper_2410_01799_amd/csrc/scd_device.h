@@ -106,7 +106,8 @@ struct KronArgs {
 // 16 x 16 grid of co-resident workgroups for as many terms as requested.
 constexpr int kResGrid = 16;                       // workgroups per side
 constexpr int kResThreads = 512;
-constexpr int kResSlotWords = 512 + 8;             // exchange slot: up to 512 values + piggybacked scalars
+constexpr int kResSlotWords = 256 + 16;            // exchange slot: up to 256 words of sums, then scalars; whole lines of memory
+constexpr size_t kResXbufBytes = (size_t)4 * kResGrid * kResGrid * kResSlotWords * 8;
 
 struct ResidentResult {
     int64_t k;             // terms complete on exit
@@ -150,6 +151,7 @@ struct ResidentArgs {
     double* trace;
     int32_t mw, nw;
     double fro;              // a bound on ||R||_F (host side only: chooses the type of the sums)
+    int32_t xexp;            // exchanged sums are scaled by 2^-xexp (resident_exponent)
     ResidentResult* res;
     // least squares form: R, k_start, w_target, seq_u, seq_v, c and trace are not used
     const void* A;
@@ -159,6 +161,8 @@ struct ResidentArgs {
 };
 
 bool resident_supported(scd_dtype dt, int order, const int64_t* dims);
+int resident_exponent(double fro, int slack);  // of the scale of the exchanged sums, see ResidentArgs
+int resident_sum_bytes(scd_dtype dt, const int64_t* dims, double fro);  // of a sum in the exchange slots
 int resident_workgroups(scd_dtype dt, const int64_t* dims);  // workgroups of the launch for a supported shape
 void resident_poll_delays(scd_dtype dt, const int64_t* dims, double fro, int delay, int32_t* rows, int32_t* cols);  // of the two exchanges
 hipError_t launch_resident(const ResidentArgs& a, scd_dtype dt, hipStream_t st);

@@ -54,6 +54,42 @@ __global__ void __launch_bounds__(256) exchange_probe_kernel(uint64_t* buf, int 
     if (tid == 0) out[g] = carry;
 }
 
+// The same with the words and reads of the register-resident engine: 256 f32 sums a workgroup, groups of P neighbours.
+template <int P>
+__global__ void __launch_bounds__(kResThreads) resident_exchange_probe_kernel(uint64_t* buf, int rounds, int max_spin, unsigned* err, float* out)
+{
+    constexpr int N = 256;
+    using Read = ResRead<float, N, P>;
+    __shared__ float sum[N];
+    __shared__ int fail;
+    const int g = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(buf, 0, (int)((size_t)2 * gridDim.x * kResSlotWords * 8), 0x00027000);
+    const uint32_t off = (uint32_t)(tid % Read::L * Read::H * kResSlotWords) * 8u + (uint32_t)(tid / Read::L) * 16u;
+    if (tid < N) sum[tid] = 0.f;
+    if (tid == 0) fail = 0;
+    __syncthreads();
+    for (uint32_t r = 1; r <= (uint32_t)rounds; ++r) {
+        const uint32_t half = (r & 1u) * gridDim.x;
+        if (tid < N / 2) res_publish(buf + (size_t)(half + g) * kResSlotWords + tid, sum[2 * tid] * 0.01f, sum[2 * tid + 1] * 0.01f + 1e-3f, res_tag(r));
+        for (int d = 0; d < 16; ++d) __builtin_amdgcn_s_sleep(1);
+        double s[Read::Q] = {}, x0, x1;
+        int spin = 0;
+        if (tid < Read::waves * 64) {
+            if (!res_gather<float, Read::H, 0>(rs, (half + (uint32_t)(g / P * P)) * kResSlotWords * 8u, off, kResSlotWords * 8, true, 0, r, max_spin, s, x0,
+                                               x1, spin))
+                fail = 1;
+            const double v = res_join<Read::L, Read::Q>(s, lane);
+            if (tid % Read::L < Read::Q) sum[tid / Read::L * Read::Q + tid % Read::L] = (float)v;
+        }
+        __syncthreads();
+        if (fail) {
+            if (tid == 0) atomicExch(err, 1u);
+            return;
+        }
+    }
+    if (tid == 0) out[g] = sum[0];
+}
+
 // Classic counter barrier over the whole grid, for comparison.
 __global__ void __launch_bounds__(256) barrier_probe_kernel(unsigned* counter, int rounds, int max_spin, unsigned* err,
                                                            float* out)
@@ -84,7 +120,9 @@ __global__ void __launch_bounds__(256) barrier_probe_kernel(unsigned* counter, i
 hipError_t launch_exchange_probe(int which, int grid, uint64_t* buf, unsigned* counter, int rounds, int group,
                                  int max_spin, unsigned* err, float* out, hipStream_t st)
 {
-    if (which == 0)
+    if (which == 0 && group == 16)
+        hipLaunchKernelGGL(resident_exchange_probe_kernel<16>, dim3(grid), dim3(kResThreads), 0, st, buf, rounds, max_spin, err, out);
+    else if (which == 0)
         hipLaunchKernelGGL(exchange_probe_kernel, dim3(grid), dim3(256), 0, st, buf, rounds, group, max_spin, err, out);
     else
         hipLaunchKernelGGL(barrier_probe_kernel, dim3(grid), dim3(256), 0, st, counter, rounds, max_spin, err, out);
@@ -103,26 +141,43 @@ int resident_workgroups(scd_dtype dt, const int64_t* dims)
     return resident_shape(dt, dims[0], dims[1], &p, &tr, &tc) ? p * p : 0;
 }
 
+// Exponent e such that a workgroup's sums, which are at most 16 ||R||_F, stay below 2^e, with `slack` more: what is
+// exchanged is scaled by 2^-e.  No scaling up: a sum then keeps all its bits down to 2^-126 or 2^-1022 of that scale.
+int resident_exponent(double fro, int slack)
+{
+    int e = 0;
+    (void)frexp(16.0 * fro, &e);
+    e += slack;
+    return e > 0 ? e : 0;
+}
+
+int resident_sum_bytes(scd_dtype dt, const int64_t* dims, double fro)
+{
+    return resident_sums(dt, dims[0], dims[1], fro) == ResSums::wide ? 8 : 4;
+}
+
 // Sleep units between publishing and the first read, per exchange, from the option's value (default 16).  A read
 // that comes before the last partner's words costs another trip to memory (0.4 us and its traffic), one that comes
-// late costs what it waits, so the optimum is just behind the arrival, which moves with the words of an exchange.
-// Measured in us per alternation: grids of up to 8 x 8 at 10 units 2.87 (256^2) and 3.41 (1024^2), at 16 3.17 and
-// 3.70; 16 x 16 with slots of 256 columns at 18 / 14 units (rows / columns) 5.38 (4096^2), at 16 / 16 5.44, at
-// 12 / 8 5.84; with shorter slots at 16 / 8 4.55 (2048^2) and 4.95 (4096x1024), at 16 / 16 4.69 and 5.14.
-// f64 has twice the words: up to 8 x 8 at 10 / 10 3.40 (256^2), 4.55 (600x400) and 4.78 (1024^2), at 18 / 14 3.66, 4.71
-// and 4.81; 16 x 16 at 22 / 18 6.78 (1501x999) and 6.93 (2048^2), at 18 / 14 7.03 and 7.24, at 26 / 22 6.95 and 7.09; with
-// column slots of 256 values at 26 / 22 7.68 (2048x4096), at 22 / 18 8.56.  f64 sums inside a workgroup make the slots of
-// tall blocks later: three units more, 5.50 instead of 5.99 (3000x1999) and 6.77 instead of 7.40 (4095x4093).
+// late costs what it waits, so the optimum is just behind the arrival, which moves with the words of an exchange and with
+// what the slowest partner does before it publishes.  Rows (partners on all dies) need more than columns (one die).
+// Measured in us per alternation at (rows / columns): up to 8 x 8 workgroups at 17 / 8 2.87 (512^2), 3.10 (1024^2), f64 3.16
+// (600x400), 3.40 (1024^2), at 10 / 10 2.93, 3.18, 3.20, 3.42; 16 x 16 with at most 16 values a thread at 16 / 8 3.32 (1501x999),
+// f64 3.56, at 20 / 8 3.42, 3.57; f32 beyond at 19 / 8 3.45 (2048^2), at 18 / 14 3.56, with 256 columns a block at 19 / 11 4.37
+// (4096^2), 3.93 (1024x4096), at 18 / 8 4.62, 4.08; f64 at 23 / 8 4.02 (2048^2), 4.78 (4096x2048), at 16 / 8 4.21, 5.19, with 256
+// columns a block at 23 / 13 5.13 (2048x4096), at 22 / 8 5.41, and at 16 / 13 4.73 with two rows a thread (1024x4096), at 24 / 12 4.89.
 void resident_poll_delays(scd_dtype dt, const int64_t* dims, double fro, int delay, int32_t* rows, int32_t* cols)
 {
     int p = 16, tr = 8, tc = 16;
     (void)resident_shape(dt, dims[0], dims[1], &p, &tr, &tc);
-    int u = delay - 6, v = delay - 6;
     const ResSums sums = resident_sums(dt, dims[0], dims[1], fro);
-    const bool wide = sums == ResSums::wide;  // twice the words
-    if (sums == ResSums::wide_inside && p > 8 && tr > 2) delay = delay ? delay + 3 : 0;
-    if (p > 8 && !wide) u = delay + 2, v = tc == 16 ? delay - 2 : delay - 8;
-    if (p > 8 && wide) u = tc == 16 ? delay + 10 : delay + 6, v = tc == 16 ? delay + 6 : delay + 2;
+    int u = delay + 1, v = delay - 8;
+    if (p > 8 && sums == ResSums::wide) {
+        u = tr * tc <= 16 || tr == 2 ? delay : delay + 7;
+        if (tc == 16) v = delay - 3;
+    } else if (p > 8) {
+        u = tr * tc <= 16 ? delay : delay + 3;
+        if (tc == 16 && sums == ResSums::plain) v = delay - 5;
+    }
     *rows = delay == 0 || u < 0 ? 0 : u;
     *cols = delay == 0 || v < 0 ? 0 : v;
 }

@@ -71,25 +71,23 @@ __device__ __forceinline__ double wave_sum_res(double a)
 //   col phase   q_l = sum over the block's rows of +-R_il (signs s), published to the 16 workgroups
 //               of the same block column -> v_l, t_l, and this column block's share of c = sum |v_l|
 //
-// Exchange: value and sequence number travel in one 8-byte store (the datum is its own flag), read
+// Exchange: values and tag travel in one 8-byte store (the datum is its own flag, see res_tag below), read
 // back with loads that bypass the non-coherent caches; no counter, no fence.  Slots alternate by the
 // parity of the sequence number: a workgroup can only be one exchange ahead of the readers of its
 // slot, because finishing exchange e+1 needs data its readers publish after they have read e.
 // An alternation is bound by the latency of the two exchanges and by what lies between them on one workgroup per
 // compute unit (two waves per SIMD, so every vector instruction costs 8 cycles of the chain).  Measured at 4096x4096
 // (us per alternation): 6.33 with barriers that also join a predicate, full-width lane reductions (every lane ends
-// with every sum) and the stop test ahead of the column sums; 5.47 with one plain barrier per exchange, reductions
+// with every sum) and the stop test ahead of the column sums; 5.42 with one plain barrier per exchange, reductions
 // that halve the registers at each step, signs kept as factor bytes, scalar bases for the gathers and the test
-// behind the column sums; 5.40 with the poll delays of resident_poll_delays.  256x256: 3.9 -> 2.9, 1024x1024:
-// 4.4 -> 3.4, 2048x2048: 5.45 -> 4.65.
+// behind the column sums; 4.37 with two sums in a word and 16-byte reads (2048x2048 4.59 -> 3.43, 1024x1024 3.44 -> 3.10,
+// 512x512 3.31 -> 2.87).
 //
 // f64 (TE = double): everything the exchanges carry and the tiles hold stays 64 bits wide, so a thread holds at most 64
-// values (matrices up to 4096x2048 or 2048x4096) and a published value is two tagged words, all lower halves of a slot
-// before all upper ones, so that a wave's loads stay contiguous.  The same chain with twice the words; measured in us per
-// alternation against the best of the other engines on the same matrix: 256x256 3.4 (9.4 persistent stream), 1024x1024
-// 4.8 (11.2), 1501x999 6.8 (19.4, launch stream), 1024x4096 7.5 (15.2), 2048x2048 6.9 (13.6), 4096x2048 8.0 (9.7,
-// sparse), 2048x4096 7.7 (9.9, sparse), 2000x3999 7.7 (65.9, launch stream).  The 64-value tiles on 16 x 16 workgroups
-// spill 28 to 56 bytes a thread.
+// values (matrices up to 4096x2048 or 2048x4096) and a word is one sum.  Us per alternation with two words a sum / with one
+// (and the best of the other engines on the same matrix): 600x400 4.56 / 3.16 (9.0), 1024x1024 4.78 / 3.40 (11.2), 1501x999
+// 6.79 / 3.56 (19.4, launch stream), 1024x4096 7.68 / 4.73 (15.2), 2048x2048 6.95 / 4.02 (13.6), 4096x2048 8.00 / 4.78 (9.7,
+// sparse), 2048x4096 7.70 / 5.13 (9.9, sparse).
 // The sum of the 16 column-block shares of c rides on the next row-phase exchange, so the test of
 // Algorithm 4 line 8 is taken one phase late: the row phase already done with the final t is then
 // dropped.  ||R||_F^2 after an update travels the same way (block row sums, then the total).
@@ -104,10 +102,6 @@ __device__ __forceinline__ uint64_t* res_slot(const ResidentArgs& a, int kind, u
 {
     return a.xbuf + res_slot_off(kind, seq, wg);
 }
-__device__ __forceinline__ const char* res_slot_bytes(const ResidentArgs& a, int kind, uint32_t seq, int wg)
-{
-    return (const char*)(a.xbuf + res_slot_off(kind, seq, wg));
-}
 
 __device__ __forceinline__ double uniform_f64(double v)
 {
@@ -118,72 +112,125 @@ __device__ __forceinline__ double uniform_f64(double v)
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// Tagged words per published sum: the value itself (f32), or its two halves, `apart` words from each other (f64).
-template <typename TX>
-constexpr int kResWords = (int)(sizeof(TX) / 4);
+// Words of an exchange.  A sum that is published is scaled by a power of two so that it stays below 2 (a.xexp; a sum of up to
+// 256 entries is at most 16 ||R||_F), which leaves the top bit of its exponent clear: that bit carries the tag, so that
+// two f32 sums or one f64 sum fill an 8-byte word, a word is still stored and seen whole, and nothing else has to tell a fresh
+// word from the one that it replaces.  The tag flips each time that a slot is written (slots alternate, so every second
+// exchange); cleared slots are older than exchange 1.  f32 sums below 2^-126 of that scale lose bits, f64 ones 2^-1022.
+// A slot is read 16 bytes a lane.  Us per exchange of 256 sums alone, among 16 partners on one die / on eight: one f32 and a
+// 32-bit sequence number in a word, read 8 bytes a lane 1.55 / 1.85, read 16 bytes a lane 1.60 / 1.88, two f32 in a word
+// read 16 bytes a lane 1.17 / 1.49; f64 as two such words 2.50 / 2.87, as one word 1.58 / 1.89.
+constexpr uint32_t kResTagBit = 0x40000000u;
+__device__ __forceinline__ uint32_t res_tag(uint32_t seq) { return (((seq + 1u) >> 1) & 1u) ? kResTagBit : 0u; }
+__device__ __forceinline__ uint32_t res_tagged(uint32_t v, uint32_t tag) { return (v & ~kResTagBit) | tag; }
+__device__ __forceinline__ float res_scaled(float v, int e) { return __builtin_ldexpf(v, e); }
+__device__ __forceinline__ double res_scaled(double v, int e) { return __builtin_ldexp(v, e); }
 
-__device__ __forceinline__ void res_publish(uint64_t* p, int apart, float v, uint32_t seq)
+__device__ __forceinline__ void res_store(uint64_t* p, uint32_t lo, uint32_t hi)
 {
-    (void)apart;
-    __hip_atomic_store(p, ((uint64_t)seq << 32) | (uint64_t)__float_as_uint(v), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p, ((uint64_t)hi << 32) | (uint64_t)lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void res_publish(uint64_t* p, int apart, double v, uint32_t seq)
+// two neighbouring sums, or one
+__device__ __forceinline__ void res_publish(uint64_t* p, float v0, float v1, uint32_t tag)
 {
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    __hip_atomic_store(p, ((uint64_t)seq << 32) | (b & 0xFFFFFFFFull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(p + apart, ((uint64_t)seq << 32) | (b >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    res_store(p, res_tagged(__float_as_uint(v0), tag), res_tagged(__float_as_uint(v1), tag));
+}
+__device__ __forceinline__ void res_publish(uint64_t* p, double v, uint32_t tag)
+{
+    res_store(p, (uint32_t)__double2loint(v), res_tagged((uint32_t)__double2hiint(v), tag));
+}
+// a scalar of any size: two words of half of it and the exchange's sequence number
+__device__ __forceinline__ void res_publish_scalar(uint64_t* p, double v, uint32_t seq)
+{
+    res_store(p, (uint32_t)__double2loint(v), seq);
+    res_store(p + 1, (uint32_t)__double2hiint(v), seq);
 }
 
-__device__ __forceinline__ void res_publish_f64(uint64_t* p, double v, uint32_t seq)
+// How the 512 threads read a slot of N sums of P partners: 16 bytes a lane and partner, L neighbouring lanes on the same
+// 16 bytes of different partners, H partners a lane.
+template <typename TX, int N, int P>
+struct ResRead {
+    static constexpr int Q = 16 / (int)sizeof(TX), U = N / Q;  // sums in 16 bytes, 16-byte pieces of a slot
+    static constexpr int fit = kResThreads / U;
+    static constexpr int L = P < 2 ? 1 : fit < P ? fit : P, H = P / L;
+    static constexpr int waves = U * L / 64;  // waves that read sums
+    static_assert(P < 2 || (L >= 4 && L <= 16 && U * L % 64 == 0 && U * L <= kResThreads), "lanes of a piece");
+};
+
+typedef unsigned res_u4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ res_u4 res_load16(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff)
 {
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    __hip_atomic_store(p, ((uint64_t)seq << 32) | (b & 0xFFFFFFFFull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(p + 1, ((uint64_t)seq << 32) | (b >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff, (int)soff, (int)0x80000010);  // volatile, device scope
 }
 
-// H members' values of one element (one half of a group of 2H) plus NX / 2 piggybacked doubles of one
-// member (NX = 0, 2 or 4 more words; only what the phase at hand uses is published and read: every word is a
-// trip through the fabric), all loads in flight together.  If any word of the wave is still from an earlier
-// exchange, all are read again (re-reads are rare once the first read is delayed a little).  `base` is the same
-// for the whole workgroup and `off` (bytes) the same in every exchange: the loads take a scalar base and a 32-bit
-// lane offset, so that no 64-bit lane address is worked out between the wait and the first load.
+// H partners' 16 bytes (none where `sums` is not set, the same for a wave), plus NX / 2 scalars of one partner (NX = 0, 2 or 4
+// words; only what the phase at hand uses is published and read: every word is a trip through the fabric), all loads in flight together.
+// If any word of the wave is still from an earlier exchange, all are read again (re-reads are rare once the first read is
+// delayed a little).  soff is the same for the whole workgroup and voff in every exchange: nothing is worked out
+// between the wait and the first load.  s: the sums over the partners.
 template <typename TX, int H, int NX>
-__device__ __forceinline__ bool res_gather(const char* base, uint32_t off, uint32_t stride, uint32_t apart, const char* xbase, uint32_t xoff,
-                                           uint32_t seq, int max_spin, double& sum, double& x0, double& x1, int& spin)
+__device__ __forceinline__ bool res_gather(__amdgpu_buffer_rsrc_t rs, uint32_t soff, uint32_t voff, uint32_t stride, bool sums, uint32_t xoff,
+                                           uint32_t seq, int max_spin, double (&s)[16 / sizeof(TX)], double& x0, double& x1, int& spin)
 {
-    static_assert(NX == 0 || NX == 2 || NX == 4, "none, one or two piggybacked doubles");
-    constexpr int W = kResWords<TX>, N = W * H;
-    uint64_t w[N + 4];
-    w[N + 2] = 0;
-    w[N + 3] = 0;
+    static_assert(NX == 0 || NX == 2 || NX == 4, "none, one or two scalars");
+    const uint32_t tag = res_tag(seq);
+    res_u4 w[H], x[2];
+#pragma unroll
+    for (int q = 0; q < H; ++q) w[q] = res_u4{tag, tag, tag, tag};
     for (;;) {
+        if (sums) {
 #pragma unroll
-        for (int q = 0; q < H; ++q)
+            for (int q = 0; q < H; ++q) w[q] = res_load16(rs, voff, soff + (uint32_t)q * stride);
+        }
 #pragma unroll
-            for (int h = 0; h < W; ++h)
-                w[W * q + h] = __hip_atomic_load((const uint64_t*)(base + (size_t)q * stride + (size_t)h * apart + off), __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-        for (int q = 0; q < NX; ++q)
-            w[N + q] = __hip_atomic_load((const uint64_t*)(xbase + q * 8 + xoff), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int q = 0; q < NX / 2; ++q) x[q] = res_load16(rs, xoff + 16u * (uint32_t)q, soff);
         uint32_t stale = 0;
 #pragma unroll
-        for (int q = 0; q < N + NX; ++q) stale |= (uint32_t)(w[q] >> 32) ^ seq;
+        for (int q = 0; q < H; ++q) {
+            stale |= (w[q].y ^ tag) | (w[q].w ^ tag);
+            if constexpr (sizeof(TX) == 4) stale |= (w[q].x ^ tag) | (w[q].z ^ tag);
+        }
+        stale &= kResTagBit;
+#pragma unroll
+        for (int q = 0; q < NX / 2; ++q) stale |= (x[q].y ^ seq) | (x[q].w ^ seq);
         if (__ballot(stale != 0) == 0) break;
         if (++spin > max_spin) return false;
         __builtin_amdgcn_s_sleep(1);
     }
-    double s = 0.0;
 #pragma unroll
     for (int q = 0; q < H; ++q) {
-        if constexpr (W == 1) s += (double)__uint_as_float((uint32_t)w[q]);
-        else s += __longlong_as_double((long long)((w[2 * q + 1] << 32) | (w[2 * q] & 0xFFFFFFFFull)));
+        double v[16 / sizeof(TX)];
+        if constexpr (sizeof(TX) == 4) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = (double)__uint_as_float(w[q][e] & ~kResTagBit);
+        } else {
+            v[0] = __hiloint2double((int)(w[q].y & ~kResTagBit), (int)w[q].x);
+            v[1] = __hiloint2double((int)(w[q].w & ~kResTagBit), (int)w[q].z);
+        }
+#pragma unroll
+        for (int e = 0; e < (int)(16 / sizeof(TX)); ++e) s[e] = q == 0 ? v[e] : s[e] + v[e];
     }
-    sum = s;
-    if constexpr (NX >= 2) x0 = __longlong_as_double((long long)((w[N + 1] << 32) | (w[N] & 0xFFFFFFFFull)));
-    if constexpr (NX == 4) x1 = __longlong_as_double((long long)((w[N + 3] << 32) | (w[N + 2] & 0xFFFFFFFFull)));
+    if constexpr (NX >= 2) x0 = __hiloint2double((int)x[0].z, (int)x[0].x);
+    if constexpr (NX == 4) x1 = __hiloint2double((int)x[1].z, (int)x[1].x);
     return true;
+}
+
+// Sum over the L lanes of a 16-byte piece.  At distances 1 and 2 a lane keeps only the sums whose low index bits are its own:
+// lane h ends with sum h mod Q, the same bits in every lane that holds it.
+template <int L, int Q>
+__device__ __forceinline__ double res_join(const double (&s)[Q], int lane)
+{
+    const bool odd1 = (lane & 1) != 0, odd2 = (lane & 2) != 0;
+    double a = (odd1 ? s[1] : s[0]) + dpp_f64_res<0xB1, 0>(odd1 ? s[0] : s[1]);  // lane ^ 1
+    if constexpr (Q == 4) {
+        const double b = (odd1 ? s[3] : s[2]) + dpp_f64_res<0xB1, 0>(odd1 ? s[2] : s[3]);
+        a = (odd2 ? b : a) + dpp_f64_res<0x4E, 0>(odd2 ? a : b);  // lane ^ 2
+    } else {
+        a += dpp_f64_res<0x4E, 0>(a);
+    }
+    if constexpr (L >= 8) a += dpp_f64_res<0x141, 0x1B>(a);    // lane ^ 4
+    if constexpr (L >= 16) a += dpp_f64_res<0x140, 0x141>(a);  // lane ^ 8
+    return a;
 }
 
 template <int CTRL>
@@ -238,15 +285,6 @@ struct ResVec<double> {
     }
     static __device__ __forceinline__ void put(double* p, const double* x) { *(double2*)p = make_double2(x[0], x[1]); }
 };
-
-// the value of the neighbouring lane (lane ^ 1), for doubles
-__device__ __forceinline__ double dpp_swap1_f64(double v)
-{
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xFFFFFFFFll), 0xB1, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0xB1, 0xF, 0xF, true);
-    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
 
 // Sum over the four 16-lane rows of a wave for two registers at once: the row-swap instructions of gfx950 exchange
 // the odd rows (the upper half of the wave) of one register with the even rows (the lower half) of the other, after
@@ -417,17 +455,19 @@ __device__ __forceinline__ void res_subtract_terms(const ResidentArgs& a, int64_
 template <typename TE, typename TA, typename TX, int TR, int TC, int P, bool PAD, bool LSQ = false>
 __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
 {
-    constexpr int W = kResWords<TX>, VE = ResVec<TE>::N;
+    constexpr int VE = ResVec<TE>::N;
     TE* const Rm = (TE*)a.R;
     constexpr bool SOLO = P == 1;         // one workgroup holds the matrix: its sums are the sums, nothing is exchanged
-    constexpr int H = SOLO ? 1 : P / 2;   // members per half of an exchange group
     static_assert(SOLO || P == 4 || P == 8 || P == 16, "grid side");
     constexpr bool kEarly = SOLO && TR * TC >= 32;  // (with less to save, the branch costs more: 61x67 1.44 us per alternation, with it 1.53)
     using TI = std::conditional_t<SOLO && sizeof(TX) == 4, float, TA>;  // of a thread's own sums
     constexpr int BM = 32 * TR, BN = 16 * TC;  // block of this workgroup
     static_assert(TR >= 2 && TR <= 16 && (TR % 2) == 0, "rows per thread");
     static_assert(TC >= 4 && TC <= 32 && (TC % 4) == 0, "columns per thread");
-    static_assert(W * BM + 4 <= kResSlotWords && W * BN + 4 <= kResSlotWords, "slot size");
+    using RowRead = ResRead<TX, BM, P>;
+    using ColRead = ResRead<TX, BN, P>;
+    constexpr int WM = BM * (int)sizeof(TX) / 8, WN = BN * (int)sizeof(TX) / 8;  // words of sums in a slot; the scalars follow
+    static_assert(WM + 4 <= kResSlotWords && WN + 4 <= kResSlotWords, "slot size");
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int tr = tid >> 4, tc = tid & 15;  // 32 x 16 threads, each TR x TC elements
     const int pr = blockIdx.x / P, pc = blockIdx.x % P;
@@ -499,11 +539,11 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
     const double total = (double)a.m * (double)a.n;
     bool need_t0 = true;
     int spin = 0, spins = 0;
-    // lane offsets of the two gathers (bytes; the same in every exchange): thread (element, half) reads the
-    // element's words of one half of the partners; threads past the block read a valid element and drop it
-    const int half = tid & 1;
-    const uint32_t off_u = (uint32_t)(half * H * kResSlotWords + ((tid >> 1) < BM ? (tid >> 1) : BM - 1)) * 8u;
-    const uint32_t off_v = (uint32_t)(half * H * P * kResSlotWords + ((tid >> 1) < BN ? (tid >> 1) : BN - 1)) * 8u;
+    // the exchange slots as a buffer, and a thread's offsets in the two gathers (bytes; the same in every exchange)
+    const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(a.xbuf, 0, SOLO ? 0 : (int)kResXbufBytes, 0x00027000);
+    const uint32_t off_u = (uint32_t)(tid % RowRead::L * RowRead::H * kResSlotWords) * 8u + (uint32_t)(tid / RowRead::L) * 16u;
+    const uint32_t off_v = (uint32_t)(tid % ColRead::L * ColRead::H * P * kResSlotWords) * 8u + (uint32_t)(tid / ColRead::L) * 16u;
+    const int wave = __builtin_amdgcn_readfirstlane(wv);
 
     for (;;) {
         if (!LSQ && k >= a.w_target && norm_stage == 0) break;
@@ -584,35 +624,41 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
                 ++seq_u;
                 {
                     uint64_t* mine = res_slot(a, 0, seq_u, wg);
-                    if (tc < TR) res_publish(mine + tr * TR + tc, BM, (TX)prow, seq_u);
+                    const TX pv = res_scaled((TX)prow, -a.xexp);
+                    if constexpr (sizeof(TX) == 4) {
+                        const float next = dpp_f32<0xB1>(pv);  // lane ^ 1: the row after
+                        if (tc < TR && !(lane & 1)) res_publish(mine + (tr * TR + tc) / 2, pv, next, res_tag(seq_u));
+                    } else {
+                        if (tc < TR) res_publish(mine + tr * TR + tc, pv, res_tag(seq_u));
+                    }
                     if (tid == 0) {
-                        res_publish_f64(mine + W * BM, cpart, seq_u);
-                        if (norm_stage == 1) res_publish_f64(mine + W * BM + 2, fsq_block, seq_u);  // (only the exchange after an update)
+                        res_publish_scalar(mine + WM, cpart, seq_u);
+                        if (norm_stage == 1) res_publish_scalar(mine + WM + 2, fsq_block, seq_u);  // (only the exchange after an update)
                     }
                 }
                 for (int d = 0; d < a.poll_delay; ++d) __builtin_amdgcn_s_sleep(1);
                 {
-                    // gather: thread (row, half) adds eight members in order, the two halves are combined low
-                    // first.  The last wave also fetches the piggybacked scalars (lane mod P = member), in the
-                    // same batch of loads.
-                    const int row = tid >> 1;
-                    const char* base = res_slot_bytes(a, 0, seq_u, pr * P);
-                    double hs = 0.0, x0 = 0.0, x1 = 0.0;
-                    bool ok;
-                    if (wv == NWV - 1) {
-                        const uint32_t xoff = (uint32_t)((lane & (P - 1)) * kResSlotWords + W * BM) * 8u;
-                        if (norm_stage == 1) ok = res_gather<TX, H, 4>(base, off_u, kResSlotWords * 8, BM * 8, base, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
-                        else ok = res_gather<TX, H, 2>(base, off_u, kResSlotWords * 8, BM * 8, base, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
+                    // gather; the last wave also fetches the scalars (lane mod P = partner), in the same batch of loads
+                    constexpr int L = RowRead::L, H = RowRead::H, Q = RowRead::Q;
+                    const uint32_t soff = res_slot_off(0, seq_u, pr * P) * 8u;
+                    double hs[Q], x0 = 0.0, x1 = 0.0;
+                    bool ok = true;
+                    if (wave == NWV - 1) {
+                        constexpr bool sums = RowRead::waves == NWV;
+                        const uint32_t xoff = (uint32_t)((lane & (P - 1)) * kResSlotWords + WM) * 8u;
+                        if (norm_stage == 1) ok = res_gather<TX, H, 4>(xrs, soff, off_u, kResSlotWords * 8, sums, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
+                        else ok = res_gather<TX, H, 2>(xrs, soff, off_u, kResSlotWords * 8, sums, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
                         if (lane < P) {
                             lds_x[0][lane] = x0;
                             if (norm_stage == 1) lds_x[1][lane] = x1;
                         }
-                    } else {
-                        ok = res_gather<TX, H, 0>(base, off_u, kResSlotWords * 8, BM * 8, base, 0, seq_u, a.max_spin, hs, x0, x1, spin);
+                    } else if (wave < RowRead::waves) {
+                        ok = res_gather<TX, H, 0>(xrs, soff, off_u, kResSlotWords * 8, true, 0, seq_u, a.max_spin, hs, x0, x1, spin);
                     }
-                    const double other = dpp_swap1_f64(hs);
-                    const double u = half ? other + hs : hs + other;
-                    if (half == 0 && row < BM) lds_s[cur ^ 1][row] = (u < 0.0) ? kNegByte : kPosByte;
+                    if (wave < RowRead::waves) {
+                        const double u = res_join<L, Q>(hs, lane);
+                        if (tid % L < Q) lds_s[cur ^ 1][tid / L * Q + tid % L] = (u < 0.0) ? kNegByte : kPosByte;
+                    }
                     if (!ok) lds_fail = 1;
                 }
             }
@@ -761,40 +807,51 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
             ++seq_v;
             {
                 uint64_t* mine = res_slot(a, 1, seq_v, wg);
-                if (tid < BN) {
+                constexpr int C = 8 / (int)sizeof(TX);  // columns of a word
+                if (tid < BN / C) {
                     // (all loads in flight together, then the adds in wave order: the empty asm keeps the compiler from
                     // loading two, waiting, adding two)
-                    TA w[NWV];
+                    TA w[C][NWV];
 #pragma unroll
-                    for (int q = 0; q < NWV; ++q) w[q] = lds_q[q][tid];
+                    for (int q = 0; q < NWV; ++q)
+#pragma unroll
+                        for (int e = 0; e < C; ++e) w[e][q] = lds_q[q][tid * C + e];
                     static_assert(NWV == 8, "operands of the asm");
-                    asm volatile("" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(w[4]), "+v"(w[5]), "+v"(w[6]), "+v"(w[7]));
-                    TA s = 0;
+                    TX s[C];
 #pragma unroll
-                    for (int q = 0; q < NWV; ++q) s += w[q];
-                    res_publish(mine + tid, BN, (TX)s, seq_v);
+                    for (int e = 0; e < C; ++e) asm volatile("" : "+v"(w[e][0]), "+v"(w[e][1]), "+v"(w[e][2]), "+v"(w[e][3]), "+v"(w[e][4]), "+v"(w[e][5]), "+v"(w[e][6]), "+v"(w[e][7]));
+#pragma unroll
+                    for (int e = 0; e < C; ++e) {
+                        TA t = 0;
+#pragma unroll
+                        for (int q = 0; q < NWV; ++q) t += w[e][q];
+                        s[e] = res_scaled((TX)t, -a.xexp);
+                    }
+                    if constexpr (C == 2) res_publish(mine + tid, s[0], s[1], res_tag(seq_v));
+                    else res_publish(mine + tid, s[0], res_tag(seq_v));
                 }
-                if (norm_stage == 2 && tid == kResThreads - 1) res_publish_f64(mine + W * BN, frow, seq_v);
+                if (norm_stage == 2 && tid == kResThreads - 1) res_publish_scalar(mine + WN, frow, seq_v);
             }
             for (int d = 0; d < a.poll_delay_v; ++d) __builtin_amdgcn_s_sleep(1);
             {
-                const int col = tid >> 1;
-                const char* base = res_slot_bytes(a, 1, seq_v, pc);
-                double hs = 0.0, x0 = 0.0, x1 = 0.0;
-                bool ok;
-                if (norm_stage == 2 && wv == NWV - 1) {
+                constexpr int L = ColRead::L, H = ColRead::H, Q = ColRead::Q;
+                const uint32_t soff = res_slot_off(1, seq_v, pc) * 8u;
+                double hs[Q], x0 = 0.0, x1 = 0.0;
+                bool ok = true;
+                if (norm_stage == 2 && wave == NWV - 1) {
                     // the block-row sums of squares travel on this exchange once per term
-                    ok = res_gather<TX, H, 2>(base, off_v, P * kResSlotWords * 8, BN * 8, base,
-                                              (uint32_t)((lane & (P - 1)) * P * kResSlotWords + W * BN) * 8u, seq_v, a.max_spin, hs, x0, x1, spin);
+                    const uint32_t xoff = (uint32_t)((lane & (P - 1)) * P * kResSlotWords + WN) * 8u;
+                    ok = res_gather<TX, H, 2>(xrs, soff, off_v, P * kResSlotWords * 8, ColRead::waves == NWV, xoff, seq_v, a.max_spin, hs, x0, x1, spin);
                     if (lane < P) lds_x[1][lane] = x0;
-                } else {
-                    ok = res_gather<TX, H, 0>(base, off_v, P * kResSlotWords * 8, BN * 8, base, 0, seq_v, a.max_spin, hs, x0, x1, spin);
+                } else if (wave < ColRead::waves) {
+                    ok = res_gather<TX, H, 0>(xrs, soff, off_v, P * kResSlotWords * 8, true, 0, seq_v, a.max_spin, hs, x0, x1, spin);
                 }
-                const double other = dpp_swap1_f64(hs);
-                const double v = half ? other + hs : hs + other;
-                if (half == 0 && col < BN) {
-                    lds_t[col] = (v < 0.0) ? kNegByte : kPosByte;
-                    absv = fabs(v);
+                if (wave < ColRead::waves) {
+                    const double v = res_join<L, Q>(hs, lane);
+                    if (tid % L < Q) {
+                        lds_t[tid / L * Q + tid % L] = (v < 0.0) ? kNegByte : kPosByte;
+                        absv = fabs(v);
+                    }
                 }
                 if (!ok) lds_fail = 1;
             }
@@ -808,6 +865,7 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
         }
         // this column block's share of c travels on the next row exchange (published by thread 0)
         if (SOLO || wv == 0) cpart = group_sum_res<8>(lds_red[lane & (NWV - 1)]);
+        if constexpr (!SOLO) cpart = res_scaled(cpart, a.xexp);
         if constexpr (!SOLO) {
             if (norm_stage == 2) {
                 const double ft = group_sum_res<P>(lds_x[1][lane & (P - 1)]);

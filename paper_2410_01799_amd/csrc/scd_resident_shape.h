@@ -64,14 +64,15 @@ constexpr bool resident_shape(scd_dtype dt, int64_t m, int64_t n, int* p, int* t
 // f32 words where one rounding a workgroup is no more than those f32 sums cost, that is from two of them on each side
 // (emulated, rms error of the row and column sums against f64, launch stream / here: 257x255 4.5e-8, 3.0e-8 / 2.6e-8,
 // 2.7e-8; 1501x999 7.3e-8, 5.1e-8 / 2.4e-8, 2.5e-8; 4095x4093 1.5e-7, 7.8e-8 / 2.6e-8, 2.5e-8; with f32 sums inside the
-// workgroup too the column sums of 1501x999 are off by 7.9e-8).  Smaller ones exchange f64, and those whose sums of up
-// to 256 entries a workgroup could pass the largest f32: they are at most 16 ||R||_F.
+// workgroup too the column sums of 1501x999 are off by 7.9e-8).  Smaller ones exchange f64, and so do those of any row
+// length whose sums of up to 256 entries a workgroup could pass the largest f32: they are at most 16 ||R||_F.
 // plain: the input's type (one workgroup: see the kernel), wide: f64 throughout.
 enum class ResSums { plain, wide_inside, wide };
 constexpr ResSums resident_sums(scd_dtype dt, int64_t m, int64_t n, double fro)
 {
-    if (dt == SCD_F32 && n % 4 == 0) return ResSums::plain;
-    return dt == SCD_F32 && m > 256 && n > 128 && fro < 1e36 ? ResSums::wide_inside : ResSums::wide;
+    if (dt == SCD_F64 || fro >= 1e36) return ResSums::wide;
+    if (n % 4 == 0) return ResSums::plain;
+    return m > 256 && n > 128 ? ResSums::wide_inside : ResSums::wide;
 }
 
 // The forms of the kernel that some matrix takes; no others are built.  The rules above change only where a side passes what a
@@ -88,7 +89,9 @@ struct ResForms {
 };
 constexpr int resident_form(scd_dtype dt, int64_t m, int64_t n, double fro, int p, int tr, int tc)
 {
-    return m == (int64_t)p * 32 * tr && n == (int64_t)p * 16 * tc ? kResExact : (int)resident_sums(dt, m, n, fro);
+    if (p == 1) fro = 0.0;  // (nothing is exchanged)
+    const ResSums sums = resident_sums(dt, m, n, fro);
+    return m == (int64_t)p * 32 * tr && n == (int64_t)p * 16 * tc && (dt == SCD_F64 || sums == ResSums::plain) ? kResExact : (int)sums;
 }
 constexpr ResForms res_forms()
 {
