@@ -127,6 +127,21 @@ __device__ __forceinline__ double sp_sum_xor32(double a)
            __longlong_as_double((long long)(((unsigned long long)rh[1] << 32) | rl[1]));
 }
 
+// Half-width sums of two registers: even 16-lane rows (the lower 32 lanes) end with a's sum over distance 16 (32), the others
+// with b's.
+__device__ __forceinline__ double sp_half16(double a, double b)
+{
+    const auto l = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+__device__ __forceinline__ double sp_half32(double a, double b)
+{
+    const auto l = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+
 // Sum of an int over the 64 lanes (every lane gets it) and inclusive prefix sum across the lanes, both
 // without LDS traffic.  The scan is the classic one of this architecture: shifts by 1, 2, 4, 8 within each
 // row of 16 lanes (lanes without a source add zero), then lane 15 of rows 0 and 2 is added to rows 1 and 3,
@@ -746,7 +761,6 @@ struct SpPending {
     double* ej;          // [32] coefficient times inner product, per half step
     double* effu;        // [kSpThreads] u of the true remainder on this workgroup's rows
     double* effv;        // [kSpThreads] v on its columns
-    uint32_t* rowmask;   // [4]
     uint32_t* T0;        // [kSpAhead][pt_stride] random starts t_0 of the next terms
     double* U0;          // [kSpAhead][kSpThreads] their first products R' t_0 on this workgroup's rows
     int ps_stride, pt_stride;
@@ -800,10 +814,14 @@ __device__ __forceinline__ void sp_effective(const double* acc, int len, uint32_
 // left are summed, and the signed row sums with each of the nvec <= NV bit vectors sums + j * sstride are
 // formed: out[j * kSpThreads + row].  Columns are taken in tiles of one 16-byte chunk per thread, so that a
 // thread keeps its columns' pending signs in registers while it streams down the rows.
+// On few workgroups a batch of rows was a chain of its own: masks, barrier, loads, sums over LDS, barrier.  Now the masks are formed
+// once, the rows of the next batch are on their way, the sums stay in registers and alternate between two halves of
+// red: one barrier a batch.  Us per term for both copies, before / here: f32 4096x4096 on 32 workgroups 75 / 57, 14336x4096 on 64 136 / 99,
+// alone 38 / 28; f64 8192x512 on 32 55 / 39 (41.0 / 32.1 us per alternation).
 template <typename TE, int NV>
 __device__ void sp_flush_rows(TE* __restrict__ Y, int64_t ld, int64_t row0, int nrows, const uint32_t* Prow, int prs,
                               const uint32_t* Pcol, int pcs, int np, const double* coef, const uint32_t* sums, int sstride,
-                              int nvec, double* out, double& fsq_out, double* red, uint32_t* rowmask)
+                              int nvec, double* out, double& fsq_out, double* red)
 {
     constexpr int VE = SpVec<TE>::N;
     constexpr int RB = 4;
@@ -811,8 +829,16 @@ __device__ void sp_flush_rows(TE* __restrict__ Y, int64_t ld, int64_t row0, int 
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
     const int64_t nch = ld / VE;
     double fsq = 0.0;
-    if (tid < nrows)
+    int half = 0;  // the sums of a batch go to one half of red while those of the last are read from the other
+    uint32_t* rowmask = (uint32_t*)(red + kSpThreads);  // pending signs of the rows
+    if (tid < nrows) {
         for (int j = 0; j < nvec; ++j) out[j * kSpThreads + tid] = 0.0;
+        const int64_t row = row0 + tid;
+        uint32_t mk = 0u;
+        for (int j = 0; j < np; ++j) mk |= ((Prow[j * prs + (int)(row >> 5)] >> (row & 31)) & 1u) << j;
+        rowmask[tid] = mk;
+    }
+    __syncthreads();
     for (int64_t c0 = 0; c0 < nch; c0 += kSpThreads) {
         const int64_t c = c0 + tid;
         const bool active = c < nch;
@@ -829,27 +855,22 @@ __device__ void sp_flush_rows(TE* __restrict__ Y, int64_t ld, int64_t row0, int 
 #pragma unroll
         for (int j = 0; j < NV; ++j)
             if (j < nvec) bsum |= ((sp_bits4(sums + j * sstride, col & ~3ll) >> (col & 3)) & 0xFu) << (4 * j);
+        // the rows of the next batch are on their way while this one is worked on
+        V* const colp = (V*)(Y + row0 * ld) + (active ? c : 0);
+        V next[RB];
+#pragma unroll
+        for (int r = 0; r < RB; ++r) next[r] = colp[(int64_t)(r < nrows ? r : nrows - 1) * nch];
         for (int rb = 0; rb < nrows; rb += RB) {
-            __syncthreads();  // rowmask and red are free again
-            if (tid < RB) {
-                const int rr = rb + tid < nrows ? rb + tid : nrows - 1;
-                const int64_t row = row0 + rr;
-                uint32_t mk = 0u;
-                for (int j = 0; j < np; ++j) mk |= ((Prow[j * prs + (int)(row >> 5)] >> (row & 31)) & 1u) << j;
-                rowmask[tid] = mk;
-            }
-            __syncthreads();
             double ps[RB][NV];
             V v[RB];
-            V* rowp[RB];
 #pragma unroll
             for (int r = 0; r < RB; ++r) {
-                const int rr = rb + r < nrows ? rb + r : nrows - 1;
-                rowp[r] = (V*)(Y + (row0 + rr) * ld);
 #pragma unroll
                 for (int j = 0; j < NV; ++j) ps[r][j] = 0.0;
-                v[r] = rowp[r][active ? c : 0];
+                v[r] = next[r];
             }
+#pragma unroll
+            for (int r = 0; r < RB; ++r) next[r] = colp[(int64_t)(rb + RB + r < nrows ? rb + RB + r : nrows - 1) * nch];
 #pragma unroll
             for (int r = 0; r < RB; ++r) {
                 if (rb + r >= nrows || !active) continue;
@@ -862,7 +883,7 @@ __device__ void sp_flush_rows(TE* __restrict__ Y, int64_t ld, int64_t row0, int 
                 if (np > 0) {
                     uint32_t z[VE];
 #pragma unroll
-                    for (int e = 0; e < VE; ++e) z[e] = rowmask[r] ^ cm[e];
+                    for (int e = 0; e < VE; ++e) z[e] = rowmask[rb + r] ^ cm[e];
                     for (int j = 0; j < np; ++j) {
                         const TE ck = (TE)coef[j];
 #pragma unroll
@@ -871,7 +892,7 @@ __device__ void sp_flush_rows(TE* __restrict__ Y, int64_t ld, int64_t row0, int 
                     V o;
                     if constexpr (VE == 4) o = V{x[0], x[1], x[2], x[3]};
                     else o = V{x[0], x[1]};
-                    rowp[r][c] = o;
+                    colp[(int64_t)(rb + r) * nch] = o;
                 }
                 double xd[VE];
 #pragma unroll
@@ -896,17 +917,25 @@ __device__ void sp_flush_rows(TE* __restrict__ Y, int64_t ld, int64_t row0, int 
 #pragma unroll
                     for (int j = 0; j < NV; ++j) vv[r * NV + j] = ps[r][j];
 #pragma unroll
-                for (int h = 16; h >= 1; h >>= 1) {
-                    const bool upper = (lane & (2 * h)) != 0;  // distance 2 h: 32, 16, 8, 4, 2
+                for (int i = 0; i < 16; ++i) vv[i] = sp_half32(vv[i], vv[i + 16]);
 #pragma unroll
-                    for (int i = 0; i < h; ++i) {
-                        const double send = upper ? vv[i] : vv[i + h];
-                        const double keep = upper ? vv[i + h] : vv[i];
-                        vv[i] = keep + __shfl_xor(send, 2 * h, kWave);
-                    }
+                for (int i = 0; i < 8; ++i) vv[i] = sp_half16(vv[i], vv[i + 8]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const bool upper = (lane & 8) != 0;
+                    vv[i] = (upper ? vv[i + 4] : vv[i]) + sp_lane_xor_f64<8>(upper ? vv[i] : vv[i + 4]);
                 }
-                vv[0] += __shfl_xor(vv[0], 1, kWave);
-                if ((lane & 1) == 0) red[wv * 32 + (lane >> 1)] = vv[0];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const bool upper = (lane & 4) != 0;
+                    vv[i] = (upper ? vv[i + 2] : vv[i]) + sp_lane_xor_f64<4>(upper ? vv[i] : vv[i + 2]);
+                }
+                {
+                    const bool upper = (lane & 2) != 0;
+                    vv[0] = (upper ? vv[1] : vv[0]) + sp_lane_xor_f64<2>(upper ? vv[0] : vv[1]);
+                }
+                vv[0] += sp_lane_xor_f64<1>(vv[0]);
+                if ((lane & 1) == 0) red[half + wv * 32 + (lane >> 1)] = vv[0];
             } else {
 #pragma unroll
                 for (int r = 0; r < RB; ++r)
@@ -914,18 +943,22 @@ __device__ void sp_flush_rows(TE* __restrict__ Y, int64_t ld, int64_t row0, int 
                     for (int j = 0; j < NV; ++j) {
                         if (j >= nvec) continue;
                         const double t = sp_wave_sum(ps[r][j]);
-                        if (lane == 0) red[(wv * RB + r) * NV + j] = t;
+                        if (lane == 0) red[half + (wv * RB + r) * NV + j] = t;
                     }
             }
             __syncthreads();
             if (tid < RB * NV) {
                 const int r = tid / NV, j = tid % NV;
                 if (rb + r < nrows && j < nvec) {
-                    double t = 0.0;
-                    for (int q = 0; q < kSpWaves; ++q) t += red[(q * RB + r) * NV + j];
+                    double q[kSpWaves], t = 0.0;
+#pragma unroll
+                    for (int i = 0; i < kSpWaves; ++i) q[i] = red[half + (i * RB + r) * NV + j];
+#pragma unroll
+                    for (int i = 0; i < kSpWaves; ++i) t += q[i];
                     out[j * kSpThreads + rb + r] += t;
                 }
             }
+            half ^= kSpThreads / 2;
         }
     }
     fsq = sp_wave_sum(fsq);
@@ -964,7 +997,7 @@ __global__ void __launch_bounds__(kSpThreads) sparse_delay_kernel(SparseArgs a)
         sh.list = (uint16_t*)take((size_t)kSpListCap * 2);
         sh.accu = (double*)take((size_t)kSpThreads * 8);
         sh.accv = (double*)take((size_t)kSpThreads * 8);
-        sh.red = (double*)take((size_t)kSpThreads * 8);
+        sh.red = (double*)take((size_t)kSpThreads * (8 + 4));  // (and the row masks of a flush)
         sh.scal = (uint32_t*)take((size_t)2 * kSpGrid * 2 * 4);
         sh.cred = (double*)take((size_t)kSpWaves * 8);
         sh.scan = (int*)take((size_t)(kSpWaves + 2) * 4);
@@ -974,7 +1007,6 @@ __global__ void __launch_bounds__(kSpThreads) sparse_delay_kernel(SparseArgs a)
         pd.ej = (double*)take(32 * 8);
         pd.effu = (double*)take((size_t)kSpThreads * 8);
         pd.effv = (double*)take((size_t)kSpThreads * 8);
-        pd.rowmask = (uint32_t*)take(16);
         pd.PS = (uint32_t*)take((size_t)width * pd.ps_stride * 4);
         pd.PT = (uint32_t*)take((size_t)width * pd.pt_stride * 4);
         pd.T0 = (uint32_t*)take((size_t)kSpAhead * pd.pt_stride * 4);
@@ -1048,7 +1080,7 @@ __global__ void __launch_bounds__(kSpThreads) sparse_delay_kernel(SparseArgs a)
             __syncthreads();
             if (rlen > 0)
                 sp_flush_rows<TE, kSpAhead>(R, n, i0, rlen, pd.PS, pd.ps_stride, pd.PT, pd.pt_stride, np, pd.coef, pd.T0,
-                                            pd.pt_stride, nvec, pd.U0, fsq, sh.red, pd.rowmask);
+                                            pd.pt_stride, nvec, pd.U0, fsq, sh.red);
             ahead = nvec;
             ahead_made = nvec;
         }
@@ -1079,7 +1111,7 @@ __global__ void __launch_bounds__(kSpThreads) sparse_delay_kernel(SparseArgs a)
         if (flush) {
             if (clen > 0)
                 sp_flush_rows<TE, 1>(RT, m, j0, clen, pd.PT, pd.pt_stride, pd.PS, pd.ps_stride, np, pd.coef, s_oth, 0, 1, sh.accv,
-                                     dummy, sh.red, pd.rowmask);
+                                     dummy, sh.red);
             updates += np;
             np = 0;
             own_u = 0u;
@@ -1202,7 +1234,7 @@ size_t sparse_lds_bytes(int64_t m, int64_t n, int delay_width)
     size_t b = 2 * al(mw * 4 + 8) + 2 * al(nw * 4 + 8) + al((size_t)kSpListCap * 2) + 3 * al((size_t)kSpThreads * 8) +
                al((size_t)2 * kSpGrid * 2 * 4) + al((size_t)kSpWaves * 8) + al((size_t)(kSpWaves + 2) * 4);
     if (delay_width > 0)
-        b += 2 * al(32 * 8) + 2 * al((size_t)kSpThreads * 8) + al(16) + al((size_t)delay_width * (mw + 1) * 4) +
+        b += 2 * al(32 * 8) + 2 * al((size_t)kSpThreads * 8) + al((size_t)kSpThreads * 4) + al((size_t)delay_width * (mw + 1) * 4) +
              al((size_t)delay_width * (nw + 1) * 4) + al((size_t)kSpAhead * (nw + 1) * 4) +
              al((size_t)kSpAhead * kSpThreads * 8);
     return b;
