@@ -109,7 +109,8 @@ struct scd_ctx {
     bool rt_stale = true;           // RT does not mirror R (R was changed by the launch-stream kernels)
     void* RT = nullptr;
     uint64_t* xbuf_sp = nullptr;
-    uint32_t seq_sp = 0;
+    uint32_t seq_sp = 0, seq_late[2] = {0, 0};
+    int slots_sp = 0;               // workgroups that wrote the sparse engine's slots last (0: cleared)
     int rs = 0, cs = 0;
     // persistent streaming engine
     bool pstream = false;
@@ -600,7 +601,16 @@ int run_sparse(scd_ctx* c, int64_t n)
     a.max_iters = c->hs.max_iters;
     a.max_spin = (int32_t)c->opt[SCD_OPT_MAX_SPIN];
     a.poll_delay = (int32_t)c->opt[SCD_OPT_POLL_DELAY];
+    // a member that took no part for a while left words of any age in its slots, and the tag of a share of c has one bit: another
+    // number of workgroups starts the numbering again on cleared slots
+    if (c->slots_sp && c->slots_sp != c->sp_grid) {
+        HIP_TRY(hipMemsetAsync(c->xbuf_sp, 0, sparse_xbuf_bytes(), c->stream));
+        c->seq_sp = c->seq_late[0] = c->seq_late[1] = 0;
+    }
+    c->slots_sp = c->sp_grid;
     a.seq = c->seq_sp;
+    a.seq_late[0] = c->seq_late[0];
+    a.seq_late[1] = c->seq_late[1];
     a.xbuf = c->xbuf_sp;
     a.S = c->out_signs[0];
     a.T = c->out_signs[1];
@@ -650,6 +660,10 @@ int run_sparse(scd_ctx* c, int64_t n)
                 (long long)r.alternations, (long long)(r.flips + r.flips_rows), (long long)r.spins, r.ticks[0] * 0.01, r.ticks[1] * 0.01,
                 r.ticks[2] * 0.01, r.ticks[3] * 0.01, r.ticks[4] * 0.01, r.ticks[5] * 0.01);
     c->seq_sp = r.seq_u;
+    if (a.delay_width > 0) {
+        c->seq_late[0] = r.seq_late[0];
+        c->seq_late[1] = r.seq_late[1];
+    }
     c->flips += r.flips;
     c->flips_rows += r.flips_rows;
     c->hs.k = r.k;
@@ -1089,7 +1103,7 @@ int scd_set_remainder(scd_ctx* c, const void* R_in)
         if (c->xbuf_sp) HIP_TRY(hipMemsetAsync(c->xbuf_sp, 0, sparse_xbuf_bytes(), c->stream));
         if (c->xbuf_p1) HIP_TRY(hipMemsetAsync(c->xbuf_p1, 0, c->xbuf_p1_bytes, c->stream));
         if (c->xbuf_p2) HIP_TRY(hipMemsetAsync(c->xbuf_p2, 0, c->xbuf_p2_bytes, c->stream));
-        c->seq_u = c->seq_v = c->seq_sp = c->seq_ps = 0;
+        c->seq_u = c->seq_v = c->seq_sp = c->seq_ps = c->seq_late[0] = c->seq_late[1] = 0;
     }
     c->broken = false;
     HIP_TRY(hipMemcpyAsync(c->R, R_in, (size_t)c->total * c->esize, hipMemcpyDeviceToDevice, c->stream));

@@ -120,6 +120,7 @@ struct ResidentResult {
     int64_t flips;         // sparse engine: column signs that changed (each costs one column of R)
     int64_t flips_rows;    // sparse engine: row signs that changed (each costs one row of R)
     int64_t ticks[6];      // sparse engine, profile mode: 100 MHz ticks of workgroup 0 per phase
+    uint32_t seq_late[2];  // sparse engine: sequence numbers of the late alternations' exchanges (columns, rows)
 };
 
 // Least squares decomposition of a matrix: position of the loop on the device.
@@ -182,6 +183,7 @@ struct SparseArgs {
     int32_t max_iters, max_spin;
     int32_t poll_delay;
     uint32_t seq;            // exchange sequence numbers already used
+    uint32_t seq_late[2];    // the same of the late alternations' exchanges (columns, rows)
     uint64_t* xbuf;          // sparse_xbuf_bytes()
     uint64_t* S;
     uint64_t* T;

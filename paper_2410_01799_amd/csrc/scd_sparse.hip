@@ -25,6 +25,8 @@
 #include "scd_device.h"
 #include "scd_rng.h"
 
+#include <type_traits>
+
 namespace scd {
 
 namespace {
@@ -48,12 +50,20 @@ constexpr int kSpHalfWords = 3 * 8 * kSpGrid;     // words of one parity: up to 
 // 22.9 with a fixed wait, 23.1 with 16, 26.9 with 80; one context alone 9.53 us with 32, 9.51 with 16 (f64 4096x4096),
 // 14.55 and 14.99 (14336x4096 f32).
 constexpr int kSpWaitShift = 4, kSpWaitUp = 12, kSpWaitDown = 1, kSpWaitMax = 32 << kSpWaitShift;
+// Exchanges of late alternations (sp_late_exchange): kind (columns, rows), parity, then up to kSpLateWords sign words of every
+// member, those of the same number side by side (word k of member g at k * 256 + g), and its share of c.
+constexpr int kSpLateWords = 8;
+constexpr int kSpLateHalf = (kSpLateWords + 1) * kSpGrid;
 constexpr int kSpListCap = 32 * kSpThreads;       // flips handled per compaction round: one 32-bit word per thread
 constexpr size_t kSpMaxLds = 150 * 1024 + 64;     // most dynamic LDS a launch may ask for
 // Words a thread may have to gather: grid * (ceil(slice / 32) + 2) over the supported pairs, where
 // grid * slice <= 65536 + 8 * grid: at most 67584 / 32 + 256 + 512 = 2880 words for the 512 threads
 // (sparse_supported checks it).
 constexpr int kSpMaxItems = 6;
+
+// What follows from the thread's number is worked out where it is used: the compiler would do it once at the start of the launch,
+// for every place that a function is inlined, and keep it all in registers, most of which then go through scratch in each alternation.
+#define SP_FRESH(tid) asm volatile("" : "+v"(tid))
 
 // The value of lane (l ^ D) for D = 1, 2, 4, 8 by the data-parallel lane modes (vector-unit latency; a
 // ds_bpermute would cost an LDS round trip per step of a dependent chain).
@@ -431,7 +441,9 @@ __device__ __forceinline__ int sp_adapt(int wait, bool late)
 __device__ bool sp_exchange(const SparseArgs& a, uint32_t seq, const double* acc, int len, int slice, int64_t total_bits,
                             double sc0, bool has_scalar, uint32_t* dest, SpShared& sh, int& spins, bool fence, int wait, bool& late)
 {
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    int tid = threadIdx.x;
+    SP_FRESH(tid);
+    const int lane = tid & (kWave - 1), wv = tid / kWave;
     const int g = blockIdx.x;
     if (fence) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
@@ -826,7 +838,9 @@ __device__ void sp_flush_rows(TE* __restrict__ Y, int64_t ld, int64_t row0, int 
     constexpr int VE = SpVec<TE>::N;
     constexpr int RB = 4;
     typedef typename SpVec<TE>::type V;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    int tid = threadIdx.x;
+    SP_FRESH(tid);
+    const int lane = tid & (kWave - 1), wv = tid / kWave;
     const int64_t nch = ld / VE;
     double fsq = 0.0;
     int half = 0;  // the sums of a batch go to one half of red while those of the last are read from the other
@@ -971,7 +985,477 @@ __device__ void sp_flush_rows(TE* __restrict__ Y, int64_t ld, int64_t row0, int 
     __syncthreads();
 }
 
+// ---------------------------------------------------------------------------------------------------------------------
+// Late alternations.  After the first few alternations of a term some ten to a hundred signs change per half step, and what a half
+// step costs is not its work but the barriers, LDS trips and predicates that keep eight waves in step.  From then on wave 0
+// goes on alone: what it needs is in its registers (the members' sign words, the slices of u and v, the inner products with
+// the pending terms, which change by the flips) or in LDS that nobody else touches; the exchanges are words that one wave reads, and
+// an alternation of few flips has no barrier at all.  Where the flipped entries are more than one batch of loads for a wave, the
+// others, which wait at a barrier, add them up.  It ends when the term is complete or the flips become many.
+// Us of a late alternation, f64 4096x4096 on 256 workgroups: exchange of t with the shares of c 1.45, of s 1.05, products with the
+// flipped columns 1.3, rows 1.3 (0.9 of it a trip to memory), where the eight waves in step took 9.4; per term it costs 4 us to
+// begin.  Us per alternation over all, without / with: 9.4 / 6.0, f32 14336x4096 14.1 / 11.5, 1024x4096 on 32 workgroups 12.2 / 10.6,
+// 4096x4096 on 64 9.9 / 6.7.
+constexpr int kSpLateItems = 8;    // sign words of a side that a lane gathers: at most 512 words of all members
+constexpr int kSpLateEntries = 2;  // entries of a slice that a lane holds: slices of at most 128
+constexpr int kSpLatePending = 8;  // longest list of pending terms
+constexpr int kSpLateDots = 64;    // place of the inner products in sh.scal
+constexpr int kSpLateShare = 64;   // most flipped entries a thread of the other waves adds in a half step (twice as many end it)
+constexpr int kSpLateLoads = 8;    // flipped entries a lane of wave 0 adds by itself
+
+// What the late loop is given and hands back, in LDS (in sh.scal; pointers into LDS as its 32-bit addresses).
+struct SpLateArgs {
+    const void *R, *RT;
+    uint64_t* xbuf;  // exchange slots of the late alternations
+    int64_t i0, j0, m, n;
+    double c_prev, c;
+    uint32_t t_cur, s_cur, owns, list, dots, red, accu, accv, effv, coef, PS, PT;
+    int ps_stride, pt_stride;
+    int grid, rs, cs, rlen, clen, np, cap_t, cap_s, cexp, max_iters, max_spin;
+    int cmd, total;   // to the other waves: 0 the end, 1 / 2 add up the flipped columns / rows of the list
+    uint32_t seq_t, seq_s;
+    int wait_t, wait_s, j;
+    int status;  // 0: many flips, 1: the term is complete, 2: a wait ran out
+    int halves, spins, pad;
+    int64_t flips, flips_rows;
+};
+static_assert(sizeof(SpLateArgs) % 8 == 0 && sizeof(SpLateArgs) <= 4 * kSpLateDots, "place in sh.scal");
+typedef __attribute__((address_space(3))) uint8_t lds_u8;
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+typedef __attribute__((address_space(3))) int32_t lds_i32;
+typedef __attribute__((address_space(3))) double lds_f64;
+typedef __attribute__((address_space(3))) SpLateArgs lds_args;
+template <typename T>
+__device__ __forceinline__ T* lds_at(uint32_t address)
+{
+    return (T*)(uintptr_t)address;
+}
+__device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p; }
+
+template <int NE, int NI>
+struct SpLateSide {  // one side: the columns (t, v) or the rows (s, u)
+    uint32_t addr[NI];  // the lane's words: place in the exchange (bytes); a lane past the last word reads that one and keeps no flip
+    int base[NI];       // ... first index that the word covers | bytes of it that exist << 24
+    uint32_t old[NI];   // ... signs as they are
+    uint32_t keep[NI];  // ... all ones, or zero for a lane past the last word
+    double acc[NE], eff[NE];  // products with R', with the remainder: entry 64 i + lane mod slp
+    uint32_t own[NE];         // signs of the pending terms at these entries
+    int dot;            // inner product of this side's signs with pending term (lane mod 8)
+    int len, slice, slp;
+};
+
+template <int NE, int NI>
+__device__ __forceinline__ void sp_late_init(int lane, SpLateSide<NE, NI>& x, int len, int slice, int64_t nbits, int grid, lds_u32* cur,
+                                             lds_f64* acc, lds_u32* own, int dot)
+{
+    const int words = (slice + 31) >> 5, sbytes = slice >> 3, items = grid * words;
+    const int64_t tbytes = (nbits + 7) >> 3;
+    lds_u8* bytes = (lds_u8*)cur;
+    x.len = len;
+    x.slice = slice;
+    x.slp = 16;
+    while (x.slp < len && x.slp < kWave) x.slp <<= 1;
+    const float rgrid = 1.0f / (float)grid;
+#pragma unroll
+    for (int it = 0; it < NI; ++it) {
+        const int at = lane + it * kWave, idx = at < items ? at : items - 1;
+        const int k = (int)(((float)idx + 0.5f) * rgrid), mem = idx - k * grid;  // (exact, see sp_exchange)
+        const int64_t b0 = (int64_t)mem * sbytes + 4 * k;
+        int nb = sbytes - 4 * k < 4 ? sbytes - 4 * k : 4;
+        if (tbytes - b0 < nb) nb = tbytes > b0 ? (int)(tbytes - b0) : 0;
+        x.addr[it] = (uint32_t)(k * kSpGrid + mem) * 8u;
+        x.base[it] = nb > 0 ? (int)(b0 * 8) | (nb << 24) : 0;
+        x.keep[it] = at < items ? ~0u : 0u;
+        uint32_t v = 0u;
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+            if (b < nb) v |= (uint32_t)bytes[b0 + b] << (8 * b);
+        x.old[it] = v;
+    }
+#pragma unroll
+    for (int i = 0; i < NE; ++i) {
+        const int e = i * kWave + (lane & (x.slp - 1));
+        x.acc[i] = e < len ? acc[e] : 0.0;
+        x.own[i] = e < len ? own[e] : 0u;
+        x.eff[i] = 0.0;
+    }
+    x.dot = dot;
+}
+
+// The words as they are now to the sign array in LDS.
+template <int NE, int NI>
+__device__ __forceinline__ void sp_late_signs(const SpLateSide<NE, NI>& x, lds_u32* cur)
+{
+#pragma unroll
+    for (int it = 0; it < NI; ++it) {
+        lds_u8* p = (lds_u8*)cur + ((x.base[it] & 0xFFFFFF) >> 3);
+        const int nb = x.base[it] >> 24;
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+            if (b < nb) p[b] = (uint8_t)(x.old[it] >> (8 * b));
+    }
+}
+
+// Publishes the signs of x.eff (and, if asked, the share sum |x.eff|, scaled by 2^-cexp below 1 so that bit 62 can carry a tag
+// that flips with every write of the word), reads everybody's: x.old becomes the new signs, flip the bits that changed, c this
+// lane's part of the sum of the shares (their wave sum is c, in the order of sp_sum_scalar).  false: a wait ran out.
+template <int NE, int NI, bool SHARE>
+__device__ __forceinline__ bool sp_late_exchange(int lane, const SpLateArgs& a, uint64_t* xb, uint32_t seq, SpLateSide<NE, NI>& x, int cexp, int wait,
+                                                 uint32_t (&flip)[NI], double& c, int& spins, bool& late)
+{
+    constexpr uint32_t kTag = 0x40000000u;
+    constexpr int NC = SHARE ? kSpGrid / kWave : 0;
+    const int g = blockIdx.x;
+#pragma unroll
+    for (int i = 0; i < NE; ++i) {
+        const uint64_t bal = __ballot(i * kWave + lane < x.len && lane < x.slp && x.eff[i] < 0.0);
+        if (lane < 2 && i * kWave + lane * 32 < x.slice)
+            sp_store_tagged(xb + (2 * i + lane) * kSpGrid + g, lane ? (uint32_t)(bal >> 32) : (uint32_t)bal, seq);
+    }
+    const uint32_t ctag = (((seq + 1u) >> 1) & 1u) ? kTag : 0u;
+    if constexpr (SHARE) {
+        double t = 0.0;
+#pragma unroll
+        for (int i = 0; i < NE; ++i) t += sp_wave_sum(i * kWave + lane < x.len && lane < x.slp ? fabs(x.eff[i]) : 0.0);
+        t = __builtin_ldexp(t, -cexp);
+        if (lane == 0)
+            __hip_atomic_store(xb + kSpLateWords * kSpGrid + g,
+                               ((uint64_t)(((uint32_t)__double2hiint(t) & ~kTag) | ctag) << 32) | (uint64_t)(uint32_t)__double2loint(t),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    uint64_t w[NI], cw[NC + 1];
+    uint32_t caddr[NC + 1];
+#pragma unroll
+    for (int i = 0; i < NC; ++i) caddr[i] = (uint32_t)(kSpLateWords * kSpGrid + (lane + i * kWave < a.grid ? lane + i * kWave : a.grid - 1)) * 8u;
+    for (int d = 0; d < (wait >> kSpWaitShift); ++d) __builtin_amdgcn_s_sleep(1);
+    int spin = 0;
+    for (;;) {
+#pragma unroll
+        for (int it = 0; it < NI; ++it) w[it] = __hip_atomic_load((const uint64_t*)((const char*)xb + x.addr[it]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int i = 0; i < NC; ++i) cw[i] = __hip_atomic_load((const uint64_t*)((const char*)xb + caddr[i]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint32_t stale = 0u, cstale = 0u;
+#pragma unroll
+        for (int it = 0; it < NI; ++it) stale |= (uint32_t)(w[it] >> 32) ^ seq;
+#pragma unroll
+        for (int i = 0; i < NC; ++i) cstale |= (uint32_t)(cw[i] >> 32) ^ ctag;
+        if (__ballot((stale | (cstale & kTag)) != 0u) == 0) break;
+        if (++spin > a.max_spin) return false;
+        __builtin_amdgcn_s_sleep(1);
+    }
+    spins += spin;
+    late = spin > 0;
+#pragma unroll
+    for (int it = 0; it < NI; ++it) {
+        flip[it] = ((uint32_t)w[it] ^ x.old[it]) & x.keep[it];
+        x.old[it] = (uint32_t)w[it];
+    }
+    if constexpr (SHARE) {
+        double t = 0.0;
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            const double v = __builtin_ldexp(__hiloint2double((int)((uint32_t)(cw[i] >> 32) & ~kTag), (int)(uint32_t)cw[i]), cexp);
+            t += lane + i * kWave < a.grid ? v : 0.0;
+        }
+        c = t;
+    }
+    return true;
+}
+
+// part + the signed entries (at ycol of the flipped row) of flips f, f + Q, .., f + (Z - 1) Q of the list, those below total; all
+// loads are issued before the first add
+template <typename TE, int Z, typename List>
+__device__ __forceinline__ double sp_late_batch(const TE* __restrict__ ycol, int64_t ld, List list, int f, int Q, int total, double part)
+{
+    uint32_t en[Z];
+    TE val[Z];
+#pragma unroll
+    for (int z = 0; z < Z; ++z) en[z] = list[f + z * Q < total ? f + z * Q : 0];
+#pragma unroll
+    for (int z = 0; z < Z; ++z) val[z] = ycol[(int64_t)(en[z] & 0x7FFFFFFFu) * ld];
+#pragma unroll
+    for (int z = 0; z < Z; ++z) part += f + z * Q < total ? (double)sp_flip(val[z], en[z] >> 31) : 0.0;
+    return part;
+}
+
+// Waves 1 .. 7: the flipped entries of one half step, partial sums to red (slices of at most 64 entries: one per wave and entry,
+// else one per group of threads and entry).
 template <typename TE>
+__device__ __forceinline__ void sp_late_share(const TE* __restrict__ M, int64_t ld, int64_t off, int len, const uint32_t* list, int total, double* red)
+{
+    constexpr int kThreads = kSpThreads - kWave;
+    const int tid = (int)threadIdx.x - kWave, lane = tid & (kWave - 1), wv = tid / kWave;
+    int slp = 16;
+    while (slp < len) slp <<= 1;
+    const int Q = kThreads / slp, e = tid & (slp - 1), q = tid / slp;
+    double part = 0.0;
+    if (e < len && q < Q) {
+        const TE* ycol = M + off + e;
+        int f0 = 0;
+        while (f0 < total) {
+            const int left = (total - f0 + Q - 1) / Q;
+            if (left > 8) {
+                part = sp_late_batch<TE, 16>(ycol, ld, list, f0 + q, Q, total, part);
+                f0 += 16 * Q;
+            } else if (left > 4) {
+                part = sp_late_batch<TE, 8>(ycol, ld, list, f0 + q, Q, total, part);
+                f0 += 8 * Q;
+            } else if (left > 2) {
+                part = sp_late_batch<TE, 4>(ycol, ld, list, f0 + q, Q, total, part);
+                f0 += 4 * Q;
+            } else {
+                part = sp_late_batch<TE, 2>(ycol, ld, list, f0 + q, Q, total, part);
+                f0 += 2 * Q;
+            }
+        }
+    }
+    if (slp <= 16) part = sp_sum_xor16(part);
+    if (slp <= 32) part = sp_sum_xor32(part);
+    if (slp >= kWave) red[tid] = part;
+    else if (lane < slp) red[wv * slp + e] = part;
+}
+
+// The other side's products after x's signs changed by `flip`: y.acc += 2 sum over the flips of +-M[index][off + e] (rows of M are
+// indexed by x), the inner products of x's signs with the pending terms, y.eff.  Returns the number of flips.
+// cmd: what the other waves are told (1: t changed, 2: s changed).  stop(): asked while the entries are on their way; if it is true
+// nothing is changed.
+template <typename TE, int NE, int NI, typename Stop>
+__device__ __forceinline__ int sp_late_update(int lane, SpLateSide<NE, NI>& x, const uint32_t (&flip)[NI], SpLateSide<NE, NI>& y,
+                                              const TE* __restrict__ M, int64_t ld, int64_t off, lds_u32* P, int pstride, int np, double coef,
+                                              lds_u32* list, lds_f64* red, lds_args* la, int cmd, Stop stop)
+{
+    int cnt = 0;
+#pragma unroll
+    for (int it = 0; it < NI; ++it) cnt += __popc(flip[it]);
+    const int incl = sp_wave_scan_int(cnt);
+    const int all = __builtin_amdgcn_readlane(incl, kWave - 1);
+    const int Q = kWave / y.slp;
+    const bool alone = y.len <= kWave && all <= kSpLateLoads * Q;
+    double part[NE];
+#pragma unroll
+    for (int i = 0; i < NE; ++i) part[i] = 0.0;
+    // more flips than the list holds (hardly ever): one word of every lane at a time
+    const int rounds = all > kSpListCap / 2 ? NI : 1;
+    int delta = 0;
+    bool stopped = false;
+    for (int r = 0; r < rounds; ++r) {
+        int total = all, pos = incl - cnt;
+        if (rounds > 1) {
+            int one = 0;
+#pragma unroll
+            for (int it = 0; it < NI; ++it) one = it == r ? __popc(flip[it]) : one;
+            const int in = sp_wave_scan_int(one);
+            total = __builtin_amdgcn_readlane(in, kWave - 1);
+            pos = in - one;
+        }
+#pragma unroll
+        for (int it = 0; it < NI; ++it) {
+            uint32_t bits = rounds == 1 || it == r ? flip[it] : 0u;
+            while (bits) {
+                const int b = __ffs(bits) - 1;
+                bits &= bits - 1;
+                list[pos++] = (uint32_t)((x.base[it] & 0xFFFFFF) + b) | (((x.old[it] >> b) & 1u) << 31);
+            }
+        }
+        const int f0 = lane / y.slp;
+        uint32_t en[kSpLateLoads];
+        TE val[kSpLateLoads];
+        if (alone) {
+            // (the list is written and read by the lanes of one wave, whose LDS accesses keep their order)
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (y.len > 0 && total > 0) {
+                const int e = lane & (y.slp - 1);
+                const TE* ycol = M + off + (e < y.len ? e : y.len - 1);  // (past the slice its last entry is read and not used)
+                auto fetch = [&](auto z0, auto z1) {
+#pragma unroll
+                    for (int z = z0(); z < z1(); ++z) en[z] = list[f0 + z * Q < total ? f0 + z * Q : 0];
+#pragma unroll
+                    for (int z = z0(); z < z1(); ++z) val[z] = ycol[(int64_t)(en[z] & 0x7FFFFFFFu) * ld];
+                };
+                fetch(std::integral_constant<int, 0>(), std::integral_constant<int, 2>());
+                if (total > 2 * Q) fetch(std::integral_constant<int, 2>(), std::integral_constant<int, 4>());
+                if (total > 4 * Q) fetch(std::integral_constant<int, 4>(), std::integral_constant<int, kSpLateLoads>());
+            }
+        } else {
+            if (lane == 0) {
+                la->cmd = cmd;
+                la->total = total;
+            }
+            __syncthreads();
+        }
+        // ---- meanwhile.  Lane (pending term j, flip f): every sign that changed moves the inner product by two
+        if (np > 0) {
+            const int j = lane & (kSpLatePending - 1);
+            for (int f = lane / kSpLatePending; f < total; f += kWave / kSpLatePending) {
+                const uint32_t e = list[f], idx = e & 0x7FFFFFFFu;
+                if (j < np) delta += ((P[j * pstride + (int)(idx >> 5)] >> (idx & 31)) & 1u) != (e >> 31) ? -2 : 2;
+            }
+        }
+        if (r == 0) stopped = stop();
+        // ----
+        if (alone) {
+            if (y.len > 0 && total > 0) {
+#pragma unroll
+                for (int z = 0; z < 2; ++z) part[0] += f0 + z * Q < total ? (double)sp_flip(val[z], en[z] >> 31) : 0.0;
+                if (total > 2 * Q) {
+#pragma unroll
+                    for (int z = 2; z < 4; ++z) part[0] += f0 + z * Q < total ? (double)sp_flip(val[z], en[z] >> 31) : 0.0;
+                }
+                if (total > 4 * Q) {
+#pragma unroll
+                    for (int z = 4; z < kSpLateLoads; ++z) part[0] += f0 + z * Q < total ? (double)sp_flip(val[z], en[z] >> 31) : 0.0;
+                }
+                if (y.slp <= 16) part[0] = sp_sum_xor16(part[0]);
+                if (y.slp <= 32) part[0] = sp_sum_xor32(part[0]);
+            }
+        } else {
+            __syncthreads();
+            static_assert(kSpLateEntries == 2, "two steps of the lanes of an entry beyond 64");
+            const int stride = y.len > kWave ? 2 * kWave : y.slp, groups = y.len > kWave ? (kSpThreads - kWave) / stride : kSpWaves - 1;
+#pragma unroll
+            for (int i = 0; i < NE; ++i) {
+                const int e = i * kWave + (lane & (y.slp - 1));
+                double g[kSpWaves - 1];
+#pragma unroll
+                for (int z = 0; z < kSpWaves - 1; ++z) g[z] = z < groups && e < y.len ? red[z * stride + e] : 0.0;
+#pragma unroll
+                for (int z = 0; z < kSpWaves - 1; ++z) part[i] += g[z];
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    if (stopped) return all;
+    double ej = 0.0;
+    if (np > 0) {
+        // over the flips: lane distances 8, 16, 32
+        delta += __builtin_amdgcn_update_dpp(0, __builtin_amdgcn_update_dpp(0, delta, 0x140, 0xF, 0xF, true), 0x141, 0xF, 0xF, true);
+        {
+            const auto r = __builtin_amdgcn_permlane16_swap((unsigned)delta, (unsigned)delta, false, false);
+            delta = (int)(r[0] + r[1]);
+        }
+        {
+            const auto r = __builtin_amdgcn_permlane32_swap((unsigned)delta, (unsigned)delta, false, false);
+            delta = (int)(r[0] + r[1]);
+        }
+        x.dot += delta;
+        ej = coef * (double)x.dot;
+    }
+    double ejs[kSpLatePending];
+#pragma unroll
+    for (int j = 0; j < kSpLatePending; ++j)
+        ejs[j] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(ej), j), __builtin_amdgcn_readlane(__double2loint(ej), j));
+#pragma unroll
+    for (int i = 0; i < NE; ++i) {
+        y.acc[i] += 2.0 * part[i];
+        double v = y.acc[i];
+#pragma unroll
+        for (int j = 0; j < kSpLatePending; ++j) v -= sp_flip(ejs[j], (y.own[i] >> j) & 1u);
+        y.eff[i] = v;
+    }
+    return all;
+}
+
+// The loop.  A function of its own, not inlined: among the values that the rest of the kernel keeps in registers it goes through
+// scratch, and so do they (dense starts half as fast again).  All it is given and hands back is in LDS.
+template <typename TE, int NE, int NI>
+__device__ __attribute__((noinline)) void sp_late_loop(lds_args* la)
+{
+    int lane = threadIdx.x & (kWave - 1);
+    SpLateArgs a;
+    {
+        // (the same in every lane: into scalar registers)
+        uint32_t w[sizeof(SpLateArgs) / 4];
+#pragma unroll
+        for (int i = 0; i < (int)(sizeof(SpLateArgs) / 4); ++i) w[i] = __builtin_amdgcn_readfirstlane(((lds_u32*)la)[i]);
+        __builtin_memcpy(&a, w, sizeof(a));
+    }
+    lds_u32* const t_cur = lds_at<lds_u32>(a.t_cur);
+    lds_u32* const s_cur = lds_at<lds_u32>(a.s_cur);
+    lds_u32* const owns = lds_at<lds_u32>(a.owns);
+    lds_u32* const list = lds_at<lds_u32>(a.list);
+    lds_i32* const dots = lds_at<lds_i32>(a.dots);
+    lds_f64* const accu = lds_at<lds_f64>(a.accu);
+    lds_f64* const accv = lds_at<lds_f64>(a.accv);
+    lds_f64* const effv = lds_at<lds_f64>(a.effv);
+    lds_f64* const red = lds_at<lds_f64>(a.red);
+    const int pj = lane & (kSpLatePending - 1);
+    SpLateSide<NE, NI> ts, ss;
+    sp_late_init(lane, ts, a.clen, a.cs, a.n, a.grid, t_cur, accv, owns + kSpThreads, pj < a.np ? dots[pj] : 0);
+    sp_late_init(lane, ss, a.rlen, a.rs, a.m, a.grid, s_cur, accu, owns, pj < a.np ? dots[kSpLatePending + pj] : 0);
+    const double coef = pj < a.np ? lds_at<lds_f64>(a.coef)[pj] : 0.0;
+#pragma unroll
+    for (int i = 0; i < NE; ++i) {
+        const int e = i * kWave + (lane & (ts.slp - 1));
+        ts.eff[i] = e < a.clen ? effv[e] : 0.0;
+    }
+    uint32_t flip[NI];
+    int status = 2, halves = 0, spins = 0, j = a.j;
+    int64_t fl = 0, flr = 0;
+    double c = 0.0, c_prev = a.c_prev, none = 0.0;
+    bool late = false;
+    for (;;) {
+        // t = sgn(v), c = sum |v| (Algorithm 4 lines 6-7)
+        ++a.seq_t;
+        if (!sp_late_exchange<NE, NI, true>(lane, a, a.xbuf + (a.seq_t & 1u) * kSpLateHalf, a.seq_t, ts, a.cexp, a.wait_t, flip, c, spins, late)) break;
+        a.wait_t = sp_adapt(a.wait_t, late);
+        ++j;
+        // u += 2 sum over flipped columns, s = sgn(u).  Line 8 is tested while the entries of the flipped columns are on their way.
+        const int ft = sp_late_update<TE>(lane, ts, flip, ss, (const TE*)a.RT, a.m, a.i0, lds_at<lds_u32>(a.PT), a.pt_stride, a.np, coef, list, red, la, 1,
+                                          [&]() {
+                                              c = sp_wave_sum(c);
+                                              if (c <= c_prev || j >= a.max_iters) status = 1;
+                                              return __builtin_amdgcn_readfirstlane(status) == 1;
+                                          });
+        if (__builtin_amdgcn_readfirstlane(status) == 1) break;
+        c_prev = c;
+        fl += ft;
+        ++a.seq_s;
+        if (!sp_late_exchange<NE, NI, false>(lane, a, a.xbuf + (2 + (a.seq_s & 1u)) * kSpLateHalf, a.seq_s, ss, 0, a.wait_s, flip, none, spins, late)) break;
+        a.wait_s = sp_adapt(a.wait_s, late);
+        ++halves;
+        // v += 2 sum over flipped rows
+        const int fs = sp_late_update<TE>(lane, ss, flip, ts, (const TE*)a.R, a.n, a.j0, lds_at<lds_u32>(a.PS), a.ps_stride, a.np, coef, list, red, la, 2, []() { return false; });
+        flr += fs;
+        if (ft > 2 * a.cap_t || fs > 2 * a.cap_s) {
+            status = 0;
+            break;
+        }
+    }
+    sp_late_signs(ts, t_cur);
+    sp_late_signs(ss, s_cur);
+    if (status == 0) {
+#pragma unroll
+        for (int i = 0; i < NE; ++i) {
+            const int e = i * kWave + lane;
+            if (lane < ts.slp && e < a.clen) {
+                accv[e] = ts.acc[i];
+                effv[e] = ts.eff[i];
+            }
+            if (lane < ss.slp && e < a.rlen) accu[e] = ss.acc[i];
+        }
+    }
+    if (lane == 0) {
+        la->c = c;
+        la->c_prev = c_prev;
+        la->status = status;
+        la->j = j;
+        la->halves = halves;
+        la->spins = spins;
+        la->seq_t = a.seq_t;
+        la->seq_s = a.seq_s;
+        la->wait_t = a.wait_t;
+        la->wait_s = a.wait_s;
+        la->flips = fl;
+        la->flips_rows = flr;
+        la->cmd = 0;
+    }
+}
+
+// LATE: with late alternations.  Its code costs the rest registers: dense starts and flushes of the kernel without it are up to
+// a tenth faster, so that matrices whose terms are short take that one (see sparse_late).
+template <typename TE, bool LATE>
 __global__ void __launch_bounds__(kSpThreads) sparse_delay_kernel(SparseArgs a)
 {
     extern __shared__ __align__(16) unsigned char sp_lds[];
@@ -1041,12 +1525,22 @@ __global__ void __launch_bounds__(kSpThreads) sparse_delay_kernel(SparseArgs a)
     const int wait0 = a.poll_delay << kSpWaitShift;  // of the exchanges behind a dense pass
     int waits = wait0, waitt = wait0;
     int np = 0;  // pending terms
+    // late alternations on one wave: sequence numbers of their exchanges, waits, flips that a half step may have
+    uint32_t late_seq_t = a.seq_late[0], late_seq_s = a.seq_late[1];
+    int late_wait_t = wait0, late_wait_s = wait0, late_cexp = 0;
+    const int late_items = a.grid * (((rs > cs ? rs : cs) + 31) >> 5);
+    const int late_cap_t = kSpLateShare * (kSpThreads - kWave) / rs, late_cap_s = kSpLateShare * (kSpThreads - kWave) / cs;  // (flips of t change u)
     int ahead = 0, ahead_made = 0;  // first products R' t_0 formed in advance: still unused / formed by the last pass
     uint32_t own_u = 0u, own_v = 0u;  // their signs at this thread's row of I_g / column of J_g, bit j for term j
     double F;    // ||R_k||_F^2 of the true remainder
     {
         const double f0 = a.trace[k];
         F = f0 * f0;
+        // a share of c is at most ||R||_F sqrt(mn)
+        int e0 = 0, e1 = 0;
+        (void)frexp(f0, &e0);
+        (void)frexp(sqrt(total), &e1);
+        late_cexp = e0 + e1 + 1;
     }
 
     for (;;) {
@@ -1132,23 +1626,98 @@ __global__ void __launch_bounds__(kSpThreads) sparse_delay_kernel(SparseArgs a)
         int j = 0;
         double c_prev = -INFINITY;
         bool handover = flush;  // the transposed copy was rewritten: the next exchange carries the fences
+        bool few = false;       // the flips of the last alternation are few enough for one wave
         for (;;) {
-            // ---- finish the column half: t = sgn(v), c = sum |v| (Algorithm 4 lines 6-7), all-gather
-            const double cabs = (tid < clen) ? fabs(pd.effv[tid]) : 0.0;
-            const double cpart = sp_share_of_c(cabs, sh);
-            if (!sp_exchange(a, ++seq, pd.effv, clen, cs, n, cpart, true, t_oth, sh, spins, handover, waitt, late)) {
-                if (tid == 0) atomicExch((unsigned*)&a.res->err, 1u);
-                return;
+            double c = 0.0;
+            bool complete = false, late_done = false;
+            if (LATE && few) {
+                // ---- late alternations, wave 0 alone (see sp_late_exchange)
+                SpLateArgs& la = *(SpLateArgs*)sh.scal;
+                int* dots = (int*)(sh.scal + kSpLateDots);  // [2][8]
+                uint32_t* owns = (uint32_t*)pd.effu;        // [2][kSpThreads] (u is formed anew)
+                owns[tid] = own_u;
+                owns[kSpThreads + tid] = own_v;
+                if (wv < np) {
+                    int ct = 0, cr = 0;
+                    for (int p = lane; p < (int)nwords32; p += kWave) ct += __popc(pd.PT[wv * pd.pt_stride + p] ^ t_cur[p]);
+                    for (int p = lane; p < (int)mwords32; p += kWave) cr += __popc(pd.PS[wv * pd.ps_stride + p] ^ s_cur[p]);
+                    ct = sp_wave_sum_int(ct);
+                    cr = sp_wave_sum_int(cr);
+                    if (lane == 0) {
+                        dots[wv] = (int)n - 2 * ct;
+                        dots[kSpLatePending + wv] = (int)m - 2 * cr;
+                    }
+                }
+                if (tid == kSpThreads - 1) {
+                    la.R = a.R, la.RT = a.RT, la.xbuf = a.xbuf + 2 * kSpHalfWords;
+                    la.i0 = i0, la.j0 = j0, la.m = m, la.n = n, la.c_prev = c_prev;
+                    la.t_cur = lds_address(t_cur), la.s_cur = lds_address(s_cur), la.owns = lds_address(owns), la.list = lds_address(sh.list);
+                    la.dots = lds_address(dots), la.accu = lds_address(sh.accu), la.accv = lds_address(sh.accv), la.effv = lds_address(pd.effv);
+                    la.coef = lds_address(pd.coef), la.PS = lds_address(pd.PS), la.PT = lds_address(pd.PT);
+                    la.ps_stride = pd.ps_stride, la.pt_stride = pd.pt_stride, la.grid = a.grid, la.rs = rs, la.cs = cs, la.rlen = rlen, la.clen = clen;
+                    la.np = np, la.cap_t = late_cap_t, la.cap_s = late_cap_s, la.red = lds_address(pd.effu), la.cexp = late_cexp;
+                    la.max_iters = a.max_iters, la.max_spin = a.max_spin;
+                    la.seq_t = late_seq_t, la.seq_s = late_seq_s, la.wait_t = late_wait_t, la.wait_s = late_wait_s, la.j = j;
+                }
+                __syncthreads();
+                if (__builtin_amdgcn_readfirstlane(wv) == 0) {
+                    lds_args* l = (lds_args*)&la;
+                    const bool one = rs <= kWave && cs <= kWave, few_items = late_items <= kWave * kSpLateItems / 2;
+                    if (one && few_items) sp_late_loop<TE, 1, kSpLateItems / 2>(l);
+                    else if (one) sp_late_loop<TE, 1, kSpLateItems>(l);
+                    else if (few_items) sp_late_loop<TE, kSpLateEntries, kSpLateItems / 2>(l);
+                    else sp_late_loop<TE, kSpLateEntries, kSpLateItems>(l);
+                    __syncthreads();
+                } else {
+                    for (;;) {
+                        __syncthreads();
+                        const int cmd = __builtin_amdgcn_readfirstlane(la.cmd), total_f = __builtin_amdgcn_readfirstlane(la.total);
+                        if (cmd == 0) break;
+                        const bool rows = cmd == 1;  // flipped columns change the rows' products
+                        sp_late_share<TE>(rows ? RT : R, rows ? m : n, rows ? i0 : j0, rows ? rlen : clen, (const uint32_t*)sh.list, total_f, pd.effu);
+                        __syncthreads();
+                    }
+                }
+                const int status = __builtin_amdgcn_readfirstlane(la.status);
+                if (status == 2) {
+                    if (tid == 0) atomicExch((unsigned*)&a.res->err, 1u);
+                    return;
+                }
+                c = la.c;
+                c_prev = la.c_prev;
+                j = la.j;
+                alternations += la.halves;
+                spins += la.spins;
+                late_seq_t = la.seq_t;
+                late_seq_s = la.seq_s;
+                late_wait_t = la.wait_t;
+                late_wait_s = la.wait_s;
+                flips += la.flips;
+                flips_rows += la.flips_rows;
+                complete = status == 1;
+                few = false;
+                late_done = true;
+                __syncthreads();  // (sh.scal is written again)
+                if (!complete) continue;
             }
-            if (!handover) waitt = sp_adapt(waitt, late);
-            handover = false;
-            {
-                uint32_t* z = t_cur; t_cur = t_oth; t_oth = z;
+            if (!LATE || !late_done) {
+                // ---- finish the column half: t = sgn(v), c = sum |v| (Algorithm 4 lines 6-7), all-gather
+                const double cabs = (tid < clen) ? fabs(pd.effv[tid]) : 0.0;
+                const double cpart = sp_share_of_c(cabs, sh);
+                if (!sp_exchange(a, ++seq, pd.effv, clen, cs, n, cpart, true, t_oth, sh, spins, handover, waitt, late)) {
+                    if (tid == 0) atomicExch((unsigned*)&a.res->err, 1u);
+                    return;
+                }
+                if (!handover) waitt = sp_adapt(waitt, late);
+                handover = false;
+                {
+                    uint32_t* z = t_cur; t_cur = t_oth; t_oth = z;
+                }
+                ++j;
+                c = sp_sum_scalar(sh, a.grid);
+                complete = c <= c_prev || j >= a.max_iters;  // ---- Algorithm 4 line 8
             }
-            ++j;
-            const double c = sp_sum_scalar(sh, a.grid);
-            // ---- Algorithm 4 line 8
-            if (c <= c_prev || j >= a.max_iters) {
+            if (complete) {
                 if (!(c <= c_prev)) warn = 1;
                 const double ck = c / total;
                 const double ckt = (double)(TE)ck;  // the stored coefficient is what the flush subtracts
@@ -1181,6 +1750,7 @@ __global__ void __launch_bounds__(kSpThreads) sparse_delay_kernel(SparseArgs a)
             c_prev = c;
             // ---- row half, sparse: u' += 2 sum over flipped columns (rows of the transposed copy), correction, s
             // (the products go first: the barriers of the compaction publish them)
+            const int64_t flips0 = flips, flips_rows0 = flips_rows;
             sp_pending_dots(pd.PT, pd.pt_stride, (int)nwords32, n, t_cur, np, width, pd.coef, pd.ej);
             sp_accumulate_flips<TE>(RT, m, i0, rlen, t_cur, t_oth, n, sh.accu, sh, flips);
             sp_effective(sh.accu, rlen, own_u, pd.ej, width, pd.effu);
@@ -1197,9 +1767,12 @@ __global__ void __launch_bounds__(kSpThreads) sparse_delay_kernel(SparseArgs a)
             sp_pending_dots(pd.PS, pd.ps_stride, (int)mwords32, m, s_cur, np, width, pd.coef, pd.ej);
             sp_accumulate_flips<TE>(R, n, j0, clen, s_cur, s_oth, m, sh.accv, sh, flips_rows);
             sp_effective(sh.accv, clen, own_v, pd.ej, width, pd.effv);
+            few = LATE && j >= (alternations > 6 * (int)(k - a.k_start + 1) ? 1 : 3) && flips - flips0 <= late_cap_t && flips_rows - flips_rows0 <= late_cap_s;
         }
     }
     if (g == 0 && tid == 0) {
+        a.res->seq_late[0] = late_seq_t;
+        a.res->seq_late[1] = late_seq_s;
         a.res->k = k;
         a.res->alternations = alternations;
         a.res->updates = updates;
@@ -1261,7 +1834,7 @@ bool sparse_supported(scd_dtype dt, int order, const int64_t* dims, int grid, in
     return true;
 }
 
-size_t sparse_xbuf_bytes() { return (size_t)2 * kSpHalfWords * 8; }
+size_t sparse_xbuf_bytes() { return ((size_t)2 * kSpHalfWords + 4 * kSpLateHalf) * 8; }
 
 hipError_t launch_transpose(const void* in, void* out, scd_dtype dt, int64_t rows, int64_t cols, hipStream_t st)
 {
@@ -1281,28 +1854,36 @@ int sparse_delay_width(int64_t m, int64_t n)
     return w >= 4 ? w : 0;
 }
 
+// Whether late alternations run on one wave: slices and words that its registers hold, and terms of more than a few
+// alternations, which go with min(m, n) / sqrt(max(m, n)) (2.5 alternations at 8192x512, where it is 6, 11 at 200x200, where it is
+// 14).  Us per alternation without / with: f64 4096x256 on 64 workgroups 14.4 / 15.8, 8192x512 on 32 32.1 / 34.9, 200x200 on 32 8.1
+// / 5.8, 512x512 8.1 / 5.5, 4096x4096 9.4 / 6.0; f32 1024x4096 on 32 12.2 / 10.7, 14336x4096 14.1 / 11.5, 4096x4096 on 64 9.9 / 6.7;
+// slices of up to 256 as well (14336x4096 on 64): 21.6 / 25.9.
+static bool sparse_late(const SparseArgs& a)
+{
+    const int slice = a.rs > a.cs ? a.rs : a.cs;
+    const int64_t lo = a.m < a.n ? a.m : a.n, hi = a.m < a.n ? a.n : a.m;
+    return a.delay_width <= kSpLatePending && slice <= kWave * kSpLateEntries && a.grid * ((slice + 31) / 32) <= kWave * kSpLateItems && lo * lo > 64 * hi;
+}
+
 template <typename TE>
 static hipError_t launch_sparse_t(const SparseArgs& a, hipStream_t st)
 {
     const size_t lds = sparse_lds_bytes(a.m, a.n, a.delay_width);
     if (lds > kSpMaxLds || a.delay_width < 0 || a.delay_width > 32) return hipErrorInvalidValue;
-    const void* fn = a.delay_width > 0 ? (const void*)sparse_delay_kernel<TE> : (const void*)sparse_kernel<TE>;
+    void (*const fn)(SparseArgs) = a.delay_width == 0 ? sparse_kernel<TE> : sparse_late(a) ? sparse_delay_kernel<TE, true> : sparse_delay_kernel<TE, false>;
     // always the same ceiling, whatever this launch needs: launches from several host threads set it too
-    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSpMaxLds);
+    hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSpMaxLds);
     if (e != hipSuccess) return e;
     int dev = 0, per_cu = 0, cus = 0;
     e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e == hipSuccess) {
-        if (a.delay_width > 0) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sparse_delay_kernel<TE>, kSpThreads, lds);
-        else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sparse_kernel<TE>, kSpThreads, lds);
-    }
+    if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kSpThreads, lds);
     if (e != hipSuccess) return e;
     // all workgroups must be resident at once (every wait in the kernel is bounded in case they are not)
     if (a.grid < 1 || a.grid > kSpGrid) return hipErrorInvalidValue;
     if ((int64_t)per_cu * cus < a.grid) return hipErrorCooperativeLaunchTooLarge;
-    if (a.delay_width > 0) hipLaunchKernelGGL((sparse_delay_kernel<TE>), dim3(a.grid), dim3(kSpThreads), lds, st, a);
-    else hipLaunchKernelGGL((sparse_kernel<TE>), dim3(a.grid), dim3(kSpThreads), lds, st, a);
+    hipLaunchKernelGGL(fn, dim3(a.grid), dim3(kSpThreads), lds, st, a);
     return hipGetLastError();
 }
 
