@@ -709,7 +709,9 @@ int run_pstream(scd_ctx* c, int64_t n)
     a.grid = geo.grid;
     a.rpw = geo.rpw;
     a.cs = geo.cs;
-    a.lds_rows = geo.lds_rows;
+    a.lds_rows = geo.lds_rows + 1;
+    a.xexp = resident_exponent(c->fro * sqrt((double)geo.rpw) / 16.0, 1);
+    a.cexp = resident_exponent(c->fro * sqrt((double)c->total) / 16.0, 1);
     a.profile = (int32_t)c->opt[SCD_OPT_VERBOSE];
     a.res = c->res_dev;
     SlotLease lease;

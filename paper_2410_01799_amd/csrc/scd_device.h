@@ -209,7 +209,7 @@ struct PStreamGeometry {
     int grid;        // workgroups (one per compute unit)
     int rpw;         // rows per workgroup
     int cs;          // columns per slice of the hop-1 reduction (multiple of 8, at most 256)
-    int lds_rows;    // rows of a workgroup's block kept in LDS for the whole launch
+    int lds_rows;    // rows of a workgroup's block kept in LDS for the whole launch, beside one more (PStreamArgs::lds_rows)
     size_t lds_bytes, xp_bytes, xq_bytes;
 };
 
@@ -222,7 +222,7 @@ struct PStreamArgs {
     int32_t max_iters, max_spin;
     int32_t poll_delay;
     uint32_t seq;            // exchange sequence numbers already used
-    uint64_t* xp;            // hop 1: [2 parities][grid][n values as tagged words]
+    uint64_t* xp;            // hop 1: [2 parities][grid][n values]
     uint64_t* xq;            // hop 2: [2 parities][grid][16 words]
     uint64_t* S;             // term-major outputs; rows k_start.. of S must be zero (bits are OR-ed in)
     uint64_t* T;             // second mode's sign vectors
@@ -233,6 +233,7 @@ struct PStreamArgs {
     int32_t mw, nw;
     int32_t grid, rpw, cs, lds_rows;
     int32_t profile;         // 1: workgroup 0 times its phases
+    int32_t xexp, cexp;      // column sums of a workgroup's rows are below 2^xexp, shares of c below 2^cexp
     int32_t scalars;         // order 3, 1: real last mode ("RGB scalars"): c holds n3 coefficients per term, S3 is not written
     ResidentResult* res;
 };

@@ -11,20 +11,25 @@
 //               launch (they are read from memory once per launch, not once per alternation); the others are
 //               streamed with a second register tile in flight.  On a converged term the same pass first
 //               subtracts c_k s t^T (Algorithm 5 line 10) and sums the squares.
-//   hop 1       every workgroup lays its partial column sums out in column order in LDS and publishes them as
-//               tagged 8-byte words, every store instruction writing contiguous words; the owner of a slice of
+//   hop 1       every workgroup publishes its partial column sums, 16 bytes of words per chunk of a thread, so that every store
+//               instruction writes contiguous words; the owner of a slice of
 //               `cs` columns adds the partials of all workgroups in a fixed order (f64) -> its entries of
 //               v = R^T s, its bits of t = sgn(v) and its share of c = sum |v| (lines 6-7).
 //   hop 2       the owners publish sign bits and shares, every workgroup gathers all of them: the full t,
 //               c (and ||R||_F^2 after an update), added in the same order everywhere, so that every
 //               workgroup takes the same decision of line 8 without any further communication.
-// Exchange: value and sequence number travel in one 8-byte relaxed agent-scope store and are read back with
-// agent-scope loads; slots alternate by the parity of the sequence number.  Every wait is bounded; when one
+// Exchange: values and tag (a free bit of the exponent, see kPsTag; sign bits: a sequence number) travel in one 8-byte word and
+// are read back with device-scope loads; slots alternate by the parity of the sequence number.  Every wait is bounded; when one
 // runs out all workgroups leave and the host reports SCD_ETIMEOUT.  No float atomics: bit-identical reruns.
 // What an alternation costs beyond its pass is a chain of LDS steps, barriers and the two hops: a barrier that joins a
 // predicate costs three, so a wait that ran out is a sticky flag in LDS read behind the plain barrier; the words a
 // thread gathers in hop 2 are worked out before the wait, with reciprocals.  Measured, us per alternation: 4000x3000x3
 // 34.7 -> 33.9, 640x480x3 11.7 -> 11.2, 256x256x3 11.9 -> 11.3, 8192x1024 f32 15.4 -> 14.8, the same bits.
+// The exchanges' bytes came next: one f32 and a sequence number in a word, laid out in column order through LDS and read 8
+// bytes a lane, were 18 MB each way at 4000x3000x3 (hop 1 8.1 us of a pass); two f32 or one f64 in a word straight from the
+// registers, read 16 bytes a lane, 5.4, and the LDS row that the layout took holds a row of R.  With the rows in registers (ps_launch_rb) and
+// chunks counted one by one, us per pass before / now: 4000x3000x3 37.5 / 32.1, 2000x1500x3 20.4 / 15.5, 640x480x3 11.8 / 9.6,
+// 1024x1024x3 f64 16.7 / 12.8, 5000x2048 f32 14.7 / 10.8, 3000x5000 f64 29.8 / 21.7, 700x16384 36.1 / 22.3, 8192x1024 14.8 / 14.7.
 #include "scd_device.h"
 #include "scd_rng.h"
 
@@ -46,13 +51,11 @@ template <>
 struct PsVec<float> {
     typedef float4 type;
     static constexpr int N = 4;
-    static constexpr int WPE = 1;  // tagged words per published value
 };
 template <>
 struct PsVec<double> {
     typedef double2 type;
     static constexpr int N = 2;
-    static constexpr int WPE = 2;
 };
 
 __device__ __forceinline__ float ps_fma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
@@ -127,41 +130,91 @@ __device__ __forceinline__ uint64_t ps_load(const uint64_t* p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Hop 1, one thread: the partial sums of members q, q + Q, q + 2 Q, ... < G for one column (at basep + member *
-// slot1, WPE tagged words n apart), added in that order; NF members are in flight together.  false: a wait ran out.
-template <int WPE, int NF>
-__device__ __forceinline__ bool ps_hop1_gather(const uint64_t* basep, int q, int Q, int G, size_t slot1, int64_t n, uint32_t seq,
-                                               int max_spin, double& s, int& spin)
+// Published sums are scaled by a power of two below 1 (a.xexp, a.cexp), so that the top bit of their exponents is free for a tag
+// that flips with every write of a slot: two f32 or one f64 fill an 8-byte word, which is stored and seen whole.
+constexpr uint32_t kPsTag = 0x40000000u;
+__device__ __forceinline__ uint32_t ps_tag(uint32_t seq) { return (((seq + 1u) >> 1) & 1u) ? kPsTag : 0u; }
+typedef unsigned ps_u4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ ps_u4 ps_load16(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff)
+{
+    return __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff, (int)soff, (int)0x80000010);  // volatile, device scope
+}
+// 16 bytes of sums (two words)
+__device__ __forceinline__ void ps_publish16(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff, const float* v, int e, uint32_t tag)
+{
+    ps_u4 w;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i] = (__float_as_uint(__builtin_ldexpf(v[i], -e)) & ~kPsTag) | tag;
+    __builtin_amdgcn_raw_buffer_store_b128(w, rs, (int)voff, (int)soff, (int)0x80000010);
+}
+__device__ __forceinline__ void ps_publish16(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff, const double* v, int e, uint32_t tag)
+{
+    ps_u4 w;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const double x = __builtin_ldexp(v[i], -e);
+        w[2 * i] = (uint32_t)__double2loint(x);
+        w[2 * i + 1] = ((uint32_t)__double2hiint(x) & ~kPsTag) | tag;
+    }
+    __builtin_amdgcn_raw_buffer_store_b128(w, rs, (int)voff, (int)soff, (int)0x80000010);
+}
+
+// Hop 1, one thread: 16 bytes of the partial sums of members q, q + Q, q + 2 Q, ... < G (member i's at voff + i * slot), added in
+// that order; NF members are in flight together.  false: a wait ran out.
+template <typename TE, int NF>
+__device__ __forceinline__ bool ps_hop1_gather(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff, int q, int Q, int G, uint32_t slot, uint32_t tag,
+                                               int max_spin, double (&s)[PsVec<TE>::N], int& spin)
 {
 #pragma nounroll
     for (int m0 = q; m0 < G; m0 += NF * Q) {
-        uint64_t w[NF][WPE];
+        ps_u4 w[NF];
         for (;;) {
-            bool fresh = true;
+            uint32_t stale = 0u;
+#pragma unroll
+            for (int i = 0; i < NF; ++i) w[i] = ps_load16(rs, voff + (uint32_t)(m0 + i * Q < G ? m0 + i * Q : m0) * slot, soff);
 #pragma unroll
             for (int i = 0; i < NF; ++i) {
-                const int mem = m0 + i * Q < G ? m0 + i * Q : m0;
-#pragma unroll
-                for (int h = 0; h < WPE; ++h) w[i][h] = ps_load(basep + (size_t)mem * slot1 + (size_t)h * n);
+                stale |= (w[i].y ^ tag) | (w[i].w ^ tag);
+                if constexpr (sizeof(TE) == 4) stale |= (w[i].x ^ tag) | (w[i].z ^ tag);
             }
-#pragma unroll
-            for (int i = 0; i < NF; ++i)
-#pragma unroll
-                for (int h = 0; h < WPE; ++h) fresh = fresh && ((uint32_t)(w[i][h] >> 32) == seq);
-            if (fresh) break;
+            if (!(stale & kPsTag)) break;
             if (++spin > max_spin) return false;
             __builtin_amdgcn_s_sleep(1);
         }
 #pragma unroll
         for (int i = 0; i < NF; ++i) {
             if (m0 + i * Q < G) {
-                if constexpr (WPE == 1) s += (double)__uint_as_float((uint32_t)w[i][0]);
-                else s += __longlong_as_double((long long)((w[i][1] << 32) | (w[i][0] & 0xFFFFFFFFull)));
+                if constexpr (sizeof(TE) == 4) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) s[e] += (double)__uint_as_float(w[i][e] & ~kPsTag);
+                } else {
+                    s[0] += __hiloint2double((int)(w[i].y & ~kPsTag), (int)w[i].x);
+                    s[1] += __hiloint2double((int)(w[i].w & ~kPsTag), (int)w[i].z);
+                }
             }
         }
     }
     return true;
 }
+
+// Half-width sums of two registers: even 16-lane rows (the lower 32 lanes) end with a's sum over distance 16 (32), the others
+// with b's.
+__device__ __forceinline__ double ps_half16(double a, double b)
+{
+    const auto l = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+__device__ __forceinline__ double ps_half32(double a, double b)
+{
+    const auto l = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+
+// Of `rows` rows, those kept in LDS where there is room for `room`: whole batches, unless all fit (a batch costs a join across the waves
+// however few rows it has).
+__device__ __host__ __forceinline__ int ps_lds_rows(int rows, int room, int batch) { return rows <= room ? rows : room >= batch ? room / batch * batch : room; }
 
 // profile mode: 100 MHz ticks of workgroup 0 per phase
 #define PS_TICK(slot)                                                  \
@@ -178,7 +231,7 @@ struct PsShared {
     union {
         // the two exchanges use this space one after the other (barriers in between)
         struct {
-            double part[kPsThreads];   // hop 1: partial sums per (member group, column)
+            double part[2 * kPsThreads];  // hop 1: partial sums per (member group, column)
             double v[kPsMaxSlice];     // order 3: the own slice of W_1
         };
         uint32_t scal[2 * kPsMaxLast + 2][kSpGrid];  // hop 2: low/high halves of the members' scalars
@@ -188,6 +241,7 @@ struct PsShared {
     uint32_t tw32[8];              // sign words of the own slice
     uint32_t fail;                 // a wait of some thread ran out (sticky: every workgroup leaves then)
     double w2part[kPsMaxLast];     // order 3: the own slice's part of the last mode's sums
+    double mag[2 * kPsMaxLast];    // real last mode: magnitudes of the columns, by column mod n3
     int64_t ticks[6];              // profile mode
     uint64_t tick0;
 };
@@ -200,13 +254,13 @@ struct PsTile {
 
 // bits of this thread's columns from a bit array in LDS: element e of chunk c in bit c * VE + e
 template <typename TE, int CPT>
-__device__ __forceinline__ uint64_t ps_gather_bits(const uint64_t* bits, int64_t nch)
+__device__ __forceinline__ uint64_t ps_gather_bits(int tid, const uint64_t* bits, int64_t nch)
 {
     constexpr int VE = PsVec<TE>::N;
     uint64_t out = 0;
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
-        const int64_t ch = threadIdx.x + c * kPsThreads;
+        const int64_t ch = tid + c * kPsThreads;
         const int64_t chc = ch < nch ? ch : nch - 1;
         const int64_t col = chc * VE;  // VE divides 64: a chunk never straddles a word
         const uint64_t b = (bits[col >> 6] >> (col & 63)) & ((1ull << VE) - 1);
@@ -229,27 +283,28 @@ __device__ __forceinline__ uint32_t ps_rowsigns(const uint8_t* sb, int rb, int n
 // RB rows of the block from `base` (global memory or the LDS copy), never predicated: indices past the end
 // are clamped and the values dropped later.  rb: first row of the batch relative to `base`, rows: rows there.
 template <typename TE, int CPT, int RB>
-__device__ __forceinline__ void ps_tile_load(PsTile<TE, CPT, RB>& t, const TE* base, int64_t cols, int rb, int rows,
+__device__ __forceinline__ void ps_tile_load(int tid, PsTile<TE, CPT, RB>& t, const TE* base, int64_t cols, int rb, int rows,
                                              int64_t nch, bool valid)
 {
     constexpr int VE = PsVec<TE>::N;
     typedef typename PsVec<TE>::type V;
-    int64_t chs[CPT];
+    // (a scalar row and a 32-bit lane offset)
+    uint32_t at[CPT];
+    const uint32_t mask = valid ? ~0u : 0u;
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
-        const int64_t ch = threadIdx.x + c * kPsThreads;
-        const int64_t chc = ch < nch ? ch : nch - 1;
-        chs[c] = valid ? chc : 0;
+        const int ch = tid + c * kPsThreads;
+        at[c] = (uint32_t)(ch < (int)nch ? ch : (int)nch - 1) * 16u & mask;
     }
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
         int row = rb + r;
         row = row < rows ? row : rows - 1;
         row = valid ? row : 0;
-        const V* rowp = (const V*)(base + (int64_t)row * cols);
+        const char* rowp = (const char*)(base + (int64_t)row * cols);
 #pragma unroll
         for (int c = 0; c < CPT; ++c) {
-            const V v = rowp[chs[c]];
+            const V v = *(const V*)(rowp + at[c]);
             if constexpr (VE == 4) {
                 t.x[r][c * 4 + 0] = v.x;
                 t.x[r][c * 4 + 1] = v.y;
@@ -264,26 +319,27 @@ __device__ __forceinline__ void ps_tile_load(PsTile<TE, CPT, RB>& t, const TE* b
 }
 
 // One batch of RB rows.  mode 0: a further alternation; 1: first subtract the finished term, write the rows
-// back (to `base`: memory or the LDS copy) and sum the squares; 2: only sum the squares (start of a launch).
-// full: every row of the batch and every chunk of this thread exists.  mode and full are the same for every
-// thread: the branches on them are scalar.
+// back (to `base`: memory or the LDS copy; null: they stay in registers) and sum the squares; 2: only sum the squares (start of a
+// launch).  full: every row of the batch and every chunk of this thread exists.  mode and full are the same for every
+// thread: the branches on them are scalar.  n3: the last mode where the magnitudes to subtract differ along it, else 0.
 template <typename TE, int CPT, int RB>
-__device__ __forceinline__ void ps_process(PsTile<TE, CPT, RB>& t, TE* base, int64_t cols, int rb, int rows, int64_t nch,
-                                           int mode, bool full, const TE* sf, uint64_t updb, TE ck, const TE* magrow, TE* acc, double& fsq,
+__device__ __forceinline__ void ps_process(int tid, PsTile<TE, CPT, RB>& t, TE* base, int64_t cols, int rb, int rows, int64_t nch,
+                                           int mode, bool full, const TE* sf, uint64_t updb, TE ck, int n3, TE* acc, double& fsq,
                                            uint8_t* s_new, PsShared& sh, int parity)
 {
     constexpr int VE = PsVec<TE>::N;
     constexpr int NE = CPT * VE;
     typedef typename PsVec<TE>::type V;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int lane = tid & 63, wv = tid >> 6;
     double ps[RB];
-    if (!full) {
+    // (an alternation leaves what lies past the end as it was loaded: the factors of those columns and rows are zero)
+    if (mode >= 1 && !full) {
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
             const bool rok = rb + r < rows;
 #pragma unroll
             for (int c = 0; c < CPT; ++c) {
-                const bool ok = rok && (threadIdx.x + c * kPsThreads < nch);
+                const bool ok = rok && (tid + c * kPsThreads < nch);
 #pragma unroll
                 for (int e = 0; e < VE; ++e) t.x[r][c * VE + e] = ok ? t.x[r][c * VE + e] : (TE)0;
             }
@@ -291,34 +347,33 @@ __device__ __forceinline__ void ps_process(PsTile<TE, CPT, RB>& t, TE* base, int
     }
     if (mode == 1) {
         // R <- R - ck s t^T (Algorithm 5 line 10): the product of the two signs picks +ck or -ck
+        const float rn3 = n3 ? 1.0f / (float)n3 : 0.0f;
 #pragma unroll
-        for (int r = 0; r < RB; ++r) {
-            const bool rok = full || (rb + r < rows);
-            const uint32_t sold = (t.rowsign >> r) & 1u;
-            V* rowp = (V*)(base + (int64_t)(rok ? rb + r : rows - 1) * cols);
+        for (int c = 0; c < CPT; ++c) {
+            TE mg[VE];
 #pragma unroll
-            for (int c = 0; c < CPT; ++c) {
-                const bool ok = full || (rok && (threadIdx.x + c * kPsThreads < nch));
-                // real last mode (magrow != null): the magnitude depends on the column; the row of magnitudes sits in LDS
-                TE mg[VE];
-                if (magrow) {
-                    const V mv = ((const V*)magrow)[ok ? threadIdx.x + c * kPsThreads : 0];
-                    if constexpr (VE == 4) mg[0] = mv.x, mg[1] = mv.y, mg[2] = mv.z, mg[3] = mv.w;
-                    else mg[0] = mv.x, mg[1] = mv.y;
-                } else {
+            for (int e = 0; e < VE; ++e) mg[e] = ck;
+            if (n3) {
+                // real last mode: the magnitude depends on the column (column mod n3 by a float product, exact below 2^20)
+                int col = (tid + c * kPsThreads) * VE;
+                asm volatile("" : "+v"(col));  // (not kept from one batch to the next)
+                const int m0 = col - (int)(((float)col + 0.5f) * rn3) * n3;
 #pragma unroll
-                    for (int e = 0; e < VE; ++e) mg[e] = ck;
-                }
+                for (int e = 0; e < VE; ++e) mg[e] = (TE)sh.mag[m0 + e];
+            }
+#pragma unroll
+            for (int r = 0; r < RB; ++r) {
+                const uint32_t sold = (t.rowsign >> r) & 1u;
+                const bool ok = full || (rb + r < rows && tid + c * kPsThreads < nch);
 #pragma unroll
                 for (int e = 0; e < VE; ++e) {
-                    const TE mag = mg[e];
-                    const TE d = t.x[r][c * VE + e] - ps_flip(mag, sold ^ (uint32_t)((updb >> (c * VE + e)) & 1ull));
+                    const TE d = t.x[r][c * VE + e] - ps_flip(mg[e], sold ^ (uint32_t)((updb >> (c * VE + e)) & 1ull));
                     t.x[r][c * VE + e] = ok ? d : (TE)0;  // padding stays zero
                 }
                 V v;
                 if constexpr (VE == 4) v = V{t.x[r][c * 4], t.x[r][c * 4 + 1], t.x[r][c * 4 + 2], t.x[r][c * 4 + 3]};
                 else v = V{t.x[r][c * 2], t.x[r][c * 2 + 1]};
-                if (ok) rowp[threadIdx.x + c * kPsThreads] = v;
+                if (base && ok) ((V*)(base + (int64_t)(rb + r) * cols))[tid + c * kPsThreads] = v;
             }
         }
     }
@@ -349,39 +404,45 @@ __device__ __forceinline__ void ps_process(PsTile<TE, CPT, RB>& t, TE* base, int
     if (lane < RB && wv == 0 && (full || rb + lane < rows)) s_new[rb + lane] = (uint8_t)((negs >> (8 * lane)) & 1ull);
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
-        const TE sg = ((negs >> (8 * r)) & 1ull) ? (TE)-1 : (TE)1;
+        const TE sg = !full && rb + r >= rows ? (TE)0 : ((negs >> (8 * r)) & 1ull) ? (TE)-1 : (TE)1;
 #pragma unroll
         for (int e = 0; e < NE; ++e) acc[e] = ps_fma(t.x[r][e], sg, acc[e]);
     }
 }
 
-// One pass over the block: the nl rows kept in LDS, then the ng rows streamed from memory (`first` already
+// One pass over the block: the nk rows kept in registers, the nl rows kept in LDS, then the ng rows streamed from memory (`first` already
 // holds their first batch, loaded while the previous exchange was waiting).  s_old / s_new: sign bytes of the
 // block's rows before and after this pass.
-template <typename TE, int CPT, int RB>
-__device__ __forceinline__ void ps_pass(int mode, TE* lds_rows, int nl, TE* grows, const TE* gsafe, int ng,
+template <typename TE, int CPT, int RB, int KR>
+__device__ __forceinline__ void ps_pass(int tid, int mode, PsTile<TE, CPT, KR ? KR : 1>& keep, int nk, TE* lds_rows, int nl, TE* grows, int ng,
                                         PsTile<TE, CPT, RB>& first,
-                                        int64_t cols, uint64_t sumb, uint64_t updb, TE ck, const TE* magrow, TE* acc, double& fsq,
+                                        int64_t cols, uint64_t sumb, uint64_t updb, TE ck, int n3, TE* acc, double& fsq,
                                         const uint8_t* s_old, uint8_t* s_new, PsShared& sh)
 {
-    static_assert(RB <= 8, "ps_rowsigns packs at most 8 rows");
+    static_assert(RB <= 8 && KR <= 8, "ps_rowsigns packs at most 8 rows");
     constexpr int VE = PsVec<TE>::N;
     constexpr int NE = CPT * VE;
     const int64_t nch = cols / VE;
     const bool full_cols = nch == (int64_t)CPT * kPsThreads;
     int parity = 0;
-    TE sf[NE];  // the signs of this thread's columns as factors +-1.0
+    TE sf[NE];  // the signs of this thread's columns as factors +-1.0, zero past the end
 #pragma unroll
-    for (int e = 0; e < NE; ++e) sf[e] = ((sumb >> e) & 1ull) ? (TE)-1 : (TE)1;
+    for (int e = 0; e < NE; ++e) sf[e] = tid + e / VE * kPsThreads >= nch ? (TE)0 : ((sumb >> e) & 1ull) ? (TE)-1 : (TE)1;
+    if constexpr (KR > 0) {
+        if (mode == 1) keep.rowsign = ps_rowsigns(s_old, 0, nk);
+        ps_process<TE, CPT, KR>(tid, keep, (TE*)nullptr, cols, 0, nk, nch, mode, full_cols && nk == KR, sf, updb, ck, n3, acc, fsq, s_new, sh, parity);
+        parity ^= 1;
+        s_old += nk;
+        s_new += nk;
+    }
     PsTile<TE, CPT, RB> tb;
     const int nb = (ng + RB - 1) / RB;
-    (void)gsafe;
     // (the rows kept in LDS go through the second tile: it is free until the streamed rows start)
 #pragma nounroll
     for (int rb = 0; rb < nl; rb += RB) {
-        ps_tile_load<TE, CPT, RB>(tb, lds_rows, cols, rb, nl, nch, true);
+        ps_tile_load<TE, CPT, RB>(tid, tb, lds_rows, cols, rb, nl, nch, true);
         if (mode == 1) tb.rowsign = ps_rowsigns(s_old, rb, nl);
-        ps_process<TE, CPT, RB>(tb, lds_rows, cols, rb, nl, nch, mode, full_cols && rb + RB <= nl, sf, updb, ck, magrow, acc, fsq, s_new,
+        ps_process<TE, CPT, RB>(tid, tb, lds_rows, cols, rb, nl, nch, mode, full_cols && rb + RB <= nl, sf, updb, ck, n3, acc, fsq, s_new,
                                 sh, parity);
         parity ^= 1;
     }
@@ -390,14 +451,14 @@ __device__ __forceinline__ void ps_pass(int mode, TE* lds_rows, int nl, TE* grow
 #pragma nounroll
     for (int b = 0; b < nb; b += 2) {
         const int rb = b * RB;
-        ps_tile_load<TE, CPT, RB>(tb, grows, cols, rb + RB, ng, nch, b + 1 < nb);
+        ps_tile_load<TE, CPT, RB>(tid, tb, grows, cols, rb + RB, ng, nch, b + 1 < nb);
         if (mode == 1) first.rowsign = ps_rowsigns(s_old + nl, rb, ng);
-        ps_process<TE, CPT, RB>(first, grows, cols, rb, ng, nch, mode, full_cols && rb + RB <= ng, sf, updb, ck, magrow, acc, fsq,
+        ps_process<TE, CPT, RB>(tid, first, grows, cols, rb, ng, nch, mode, full_cols && rb + RB <= ng, sf, updb, ck, n3, acc, fsq,
                                 s_new + nl, sh, parity);
         if (b + 1 < nb) {
-            ps_tile_load<TE, CPT, RB>(first, grows, cols, rb + 2 * RB, ng, nch, b + 2 < nb);
+            ps_tile_load<TE, CPT, RB>(tid, first, grows, cols, rb + 2 * RB, ng, nch, b + 2 < nb);
             if (mode == 1) tb.rowsign = ps_rowsigns(s_old + nl, rb + RB, ng);
-            ps_process<TE, CPT, RB>(tb, grows, cols, rb + RB, ng, nch, mode, full_cols && rb + 2 * RB <= ng, sf, updb, ck, magrow, acc,
+            ps_process<TE, CPT, RB>(tid, tb, grows, cols, rb + RB, ng, nch, mode, full_cols && rb + 2 * RB <= ng, sf, updb, ck, n3, acc,
                                     fsq, s_new + nl, sh, parity ^ 1);
         }
     }
@@ -474,31 +535,30 @@ __device__ __forceinline__ void ps_kron_bits(uint64_t* out, int64_t n, int n3, c
 }
 
 // SC: real last mode (a template parameter: the all-signs kernels then carry none of its code).
-template <typename TE, int CPT, int RB, bool SC>
+// KR: rows of a workgroup's block that stay in registers.
+template <typename TE, int CPT, int RB, int KR, bool SC>
 __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
 {
     constexpr int VE = PsVec<TE>::N;
     constexpr int NE = CPT * VE;
-    constexpr int WPE = PsVec<TE>::WPE;
     typedef typename PsVec<TE>::type V;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int g = blockIdx.x, G = a.grid;
     const int64_t n = a.n, nch = n / VE;
     const int r0 = g * a.rpw;
     const int nrows = (int)((int64_t)r0 + a.rpw <= a.m ? a.rpw : a.m - r0);  // >= 1 for every workgroup of the grid
-    const int nl = nrows < a.lds_rows ? nrows : a.lds_rows;                 // rows kept in LDS
-    const int ng = nrows - nl;                                              // rows streamed every alternation
+    const int nk = nrows < KR ? nrows : KR;                                 // rows kept in registers
+    const int nl = ps_lds_rows(nrows - nk, a.lds_rows, RB);                 // rows kept in LDS
+    const int ng = nrows - nk - nl;                                         // rows streamed every alternation
     const int nw = a.nw;
     const bool tensor = a.n3 > 0;               // order 3: the columns are (mode 1) x (mode 2), n = n2 * n3
     const int n3 = a.n3, w2 = a.w2;             // w2: words of a mode-1 sign vector (n2 bits)
 
     extern __shared__ __align__(16) unsigned char ps_lds[];
-    // layout: [rows kept in LDS][one row of partial sums][column signs t][t_0 of the coming term][sign bytes x 2]
+    // layout: [rows kept in LDS][column signs t][t_0 of the coming term][sign bytes x 2]
     //         [order 3: s^(2) and its random start][fixed part]
     TE* lds_rows = (TE*)ps_lds;
     size_t off = (((size_t)a.lds_rows * (size_t)n * sizeof(TE)) + 15) & ~(size_t)15;
-    TE* pub = (TE*)(ps_lds + off);
-    off += (((size_t)n * sizeof(TE)) + 15) & ~(size_t)15;
     uint64_t* t_cur = (uint64_t*)(ps_lds + off);
     off += (size_t)nw * 8;
     uint64_t* t_rng = (uint64_t*)(ps_lds + off);
@@ -510,17 +570,21 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
     uint8_t* sbuf1 = ps_lds + off;
     off += ((size_t)a.rpw + 15) & ~(size_t)15;
     PsShared& sh = *(PsShared*)(ps_lds + off);
+    // (wide slices: behind everything)
+    double* const part = a.cs > kPsMaxSlice / 2 ? (double*)(ps_lds + ((off + sizeof(PsShared) + 15) & ~(size_t)15)) : sh.part;
 
-    TE* const grows = (TE*)a.R + ((int64_t)r0 + nl) * n;  // first streamed row (only dereferenced when ng > 0)
+    TE* const grows = (TE*)a.R + ((int64_t)r0 + nk + nl) * n;  // first streamed row (only dereferenced when ng > 0)
     TE* const gfirst = ng > 0 ? grows : (TE*)a.R + (int64_t)r0 * n;
 
     // ---- the block's first rows into LDS (read from memory once per launch)
     {
-        const V* src = (const V*)((const TE*)a.R + (int64_t)r0 * n);
+        const V* src = (const V*)((const TE*)a.R + ((int64_t)r0 + nk) * n);
         V* dst = (V*)lds_rows;
         const int64_t tot = (int64_t)nl * nch;
         for (int64_t i = tid; i < tot; i += kPsThreads) dst[i] = src[i];
     }
+    PsTile<TE, CPT, KR ? KR : 1> keep;
+    if constexpr (KR > 0) ps_tile_load<TE, CPT, KR>(tid, keep, (const TE*)a.R + (int64_t)r0 * n, n, 0, nk, nch, true);
     // the random start of the first term (Algorithm 4 line 2; Algorithm 12 line 1 for the modes after the first)
     uint64_t s3_cur = 0;  // order 3: the signs of the last mode (at most 64), the same in every thread
     if (tensor) {
@@ -539,17 +603,19 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
     const int cs = a.cs;
     const int64_t c0 = (int64_t)g * cs;
     const int ncol = (int)(c0 >= n ? 0 : (n - c0 < cs ? n - c0 : cs));
-    const int Q = kPsThreads / cs;                // member groups of the hop-1 reduction (cs <= 256)
+    int ncp = 2;                                  // lanes across a slice: a power of two, 16 bytes each
+    while (ncp * VE < cs) ncp <<= 1;
+    const int Q = kPsThreads / ncp;               // member groups of the hop-1 reduction
     const int unit = tensor ? n3 : 1;             // columns per sign bit that a slice publishes
     const int sbits = cs / unit;                  // sign bits of a slice (a multiple of 8)
     const int tw = (sbits + 31) / 32;             // sign words of a slice
     const int sbytes = sbits >> 3;
-    const int nsc = tensor ? 2 * n3 : 2;          // words of scalars per slot: c (or the n3 mode sums) as halves
-    const size_t slot1 = (size_t)n * WPE;         // words of a hop-1 slot
+    const int nsc = tensor ? n3 : 1;              // scalars per slot: c or the n3 mode sums
+    const uint32_t slot1 = (uint32_t)n * (uint32_t)sizeof(TE);  // bytes of a hop-1 slot (a row of 64 KB at most)
+    const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(a.xp, 0, (int)(2u * (uint32_t)G * slot1), 0x00027000);
     const int nr2 = tensor ? ncol / n3 : 0;       // order 3: rows of W_1 in the own slice
     // Quotients by these are products with a reciprocal: (x + 0.5) / d is at least 0.5 / d away from an integer, and
     // x < 4096, d <= 512 here, so that the two roundings cannot reach one.
-    const float rcs = 1.0f / (float)cs;
     const float rper[2] = {1.0f / (float)(tw + nsc), 1.0f / (float)(tw + nsc + 2)};  // hop-2 words of a member
 
     int64_t k = a.k_start;
@@ -560,10 +626,10 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
     double c_prev = -INFINITY;
     TE ck = (TE)0;
     const double total = (double)a.m * (double)a.n;
-    uint64_t bcur = 0, brng = ps_gather_bits<TE, CPT>(t_rng, nch);
+    uint64_t bcur = 0, brng = ps_gather_bits<TE, CPT>(tid, t_rng, nch);
 
     PsTile<TE, CPT, RB> first;
-    ps_tile_load<TE, CPT, RB>(first, gfirst, n, 0, ng > 0 ? ng : 1, nch, ng > 0);
+    ps_tile_load<TE, CPT, RB>(tid, first, gfirst, n, 0, ng > 0 ? ng : 1, nch, ng > 0);
     if (tid == 0) {
         sh.fail = 0;
         for (int i = 0; i < 6; ++i) sh.ticks[i] = 0;
@@ -571,6 +637,10 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
     }
 
     for (;;) {
+        // What follows from the thread's number is worked out anew: the compiler would do it once per launch and keep it in
+        // registers, 55 of them, which long rows need for their tiles (they went through scratch).
+        if constexpr (CPT > 2) asm volatile("" : "+v"(tid));
+        lane = tid & 63, wv = tid >> 6;
         // ================= the pass over the block
         TE acc[NE];
 #pragma unroll
@@ -578,64 +648,72 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
         double fsq = 0.0;
         uint8_t* s_old = sp ? sbuf1 : sbuf0;
         uint8_t* s_new = sp ? sbuf0 : sbuf1;
-        ps_pass<TE, CPT, RB>(mode, lds_rows, nl, grows, gfirst, ng, first, n, mode == 0 ? bcur : brng, bcur, ck, SC ? pub : (TE*)nullptr, acc, fsq,
-                             s_old, s_new, sh);
+        ps_pass<TE, CPT, RB, KR>(tid, mode, keep, nk, lds_rows, nl, grows, ng, first, n, mode == 0 ? bcur : brng, bcur, ck, SC ? n3 : 0, acc, fsq,
+                                 s_old, s_new, sh);
+        if constexpr (CPT > 2) asm volatile("" : "+v"(tid));
+        lane = tid & 63, wv = tid >> 6;
         sp ^= 1;  // s_new is the current s
         PS_TICK(0);
         ++alternations;
         ++seq;
         const bool with_norm = mode != 0;
 
-        // ================= hop 1: publish the partial column sums, reduce the own slice
-        // (through LDS, so that every store instruction writes 512 consecutive tagged words: the 16-byte chunks
-        // of a thread are 2 KB apart, and partial-line stores to the fabric are what costs)
+        // ================= hop 1: publish the partial column sums, reduce the own slice.  A thread's chunk of columns is 16 bytes
+        // of words: every store instruction of a wave writes 1 KB
+        {
+            const uint32_t soff = ((seq & 1u) * (uint32_t)G + (uint32_t)g) * slot1, tag = ps_tag(seq);
 #pragma unroll
-        for (int c = 0; c < CPT; ++c) {
-            const int64_t ch = tid + c * kPsThreads;
-            if (ch < nch) {
-                V v;
-                if constexpr (VE == 4) v = V{acc[c * 4], acc[c * 4 + 1], acc[c * 4 + 2], acc[c * 4 + 3]};
-                else v = V{acc[c * 2], acc[c * 2 + 1]};
-                ((V*)pub)[ch] = v;
+            for (int c = 0; c < CPT; ++c) {
+                const int64_t ch = tid + c * kPsThreads;
+                if (ch < nch) ps_publish16(xrs, (uint32_t)ch * 16u, soff, acc + c * VE, a.xexp, tag);
             }
         }
         if (with_norm) {
             fsq = ps_wave_sum(fsq);
             if (lane == 0) sh.red[1][wv] = fsq;
         }
-        __syncthreads();
-        {
-            uint64_t* mine = a.xp + ((size_t)(seq & 1u) * G + g) * slot1;
-#pragma nounroll
-            for (int64_t col = tid; col < n; col += kPsThreads) {
-                if constexpr (WPE == 1) {
-                    ps_store_tagged(mine + col, __float_as_uint((float)pub[col]), seq);
-                } else {
-                    const uint64_t b = (uint64_t)__double_as_longlong((double)pub[col]);
-                    ps_store_tagged(mine + col, (uint32_t)b, seq);
-                    ps_store_tagged(mine + n + col, (uint32_t)(b >> 32), seq);
-                }
-            }
-        }
         // the first streamed batch of the next pass does not depend on the exchange: its loads fly meanwhile
-        ps_tile_load<TE, CPT, RB>(first, gfirst, n, 0, ng > 0 ? ng : 1, nch, ng > 0);
+        ps_tile_load<TE, CPT, RB>(tid, first, gfirst, n, 0, ng > 0 ? ng : 1, nch, ng > 0);
         PS_TICK(1);
-        for (int d = 0; d < a.poll_delay; ++d) __builtin_amdgcn_s_sleep(1);
+        for (int d = 0; d < a.poll_delay * 5 / 8; ++d) __builtin_amdgcn_s_sleep(1);
         bool ok = true;
         double vj = 0.0;
+        const int stride = ncp * VE;  // of the member groups' sums in LDS
         {
-            const int q = (int)(((float)tid + 0.5f) * rcs), jc = tid - q * cs;
-            double s = 0.0;
-            if (q < Q && jc < ncol) {
-                const uint64_t* basep = a.xp + ((size_t)(seq & 1u) * G) * slot1 + (size_t)(c0 + jc);
+            const int jc = tid & (ncp - 1), q = tid / ncp;
+            double x[VE];
+#pragma unroll
+            for (int e = 0; e < VE; ++e) x[e] = 0.0;
+            if (jc * VE < ncol) {
+                const uint32_t voff = (uint32_t)c0 * (uint32_t)sizeof(TE) + (uint32_t)jc * 16u, soff = (seq & 1u) * (uint32_t)G * slot1;
                 int spin = 0;
-                // members q, q + Q, ... in that order; 16 in flight when a thread has more than 8 of them (one-word
-                // values only: 32 words in flight would not fit the registers)
-                if (WPE == 1 && G > 8 * Q) ok = ps_hop1_gather<WPE, WPE == 1 ? 16 : 8>(basep, q, Q, G, slot1, n, seq, a.max_spin, s, spin);
-                else ok = ps_hop1_gather<WPE, 8>(basep, q, Q, G, slot1, n, seq, a.max_spin, s, spin);
+                // members q, q + Q, ... in that order
+                if (G > 4 * Q) ok = ps_hop1_gather<TE, CPT >= 8 ? 2 : 8>(xrs, voff, soff, q, Q, G, slot1, ps_tag(seq), a.max_spin, x, spin);
+                else ok = ps_hop1_gather<TE, CPT >= 8 ? 2 : 4>(xrs, voff, soff, q, Q, G, slot1, ps_tag(seq), a.max_spin, x, spin);
                 spins += spin;
             }
-            sh.part[tid] = s;
+            // the groups of a wave are joined first, the registers halving where two distances are left
+            double* mine = part + (ncp <= 64 ? wv : q) * stride + jc * VE;
+            if (ncp <= 16) {
+                double v;
+                if constexpr (VE == 4) v = ps_half32(ps_half16(x[0], x[1]), ps_half16(x[2], x[3]));
+                else v = ps_swap_sum_f64<32>(ps_half16(x[0], x[1]));
+                if (ncp <= 8) v += ps_dpp_f64<0x140, 0x141>(v);  // lane ^ 8
+                if (ncp <= 4) v += ps_dpp_f64<0x141, 0x1B>(v);   // lane ^ 4
+                if (ncp <= 2) v += ps_dpp_f64<0x4E, 0>(v);       // lane ^ 2
+                if ((lane & 15) < ncp && (lane >> 4) < VE) mine[lane >> 4] = v;
+            } else if (ncp == 32) {
+                const int up = lane >> 5;
+                if constexpr (VE == 4) {
+                    mine[2 * up] = ps_half32(x[0], x[2]);
+                    mine[2 * up + 1] = ps_half32(x[1], x[3]);
+                } else {
+                    mine[up] = ps_half32(x[0], x[1]);
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < VE; ++e) mine[e] = x[e];
+            }
             if (tid < 8) sh.tw32[tid] = 0;
         }
         if (!ok) sh.fail = 1;
@@ -645,30 +723,29 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
             return;
         }
         PS_TICK(2);
-        // v at the own columns: L neighbouring lanes share a column, each adds every L-th member group in order,
-        // a butterfly joins them
+        // v at the own columns, a thread each: the groups' sums in order
         {
-            const int lsh = cs <= 64 ? 3 : (cs <= 128 ? 2 : 1), L = 1 << lsh;
-            const int jc = tid >> lsh, ql = tid & (L - 1);
-            double pq[8];
+            const bool mine = tid < ncol;
+            if (wv * 64 < ncol) {
+                const int groups = ncp <= 64 ? kPsWaves : Q;
+                double pq[kPsWaves];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int q = ql + i * L;
-                pq[i] = (jc < ncol && q < Q) ? sh.part[q * cs + jc] : 0.0;
+                for (int i = 0; i < kPsWaves; ++i) pq[i] = mine && i < groups ? part[i * stride + tid] : 0.0;
+#pragma unroll
+                for (int i = 0; i < kPsWaves; ++i) vj += pq[i];
+                vj = __builtin_ldexp(vj, a.xexp);
             }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) vj += pq[i];
-            vj += ps_dpp_f64<0xB1, 0>(vj);                    // lane ^ 1
-            if (L >= 4) vj += ps_dpp_f64<0x4E, 0>(vj);        // lane ^ 2
-            if (L >= 8) vj += ps_dpp_f64<0x141, 0x1B>(vj);    // lane ^ 4
-            const bool mine = jc < ncol && ql == 0;
             if (!tensor) {
                 // t_l = sgn(v_l), share of c = sum |v_l| (Algorithm 4 lines 6-7)
-                if (mine && vj < 0.0) atomicOr(&sh.tw32[jc >> 5], 1u << (jc & 31));
+                const uint64_t neg = __ballot(mine && vj < 0.0);
+                if (lane == 0 && wv * 64 < cs) {
+                    sh.tw32[2 * wv] = (uint32_t)neg;
+                    sh.tw32[2 * wv + 1] = (uint32_t)(neg >> 32);
+                }
                 const double ca = ps_wave_sum(mine ? fabs(vj) : 0.0);
                 if (lane == 0) sh.red[0][wv] = ca;
             } else if (mine) {
-                sh.v[jc] = vj;  // the slice of W_1 = a x_1 s^(1): whole rows of the n2 x n3 array
+                sh.v[tid] = vj;  // the slice of W_1 = a x_1 s^(1): whole rows of the n2 x n3 array
             }
         }
         __syncthreads();
@@ -699,9 +776,14 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
         }
         PS_TICK(3);
         // ================= hop 2: publish the slice's sign bits and scalars, gather everybody's
+        const uint32_t tag = ps_tag(seq);
         {
             uint64_t* mine = a.xq + ((size_t)(seq & 1u) * G + g) * kPsSlot2;
             if (tid < tw) ps_store_tagged(mine + tid, sh.tw32[tid], seq);
+            auto scalar = [&](uint64_t* p, double x) {
+                x = __builtin_ldexp(x, -a.cexp);
+                ps_store_tagged(p, (uint32_t)__double2loint(x), ((uint32_t)__double2hiint(x) & ~kPsTag) | tag);
+            };
             if (!tensor) {
                 if (tid == 64) {
                     double cq[kPsWaves], cshare = 0.0;
@@ -709,14 +791,10 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
                     for (int q = 0; q < kPsWaves; ++q) cq[q] = sh.red[0][q];
 #pragma unroll
                     for (int q = 0; q < kPsWaves; ++q) cshare += cq[q];
-                    const uint64_t b = (uint64_t)__double_as_longlong(cshare);
-                    ps_store_tagged(mine + tw, (uint32_t)b, seq);
-                    ps_store_tagged(mine + tw + 1, (uint32_t)(b >> 32), seq);
+                    scalar(mine + tw, cshare);
                 }
             } else if (tid >= 64 && tid < 64 + n3) {
-                const uint64_t b = (uint64_t)__double_as_longlong(sh.w2part[tid - 64]);
-                ps_store_tagged(mine + tw + 2 * (tid - 64), (uint32_t)b, seq);
-                ps_store_tagged(mine + tw + 2 * (tid - 64) + 1, (uint32_t)(b >> 32), seq);
+                scalar(mine + tw + tid - 64, sh.w2part[tid - 64]);
             }
             if (with_norm && tid == 128) {
                 double f = 0.0;
@@ -732,26 +810,30 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
             const float rp = rper[with_norm ? 1 : 0];
             const int items = G * per;
             int where[kPsMaxItems2];  // member * kPsSlot2 + word, or -1
+            uint32_t want[kPsMaxItems2], bits[kPsMaxItems2];  // bits of the upper half that tell a fresh word, what they are
 #pragma unroll
             for (int it = 0; it < kPsMaxItems2; ++it) {
                 const int idx = tid + it * kPsThreads;
                 const int mem = (int)(((float)idx + 0.5f) * rp), wd = idx - mem * per;
+                const bool sum = wd >= tw && wd < tw + nsc;
                 where[it] = idx < items ? mem * kPsSlot2 + wd : -1;
+                bits[it] = sum ? kPsTag : ~0u;
+                want[it] = sum ? tag : seq;
             }
-            for (int d = 0; d < a.poll_delay; ++d) __builtin_amdgcn_s_sleep(1);
+            for (int d = 0; d < a.poll_delay / 4; ++d) __builtin_amdgcn_s_sleep(1);
             const uint64_t* xb = a.xq + (size_t)(seq & 1u) * G * kPsSlot2;
             uint64_t w[kPsMaxItems2];
 #pragma unroll
-            for (int it = 0; it < kPsMaxItems2; ++it) w[it] = (uint64_t)(where[it] >= 0 ? ~seq : seq) << 32;
+            for (int it = 0; it < kPsMaxItems2; ++it) w[it] = (uint64_t)(where[it] >= 0 ? ~want[it] : want[it]) << 32;
             int spin = 0;
             for (;;) {
-                bool fresh = true;
+                uint32_t stale = 0u;
 #pragma unroll
                 for (int it = 0; it < kPsMaxItems2; ++it)
-                    if ((uint32_t)(w[it] >> 32) != seq) w[it] = ps_load(xb + where[it]);
+                    if (((uint32_t)(w[it] >> 32) ^ want[it]) & bits[it]) w[it] = ps_load(xb + where[it]);
 #pragma unroll
-                for (int it = 0; it < kPsMaxItems2; ++it) fresh = fresh && ((uint32_t)(w[it] >> 32) == seq);
-                if (fresh) break;
+                for (int it = 0; it < kPsMaxItems2; ++it) stale |= ((uint32_t)(w[it] >> 32) ^ want[it]) & bits[it];
+                if (!stale) break;
                 if (++spin > a.max_spin) {
                     ok = false;
                     break;
@@ -773,8 +855,11 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
 #pragma unroll
                             for (int b = 0; b < 4; ++b)
                                 if (4 * wd + b < sbytes && b0 + b < nbytes) tbytes[b0 + b] = (uint8_t)(v >> (8 * b));
+                        } else if (wd < tw + nsc) {
+                            sh.scal[2 * (wd - tw)][mem] = v;
+                            sh.scal[2 * (wd - tw) + 1][mem] = (uint32_t)(w[it] >> 32) & ~kPsTag;
                         } else {
-                            sh.scal[wd - tw][mem] = v;
+                            sh.scal[nsc + wd - tw][mem] = v;
                         }
                     }
                 }
@@ -790,18 +875,17 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
         // the scalars: sums of the members' shares, the same order in every workgroup
         double c_tot = 0.0, f_tot = 0.0;
         double wl[kPsMaxLast] = {0.0, 0.0, 0.0, 0.0};  // order 3: the last mode's sums W_2[c] of this sweep
-        auto share = [&](int slot) {
-            return tid < G ? __longlong_as_double((long long)(((uint64_t)sh.scal[2 * slot + 1][tid] << 32) | sh.scal[2 * slot][tid]))
-                           : 0.0;
+        auto share = [&](int slot, int e) {
+            return tid < G ? __builtin_ldexp(__hiloint2double((int)sh.scal[2 * slot + 1][tid], (int)sh.scal[2 * slot][tid]), e) : 0.0;
         };
         if (!tensor) {
-            c_tot = ps_sum_members(share(0), sh, 0);
+            c_tot = ps_sum_members(share(0, a.cexp), sh, 0);
         } else {
             // last mode: s^(3)_c = sgn(W_2[c]); the cut value is <s, a> = sum_c |W_2[c]| (Algorithm 12 line 10)
             uint64_t s3n = 0;
             double sv[kPsMaxLast];
 #pragma unroll
-            for (int c = 0; c < kPsMaxLast; ++c) sv[c] = c < n3 ? share(c) : 0.0;
+            for (int c = 0; c < kPsMaxLast; ++c) sv[c] = c < n3 ? share(c, a.cexp) : 0.0;
             ps_sum_members_n(sv, n3, sh, wl);
 #pragma unroll
             for (int c = 0; c < kPsMaxLast; ++c) {
@@ -813,12 +897,12 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
             s3_cur = s3n;
             ps_kron_bits(t_cur, n, n3, s2_cur, a.n2, s3_cur);
         }
-        if (with_norm) f_tot = ps_sum_members(share(nsc / 2), sh, 1);
+        if (with_norm) f_tot = ps_sum_members(share(nsc, 0), sh, 1);
         if (with_norm && g == 0 && tid == 0) a.trace[k] = sqrt(f_tot);
         if (final_pass) break;
         ++j;
         if (tensor) __syncthreads();  // t_cur was just rebuilt (a matrix: before the barrier of hop 2)
-        bcur = ps_gather_bits<TE, CPT>(t_cur, nch);  // this thread's bits of t_j: row sums of the next pass, or the update
+        bcur = ps_gather_bits<TE, CPT>(tid, t_cur, nch);  // this thread's bits of t_j: row sums of the next pass, or the update
         const bool conv = (c_tot <= c_prev) || (j >= a.max_iters);  // Algorithm 4 line 8 / Algorithm 12 line 11
         if (conv) {
             // the term is complete: append it (Algorithm 5 lines 7-9); the next pass subtracts it (line 10)
@@ -829,18 +913,16 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
                 // real last mode: the coefficient of slice c is <s (x) t, r[..., c]> / (n_1 n_2) = W_2[c] / (n_1 n_2), the
                 // least squares coefficient for these sign vectors; its sign is s^(3)_c, so the update of the next
                 // pass subtracts its magnitude with the signs of the all-signs term.  Stored rounded; what is stored
-                // is what is subtracted.  The magnitudes go, column by column, into the LDS row that holds the partial
-                // sums during an exchange (it is free during a pass).
+                // is what is subtracted.
                 TE coef[kPsMaxLast];
 #pragma unroll
                 for (int c = 0; c < kPsMaxLast; ++c) coef[c] = (TE)(wl[c] / (total / (double)n3));
-                const float rn3 = 1.0f / (float)n3;
-                for (int64_t col = tid; col < n; col += kPsThreads) {
-                    const int cc = (int)col - (int)(((float)col + 0.5f) * rn3) * n3;  // col mod n3 (exact below 2^20)
+                if (tid < 2 * kPsMaxLast) {
+                    const int cc = tid % n3;
                     TE v = coef[0];
 #pragma unroll
                     for (int c = 1; c < kPsMaxLast; ++c) v = cc == c ? coef[c] : v;
-                    pub[col] = v < (TE)0 ? -v : v;
+                    sh.mag[tid] = (double)(v < (TE)0 ? -v : v);
                 }
                 if (g == 0 && tid < n3) {
                     TE v = coef[0];
@@ -893,7 +975,7 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
                 for (int p = tid; p < nw; p += kPsThreads) t_rng[p] = rng_word_masked(a.seed, (uint64_t)k, 1u, p, n);
             }
             __syncthreads();
-            brng = ps_gather_bits<TE, CPT>(t_rng, nch);
+            brng = ps_gather_bits<TE, CPT>(tid, t_rng, nch);
         } else {
             c_prev = c_tot;
             mode = 0;
@@ -903,10 +985,22 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
         PS_TICK(5);
     }
 
-    // ---- the rows kept in LDS go back to memory
+    // ---- the rows kept in registers and in LDS go back to memory
     __syncthreads();
+    if constexpr (KR > 0) {
+#pragma unroll
+        for (int r = 0; r < KR; ++r)
+#pragma unroll
+            for (int c = 0; c < CPT; ++c) {
+                const int64_t ch = tid + c * kPsThreads;
+                V v;
+                if constexpr (VE == 4) v = V{keep.x[r][c * 4], keep.x[r][c * 4 + 1], keep.x[r][c * 4 + 2], keep.x[r][c * 4 + 3]};
+                else v = V{keep.x[r][c * 2], keep.x[r][c * 2 + 1]};
+                if (r < nk && ch < nch) ((V*)((TE*)a.R + ((int64_t)r0 + r) * n))[ch] = v;
+            }
+    }
     {
-        V* dst = (V*)((TE*)a.R + (int64_t)r0 * n);
+        V* dst = (V*)((TE*)a.R + ((int64_t)r0 + nk) * n);
         const V* src = (const V*)lds_rows;
         const int64_t tot = (int64_t)nl * nch;
         for (int64_t i = tid; i < tot; i += kPsThreads) dst[i] = src[i];
@@ -922,10 +1016,10 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
     }
 }
 
-template <typename TE, int CPT, int RB, bool SC>
+template <typename TE, int CPT, int RB, int KR, bool SC>
 hipError_t ps_launch_k(const PStreamArgs& a, size_t lds_bytes, hipStream_t st)
 {
-    auto kern = pstream_kernel<TE, CPT, RB, SC>;
+    auto kern = pstream_kernel<TE, CPT, RB, KR, SC>;
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
     if (e != hipSuccess) return e;
     // every workgroup of the grid must be resident at once: one per compute unit is enough
@@ -948,8 +1042,19 @@ hipError_t ps_launch_rb(const PStreamArgs& a, size_t lds_bytes, hipStream_t st)
     // values to odd register pairs, which this compiler then rejects)
     constexpr int kRegsPerRow = CPT * VE * (int)sizeof(TE) / 4;
     constexpr int RB = kRegsPerRow > 16 ? 1 : (kRegsPerRow > 8 ? 2 : (kRegsPerRow > 4 ? 4 : 8));
-    if (a.scalars && a.n3 > 0) return ps_launch_k<TE, CPT, RB, true>(a, lds_bytes, st);
-    return ps_launch_k<TE, CPT, RB, false>(a, lds_bytes, st);
+    // Rows in registers: as many as leave the kernel without scratch, where they save a row of the stream (f32 4000x3000x3
+    // 33.1 -> 32.1 us per pass, 5000x2048 14.2 -> 10.8, 3500x1301x4 21.4 -> 20.2) and no batch more.
+    constexpr int KR = CPT == 1 ? 4 : CPT == 3 ? 2 : CPT == 5 ? 1 : 0;
+    auto batches = [&](int kept) {
+        const int nl = ps_lds_rows(a.rpw - kept, a.lds_rows, RB);
+        return (kept ? 1 : 0) + (nl + RB - 1) / RB + (a.rpw - kept - nl + RB - 1) / RB;
+    };
+    if (KR > 0 && (a.rpw <= KR || batches(KR) <= batches(0))) {
+        if (a.scalars && a.n3 > 0) return ps_launch_k<TE, CPT, RB, KR, true>(a, lds_bytes, st);
+        return ps_launch_k<TE, CPT, RB, KR, false>(a, lds_bytes, st);
+    }
+    if (a.scalars && a.n3 > 0) return ps_launch_k<TE, CPT, RB, 0, true>(a, lds_bytes, st);
+    return ps_launch_k<TE, CPT, RB, 0, false>(a, lds_bytes, st);
 }
 
 template <typename TE>
@@ -961,11 +1066,11 @@ hipError_t ps_launch(const PStreamArgs& a, size_t lds_bytes, hipStream_t st)
     switch (cpt) {
         case 1: return ps_launch_rb<TE, 1>(a, lds_bytes, st);
         case 2: return ps_launch_rb<TE, 2>(a, lds_bytes, st);
-        case 3:
+        case 3: return ps_launch_rb<TE, 3>(a, lds_bytes, st);
         case 4: return ps_launch_rb<TE, 4>(a, lds_bytes, st);
-        case 5:
+        case 5: return ps_launch_rb<TE, 5>(a, lds_bytes, st);
         case 6: return ps_launch_rb<TE, 6>(a, lds_bytes, st);
-        case 7:
+        case 7: return ps_launch_rb<TE, 7>(a, lds_bytes, st);
         case 8: return ps_launch_rb<TE, 8>(a, lds_bytes, st);
         default: return hipErrorInvalidValue;
     }
@@ -975,9 +1080,7 @@ hipError_t ps_launch(const PStreamArgs& a, size_t lds_bytes, hipStream_t st)
 int ps_cpt(int64_t nch)
 {
     const int64_t cpt = (nch + kPsThreads - 1) / kPsThreads;
-    if (cpt <= 2) return (int)cpt;
-    if (cpt <= 8) return (int)((cpt + 1) / 2 * 2);
-    return 0;
+    return cpt <= 8 ? (int)cpt : 0;
 }
 
 size_t ps_fixed_lds(int64_t n, size_t es, int64_t n2, int rpw)
@@ -1009,7 +1112,8 @@ bool pstream_supported(scd_dtype dt, int order, const int64_t* dims, int limit, 
     int64_t cs = (n + grid - 1) / grid;
     cs = (cs + unit - 1) / unit * unit;
     if (cs > kPsMaxSlice || rpw > (1 << 20)) return false;
-    const size_t fixed = ps_fixed_lds(n, es, n2, (int)rpw);
+    // (wide slices: the member groups' sums of hop 1 do not fit the space that the exchanges share)
+    const size_t fixed = ps_fixed_lds(n, es, n2, (int)rpw) + (cs > kPsMaxSlice / 2 ? (size_t)kPsWaves * kPsMaxSlice * 8 + 16 : 0);
     if (fixed > kPsMaxLds) return false;
     int64_t lds_rows = (int64_t)((kPsMaxLds - fixed) / ((size_t)n * es));
     if (lds_rows > rpw) lds_rows = rpw;
