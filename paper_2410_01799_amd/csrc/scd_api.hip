@@ -1237,14 +1237,12 @@ int scd_decompose(const void* A, scd_dtype dt, int order, const int64_t* dims, i
 
 // ---------------------------------------------------------------------------------------------- half steps
 
-static int halfstep_geometry(int64_t m, int* rows_per_wg, int* grid)
+// The most groups of rows whose f64 partial sums a column step keeps: a group has 32 rows or more, and a few hundred of them
+// fill the chip whatever the number of columns.
+static int halfstep_groups(int64_t m)
 {
-    int64_t rpw = (m + 1023) / 1024;
-    if (rpw < 1) rpw = 1;
-    if (rpw > kMaxRowsPerWg) rpw = kMaxRowsPerWg;
-    *rows_per_wg = (int)rpw;
-    *grid = (int)((m + rpw - 1) / rpw);
-    return SCD_OK;
+    const int64_t most = (m + 31) / 32;
+    return (int)(most < 256 ? most : 256);
 }
 
 int scd_row_signed_sum(const void* R, scd_dtype dt, int64_t m, int64_t n, const uint64_t* tbits, void* stream, double* u,
@@ -1281,16 +1279,19 @@ int scd_row_signed_sum(const void* R, scd_dtype dt, int64_t m, int64_t n, const 
     return SCD_OK;
 }
 
-// The three launches of a column half step on caller data: per-workgroup partial column sums, their
-// fixed-order join (v, t, partial sums of |v|), the sum of those.  `partials` holds grid * n elements of dt,
-// `cparts` ceil(n/64) doubles.
-static hipError_t enqueue_col_signed_sum(const void* R, scd_dtype dt, int64_t m, int64_t n, int rpw, int grid,
-                                         const uint64_t* sbits, void* partials, double* cparts, double* v, uint64_t* tbits,
+// The launches of a column half step on caller data: partial column sums per group of rows, their fixed-order join (v, t,
+// partial sums of |v|) with the sum of those.  `head` is 256 bytes: the cut value when the caller does not want it, then the
+// join's count of workgroups.  `partials` holds `most` * n f64 values (a single f32 row: n f32 values), `cparts` ceil(n/64) doubles.
+static hipError_t enqueue_col_signed_sum(const void* R, scd_dtype dt, int64_t m, int64_t n, int most, const uint64_t* sbits,
+                                         unsigned char* head, void* partials, double* cparts, double* v, uint64_t* tbits,
                                          double* cout, hipStream_t st)
 {
-    hipError_t e = launch_col_partials(R, dt, m, n, rpw, grid, sbits, partials, st);
-    if (e == hipSuccess) e = launch_reduce_plain(partials, dt, grid, n, v, tbits, cparts, st);
-    if (e == hipSuccess) e = launch_sum_parts(cparts, (int)words_for(n), cout, st);
+    const bool narrow = dt == SCD_F32 && m == 1;
+    unsigned* arrived = (unsigned*)(head + 128);
+    int groups;
+    hipError_t e = launch_col_partials(R, dt, m, n, most, sbits, partials, narrow, arrived, &groups, st);
+    if (e == hipSuccess)
+        e = launch_reduce_plain(partials, narrow ? SCD_F32 : SCD_F64, groups, n, v, tbits, cparts, arrived, cout ? cout : (double*)head, st);
     return e;
 }
 
@@ -1299,12 +1300,9 @@ int scd_col_signed_sum(const void* R, scd_dtype dt, int64_t m, int64_t n, const 
 {
     if (!R || !sbits || !dtype_ok(dt) || m < 1 || n < 1) return SCD_EINVAL;
     hipStream_t st = (hipStream_t)stream;
-    int rpw, grid;
-    halfstep_geometry(m, &rpw, &grid);
-    const size_t es = dt == SCD_F32 ? 4 : 8;
-    const int ncp = (int)words_for(n);
-    // one block: the cut value when the caller does not want it, the partial sums of |v|, the partial column sums
-    const size_t cparts_bytes = (((size_t)ncp * 8 + 255) / 256) * 256, bytes = 256 + cparts_bytes + (size_t)grid * (size_t)n * es;
+    const int most = halfstep_groups(m);
+    // one block: the head, the partial sums of |v|, the partial column sums
+    const size_t cparts_bytes = (((size_t)words_for(n) * 8 + 255) / 256) * 256, bytes = 256 + cparts_bytes + (size_t)most * (size_t)n * 8;
     unsigned char* base = nullptr;
     hipError_t e = pool_malloc((void**)&base, bytes, false);
     if (e != hipSuccess) {
@@ -1312,8 +1310,7 @@ int scd_col_signed_sum(const void* R, scd_dtype dt, int64_t m, int64_t n, const 
         (void)hipGetLastError();
         return SCD_ENOMEM;
     }
-    e = enqueue_col_signed_sum(R, dt, m, n, rpw, grid, sbits, base + 256 + cparts_bytes, (double*)(base + 256), v, tbits,
-                               cout ? cout : (double*)base, st);
+    e = enqueue_col_signed_sum(R, dt, m, n, most, sbits, base, base + 256 + cparts_bytes, (double*)(base + 256), v, tbits, cout, st);
     hipError_t es2 = hipStreamSynchronize(st);
     if (e == hipSuccess) e = es2;
     if (es2 != hipSuccess) settle(st);
@@ -1360,23 +1357,22 @@ int scd_col_signed_sum_noalloc(const void* R, scd_dtype dt, int64_t m, int64_t n
                                double* v, uint64_t* tbits, double* cout)
 {
     if (!R || !sbits || !dtype_ok(dt) || m < 1 || n < 1) return SCD_EINVAL;
-    int rpw, grid;
-    halfstep_geometry(m, &rpw, &grid);
     const size_t es = dt == SCD_F32 ? 4 : 8;
-    // layout: [0, 256) the cut value when the caller does not want it; then ceil(n/64) doubles of partial
-    // sums of |v|, padded to 256 bytes; then grid * n partial column sums
+    // layout: [0, 256) the head; then ceil(n/64) doubles of partial sums of |v|, padded to 256 bytes; then the partial column
+    // sums.  The limit is that of partial sums of the input's type for up to 1024 groups of rows (of at most 2048 rows): what
+    // halfstep_groups takes in f64 is never more (two rows of f32 sums and more for each group; a single row is kept in f32).
+    int64_t per = (m + 1023) / 1024;
+    if (per > kMaxRowsPerWg) per = kMaxRowsPerWg;
+    const int64_t grid = (m + per - 1) / per;
     const size_t cparts_bytes = (((size_t)words_for(n) * 8 + 255) / 256) * 256;
     const size_t need = 256 + cparts_bytes + (size_t)grid * (size_t)n * es;
     if ((double)grid * (double)n * (double)es > (double)SCD_NOALLOC_SCRATCH_BYTES || need > (size_t)SCD_NOALLOC_SCRATCH_BYTES)
         return SCD_ETOOBIG;
     unsigned char* base = nullptr;
     SCD_TRY(scratch_address(&base));
-    double* ctmp = (double*)base;
-    double* cparts = (double*)(base + 256);
-    void* partials = base + 256 + cparts_bytes;
     // every word of the work space that is read was written by this call: nothing to clear
-    HIP_TRY(enqueue_col_signed_sum(R, dt, m, n, rpw, grid, sbits, partials, cparts, v, tbits, cout ? cout : ctmp,
-                                   (hipStream_t)stream));
+    HIP_TRY(enqueue_col_signed_sum(R, dt, m, n, halfstep_groups(m), sbits, base, base + 256 + cparts_bytes, (double*)(base + 256), v,
+                                   tbits, cout, (hipStream_t)stream));
     return SCD_OK;
 }
 
@@ -1481,9 +1477,8 @@ struct ModeSums {
             if (i > 0) {
                 const int64_t wcols = d[i] * inner[i];
                 if (wcols > max_w) max_w = wcols;
-                int rpw, grid;
-                halfstep_geometry(d[i - 1], &rpw, &grid);
-                if ((int64_t)grid * wcols > max_part) max_part = (int64_t)grid * wcols;
+                const int64_t groups = halfstep_groups(d[i - 1]);
+                if (groups * wcols > max_part) max_part = groups * wcols;
             }
             if (inner[i] > max_kron) max_kron = inner[i];
         }
@@ -1511,11 +1506,10 @@ struct ModeSums {
             const void* from = i == 1 ? x : (const void*)W[(i - 1) & 1];
             const scd_dtype fdt = i == 1 ? dt : SCD_F64;
             double* to = trailing ? W[i & 1] : uA;
-            int rpw, grid;
-            halfstep_geometry(rows, &rpw, &grid);
-            err = launch_col_partials(from, fdt, rows, wcols, rpw, grid, cur[i - 1], partials, st);
+            int groups;
+            err = launch_col_partials(from, fdt, rows, wcols, halfstep_groups(rows), cur[i - 1], partials, false, nullptr, &groups, st);
             if (err != hipSuccess) return err;
-            err = launch_reduce_plain(partials, fdt, grid, wcols, to, nullptr, cparts, st);
+            err = launch_reduce_plain(partials, SCD_F64, groups, wcols, to, nullptr, cparts, nullptr, nullptr, st);
             if (err != hipSuccess) return err;
             src = to;
             sdt = SCD_F64;

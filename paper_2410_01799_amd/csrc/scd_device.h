@@ -316,11 +316,10 @@ hipError_t launch_kron_terms(int order, const int64_t* dims, const uint64_t* con
                              uint64_t* out, int64_t cols, hipStream_t st);
 hipError_t launch_row_sums(const void* R, scd_dtype dt, int64_t m, int64_t n, const uint64_t* tbits, double* u, uint64_t* sbits,
                            hipStream_t st);  // u, sbits: optional
-hipError_t launch_col_partials(const void* R, scd_dtype dt, int64_t m, int64_t n, int rows_per_wg, int grid, const uint64_t* rowbits,
-                               void* partials, hipStream_t st);
+hipError_t launch_col_partials(const void* R, scd_dtype dt, int64_t m, int64_t n, int most, const uint64_t* rowbits, void* partials,
+                               bool narrow, unsigned* arrived, int* groups, hipStream_t st);
 hipError_t launch_reduce_plain(const void* partials, scd_dtype dt, int nparts, int64_t cols, double* W, uint64_t* bits,
-                               double* cparts, hipStream_t st);
-hipError_t launch_sum_parts(const double* parts, int n, double* out, hipStream_t st);
+                               double* cparts, unsigned* arrived, double* cout, hipStream_t st);
 hipError_t launch_stream_read(const void* x, int64_t bytes, int grid, float* sink, hipStream_t st);
 hipError_t launch_stream_copy(const void* x, void* y, int64_t bytes, int grid, hipStream_t st);
 hipError_t launch_exchange_probe(int which, int grid, uint64_t* buf, unsigned* counter, int rounds, int group,

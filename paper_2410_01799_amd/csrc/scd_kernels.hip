@@ -12,6 +12,7 @@
 //             via Section 3.1: <s, R t> = ||R^T s||_1), packs s from u with 64-lane ballots.
 //  kron     : Kronecker products of sign bitsets for the tensor sweep (Algorithm 12 lines 5-7).
 //  row_sums, col_partials : the half steps on caller data.
+#include <type_traits>
 #include <stddef.h>
 
 #include "scd_device.h"
@@ -333,64 +334,89 @@ __global__ void __launch_bounds__(kBlock)
     }
 }
 
-// Column step: partials[g][l] = sum over the rows of group g (rows_per_wg of them, in order) of the entries with the
-// signs `rowbits`.  A thread takes 16-byte chunks of the columns (VEC) or single ones, RB rows in flight.  Tall matrices
-// with few columns leave most of a workgroup's threads idle and are bound by the trips of the others: eight rows a trip
-// below 1024 columns from eight rows a group on (14336x4096 73 with four, 75 with eight), and no chunks below 128 columns.  Us a call with four rows and chunks throughout, and now:
-// 1000000x4 f32 158 and 94, 200000x100 104 and 60, 100000x200 75 and 55, 1000000x2 f64 139 and 97; 16 rows in flight
-// lose from 512 columns on (50000x512 95, eight rows 57, four 61).
+// Column step: partials[g][l] = sum over the rows of group g of the entries with the signs `rowbits`, in f64 from the
+// first addition on.  A read of the matrix bounds it.  A workgroup takes a tile of columns, 2^lanes_log2 lanes wide (a lane
+// holds 16 bytes of a row, or one entry), and as many threads side by side on the rows as that leaves; a thread asks for RB
+// rows at once, whose signs are in one word.  The threads' sums are joined in the workgroup, so that a partial sum stands
+// for 32 rows and more: with whole rows per workgroup (four at 4096x4096, 1024 partial sums a column) the partial sums were
+// half as many bytes as the matrix and narrow matrices left most threads idle.  Us a call of the column step, whole rows per
+// workgroup / this: f32 4096x4096 37.8 / 34.4, 14336x8192 130 / 107, 14336x4096 60.0 / 60.3, 4095x4093 50.3 / 37.7, 1501x999
+// 31.5 / 25.0, 256x256 24.3 / 23.2, 1x100000 54.7 / 33.6, 200000x100 45.8 / 37.7, 1000000x4 79 / 28.5; f64 4096x4096 52.8 /
+// 45.0, 1000000x2 83.6 / 30.1.  The kernel takes 13.7 us at 4096x4096 (before 13.5, with f32 sums and their 16 MiB); without
+// the loads ahead of the sums, as the compiler orders them by itself, 15.8.
+constexpr int kColBlock = 512;
+constexpr int kColWaves = kColBlock / kWave;
+
 template <typename TE, bool VEC, int RB>
-__global__ void __launch_bounds__(kBlock)
-    col_partials_kernel(const TE* __restrict__ X, int64_t rows, int64_t cols, int rows_per_wg, const uint64_t* __restrict__ rowbits,
-                        TE* __restrict__ partials)
+__global__ void __launch_bounds__(kColBlock)
+    col_partials_kernel(const TE* __restrict__ X, int64_t rows, int64_t cols, int lanes_log2, int batches, const uint64_t* __restrict__ rowbits,
+                        void* partials, bool narrow, unsigned* arrived)
 {
+    static_assert(64 % RB == 0, "the signs of a batch are in one word");
     constexpr int VE = VEC ? Vec16<TE>::N : 1;
     typedef typename Vec16<TE>::type V;
-    const int64_t r0 = (int64_t)blockIdx.x * rows_per_wg;
-    const int nr = (int)(r0 + rows_per_wg < rows ? rows_per_wg : rows - r0);
-    const int64_t nch = cols / VE;
-    for (int64_t ch = threadIdx.x; ch < nch; ch += kBlock) {
-        TE acc[VE];
+    __shared__ double join[kColWaves][kWave * VE];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    const int L = 1 << lanes_log2, tx = tid & (L - 1), ty = tid >> lanes_log2;
+    const int64_t nch = cols / VE, tiles = (nch + L - 1) >> lanes_log2;
+    const int64_t r0 = ((int64_t)blockIdx.y * (kColBlock >> lanes_log2) + ty) * RB * batches;
+    if (arrived && tid == 0 && blockIdx.x == 0 && blockIdx.y == 0) *arrived = 0u;  // (for the launch after this one)
+    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const int64_t ch = (tile << lanes_log2) + tx;
+        const TE* base = X + (ch < nch ? ch : nch - 1) * VE;
+        double acc[VE];
 #pragma unroll
-        for (int e = 0; e < VE; ++e) acc[e] = 0;
-        for (int rb = 0; rb < nr; rb += RB) {
-            const int64_t g = r0 + rb;
-            const int left = nr - rb;
+        for (int e = 0; e < VE; ++e) acc[e] = 0.0;
+        for (int b = 0; b < batches; ++b) {
+            const int64_t g = r0 + (int64_t)b * RB;
+            if (g >= rows) break;
+            const int64_t left = rows - g;
+            const uint32_t word = (uint32_t)(rowbits[g >> 6] >> (g & 63));
             TE x[RB][VE];
+            // the rows past the last are read from the batch's first one and count as zeros
+            const TE* q = base + g * cols;
 #pragma unroll
             for (int i = 0; i < RB; ++i) {
-                const TE* p = X + (g + (i < left ? i : 0)) * cols + ch * VE;
                 if constexpr (VEC) {
-                    const V v = *(const V*)p;
+                    const V v = *(const V*)q;
                     x[i][0] = v.x;
                     x[i][1] = v.y;
                     if constexpr (VE == 4) x[i][2] = v.z, x[i][3] = v.w;
                 } else {
-                    x[i][0] = p[0];
+                    x[i][0] = q[0];
                 }
+                q += i + 1 < left ? cols : -(i < left ? i : 0) * cols;
             }
-            // the signs of a long batch: bits of one word, or of two
-            uint64_t word = 0;
-            if constexpr (RB > 4) {
-                const int sh = (int)(g & 63);
-                word = rowbits[g >> 6] >> sh;
-                if (sh + RB > 64) word |= rowbits[(g + (left < RB ? left : RB) - 1) >> 6] << (64 - sh);
+            __builtin_amdgcn_sched_barrier(0);  // (all of them requested before the first is waited for)
+            if (left < RB) {
+#pragma unroll
+                for (int i = 0; i < RB; ++i)
+#pragma unroll
+                    for (int e = 0; e < VE; ++e) x[i][e] = i < left ? x[i][e] : (TE)0;
             }
 #pragma unroll
             for (int i = 0; i < RB; ++i) {
-                if (i >= left) break;
-                const uint32_t neg = RB > 4 ? (uint32_t)(word >> i) & 1u : bit_at(rowbits, g + i);
+                const double sg = __hiloint2double((int)(0x3FF00000u | (((word >> i) & 1u) << 31)), 0);
 #pragma unroll
-                for (int e = 0; e < VE; ++e) acc[e] += flip(x[i][e], neg);
+                for (int e = 0; e < VE; ++e) acc[e] = __builtin_fma((double)x[i][e], sg, acc[e]);
             }
         }
-        TE* dst = partials + (int64_t)blockIdx.x * cols + ch * VE;
-        if constexpr (VEC) {
-            if constexpr (VE == 4) *(V*)dst = V{acc[0], acc[1], acc[2], acc[3]};
-            else *(V*)dst = V{acc[0], acc[1]};
-        } else {
-            dst[0] = acc[0];
+        for (int off = L; off < kWave; off <<= 1)
+#pragma unroll
+            for (int e = 0; e < VE; ++e) acc[e] += __shfl_xor(acc[e], off);
+        if (lane < L)
+#pragma unroll
+            for (int e = 0; e < VE; ++e) join[wv][tx * VE + e] = acc[e];
+        __syncthreads();
+        const int64_t col = (tile << lanes_log2) * VE + tid;
+        if (tid < L * VE && col < cols) {
+            double v = 0.0;
+#pragma unroll
+            for (int q = 0; q < kColWaves; ++q) v += join[q][tid];
+            if (narrow) ((float*)partials)[(int64_t)blockIdx.y * cols + col] = (float)v;
+            else ((double*)partials)[(int64_t)blockIdx.y * cols + col] = v;
         }
+        if (tile + gridDim.x < tiles) __syncthreads();
     }
 }
 
@@ -773,10 +799,11 @@ __global__ void __launch_bounds__(kRedBlock) reduce_kernel(ReduceArgs a)
     }
 }
 
-// Column half step on caller data: same reduction without any state.
+// Column half step on caller data: same reduction without any state.  With `arrived` (zero at the start of the launch) the
+// workgroup that comes last also adds the partial sums of |v|, in the order of sum_parts_kernel.
 template <typename TA>
 __global__ void __launch_bounds__(kRedBlock)
-    reduce_plain_kernel(const TA* P, int nparts, int64_t cols, double* W, uint64_t* bits, double* cparts)
+    reduce_plain_kernel(const TA* P, int nparts, int64_t cols, double* W, uint64_t* bits, double* cparts, unsigned* arrived, double* cout)
 {
     __shared__ double sh[kRedWaves][kWave];
     const int lane = threadIdx.x & (kWave - 1);
@@ -791,6 +818,13 @@ __global__ void __launch_bounds__(kRedBlock)
             if (bits) bits[blockIdx.x] = word;
             cparts[blockIdx.x] = cabs;
         }
+        if (!arrived) return;
+        unsigned before = 0;
+        if (lane == 0) before = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        if ((unsigned)__builtin_amdgcn_readfirstlane((int)before) != gridDim.x - 1) return;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        const double c = sum_fixed(cparts, (int)gridDim.x);
+        if (lane == 0) *cout = c;
     }
 }
 
@@ -1124,44 +1158,73 @@ hipError_t launch_row_sums(const void* R, scd_dtype dt, int64_t m, int64_t n, co
     return hipSuccess;
 }
 
-template <typename TE, bool VEC>
-static void col_partials_launch(const TE* R, int64_t m, int64_t n, int rows_per_wg, int grid, const uint64_t* rowbits, TE* partials,
-                                hipStream_t st)
+// Tile and grid of the column step.  A workgroup takes up to 64 chunks of a row (fewer where a row has fewer: the threads
+// go to the rows).  16 rows a thread where that fills the chip, else 4; several batches of rows a thread where there
+// would be more groups of rows than `most`, the number whose partial sums have room.
+struct ColGeometry {
+    bool vec;
+    int lanes_log2, rb, batches, groups;
+    unsigned grid_x;
+};
+
+static ColGeometry col_geometry(const void* R, scd_dtype dt, int64_t m, int64_t n, int most)
 {
-    if (rows_per_wg >= 8 && n < 1024)
-        hipLaunchKernelGGL((col_partials_kernel<TE, VEC, 8>), dim3(grid), dim3(kBlock), 0, st, R, m, n, rows_per_wg, rowbits, partials);
-    else
-        hipLaunchKernelGGL((col_partials_kernel<TE, VEC, 4>), dim3(grid), dim3(kBlock), 0, st, R, m, n, rows_per_wg, rowbits, partials);
+    ColGeometry g;
+    g.vec = rows_aligned(R, dt, n);
+    const int64_t nch = g.vec ? n / (dt == SCD_F32 ? 4 : 2) : n;
+    g.lanes_log2 = 0;
+    while (g.lanes_log2 < 6 && ((int64_t)1 << g.lanes_log2) < nch) ++g.lanes_log2;
+    const int64_t tiles = (nch + ((int64_t)1 << g.lanes_log2) - 1) >> g.lanes_log2, side = kColBlock >> g.lanes_log2;
+    for (g.rb = 16;; g.rb = 4) {
+        const int64_t units = (m + side * g.rb - 1) / (side * g.rb);
+        g.batches = (int)((units + most - 1) / most);
+        g.groups = (int)((units + g.batches - 1) / g.batches);
+        if (g.rb == 4 || tiles * g.groups >= 256) break;
+    }
+    g.grid_x = (unsigned)(tiles < 4096 ? tiles : 4096);
+    return g;
 }
 
-hipError_t launch_col_partials(const void* R, scd_dtype dt, int64_t m, int64_t n, int rows_per_wg, int grid, const uint64_t* rowbits,
-                               void* partials, hipStream_t st)
+// `most` groups of rows have room in `partials`, in f64; *groups is how many there are.  A single row is written as it
+// is (`narrow`: f32 partial sums of an f32 matrix), so that the partial sums never take more than most * n elements of dt
+// where most is half the rows or less.
+hipError_t launch_col_partials(const void* R, scd_dtype dt, int64_t m, int64_t n, int most, const uint64_t* rowbits, void* partials,
+                               bool narrow, unsigned* arrived, int* groups, hipStream_t st)
 {
-    const bool vec = n >= 128 && rows_aligned(R, dt, n) && ((uintptr_t)partials & 15u) == 0;
-    if (dt == SCD_F32) {
-        if (vec) col_partials_launch<float, true>((const float*)R, m, n, rows_per_wg, grid, rowbits, (float*)partials, st);
-        else col_partials_launch<float, false>((const float*)R, m, n, rows_per_wg, grid, rowbits, (float*)partials, st);
-    } else {
-        if (vec) col_partials_launch<double, true>((const double*)R, m, n, rows_per_wg, grid, rowbits, (double*)partials, st);
-        else col_partials_launch<double, false>((const double*)R, m, n, rows_per_wg, grid, rowbits, (double*)partials, st);
-    }
+    const ColGeometry g = col_geometry(R, dt, m, n, most);
+    const dim3 grid(g.grid_x, (unsigned)g.groups), block(kColBlock);
+    auto run = [&](auto zero, auto vec, auto rb) {
+        typedef decltype(zero) TE;
+        hipLaunchKernelGGL((col_partials_kernel<TE, decltype(vec)::value, decltype(rb)::value>), grid, block, 0, st, (const TE*)R, m, n,
+                           g.lanes_log2, g.batches, rowbits, partials, narrow, arrived);
+    };
+    auto pick = [&](auto zero) {
+        using std::bool_constant;
+        using std::integral_constant;
+        if (g.vec && g.rb == 16) run(zero, bool_constant<true>{}, integral_constant<int, 16>{});
+        else if (g.vec) run(zero, bool_constant<true>{}, integral_constant<int, 4>{});
+        else if (g.rb == 16) run(zero, bool_constant<false>{}, integral_constant<int, 16>{});
+        else run(zero, bool_constant<false>{}, integral_constant<int, 4>{});
+    };
+    if (dt == SCD_F32) pick(0.0f);
+    else pick(0.0);
+    *groups = g.groups;
     return hipGetLastError();
 }
 
+// cout: where the sum of `cparts` goes, by the last workgroup of this launch (`arrived`, cleared by launch_col_partials) or,
+// from 512 words on, by a launch of its own: that many workgroups in turn at one counter take longer than a launch.
+// Without cout there is no such sum.
 hipError_t launch_reduce_plain(const void* partials, scd_dtype dt, int nparts, int64_t cols, double* W, uint64_t* bits,
-                               double* cparts, hipStream_t st)
+                               double* cparts, unsigned* arrived, double* cout, hipStream_t st)
 {
     const int grid = (int)((cols + kWave - 1) / kWave);
+    unsigned* last = cout && grid <= 512 ? arrived : nullptr;
     if (dt == SCD_F32)
-        hipLaunchKernelGGL((reduce_plain_kernel<float>), dim3(grid), dim3(kRedBlock), 0, st, (const float*)partials, nparts, cols, W, bits, cparts);
+        hipLaunchKernelGGL((reduce_plain_kernel<float>), dim3(grid), dim3(kRedBlock), 0, st, (const float*)partials, nparts, cols, W, bits, cparts, last, cout);
     else
-        hipLaunchKernelGGL((reduce_plain_kernel<double>), dim3(grid), dim3(kRedBlock), 0, st, (const double*)partials, nparts, cols, W, bits, cparts);
-    return hipGetLastError();
-}
-
-hipError_t launch_sum_parts(const double* parts, int n, double* out, hipStream_t st)
-{
-    hipLaunchKernelGGL(sum_parts_kernel, dim3(1), dim3(kWave), 0, st, parts, n, out);
+        hipLaunchKernelGGL((reduce_plain_kernel<double>), dim3(grid), dim3(kRedBlock), 0, st, (const double*)partials, nparts, cols, W, bits, cparts, last, cout);
+    if (cout && !last) hipLaunchKernelGGL(sum_parts_kernel, dim3(1), dim3(kWave), 0, st, cparts, grid, cout);
     return hipGetLastError();
 }
 
