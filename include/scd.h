@@ -171,10 +171,10 @@ int scd_col_signed_sum(const void* R, scd_dtype dt, int64_t m, int64_t n, const 
 /* The column half step for callers that cannot allocate device memory: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels, same geometry and therefore the
  * same bits in v, tbits and c as scd_col_signed_sum, but
- *  - the per-workgroup partial column sums and the partial sums of |v| live in a fixed work space of
+ *  - the partial column sums and the partial sums of |v| live in a fixed work space of
  *    SCD_NOALLOC_SCRATCH_BYTES that is part of the library's code object (one copy per device, held until the
  *    process ends); the call allocates and frees nothing;
- *  - the call only enqueues its three launches on `stream` and returns: v, tbits and c are complete once the
+ *  - the call only enqueues its launches on `stream` and returns: v, tbits and c are complete once the
  *    stream has reached that point (the caller synchronises, or orders later work on the same stream);
  *  - inputs with 256 + 256*ceil(ceil(n/64)/32) + ceil(m / ceil(m/1024)) * n * sizeof(dt) bytes of work space above
  *    the limit are refused with SCD_ETOOBIG before anything is enqueued (4096 x 4096 f32 fits; f64 does not);

@@ -172,178 +172,219 @@ __global__ void __launch_bounds__(kApInnerWaves* kWave)
 // vectors (16 columns); <t, x> = sum x - 2 sum over the -1 signs, exact in integers, the digits recombined in f64.
 // The order of the contraction index is free as long as both operands share it, and is chosen for the bits: lane
 // (term, kq) reads words 2 kq and 2 kq + 1 of eight neighbouring words of its term (64 bytes per term and load), and
-// byte b of operand dword q of its instruction t = 0..7 is bit (t & 1) * 4 + q + 8 b of the half word t / 2 of the two:
-// one shift and one mask per four signs.  (With v_mfma_i32_4x4x4_16B_i8 and a table look-up per nibble the pass used a
-// quarter of the instruction's columns for one vector and took them one after the other: 14336x4096 transposed, four
-// vectors, 4 x 30 us; now 34 us for the four.)
+// byte b of operand dword q of its instruction k = 0..7 is bit k + 8 b of half word q of the two: a mask, and for odd k a shift.
+// (With v_mfma_i32_4x4x4_16B_i8 and a table look-up per nibble the pass used a quarter of the instruction's columns for one
+// vector and took them one after the other: 14336x4096 transposed, four vectors, 4 x 30 us.)
 typedef int ap_int4 __attribute__((ext_vector_type(4)));
 
-constexpr int kApMfmaWaves = 8;                      // waves per workgroup of the outer pass: one word of outputs each
-constexpr int kApFxWaves = 4;                        // waves per workgroup of the inner pass: 16 terms each
-constexpr int kApFxThreads = kApFxWaves * kWave;
-constexpr int kApFxTile = 16 * kApFxWaves;           // terms per workgroup and turn
-constexpr int kApFxSets = 1024 / kApFxThreads;       // dwords of the fixed point per thread and digit
+// a barrier for what goes through LDS: loads stay on their way
+__device__ __forceinline__ void ap_lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// |v| as an integer below 2^30 in the chunk's scale -> digit jd of four of them as one dword per digit
+constexpr int kApMfmaWaves = 8;                      // waves per workgroup of the outer pass: one word of outputs each
+constexpr int kApFxRows = 4, kApFxQuarters = 4;      // waves of the inner pass: 16 terms, a quarter of the chunk each
+constexpr int kApFxWaves = kApFxRows * kApFxQuarters;
+constexpr int kApFxThreads = kApFxWaves * kWave;     // one dword of the fixed point per thread and digit
+constexpr int kApFxTile = 16 * kApFxRows;            // terms per workgroup and turn
+constexpr int kApInnerGrid = 256;                    // most workgroups of the inner pass
+static_assert(kApFxThreads == kApChunkWords * 16, "a thread per four entries of the chunk");
+
+// four integers |q| < 2^30 -> digit jd of each as one dword per digit.  With 128 added to each of the three lower digits they
+// are the bytes of q + 128 (1 + 256 + 65536), and flipping the top bit of a byte takes the 128 off again.
 __device__ __forceinline__ void ap_digits(const int (&q4)[4], uint32_t (&dig)[4])
 {
+    uint32_t r[4];
 #pragma unroll
-    for (int jd = 0; jd < 4; ++jd) dig[jd] = 0u;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        int q = q4[k];
-#pragma unroll
-        for (int jd = 0; jd < 3; ++jd) {
-            const int d = (int)(int8_t)(q & 0xFF);
-            dig[jd] |= (uint32_t)(d & 0xFF) << (8 * k);
-            q = (q - d) >> 8;
-        }
-        dig[3] |= (uint32_t)(q & 0xFF) << (8 * k);
-    }
+    for (int k = 0; k < 4; ++k) r[k] = ((uint32_t)q4[k] + 0x00808080u) ^ 0x00808080u;
+    const uint32_t t0 = __builtin_amdgcn_perm(r[1], r[0], 0x05010400u), t1 = __builtin_amdgcn_perm(r[1], r[0], 0x07030602u);
+    const uint32_t u0 = __builtin_amdgcn_perm(r[3], r[2], 0x05010400u), u1 = __builtin_amdgcn_perm(r[3], r[2], 0x07030602u);
+    dig[0] = __builtin_amdgcn_perm(u0, t0, 0x05040100u);
+    dig[1] = __builtin_amdgcn_perm(u0, t0, 0x07060302u);
+    dig[2] = __builtin_amdgcn_perm(u1, t1, 0x05040100u);
+    dig[3] = __builtin_amdgcn_perm(u1, t1, 0x07060302u);
 }
 
-// part[v * pstride + chunk * w + j] = <t_j, x_v> restricted to the chunk, for nv <= NV vectors
-template <int NV>
+// part[v * pstride + chunk * w + j] = <t_j, x_v> restricted to the chunk, for nv <= NV vectors.
+//
+// Vector instructions bound the pass, not bits or matrix cores.  Sixteen waves form the fixed point of a workgroup once,
+// four entries a thread and vector, and share the contraction: wave (r, k) takes 16 terms and a quarter of the chunk.  The
+// quarters' integers are added through LDS (exact, so the split changes no bit), by the four waves of a row for one register
+// each.  Half of the sign bytes need no shift: bit 2 c of a byte counts 4^c in an accumulator of its own.  sum x comes from the
+// matrix cores too, as a term of 1 bits.  The bits of the next two tiles are on their way meanwhile; with one tile per workgroup
+// (ONE) there are none, and asking for it again would cost two microseconds (9.2 and 6.9).  Us a launch, with four waves that
+// each took whole rows, a shift and a mask for every four signs, the digits cut one after the other and f64 sums / now:
+// 14336x4096 transposed to 25442 terms, four vectors 32.6 / 25.0, 4096x4096 to 16320, one vector 8.5 / 6.9.
+template <int NV, bool ONE>
 __global__ void __launch_bounds__(kApFxThreads)
     apply_inner_fx_kernel(const uint64_t* __restrict__ bits, int64_t nw, int64_t w, const float* __restrict__ x, int nv, int64_t n,
                           double* __restrict__ part, int64_t pstride, int tiles_per_wg)
 {
     constexpr int NC = 4 * NV;  // columns in use
-    __shared__ __align__(16) uint32_t xd[kApChunkWords * 4 * NC * 4];  // [8 words][t][kq][column][dword]
-    __shared__ float redmax[NV][kApFxWaves];
-    __shared__ double redsum[NV][kApFxWaves];
-    __shared__ int bad[NV];
+    constexpr int kAhead = 3;   // tiles whose bits are held or requested
+    __shared__ __align__(16) uint32_t xd[kApChunkWords * 4 * NC * 4];  // [8 words][bit of a byte][kq][column ^ bit][dword]
+    __shared__ int quarter[2][4][kApFxWaves][kWave];                  // [turn][register][wave][lane]
+    __shared__ int total_of[kApFxQuarters][kWave];
+    __shared__ uint32_t most[NV];
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int wr = wv & (kApFxRows - 1), wk = wv / kApFxRows;
     const int64_t chunk = blockIdx.y;
     const int64_t p0 = chunk * kApChunkWords;
     const int nwc = (int)(nw - p0 < kApChunkWords ? nw - p0 : kApChunkWords);
     const int ngrp = (nwc + 7) / 8;
     const int row = lane & 15, kq = lane >> 4;
+    const int64_t tile0 = (int64_t)blockIdx.x * tiles_per_wg, last0 = w > kApFxTile ? w - kApFxTile : 0;
 
-    // the sign bits of the first 16 terms are requested before anything else: their latency hides behind the fixed point
-    uint64_t wbuf[8][2];
-    auto fetch = [&](int64_t jbase) {
-        int64_t j = jbase + wv * 16 + row;
-        j = j < w ? j : w - 1;
-        const uint64_t* r = bits + j * nw + p0;
-#pragma unroll
-        for (int g = 0; g < 8; ++g) {
-            const int q = (g < ngrp ? g : 0) * 8 + 2 * kq;  // (words past the end meet digits that are zero)
-            wbuf[g][0] = r[q < nwc ? q : nwc - 1];
-            wbuf[g][1] = r[q + 1 < nwc ? q + 1 : nwc - 1];
-        }
-    };
-    fetch((int64_t)blockIdx.x * tiles_per_wg * kApFxTile);
-
-    // ---- fixed point of this chunk: thread t owns dwords t + kApFxThreads i (word, half, d): entries d + 8 b of the half word
-    if (tid < NV) bad[tid] = 0;
-    __syncthreads();
-    float xv[NV][kApFxSets][4];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        if (v >= nv) continue;  // (the columns of vectors past nv hold what they hold and are not stored)
-        float amax = 0.f;
-        bool finite = true;
-#pragma unroll
-        for (int i = 0; i < kApFxSets; ++i)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const int sidx = tid + kApFxThreads * i;
-                const int64_t l = p0 * 64 + (sidx >> 4) * 64 + ((sidx >> 3) & 1) * 32 + (sidx & 7) + 8 * b;
-                const float val = x[(int64_t)v * n + (l < n ? l : n - 1)];
-                xv[v][i][b] = l < n ? val : 0.f;
-                finite = finite && (fabsf(xv[v][i][b]) <= 3.0e38f);
-                amax = fmaxf(amax, fabsf(xv[v][i][b]));
-            }
-        amax = ap_wave_max(amax);
-        if (lane == 0) redmax[v][wv] = amax;
-        if (!finite) bad[v] = 1;
-    }
-    __syncthreads();
-    double inv_scale[NV];
-    bool all_finite[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        inv_scale[v] = 1.0;
-        all_finite[v] = true;
-        if (v >= nv) continue;
-        float amax = 0.f;
-#pragma unroll
-        for (int q = 0; q < kApFxWaves; ++q) amax = fmaxf(amax, redmax[v][q]);
-        all_finite[v] = bad[v] == 0;
-        int ex = 0;
-        if (amax > 0.f) (void)frexpf(amax, &ex);  // amax < 2^ex
-        const int sh = 30 - ex;
-        const double scale = ldexp(1.0, sh);
-        inv_scale[v] = ldexp(1.0, -sh);
-        double sum = 0.0;  // of integers below 2^30: exact
-#pragma unroll
-        for (int i = 0; i < kApFxSets; ++i) {
-            int q4[4];
-            uint32_t dig[4];
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                q4[b] = all_finite[v] ? (int)rint((double)xv[v][i][b] * scale) : 0;
-                sum += (double)q4[b];
-            }
-            ap_digits(q4, dig);
-            const int sidx = tid + kApFxThreads * i, wd = sidx >> 4, h = (sidx >> 3) & 1, d = sidx & 7;
-            const int t = (wd & 1) * 4 + h * 2 + (d >> 2);
-            uint32_t* dst = xd + ((((wd >> 3) * 8 + t) * 4 + ((wd & 7) >> 1)) * NC + 4 * v) * 4 + (d & 3);
-#pragma unroll
-            for (int jd = 0; jd < 4; ++jd) dst[jd * 4] = dig[jd];
-        }
-        sum = ap_wave_sum(sum);
-        if (lane == 0) redsum[v][wv] = sum;
-    }
-    __syncthreads();
-    // this lane's column: digit jd of vector vc
-    const int jd = lane & 3, vc = (row & (NC - 1)) >> 2;
-    double total = 0.0, inv = 0.0;
-    bool fin = true;
+    // ---- fixed point of this chunk: thread t owns dword t (word, half, d): entries d + 8 b of the half word
+    if (tid < NV) most[tid] = 0u;
+    float xv[NV][4];
+    const int64_t l0 = p0 * 64 + (tid >> 4) * 64 + ((tid >> 3) & 1) * 32 + (tid & 7);
 #pragma unroll
     for (int v = 0; v < NV; ++v)
-        if (v == vc) {
 #pragma unroll
-            for (int q = 0; q < kApFxWaves; ++q) total += redsum[v][q];
-            inv = inv_scale[v];
-            fin = all_finite[v];
+        for (int b = 0; b < 4; ++b) {
+            const int64_t l = l0 + 8 * b;
+            const float val = x[(int64_t)(v < nv ? v : nv - 1) * n + (l < n ? l : n - 1)];
+            xv[v][b] = l < n ? val : 0.f;
         }
-    const double digit_weight = (double)(1u << (8 * jd));
-    const ap_int4* xb = (const ap_int4*)xd + kq * NC + (row & (NC - 1));
+    // The sign bits of the first tiles are requested before x is waited for (no barrier here waits for loads): their latency
+    // hides behind the fixed point.  A tile that would pass the last term starts 64 terms before it.
+    const uint64_t* from[2][2];
+    {
+        const int local = wr * 16 + row;
+        const uint64_t* r = bits + (local < w ? local : w - 1) * nw + p0;
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            const int gg = 2 * wk + g;
+            const int q = (gg < ngrp ? gg : 0) * 8 + 2 * kq;  // (words past the end meet digits that are zero)
+            from[g][0] = r + (q < nwc ? q : nwc - 1);
+            from[g][1] = r + (q + 1 < nwc ? q + 1 : nwc - 1);
+        }
+    }
+    auto first_term = [&](int64_t tile) { return tile * kApFxTile < last0 ? tile * kApFxTile : last0; };
+    uint64_t wbuf[kAhead][2][2];
+    auto fetch = [&](int64_t tile, uint64_t (&to)[2][2]) {
+        // (unconditional, else the compiler waits for them where the paths meet)
+        const int64_t off = first_term(tile < tile0 + tiles_per_wg ? tile : tile0 + tiles_per_wg - 1) * nw;
+#pragma unroll
+        for (int g = 0; g < 2; ++g) to[g][0] = from[g][0][off], to[g][1] = from[g][1][off];
+    };
+#pragma unroll
+    for (int a = 0; a < (ONE ? 1 : kAhead - 1); ++a) fetch(tile0 + a, wbuf[a]);
+    ap_lds_barrier();
+    // the largest |x|, by its bits: those of infinities and NaNs lie above
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        if (v >= nv) continue;
+        uint32_t m = 0u;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const uint32_t u = __float_as_uint(xv[v][b]) & 0x7FFFFFFFu;
+            m = u > m ? u : m;
+        }
+        auto join = [&](uint32_t o) { m = o > m ? o : m; };
+        join(ap_dpp_xor<1>(m));
+        join(ap_dpp_xor<2>(m));
+        join(ap_dpp_xor<4>(m));
+        join(ap_dpp_xor<8>(m));
+        if (row == 0) atomicMax(&most[v], m);
+    }
+    ap_lds_barrier();
+    const uint32_t finite_most = __float_as_uint(3.0e38f);
+    const int wd = tid >> 4, hd = tid & 7;
+    uint32_t* dst = xd + (((wd >> 3) * 8 + hd) * 4 + ((wd & 7) >> 1)) * NC * 4 + (wd & 1) * 2 + ((tid >> 3) & 1);
+    int shift[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        shift[v] = 0;
+        if (v >= nv) continue;  // (the columns of vectors past nv hold what they hold and are not stored)
+        const uint32_t am = most[v];
+        const bool finite = am <= finite_most;
+        shift[v] = 30 - __builtin_amdgcn_frexp_expf(__uint_as_float(am));  // |x| < 2^(30 - shift); exponent 0 for zero
+        int q4[4];
+        uint32_t dig[4];
+        // (scaled in f32: exact but for values that are zero once rounded)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) q4[b] = finite ? (int)rintf(__builtin_amdgcn_ldexpf(xv[v][b], shift[v])) : 0;
+        ap_digits(q4, dig);
+#pragma unroll
+        for (int jd = 0; jd < 4; ++jd) dst[((4 * v + jd) ^ (hd & (NC - 1))) * 4] = dig[jd];
+    }
+    ap_lds_barrier();
+    // this lane's column: digit jd of vector vc
+    const int col = row & (NC - 1), jd = lane & 3, vc = col >> 2;
+    int sh = 0;
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+        if (v == vc) sh = shift[v];
+    const bool fin = most[vc] <= finite_most;
+    // the digits' weight in units of x
+    const double weight = fin ? __hiloint2double((1023 + 8 * jd - sh) << 20, 0) : __longlong_as_double(0x7FF8000000000000ll);
+    const ap_int4* xb[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) xb[k] = (const ap_int4*)xd + (2 * wk * 8 + k) * 4 * NC + kq * NC + (col ^ (k & (NC - 1)));
+    if (wr == 0) {
+        ap_int4 acc = {0, 0, 0, 0};
+        const ap_int4 ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+            if (2 * wk + g < ngrp)
+#pragma unroll
+                for (int k = 0; k < 8; ++k) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(ones, xb[k][g * 8 * 4 * NC], acc, 0, 0, 0);
+        total_of[wk][lane] = acc[0];  // (all rows are the same)
+    }
+    ap_lds_barrier();
+    int total = 0;
+#pragma unroll
+    for (int k = 0; k < kApFxQuarters; ++k) total += total_of[k][lane];
     double* mypart = part + (int64_t)vc * pstride + chunk * w;
-    for (int t0 = 0; t0 < tiles_per_wg; ++t0) {
-        const int64_t jbase = ((int64_t)blockIdx.x * tiles_per_wg + t0) * kApFxTile;
-        if (jbase >= w) break;
-        ap_int4 acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};
+    const int local = wr * 16 + 4 * kq + wk;  // register wk of this lane: the term, column lane mod 16
+    const bool store = jd == 0 && row < NC && vc < nv && local < w;
+    auto turn = [&](int t0, uint64_t (&mine)[2][2], uint64_t (&next)[2][2]) {
+        if constexpr (!ONE) fetch(tile0 + t0 + kAhead - 1, next);
+        ap_int4 acc[4];
 #pragma unroll
-        for (int g = 0; g < 8; ++g) {
-            if (g < ngrp) {
+        for (int c = 0; c < 4; ++c) acc[c] = ap_int4{0, 0, 0, 0};
 #pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const uint64_t word = wbuf[g][t >> 2];
-                    const uint32_t half = (t >> 1) & 1 ? (uint32_t)(word >> 32) : (uint32_t)word;
-                    ap_int4 A;
+        for (int g = 0; g < 2; ++g) {
+            if (2 * wk + g < ngrp) {
+                const uint32_t d4[4] = {(uint32_t)mine[g][0], (uint32_t)(mine[g][0] >> 32), (uint32_t)mine[g][1], (uint32_t)(mine[g][1] >> 32)};
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) A[q] = (int)((half >> ((t & 1) * 4 + q)) & 0x01010101u);
-                    const ap_int4 B = xb[(g * 8 + t) * 4 * NC];
-                    if (t & 1) acc1 = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, B, acc1, 0, 0, 0);
-                    else acc0 = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, B, acc0, 0, 0, 0);
-                }
+                for (int odd = 0; odd < 2; ++odd)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        ap_int4 A;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) A[q] = (int)((d4[q] >> odd) & (0x01010101u << (2 * c)));
+                        acc[c] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, xb[2 * c + odd][g * 8 * 4 * NC], acc[c], 0, 0, 0);
+                    }
             }
         }
-        if (t0 + 1 < tiles_per_wg && jbase + kApFxTile < w) fetch(jbase + kApFxTile);
-        // register i = term jbase + 16 wave + 4 (lane / 16) + i, column lane mod 16: recombine the digits (exact in f64)
+        int(*mail)[kApFxWaves][kWave] = quarter[t0 & 1];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            double v = (double)(acc0[i] + acc1[i]) * digit_weight;
-            v += ap_dpp_xor_f64<1>(v);
-            v += ap_dpp_xor_f64<2>(v);
-            const int64_t j = jbase + wv * 16 + 4 * kq + i;
-            if (jd == 0 && row < NC && vc < nv && j < w)
-                mypart[j] = fin ? (total - 2.0 * v) * inv : __longlong_as_double(0x7FF8000000000000ll);
-        }
+        for (int i = 0; i < 4; ++i) mail[i][wv][lane] = ((acc[0][i] * 4 + acc[1][i]) * 4 + acc[2][i]) * 4 + acc[3][i];
+        ap_lds_barrier();
+        int sum = 0;
+#pragma unroll
+        for (int k = 0; k < kApFxQuarters; ++k) sum += mail[wk][k * kApFxRows + wr][lane];
+        // recombine the digits: exact in f64
+        double v = (double)(total - 2 * (sum >> 6)) * weight;
+        v += ap_dpp_xor_f64<1>(v);
+        v += ap_dpp_xor_f64<2>(v);
+        const int64_t j = first_term(tile0 + t0) + local;
+        if (store && j >= (tile0 + t0) * kApFxTile) mypart[j] = v;
+    };
+    static_assert(kAhead == 3, "the turns below");
+    if constexpr (ONE) {
+        turn(0, wbuf[0], wbuf[1]);
+        return;
+    }
+    for (int t0 = 0; t0 < tiles_per_wg; t0 += kAhead) {
+        if ((tile0 + t0) * kApFxTile >= w) break;
+        turn(t0, wbuf[0], wbuf[2]);
+        if (t0 + 1 >= tiles_per_wg || (tile0 + t0 + 1) * kApFxTile >= w) break;
+        turn(t0 + 1, wbuf[1], wbuf[0]);
+        if (t0 + 2 >= tiles_per_wg || (tile0 + t0 + 2) * kApFxTile >= w) break;
+        turn(t0 + 2, wbuf[2], wbuf[1]);
     }
 }
 
@@ -840,14 +881,17 @@ hipError_t launch_fx(const uint64_t* in_bits, const uint64_t* out_bits, const fl
     const int64_t pstride = (int64_t)pl.parts * w;
     double* part = (double*)workspace;
     double* ypart = part + nv * pstride;
-    // a workgroup per tile of 64 terms; several tiles per workgroup once there are more than two per compute unit, to pay
-    // for the fixed point less often (14336x4096 transposed, three vectors and one more: 113 us, with up to 1024 workgroups 123)
+    // a workgroup per tile of 64 terms; several tiles per workgroup once there are more workgroups than compute units, which
+    // hold one each: the fixed point, half of a workgroup's time with seven tiles, is paid for once
     const int64_t tiles = (w + kApFxTile - 1) / kApFxTile;
-    int tpw = (int)((tiles * pl.chunks + 511) / 512);
+    int tpw = (int)((tiles * pl.chunks + kApInnerGrid - 1) / kApInnerGrid);
     if (tpw < 1) tpw = 1;
     const int64_t wgs = (tiles + tpw - 1) / tpw;
-    hipLaunchKernelGGL((apply_inner_fx_kernel<NV>), dim3((unsigned)wgs, (unsigned)pl.chunks), dim3(kApFxThreads), 0, st, in_bits, win, w, x,
-                       nv, nin, part, pstride, tpw);
+    const dim3 gi((unsigned)wgs, (unsigned)pl.chunks);
+    if (tpw == 1)
+        hipLaunchKernelGGL((apply_inner_fx_kernel<NV, true>), gi, dim3(kApFxThreads), 0, st, in_bits, win, w, x, nv, nin, part, pstride, tpw);
+    else
+        hipLaunchKernelGGL((apply_inner_fx_kernel<NV, false>), gi, dim3(kApFxThreads), 0, st, in_bits, win, w, x, nv, nin, part, pstride, tpw);
     const int splits = (pl.splits_fx + group - 1) / group;
     dim3 go((unsigned)((wout + kApMfmaWaves - 1) / kApMfmaWaves), (unsigned)splits);
     bool one_each = true;
