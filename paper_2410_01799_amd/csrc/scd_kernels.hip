@@ -340,9 +340,9 @@ __global__ void __launch_bounds__(kBlock)
 // rows at once, whose signs are in one word.  The threads' sums are joined in the workgroup, so that a partial sum stands
 // for 32 rows and more: with whole rows per workgroup (four at 4096x4096, 1024 partial sums a column) the partial sums were
 // half as many bytes as the matrix and narrow matrices left most threads idle.  Us a call of the column step, whole rows per
-// workgroup / this: f32 4096x4096 37.8 / 34.4, 14336x8192 130 / 107, 14336x4096 60.0 / 60.3, 4095x4093 50.3 / 37.7, 1501x999
+// workgroup / this: f32 4096x4096 37.8 / 34.4, 14336x8192 130 / 101, 14336x4096 60.0 / 57.3, 4095x4093 50.3 / 37.7, 1501x999
 // 31.5 / 25.0, 256x256 24.3 / 23.2, 1x100000 54.7 / 33.6, 200000x100 45.8 / 37.7, 1000000x4 79 / 28.5; f64 4096x4096 52.8 /
-// 45.0, 1000000x2 83.6 / 30.1.  The kernel takes 13.7 us at 4096x4096 (before 13.5, with f32 sums and their 16 MiB); without
+// 42.4, 1000000x2 83.6 / 30.1.  The kernel takes 13.7 us at 4096x4096 (before 13.5, with f32 sums and their 16 MiB); without
 // the loads ahead of the sums, as the compiler orders them by itself, 15.8.
 constexpr int kColBlock = 512;
 constexpr int kColWaves = kColBlock / kWave;
@@ -1160,7 +1160,11 @@ hipError_t launch_row_sums(const void* R, scd_dtype dt, int64_t m, int64_t n, co
 
 // Tile and grid of the column step.  A workgroup takes up to 64 chunks of a row (fewer where a row has fewer: the threads
 // go to the rows).  16 rows a thread where that fills the chip, else 4; several batches of rows a thread where there
-// would be more groups of rows than `most`, the number whose partial sums have room.
+// would be more groups of rows than `most`, the number whose partial sums have room, or more workgroups than two a compute
+// unit, which is one round of them: us a call with a batch each / in one round, 14336x4096 f32 59.5 / 57.0, 14336x8192 108 / 101.6
+// (1024 workgroups: 124), 4096x4096 f64 45.4 / 42.6.
+constexpr int kColRound = 512;
+
 struct ColGeometry {
     bool vec;
     int lanes_log2, rb, batches, groups;
@@ -1177,7 +1181,8 @@ static ColGeometry col_geometry(const void* R, scd_dtype dt, int64_t m, int64_t 
     const int64_t tiles = (nch + ((int64_t)1 << g.lanes_log2) - 1) >> g.lanes_log2, side = kColBlock >> g.lanes_log2;
     for (g.rb = 16;; g.rb = 4) {
         const int64_t units = (m + side * g.rb - 1) / (side * g.rb);
-        g.batches = (int)((units + most - 1) / most);
+        const int64_t round = kColRound / tiles > 1 ? kColRound / tiles : 1, room = most < round ? most : round;
+        g.batches = (int)((units + room - 1) / room);
         g.groups = (int)((units + g.batches - 1) / g.batches);
         if (g.rb == 4 || tiles * g.groups >= 256) break;
     }
