@@ -103,7 +103,7 @@ struct scd_ctx {
     ResidentResult* res_pin = nullptr;
     uint32_t seq_u = 0, seq_v = 0;
     int xbuf_sum = 0;               // bytes of a sum in the exchange slots as they were last written (0: cleared)
-    double fro = 0.0;               // ||R||_F when the remainder was last given (terms only lower it)
+    double fro = 0.0;               // ||R||_F when the remainder was last given (terms only lower it); not finite if the remainder is not
     // sparse engine
     bool sparse = false;
     bool rt_stale = true;           // RT does not mirror R (R was changed by the launch-stream kernels)
@@ -582,6 +582,15 @@ int setup_engines(scd_ctx* c)
     return SCD_OK;
 }
 
+// Engine of the next terms, as scd_engine counts them.  The words that the persistent engines exchange are scaled by the norm
+// of the remainder and have no room for infinities and NaNs: a remainder without a norm goes to the launch stream, which
+// carries them into the results.
+int engine_of(const scd_ctx* c)
+{
+    if (!isfinite(c->fro)) return 0;
+    return c->resident ? 1 : c->sparse ? 2 : c->pstream ? 3 : 0;
+}
+
 // n terms in one persistent launch that updates the cached products from the flipped signs only.
 int run_sparse(scd_ctx* c, int64_t n)
 {
@@ -1019,8 +1028,9 @@ int scd_run(scd_ctx* c, int64_t n)
     if (c->broken) return SCD_ETIMEOUT;
     if (n == 0) return c->hs.warn ? SCD_WMAXITER : SCD_OK;
     if (c->hs.k + n > c->w_capacity) return SCD_EFULL;
-    if (c->resident || c->sparse || c->pstream) {
-        SCD_TRY(c->resident ? run_resident(c, n) : (c->sparse ? run_sparse(c, n) : run_pstream(c, n)));
+    const int engine = engine_of(c);
+    if (engine != 0) {
+        SCD_TRY(engine == 1 ? run_resident(c, n) : (engine == 2 ? run_sparse(c, n) : run_pstream(c, n)));
         return c->hs.warn ? SCD_WMAXITER : SCD_OK;
     }
     SCD_TRY(resync_stream_state(c));  // a persistent engine may have advanced the context before it lost its share
@@ -1120,15 +1130,14 @@ int scd_set_remainder(scd_ctx* c, const void* R_in)
     SCD_TRY(read_state(c));
     double f = 0.0;
     HIP_TRY(hipMemcpy(&f, c->trace + c->hs.k, sizeof(double), hipMemcpyDeviceToHost));
-    if (!isfinite(f)) return SCD_ENONFINITE;
     c->fro = f;
-    return SCD_OK;
+    return isfinite(f) ? SCD_OK : SCD_ENONFINITE;
 }
 
 int scd_engine(const scd_ctx* c, int* engine, double* last_launch_seconds, double* last_launch_bytes)
 {
     if (!c) return SCD_EINVAL;
-    if (engine) *engine = c->resident ? 1 : (c->sparse ? 2 : (c->pstream ? 3 : 0));
+    if (engine) *engine = engine_of(c);
     if (last_launch_seconds) *last_launch_seconds = c->last_launch_seconds;
     if (last_launch_bytes) *last_launch_bytes = c->last_launch_bytes;
     return SCD_OK;
