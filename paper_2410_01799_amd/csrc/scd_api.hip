@@ -584,11 +584,16 @@ int setup_engines(scd_ctx* c)
 
 // Engine of the next terms, as scd_engine counts them.  The words that the persistent engines exchange are scaled by the norm
 // of the remainder and have no room for infinities and NaNs: a remainder without a norm goes to the launch stream, which
-// carries them into the results.
+// carries them into the results, and so does one whose f32 column sums in a workgroup of the streaming engine could pass the
+// largest f32 (the other two take the matrix with f64 sums then).
+bool pstream_sums_fit(const scd_ctx* c)
+{
+    return c->dt == SCD_F64 || c->fro * sqrt((double)c->ps_geo.rpw) < 0x1p127;
+}
 int engine_of(const scd_ctx* c)
 {
     if (!isfinite(c->fro)) return 0;
-    return c->resident ? 1 : c->sparse ? 2 : c->pstream ? 3 : 0;
+    return c->resident ? 1 : c->sparse ? 2 : c->pstream && pstream_sums_fit(c) ? 3 : 0;
 }
 
 // n terms in one persistent launch that updates the cached products from the flipped signs only.
@@ -1928,7 +1933,7 @@ int scd_decompose_scalars(const void* A, scd_dtype dt, int order, const int64_t*
         int rc = scd_create(&c, A, dt, order, dims, w, seed, stream);
         if (rc < 0) return rc;
         rc = scd_set_max_iters(c, max_iters);
-        if (rc >= 0 && c->pstream) {
+        if (rc >= 0 && engine_of(c) == 3) {
             hipError_t e = pool_malloc(&c->c_scal, (size_t)w * (size_t)q * es, false);
             if (e != hipSuccess) {
                 g_last_hip = (int)e;

@@ -4,6 +4,8 @@ import numpy as np
 import pytest
 import torch
 
+from helpers import C_RTOL, CURVE_RTOL
+
 pytestmark = pytest.mark.gpu
 
 RESIDENT = {}
@@ -56,3 +58,45 @@ def test_a_remainder_that_is_not_finite(scd, dims, dtype, options, engine, bad):
         assert torch.equal(out[0][key][3:], out[1][key][3:])
     for mode in range(len(dims)):
         assert torch.equal(out[0]["signs"][mode][3:], out[1]["signs"][mode][3:])
+
+
+# rows a workgroup: 64, 40, 64
+TALL = [(16384, 8, 3), (10000, 12, 4), (16384, 24)]
+
+
+def tall(dims):
+    return gauss(dims, sum(dims), torch.float32) * 0.25 + 1.0
+
+
+@pytest.mark.parametrize("dims", TALL)
+def test_column_sums_past_the_largest_f32(scd, dims):
+    """f32 sums of a workgroup's rows that overflow: infinite with one launch per alternation, and so with one for all of them."""
+    A = tall(dims) * 2.0 ** 124
+    for options in (STREAM, LAUNCH):
+        with scd.ScdContext(A, 1, 3, options=options) as ctx:
+            ctx.set_max_iters(6)
+            ctx.run(1)
+            assert not torch.isfinite(ctx.results()["c"]).any()
+
+
+@pytest.mark.parametrize("dims", TALL)
+def test_norms_on_either_side_of_the_streaming_engines_limit(scd, dims):
+    A, w = tall(dims), 4
+    fro, rows = float(A.double().norm()), -(-dims[0] // 256)
+    top = int(np.floor(127 - np.log2(fro * rows ** 0.5)))  # largest power of two at which no sum can overflow
+    with scd.ScdContext(A, w, 3, options=STREAM) as ctx:
+        assert ctx.engine()["engine"] == 3
+        ctx.run(w)
+        base = ctx.results()
+    for k, engine in ((top, 3), (top + 1, 0)):
+        with scd.ScdContext(A * 2.0 ** k, w, 3, options=STREAM) as ctx:
+            assert ctx.engine()["engine"] == engine
+            ctx.run(w)
+            res = ctx.results()
+        np.testing.assert_allclose(np.ldexp(res["trace"].cpu().numpy(), -k), base["trace"].cpu().numpy(), rtol=CURVE_RTOL)
+        np.testing.assert_allclose(np.ldexp(res["c"].double().cpu().numpy(), -k)[:1], base["c"].double().cpu().numpy()[:1], rtol=C_RTOL)
+    if len(dims) == 3:
+        base = scd.scd_decompose_scalars(A, w, 3)
+        for k in (top, top + 1):
+            res = scd.scd_decompose_scalars(A * 2.0 ** k, w, 3)
+            np.testing.assert_allclose(np.ldexp(res["trace"].cpu().numpy(), -k), base["trace"].cpu().numpy(), rtol=CURVE_RTOL)
