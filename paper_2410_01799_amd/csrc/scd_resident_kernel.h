@@ -116,7 +116,8 @@ __device__ __forceinline__ double uniform_f64(double v)
 // 256 entries is at most 16 ||R||_F), which leaves the top bit of its exponent clear: that bit carries the tag, so that
 // two f32 sums or one f64 sum fill an 8-byte word, a word is still stored and seen whole, and nothing else has to tell a fresh
 // word from the one that it replaces.  The tag flips each time that a slot is written (slots alternate, so every second
-// exchange); cleared slots are older than exchange 1.  f32 sums below 2^-126 of that scale lose bits, f64 ones 2^-1022.
+// exchange); cleared slots are older than exchange 1.  f32 sums below 2^-126 of that scale lose bits, f64 ones 2^-1022; infinities
+// and NaNs have no room (the host lets none come here).
 // A slot is read 16 bytes a lane.  Us per exchange of 256 sums alone, among 16 partners on one die / on eight: one f32 and a
 // 32-bit sequence number in a word, read 8 bytes a lane 1.55 / 1.85, read 16 bytes a lane 1.60 / 1.88, two f32 in a word
 // read 16 bytes a lane 1.17 / 1.49; f64 as two such words 2.50 / 2.87, as one word 1.58 / 1.89.

@@ -1097,7 +1097,7 @@ __device__ __forceinline__ void sp_late_signs(const SpLateSide<NE, NI>& x, lds_u
 }
 
 // Publishes the signs of x.eff (and, if asked, the share sum |x.eff|, scaled by 2^-cexp below 1 so that bit 62 can carry a tag
-// that flips with every write of the word), reads everybody's: x.old becomes the new signs, flip the bits that changed, c this
+// that flips with every write of the word; shares below 2^-1022 of that scale, which c does not feel, lose bits), reads everybody's: x.old becomes the new signs, flip the bits that changed, c this
 // lane's part of the sum of the shares (their wave sum is c, in the order of sp_sum_scalar).  false: a wait ran out.
 template <int NE, int NI, bool SHARE>
 __device__ __forceinline__ bool sp_late_exchange(int lane, const SpLateArgs& a, uint64_t* xb, uint32_t seq, SpLateSide<NE, NI>& x, int cexp, int wait,

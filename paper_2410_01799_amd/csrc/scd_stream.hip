@@ -131,7 +131,8 @@ __device__ __forceinline__ uint64_t ps_load(const uint64_t* p)
 }
 
 // Published sums are scaled by a power of two below 1 (a.xexp, a.cexp), so that the top bit of their exponents is free for a tag
-// that flips with every write of a slot: two f32 or one f64 fill an 8-byte word, which is stored and seen whole.
+// that flips with every write of a slot: two f32 or one f64 fill an 8-byte word, which is stored and seen whole.  What lies below
+// 2^-126 (f32) or 2^-1022 (f64) once scaled loses bits; infinities and NaNs have no room (the host lets none come here).
 constexpr uint32_t kPsTag = 0x40000000u;
 __device__ __forceinline__ uint32_t ps_tag(uint32_t seq) { return (((seq + 1u) >> 1) & 1u) ? kPsTag : 0u; }
 typedef unsigned ps_u4 __attribute__((ext_vector_type(4)));

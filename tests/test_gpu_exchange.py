@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 import torch
 
-from helpers import CURVE_RTOL
+from helpers import CURVE_RTOL, dense
 
 pytestmark = pytest.mark.gpu
 
@@ -87,3 +87,29 @@ def test_least_squares_powers_of_two(scd, m, n):
     base = scd.scd_lsq_decompose(A, w, seed)
     for k in (-300, 300):
         same_up_to(base, scd.scd_lsq_decompose(A * 2.0 ** k, w, seed), k)
+
+
+@pytest.mark.parametrize("options,engine", [({}, 1), ({"resident": 0, "sparse": 0}, 3)], ids=["resident", "stream"])
+@pytest.mark.parametrize("dtype,low", [(torch.float32, -105), (torch.float64, -990)], ids=["f32", "f64"])
+@pytest.mark.parametrize("m,n", [(512, 512), (300, 260)])
+def test_small_sums_beside_large_ones(scd, m, n, dtype, low, options, engine):
+    """Columns of size 2^low beside columns of size 1: within the range that the words keep, so the signs of their sums count.
+    Odd whole numbers, so that the columns' sums are exact and those of the rows, over an odd number of large columns, not zero."""
+    g = np.random.Generator(np.random.PCG64(1))
+    x = 2.0 * g.integers(-4, 4, (m, n)) + 1.0
+    size = np.where(np.arange(n) % 7 < 3, 2.0 ** low, 1.0)
+    if (size == 1.0).sum() % 2 == 0:
+        size[n - 1] = 2.0 ** low if size[n - 1] == 1.0 else 1.0
+    A = torch.from_numpy(x * size).to(dtype).cuda()
+    out = []
+    for opts in (options, {"resident": 0, "sparse": 0, "persistent_stream": 0}):
+        with scd.ScdContext(A, 1, 5, options=opts) as ctx:
+            assert ctx.engine()["engine"] == (engine if opts is options else 0)
+            ctx.set_max_iters(1)
+            ctx.run(1)
+            out.append(ctx.results())
+    assert torch.equal(out[0]["signs"][0], out[1]["signs"][0]) and torch.equal(out[0]["signs"][1], out[1]["signs"][1])
+    S = out[0]["signs"][0][0].cpu().numpy().view(np.uint64)
+    T = out[0]["signs"][1][0].cpu().numpy().view(np.uint64)
+    v = dense(S, m) @ x
+    assert np.array_equal(dense(T, n), np.where(v < 0, -1.0, 1.0))
