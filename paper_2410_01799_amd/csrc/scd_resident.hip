@@ -70,7 +70,7 @@ __global__ void __launch_bounds__(kResThreads) resident_exchange_probe_kernel(ui
     __syncthreads();
     for (uint32_t r = 1; r <= (uint32_t)rounds; ++r) {
         const uint32_t half = (r & 1u) * gridDim.x;
-        if (tid < N / 2) res_publish(buf + (size_t)(half + g) * kResSlotWords + tid, sum[2 * tid] * 0.01f, sum[2 * tid + 1] * 0.01f + 1e-3f, res_tag(r));
+        if (tid < N / 2) res_publish(buf + (size_t)(half + g) * kResSlotWords + tid, sum[2 * tid] * 0.01f, sum[2 * tid + 1] * 0.01f + 1e-3f, exchange_tag(r));
         for (int d = 0; d < 16; ++d) __builtin_amdgcn_s_sleep(1);
         double s[Read::Q] = {}, x0, x1;
         int spin = 0;

@@ -4,6 +4,7 @@
 #include <type_traits>
 
 #include "scd_device.h"
+#include "scd_exchange.h"
 #include "scd_resident_shape.h"
 #include "scd_rng.h"
 
@@ -71,7 +72,7 @@ __device__ __forceinline__ double wave_sum_res(double a)
 //   col phase   q_l = sum over the block's rows of +-R_il (signs s), published to the 16 workgroups
 //               of the same block column -> v_l, t_l, and this column block's share of c = sum |v_l|
 //
-// Exchange: values and tag travel in one 8-byte store (the datum is its own flag, see res_tag below), read
+// Exchange: values and tag travel in one 8-byte store (the datum is its own flag, see exchange_tag), read
 // back with loads that bypass the non-coherent caches; no counter, no fence.  Slots alternate by the
 // parity of the sequence number: a workgroup can only be one exchange ahead of the readers of its
 // slot, because finishing exchange e+1 needs data its readers publish after they have read e.
@@ -115,15 +116,12 @@ __device__ __forceinline__ double uniform_f64(double v)
 // Words of an exchange.  A sum that is published is scaled by a power of two so that it stays below 2 (a.xexp; a sum of up to
 // 256 entries is at most 16 ||R||_F), which leaves the top bit of its exponent clear: that bit carries the tag, so that
 // two f32 sums or one f64 sum fill an 8-byte word, a word is still stored and seen whole, and nothing else has to tell a fresh
-// word from the one that it replaces.  The tag flips each time that a slot is written (slots alternate, so every second
-// exchange); cleared slots are older than exchange 1.  f32 sums below 2^-126 of that scale lose bits, f64 ones 2^-1022; infinities
+// word from the one that it replaces.  f32 sums below 2^-126 of that scale lose bits, f64 ones 2^-1022; infinities
 // and NaNs have no room (the host lets none come here).
 // A slot is read 16 bytes a lane.  Us per exchange of 256 sums alone, among 16 partners on one die / on eight: one f32 and a
 // 32-bit sequence number in a word, read 8 bytes a lane 1.55 / 1.85, read 16 bytes a lane 1.60 / 1.88, two f32 in a word
 // read 16 bytes a lane 1.17 / 1.49; f64 as two such words 2.50 / 2.87, as one word 1.58 / 1.89.
-constexpr uint32_t kResTagBit = 0x40000000u;
-__device__ __forceinline__ uint32_t res_tag(uint32_t seq) { return (((seq + 1u) >> 1) & 1u) ? kResTagBit : 0u; }
-__device__ __forceinline__ uint32_t res_tagged(uint32_t v, uint32_t tag) { return (v & ~kResTagBit) | tag; }
+__device__ __forceinline__ uint32_t res_tagged(uint32_t v, uint32_t tag) { return (v & ~kTagBit) | tag; }
 __device__ __forceinline__ float res_scaled(float v, int e) { return __builtin_ldexpf(v, e); }
 __device__ __forceinline__ double res_scaled(double v, int e) { return __builtin_ldexp(v, e); }
 
@@ -158,12 +156,6 @@ struct ResRead {
     static_assert(P < 2 || (L >= 4 && L <= 16 && U * L % 64 == 0 && U * L <= kResThreads), "lanes of a piece");
 };
 
-typedef unsigned res_u4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ res_u4 res_load16(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff)
-{
-    return __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff, (int)soff, (int)0x80000010);  // volatile, device scope
-}
-
 // H partners' 16 bytes (none where `sums` is not set, the same for a wave), plus NX / 2 scalars of one partner (NX = 0, 2 or 4
 // words; only what the phase at hand uses is published and read: every word is a trip through the fabric), all loads in flight together.
 // If any word of the wave is still from an earlier exchange, all are read again (re-reads are rare once the first read is
@@ -174,24 +166,24 @@ __device__ __forceinline__ bool res_gather(__amdgpu_buffer_rsrc_t rs, uint32_t s
                                            uint32_t seq, int max_spin, double (&s)[16 / sizeof(TX)], double& x0, double& x1, int& spin)
 {
     static_assert(NX == 0 || NX == 2 || NX == 4, "none, one or two scalars");
-    const uint32_t tag = res_tag(seq);
-    res_u4 w[H], x[2];
+    const uint32_t tag = exchange_tag(seq);
+    u32x4 w[H], x[2];
 #pragma unroll
-    for (int q = 0; q < H; ++q) w[q] = res_u4{tag, tag, tag, tag};
+    for (int q = 0; q < H; ++q) w[q] = u32x4{tag, tag, tag, tag};
     for (;;) {
         if (sums) {
 #pragma unroll
-            for (int q = 0; q < H; ++q) w[q] = res_load16(rs, voff, soff + (uint32_t)q * stride);
+            for (int q = 0; q < H; ++q) w[q] = exchange_load16(rs, voff, soff + (uint32_t)q * stride);
         }
 #pragma unroll
-        for (int q = 0; q < NX / 2; ++q) x[q] = res_load16(rs, xoff + 16u * (uint32_t)q, soff);
+        for (int q = 0; q < NX / 2; ++q) x[q] = exchange_load16(rs, xoff + 16u * (uint32_t)q, soff);
         uint32_t stale = 0;
 #pragma unroll
         for (int q = 0; q < H; ++q) {
             stale |= (w[q].y ^ tag) | (w[q].w ^ tag);
             if constexpr (sizeof(TX) == 4) stale |= (w[q].x ^ tag) | (w[q].z ^ tag);
         }
-        stale &= kResTagBit;
+        stale &= kTagBit;
 #pragma unroll
         for (int q = 0; q < NX / 2; ++q) stale |= (x[q].y ^ seq) | (x[q].w ^ seq);
         if (__ballot(stale != 0) == 0) break;
@@ -203,10 +195,10 @@ __device__ __forceinline__ bool res_gather(__amdgpu_buffer_rsrc_t rs, uint32_t s
         double v[16 / sizeof(TX)];
         if constexpr (sizeof(TX) == 4) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = (double)__uint_as_float(w[q][e] & ~kResTagBit);
+            for (int e = 0; e < 4; ++e) v[e] = (double)__uint_as_float(w[q][e] & ~kTagBit);
         } else {
-            v[0] = __hiloint2double((int)(w[q].y & ~kResTagBit), (int)w[q].x);
-            v[1] = __hiloint2double((int)(w[q].w & ~kResTagBit), (int)w[q].z);
+            v[0] = __hiloint2double((int)(w[q].y & ~kTagBit), (int)w[q].x);
+            v[1] = __hiloint2double((int)(w[q].w & ~kTagBit), (int)w[q].z);
         }
 #pragma unroll
         for (int e = 0; e < (int)(16 / sizeof(TX)); ++e) s[e] = q == 0 ? v[e] : s[e] + v[e];
@@ -286,33 +278,6 @@ struct ResVec<double> {
     }
     static __device__ __forceinline__ void put(double* p, const double* x) { *(double2*)p = make_double2(x[0], x[1]); }
 };
-
-// Sum over the four 16-lane rows of a wave for two registers at once: the row-swap instructions of gfx950 exchange
-// the odd rows (the upper half of the wave) of one register with the even rows (the lower half) of the other, after
-// which one addition serves both.  half16(a, b): even rows hold a's pair sums, odd rows b's.  half32 of two such:
-// row r of the result holds the full sum of the r-th of the four registers.
-__device__ __forceinline__ float half16(float a, float b)
-{
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ float half32(float a, float b)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ double half16(double a, double b)
-{
-    const auto l = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
-    const auto h = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
-    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-}
-__device__ __forceinline__ double half32(double a, double b)
-{
-    const auto l = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
-    const auto h = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
-    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-}
 
 // Sum over groups of N = 4, 8 or 16 neighbouring lanes, the same bits in every lane of a group.
 template <int N>
@@ -628,9 +593,9 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
                     const TX pv = res_scaled((TX)prow, -a.xexp);
                     if constexpr (sizeof(TX) == 4) {
                         const float next = dpp_f32<0xB1>(pv);  // lane ^ 1: the row after
-                        if (tc < TR && !(lane & 1)) res_publish(mine + (tr * TR + tc) / 2, pv, next, res_tag(seq_u));
+                        if (tc < TR && !(lane & 1)) res_publish(mine + (tr * TR + tc) / 2, pv, next, exchange_tag(seq_u));
                     } else {
-                        if (tc < TR) res_publish(mine + tr * TR + tc, pv, res_tag(seq_u));
+                        if (tc < TR) res_publish(mine + tr * TR + tc, pv, exchange_tag(seq_u));
                     }
                     if (tid == 0) {
                         res_publish_scalar(mine + WM, cpart, seq_u);
@@ -828,8 +793,8 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
                         for (int q = 0; q < NWV; ++q) t += w[e][q];
                         s[e] = res_scaled((TX)t, -a.xexp);
                     }
-                    if constexpr (C == 2) res_publish(mine + tid, s[0], s[1], res_tag(seq_v));
-                    else res_publish(mine + tid, s[0], res_tag(seq_v));
+                    if constexpr (C == 2) res_publish(mine + tid, s[0], s[1], exchange_tag(seq_v));
+                    else res_publish(mine + tid, s[0], exchange_tag(seq_v));
                 }
                 if (norm_stage == 2 && tid == kResThreads - 1) res_publish_scalar(mine + WN, frow, seq_v);
             }

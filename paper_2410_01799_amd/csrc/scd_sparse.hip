@@ -23,6 +23,7 @@
 // terms live in LDS, the products are corrected from their bitsets, one pass flushes the list and, while
 // it is at it, forms the first products R' t_0 of the next terms (their random starts are known in advance).
 #include "scd_device.h"
+#include "scd_exchange.h"
 #include "scd_rng.h"
 
 #include <type_traits>
@@ -135,21 +136,6 @@ __device__ __forceinline__ double sp_sum_xor32(double a)
     const auto rh = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
     return __longlong_as_double((long long)(((unsigned long long)rh[0] << 32) | rl[0])) +
            __longlong_as_double((long long)(((unsigned long long)rh[1] << 32) | rl[1]));
-}
-
-// Half-width sums of two registers: even 16-lane rows (the lower 32 lanes) end with a's sum over distance 16 (32), the others
-// with b's.
-__device__ __forceinline__ double sp_half16(double a, double b)
-{
-    const auto l = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
-    const auto h = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
-    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-}
-__device__ __forceinline__ double sp_half32(double a, double b)
-{
-    const auto l = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
-    const auto h = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
-    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
 }
 
 // Sum of an int over the 64 lanes (every lane gets it) and inclusive prefix sum across the lanes, both
@@ -931,9 +917,9 @@ __device__ void sp_flush_rows(TE* __restrict__ Y, int64_t ld, int64_t row0, int 
 #pragma unroll
                     for (int j = 0; j < NV; ++j) vv[r * NV + j] = ps[r][j];
 #pragma unroll
-                for (int i = 0; i < 16; ++i) vv[i] = sp_half32(vv[i], vv[i + 16]);
+                for (int i = 0; i < 16; ++i) vv[i] = half32(vv[i], vv[i + 16]);
 #pragma unroll
-                for (int i = 0; i < 8; ++i) vv[i] = sp_half16(vv[i], vv[i + 8]);
+                for (int i = 0; i < 8; ++i) vv[i] = half16(vv[i], vv[i + 8]);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const bool upper = (lane & 8) != 0;
@@ -1103,7 +1089,6 @@ template <int NE, int NI, bool SHARE>
 __device__ __forceinline__ bool sp_late_exchange(int lane, const SpLateArgs& a, uint64_t* xb, uint32_t seq, SpLateSide<NE, NI>& x, int cexp, int wait,
                                                  uint32_t (&flip)[NI], double& c, int& spins, bool& late)
 {
-    constexpr uint32_t kTag = 0x40000000u;
     constexpr int NC = SHARE ? kSpGrid / kWave : 0;
     const int g = blockIdx.x;
 #pragma unroll
@@ -1112,7 +1097,7 @@ __device__ __forceinline__ bool sp_late_exchange(int lane, const SpLateArgs& a, 
         if (lane < 2 && i * kWave + lane * 32 < x.slice)
             sp_store_tagged(xb + (2 * i + lane) * kSpGrid + g, lane ? (uint32_t)(bal >> 32) : (uint32_t)bal, seq);
     }
-    const uint32_t ctag = (((seq + 1u) >> 1) & 1u) ? kTag : 0u;
+    const uint32_t ctag = exchange_tag(seq);
     if constexpr (SHARE) {
         double t = 0.0;
 #pragma unroll
@@ -1120,7 +1105,7 @@ __device__ __forceinline__ bool sp_late_exchange(int lane, const SpLateArgs& a, 
         t = __builtin_ldexp(t, -cexp);
         if (lane == 0)
             __hip_atomic_store(xb + kSpLateWords * kSpGrid + g,
-                               ((uint64_t)(((uint32_t)__double2hiint(t) & ~kTag) | ctag) << 32) | (uint64_t)(uint32_t)__double2loint(t),
+                               ((uint64_t)(((uint32_t)__double2hiint(t) & ~kTagBit) | ctag) << 32) | (uint64_t)(uint32_t)__double2loint(t),
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     uint64_t w[NI], cw[NC + 1];
@@ -1139,7 +1124,7 @@ __device__ __forceinline__ bool sp_late_exchange(int lane, const SpLateArgs& a, 
         for (int it = 0; it < NI; ++it) stale |= (uint32_t)(w[it] >> 32) ^ seq;
 #pragma unroll
         for (int i = 0; i < NC; ++i) cstale |= (uint32_t)(cw[i] >> 32) ^ ctag;
-        if (__ballot((stale | (cstale & kTag)) != 0u) == 0) break;
+        if (__ballot((stale | (cstale & kTagBit)) != 0u) == 0) break;
         if (++spin > a.max_spin) return false;
         __builtin_amdgcn_s_sleep(1);
     }
@@ -1154,7 +1139,7 @@ __device__ __forceinline__ bool sp_late_exchange(int lane, const SpLateArgs& a, 
         double t = 0.0;
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
-            const double v = __builtin_ldexp(__hiloint2double((int)((uint32_t)(cw[i] >> 32) & ~kTag), (int)(uint32_t)cw[i]), cexp);
+            const double v = __builtin_ldexp(__hiloint2double((int)((uint32_t)(cw[i] >> 32) & ~kTagBit), (int)(uint32_t)cw[i]), cexp);
             t += lane + i * kWave < a.grid ? v : 0.0;
         }
         c = t;

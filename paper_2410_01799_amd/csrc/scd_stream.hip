@@ -18,7 +18,7 @@
 //   hop 2       the owners publish sign bits and shares, every workgroup gathers all of them: the full t,
 //               c (and ||R||_F^2 after an update), added in the same order everywhere, so that every
 //               workgroup takes the same decision of line 8 without any further communication.
-// Exchange: values and tag (a free bit of the exponent, see kPsTag; sign bits: a sequence number) travel in one 8-byte word and
+// Exchange: values and tag (a free bit of the exponent, see kTagBit; sign bits: a sequence number) travel in one 8-byte word and
 // are read back with device-scope loads; slots alternate by the parity of the sequence number.  Every wait is bounded; when one
 // runs out all workgroups leave and the host reports SCD_ETIMEOUT.  No float atomics: bit-identical reruns.
 // What an alternation costs beyond its pass is a chain of LDS steps, barriers and the two hops: a barrier that joins a
@@ -31,6 +31,7 @@
 // chunks counted one by one, us per pass before / now: 4000x3000x3 37.5 / 32.1, 2000x1500x3 20.4 / 15.5, 640x480x3 11.8 / 9.6,
 // 1024x1024x3 f64 16.7 / 12.8, 5000x2048 f32 14.7 / 10.8, 3000x5000 f64 29.8 / 21.7, 700x16384 36.1 / 22.3, 8192x1024 14.8 / 14.7.
 #include "scd_device.h"
+#include "scd_exchange.h"
 #include "scd_rng.h"
 
 namespace scd {
@@ -133,31 +134,24 @@ __device__ __forceinline__ uint64_t ps_load(const uint64_t* p)
 // Published sums are scaled by a power of two below 1 (a.xexp, a.cexp), so that the top bit of their exponents is free for a tag
 // that flips with every write of a slot: two f32 or one f64 fill an 8-byte word, which is stored and seen whole.  What lies below
 // 2^-126 (f32) or 2^-1022 (f64) once scaled loses bits; infinities and NaNs have no room (the host lets none come here).
-constexpr uint32_t kPsTag = 0x40000000u;
-__device__ __forceinline__ uint32_t ps_tag(uint32_t seq) { return (((seq + 1u) >> 1) & 1u) ? kPsTag : 0u; }
-typedef unsigned ps_u4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ ps_u4 ps_load16(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff)
-{
-    return __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff, (int)soff, (int)0x80000010);  // volatile, device scope
-}
 // 16 bytes of sums (two words)
 __device__ __forceinline__ void ps_publish16(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff, const float* v, int e, uint32_t tag)
 {
-    ps_u4 w;
+    u32x4 w;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) w[i] = (__float_as_uint(__builtin_ldexpf(v[i], -e)) & ~kPsTag) | tag;
-    __builtin_amdgcn_raw_buffer_store_b128(w, rs, (int)voff, (int)soff, (int)0x80000010);
+    for (int i = 0; i < 4; ++i) w[i] = (__float_as_uint(__builtin_ldexpf(v[i], -e)) & ~kTagBit) | tag;
+    __builtin_amdgcn_raw_buffer_store_b128(w, rs, (int)voff, (int)soff, kDeviceScope);
 }
 __device__ __forceinline__ void ps_publish16(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff, const double* v, int e, uint32_t tag)
 {
-    ps_u4 w;
+    u32x4 w;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const double x = __builtin_ldexp(v[i], -e);
         w[2 * i] = (uint32_t)__double2loint(x);
-        w[2 * i + 1] = ((uint32_t)__double2hiint(x) & ~kPsTag) | tag;
+        w[2 * i + 1] = ((uint32_t)__double2hiint(x) & ~kTagBit) | tag;
     }
-    __builtin_amdgcn_raw_buffer_store_b128(w, rs, (int)voff, (int)soff, (int)0x80000010);
+    __builtin_amdgcn_raw_buffer_store_b128(w, rs, (int)voff, (int)soff, kDeviceScope);
 }
 
 // Hop 1, one thread: 16 bytes of the partial sums of members q, q + Q, q + 2 Q, ... < G (member i's at voff + i * slot), added in
@@ -168,17 +162,17 @@ __device__ __forceinline__ bool ps_hop1_gather(__amdgpu_buffer_rsrc_t rs, uint32
 {
 #pragma nounroll
     for (int m0 = q; m0 < G; m0 += NF * Q) {
-        ps_u4 w[NF];
+        u32x4 w[NF];
         for (;;) {
             uint32_t stale = 0u;
 #pragma unroll
-            for (int i = 0; i < NF; ++i) w[i] = ps_load16(rs, voff + (uint32_t)(m0 + i * Q < G ? m0 + i * Q : m0) * slot, soff);
+            for (int i = 0; i < NF; ++i) w[i] = exchange_load16(rs, voff + (uint32_t)(m0 + i * Q < G ? m0 + i * Q : m0) * slot, soff);
 #pragma unroll
             for (int i = 0; i < NF; ++i) {
                 stale |= (w[i].y ^ tag) | (w[i].w ^ tag);
                 if constexpr (sizeof(TE) == 4) stale |= (w[i].x ^ tag) | (w[i].z ^ tag);
             }
-            if (!(stale & kPsTag)) break;
+            if (!(stale & kTagBit)) break;
             if (++spin > max_spin) return false;
             __builtin_amdgcn_s_sleep(1);
         }
@@ -187,30 +181,15 @@ __device__ __forceinline__ bool ps_hop1_gather(__amdgpu_buffer_rsrc_t rs, uint32
             if (m0 + i * Q < G) {
                 if constexpr (sizeof(TE) == 4) {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) s[e] += (double)__uint_as_float(w[i][e] & ~kPsTag);
+                    for (int e = 0; e < 4; ++e) s[e] += (double)__uint_as_float(w[i][e] & ~kTagBit);
                 } else {
-                    s[0] += __hiloint2double((int)(w[i].y & ~kPsTag), (int)w[i].x);
-                    s[1] += __hiloint2double((int)(w[i].w & ~kPsTag), (int)w[i].z);
+                    s[0] += __hiloint2double((int)(w[i].y & ~kTagBit), (int)w[i].x);
+                    s[1] += __hiloint2double((int)(w[i].w & ~kTagBit), (int)w[i].z);
                 }
             }
         }
     }
     return true;
-}
-
-// Half-width sums of two registers: even 16-lane rows (the lower 32 lanes) end with a's sum over distance 16 (32), the others
-// with b's.
-__device__ __forceinline__ double ps_half16(double a, double b)
-{
-    const auto l = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
-    const auto h = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
-    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
-}
-__device__ __forceinline__ double ps_half32(double a, double b)
-{
-    const auto l = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
-    const auto h = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
-    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
 }
 
 // Of `rows` rows, those kept in LDS where there is room for `room`: whole batches, unless all fit (a batch costs a join across the waves
@@ -662,7 +641,7 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
         // ================= hop 1: publish the partial column sums, reduce the own slice.  A thread's chunk of columns is 16 bytes
         // of words: every store instruction of a wave writes 1 KB
         {
-            const uint32_t soff = ((seq & 1u) * (uint32_t)G + (uint32_t)g) * slot1, tag = ps_tag(seq);
+            const uint32_t soff = ((seq & 1u) * (uint32_t)G + (uint32_t)g) * slot1, tag = exchange_tag(seq);
 #pragma unroll
             for (int c = 0; c < CPT; ++c) {
                 const int64_t ch = tid + c * kPsThreads;
@@ -689,16 +668,16 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
                 const uint32_t voff = (uint32_t)c0 * (uint32_t)sizeof(TE) + (uint32_t)jc * 16u, soff = (seq & 1u) * (uint32_t)G * slot1;
                 int spin = 0;
                 // members q, q + Q, ... in that order
-                if (G > 4 * Q) ok = ps_hop1_gather<TE, CPT >= 8 ? 2 : 8>(xrs, voff, soff, q, Q, G, slot1, ps_tag(seq), a.max_spin, x, spin);
-                else ok = ps_hop1_gather<TE, CPT >= 8 ? 2 : 4>(xrs, voff, soff, q, Q, G, slot1, ps_tag(seq), a.max_spin, x, spin);
+                if (G > 4 * Q) ok = ps_hop1_gather<TE, CPT >= 8 ? 2 : 8>(xrs, voff, soff, q, Q, G, slot1, exchange_tag(seq), a.max_spin, x, spin);
+                else ok = ps_hop1_gather<TE, CPT >= 8 ? 2 : 4>(xrs, voff, soff, q, Q, G, slot1, exchange_tag(seq), a.max_spin, x, spin);
                 spins += spin;
             }
             // the groups of a wave are joined first, the registers halving where two distances are left
             double* mine = part + (ncp <= 64 ? wv : q) * stride + jc * VE;
             if (ncp <= 16) {
                 double v;
-                if constexpr (VE == 4) v = ps_half32(ps_half16(x[0], x[1]), ps_half16(x[2], x[3]));
-                else v = ps_swap_sum_f64<32>(ps_half16(x[0], x[1]));
+                if constexpr (VE == 4) v = half32(half16(x[0], x[1]), half16(x[2], x[3]));
+                else v = ps_swap_sum_f64<32>(half16(x[0], x[1]));
                 if (ncp <= 8) v += ps_dpp_f64<0x140, 0x141>(v);  // lane ^ 8
                 if (ncp <= 4) v += ps_dpp_f64<0x141, 0x1B>(v);   // lane ^ 4
                 if (ncp <= 2) v += ps_dpp_f64<0x4E, 0>(v);       // lane ^ 2
@@ -706,10 +685,10 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
             } else if (ncp == 32) {
                 const int up = lane >> 5;
                 if constexpr (VE == 4) {
-                    mine[2 * up] = ps_half32(x[0], x[2]);
-                    mine[2 * up + 1] = ps_half32(x[1], x[3]);
+                    mine[2 * up] = half32(x[0], x[2]);
+                    mine[2 * up + 1] = half32(x[1], x[3]);
                 } else {
-                    mine[up] = ps_half32(x[0], x[1]);
+                    mine[up] = half32(x[0], x[1]);
                 }
             } else {
 #pragma unroll
@@ -777,13 +756,13 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
         }
         PS_TICK(3);
         // ================= hop 2: publish the slice's sign bits and scalars, gather everybody's
-        const uint32_t tag = ps_tag(seq);
+        const uint32_t tag = exchange_tag(seq);
         {
             uint64_t* mine = a.xq + ((size_t)(seq & 1u) * G + g) * kPsSlot2;
             if (tid < tw) ps_store_tagged(mine + tid, sh.tw32[tid], seq);
             auto scalar = [&](uint64_t* p, double x) {
                 x = __builtin_ldexp(x, -a.cexp);
-                ps_store_tagged(p, (uint32_t)__double2loint(x), ((uint32_t)__double2hiint(x) & ~kPsTag) | tag);
+                ps_store_tagged(p, (uint32_t)__double2loint(x), ((uint32_t)__double2hiint(x) & ~kTagBit) | tag);
             };
             if (!tensor) {
                 if (tid == 64) {
@@ -818,7 +797,7 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
                 const int mem = (int)(((float)idx + 0.5f) * rp), wd = idx - mem * per;
                 const bool sum = wd >= tw && wd < tw + nsc;
                 where[it] = idx < items ? mem * kPsSlot2 + wd : -1;
-                bits[it] = sum ? kPsTag : ~0u;
+                bits[it] = sum ? kTagBit : ~0u;
                 want[it] = sum ? tag : seq;
             }
             for (int d = 0; d < a.poll_delay / 4; ++d) __builtin_amdgcn_s_sleep(1);
@@ -858,7 +837,7 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
                                 if (4 * wd + b < sbytes && b0 + b < nbytes) tbytes[b0 + b] = (uint8_t)(v >> (8 * b));
                         } else if (wd < tw + nsc) {
                             sh.scal[2 * (wd - tw)][mem] = v;
-                            sh.scal[2 * (wd - tw) + 1][mem] = (uint32_t)(w[it] >> 32) & ~kPsTag;
+                            sh.scal[2 * (wd - tw) + 1][mem] = (uint32_t)(w[it] >> 32) & ~kTagBit;
                         } else {
                             sh.scal[nsc + wd - tw][mem] = v;
                         }
