@@ -1103,7 +1103,7 @@ bool pstream_supported(scd_dtype dt, int order, const int64_t* dims, int limit, 
         geo->cs = (int)cs;
         geo->lds_rows = (int)lds_rows;
         geo->lds_bytes = ((((size_t)lds_rows * (size_t)n * es) + 15) & ~(size_t)15) + fixed;
-        geo->xp_bytes = (size_t)2 * (size_t)grid * (size_t)n * (dt == SCD_F32 ? 1 : 2) * 8;
+        geo->xp_bytes = (size_t)2 * (size_t)grid * (size_t)n * es;
         geo->xq_bytes = (size_t)2 * (size_t)grid * kPsSlot2 * 8;
     }
     return true;

@@ -98,7 +98,7 @@ def test_stream_engine_geometry_stays_inside_what_the_kernel_assumes():
                 assert 0 <= lds_rows <= rpw
                 need = -(-lds_rows * n * es // 16) * 16 + -(-n * es // 16) * 16 + 2 * nw * 8 + w2 * 8 + 2 * (-(-rpw // 16) * 16)
                 assert need < geo["lds_bytes"] <= max_lds + 64, (dims, limit)
-                assert geo["xp_bytes"] == 2 * G * n * (1 if es == 4 else 2) * 8 and geo["xq_bytes"] == 2 * G * slot2 * 8
+                assert geo["xp_bytes"] == 2 * G * n * es and geo["xq_bytes"] == 2 * G * slot2 * 8
     assert seen > 60
     # shapes it must refuse: rows that are no multiple of 16 bytes or longer than 64 KB, too few workgroups for the
     # slices, orders above 3, a last mode above 4
