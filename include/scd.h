@@ -22,7 +22,7 @@
  *    ceil(n/64) words; padding bits are 0.  Sign matrices are term-major: term j of mode i
  *    starts at word j*ceil(dims[i]/64).
  *  - sgn(x) = -1 iff x < 0 (both zeros give +1).  The resident and the streaming engine exchange their sums with half the
- *    range of the exponent, set by ||R||_F: a signed row or column sum of an f32 matrix below 2^-114 ||R||_F (f64: 2^-1010)
+ *    range of the exponent, set by ||R||_F: a signed row or column sum of an f32 matrix below 2^-114 ||R||_F (f64: 2^-370)
  *    may lose bits or count as zero.  Above that every bit of the type is kept.
  *  - Coefficients are normalised, c_j = <s_j, R_{j-1} t_j> / (product of dims), which is what the
  *    definition above needs; Algorithm 5 line 10 divides by mn at the update, the same sequence.

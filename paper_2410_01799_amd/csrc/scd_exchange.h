@@ -14,6 +14,21 @@ namespace scd {
 constexpr uint32_t kTagBit = 0x40000000u;
 __device__ __forceinline__ uint32_t exchange_tag(uint32_t seq) { return (((seq + 1u) >> 1) & 1u) ? kTagBit : 0u; }
 
+// A word of one f64 sum that travels in accesses of 16 bytes.  Only of naturally aligned accesses of up to 64 bits does the
+// memory model say that they are seen whole, and of wider ones no more than that each of their 32 bits are: so both halves of the
+// word carry the tag.  The sum is scaled below 2^-511 (kF64Exp below what suffices for an f32 or an atomic word), which leaves
+// two bits of its exponent clear: one for the tag, one for the lowest bit of the mantissa, whose place takes the other tag.
+constexpr int kF64Exp = 512;
+__device__ __forceinline__ void exchange_pack(double v, uint32_t tag, uint32_t& lo, uint32_t& hi)
+{
+    lo = ((uint32_t)__double2loint(v) & ~1u) | (tag >> 30);
+    hi = (uint32_t)__double2hiint(v) | ((uint32_t)__double2loint(v) & 1u) << 29 | tag;
+}
+__device__ __forceinline__ double exchange_unpack(uint32_t lo, uint32_t hi)
+{
+    return __hiloint2double((int)(hi & 0x9FFFFFFFu), (int)((lo & ~1u) | ((hi >> 29) & 1u)));
+}
+
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kDeviceScope = (int)0x80000010;  // volatile, device scope: past the caches that are not coherent
 __device__ __forceinline__ u32x4 exchange_load16(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff)

@@ -75,7 +75,7 @@ __global__ void __launch_bounds__(kResThreads) resident_exchange_probe_kernel(ui
         double s[Read::Q] = {}, x0, x1;
         int spin = 0;
         if (tid < Read::waves * 64) {
-            if (!res_gather<float, Read::H, 0>(rs, (half + (uint32_t)(g / P * P)) * kResSlotWords * 8u, off, kResSlotWords * 8, true, 0, r, max_spin, s, x0,
+            if (!res_gather<float, Read::H, false, false>(buf, rs, (half + (uint32_t)(g / P * P)) * kResSlotWords * 8u, off, kResSlotWords * 8, true, 0, r, max_spin, s, x0,
                                                x1, spin))
                 fail = 1;
             const double v = res_join<Read::L, Read::Q>(s, lane);
@@ -160,11 +160,12 @@ int resident_sum_bytes(scd_dtype dt, const int64_t* dims, double fro)
 // that comes before the last partner's words costs another trip to memory (0.4 us and its traffic), one that comes
 // late costs what it waits, so the optimum is just behind the arrival, which moves with the words of an exchange and with
 // what the slowest partner does before it publishes.  Rows (partners on all dies) need more than columns (one die).
-// Measured in us per alternation at (rows / columns): up to 8 x 8 workgroups at 17 / 8 2.87 (512^2), 3.10 (1024^2), f64 3.16
-// (600x400), 3.40 (1024^2), at 10 / 10 2.93, 3.18, 3.20, 3.42; 16 x 16 with at most 16 values a thread at 16 / 8 3.32 (1501x999),
-// f64 3.56, at 20 / 8 3.42, 3.57; f32 beyond at 19 / 8 3.45 (2048^2), at 18 / 14 3.56, with 256 columns a block at 19 / 11 4.37
-// (4096^2), 3.93 (1024x4096), at 18 / 8 4.62, 4.08; f64 at 23 / 8 4.02 (2048^2), 4.78 (4096x2048), at 16 / 8 4.21, 5.19, with 256
-// columns a block at 23 / 13 5.13 (2048x4096), at 22 / 8 5.41, and at 16 / 13 4.73 with two rows a thread (1024x4096), at 24 / 12 4.89.
+// Measured in us per alternation at (rows / columns): up to 8 x 8 workgroups at 17 / 8 2.87 (512^2), 3.10 (1024^2), f64 3.23
+// (600x400), 3.44 (1024^2), at 10 / 10 2.93, 3.18, f64 half a tenth more; 16 x 16 with at most 16 values a thread at 16 / 8 3.32
+// (1501x999), at 20 / 8 3.42, f64 at 17 / 8 3.61, at 16 / 8 3.69; f32 beyond at 19 / 8 3.45 (2048^2), at 18 / 14 3.56, with 256
+// columns a block at 19 / 11 4.34 (4096^2), 3.93 (1024x4096), at 18 / 8 4.62, 4.08; f64 at 23 / 8 4.03 (2048^2), at 16 / 8 4.21, with
+// eight rows a thread at 23 / 9 4.89 (4096x2048), at 23 / 8 5.07, with 256 columns a block at 23 / 13 5.16 (2048x4096), at 22 / 8
+// 5.41, and at 16 / 13 4.72 with two rows a thread (1024x4096), at 24 / 12 4.89.
 void resident_poll_delays(scd_dtype dt, const int64_t* dims, double fro, int delay, int32_t* rows, int32_t* cols)
 {
     int p = 16, tr = 8, tc = 16;
@@ -172,8 +173,9 @@ void resident_poll_delays(scd_dtype dt, const int64_t* dims, double fro, int del
     const ResSums sums = resident_sums(dt, dims[0], dims[1], fro);
     int u = delay + 1, v = delay - 8;
     if (p > 8 && sums == ResSums::wide) {
-        u = tr * tc <= 16 || tr == 2 ? delay : delay + 7;
+        u = tr * tc <= 16 ? delay + 1 : tr == 2 ? delay : delay + 7;
         if (tc == 16) v = delay - 3;
+        if (tr == 8) v = delay - 7;
     } else if (p > 8) {
         u = tr * tc <= 16 ? delay : delay + 3;
         if (tc == 16 && sums == ResSums::plain) v = delay - 5;

@@ -86,9 +86,9 @@ __device__ __forceinline__ double wave_sum_res(double a)
 //
 // f64 (TE = double): everything the exchanges carry and the tiles hold stays 64 bits wide, so a thread holds at most 64
 // values (matrices up to 4096x2048 or 2048x4096) and a word is one sum.  Us per alternation with two words a sum / with one
-// (and the best of the other engines on the same matrix): 600x400 4.56 / 3.16 (9.0), 1024x1024 4.78 / 3.40 (11.2), 1501x999
-// 6.79 / 3.56 (19.4, launch stream), 1024x4096 7.68 / 4.73 (15.2), 2048x2048 6.95 / 4.02 (13.6), 4096x2048 8.00 / 4.78 (9.7,
-// sparse), 2048x4096 7.70 / 5.13 (9.9, sparse).
+// (and the best of the other engines on the same matrix): 600x400 4.56 / 3.23 (9.0), 1024x1024 4.78 / 3.44 (11.2), 1501x999
+// 6.79 / 3.61 (19.4, launch stream), 1024x4096 7.68 / 4.72 (15.2), 2048x2048 6.95 / 4.03 (13.6), 4096x2048 8.00 / 4.89 (9.7,
+// sparse), 2048x4096 7.70 / 5.16 (9.9, sparse).
 // The sum of the 16 column-block shares of c rides on the next row-phase exchange, so the test of
 // Algorithm 4 line 8 is taken one phase late: the row phase already done with the final t is then
 // dropped.  ||R||_F^2 after an update travels the same way (block row sums, then the total).
@@ -115,12 +115,13 @@ __device__ __forceinline__ double uniform_f64(double v)
 
 // Words of an exchange.  A sum that is published is scaled by a power of two so that it stays below 2 (a.xexp; a sum of up to
 // 256 entries is at most 16 ||R||_F), which leaves the top bit of its exponent clear: that bit carries the tag, so that
-// two f32 sums or one f64 sum fill an 8-byte word, a word is still stored and seen whole, and nothing else has to tell a fresh
-// word from the one that it replaces.  f32 sums below 2^-126 of that scale lose bits, f64 ones 2^-1022; infinities
-// and NaNs have no room (the host lets none come here).
+// two f32 sums or one f64 sum (see exchange_pack) fill an 8-byte word, every 32 bits of it tell whether they are fresh, and nothing
+// else has to.  f32 sums below 2^-126 of that scale lose bits, f64 ones 2^-510; infinities and NaNs have no room (the host lets
+// none come here).
 // A slot is read 16 bytes a lane.  Us per exchange of 256 sums alone, among 16 partners on one die / on eight: one f32 and a
 // 32-bit sequence number in a word, read 8 bytes a lane 1.55 / 1.85, read 16 bytes a lane 1.60 / 1.88, two f32 in a word
-// read 16 bytes a lane 1.17 / 1.49; f64 as two such words 2.50 / 2.87, as one word 1.58 / 1.89.
+// read 16 bytes a lane 1.17 / 1.49; f64 as two such words 2.50 / 2.87, as one word 1.58 / 1.89 (before
+// it had a tag in both halves, 0.03 us an alternation; read by 64-bit loads instead an alternation takes 0.3 to 0.8 us more).
 __device__ __forceinline__ uint32_t res_tagged(uint32_t v, uint32_t tag) { return (v & ~kTagBit) | tag; }
 __device__ __forceinline__ float res_scaled(float v, int e) { return __builtin_ldexpf(v, e); }
 __device__ __forceinline__ double res_scaled(double v, int e) { return __builtin_ldexp(v, e); }
@@ -136,9 +137,18 @@ __device__ __forceinline__ void res_publish(uint64_t* p, float v0, float v1, uin
 }
 __device__ __forceinline__ void res_publish(uint64_t* p, double v, uint32_t tag)
 {
+    uint32_t lo, hi;
+    exchange_pack(v, tag, lo, hi);
+    res_store(p, lo, hi);
+}
+// The share of c, a sum over up to 256 columns of up to 4096 entries each: below 2^10 ||R||_F, so that with kShareExp more than
+// the f32 sums' scale it is below 1.  Its word is stored and read by 64-bit atomics, and the upper half alone has a tag.
+constexpr int kShareExp = 12;
+__device__ __forceinline__ void res_publish_share(uint64_t* p, double v, uint32_t tag)
+{
     res_store(p, (uint32_t)__double2loint(v), res_tagged((uint32_t)__double2hiint(v), tag));
 }
-// a scalar of any size: two words of half of it and the exchange's sequence number
+// a scalar of any size: two words of half of it and the exchange's sequence number, by 64-bit atomics too
 __device__ __forceinline__ void res_publish_scalar(uint64_t* p, double v, uint32_t seq)
 {
     res_store(p, (uint32_t)__double2loint(v), seq);
@@ -156,36 +166,40 @@ struct ResRead {
     static_assert(P < 2 || (L >= 4 && L <= 16 && U * L % 64 == 0 && U * L <= kResThreads), "lanes of a piece");
 };
 
-// H partners' 16 bytes (none where `sums` is not set, the same for a wave), plus NX / 2 scalars of one partner (NX = 0, 2 or 4
-// words; only what the phase at hand uses is published and read: every word is a trip through the fabric), all loads in flight together.
-// If any word of the wave is still from an earlier exchange, all are read again (re-reads are rare once the first read is
-// delayed a little).  soff is the same for the whole workgroup and voff in every exchange: nothing is worked out
-// between the wait and the first load.  s: the sums over the partners.
-template <typename TX, int H, int NX>
-__device__ __forceinline__ bool res_gather(__amdgpu_buffer_rsrc_t rs, uint32_t soff, uint32_t voff, uint32_t stride, bool sums, uint32_t xoff,
-                                           uint32_t seq, int max_spin, double (&s)[16 / sizeof(TX)], double& x0, double& x1, int& spin)
+// H partners' 16 bytes (none where `sums` is not set, the same for a wave), and of one partner, at xoff, its share of c (SHARE, as
+// scaled) and a scalar (SCALAR, two words later or in its place; only what the phase at hand uses is published and read: every word
+// is a trip through the fabric), all loads in flight together.  If any word of the wave is still from an earlier exchange, all are
+// read again (re-reads are rare once the first read is delayed a little).  xbuf and rs are the slots; soff is the same for the whole
+// workgroup and voff in every exchange: nothing is worked out between the wait and the first load.  s: the sums over the partners.
+template <typename TX, int H, bool SHARE, bool SCALAR>
+__device__ __forceinline__ bool res_gather(const uint64_t* xbuf, __amdgpu_buffer_rsrc_t rs, uint32_t soff, uint32_t voff, uint32_t stride, bool sums,
+                                           uint32_t xoff, uint32_t seq, int max_spin, double (&s)[16 / sizeof(TX)], double& share, double& scalar, int& spin)
 {
-    static_assert(NX == 0 || NX == 2 || NX == 4, "none, one or two scalars");
-    const uint32_t tag = exchange_tag(seq);
-    u32x4 w[H], x[2];
+    constexpr int at = SHARE ? 2 : 0;  // words before the scalar
+    const uint32_t tag = exchange_tag(seq), low = tag >> 30;
+    const char* base = (const char*)xbuf + soff;
+    auto load = [&](int word) { return __hip_atomic_load((const uint64_t*)(base + 8 * word + xoff), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    u32x4 w[H];
+    uint64_t c = 0, x0 = 0, x1 = 0;
 #pragma unroll
-    for (int q = 0; q < H; ++q) w[q] = u32x4{tag, tag, tag, tag};
+    for (int q = 0; q < H; ++q) w[q] = sizeof(TX) == 4 ? u32x4{tag, tag, tag, tag} : u32x4{low, tag, low, tag};
     for (;;) {
         if (sums) {
 #pragma unroll
             for (int q = 0; q < H; ++q) w[q] = exchange_load16(rs, voff, soff + (uint32_t)q * stride);
         }
-#pragma unroll
-        for (int q = 0; q < NX / 2; ++q) x[q] = exchange_load16(rs, xoff + 16u * (uint32_t)q, soff);
-        uint32_t stale = 0;
+        if constexpr (SHARE) c = load(0);
+        if constexpr (SCALAR) x0 = load(at), x1 = load(at + 1);
+        uint32_t stale = 0, stale_low = 0;
 #pragma unroll
         for (int q = 0; q < H; ++q) {
             stale |= (w[q].y ^ tag) | (w[q].w ^ tag);
             if constexpr (sizeof(TX) == 4) stale |= (w[q].x ^ tag) | (w[q].z ^ tag);
+            else stale_low |= (w[q].x ^ low) | (w[q].z ^ low);
         }
-        stale &= kTagBit;
-#pragma unroll
-        for (int q = 0; q < NX / 2; ++q) stale |= (x[q].y ^ seq) | (x[q].w ^ seq);
+        if constexpr (SHARE) stale |= (uint32_t)(c >> 32) ^ tag;
+        stale = (stale & kTagBit) | (stale_low & 1u);
+        if constexpr (SCALAR) stale |= ((uint32_t)(x0 >> 32) ^ seq) | ((uint32_t)(x1 >> 32) ^ seq);
         if (__ballot(stale != 0) == 0) break;
         if (++spin > max_spin) return false;
         __builtin_amdgcn_s_sleep(1);
@@ -197,14 +211,14 @@ __device__ __forceinline__ bool res_gather(__amdgpu_buffer_rsrc_t rs, uint32_t s
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = (double)__uint_as_float(w[q][e] & ~kTagBit);
         } else {
-            v[0] = __hiloint2double((int)(w[q].y & ~kTagBit), (int)w[q].x);
-            v[1] = __hiloint2double((int)(w[q].w & ~kTagBit), (int)w[q].z);
+            v[0] = exchange_unpack(w[q].x, w[q].y);
+            v[1] = exchange_unpack(w[q].z, w[q].w);
         }
 #pragma unroll
         for (int e = 0; e < (int)(16 / sizeof(TX)); ++e) s[e] = q == 0 ? v[e] : s[e] + v[e];
     }
-    if constexpr (NX >= 2) x0 = __hiloint2double((int)x[0].z, (int)x[0].x);
-    if constexpr (NX == 4) x1 = __hiloint2double((int)x[1].z, (int)x[1].x);
+    if constexpr (SHARE) share = __hiloint2double((int)((uint32_t)(c >> 32) & ~kTagBit), (int)(uint32_t)c);
+    if constexpr (SCALAR) scalar = __hiloint2double((int)(uint32_t)x1, (int)(uint32_t)x0);
     return true;
 }
 
@@ -497,7 +511,7 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
     int alternations = 0, updates = 0;
     int j = 0, warn = 0, cur = 0;
     double c_prev = -INFINITY;
-    double cpart = 0.0;      // wave 0: this column block's sum |v_l| of the last column phase
+    double cpart = 0.0;      // wave 0: this column block's sum |v_l| of the last column phase (several workgroups: times 2^-xexp)
     double fsq_block = 0.0;  // wave 0: sum of squares of this block after the last update
     double frow = 0.0;       // ... of this block row
     int norm_stage = 0;      // 1: fsq_block to publish (row exchange); 2: frow to publish (col exchange)
@@ -510,6 +524,7 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
     const uint32_t off_u = (uint32_t)(tid % RowRead::L * RowRead::H * kResSlotWords) * 8u + (uint32_t)(tid / RowRead::L) * 16u;
     const uint32_t off_v = (uint32_t)(tid % ColRead::L * ColRead::H * P * kResSlotWords) * 8u + (uint32_t)(tid / ColRead::L) * 16u;
     const int wave = __builtin_amdgcn_readfirstlane(wv);
+    const int xexp = a.xexp + (sizeof(TX) == 8 ? kF64Exp : 0);  // sums are published times 2^-xexp
 
     for (;;) {
         if (!LSQ && k >= a.w_target && norm_stage == 0) break;
@@ -590,7 +605,7 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
                 ++seq_u;
                 {
                     uint64_t* mine = res_slot(a, 0, seq_u, wg);
-                    const TX pv = res_scaled((TX)prow, -a.xexp);
+                    const TX pv = res_scaled((TX)prow, -xexp);
                     if constexpr (sizeof(TX) == 4) {
                         const float next = dpp_f32<0xB1>(pv);  // lane ^ 1: the row after
                         if (tc < TR && !(lane & 1)) res_publish(mine + (tr * TR + tc) / 2, pv, next, exchange_tag(seq_u));
@@ -598,7 +613,7 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
                         if (tc < TR) res_publish(mine + tr * TR + tc, pv, exchange_tag(seq_u));
                     }
                     if (tid == 0) {
-                        res_publish_scalar(mine + WM, cpart, seq_u);
+                        res_publish_share(mine + WM, sizeof(TX) == 4 ? res_scaled(cpart, -kShareExp) : cpart, exchange_tag(seq_u));
                         if (norm_stage == 1) res_publish_scalar(mine + WM + 2, fsq_block, seq_u);  // (only the exchange after an update)
                     }
                 }
@@ -612,14 +627,14 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
                     if (wave == NWV - 1) {
                         constexpr bool sums = RowRead::waves == NWV;
                         const uint32_t xoff = (uint32_t)((lane & (P - 1)) * kResSlotWords + WM) * 8u;
-                        if (norm_stage == 1) ok = res_gather<TX, H, 4>(xrs, soff, off_u, kResSlotWords * 8, sums, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
-                        else ok = res_gather<TX, H, 2>(xrs, soff, off_u, kResSlotWords * 8, sums, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
+                        if (norm_stage == 1) ok = res_gather<TX, H, true, true>(a.xbuf, xrs, soff, off_u, kResSlotWords * 8, sums, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
+                        else ok = res_gather<TX, H, true, false>(a.xbuf, xrs, soff, off_u, kResSlotWords * 8, sums, xoff, seq_u, a.max_spin, hs, x0, x1, spin);
                         if (lane < P) {
-                            lds_x[0][lane] = x0;
+                            lds_x[0][lane] = res_scaled(x0, xexp + (sizeof(TX) == 4 ? kShareExp : 0));
                             if (norm_stage == 1) lds_x[1][lane] = x1;
                         }
                     } else if (wave < RowRead::waves) {
-                        ok = res_gather<TX, H, 0>(xrs, soff, off_u, kResSlotWords * 8, true, 0, seq_u, a.max_spin, hs, x0, x1, spin);
+                        ok = res_gather<TX, H, false, false>(a.xbuf, xrs, soff, off_u, kResSlotWords * 8, true, 0, seq_u, a.max_spin, hs, x0, x1, spin);
                     }
                     if (wave < RowRead::waves) {
                         const double u = res_join<L, Q>(hs, lane);
@@ -791,7 +806,7 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
                         TA t = 0;
 #pragma unroll
                         for (int q = 0; q < NWV; ++q) t += w[e][q];
-                        s[e] = res_scaled((TX)t, -a.xexp);
+                        s[e] = res_scaled((TX)t, -xexp);
                     }
                     if constexpr (C == 2) res_publish(mine + tid, s[0], s[1], exchange_tag(seq_v));
                     else res_publish(mine + tid, s[0], exchange_tag(seq_v));
@@ -807,10 +822,10 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
                 if (norm_stage == 2 && wave == NWV - 1) {
                     // the block-row sums of squares travel on this exchange once per term
                     const uint32_t xoff = (uint32_t)((lane & (P - 1)) * P * kResSlotWords + WN) * 8u;
-                    ok = res_gather<TX, H, 2>(xrs, soff, off_v, P * kResSlotWords * 8, ColRead::waves == NWV, xoff, seq_v, a.max_spin, hs, x0, x1, spin);
-                    if (lane < P) lds_x[1][lane] = x0;
+                    ok = res_gather<TX, H, false, true>(a.xbuf, xrs, soff, off_v, P * kResSlotWords * 8, ColRead::waves == NWV, xoff, seq_v, a.max_spin, hs, x0, x1, spin);
+                    if (lane < P) lds_x[1][lane] = x1;
                 } else if (wave < ColRead::waves) {
-                    ok = res_gather<TX, H, 0>(xrs, soff, off_v, P * kResSlotWords * 8, true, 0, seq_v, a.max_spin, hs, x0, x1, spin);
+                    ok = res_gather<TX, H, false, false>(a.xbuf, xrs, soff, off_v, P * kResSlotWords * 8, true, 0, seq_v, a.max_spin, hs, x0, x1, spin);
                 }
                 if (wave < ColRead::waves) {
                     const double v = res_join<L, Q>(hs, lane);
@@ -829,9 +844,8 @@ __global__ void __launch_bounds__(kResThreads) resident_kernel(ResidentArgs a)
             if (tid == 0) atomicExch((unsigned*)&a.res->err, 1u);
             return;
         }
-        // this column block's share of c travels on the next row exchange (published by thread 0)
+        // this column block's share of c (in the exchange's scale) travels on the next row exchange (published by thread 0)
         if (SOLO || wv == 0) cpart = group_sum_res<8>(lds_red[lane & (NWV - 1)]);
-        if constexpr (!SOLO) cpart = res_scaled(cpart, a.xexp);
         if constexpr (!SOLO) {
             if (norm_stage == 2) {
                 const double ft = group_sum_res<P>(lds_x[1][lane & (P - 1)]);

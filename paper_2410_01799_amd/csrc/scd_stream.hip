@@ -132,8 +132,8 @@ __device__ __forceinline__ uint64_t ps_load(const uint64_t* p)
 }
 
 // Published sums are scaled by a power of two below 1 (a.xexp, a.cexp), so that the top bit of their exponents is free for a tag
-// that flips with every write of a slot: two f32 or one f64 fill an 8-byte word, which is stored and seen whole.  What lies below
-// 2^-126 (f32) or 2^-1022 (f64) once scaled loses bits; infinities and NaNs have no room (the host lets none come here).
+// that flips with every write of a slot: two f32 or one f64 (see exchange_pack) fill an 8-byte word of hop 1.  What lies below
+// 2^-126 (f32) or 2^-510 (f64) once scaled loses bits; infinities and NaNs have no room (the host lets none come here).
 // 16 bytes of sums (two words)
 __device__ __forceinline__ void ps_publish16(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff, const float* v, int e, uint32_t tag)
 {
@@ -147,9 +147,10 @@ __device__ __forceinline__ void ps_publish16(__amdgpu_buffer_rsrc_t rs, uint32_t
     u32x4 w;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const double x = __builtin_ldexp(v[i], -e);
-        w[2 * i] = (uint32_t)__double2loint(x);
-        w[2 * i + 1] = ((uint32_t)__double2hiint(x) & ~kTagBit) | tag;
+        uint32_t lo, hi;
+        exchange_pack(__builtin_ldexp(v[i], -e), tag, lo, hi);
+        w[2 * i] = lo;
+        w[2 * i + 1] = hi;
     }
     __builtin_amdgcn_raw_buffer_store_b128(w, rs, (int)voff, (int)soff, kDeviceScope);
 }
@@ -164,15 +165,16 @@ __device__ __forceinline__ bool ps_hop1_gather(__amdgpu_buffer_rsrc_t rs, uint32
     for (int m0 = q; m0 < G; m0 += NF * Q) {
         u32x4 w[NF];
         for (;;) {
-            uint32_t stale = 0u;
+            uint32_t stale = 0u, stale_low = 0u;
 #pragma unroll
             for (int i = 0; i < NF; ++i) w[i] = exchange_load16(rs, voff + (uint32_t)(m0 + i * Q < G ? m0 + i * Q : m0) * slot, soff);
 #pragma unroll
             for (int i = 0; i < NF; ++i) {
                 stale |= (w[i].y ^ tag) | (w[i].w ^ tag);
                 if constexpr (sizeof(TE) == 4) stale |= (w[i].x ^ tag) | (w[i].z ^ tag);
+                else stale_low |= (w[i].x ^ (tag >> 30)) | (w[i].z ^ (tag >> 30));
             }
-            if (!(stale & kTagBit)) break;
+            if (!((stale & kTagBit) | (stale_low & 1u))) break;
             if (++spin > max_spin) return false;
             __builtin_amdgcn_s_sleep(1);
         }
@@ -183,8 +185,8 @@ __device__ __forceinline__ bool ps_hop1_gather(__amdgpu_buffer_rsrc_t rs, uint32
 #pragma unroll
                     for (int e = 0; e < 4; ++e) s[e] += (double)__uint_as_float(w[i][e] & ~kTagBit);
                 } else {
-                    s[0] += __hiloint2double((int)(w[i].y & ~kTagBit), (int)w[i].x);
-                    s[1] += __hiloint2double((int)(w[i].w & ~kTagBit), (int)w[i].z);
+                    s[0] += exchange_unpack(w[i].x, w[i].y);
+                    s[1] += exchange_unpack(w[i].z, w[i].w);
                 }
             }
         }
@@ -592,6 +594,7 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
     const int sbytes = sbits >> 3;
     const int nsc = tensor ? n3 : 1;              // scalars per slot: c or the n3 mode sums
     const uint32_t slot1 = (uint32_t)n * (uint32_t)sizeof(TE);  // bytes of a hop-1 slot (a row of 64 KB at most)
+    const int xexp = a.xexp + (sizeof(TE) == 8 ? kF64Exp : 0);  // sums of hop 1 are published times 2^-xexp
     const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(a.xp, 0, (int)(2u * (uint32_t)G * slot1), 0x00027000);
     const int nr2 = tensor ? ncol / n3 : 0;       // order 3: rows of W_1 in the own slice
     // Quotients by these are products with a reciprocal: (x + 0.5) / d is at least 0.5 / d away from an integer, and
@@ -645,7 +648,7 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
 #pragma unroll
             for (int c = 0; c < CPT; ++c) {
                 const int64_t ch = tid + c * kPsThreads;
-                if (ch < nch) ps_publish16(xrs, (uint32_t)ch * 16u, soff, acc + c * VE, a.xexp, tag);
+                if (ch < nch) ps_publish16(xrs, (uint32_t)ch * 16u, soff, acc + c * VE, xexp, tag);
             }
         }
         if (with_norm) {
@@ -713,7 +716,7 @@ __global__ void __launch_bounds__(kPsThreads) pstream_kernel(PStreamArgs a)
                 for (int i = 0; i < kPsWaves; ++i) pq[i] = mine && i < groups ? part[i * stride + tid] : 0.0;
 #pragma unroll
                 for (int i = 0; i < kPsWaves; ++i) vj += pq[i];
-                vj = __builtin_ldexp(vj, a.xexp);
+                vj = __builtin_ldexp(vj, xexp);
             }
             if (!tensor) {
                 // t_l = sgn(v_l), share of c = sum |v_l| (Algorithm 4 lines 6-7)

@@ -149,3 +149,30 @@ def test_column_signs_of_a_tensor_built_32_bits_per_thread():
             want = np.bitwise_xor.outer(s2, s3).reshape(-1)               # q = j * n3 + c
             assert np.array_equal(bits[:n], want), (n3, n2)
             assert not bits[n:].any()
+
+
+def test_words_of_one_f64_sum_are_fresh_or_stale_by_halves():
+    """Host model of exchange_pack and exchange_unpack (scd_exchange.h): any f64 below 2^-511 comes back bit for bit, and a word of
+    which one half is still that of the write before is told from a fresh one, whatever the two values."""
+    rs = np.random.default_rng(11)
+    n = 20000
+    v = rs.choice([-1.0, 1.0], n) * (1.0 + rs.random(n)) * np.exp2(rs.integers(-1022, -512, n).astype(np.float64))
+    v[:8] = [0.0, -0.0, np.nextafter(2.0 ** -511, 0.0), -np.nextafter(2.0 ** -511, 0.0), 5e-324, -5e-324, 2.0 ** -512, 2.0 ** -1022]
+    bits = v.view(np.uint64)
+    lo, hi = (bits & np.uint64(0xFFFFFFFF)).astype(np.uint32), (bits >> np.uint64(32)).astype(np.uint32)
+    u = np.uint32
+    halves = []
+    for tag in (u(0), u(0x40000000)):
+        plo = (lo & u(0xFFFFFFFE)) | (tag >> u(30))
+        phi = hi | ((lo & u(1)) << u(29)) | tag
+        halves.append((plo, phi))
+        rlo, rhi = (plo & u(0xFFFFFFFE)) | ((phi >> u(29)) & u(1)), phi & u(0x9FFFFFFF)
+        assert np.array_equal((rhi.astype(np.uint64) << np.uint64(32)) | rlo, bits)
+
+    def stale(plo, phi, tag):
+        return ((phi ^ tag) & u(0x40000000)) | ((plo ^ (tag >> u(30))) & u(1))
+
+    for tag, new, old in ((u(0), halves[0], halves[1]), (u(0x40000000), halves[1], halves[0])):
+        mix = rs.permutation(n)
+        assert not stale(new[0], new[1], tag).any()
+        assert stale(new[0], old[1][mix], tag).all() and stale(old[0][mix], new[1], tag).all() and stale(old[0], old[1], tag).all()
