@@ -18,6 +18,17 @@ extern "C" {
  * paper's own method moves (host pointers, may be NULL). */
 int scd_sparse_flips(const scd_ctx* ctx, int64_t* row_flips, int64_t* col_flips);
 
+/* Late alternations of the sparse engine (after the first few of a term one wave per workgroup goes on alone): out (host) =
+ * entries of a slice and sign words of a side that a lane holds in the form of the most recent launch (0, 0: it had no late
+ * alternations), then, over all launches so far, how many of them began, and how often they ended because many signs changed
+ * rather than because the term was complete. */
+int scd_probe_late(const scd_ctx* ctx, int64_t out[4]);
+
+/* Test hook, for this context's later launches: a half step with more than `flips` changed signs ends the late alternations,
+ * and every list of changed signs is taken in parts, as otherwise one that is longer than 8192 (below 0: the engine's
+ * own limits again).  Results do not depend on it. */
+int scd_probe_late_limit(scd_ctx* ctx, int64_t flips);
+
 /* Algorithmic bytes the row-pass kernels of this context have read+written so far and the number
  * of passes (launches) they took: the counters behind the bandwidth figures.  host pointers. */
 int scd_traffic(const scd_ctx* ctx, double* bytes, int64_t* passes, int64_t* sweeps);

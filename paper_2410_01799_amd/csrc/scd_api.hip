@@ -111,6 +111,8 @@ struct scd_ctx {
     uint64_t* xbuf_sp = nullptr;
     uint32_t seq_sp = 0, seq_late[2] = {0, 0};
     int slots_sp = 0;               // workgroups that wrote the sparse engine's slots last (0: cleared)
+    int late_flips = -1;            // scd_probe_late_limit
+    int64_t late[4] = {0, 0, 0, 0};    // scd_probe_late
     int rs = 0, cs = 0;
     // persistent streaming engine
     bool pstream = false;
@@ -647,6 +649,7 @@ int run_sparse(scd_ctx* c, int64_t n)
         if (width > cap) width = cap;
         a.delay_width = width;
     }
+    a.late_flips = c->late_flips;
     a.profile = (int32_t)c->opt[SCD_OPT_VERBOSE];
     a.res = c->res_dev;
     SlotLease lease;
@@ -678,6 +681,12 @@ int run_sparse(scd_ctx* c, int64_t n)
         c->seq_late[0] = r.seq_late[0];
         c->seq_late[1] = r.seq_late[1];
     }
+    int entries = 0, words = 0;
+    sparse_late_form(a, &entries, &words);
+    c->late[0] = entries;
+    c->late[1] = words;
+    c->late[2] += r.late_alternations;
+    c->late[3] += r.late_returns;
     c->flips += r.flips;
     c->flips_rows += r.flips_rows;
     c->hs.k = r.k;
@@ -1169,6 +1178,20 @@ int scd_sparse_flips(const scd_ctx* c, int64_t* row_flips, int64_t* col_flips)
     if (!c) return SCD_EINVAL;
     if (row_flips) *row_flips = c->flips_rows;
     if (col_flips) *col_flips = c->flips;
+    return SCD_OK;
+}
+
+int scd_probe_late(const scd_ctx* c, int64_t out[4])
+{
+    if (!c || !out) return SCD_EINVAL;
+    for (int i = 0; i < 4; ++i) out[i] = c->late[i];
+    return SCD_OK;
+}
+
+int scd_probe_late_limit(scd_ctx* c, int64_t flips)
+{
+    if (!c || flips > INT32_MAX) return SCD_EINVAL;
+    c->late_flips = flips < 0 ? -1 : (int)flips;
     return SCD_OK;
 }
 

@@ -121,6 +121,7 @@ struct ResidentResult {
     int64_t flips_rows;    // sparse engine: row signs that changed (each costs one row of R)
     int64_t ticks[6];      // sparse engine, profile mode: 100 MHz ticks of workgroup 0 per phase
     uint32_t seq_late[2];  // sparse engine: sequence numbers of the late alternations' exchanges (columns, rows)
+    int32_t late_alternations, late_returns;  // ... how many there were, how often many flips ended them
 };
 
 // Least squares decomposition of a matrix: position of the loop on the device.
@@ -195,12 +196,14 @@ struct SparseArgs {
     int32_t grid;            // workgroups of this launch (at most kSpGrid)
     int32_t profile;         // 1: workgroup 0 times its phases
     int32_t delay_width;     // > 0: finished terms wait in a list of this length before they are subtracted
+    int32_t late_flips;      // tests: most flips of a late half step, whose list is taken in parts; -1: as serves best
     ResidentResult* res;
 };
 
 int sparse_delay_width(int64_t m, int64_t n);
 bool sparse_supported(scd_dtype dt, int order, const int64_t* dims, int grid, int* rs, int* cs);
 size_t sparse_xbuf_bytes();
+void sparse_late_form(const SparseArgs& a, int* entries, int* words);  // a lane's registers of late alternations, 0: none in this launch
 hipError_t launch_sparse(const SparseArgs& a, scd_dtype dt, hipStream_t st);
 hipError_t launch_transpose(const void* in, void* out, scd_dtype dt, int64_t rows, int64_t cols, hipStream_t st);
 

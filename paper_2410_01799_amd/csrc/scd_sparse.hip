@@ -588,7 +588,7 @@ __global__ void __launch_bounds__(kSpThreads) sparse_kernel(SparseArgs a)
         sh.red = (double*)take((size_t)kSpThreads * 8);
         sh.scal = (uint32_t*)take((size_t)2 * kSpGrid * 2 * 4);
         sh.cred = (double*)take((size_t)kSpWaves * 8);
-        sh.scan = (int*)take((size_t)(kSpWaves + 2) * 4);
+        sh.scan = (int*)take((size_t)(kSpWaves + 4) * 4);
     }
     for (int64_t i = tid; i < mwords32 + 2; i += kSpThreads) {
         sh.sA[i] = 0;
@@ -995,9 +995,9 @@ struct SpLateArgs {
     uint64_t* xbuf;  // exchange slots of the late alternations
     int64_t i0, j0, m, n;
     double c_prev, c;
-    uint32_t t_cur, s_cur, owns, list, dots, red, accu, accv, effv, coef, PS, PT;
+    uint32_t t_cur, s_cur, owns, list, dots, red, accu, accv, effv, coef, PS, PT, counts;
     int ps_stride, pt_stride;
-    int grid, rs, cs, rlen, clen, np, cap_t, cap_s, cexp, max_iters, max_spin;
+    int grid, rs, cs, rlen, clen, np, cap_t, cap_s, most, cexp, max_iters, max_spin;
     int cmd, total;   // to the other waves: 0 the end, 1 / 2 add up the flipped columns / rows of the list
     uint32_t seq_t, seq_s;
     int wait_t, wait_s, j;
@@ -1207,7 +1207,7 @@ __device__ __forceinline__ void sp_late_share(const TE* __restrict__ M, int64_t 
 template <typename TE, int NE, int NI, typename Stop>
 __device__ __forceinline__ int sp_late_update(int lane, SpLateSide<NE, NI>& x, const uint32_t (&flip)[NI], SpLateSide<NE, NI>& y,
                                               const TE* __restrict__ M, int64_t ld, int64_t off, lds_u32* P, int pstride, int np, double coef,
-                                              lds_u32* list, lds_f64* red, lds_args* la, int cmd, Stop stop)
+                                              lds_u32* list, int list_cap, lds_f64* red, lds_args* la, int cmd, Stop stop)
 {
     int cnt = 0;
 #pragma unroll
@@ -1220,7 +1220,7 @@ __device__ __forceinline__ int sp_late_update(int lane, SpLateSide<NE, NI>& x, c
 #pragma unroll
     for (int i = 0; i < NE; ++i) part[i] = 0.0;
     // more flips than the list holds (hardly ever): one word of every lane at a time
-    const int rounds = all > kSpListCap / 2 ? NI : 1;
+    const int rounds = all > list_cap ? NI : 1;
     int delta = 0;
     bool stopped = false;
     for (int r = 0; r < rounds; ++r) {
@@ -1375,6 +1375,8 @@ __device__ __attribute__((noinline)) void sp_late_loop(lds_args* la)
         const int e = i * kWave + (lane & (ts.slp - 1));
         ts.eff[i] = e < a.clen ? effv[e] : 0.0;
     }
+    const int most_t = a.most < 0 ? 2 * a.cap_t : a.most, most_s = a.most < 0 ? 2 * a.cap_s : a.most;
+    const int list_cap = a.most < 0 ? kSpListCap / 2 : 0;
     uint32_t flip[NI];
     int status = 2, halves = 0, spins = 0, j = a.j;
     int64_t fl = 0, flr = 0;
@@ -1387,7 +1389,7 @@ __device__ __attribute__((noinline)) void sp_late_loop(lds_args* la)
         a.wait_t = sp_adapt(a.wait_t, late);
         ++j;
         // u += 2 sum over flipped columns, s = sgn(u).  Line 8 is tested while the entries of the flipped columns are on their way.
-        const int ft = sp_late_update<TE>(lane, ts, flip, ss, (const TE*)a.RT, a.m, a.i0, lds_at<lds_u32>(a.PT), a.pt_stride, a.np, coef, list, red, la, 1,
+        const int ft = sp_late_update<TE>(lane, ts, flip, ss, (const TE*)a.RT, a.m, a.i0, lds_at<lds_u32>(a.PT), a.pt_stride, a.np, coef, list, list_cap, red, la, 1,
                                           [&]() {
                                               c = sp_wave_sum(c);
                                               if (c <= c_prev || j >= a.max_iters) status = 1;
@@ -1401,9 +1403,9 @@ __device__ __attribute__((noinline)) void sp_late_loop(lds_args* la)
         a.wait_s = sp_adapt(a.wait_s, late);
         ++halves;
         // v += 2 sum over flipped rows
-        const int fs = sp_late_update<TE>(lane, ss, flip, ts, (const TE*)a.R, a.n, a.j0, lds_at<lds_u32>(a.PS), a.ps_stride, a.np, coef, list, red, la, 2, []() { return false; });
+        const int fs = sp_late_update<TE>(lane, ss, flip, ts, (const TE*)a.R, a.n, a.j0, lds_at<lds_u32>(a.PS), a.ps_stride, a.np, coef, list, list_cap, red, la, 2, []() { return false; });
         flr += fs;
-        if (ft > 2 * a.cap_t || fs > 2 * a.cap_s) {
+        if (ft > most_t || fs > most_s) {
             status = 0;
             break;
         }
@@ -1435,6 +1437,8 @@ __device__ __attribute__((noinline)) void sp_late_loop(lds_args* la)
         la->flips = fl;
         la->flips_rows = flr;
         la->cmd = 0;
+        lds_at<lds_i32>(a.counts)[0] += j - a.j;
+        lds_at<lds_i32>(a.counts)[1] += status == 0;
     }
 }
 
@@ -1469,7 +1473,7 @@ __global__ void __launch_bounds__(kSpThreads) sparse_delay_kernel(SparseArgs a)
         sh.red = (double*)take((size_t)kSpThreads * (8 + 4));  // (and the row masks of a flush)
         sh.scal = (uint32_t*)take((size_t)2 * kSpGrid * 2 * 4);
         sh.cred = (double*)take((size_t)kSpWaves * 8);
-        sh.scan = (int*)take((size_t)(kSpWaves + 2) * 4);
+        sh.scan = (int*)take((size_t)(kSpWaves + 4) * 4);
         pd.ps_stride = (int)mwords32 + 1;
         pd.pt_stride = (int)nwords32 + 1;
         pd.coef = (double*)take(32 * 8);
@@ -1512,6 +1516,7 @@ __global__ void __launch_bounds__(kSpThreads) sparse_delay_kernel(SparseArgs a)
     int np = 0;  // pending terms
     // late alternations on one wave: sequence numbers of their exchanges, waits, flips that a half step may have
     uint32_t late_seq_t = a.seq_late[0], late_seq_s = a.seq_late[1];
+    if (tid == 0) sh.scan[kSpWaves + 2] = sh.scan[kSpWaves + 3] = 0;  // how many there were, how often many flips ended them
     int late_wait_t = wait0, late_wait_s = wait0, late_cexp = 0;
     const int late_items = a.grid * (((rs > cs ? rs : cs) + 31) >> 5);
     const int late_cap_t = kSpLateShare * (kSpThreads - kWave) / rs, late_cap_s = kSpLateShare * (kSpThreads - kWave) / cs;  // (flips of t change u)
@@ -1640,7 +1645,8 @@ __global__ void __launch_bounds__(kSpThreads) sparse_delay_kernel(SparseArgs a)
                     la.dots = lds_address(dots), la.accu = lds_address(sh.accu), la.accv = lds_address(sh.accv), la.effv = lds_address(pd.effv);
                     la.coef = lds_address(pd.coef), la.PS = lds_address(pd.PS), la.PT = lds_address(pd.PT);
                     la.ps_stride = pd.ps_stride, la.pt_stride = pd.pt_stride, la.grid = a.grid, la.rs = rs, la.cs = cs, la.rlen = rlen, la.clen = clen;
-                    la.np = np, la.cap_t = late_cap_t, la.cap_s = late_cap_s, la.red = lds_address(pd.effu), la.cexp = late_cexp;
+                    la.np = np, la.cap_t = late_cap_t, la.cap_s = late_cap_s, la.most = a.late_flips, la.counts = lds_address(sh.scan + kSpWaves + 2);
+                    la.red = lds_address(pd.effu), la.cexp = late_cexp;
                     la.max_iters = a.max_iters, la.max_spin = a.max_spin;
                     la.seq_t = late_seq_t, la.seq_s = late_seq_s, la.wait_t = late_wait_t, la.wait_s = late_wait_s, la.j = j;
                 }
@@ -1758,6 +1764,8 @@ __global__ void __launch_bounds__(kSpThreads) sparse_delay_kernel(SparseArgs a)
     if (g == 0 && tid == 0) {
         a.res->seq_late[0] = late_seq_t;
         a.res->seq_late[1] = late_seq_s;
+        a.res->late_alternations = sh.scan[kSpWaves + 2];
+        a.res->late_returns = sh.scan[kSpWaves + 3];
         a.res->k = k;
         a.res->alternations = alternations;
         a.res->updates = updates;
@@ -1790,7 +1798,7 @@ size_t sparse_lds_bytes(int64_t m, int64_t n, int delay_width)
     auto al = [](size_t b) { return (b + 15) & ~(size_t)15; };
     const size_t mw = (size_t)((m + 31) >> 5), nw = (size_t)((n + 31) >> 5);
     size_t b = 2 * al(mw * 4 + 8) + 2 * al(nw * 4 + 8) + al((size_t)kSpListCap * 2) + 3 * al((size_t)kSpThreads * 8) +
-               al((size_t)2 * kSpGrid * 2 * 4) + al((size_t)kSpWaves * 8) + al((size_t)(kSpWaves + 2) * 4);
+               al((size_t)2 * kSpGrid * 2 * 4) + al((size_t)kSpWaves * 8) + al((size_t)(kSpWaves + 4) * 4);
     if (delay_width > 0)
         b += 2 * al(32 * 8) + 2 * al((size_t)kSpThreads * 8) + al((size_t)kSpThreads * 4) + al((size_t)delay_width * (mw + 1) * 4) +
              al((size_t)delay_width * (nw + 1) * 4) + al((size_t)kSpAhead * (nw + 1) * 4) +
@@ -1849,6 +1857,14 @@ static bool sparse_late(const SparseArgs& a)
     const int slice = a.rs > a.cs ? a.rs : a.cs;
     const int64_t lo = a.m < a.n ? a.m : a.n, hi = a.m < a.n ? a.n : a.m;
     return a.delay_width <= kSpLatePending && slice <= kWave * kSpLateEntries && a.grid * ((slice + 31) / 32) <= kWave * kSpLateItems && lo * lo > 64 * hi;
+}
+
+void sparse_late_form(const SparseArgs& a, int* entries, int* words)
+{
+    const int slice = a.rs > a.cs ? a.rs : a.cs;
+    const bool late = a.delay_width > 0 && sparse_late(a);
+    *entries = !late ? 0 : slice <= kWave ? 1 : kSpLateEntries;
+    *words = !late ? 0 : a.grid * ((slice + 31) / 32) <= kWave * kSpLateItems / 2 ? kSpLateItems / 2 : kSpLateItems;
 }
 
 template <typename TE>

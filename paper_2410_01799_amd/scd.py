@@ -25,7 +25,7 @@ EXPORTS = [
     "scd_decompose", "scd_create", "scd_destroy", "scd_set_max_iters", "scd_step", "scd_run", "scd_step_from",
     "scd_width", "scd_results", "scd_remainder", "scd_set_remainder", "scd_row_signed_sum", "scd_col_signed_sum",
     "scd_expand", "scd_pack", "scd_unpack", "scd_rng_signs", "scd_strerror", "scd_last_hip_error", "scd_traffic",
-    "scd_probe_stream", "scd_profile_sweeps", "scd_probe_exchange", "scd_engine", "scd_set_workgroups",
+    "scd_probe_stream", "scd_profile_sweeps", "scd_probe_exchange", "scd_probe_late", "scd_probe_late_limit", "scd_engine", "scd_set_workgroups",
     "scd_apply", "scd_apply_workspace_bytes", "scd_lsq_decompose", "scd_lsq_decompose_tensor", "scd_lsq_decompose_form", "scd_decompose_scalars", "scd_sparse_flips",
     "scd_col_signed_sum_noalloc", "scd_set_option", "scd_get_option", "scd_stream_geometry", "scd_release_memory",
 ]
@@ -94,6 +94,8 @@ def lib() -> C.CDLL:
         L.scd_traffic.argtypes = [vp, C.POINTER(C.c_double), pi64, pi64]
         L.scd_profile_sweeps.argtypes = [vp, C.c_int, C.POINTER(C.c_double), C.POINTER(C.c_double)]
         L.scd_engine.argtypes = [vp, C.POINTER(C.c_int), C.POINTER(C.c_double), C.POINTER(C.c_double)]
+        L.scd_probe_late.argtypes = [vp, pi64]
+        L.scd_probe_late_limit.argtypes = [vp, i64]
         L.scd_probe_exchange.argtypes = [C.c_int, C.c_int, C.c_int, C.c_int, vp, C.POINTER(C.c_double)]
         L.scd_probe_stream.argtypes = [vp, vp, i64, C.c_int, C.c_int, vp, C.POINTER(C.c_double)]
         _lib = L
@@ -418,6 +420,15 @@ class ScdContext:
         r, cl = C.c_int64(), C.c_int64()
         _check(lib().scd_sparse_flips(self._h, C.byref(r), C.byref(cl)), "scd_sparse_flips")
         return dict(rows=int(r.value), cols=int(cl.value))
+
+    def late(self) -> dict:
+        """Late alternations of the sparse engine: the form of the last launch, and counts over all launches."""
+        out = (C.c_int64 * 4)()
+        _check(lib().scd_probe_late(self._h, out), "scd_probe_late")
+        return dict(entries=out[0], words=out[1], alternations=out[2], returns=out[3])
+
+    def late_limit(self, flips: int = -1):
+        _check(lib().scd_probe_late_limit(self._h, int(flips)), "scd_probe_late_limit")
 
     def set_workgroups(self, n: int):
         """Share of the device (workgroups of the persistent launches; 0 = all): lets several contexts,
