@@ -1397,7 +1397,8 @@ int scd_col_signed_sum_noalloc(const void* R, scd_dtype dt, int64_t m, int64_t n
     const size_t es = dt == SCD_F32 ? 4 : 8;
     // layout: [0, 256) the head; then ceil(n/64) doubles of partial sums of |v|, padded to 256 bytes; then the partial column
     // sums.  The limit is that of partial sums of the input's type for up to 1024 groups of rows (of at most 2048 rows): what
-    // halfstep_groups takes in f64 is never more (two rows of f32 sums and more for each group; a single row is kept in f32).
+    // halfstep_groups takes in f64 is never more (two rows of f32 sums and more for each group; a single row is kept in f32),
+    // and is checked all the same.
     int64_t per = (m + 1023) / 1024;
     if (per > kMaxRowsPerWg) per = kMaxRowsPerWg;
     const int64_t grid = (m + per - 1) / per;
@@ -1405,6 +1406,8 @@ int scd_col_signed_sum_noalloc(const void* R, scd_dtype dt, int64_t m, int64_t n
     const size_t need = 256 + cparts_bytes + (size_t)grid * (size_t)n * es;
     if ((double)grid * (double)n * (double)es > (double)SCD_NOALLOC_SCRATCH_BYTES || need > (size_t)SCD_NOALLOC_SCRATCH_BYTES)
         return SCD_ETOOBIG;
+    const size_t take = 256 + cparts_bytes + (size_t)halfstep_groups(m) * (size_t)n * (dt == SCD_F32 && m == 1 ? 4 : 8);
+    if (take > (size_t)SCD_NOALLOC_SCRATCH_BYTES) return SCD_ETOOBIG;
     unsigned char* base = nullptr;
     SCD_TRY(scratch_address(&base));
     // every word of the work space that is read was written by this call: nothing to clear

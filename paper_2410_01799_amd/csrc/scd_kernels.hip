@@ -1190,9 +1190,8 @@ static ColGeometry col_geometry(const void* R, scd_dtype dt, int64_t m, int64_t 
     return g;
 }
 
-// `most` groups of rows have room in `partials`, in f64; *groups is how many there are.  A single row is written as it
-// is (`narrow`: f32 partial sums of an f32 matrix), so that the partial sums never take more than most * n elements of dt
-// where most is half the rows or less.
+// `most` groups of rows have room in `partials`: most * n f64 values, or most * n f32 ones with `narrow` (a single row of an f32
+// matrix, which is written as it is).  *groups is how many there are.
 hipError_t launch_col_partials(const void* R, scd_dtype dt, int64_t m, int64_t n, int most, const uint64_t* rowbits, void* partials,
                                bool narrow, unsigned* arrived, int* groups, hipStream_t st)
 {

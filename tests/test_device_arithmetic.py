@@ -176,3 +176,13 @@ def test_words_of_one_f64_sum_are_fresh_or_stale_by_halves():
         mix = rs.permutation(n)
         assert not stale(new[0], new[1], tag).any()
         assert stale(new[0], old[1][mix], tag).all() and stale(old[0][mix], new[1], tag).all() and stale(old[0], old[1], tag).all()
+
+
+def test_column_step_without_allocation_takes_no_more_than_its_limit_counts():
+    """Host model of scd_col_signed_sum_noalloc: the limit counts up to 1024 groups of rows with sums of the input's type, the launch
+    keeps f64 sums of up to 256 groups of 32 rows and more (a single f32 row: f32)."""
+    m = np.unique(np.concatenate([np.arange(1, 70000), np.exp2(np.linspace(16, 31, 20000)).astype(np.int64)]))
+    per = np.minimum((m + 1023) // 1024, 2048)
+    groups, most = (m + per - 1) // per, np.minimum((m + 31) // 32, 256)
+    assert (most * 8 <= groups * 8).all()
+    assert (most * np.where(m == 1, 4, 8) <= groups * 4).all()
