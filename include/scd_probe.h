@@ -84,8 +84,9 @@ int scd_probe_stream(const void* src, void* dst, int64_t bytes, int grid, int re
                      double* seconds);
 
 /* Latency of exchanging data between the workgroups of one persistent launch, for measurement only.
- * which = 0: every workgroup publishes 256 tagged values per round and reads those of its `group`
- * neighbours (the exchange the register-resident engine uses); which = 1: a counter barrier over the
+ * which = 0: every workgroup publishes 256 f32 values per round and reads those of its `group`
+ * neighbours, in groups of 4, 8 and 16 with the words and reads of the register-resident engine, otherwise one value
+ * and a sequence number in a word, read 8 bytes a lane; which = 1: a counter barrier over the
  * whole grid.  grid workgroups (a multiple of group, at most 1024; keep it at most the number of
  * compute units) must all be resident at once; every wait is bounded and SCD_EINVAL is returned when
  * one runs out.  *seconds_per_round: host. */

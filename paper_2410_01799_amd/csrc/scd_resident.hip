@@ -54,7 +54,8 @@ __global__ void __launch_bounds__(256) exchange_probe_kernel(uint64_t* buf, int 
     if (tid == 0) out[g] = carry;
 }
 
-// The same with the words and reads of the register-resident engine: 256 f32 sums a workgroup, groups of P neighbours.
+// The same with the words and reads of the register-resident engine, in groups of as many as it has: 256 f32 sums a workgroup, P
+// neighbours.
 template <int P>
 __global__ void __launch_bounds__(kResThreads) resident_exchange_probe_kernel(uint64_t* buf, int rounds, int max_spin, unsigned* err, float* out)
 {
@@ -120,8 +121,12 @@ __global__ void __launch_bounds__(256) barrier_probe_kernel(unsigned* counter, i
 hipError_t launch_exchange_probe(int which, int grid, uint64_t* buf, unsigned* counter, int rounds, int group,
                                  int max_spin, unsigned* err, float* out, hipStream_t st)
 {
-    if (which == 0 && group == 16)
-        hipLaunchKernelGGL(resident_exchange_probe_kernel<16>, dim3(grid), dim3(kResThreads), 0, st, buf, rounds, max_spin, err, out);
+    void (*resident)(uint64_t*, int, int, unsigned*, float*) = group == 4    ? resident_exchange_probe_kernel<4>
+                                                               : group == 8  ? resident_exchange_probe_kernel<8>
+                                                               : group == 16 ? resident_exchange_probe_kernel<16>
+                                                                             : nullptr;
+    if (which == 0 && resident)
+        hipLaunchKernelGGL(resident, dim3(grid), dim3(kResThreads), 0, st, buf, rounds, max_spin, err, out);
     else if (which == 0)
         hipLaunchKernelGGL(exchange_probe_kernel, dim3(grid), dim3(256), 0, st, buf, rounds, group, max_spin, err, out);
     else

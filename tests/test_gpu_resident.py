@@ -236,8 +236,9 @@ def test_resident_iteration_cap(scd):
     np.testing.assert_allclose(tr[1:] ** 2, tr[:-1] ** 2 - 2048 * 2048 * c ** 2, rtol=ID_RTOL)
 
 
-def test_exchange_probe_runs(scd):
-    t = scd.scd_probe_exchange(0, 256, 16, 200)
+@pytest.mark.parametrize("grid,group", [(256, 16), (64, 8), (16, 4), (256, 4), (64, 32)])
+def test_exchange_probe_runs(scd, grid, group):
+    t = scd.scd_probe_exchange(0, grid, group, 200)
     assert 0 < t < 1e-3
 
 
