@@ -986,7 +986,11 @@ constexpr int kSpLateItems = 8;    // sign words of a side that a lane gathers: 
 constexpr int kSpLateEntries = 2;  // entries of a slice that a lane holds: slices of at most 128
 constexpr int kSpLatePending = 8;  // longest list of pending terms
 constexpr int kSpLateDots = 64;    // place of the inner products in sh.scal
-constexpr int kSpLateShare = 64;   // most flipped entries a thread of the other waves adds in a half step (twice as many end it)
+// Most flipped entries that a thread of the other waves would have to add in the half step before the loop begins; twice as many
+// in the loop end it.  Us per alternation with 16 / 32 / 64 / 128 / 256: 1024x4096 on 32 workgroups 12.0 / 11.75 / 11.7 / 11.7 / 11.7,
+// 14336x4096 on 128 13.5 / 13.2 / 13.2 / 13.3 / 13.3, 4096x4096 on 64 6.83 / 6.73 / 6.68 / 6.66 / 6.65; ended by as many or by four
+// times as many the same.
+constexpr int kSpLateShare = 64;
 constexpr int kSpLateLoads = 8;    // flipped entries a lane of wave 0 adds by itself
 
 // What the late loop is given and hands back, in LDS (in sh.scal; pointers into LDS as its 32-bit addresses).
@@ -1758,6 +1762,10 @@ __global__ void __launch_bounds__(kSpThreads) sparse_delay_kernel(SparseArgs a)
             sp_pending_dots(pd.PS, pd.ps_stride, (int)mwords32, m, s_cur, np, width, pd.coef, pd.ej);
             sp_accumulate_flips<TE>(R, n, j0, clen, s_cur, s_oth, m, sh.accv, sh, flips_rows);
             sp_effective(sh.accv, clen, own_v, pd.ej, width, pd.effv);
+            // The loop begins in the first alternations of a term where terms have more than six of them on average, else in the
+            // fourth: the first half steps flip too many, and short terms never pay for the beginning.  Us per alternation so / always
+            // in the fourth / always in the second: f64 512x512 5.17 / 5.55 / 5.15, 2048x2048 5.72 / 5.88 / 5.71, 1500x1000 on 16
+            // workgroups 8.30 / 8.61 / 8.31, f32 14336x4096 11.5 / 11.4 / 11.5, 1024x4096 on 32, whose terms have four, 11.7 / 11.9 / 11.8.
             few = LATE && j >= (alternations > 6 * (int)(k - a.k_start + 1) ? 1 : 3) && flips - flips0 <= late_cap_t && flips_rows - flips_rows0 <= late_cap_s;
         }
     }
