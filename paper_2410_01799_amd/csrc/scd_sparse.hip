@@ -1520,7 +1520,7 @@ __global__ void __launch_bounds__(kSpThreads) sparse_delay_kernel(SparseArgs a)
     int np = 0;  // pending terms
     // late alternations on one wave: sequence numbers of their exchanges, waits, flips that a half step may have
     uint32_t late_seq_t = a.seq_late[0], late_seq_s = a.seq_late[1];
-    if (tid == 0) sh.scan[kSpWaves + 2] = sh.scan[kSpWaves + 3] = 0;  // how many there were, how often many flips ended them
+    if (LATE && tid == 0) sh.scan[kSpWaves + 2] = sh.scan[kSpWaves + 3] = 0;  // how many there were, how often many flips ended them
     int late_wait_t = wait0, late_wait_s = wait0, late_cexp = 0;
     const int late_items = a.grid * (((rs > cs ? rs : cs) + 31) >> 5);
     const int late_cap_t = kSpLateShare * (kSpThreads - kWave) / rs, late_cap_s = kSpLateShare * (kSpThreads - kWave) / cs;  // (flips of t change u)
@@ -1772,8 +1772,10 @@ __global__ void __launch_bounds__(kSpThreads) sparse_delay_kernel(SparseArgs a)
     if (g == 0 && tid == 0) {
         a.res->seq_late[0] = late_seq_t;
         a.res->seq_late[1] = late_seq_s;
-        a.res->late_alternations = sh.scan[kSpWaves + 2];
-        a.res->late_returns = sh.scan[kSpWaves + 3];
+        if (LATE) {
+            a.res->late_alternations = sh.scan[kSpWaves + 2];
+            a.res->late_returns = sh.scan[kSpWaves + 3];
+        }
         a.res->k = k;
         a.res->alternations = alternations;
         a.res->updates = updates;
