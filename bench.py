@@ -149,8 +149,7 @@ def layer_mode(args, scd, workloads, torch, np) -> dict:
     torch.cuda.synchronize()
     t_begin[0] = time.perf_counter()
     if K == 1:
-        for i in order:
-            worker(i)
+        worker(order[0])  # (goes on with the waiting ones)
     else:
         threads = [threading.Thread(target=worker, args=(i,)) for i in first]
         for t in threads:

@@ -44,7 +44,8 @@ int scd_traffic(const scd_ctx* ctx, double* bytes, int64_t* passes, int64_t* swe
  * every flush of the list and at the end of every scd_run; between flushes it follows Section 3.2's identity
  * ||R - c s t^T||^2 = ||R||^2 - 2 c <s, R t> + c^2 mn from the cut value); 3 = one persistent launch that
  * streams the remainder from memory once per alternation (matrices whose rows are a multiple of 16 bytes and at
- * most 64 KB long; the first rows of every workgroup's block stay in LDS).  For engines 1, 2 and 3 also the
+ * most 64 KB long; the first rows of every workgroup's block stay in registers and LDS).  Remainders that are not finite,
+ * and f32 ones of a norm whose column sums could overflow in engine 3, go to engine 0 whatever the shape.  For engines 1, 2 and 3 also the
  * duration of the most recent launch by HIP events on the context's stream and its dense-equivalent bytes:
  * (alternations + updates) * bytes of the remainder, what a streaming pass per alternation would move.  host
  * pointers, each may be NULL. */
@@ -53,7 +54,7 @@ int scd_engine(const scd_ctx* ctx, int* engine, double* last_launch_seconds, dou
 /* The launch geometry the persistent streaming engine would use for an array of this dtype and shape on at most
  * `limit` workgroups (host arrays; no GPU work): out[0] = 1 if the engine takes the shape (else 0 and the rest is
  * unspecified), out[1] workgroups, out[2] rows per workgroup, out[3] columns per slice of the first exchange,
- * out[4] rows of a block kept in LDS, out[5] bytes of dynamic LDS, out[6] / out[7] bytes of the two exchange
+ * out[4] rows of a block that LDS has room for beside one more, out[5] bytes of dynamic LDS, out[6] / out[7] bytes of the two exchange
  * buffers.  For tests of the host arithmetic against the bounds the kernel assumes. */
 int scd_stream_geometry(scd_dtype dt, int order, const int64_t* dims, int limit, int64_t out[8]);
 

@@ -760,9 +760,9 @@ int run_pstream(scd_ctx* c, int64_t n)
         return SCD_ETIMEOUT;
     }
     if (c->opt[SCD_OPT_VERBOSE])
-        fprintf(stderr, "[scd stream] terms %lld passes %lld re-reads %lld; grid %d, %d rows per workgroup, %d of them in LDS; "
+        fprintf(stderr, "[scd stream] terms %lld passes %lld re-reads %lld; grid %d, %d rows per workgroup, room for %d in LDS; "
                         "us per pass: rows %.2f, publish %.2f, hop-1 gather %.2f, slice %.2f, hop-2 %.2f, decide %.2f\n",
-                (long long)n, (long long)r.alternations, (long long)r.spins, geo.grid, geo.rpw, geo.lds_rows,
+                (long long)n, (long long)r.alternations, (long long)r.spins, geo.grid, geo.rpw, a.lds_rows,
                 r.ticks[0] * 0.01 / r.alternations, r.ticks[1] * 0.01 / r.alternations, r.ticks[2] * 0.01 / r.alternations,
                 r.ticks[3] * 0.01 / r.alternations, r.ticks[4] * 0.01 / r.alternations, r.ticks[5] * 0.01 / r.alternations);
     c->seq_ps = r.seq_u;
