@@ -123,7 +123,7 @@ typedef enum {
                                        (default), 0 = the generic kernel */
     SCD_OPT_POLL_DELAY = 5,         /* persistent engines: where the wait, in sleep units, between publishing and the
                                        first read of the partners' data sets out from (default 16).  The streaming
-                                       engine waits so long; the register-resident engine adds or takes off up to 10
+                                       engine waits 5/8 and 1/4 of it; the register-resident engine adds or takes off up to 10
                                        units by grid, tile and type (0 stays 0); the sparse engine waits so long
                                        behind a pass over the matrix and elsewhere begins with it (32 at most), from
                                        where every wave follows the arrivals between 0 and 32.  Time only: results do

@@ -86,17 +86,24 @@ def test_stream_engine_geometry_stays_inside_what_the_kernel_assumes():
                 assert (G - 1) * rpw < m <= G * rpw, (dims, limit)         # the last workgroup has a row, all rows are owned
                 assert n % ve == 0 and (n // ve + threads - 1) // threads <= 8   # chunks per thread the kernel is built for
                 assert cs % 8 == 0 and 8 <= cs <= max_slice and G * cs >= n      # slices cover the columns
-                assert threads // cs >= 1
+                # first exchange: 16 bytes a lane, a power of two of lanes across a slice, the member groups' sums in LDS
+                ncp = 2
+                while ncp * ve < cs:
+                    ncp *= 2
+                stride, groups = ncp * ve, 8 if ncp <= 64 else threads // ncp
+                assert threads // ncp >= 1 and cs <= stride
+                assert groups * stride <= (2 * threads if cs <= max_slice // 2 else 8 * max_slice)
                 unit = n3 if n3 else 1
                 assert n3 <= 4 and cs % (8 * unit) == 0                          # whole bytes of sign bits per slice
                 tw = (cs // unit + 31) // 32
-                per = tw + (2 * n3 if n3 else 2) + 2
+                per = tw + (n3 if n3 else 1) + 2
                 assert per <= slot2 and (G * per + threads - 1) // threads <= max_items2
                 nw, w2 = (n + 63) // 64, ((dims[1] + 63) // 64 if n3 else 0)
                 bits = dims[1] if n3 else n
                 assert G * (cs // unit // 8) >= (bits + 7) // 8            # the slices' sign bytes cover the whole vector
                 assert 0 <= lds_rows <= rpw
-                need = -(-lds_rows * n * es // 16) * 16 + -(-n * es // 16) * 16 + 2 * nw * 8 + w2 * 8 + 2 * (-(-rpw // 16) * 16)
+                need = -(-(lds_rows + 1) * n * es // 16) * 16 + 2 * nw * 8 + w2 * 8 + 2 * (-(-rpw // 16) * 16)
+                need += 8 * 8 * max_slice if cs > max_slice // 2 else 0
                 assert need < geo["lds_bytes"] <= max_lds + 64, (dims, limit)
                 assert geo["xp_bytes"] == 2 * G * n * es and geo["xq_bytes"] == 2 * G * slot2 * 8
     assert seen > 60
